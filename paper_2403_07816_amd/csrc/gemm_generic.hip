@@ -209,41 +209,27 @@ struct Generic {
 
 bool generic_rows_ok(int R, int E) { return ceil_div(R, BT) + E <= 65535; }
 
-int generic_up_swiglu(int dtype, const void* xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
-                      void* h1, void* h3, void* act, hipStream_t s) {
-  return dtype == BTX_BF16 ? Generic<bf16_t>::up(xs, W1, W3, off, sh, h1, h3, act, s)
-                           : Generic<float>::up(xs, W1, W3, off, sh, h1, h3, act, s);
+int generic_up_swiglu(const void* xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh, void* h1,
+                      void* h3, void* act, hipStream_t s) {
+  return Generic<float>::up(xs, W1, W3, off, sh, h1, h3, act, s);
 }
-int generic_down(int dtype, const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y,
-                 hipStream_t s) {
-  return dtype == BTX_BF16 ? Generic<bf16_t>::down(act, W2, off, sh, y, s) : Generic<float>::down(act, W2, off, sh, y, s);
+int generic_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, hipStream_t s) {
+  return Generic<float>::down(act, W2, off, sh, y, s);
 }
-int generic_bwd_act(int dtype, const void* dys, const void* W2, const void* h1, const void* h3, const float* gates,
+int generic_bwd_act(const void* dys, const void* W2, const void* h1, const void* h3, const float* gates,
                     const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
                     float* dg_part, void* scratch, hipStream_t s) {
-  return dtype == BTX_BF16
-             ? Generic<bf16_t>::bwd_act(dys, W2, h1, h3, gates, perm, off, sh, dh1, dh3, ga, dg_part, scratch, s)
-             : Generic<float>::bwd_act(dys, W2, h1, h3, gates, perm, off, sh, dh1, dh3, ga, dg_part, scratch, s);
+  return Generic<float>::bwd_act(dys, W2, h1, h3, gates, perm, off, sh, dh1, dh3, ga, dg_part, scratch, s);
 }
-int generic_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off,
+int generic_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off,
                    const FfShapes& sh, void* dxs, hipStream_t s) {
-  return dtype == BTX_BF16 ? Generic<bf16_t>::bwd_dx(dh1, dh3, W1, W3, off, sh, dxs, s)
-                           : Generic<float>::bwd_dx(dh1, dh3, W1, W3, off, sh, dxs, s);
+  return Generic<float>::bwd_dx(dh1, dh3, W1, W3, off, sh, dxs, s);
 }
-int generic_bwd_dw13(int dtype, int dW_dtype, const void* xs, const void* dh1, const void* dh3, const int32_t* off,
-                     const FfShapes& sh, void* dW1, void* dW3, hipStream_t s) {
-  if (dtype == BTX_BF16) {
-    return dW_dtype == BTX_BF16 ? Generic<bf16_t>::bwd_dw13<bf16_t>(xs, dh1, dh3, off, sh, dW1, dW3, s)
-                                : Generic<bf16_t>::bwd_dw13<float>(xs, dh1, dh3, off, sh, dW1, dW3, s);
-  }
+int generic_bwd_dw13(const void* xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1,
+                     void* dW3, hipStream_t s) {
   return Generic<float>::bwd_dw13<float>(xs, dh1, dh3, off, sh, dW1, dW3, s);
 }
-int generic_bwd_dw2(int dtype, int dW_dtype, const void* ga, const void* dys, const int32_t* off, const FfShapes& sh,
-                    void* dW2, hipStream_t s) {
-  if (dtype == BTX_BF16) {
-    return dW_dtype == BTX_BF16 ? Generic<bf16_t>::bwd_dw2<bf16_t>(ga, dys, off, sh, dW2, s)
-                                : Generic<bf16_t>::bwd_dw2<float>(ga, dys, off, sh, dW2, s);
-  }
+int generic_bwd_dw2(const void* ga, const void* dys, const int32_t* off, const FfShapes& sh, void* dW2, hipStream_t s) {
   return Generic<float>::bwd_dw2<float>(ga, dys, off, sh, dW2, s);
 }
 

@@ -26,8 +26,8 @@
 //     and stores 8 bytes at a time;
 //   * grouped rows: tiles are enumerated per expert on the device (no host sync); a tile past
 //     the last one exits.  Rows beyond a group's end are loaded from a clamped address and
-//     never stored.  A last k tile that is half empty (K = 32 mod 64) has its copies re-pointed
-//     at valid data and the A fragments of its empty half zeroed in registers;
+//     never stored.  A last k tile that K fills only partly (K is a multiple of 8) has its copies
+//     re-pointed at valid data and the A fragments past K zeroed in registers;
 //   * UP, DOWN and BWD_DX: the tiles of a partly filled last round of workgroups are cut along K into
 //     up to 8 slices whose fp32 accumulators a second small kernel adds in ascending order and stores
 //     (UP: with the SwiGLU applied to the sums), so that the round fills the chip (Gemm::split_plan).
@@ -133,7 +133,7 @@ template <bool STREAM, typename V> __device__ __forceinline__ void store_out(V* 
   else *p = v;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 struct Gemm {
   // K index contiguous in memory?  A always is.  In the dW products K is the grouped-row index:
   // x (dW1/dW3) and ga, dY (dW2) arrive transposed, [columns][padded rows], every expert's rows
@@ -407,7 +407,7 @@ struct Gemm {
     uint32_t a_off[A_LOADS], b_off[B_LOADS];
     int b_k[B_LOADS], b_c[B_LOADS];                               // strided layout: k row / column
     bool b_second[B_LOADS];
-    bool a_hi[A_LOADS], b_hi[B_LOADS];                            // KC layouts: chunk lies in the upper 32 k of the tile
+    int a_k[A_LOADS], b_kc[B_LOADS];                              // KC layouts: the chunk's first k inside the tile
 #pragma unroll
     for (int q = 0; q < A_LOADS; ++q) {
       int major, minor;
@@ -416,7 +416,7 @@ struct Gemm {
       // gathered rows: the offset is taken from the first row of A0 (it fits 32 bits, checked on the host)
       a_off[q] = g.a_perm ? (uint32_t)(g.a_perm[gr] / g.a_k) * (uint32_t)(g.lda * 2) + (uint32_t)(minor * 2)
                           : (uint32_t)((gr - row0) * g.lda + minor) * 2u;
-      a_hi[q] = minor >= 32;
+      a_k[q] = minor;
     }
 #pragma unroll
     for (int q = 0; q < B_LOADS; ++q) {
@@ -431,9 +431,9 @@ struct Gemm {
         b_off[q] = (uint32_t)((min(col0 + major, g.N - 1) - col0) * g.ldb + minor) * 2u;
         b_k[q] = b_c[q] = 0;
         b_second[q] = DUAL && seg >= SEGS_PER_PANEL;
-        b_hi[q] = minor >= 32;
+        b_kc[q] = minor;
       } else {
-        b_hi[q] = false;
+        b_kc[q] = 0;
         b_k[q] = major;
         b_c[q] = min(col0 + minor, g.N - 8);
         b_off[q] = (uint32_t)(major * g.ldb + b_c[q]) * 2u;
@@ -447,16 +447,21 @@ struct Gemm {
     // a slice runs k tiles kb .. kb + nk - 1 of the tile's nk_all; below, kt counts from the slice's first one
     const int kb = sliced ? slice * nk_all / plan.n_slices : 0;
     const int nk = sliced ? (slice + 1) * nk_all / plan.n_slices - kb : nk_all;
-    // K is a multiple of 32 (of 64 in the dW products, whose rows are padded): when it is not
-    // a multiple of 64 the last k tile of a pass is half empty.  Its copies are re-pointed at
-    // the valid half (any finite data will do) and the A fragments of its second half are
-    // zeroed in registers, so those k steps add nothing.
-    // TAIL is a template parameter: the common shapes pay nothing for it.
+    // K is a multiple of 8 (of 64 in the dW products, whose rows are padded): when it is not
+    // a multiple of 64 only the first k_tail k of a pass's last k tile exist.  The copies of the
+    // 16-byte chunks (rows, where K is strided) past them are re-pointed at the tile's first chunk
+    // (last row that exists; any finite data will do) and the A fragments that lie past k_tail are
+    // zeroed in registers: a lane's fragment is one such chunk, so it exists whole or not at all.
+    // TAIL is a template parameter: 0 the common shapes, which pay nothing for it; 1 K = 32 mod 64, where only the
+    // second half of the tile has to be looked at (with 2 in its place the step with 32 split experts, where DOWN and
+    // BWD_DX run 21.5 k tiles, lost 0.7 %); 2 any other multiple of 8.  The shapes of 2 ran on plain fp32 FMA kernels
+    // before: fwd + bwd of 1501 tokens, 64 experts of 4096 x 688, top-8: 13.9 -> 1.73 ms.
     static_assert(!(TAIL && GROUP_K), "the dW products have no K tail");
     // in the slice's own count of k tiles: where the second K pass begins, and the two possible tail tiles
     const int pass2_at = nk1 - kb, tail1_at = nk1 - 1 - kb, tail2_at = nk_all - 1 - kb;
     const int k_first1 = k_begin + kb * BK, k_first2 = k_begin - pass2_at * BK;
     const int kp_first = kp_begin + kb * BK;
+    const int k_tail = TAIL == 1 ? BK / 2 : k_len - (nk1 - 1) * BK;
     auto is_tail = [&](int kt) { return TAIL && (kt == tail1_at || kt == tail2_at); };
     const uint32_t smem_base = (uint32_t)(uintptr_t)smem;   // LDS byte address of the dynamic segment
 
@@ -474,7 +479,7 @@ struct Gemm {
 #pragma unroll
       for (int q = 0; q < A_LOADS; ++q) {
         uint32_t off = a_off[q];
-        if (a_hi[q] && is_tail(kt)) off -= 64u;
+        if (is_tail(kt) && a_k[q] >= k_tail) off -= (uint32_t)(a_k[q] * 2);
         copy16_to_lds(Ab, off, stage + (wave * A_LOADS + q) * 1024);
       }
     };
@@ -494,8 +499,8 @@ struct Gemm {
         // (workspace bytes nothing has written, possibly NaN patterns).
         if (GROUP_K && !B_KC) off = (uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u;
         if (is_tail(kt)) {
-          if (B_KC) { if (b_hi[q]) off -= 64u; }
-          else off = (uint32_t)(min(b_k[q], 31) * g.ldb + b_c[q]) * 2u;
+          if (B_KC) { if (b_kc[q] >= k_tail) off -= (uint32_t)(b_kc[q] * 2); }
+          else off = (uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u;
         }
         const bool second = MODE == BWD_DX ? pass2 : (DUAL && b_second[q]);
         copy16_to_lds(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
@@ -573,13 +578,18 @@ struct Gemm {
           if (h == 0 && kt + 1 < nk) issueB(kt + 1);
           if (h == 1 && kt + 2 < nk) issueA(kt + 2);
           __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0): fragments are in registers
-          if (h == 1 && is_tail(kt)) {               // the half of the last k tile that lies past K
+          if ((TAIL == 2 || h == 1) && is_tail(kt)) {   // the part of the last k tile that lies past K
 #pragma unroll
-            for (int x = 0; x < HS; ++x)
+            for (int x = 0; x < HS; ++x) {
+              const bool past = TAIL == 1 || 32 * (h * HS + x) + 8 * (lane >> 4) >= k_tail;
 #pragma unroll
-              for (int i = 0; i < TM; ++i)
+              for (int i = 0; i < TM; ++i) {
+                u32x4 w = __builtin_bit_cast(u32x4, fa[x][i]);
 #pragma unroll
-                for (int v = 0; v < 8; ++v) fa[x][i][v] = (__bf16)0.0f;
+                for (int v = 0; v < 4; ++v) w[v] = past ? 0u : w[v];
+                fa[x][i] = __builtin_bit_cast(bf16x8, w);
+              }
+            }
           }
           if (h == 1 && grp == 1) { if (kt + 2 < nk) wait_vmcnt(A_LOADS); else wait_vmcnt(0); }
           __builtin_amdgcn_sched_barrier(0);
@@ -847,13 +857,13 @@ struct Gemm {
   }
 };
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::run(g, smem);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs g) {
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::finish(g);
 }
@@ -874,7 +884,7 @@ int compute_units() {
 // The kernels use more dynamic LDS than the default limit allows: the limit is raised once per
 // device and instantiation (idempotent, so a race between threads is harmless).  This must not
 // happen inside a stream capture; mfma_prepare() does it for every instantiation up front.
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 int raise_lds_limit() {
   using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
   static bool attr_set[64] = {};
@@ -890,7 +900,7 @@ int raise_lds_limit() {
   return BTX_OK;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, bool TAIL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 int launch(MArgs g, hipStream_t s) {
   using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
   constexpr int BNH = G::DUAL ? BN / 2 : BN;
@@ -925,9 +935,12 @@ int launch(MArgs g, hipStream_t s) {
   return BTX_OK;
 }
 
-// The direct-copy loaders need whole 16-byte chunks inside every row and K multiples of 32
-// where K is a matrix dimension (half a k tile).
-bool fast_ok(const FfShapes& sh) { return sh.d % 32 == 0 && sh.f % 32 == 0 && sh.d >= 64 && sh.f >= 64; }
+// the instantiation for this K (see TAIL)
+template <int BN, int MODE> int launch_any_k(const MArgs& g, hipStream_t s) {
+  if (g.K % 64 == 0) return launch<256, BN, 64, 2, 4, 3, 2, MODE, 0>(g, s);
+  if (g.K % 64 == 32) return launch<256, BN, 64, 2, 4, 3, 2, MODE, 1>(g, s);
+  return launch<256, BN, 64, 2, 4, 3, 2, MODE, 2>(g, s);
+}
 
 }  // namespace
 
@@ -942,9 +955,11 @@ int mfma_prepare() {
   int rc = BTX_OK;
   auto both = [&](auto mode_tag, auto bn_tag) {
     constexpr int MODE = decltype(mode_tag)::value, BN = decltype(bn_tag)::value;
-    if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, false>();
-    if constexpr (MODE != DW13 && MODE != DW2)
-      if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, true>();
+    if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 0>();
+    if constexpr (MODE != DW13 && MODE != DW2) {
+      if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 1>();
+      if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 2>();
+    }
   };
   both(std::integral_constant<int, UP>{}, std::integral_constant<int, 256>{});
   both(std::integral_constant<int, DOWN>{}, std::integral_constant<int, 256>{});
@@ -960,28 +975,25 @@ bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 < ((int64_t)1 << 3
 
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                    void* h1, void* h3, void* act, void* partial, hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs g{};
   g.A0 = (const bf16_t*)xs.base; g.a_perm = xs.perm; g.a_k = xs.k; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = h1; g.C1 = h3; g.C2 = act; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f;
   g.strideB_e = sh.s13; g.R = sh.R;
-  return sh.d % 64 ? launch<256, 256, 64, 2, 4, 3, 2, UP, true>(g, s) : launch<256, 256, 64, 2, 4, 3, 2, UP>(g, s);
+  return launch_any_k<256, UP>(g, s);
 }
 
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
               hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs g{};
   g.A0 = (const bf16_t*)act; g.B0 = (const bf16_t*)W2; g.C0 = y; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d;
   g.strideB_e = sh.s2; g.R = sh.R;
-  return sh.f % 64 ? launch<256, 256, 64, 2, 4, 3, 2, DOWN, true>(g, s) : launch<256, 256, 64, 2, 4, 3, 2, DOWN>(g, s);
+  return launch_any_k<256, DOWN>(g, s);
 }
 
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                  const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* gaT,
                  float* dg_part, hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs g{};
   g.A0 = (const bf16_t*)dys.base; g.a_perm = dys.perm; g.a_k = dys.k;
   g.B0 = (const bf16_t*)W2; g.C0 = dh1; g.C1 = dh3;
@@ -990,19 +1002,16 @@ int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const voi
   g.n_part = mfma_bwd_act_partials(sh.f);
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f;
   g.strideB_e = sh.s2; g.R = sh.R;
-  return sh.d % 64 ? launch<256, kActBN, 64, 2, 4, 3, 2, BWD_ACT, true>(g, s)
-                   : launch<256, kActBN, 64, 2, 4, 3, 2, BWD_ACT>(g, s);
+  return launch_any_k<kActBN, BWD_ACT>(g, s);
 }
 
 int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off,
                 const FfShapes& sh, void* dxs, void* partial, hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs g{};
   g.A0 = (const bf16_t*)dh1; g.A1 = (const bf16_t*)dh3; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = dxs; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d;
   g.strideB_e = sh.s13; g.R = sh.R;
-  return sh.f % 64 ? launch<256, 256, 64, 2, 4, 3, 2, BWD_DX, true>(g, s)
-                   : launch<256, 256, 64, 2, 4, 3, 2, BWD_DX>(g, s);
+  return launch_any_k<256, BWD_DX>(g, s);
 }
 
 int mfma_dw_pitch(int R, int E) { return (int)align_up((size_t)R, 64) + 64 * E; }
@@ -1010,7 +1019,6 @@ bool mfma_rows_ok(int R, int E) { return ((int64_t)align_up((size_t)R, 64) + 64 
 
 int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh3, const int32_t* off,
                   const FfShapes& sh, void* dW1, void* dW3, hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs g{};
   g.A0 = (const bf16_t*)xsT; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
   g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
@@ -1020,7 +1028,6 @@ int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh
 
 int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t* off, const FfShapes& sh, void* dW2,
                  hipStream_t s) {
-  if (!fast_ok(sh)) return BTX_ERR_UNSUPPORTED;
   MArgs h{};
   h.A0 = (const bf16_t*)gaT; h.B0 = (const bf16_t*)dysT; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;

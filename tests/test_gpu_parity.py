@@ -265,6 +265,14 @@ def test_bf16_off_the_mfma_path_with_wide_experts(T, d, f, E, k):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True)
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [(70, 8, 8, 2, 1), (300, 56, 40, 3, 2), (261, 72, 88, 4, 2), (190, 104, 120, 5, 3),
+                                       # K ranges of a cut last round that end in a partial k tile (f, d = 40, 8 mod 64)
+                                       (700, 328, 2088, 3, 2), (300, 1096, 312, 2, 1)])
+def test_bf16_contractions_that_end_inside_a_k_tile(T, d, f, E, k):
+    """d and f that are multiples of 8 only: the last k tile holds 1 to 7 chunks of 8, in both operand layouts."""
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True)
+
+
 def _random_mfma_case(i):
     rng = np.random.default_rng(1000 + i)
     E = int(rng.choice([1, 2, 3, 4, 6, 8, 16]))
