@@ -21,45 +21,40 @@ struct Carver {
 inline int esize(int dtype) { return dtype == BTX_BF16 ? 2 : 4; }
 inline bool dtype_ok(int dtype) { return dtype == BTX_F32 || dtype == BTX_BF16; }
 
-struct FwdWs { void *xs, *act, *y, *h1, *h3, *partial; size_t bytes; };
-FwdWs carve_forward(void* ws, int T, int d, int f, int k, int dtype, bool save) {
+struct FwdWs { void *xs, *act, *y, *partial; size_t bytes; };
+FwdWs carve_forward(void* ws, int T, int d, int f, int k, int dtype) {
   const size_t R = (size_t)T * k, es = esize(dtype);
   Carver c(ws);
   FwdWs w;
   // gathered token rows, unless the GEMMs read them through perm themselves
-  w.xs = ff_gather_fused(dtype, T, d, f) ? nullptr : c.take(R * d * es);
+  w.xs = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   w.act = c.take(R * f * es);
   w.y = c.take(R * d * es);
-  // h1/h3 when the caller does not keep them: only the plain path needs them at all
-  const bool own_h = !save && ff_up_needs_h(dtype, d, f);
-  w.h1 = own_h ? c.take(R * f * es) : nullptr;
-  w.h3 = own_h ? c.take(R * f * es) : nullptr;
-  const size_t split = ff_split_bytes(dtype, d, f);      // K slices of DOWN's last round
+  const size_t split = ff_split_bytes(dtype);            // K slices of DOWN's last round
   w.partial = split ? c.take(split) : nullptr;
   w.bytes = c.used;
   return w;
 }
 
-struct BwdWs { void *xs, *dysT, *dys, *dh1, *dh3, *ga, *dxs, *scratch, *router, *partial; float* dg_part; size_t bytes; };
+struct BwdWs { void *xsT, *dysT, *dys, *dh1, *dh3, *ga, *dxs, *router, *partial; float* dg_part; size_t bytes; };
 BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const size_t R = (size_t)T * k, es = esize(dtype);
   Carver c(ws);
   BwdWs w;
-  // the dW products take x and dY either as grouped rows or transposed and padded
-  const bool tr = ff_dw_transposed(dtype, d, f);
-  const size_t dw_op = tr ? (size_t)d * ff_dw_pitch((int)R, E) * es : R * d * es;
-  w.xs = c.take(dw_op);
+  // the bf16 dW products take x and dY transposed and padded
+  const bool tr = ff_dw_transposed(dtype);
+  const size_t dw_op = (size_t)d * ff_dw_pitch((int)R, E) * es;
+  w.xsT = tr ? c.take(dw_op) : nullptr;
   w.dysT = tr ? c.take(dw_op) : nullptr;
-  w.dys = ff_gather_fused(dtype, T, d, f) ? nullptr : c.take(R * d * es);
+  w.dys = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   w.dh1 = c.take(R * f * es);
   w.dh3 = c.take(R * f * es);
   // transposed path: dW2 reads ga as [f][padded rows]
   w.ga = c.take(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : R * f * es);
   w.dxs = c.take(R * d * es);
-  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials(dtype, d, f) * sizeof(float)));
-  w.scratch = c.take(ff_scratch_bytes(dtype, (int)R, f));
+  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials(dtype, f) * sizeof(float)));
   w.router = c.take(router_bwd_workspace_bytes(T, d, E));
-  const size_t split = ff_split_bytes(dtype, d, f);      // K slices of BWD_DX's last round
+  const size_t split = ff_split_bytes(dtype);            // K slices of BWD_DX's last round
   w.partial = split ? c.take(split) : nullptr;
   w.bytes = c.used;
   return w;
@@ -110,7 +105,7 @@ bool shapes_ok(int T, int d, int f, int E, int k) {
          (int64_t)T * k < (int64_t)1 << 31 && (int64_t)T * k * (int64_t)(d > f ? d : f) < (int64_t)1 << 40;
 }
 // valid shapes that the kernels' 32-bit offsets or grid limits cannot take
-bool shapes_supported(int dtype, int T, int d, int f, int E, int k) { return ff_rows_supported(dtype, T * k, d, f, E); }
+bool shapes_supported(int dtype, int T, int E, int k) { return ff_rows_supported(dtype, T * k, E); }
 
 // The kernels move rows as 16-byte pieces: every tensor of rows must start on a 16-byte boundary (NULL passes:
 // optional arguments), and with d, f multiples of 8 every row then does.
@@ -249,7 +244,7 @@ int btx_rmsnorm_backward(const void* dXn, const void* h, const float* gain, cons
 
 size_t btx_moe_ff_forward_workspace_bytes(int T, int d, int f, int E, int k, int dtype) {
   if (!dtype_ok(dtype) || !shapes_ok(T, d, f, E, k) || T == 0) return 0;
-  return carve_forward(nullptr, T, d, f, k, dtype, /*save=*/false).bytes;   // the larger of the two cases
+  return carve_forward(nullptr, T, d, f, k, dtype).bytes;
 }
 
 int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void* W2, int dtype,
@@ -261,22 +256,20 @@ int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void
   if (w13_expert_stride < (int64_t)d * f || w2_expert_stride < (int64_t)d * f) return BTX_ERR_INVALID_ARG;
   if ((save_h1 == nullptr) != (save_h3 == nullptr)) return BTX_ERR_INVALID_ARG;
   if (T == 0) return BTX_OK;
-  if (!shapes_supported(dtype, T, d, f, E, k)) return BTX_ERR_UNSUPPORTED;
+  if (!shapes_supported(dtype, T, E, k)) return BTX_ERR_UNSUPPORTED;
   if (!x || !W1 || !W3 || !W2 || !gates || !offsets || !perm || !inv_pos || !out || !workspace)
     return BTX_ERR_INVALID_ARG;
   if (!aligned16(x, W1, W3, W2, residual, out, save_h1, save_h3, workspace) || w13_expert_stride % 8 || w2_expert_stride % 8)
     return BTX_ERR_INVALID_ARG;
-  const FwdWs w = carve_forward(workspace, T, d, f, k, dtype, save_h1 != nullptr);
+  const FwdWs w = carve_forward(workspace, T, d, f, k, dtype);
   if (workspace_bytes < w.bytes) return BTX_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int R = T * k;
   const FfShapes sh{R, d, f, E, w13_expert_stride, w2_expert_stride};
-  void* h1 = save_h1 ? save_h1 : w.h1;
-  void* h3 = save_h3 ? save_h3 : w.h3;
-  const bool fused = ff_gather_fused(dtype, T, d, f);
+  const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_X, launch_gather_rows(x, w.xs, perm, R, k, d, dtype, s));
   const RowSource xs = fused ? RowSource{x, perm, k} : RowSource{w.xs, nullptr, 1};
-  BTX_STAGE(BTX_STAGE_UP, launch_up_swiglu(dtype, xs, W1, W3, offsets, sh, h1, h3, w.act, w.partial, s));
+  BTX_STAGE(BTX_STAGE_UP, launch_up_swiglu(dtype, xs, W1, W3, offsets, sh, save_h1, save_h3, w.act, w.partial, s));
   BTX_STAGE(BTX_STAGE_DOWN, launch_down(dtype, w.act, W2, offsets, sh, w.y, w.partial, s));
   BTX_STAGE(BTX_STAGE_COMBINE, launch_combine(w.y, gates, inv_pos, residual, out, T, k, d, dtype, s));
   return BTX_OK;
@@ -309,7 +302,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const int n_dw = (dW1 != nullptr) + (dW3 != nullptr) + (dW2 != nullptr);
   if (n_dw != 0 && n_dw != 3) return BTX_ERR_INVALID_ARG;
   if (T == 0) return BTX_OK;
-  if (!shapes_supported(dtype, T, d, f, E, k)) return BTX_ERR_UNSUPPORTED;
+  if (!shapes_supported(dtype, T, E, k)) return BTX_ERR_UNSUPPORTED;
   if (!dY || !x || !W_router || !W1 || !W3 || !W2 || !topk_idx || !gates || !probs || !offsets || !perm || !inv_pos ||
       !gate_sum || !prob_sum || !counts || !save_h1 || !save_h3 || !dX || !dW_router || !workspace)
     return BTX_ERR_INVALID_ARG;
@@ -321,26 +314,29 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int R = T * k;
   const FfShapes sh{R, d, f, E, w13_expert_stride, w2_expert_stride};
-  const bool fused = ff_gather_fused(dtype, T, d, f);
+  const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
-                                              w.dh3, w.ga, n_dw == 3, w.dg_part, w.scratch, s));
+                                              w.dh3, w.ga, n_dw == 3, w.dg_part, s));
   BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx(dtype, w.dh1, w.dh3, W1, W3, offsets, sh, w.dxs, w.partial, s));
   if (n_dw == 3) {
-    const bool tr = ff_dw_transposed(dtype, d, f);
-    auto gather_dw_operands = [&]() -> int {
-      if (!tr) return launch_gather_rows(x, w.xs, perm, R, k, d, dtype, s);
-      const int pitch = ff_dw_pitch(R, E);
-      if (int rc = launch_gather_rows_t(x, w.xs, perm, offsets, R, k, d, E, pitch, s)) return rc;
-      return launch_gather_rows_t(dY, w.dysT, perm, offsets, R, k, d, E, pitch, s);
-    };
-    BTX_STAGE(BTX_STAGE_GATHER_X_BWD, gather_dw_operands());
-    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dtype, dW_dtype, w.xs, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
-    BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dtype, dW_dtype, w.ga, tr ? w.dysT : w.dys, offsets, sh, dW2, s));
+    RowSource dw_x{x, perm, k}, dw_dy{dY, perm, k};
+    if (ff_dw_transposed(dtype)) {
+      auto gather_dw_operands = [&]() -> int {
+        const int pitch = ff_dw_pitch(R, E);
+        if (int rc = launch_gather_rows_t(x, w.xsT, perm, offsets, R, k, d, E, pitch, s)) return rc;
+        return launch_gather_rows_t(dY, w.dysT, perm, offsets, R, k, d, E, pitch, s);
+      };
+      BTX_STAGE(BTX_STAGE_GATHER_X_BWD, gather_dw_operands());
+      dw_x = RowSource{w.xsT, nullptr, 1};
+      dw_dy = RowSource{w.dysT, nullptr, 1};
+    }
+    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dtype, dW_dtype, dw_x, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
+    BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dtype, dW_dtype, w.ga, dw_dy, offsets, sh, dW2, s));
   }
   RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,
-                   topk_idx, gates, probs, inv_pos, gate_sum, prob_sum, counts, w.dg_part, bwd_act_partials(dtype, d, f), w.dxs, dX,
+                   topk_idx, gates, probs, inv_pos, gate_sum, prob_sum, counts, w.dg_part, bwd_act_partials(dtype, f), w.dxs, dX,
                    dW_router, db_router, w.router};
   BTX_STAGE(BTX_STAGE_ROUTER_BWD, launch_router_bwd(ra, s));
   return BTX_OK;

@@ -178,25 +178,32 @@ __device__ __forceinline__ int wave_incl_scan_i32(int v, int lane) {
   return v + (row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
 }
 
-// Which expert owns grouped row-tile `tile` when every expert's rows are cut
-// into tiles of BM rows, experts laid one after another.  Returns false past
-// the last tile.  offsets has E+1 entries.
-__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ offsets, int E, int BM, int tile,
-                                               int& expert, int& row0, int& row_end) {
-  int t = tile;
-  for (int e = 0; e < E; ++e) {
-    const int b = offsets[e], n = offsets[e + 1] - b;
-    const int nt = (n + BM - 1) / BM;
-    if (t < nt) {
-      expert = e;
-      row0 = b + t * BM;
-      row_end = b + n;
-      return true;
-    }
-    t -= nt;
+// Row tiles of the expert groups: every expert's rows are cut into tiles of BM rows, experts laid one after
+// another.  offsets has E+1 entries.  Lane x looks at expert x (E <= 64; all 64 lanes active): one load and a
+// prefix sum instead of a loop of dependent loads over the experts.
+struct RowTiles {
+  int o0, o1, nt, incl, bm;
+  __device__ __forceinline__ RowTiles(const int32_t* __restrict__ offsets, int E, int BM, int lane) : bm(BM) {
+    const int xe = min(lane, E - 1);
+    o0 = offsets[xe];
+    o1 = offsets[xe + 1];
+    nt = lane < E ? (o1 - o0 + BM - 1) / BM : 0;
+    incl = wave_incl_scan_i32(nt, lane);
   }
-  return false;
-}
+  __device__ __forceinline__ int count() const { return __builtin_amdgcn_readlane(incl, kWave - 1); }
+  // id < count() * nx, every expert's tiles (nt row tiles x nx columns) one after another: the expert, its number of
+  // row tiles and the id among its own
+  __device__ __forceinline__ void expert_of(int id, int nx, int& expert, int& n_rows, int& local) const {
+    expert = __ffsll((long long)__ballot((int64_t)incl * nx > id)) - 1;   // the first whose running total exceeds the id
+    n_rows = __builtin_amdgcn_readlane(nt, expert);
+    local = id - (__builtin_amdgcn_readlane(incl, expert) - n_rows) * nx;
+  }
+  // rows of the expert's row tile `tile`
+  __device__ __forceinline__ void rows_of(int expert, int tile, int& row0, int& row_end) const {
+    row0 = __builtin_amdgcn_readlane(o0, expert) + tile * bm;
+    row_end = __builtin_amdgcn_readlane(o1, expert);
+  }
+};
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -240,49 +247,46 @@ int launch_combine(const void* y, const float* gates, const int32_t* inv_pos, co
 // Expert GEMM stages.  `offsets` = E+1 grouped-row offsets on the device.
 struct FfShapes { int R, d, f, E; int64_t s13, s2; };
 // Grouped rows of a [.., d] operand: row r is row perm[r] / k of `base`, or simply row r of
-// `base` when perm is NULL (rows already gathered).  ff_gather_fused() says whether the
-// stages of a problem read token rows through perm themselves.
+// `base` when perm is NULL (rows already gathered).  ff_gather_fused() says whether UP and BWD_ACT of a
+// problem read token rows through perm themselves (fp32: always; bf16: unless a row's byte offset needs more
+// than 32 bits).
 struct RowSource { const void* base; const int32_t* perm; int k; };
-bool ff_gather_fused(int dtype, int T, int d, int f);
-// a = silu(xs W1) * (xs W3); h1/h3 stored when non-null.  They may be null only when
-// ff_up_needs_h() is false: the plain path computes act from the stored h1/h3.
-bool ff_up_needs_h(int dtype, int d, int f);
+bool ff_gather_fused(int dtype, int T, int d);
+// a = silu(xs W1) * (xs W3); h1/h3 stored when non-null.
 int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void* W3, const int32_t* offsets,
                      const FfShapes& sh, void* h1, void* h3, void* act, void* partial, hipStream_t s);
 // partial (here, in launch_down and in launch_bwd_dx): ff_split_bytes() of scratch (the bf16 MFMA path cuts the
 // tiles of a partly filled last round along K and adds the slices in a second kernel); may be NULL when
 // ff_split_bytes() is 0.  Products that follow each other on a stream may share it.
-size_t ff_split_bytes(int dtype, int d, int f);
+size_t ff_split_bytes(int dtype);
 // y = act W2
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, hipStream_t s);
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.
 // dh1, dh3: [R,f].  When ff_dw_transposed() holds, `ga` receives g*a transposed and padded
 // ([f][ff_dw_pitch()]), or nothing at all when want_dw is false; otherwise ga is [R,f].
-// bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per 256-column
-// tile on the bf16 MFMA path, a single sum otherwise)
-int bwd_act_partials(int dtype, int d, int f);
+// bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile)
+int bwd_act_partials(int dtype, int f);
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
-                   bool want_dw, float* dg_part, void* scratch, hipStream_t s);
+                   bool want_dw, float* dg_part, hipStream_t s);
 // dxs = dh1 W1^T + dh3 W3^T
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
 // dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When
 // ff_dw_transposed() holds, xs, dys and ga are passed in the transposed, padded form with
 // pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
-// does); otherwise as grouped rows.
-bool ff_dw_transposed(int dtype, int d, int f);
+// does); otherwise xs and dys are token rows read through perm and ga is [R,f].
+bool ff_dw_transposed(int dtype);
 int ff_dw_pitch(int R, int E);
-int launch_bwd_dw13(int dtype, int dW_dtype, const void* xs, const void* dh1, const void* dh3, const int32_t* offsets,
+int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
                     const FfShapes& sh, void* dW1, void* dW3, hipStream_t s);
-int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const void* dys, const int32_t* offsets, const FfShapes& sh,
-                   void* dW2, hipStream_t s);
-size_t ff_scratch_bytes(int dtype, int R, int f);
+int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
+                   const FfShapes& sh, void* dW2, hipStream_t s);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address
-bool ff_rows_supported(int dtype, int R, int d, int f, int E);
+bool ff_rows_supported(int dtype, int R, int E);
 
 struct RouterBwdArgs {
   const void* x; int dtype; const float* W_router; int T, d, E, k, route_mode, lb_mode; float lb_alpha, lb_grad_scale;

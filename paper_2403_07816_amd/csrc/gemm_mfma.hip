@@ -32,7 +32,6 @@
 //     up to 8 slices whose fp32 accumulators a second small kernel adds in ascending order and stores
 //     (UP: with the SwiGLU applied to the sums), so that the round fills the chip (Gemm::split_plan).
 #include "gemm_mfma.h"
-#include "gemm_generic.h"
 #include <type_traits>
 
 namespace btx {

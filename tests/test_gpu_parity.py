@@ -38,6 +38,14 @@ def test_ragged_shapes_fp32(T, d, f, E, k):
     run_layer_and_check(T, d, f, E, k, F32)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [(4000, 1032, 1160, 8, 2, {}), (4000, 1160, 1032, 8, 2, dict(cf=0.8, poison=True)),
+                                          (129, 8, 136, 2, 1, {}), (130, 136, 8, 3, 2, dict(poison=True)),
+                                          (257, 72, 184, 4, 3, {})])
+def test_fp32_tiles(T, d, f, E, k, kw):
+    """The fp32 products: many and few tiles, ragged rows, columns and contractions, token rows read through perm."""
+    run_layer_and_check(T, d, f, E, k, F32, **kw)
+
+
 @pytest.mark.parametrize("mode", [B.BTX_ROUTE_SWITCH_TOP1, B.BTX_ROUTE_SAMPLE_TOP1])
 @pytest.mark.parametrize("lb_mode,flags", [(B.BTX_LB_TOKEN_FRAC, 0), (B.BTX_LB_GATE_MEAN, 0),
                                            (B.BTX_LB_GATE_MEAN, B.BTX_FLAG_LB_GRAD_THROUGH_U)])
