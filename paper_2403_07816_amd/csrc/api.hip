@@ -105,7 +105,7 @@ bool shapes_ok(int T, int d, int f, int E, int k) {
          (int64_t)T * k < (int64_t)1 << 31 && (int64_t)T * k * (int64_t)(d > f ? d : f) < (int64_t)1 << 40;
 }
 // valid shapes that the kernels' 32-bit offsets or grid limits cannot take
-bool shapes_supported(int dtype, int T, int E, int k) { return ff_rows_supported(dtype, T * k, E); }
+bool shapes_supported(int dtype, int T, int d, int f, int E, int k) { return ff_rows_supported(dtype, T * k, d, f, E); }
 
 // The kernels move rows as 16-byte pieces: every tensor of rows must start on a 16-byte boundary (NULL passes:
 // optional arguments), and with d, f multiples of 8 every row then does.
@@ -256,7 +256,7 @@ int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void
   if (w13_expert_stride < (int64_t)d * f || w2_expert_stride < (int64_t)d * f) return BTX_ERR_INVALID_ARG;
   if ((save_h1 == nullptr) != (save_h3 == nullptr)) return BTX_ERR_INVALID_ARG;
   if (T == 0) return BTX_OK;
-  if (!shapes_supported(dtype, T, E, k)) return BTX_ERR_UNSUPPORTED;
+  if (!shapes_supported(dtype, T, d, f, E, k)) return BTX_ERR_UNSUPPORTED;
   if (!x || !W1 || !W3 || !W2 || !gates || !offsets || !perm || !inv_pos || !out || !workspace)
     return BTX_ERR_INVALID_ARG;
   if (!aligned16(x, W1, W3, W2, residual, out, save_h1, save_h3, workspace) || w13_expert_stride % 8 || w2_expert_stride % 8)
@@ -302,7 +302,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const int n_dw = (dW1 != nullptr) + (dW3 != nullptr) + (dW2 != nullptr);
   if (n_dw != 0 && n_dw != 3) return BTX_ERR_INVALID_ARG;
   if (T == 0) return BTX_OK;
-  if (!shapes_supported(dtype, T, E, k)) return BTX_ERR_UNSUPPORTED;
+  if (!shapes_supported(dtype, T, d, f, E, k)) return BTX_ERR_UNSUPPORTED;
   if (!dY || !x || !W_router || !W1 || !W3 || !W2 || !topk_idx || !gates || !probs || !offsets || !perm || !inv_pos ||
       !gate_sum || !prob_sum || !counts || !save_h1 || !save_h3 || !dX || !dW_router || !workspace)
     return BTX_ERR_INVALID_ARG;

@@ -286,7 +286,7 @@ int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address
-bool ff_rows_supported(int dtype, int R, int E);
+bool ff_rows_supported(int dtype, int R, int d, int f, int E);
 
 struct RouterBwdArgs {
   const void* x; int dtype; const float* W_router; int T, d, E, k, route_mode, lb_mode; float lb_alpha, lb_grad_scale;

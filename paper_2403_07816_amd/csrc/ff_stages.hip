@@ -8,7 +8,11 @@ namespace btx {
 
 int ff_prepare() { return mfma_prepare(); }
 
-bool ff_rows_supported(int dtype, int R, int E) { return dtype == BTX_BF16 ? mfma_rows_ok(R, E) : f32_rows_ok(R, E); }
+// bf16 with a d or f that is not a multiple of 32 keeps the documented limit of the fp32 path
+bool ff_rows_supported(int dtype, int R, int d, int f, int E) {
+  if (dtype != BTX_BF16) return f32_rows_ok(R, E);
+  return mfma_rows_ok(R, E) && ((d % 32 == 0 && f % 32 == 0 && d >= 64 && f >= 64) || f32_rows_ok(R, E));
+}
 
 bool ff_dw_transposed(int dtype) { return dtype == BTX_BF16; }
 int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
