@@ -266,7 +266,7 @@ int launch_down(int dtype, const void* act, const void* W2, const int32_t* offse
 // dh1, dh3: [R,f].  When ff_dw_transposed() holds, `ga` receives g*a transposed and padded
 // ([f][ff_dw_pitch()]), or nothing at all when want_dw is false; otherwise ga is [R,f].
 // bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile)
-int bwd_act_partials(int dtype, int f);
+int bwd_act_partials(int dtype, const FfShapes& sh);
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
                    bool want_dw, float* dg_part, hipStream_t s);

@@ -19,7 +19,9 @@ int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
 
 bool ff_gather_fused(int dtype, int T, int d) { return dtype != BTX_BF16 || mfma_gather_ok(T, d); }
 
-int bwd_act_partials(int dtype, int f) { return dtype == BTX_BF16 ? mfma_bwd_act_partials(f) : f32_bwd_act_partials(f); }
+int bwd_act_partials(int dtype, const FfShapes& sh) {
+  return dtype == BTX_BF16 ? mfma_bwd_act_partials(sh) : f32_bwd_act_partials(sh.f);
+}
 
 size_t ff_split_bytes(int dtype) { return dtype == BTX_BF16 ? mfma_split_bytes() : 0; }
 

@@ -7,7 +7,7 @@ namespace btx {
 int mfma_prepare();
 // the weight-gradient products address 255 rows of the transposed, padded operands with 32-bit byte offsets
 bool mfma_rows_ok(int R, int E);
-int mfma_bwd_act_partials(int f);
+int mfma_bwd_act_partials(const FfShapes& sh);
 // gathered A rows need every byte offset inside the source to fit 32 bits
 bool mfma_gather_ok(int T, int d);
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,

@@ -28,6 +28,8 @@
 //     the last one exits.  Rows beyond a group's end are loaded from a clamped address and
 //     never stored.  A last k tile that K fills only partly (K is a multiple of 8) has its copies
 //     re-pointed at valid data and the A fragments past K zeroed in registers;
+//   * few rows per expert (decoding, prompts, many narrow experts): the products stream the weights from HBM and
+//     the matrix cores wait, so the same code runs with smaller tiles and deeper prefetch (see row_tile());
 //   * UP, DOWN and BWD_DX: the tiles of a partly filled last round of workgroups are cut along K into
 //     up to 8 slices whose fp32 accumulators a second small kernel adds in ascending order and stores
 //     (UP: with the SwiGLU applied to the sums), so that the round fills the chip (Gemm::split_plan).
@@ -35,13 +37,18 @@
 #include <type_traits>
 
 namespace btx {
+
+// fp32 accumulators of the K slices of the last round of UP / DOWN / BWD_DX: at most cus + 8 * 8 (tile, slice) pairs
+// of 256 x 256 floats.  Small tiles keep their slices' sums here too, as many as fit.
+constexpr int kSplitMaxSlices = 8;
+constexpr int kSplitMaxCus = 256;   // compute units the K-cut of a last round is laid out for (see Gemm::split_plan)
+size_t mfma_split_bytes() { return (size_t)(kSplitMaxCus + 8 * kSplitMaxSlices) * 256 * 256 * sizeof(float); }
+
 namespace {
 
 // supertile: row tiles x column tiles that run concurrently chip-wide, and the XCDs along its
 // rows (8 / kXcdM along its columns)
 constexpr int kSupM = 16, kSupN = 16, kXcdM = 4;
-constexpr int kSplitMaxSlices = 8;
-constexpr int kSplitMaxCus = 256;   // compute units the K-cut of a last round is laid out for (see Gemm::split_plan)
 static_assert(kSupM % kXcdM == 0 && 8 % kXcdM == 0 && kSupN % (8 / kXcdM) == 0 && (kSupM * kSupN) % 8 == 0, "supertile");
 
 enum Mode { UP = 0, DOWN = 1, BWD_ACT = 2, BWD_DX = 3, DW13 = 4, DW2 = 5 };
@@ -65,20 +72,16 @@ struct MArgs {
   int total_ids;                        // tile ids of the launch (a few name no tile: padding of the id space)
   // UP / DOWN / BWD_DX: the tiles of the last, partly filled round are cut along K (see Gemm::split_plan)
   f32x4* partial; int cus;              // fp32 accumulators of the slices (NULL: never cut); compute units
+  // small tiles: every tile of the launch is cut into `slices` K ranges; slices > 1: fp32 sums in slice_sums,
+  // [slice][panel][R][N]
+  int slices; float* slice_sums;
 };
 
-__device__ __forceinline__ void wait_vmcnt(int n) {
-  // gfx9 encoding: vmcnt = bits [3:0] and [15:14]; expcnt [6:4] and lgkmcnt [11:8] left at max
-  switch (n) {
-    case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
-    case 4: __builtin_amdgcn_s_waitcnt(0x0F74); break;
-    case 6: __builtin_amdgcn_s_waitcnt(0x0F76); break;
-    case 8: __builtin_amdgcn_s_waitcnt(0x0F78); break;
-    case 12: __builtin_amdgcn_s_waitcnt(0x0F7C); break;
-    case 16: __builtin_amdgcn_s_waitcnt(0x4F70); break;
-    case 24: __builtin_amdgcn_s_waitcnt(0x4F78); break;
-    default: __builtin_amdgcn_s_waitcnt(0x0F70); break;
-  }
+// at most N vector memory operations outstanding (gfx9 encoding: vmcnt = bits [3:0] and [15:14]; expcnt [6:4] and
+// lgkmcnt [11:8] left at max)
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // Direct global -> LDS copy of 16 bytes per lane: lane l's data lands at lds_base + 16*l.
@@ -142,17 +145,21 @@ struct Gemm {
   static constexpr bool DUAL = (MODE == UP || MODE == DW13);
   static constexpr bool GROUP_K = (MODE == DW13 || MODE == DW2);
   static constexpr bool STREAM_OUT = (MODE == BWD_ACT || MODE == DOWN);
+  // 128-column tiles: one pipeline for all wavefronts, two workgroups of four per compute unit; 256: ping-pong
+  static constexpr bool SMALL = BN == 128;
   static constexpr int NW = WM * WN, NT = NW * kWave;
   static constexpr int TM = BM / WM / 16;                      // 16-row fragments per wavefront
   static constexpr int TN = BN / WN / 16;
   static constexpr int TNH = DUAL ? TN / 2 : TN;
   static constexpr int BNH = DUAL ? BN / 2 : BN;               // output columns per B panel
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
-  // LDS: NSA = 3 stages of the A tile, then NSB = 2 stages of the B tile (the ping-pong schedule)
+  // LDS: NSA stages of the A tile, then NSB of the B tile
   static constexpr int B_BASE = NSA * A_BYTES;
   static constexpr int LDS_BYTES = NSA * A_BYTES + NSB * B_BYTES;
-  static_assert(NSA == 3 && NSB == 2 && WM * WN == 8 && BK == 64, "the schedule is written for 8 wavefronts, 2 k steps");
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+  static_assert(BK == 64 && (SMALL ? NW == 4 && !GROUP_K && NSB >= NSA && NSA >= 2
+                                   : NW == 8 && ((NSA == 3 && NSB == 2) || (NSA == 2 && NSB == 3))),
+                "the ping-pong schedule is written for 8 wavefronts, 2 k steps");
+  static_assert(LDS_BYTES <= (SMALL ? 80 : 160) * 1024, "LDS");
   static constexpr int A_LOADS = A_BYTES / 1024 / NW, B_LOADS = B_BYTES / 1024 / NW;  // per wavefront per tile
   static constexpr int KSTEPS = BK / 32;                       // k steps (one MFMA deep) per tile
   static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile must split into 1 KB wave copies");
@@ -163,7 +170,10 @@ struct Gemm {
   static __device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 7; }
   // strided-K tile: [BK][COLS], 16-byte chunk index XORed with tr_swz(k): bits 2-3 keep the four
   // k rows of one transposing read apart, bit 1 the two 16-lane groups that share a pass
-  static __device__ __forceinline__ int tr_swz(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
+  // (64 columns: the rows are half as long, so that bit 0 of k keeps two rows apart by itself)
+  template <int COLS> static __device__ __forceinline__ int tr_swz(int k) {
+    return COLS >= 128 ? ((k & 3) << 2) | (((k >> 3) & 1) << 1) : (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1);
+  }
 
   // byte offset inside a wave's copy `seg` (1 KB each) -> global element offset, for both layouts
   template <bool KC, int ROWS_OR_COLS>
@@ -179,7 +189,7 @@ struct Gemm {
       const int k = o / PITCH;
       const int phys = (o % PITCH) / 16;
       major = k;                                // k row of the tile
-      minor_elem = (phys ^ tr_swz(k)) * 8;      // column offset inside the tile
+      minor_elem = (phys ^ tr_swz<ROWS_OR_COLS>(k)) * 8;      // column offset inside the tile
     }
   }
 
@@ -196,7 +206,7 @@ struct Gemm {
     const int g = lane >> 4, r = lane & 15;
     const int k = 32 * ks + 8 * g + (r >> 2);
     const int c = col + 4 * (r & 3);
-    const int off = k * (COLS * 2) + ((((c >> 3) ^ tr_swz(k)) << 4) | ((c & 7) << 1));
+    const int off = k * (COLS * 2) + ((((c >> 3) ^ tr_swz<COLS>(k)) << 4) | ((c & 7) << 1));
     typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
     const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + off));
     const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + off + 4 * COLS * 2));
@@ -274,7 +284,7 @@ struct Gemm {
       t.row_end = g.M;
       t.k_begin = g.offsets[e];
       t.k_end = g.offsets[e + 1];
-      for (int q = 0; q < e; ++q) t.kp_begin += (g.offsets[q + 1] - g.offsets[q] + 63) & ~63;
+      t.kp_begin = padded_rows_before(g, e, threadIdx.x & (kWave - 1));
     } else {
       // the expert whose row tiles include tile_m: the first lane whose running total exceeds it
       const unsigned long long owners = __ballot(x.nt_incl > tile_m);
@@ -294,6 +304,37 @@ struct Gemm {
     return true;
   }
 
+  // first padded row of expert e in the transposed operands (all 64 lanes active)
+  static __device__ __forceinline__ int padded_rows_before(const MArgs& g, int e, int lane) {
+    int p = 0;
+    if (g.E <= 8) {                                      // with 64 experts the loop cost DW13 and DW2 7 %
+      for (int q = 0; q < e; ++q) p += (g.offsets[q + 1] - g.offsets[q] + 63) & ~63;
+    } else {
+      p = lane < e ? (g.offsets[lane + 1] - g.offsets[lane] + 63) & ~63 : 0;
+      p = __builtin_amdgcn_readlane(wave_incl_scan_i32(p, lane), kWave - 1);
+    }
+    return p;
+  }
+  // Small tiles: every XCD takes one eighth of the ids, one after another: K slice by K slice of an expert, its row
+  // tiles fastest, so that what an XCD runs at a time reads a piece of the weights from HBM once and long rows of it.
+  static __device__ __forceinline__ bool locate_small(const MArgs& g, int lane, Tile& t, int& slice) {
+    const RowTiles rt(g.offsets, g.E, BM, lane);
+    const int per_row_tile = g.tiles_n * g.slices, total = rt.count() * per_row_tile;
+    const int share = (total + 7) / 8, pos = (int)(blockIdx.x / 8), id = (int)(blockIdx.x % 8) * share + pos;
+    if (pos >= share || id >= total) return false;
+    int n_rows, local;
+    rt.expert_of(id, per_row_tile, t.e, n_rows, local);
+    slice = local / (g.tiles_n * n_rows);
+    local -= slice * g.tiles_n * n_rows;
+    t.tile_n = local / n_rows;
+    rt.rows_of(t.e, local - t.tile_n * n_rows, t.row0, t.row_end);
+    t.exp_row0 = __builtin_amdgcn_readlane(rt.o0, t.e);
+    t.k_begin = 0;
+    t.k_end = g.K;
+    t.kp_begin = MODE == BWD_ACT ? padded_rows_before(g, t.e, lane) : 0;
+    return true;
+  }
+
   // DOWN and BWD_DX have few, long tiles (16 column tiles): their last round is often a small fraction of
   // the chip (8.25 rounds for the benchmark's top-2 layer, 4.1 for top-1, 2.25 for one sequence), and a
   // tile cannot be cut smaller; UP has 44.3, 22.2 and 11.4 rounds there.  So the tiles of that round are cut
@@ -302,7 +343,7 @@ struct Gemm {
   // accumulators in `partial`; a second, small kernel adds the S slices of a tile in slice order and stores
   // the result.  No atomics, and the order of every sum is fixed by the shapes and the number of compute
   // units alone.  ids >= total_ids are the workgroups of the slices 1 .. S-1.
-  static constexpr bool SPLIT = (MODE == DOWN || MODE == BWD_DX || MODE == UP);
+  static constexpr bool SPLIT = !SMALL && (MODE == DOWN || MODE == BWD_DX || MODE == UP);
   static constexpr int kMaxSlices = kSplitMaxSlices, kMinSliceTiles = 16, kIdHoles = 8;   // the id space has up to 8 ids past the last tile
   struct SplitPlan { int id_full, n_left, n_slices; };
   static __device__ __forceinline__ SplitPlan split_plan(const MArgs& g, int n_rt) {
@@ -352,7 +393,8 @@ struct Gemm {
     auto put = [&](void* C, size_t idx, const f32x4& v) {
       *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(C) + idx) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     };
-    const int m = tile.row0 + wm * (TM * 16) + i * 16 + (lane & 15);
+    const int m0 = tile.row0 + wm * (TM * 16) + i * 16, m = m0 + (lane & 15);
+    if (m0 >= tile.row_end) return;                      // 16 rows that do not exist: the slices left nothing there
 #pragma unroll
     for (int jj = 0; jj < TNH; ++jj) {
       const int n = col0 + wn * (TNH * 16) + jj * 16 + 4 * (lane >> 4);
@@ -379,19 +421,27 @@ struct Gemm {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wm = wave / WN, wn = wave % WN;
 
-    const Experts experts(g, lane);
-    const SplitPlan plan = split_plan(g, experts.n_rt);
     int id = blockIdx.x, slice = 0;
-    if (SPLIT && id >= g.total_ids) {                    // a workgroup for slice 1.. of a left-over tile
-      if (plan.n_slices <= 1) return;
-      const int w = id - g.total_ids;
-      slice = 1 + w / plan.n_left;
-      if (slice >= plan.n_slices) return;
-      id = plan.id_full + w % plan.n_left;
-    }
-    const bool sliced = SPLIT && plan.n_slices > 1 && id >= plan.id_full;
+    SplitPlan plan{0, 0, 1};
     Tile tile;
-    if (!locate(g, experts, id, tile)) return;
+    bool sliced;
+    if constexpr (SMALL) {
+      if (!locate_small(g, lane, tile, slice)) return;
+      plan.n_slices = g.slices;
+      sliced = MODE != BWD_ACT && plan.n_slices > 1;
+    } else {
+      const Experts experts(g, lane);
+      plan = split_plan(g, experts.n_rt);
+      if (SPLIT && id >= g.total_ids) {                  // a workgroup for slice 1.. of a left-over tile
+        if (plan.n_slices <= 1) return;
+        const int w = id - g.total_ids;
+        slice = 1 + w / plan.n_left;
+        if (slice >= plan.n_slices) return;
+        id = plan.id_full + w % plan.n_left;
+      }
+      sliced = SPLIT && plan.n_slices > 1 && id >= plan.id_full;
+      if (!locate(g, experts, id, tile)) return;
+    }
     const int e = tile.e, row0 = tile.row0, row_end = tile.row_end, k_begin = tile.k_begin, k_end = tile.k_end;
     const int kp_begin = tile.kp_begin, tile_n = tile.tile_n;
     const int col0 = tile_n * BNH;
@@ -536,9 +586,49 @@ struct Gemm {
         for (int j = 0; j < TN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
     };
-    // grouped-K: the k rows past an expert's last one meet the zero fill of the transposed operand
+    // the A fragments that lie past K in a pass's last k tile
+    auto zero_past = [&](bf16x8 (&af)[TM], int ks) {
+      const bool past = TAIL == 1 ? ks == 1 : 32 * ks + 8 * (lane >> 4) >= k_tail;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        u32x4 w = __builtin_bit_cast(u32x4, af[i]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[v] = past ? 0u : w[v];
+        af[i] = __builtin_bit_cast(bf16x8, w);
+      }
+    };
 
-    {
+    if constexpr (SMALL) {
+      // One pipeline for all wavefronts: A tiles are requested NSA - 1 k tiles ahead, B tiles NSB - 1, one barrier
+      // per k tile.  A's copies are issued before B's, so that of what may be outstanding when tile kt is needed
+      // only the copies behind A's of that tile remain.
+      constexpr int kAhead = (NSB > NSA ? B_LOADS : 0) + (NSA - 2) * (A_LOADS + B_LOADS);
+#pragma unroll
+      for (int j = 1 - NSB; j < 0; ++j) {
+        if (j + NSA - 1 >= 0 && j + NSA - 1 < nk) issueA(j + NSA - 1);
+        if (j + NSB - 1 < nk) issueB(j + NSB - 1);
+      }
+#pragma unroll 1
+      for (int kt = 0; kt < nk; ++kt) {
+        if (kt + NSB - 2 < nk) wait_vmcnt<kAhead>(); else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();                    // tile kt published; everybody is done with tile kt - 1
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + NSA - 1 < nk) issueA(kt + NSA - 1);
+        if (kt + NSB - 1 < nk) issueB(kt + NSB - 1);
+        bf16x8 fa[KSTEPS][TM], fb[KSTEPS][TN];
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) load_frags(kt, ks, fa[ks], fb[ks]);
+        if (is_tail(kt)) {
+#pragma unroll
+          for (int ks = 0; ks < KSTEPS; ++ks) zero_past(fa[ks], ks);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) mfma_step(fa[ks], fb[ks]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_barrier();                      // the epilogue reuses the operand stages
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
       // Ping-pong schedule.  The two wavefronts that share a SIMD (w and w+4) alternate
       // between a memory phase (LDS fragment reads of half a tile + a quarter of the copies
       // of a later tile) and a compute phase (an uninterrupted run of 32 MFMAs), half a period
@@ -553,15 +643,22 @@ struct Gemm {
       // so the address unit sees the same 16 copies in every phase.  B has two LDS stages (its
       // copies have at least 2.5 phases to land), A has three (at least 4 phases).  Every
       // wavefront waits for its copies of tile kt+1 right before the barrier that ends phase
-      // 4kt+3; its 4 youngest copies (A of tile kt+2) may stay in flight.
+      // 4kt+3; its youngest copies (A of tile kt+2) may stay in flight.
+      // NSB == 3: the roles of A and B in the copies are exchanged, for products that wait for the weights to arrive
+      // from HBM (UP of 301 tokens, 4 experts of 4096 x 11008, top-2, 192-row tiles: 177 us with three stages of A,
+      // 170 with three of B; large products lose up to 10 % with it).
       constexpr int HS = KSTEPS / 2;                 // k steps per half tile
       const int grp = wave / (NW / 2);               // group 1 lags group 0 by one phase
       bf16x8 fa[HS][TM], fb[HS][TN];
+      constexpr bool DEEP_B = NSB == 3;
+      constexpr int DEEP_LOADS = DEEP_B ? B_LOADS : A_LOADS;
+      auto issue_near = [&](int kt) { if constexpr (DEEP_B) issueA(kt); else issueB(kt); };
+      auto issue_deep = [&](int kt) { if constexpr (DEEP_B) issueB(kt); else issueA(kt); };
       if (nk > 0) {
-        issueA(0);
-        issueB(0);
-        if (nk > 1) issueA(1);
-        if (nk > 1) wait_vmcnt(A_LOADS); else wait_vmcnt(0);
+        issue_deep(0);
+        issue_near(0);
+        if (nk > 1) issue_deep(1);
+        if (nk > 1) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();                // tile 0 published
       }
       if (grp == 1 && nk > 0) __builtin_amdgcn_s_barrier();   // idle during group 0's first memory phase
@@ -574,30 +671,21 @@ struct Gemm {
           // ---- memory phase
 #pragma unroll
           for (int x = 0; x < HS; ++x) load_frags(kt, h * HS + x, fa[x], fb[x]);
-          if (h == 0 && kt + 1 < nk) issueB(kt + 1);
-          if (h == 1 && kt + 2 < nk) issueA(kt + 2);
+          if (h == 0 && kt + 1 < nk) issue_near(kt + 1);
+          if (h == 1 && kt + 2 < nk) issue_deep(kt + 2);
           __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0): fragments are in registers
           if ((TAIL == 2 || h == 1) && is_tail(kt)) {   // the part of the last k tile that lies past K
 #pragma unroll
-            for (int x = 0; x < HS; ++x) {
-              const bool past = TAIL == 1 || 32 * (h * HS + x) + 8 * (lane >> 4) >= k_tail;
-#pragma unroll
-              for (int i = 0; i < TM; ++i) {
-                u32x4 w = __builtin_bit_cast(u32x4, fa[x][i]);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) w[v] = past ? 0u : w[v];
-                fa[x][i] = __builtin_bit_cast(bf16x8, w);
-              }
-            }
+            for (int x = 0; x < HS; ++x) zero_past(fa[x], h * HS + x);
           }
-          if (h == 1 && grp == 1) { if (kt + 2 < nk) wait_vmcnt(A_LOADS); else wait_vmcnt(0); }
+          if (h == 1 && grp == 1) { if (kt + 2 < nk) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>(); }
           __builtin_amdgcn_sched_barrier(0);
           __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
           // ---- compute phase
 #pragma unroll
           for (int x = 0; x < HS; ++x) mfma_step(fa[x], fb[x]);
-          if (h == 1 && grp == 0) { if (kt + 2 < nk) wait_vmcnt(A_LOADS); else wait_vmcnt(0); }
+          if (h == 1 && grp == 0) { if (kt + 2 < nk) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>(); }
           __builtin_amdgcn_sched_barrier(0);
           if (!(grp == 1 && h == 1 && kt + 1 == nk)) __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
@@ -605,12 +693,28 @@ struct Gemm {
       }
     }
 
+    if (SMALL && sliced) {                               // row-major sums, for slices_finish_kernel
+      const size_t panel = (size_t)g.R * g.N;
+      float* P = g.slice_sums + (size_t)slice * (DUAL ? 2 : 1) * panel;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int m = row0 + wm * (TM * 16) + i * 16 + (lane & 15);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int n = col0 + wn * (TNH * 16) + (j % TNH) * 16 + 4 * (lane >> 4);
+          if (m < row_end && n < g.N) *reinterpret_cast<f32x4*>(P + (j / TNH) * panel + (size_t)m * g.N + n) = acc[i][j];
+        }
+      }
+      return;
+    }
     if (SPLIT && sliced) {                               // a slice leaves its accumulators for split_finish
       f32x4* slot = partial_slot(g, plan, id - plan.id_full, slice) + (size_t)wave * (TM * TN * kWave);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
+        if (row0 + wm * (TM * 16) + i * 16 >= row_end) break;          // finish() does not look at these rows
 #pragma unroll
         for (int j = 0; j < TN; ++j) __builtin_nontemporal_store(acc[i][j], slot + (i * TN + j) * kWave + lane);
+      }
       return;
     }
 
@@ -862,6 +966,48 @@ __global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel(MArgs g) {
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::run(g, smem);
 }
 
+// small tiles: 4 wavefronts, two workgroups per compute unit
+template <int BM, int WM, int WN, int NSA, int NSB, int MODE, int TAIL>
+__global__ __launch_bounds__(WM* WN* kWave, 2) void mfma_small_kernel(MArgs g) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL>::run(g, smem);
+}
+
+// The K slices of small tiles added in slice order, 8 columns of a row per thread; SWIGLU: [slice][2][R][N], the
+// activation (and the two products themselves, unless C0 is NULL) is stored.
+template <bool SWIGLU>
+__global__ __launch_bounds__(256) void slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N,
+                                                            const int32_t* __restrict__ offsets, int E,
+                                                            bf16_t* __restrict__ C0, bf16_t* __restrict__ C1,
+                                                            bf16_t* __restrict__ C2) {
+  const int chunks = N / 8;
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;     // R * N floats fit the scratch, so 32 bits do
+  const int row = (int)(i / (unsigned)chunks), c = (int)(i - row * (unsigned)chunks) * 8;
+  if (row >= offsets[E]) return;                         // at most R rows are kept
+  const size_t panel = (size_t)R * N, at = (size_t)row * N + c;
+  float h1[8] = {}, h3[8] = {};
+  for (int s = 0; s < slices; ++s) {
+    const float* P = sums + (size_t)s * (SWIGLU ? 2 : 1) * panel + at;
+    float v[8];
+    RowVec<float, 8>::ld(P, v);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) h1[x] += v[x];
+    if constexpr (SWIGLU) {
+      RowVec<float, 8>::ld(P + panel, v);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) h3[x] += v[x];
+    }
+  }
+  if constexpr (SWIGLU) {
+    if (C0) { RowVec<bf16_t, 8>::st(C0 + at, h1); RowVec<bf16_t, 8>::st(C1 + at, h3); }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) h1[x] = silu_f(h1[x]) * h3[x];
+    RowVec<bf16_t, 8>::st(C2 + at, h1);
+  } else {
+    RowVec<bf16_t, 8>::st(C0 + at, h1);
+  }
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs g) {
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::finish(g);
@@ -883,16 +1029,13 @@ int compute_units() {
 // The kernels use more dynamic LDS than the default limit allows: the limit is raised once per
 // device and instantiation (idempotent, so a race between threads is harmless).  This must not
 // happen inside a stream capture; mfma_prepare() does it for every instantiation up front.
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
-int raise_lds_limit() {
-  using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
+template <void (*Kernel)(MArgs), int LDS_BYTES> int raise_lds_limit() {
   static bool attr_set[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BTX_ERR_HIP;
   if (!attr_set[dev]) {
-    auto kern = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            G::LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) !=
+        hipSuccess)
       return BTX_ERR_HIP;
     attr_set[dev] = true;
   }
@@ -900,15 +1043,17 @@ int raise_lds_limit() {
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
-int launch(MArgs g, hipStream_t s) {
+int launch(MArgs g, bool prepare_only, hipStream_t s) {
   using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
+  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
+  if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
+  if (prepare_only) return BTX_OK;
   constexpr int BNH = G::DUAL ? BN / 2 : BN;
   g.tiles_n = ceil_div(g.N, BNH);
   g.tiles_m = G::GROUP_K ? ceil_div(g.M, BM) : ceil_div(g.R, BM) + g.E;
   // every tile has exactly one block id below (number of tiles) + 8; see the tile mapping
   g.blocks_per_e = (int)align_up((size_t)g.tiles_m * g.tiles_n, 8) + 8;
   g.total_ids = G::GROUP_K ? g.E * g.blocks_per_e : g.tiles_m * g.tiles_n + 8;
-  if (int rc = raise_lds_limit<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>()) return rc;
   int grid = g.total_ids;
   if constexpr (G::SPLIT) {
     // K too short for two slices of the minimum length: split_plan() would never cut
@@ -922,7 +1067,7 @@ int launch(MArgs g, hipStream_t s) {
   } else {
     g.partial = nullptr;
   }
-  mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL><<<grid, G::NT, G::LDS_BYTES, s>>>(g);
+  kernel<<<grid, G::NT, G::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
   if constexpr (G::SPLIT) {
     if (g.partial) {
@@ -934,41 +1079,114 @@ int launch(MArgs g, hipStream_t s) {
   return BTX_OK;
 }
 
-// the instantiation for this K (see TAIL)
-template <int BN, int MODE> int launch_any_k(const MArgs& g, hipStream_t s) {
-  if (g.K % 64 == 0) return launch<256, BN, 64, 2, 4, 3, 2, MODE, 0>(g, s);
-  if (g.K % 64 == 32) return launch<256, BN, 64, 2, 4, 3, 2, MODE, 1>(g, s);
-  return launch<256, BN, 64, 2, 4, 3, 2, MODE, 2>(g, s);
+// row tiles of BM rows if the rows were spread evenly over the experts
+int even_row_tiles(const MArgs& g, int BM) {
+  const int busy = std::max(std::min(g.E, g.R), 1);
+  return busy * ceil_div(ceil_div(g.R, busy), BM);
+}
+
+// K slices of a product of `tiles` small tiles of nk k tiles: as many as give every compute unit a workgroup, each of
+// at least 8 k tiles, and no more than the caller's scratch holds.  DOWN of 16 tokens (4 experts of 11008 x 4096, 128
+// tiles): 2 slices 68 us, 4 (two workgroups per unit) 73.
+int small_slices(int64_t tiles, int nk, size_t bytes_per_slice) {
+  const int64_t fill = kSplitMaxCus / std::max<int64_t>(tiles, 1), fit = (int64_t)(mfma_split_bytes() / bytes_per_slice);
+  return (int)std::max<int64_t>(std::min({fill, fit, (int64_t)(nk / 8), (int64_t)kSplitMaxSlices}), 1);
+}
+
+template <int BM, int MODE, int TAIL> int launch_small(MArgs g, bool prepare_only, hipStream_t s) {
+  // 64 rows: three stages of both operands (72 KB); 128: two of A and three of B (80 KB, half of a compute unit's LDS)
+  constexpr int WM = MODE == BWD_ACT && BM == 64 ? 1 : 2, WN = 4 / WM;
+  constexpr int NSA = BM == 64 ? 3 : 2, NSB = 3;
+  using G = Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL>;
+  constexpr auto kernel = mfma_small_kernel<BM, WM, WN, NSA, NSB, MODE, TAIL>;
+  if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
+  if (prepare_only) return BTX_OK;
+  g.tiles_n = ceil_div(g.N, G::BNH);
+  g.tiles_m = ceil_div(g.R, BM) + g.E;
+  g.slice_sums = reinterpret_cast<float*>(g.partial);
+  g.slices = 1;
+  if (MODE != BWD_ACT && g.slice_sums)
+    g.slices = small_slices((int64_t)even_row_tiles(g, BM) * g.tiles_n, ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1),
+                            (size_t)g.R * g.N * (MODE == UP ? 8 : 4));
+  const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * g.slices;
+  if (blocks > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
+  kernel<<<(unsigned)align_up((size_t)blocks, 8), G::NT, G::LDS_BYTES, s>>>(g);
+  BTX_LAUNCH_CHECK();
+  if (g.slices > 1) {
+    slices_finish_kernel<MODE == UP><<<ceil_div((int64_t)g.R * (g.N / 8), 256), 256, 0, s>>>(
+        g.slice_sums, g.slices, g.R, g.N, g.offsets, g.E, (bf16_t*)g.C0, (bf16_t*)g.C1, (bf16_t*)g.C2);
+    BTX_LAUNCH_CHECK();
+  }
+  return BTX_OK;
+}
+
+// Row tile of a row-grouped product.  With few rows per expert a product streams the weights: what counts is how
+// many bytes of them are in flight, and that no rows are computed that do not exist.  us, 4 experts of 4096 x 11008:
+//   rows per expert      8 (UP / DOWN)   32          80          150         170         210
+//   256                  190 / 104       190 / 107   192 / 110   196 / 115   195 / 117   197 / 121
+//   64                   138 /  68       145 /  72   189 / 103
+//   128                  144 /  71       150 /  74   154 /  82   222 / 125   227 / 129   235 / 133
+//   192 (3 stages of B)                              160 /  90   170 / 101   179 / 104   290 / 148
+// (how many rows an expert has is only known on the device: the average decides, and a routing that is far from it pays
+// with a second row tile for the experts that have more.)
+// A product of few 256-row tiles that are also too short to be cut along K into pieces of 32 k tiles leaves compute
+// units idle (1200 rows, 4 experts of 4096 x 1376: UP 76 us, DOWN 39, BWD_ACT 88, BWD_DX 68); with 128-row tiles 58, 34,
+// 55, 50; with 64-row tiles 67, 38, 37, 60: the smaller ones are taken, of 64 rows where those of 128 are too few as well.
+template <int MODE> int row_tile(const MArgs& g) {
+  constexpr bool DUAL = MODE == UP;
+  constexpr int64_t kEnough = 192;                       // workgroups of three quarters of the compute units
+  const int64_t avg = g.R / std::max(g.E, 1);
+  if (avg <= 48) return 64;
+  if (avg <= 110) return 128;
+  const int64_t tiles = (int64_t)even_row_tiles(g, 256) * ceil_div(g.N, DUAL ? 128 : 256);
+  const int64_t pieces = MODE == BWD_ACT || !g.partial ? 1 : ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1) / 32;
+  if (tiles * std::max<int64_t>(std::min(pieces, kSplitMaxCus / std::max<int64_t>(tiles, 1)), 1) >= kEnough)
+    return MODE != BWD_ACT && avg <= 168 ? 192 : 256;
+  return (int64_t)even_row_tiles(g, 128) * ceil_div(g.N, DUAL ? 64 : 128) >= kEnough ? 128 : 64;
+}
+
+// the instantiation for this K (see TAIL) and row tile
+template <int MODE> int launch_rows(const MArgs& g, int tile, bool prepare_only, hipStream_t s) {
+  const bool whole = g.K % 64 == 0;
+  if (tile == 64) return whole ? launch_small<64, MODE, 0>(g, prepare_only, s) : launch_small<64, MODE, 2>(g, prepare_only, s);
+  if (tile == 128) return whole ? launch_small<128, MODE, 0>(g, prepare_only, s) : launch_small<128, MODE, 2>(g, prepare_only, s);
+  if constexpr (MODE != BWD_ACT)
+    if (tile == 192)
+      return whole ? launch<192, 256, 64, 2, 4, 2, 3, MODE, 0>(g, prepare_only, s)
+                   : launch<192, 256, 64, 2, 4, 2, 3, MODE, 2>(g, prepare_only, s);
+  if (whole) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0>(g, prepare_only, s);
+  if (g.K % 64 == 32) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 1>(g, prepare_only, s);
+  return launch<256, 256, 64, 2, 4, 3, 2, MODE, 2>(g, prepare_only, s);
+}
+template <int MODE> int launch_rows(const MArgs& g, hipStream_t s) { return launch_rows<MODE>(g, row_tile<MODE>(g), false, s); }
+
+template <int MODE> int prepare_rows() {
+  MArgs g{};
+  for (int tile : {64, 128, 192, 256})
+    for (int k : {64, 32, 8}) {
+      g.K = k;
+      if (int rc = launch_rows<MODE>(g, tile, true, nullptr)) return rc;
+    }
+  return BTX_OK;
 }
 
 }  // namespace
 
-constexpr int kActBN = 256;  // column tile of the BWD_ACT kernel = width of one dg partial
-
-// fp32 accumulators of the K slices of the last round of UP / DOWN / BWD_DX: at most cus + 8 * 8 (tile, slice) pairs
-// of 256 x 256 floats
-size_t mfma_split_bytes() { return (size_t)(kSplitMaxCus + 8 * kSplitMaxSlices) * 256 * 256 * sizeof(float); }
-
 int mfma_prepare() {
   if (compute_units() <= 0) return BTX_ERR_HIP;        // looked up once per device, here rather than in a launch
-  int rc = BTX_OK;
-  auto both = [&](auto mode_tag, auto bn_tag) {
-    constexpr int MODE = decltype(mode_tag)::value, BN = decltype(bn_tag)::value;
-    if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 0>();
-    if constexpr (MODE != DW13 && MODE != DW2) {
-      if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 1>();
-      if (!rc) rc = raise_lds_limit<256, BN, 64, 2, 4, 3, 2, MODE, 2>();
-    }
-  };
-  both(std::integral_constant<int, UP>{}, std::integral_constant<int, 256>{});
-  both(std::integral_constant<int, DOWN>{}, std::integral_constant<int, 256>{});
-  both(std::integral_constant<int, BWD_ACT>{}, std::integral_constant<int, kActBN>{});
-  both(std::integral_constant<int, BWD_DX>{}, std::integral_constant<int, 256>{});
-  both(std::integral_constant<int, DW13>{}, std::integral_constant<int, 256>{});
-  both(std::integral_constant<int, DW2>{}, std::integral_constant<int, 256>{});
-  return rc;
+  if (int rc = prepare_rows<UP>()) return rc;
+  if (int rc = prepare_rows<DOWN>()) return rc;
+  if (int rc = prepare_rows<BWD_ACT>()) return rc;
+  if (int rc = prepare_rows<BWD_DX>()) return rc;
+  if (int rc = launch<256, 256, 64, 2, 4, 3, 2, DW13>(MArgs{}, true, nullptr)) return rc;
+  return launch<256, 256, 64, 2, 4, 3, 2, DW2>(MArgs{}, true, nullptr);
 }
-int mfma_bwd_act_partials(int f) { return ceil_div(f, kActBN); }
+// one dg partial per column tile of BWD_ACT
+int mfma_bwd_act_partials(const FfShapes& sh) {
+  MArgs g{};
+  g.R = sh.R; g.E = sh.E; g.N = sh.f; g.K = sh.d;
+  return ceil_div(sh.f, row_tile<BWD_ACT>(g) == 256 ? 256 : 128);
+}
 
 bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 < ((int64_t)1 << 32); }
 
@@ -978,7 +1196,7 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
   g.A0 = (const bf16_t*)xs.base; g.a_perm = xs.perm; g.a_k = xs.k; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = h1; g.C1 = h3; g.C2 = act; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f;
   g.strideB_e = sh.s13; g.R = sh.R;
-  return launch_any_k<256, UP>(g, s);
+  return launch_rows<UP>(g, s);
 }
 
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
@@ -987,7 +1205,7 @@ int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShape
   g.A0 = (const bf16_t*)act; g.B0 = (const bf16_t*)W2; g.C0 = y; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d;
   g.strideB_e = sh.s2; g.R = sh.R;
-  return launch_any_k<256, DOWN>(g, s);
+  return launch_rows<DOWN>(g, s);
 }
 
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
@@ -998,10 +1216,10 @@ int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const voi
   g.B0 = (const bf16_t*)W2; g.C0 = dh1; g.C1 = dh3;
   g.T2 = (bf16_t*)gaT; g.ldt = mfma_dw_pitch(sh.R, sh.E);
   g.H1 = (const bf16_t*)h1; g.H3 = (const bf16_t*)h3; g.gates = gates; g.perm = perm; g.dg_part = dg_part;
-  g.n_part = mfma_bwd_act_partials(sh.f);
+  g.n_part = mfma_bwd_act_partials(sh);
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f;
   g.strideB_e = sh.s2; g.R = sh.R;
-  return launch_any_k<kActBN, BWD_ACT>(g, s);
+  return launch_rows<BWD_ACT>(g, s);
 }
 
 int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off,
@@ -1010,7 +1228,7 @@ int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3
   g.A0 = (const bf16_t*)dh1; g.A1 = (const bf16_t*)dh3; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = dxs; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d;
   g.strideB_e = sh.s13; g.R = sh.R;
-  return launch_any_k<256, BWD_DX>(g, s);
+  return launch_rows<BWD_DX>(g, s);
 }
 
 int mfma_dw_pitch(int R, int E) { return (int)align_up((size_t)R, 64) + 64 * E; }
@@ -1022,7 +1240,7 @@ int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh
   g.A0 = (const bf16_t*)xsT; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
   g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
   g.strideC_e = sh.s13; g.R = sh.R; g.c_is_f32 = dW_dtype == BTX_F32;
-  return launch<256, 256, 64, 2, 4, 3, 2, DW13>(g, s);
+  return launch<256, 256, 64, 2, 4, 3, 2, DW13>(g, false, s);
 }
 
 int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t* off, const FfShapes& sh, void* dW2,
@@ -1031,7 +1249,7 @@ int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t*
   h.A0 = (const bf16_t*)gaT; h.B0 = (const bf16_t*)dysT; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
-  return launch<256, 256, 64, 2, 4, 3, 2, DW2>(h, s);
+  return launch<256, 256, 64, 2, 4, 3, 2, DW2>(h, false, s);
 }
 
 }  // namespace btx

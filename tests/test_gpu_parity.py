@@ -316,6 +316,22 @@ def test_bf16_last_round_cut_along_k(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [
+    # 64-row tiles: single rows, K slices of the down-projection / of both input-gradient passes / of the up-projection
+    (1, 264, 200, 4, 2, {}), (33, 72, 2056, 4, 2, {}), (40, 2056, 72, 5, 2, {}), (128, 1024, 64, 4, 1, {}),
+    # 128-row tiles, an expert with two of them, dropped pairs
+    (200, 136, 1096, 4, 2, {}), (220, 1032, 128, 4, 2, dict(bias=[2.0, 0, 0, 0])), (210, 320, 520, 4, 2, dict(cf=0.8, poison=True)),
+    # 192-row tiles, groups on both sides of 192 rows
+    (1120, 520, 392, 64, 8, {}), (1280, 512, 400, 64, 8, {}),
+    # 256-row tiles with every form of the last k tile
+    (1600, 520, 544, 64, 8, {}), (1700, 544, 576, 64, 8, {}),
+    # few 256-row tiles: 128 or 64 rows in their place
+    (600, 512, 176, 4, 2, {}), (700, 64, 1376, 3, 2, {}),
+])
+def test_bf16_row_tiles(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, **kw)
+
+
 def test_bf16_unrelated_experts_meet_the_plain_bar_on_router_gradients():
     """With experts that share nothing the gate Jacobian has no cancellation and
     dW_router / db_router must meet 2e-2 without any amplification factor."""
