@@ -2,7 +2,7 @@
 // the stable grouping of (token, slot) pairs by expert (Sec. 3.2 router and Top-k;
 // Sec. 3.3 load balancing, Switch and sample-top-1 routing).
 //
-// Four launches, no atomics, no host round trip:
+// Two launches for few tokens (see there), else four; no atomics, no host round trip:
 //   (optional) the RMS normalisation in front of the sublayer (the seed model's blocks
 //   normalise before their feed-forward, Sec. 4.1) is folded into route_tokens: the raw rows
 //   are read once more for their mean square (fp64), the normalised, rounded rows are written
@@ -110,6 +110,271 @@ template <> struct Raw8<float> {
   __device__ __forceinline__ float get(int i) const { return i < 4 ? a[i] : b[i - 4]; }
 };
 
+// Softmax, expert selection and gates of token t by one wavefront; lane e owns expert e, s is its logit.  What the
+// token adds to expert e's statistics is added to lane e's psum, gsum and cnt.
+__device__ __forceinline__ void select_experts(float s, bool live, int lane, int t, int E, int k, int mode, float inv_tau,
+                                               const float* __restrict__ U, int32_t* __restrict__ topk_idx,
+                                               float* __restrict__ gates, float* __restrict__ probs, float& psum,
+                                               float& gsum, int& cnt) {
+  const float smax = wave_max(s);
+  const float z = live ? __expf(s - smax) : 0.f;
+  const float zsum = wave_sum(z);
+  const float p = z / zsum;
+  if (live) probs[(size_t)t * E + lane] = p;
+  psum += p;
+  if (mode == BTX_ROUTE_TOPK_RENORM) {
+    float cand = s;
+    int my_slot = -1;
+    for (int j = 0; j < k; ++j) {
+      const Best b = wave_best(Best{cand, lane});
+      if (lane == b.i) { my_slot = j; cand = -INFINITY; }
+    }
+    const float zsel = wave_sum(my_slot >= 0 ? z : 0.f);
+    if (my_slot >= 0) {
+      const float g = z / zsel;
+      topk_idx[(size_t)t * k + my_slot] = lane;
+      gates[(size_t)t * k + my_slot] = g;
+      gsum += g;
+      cnt += 1;
+    }
+    return;
+  }
+  int chosen;
+  float g = p;
+  if (mode == BTX_ROUTE_SWITCH_TOP1) {
+    chosen = wave_best(Best{s, lane}).i;
+  } else if (mode == BTX_ROUTE_GUMBEL_TOP1) {
+    // soft sample softmax((logits + noise) / tau); its largest entry is 1 / sum of the
+    // others' ratios to it, and that entry alone is kept
+    const float noisy = live ? s + U[(size_t)t * E + lane] : -INFINITY;
+    const Best b = wave_best(Best{noisy, lane});
+    chosen = b.i;
+    g = 1.f / wave_sum(live ? __expf((noisy - b.v) * inv_tau) : 0.f);
+  } else {
+    const float c = wave_incl_scan(p, lane);
+    const unsigned long long m = __ballot(live && c > U[t]);
+    chosen = m ? (__ffsll((long long)m) - 1) : (E - 1);
+  }
+  if (lane == chosen) {
+    topk_idx[t] = lane;
+    gates[t] = g;
+    gsum += g;
+    cnt += 1;
+  }
+}
+
+// ---- few tokens: two launches ----------------------------------------------------------------------------------
+// A decoding step or a prompt is latency: the kernels below gave it one wavefront per 4 tokens, which walked its rows
+// twice, and three more launches (16 tokens of 4096 columns with the normalisation: 66 us).  Here every token has a
+// workgroup whose threads share its columns and read W_router as it lies, and one workgroup does the grouping:
+// 16 tokens of 4096 columns with the normalisation 16 us, 301 tokens 21, 512 tokens 25.  The one workgroup takes over
+// from there: 1024 tokens of 256 to 1024 columns 31 to 37 us, against 28 to 34 with the four launches.
+constexpr int kSmallTokens = 512, kSmallPairs = 4096;
+constexpr int64_t kSmallTraffic = (int64_t)1 << 25;     // T * d * E: every token reads the whole W_router (128 MB in all)
+constexpr int kSmallThreads = 256, kGroupThreads = 1024;
+
+template <typename XT, int EC, bool NORM>
+__global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
+    const XT* __restrict__ x, const float* __restrict__ Wr, const float* __restrict__ br, const float* __restrict__ U,
+    int d, int E, int k, int mode, float inv_tau, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
+    float* __restrict__ probs, const float* __restrict__ gain, float eps, XT* __restrict__ xn,
+    float* __restrict__ rstd_out) {
+  typedef f32x4 __attribute__((aligned(4))) f32x4_any;  // W_router need only be aligned to its elements
+  __shared__ float s_part[kSmallThreads / kWave][kMaxExperts];
+  __shared__ double s_ss[kSmallThreads / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, t = blockIdx.x;
+  const XT* row = x + (size_t)t * d;
+  double rs = 0.0;
+  if (NORM) {                                           // in fp64, for the reason given at route_tokens_kernel
+    double ss = 0.0;
+    for (int c0 = threadIdx.x * 8; c0 < d; c0 += kSmallThreads * 8) {
+      float v[8];
+      RowVec<XT, 8>::ld(row + c0, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss += (double)v[i] * (double)v[i];
+    }
+    ss = wave_sum_f64(ss);
+    if (lane == 0) s_ss[wave] = ss;
+    __syncthreads();
+    rs = 1.0 / sqrt(((s_ss[0] + s_ss[1]) + (s_ss[2] + s_ss[3])) / (double)d + (double)eps);
+    if (threadIdx.x == 0) rstd_out[t] = (float)rs;
+  }
+  for (int e0 = 0; e0 < E; e0 += EC) {
+    float acc[EC] = {};
+    for (int c0 = threadIdx.x * 8; c0 < d; c0 += kSmallThreads * 8) {
+      const float* w0 = Wr + (size_t)c0 * E + e0;
+      float xv[8], w[8][EC];
+      RowVec<XT, 8>::ld(row + c0, xv);
+      if (EC % 4 == 0 && e0 + EC <= E) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < EC; j += 4) {
+            const f32x4_any q = *reinterpret_cast<const f32x4_any*>(w0 + (size_t)i * E + j);
+#pragma unroll
+            for (int y = 0; y < 4 && j + y < EC; ++y) w[i][j + y] = q[y];
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < EC; ++j) w[i][j] = e0 + j < E ? w0[(size_t)i * E + j] : 0.f;
+      }
+      if (NORM) {
+        float gv[8];
+        RowVec<float, 8>::ld(gain + c0, gv);
+        XT h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] = NormRound<XT>::rnd((double)xv[i] * rs * (double)gv[i], xv[i]);
+        if (e0 == 0) NormRound<XT>::st8(xn + (size_t)t * d + c0, h);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < EC; ++j) acc[j] = fmaf(xv[i], w[i][j], acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < EC; ++j) {
+      const float sum = wave_sum(acc[j]);
+      if (lane == 0 && e0 + j < E) s_part[wave][e0 + j] = sum;
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const bool live = lane < E;
+  float s = -INFINITY, psum = 0.f, gsum = 0.f;
+  int cnt = 0;
+  if (live) s = ((s_part[0][lane] + s_part[1][lane]) + (s_part[2][lane] + s_part[3][lane])) + (br ? br[lane] : 0.f);
+  select_experts(s, live, lane, t, E, k, mode, inv_tau, U, topk_idx, gates, probs, psum, gsum, cnt);
+}
+
+// One workgroup: statistics, offsets and lb_loss, and the stable grouping of the pairs.  The rank of a pair among its
+// expert's comes from ballots, 1024 pairs a round; it waits in inv_pos until the offsets are known.  A slot that no
+// expert was written to (rows with NaN logits leave such slots) is nobody's pair and gets row 0.
+__global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
+    int T, int E, int k, int cap, int lb_mode, float lb_alpha, const int32_t* __restrict__ topk_idx,
+    const float* __restrict__ gates, const float* __restrict__ probs, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_pos,
+    float* __restrict__ gate_sum, float* __restrict__ prob_sum, float* __restrict__ lb_loss) {
+  constexpr int kWaves = kGroupThreads / kWave, kDense = 8192;
+  __shared__ int s_cnt[kWaves][kMaxExperts], s_first[kMaxExperts], s_kept;
+  __shared__ float s_dense[kDense], s_sum[2][kWaves][kMaxExperts];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, R = T * k;
+
+  // ---- gate and probability sums: thread (expert lane, group wave) adds every kWaves-th token, groups in order.  The
+  // gates are laid out [token][expert] first, as many tokens at a time as the LDS piece holds.
+  float g = 0.f, p = 0.f;
+  const int span = min(T, kDense / E);
+  for (int t0 = 0; t0 < T; t0 += span) {
+    const int n = min(span, T - t0);
+    for (int i = threadIdx.x; i < n * E; i += kGroupThreads) s_dense[i] = 0.f;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n * k; i += kGroupThreads) {
+      const int e = topk_idx[t0 * k + i];
+      if ((unsigned)e < (unsigned)E) s_dense[(i / k) * E + e] = gates[t0 * k + i];
+    }
+    __syncthreads();
+    if (lane < E)
+      for (int q = wave; q < n; q += kWaves) {
+        g += s_dense[q * E + lane];
+        p += probs[(size_t)(t0 + q) * E + lane];
+      }
+    __syncthreads();
+  }
+  s_sum[0][wave][lane] = g;
+  s_sum[1][wave][lane] = p;
+
+  // ---- ranks
+  int running = 0;                                      // wavefront 0, lane e: pairs of expert e so far
+  for (int i0 = 0; i0 < R; i0 += kGroupThreads) {
+    const int i = i0 + threadIdx.x, idx = i < R ? topk_idx[i] : -1, e = (unsigned)idx < (unsigned)E ? idx : -1;
+    int local = 0, mine = 0;
+    for (int q = 0; q < E; ++q) {
+      const unsigned long long m = __ballot(e == q);
+      if (e == q) local = __popcll(m & ((1ull << lane) - 1ull));
+      if (lane == q) mine = __popcll(m);
+    }
+    s_cnt[wave][lane] = mine;
+    __syncthreads();
+    if (wave == 0) {
+      for (int w = 0; w < kWaves; ++w) {
+        const int c = s_cnt[w][lane];
+        s_cnt[w][lane] = running;
+        running += c;
+      }
+    }
+    __syncthreads();
+    if (e >= 0) inv_pos[i] = s_cnt[wave][e] + local;
+    __syncthreads();
+  }
+
+  // ---- what every expert ends with
+  if (wave == 0) {
+    const int kept = cap > 0 ? min(running, cap) : running;
+    const int incl = wave_incl_scan_i32(kept, lane);
+    float gs = 0.f, ps = 0.f, term = 0.f;
+    for (int w = 0; w < kWaves; ++w) { gs += s_sum[0][w][lane]; ps += s_sum[1][w][lane]; }
+    s_first[lane] = incl - kept;
+    if (lane == kWave - 1) { s_kept = incl; offsets[E] = incl; }
+    if (lane < E) {
+      counts[lane] = running;
+      offsets[lane] = incl - kept;
+      gate_sum[lane] = gs;
+      prob_sum[lane] = ps;
+      const float u = lb_mode == BTX_LB_TOKEN_FRAC ? (float)running / ((float)T * (float)k) : gs / (float)T;
+      term = u * (ps / (float)T);
+    }
+    float loss = 0.f;
+    for (int e = 0; e < E; ++e) loss += __shfl(term, e, kWave);   // expert order
+    if (lane == 0) *lb_loss = lb_alpha * (float)E * loss;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < R; i += kGroupThreads) {          // the thread that left the rank reads it back
+    const int e = topk_idx[i];
+    const bool known = (unsigned)e < (unsigned)E;
+    const int rank = known ? inv_pos[i] : 0;
+    if (cap > 0 && rank >= cap) {
+      inv_pos[i] = -1;                                  // beyond the expert's capacity: dropped
+    } else {
+      const int pos = known ? s_first[e] + rank : 0;
+      perm[pos] = i;
+      inv_pos[i] = pos;
+    }
+  }
+  for (int r = s_kept + threadIdx.x; r < R; r += kGroupThreads) perm[r] = 0;   // no such rows: any valid pair
+}
+
+bool route_is_small(const RouteArgs& a) {
+  return a.T <= kSmallTokens && (int64_t)a.T * a.k <= kSmallPairs && (int64_t)a.T * a.d * a.E <= kSmallTraffic;
+}
+
+int launch_route_small(const RouteArgs& a, hipStream_t s) {
+  auto tokens = [&](auto tag, auto ec, auto norm) {
+    using XT = decltype(tag);
+    route_small_tokens_kernel<XT, decltype(ec)::value, decltype(norm)::value><<<a.T, kSmallThreads, 0, s>>>(
+        static_cast<const XT*>(a.x), a.W_router, a.b_router, a.U, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx,
+        a.gates, a.probs, a.gain, a.eps, static_cast<XT*>(a.xn), a.rstd);
+  };
+  auto by_experts = [&](auto tag, auto norm) {
+    if (a.E <= 2) tokens(tag, std::integral_constant<int, 2>{}, norm);
+    else if (a.E <= 4) tokens(tag, std::integral_constant<int, 4>{}, norm);
+    else tokens(tag, std::integral_constant<int, 8>{}, norm);
+  };
+  auto by_norm = [&](auto tag) {
+    if (a.gain) by_experts(tag, std::true_type{});
+    else by_experts(tag, std::false_type{});
+  };
+  if (a.x_dtype == BTX_BF16) by_norm(bf16_t{});
+  else by_norm(float{});
+  BTX_LAUNCH_CHECK();
+  route_small_group_kernel<<<1, kGroupThreads, 0, s>>>(a.T, a.E, a.k, a.cap, a.lb_mode, a.lb_alpha, a.topk_idx, a.gates,
+                                                       a.probs, a.counts, a.offsets, a.perm, a.inv_pos, a.gate_sum,
+                                                       a.prob_sum, a.lb_loss);
+  BTX_LAUNCH_CHECK();
+  return BTX_OK;
+}
+
+// ---- many tokens ---------------------------------------------------------------------------------------------
 // EC experts are accumulated per pass over the row; kTokPerWave tokens share each
 // load of the (transposed) W_router.
 template <typename XT, int EC, bool NORM, int MG = 1, int NS = 1>
@@ -298,51 +563,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
       const int t = t0 + q;
       if (t >= T) break;  // uniform across the wave
       const float s = live ? s_logit[wave][q][lane] + (br ? br[lane] : 0.f) : -INFINITY;
-      const float smax = wave_max(s);
-      const float z = live ? __expf(s - smax) : 0.f;
-      const float zsum = wave_sum(z);
-      const float p = z / zsum;
-      if (live) probs[(size_t)t * E + lane] = p;
-      psum += p;
-      if (mode == BTX_ROUTE_TOPK_RENORM) {
-        float cand = s;
-        int my_slot = -1;
-        for (int j = 0; j < k; ++j) {
-          const Best b = wave_best(Best{cand, lane});
-          if (lane == b.i) { my_slot = j; cand = -INFINITY; }
-        }
-        const float zsel = wave_sum(my_slot >= 0 ? z : 0.f);
-        if (my_slot >= 0) {
-          const float g = z / zsel;
-          topk_idx[(size_t)t * k + my_slot] = lane;
-          gates[(size_t)t * k + my_slot] = g;
-          gsum += g;
-          cnt += 1;
-        }
-      } else {
-        int chosen;
-        float g = p;
-        if (mode == BTX_ROUTE_SWITCH_TOP1) {
-          chosen = wave_best(Best{s, lane}).i;
-        } else if (mode == BTX_ROUTE_GUMBEL_TOP1) {
-          // soft sample softmax((logits + noise) / tau); its largest entry is 1 / sum of the
-          // others' ratios to it, and that entry alone is kept
-          const float noisy = live ? s + U[(size_t)t * E + lane] : -INFINITY;
-          const Best b = wave_best(Best{noisy, lane});
-          chosen = b.i;
-          g = 1.f / wave_sum(live ? __expf((noisy - b.v) * inv_tau) : 0.f);
-        } else {
-          const float c = wave_incl_scan(p, lane);
-          const unsigned long long m = __ballot(live && c > U[t]);
-          chosen = m ? (__ffsll((long long)m) - 1) : (E - 1);
-        }
-        if (lane == chosen) {
-          topk_idx[t] = lane;
-          gates[t] = g;
-          gsum += g;
-          cnt += 1;
-        }
-      }
+      select_experts(s, live, lane, t, E, k, mode, inv_tau, U, topk_idx, gates, probs, psum, gsum, cnt);
     }
     s_stat[wave][0][lane] = __int_as_float(cnt);
     s_stat[wave][1][lane] = gsum;
@@ -565,6 +786,7 @@ size_t route_workspace_bytes(int T, int d, int E, int /*k*/) {
 }
 
 int launch_route(const RouteArgs& a, hipStream_t s) {
+  if (route_is_small(a)) return launch_route_small(a, s);
   const int nblk = num_blocks(a.T);
   const size_t n = (size_t)nblk * a.E;
   int32_t* bc = static_cast<int32_t*>(a.workspace);

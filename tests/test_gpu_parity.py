@@ -332,6 +332,29 @@ def test_bf16_row_tiles(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, **kw)
 
 
+@pytest.mark.parametrize("T,d,E,k,kw", [
+    # both sides of the limits of the two-launch routing: tokens, pairs, tokens x columns x experts
+    (512, 64, 8, 8, {}), (513, 64, 8, 2, {}), (512, 72, 9, 8, dict(cf=0.8)), (456, 64, 9, 9, {}), (512, 1024, 64, 3, {}),
+    (512, 1032, 64, 3, {}), (1, 4104, 5, 3, {}), (17, 2056, 3, 1, dict(mode=B.BTX_ROUTE_SWITCH_TOP1, cf=1.5)),
+    (500, 64, 1, 1, dict(mode=B.BTX_ROUTE_SAMPLE_TOP1)), (499, 136, 33, 1, dict(mode=B.BTX_ROUTE_GUMBEL_TOP1)),
+])
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
+    run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
+
+
+@pytest.mark.parametrize("E", [2, 4, 8, 12])
+def test_routing_takes_a_router_matrix_at_any_float(E):
+    T, d, k = 50, 264, 2
+    L = synth.make_layer(T, d, 64, E, dtype=BF16, device="cuda", unit_rms=True)
+    shifted = torch.empty(d * E + 1, device="cuda")[1:].view(d, E).copy_(L["W_router"])
+    a, b = (B.btx_moe_route(L["x"], W, None, None, k, B.BTX_ROUTE_TOPK_RENORM, B.BTX_LB_TOKEN_FRAC, 0.01)
+            for W in (L["W_router"], shifted))
+    for x, y in zip(vars(a).values(), vars(b).values()):
+        if torch.is_tensor(x):
+            assert torch.equal(x, y)
+
+
 def test_bf16_unrelated_experts_meet_the_plain_bar_on_router_gradients():
     """With experts that share nothing the gate Jacobian has no cancellation and
     dW_router / db_router must meet 2e-2 without any amplification factor."""
