@@ -7,6 +7,8 @@
 // once.  A workgroup owns kNormTok consecutive tokens and all d columns, 4 tokens in flight; the
 // row sums are reduced through LDS in a fixed order, the column sums leave as one partial row
 // per workgroup and a second kernel adds those in a fixed order: no atomics.
+#include <type_traits>
+
 #include "common.h"
 
 namespace btx {
@@ -15,25 +17,34 @@ namespace {
 constexpr int kNormTok = 16;     // tokens per workgroup
 constexpr int kNormThreads = 256;
 
-// MAXC: 8-column chunks a thread owns (d <= MAXC * 2048); its column sums stay in registers
-template <typename XT, int MAXC>
+// MAXC: 8-column chunks a thread owns (d <= MAXC * 2048); its column sums stay in registers.
+// GROUPS: groups of kNormThreads threads that share the workgroup's tokens, 4 at a time each; their column sums are
+// added in group order.  1 while the workgroups alone fill the chip, 4 with fewer than kFewBlocks of them (4001 tokens
+// of 2048 columns: 43 -> 22 us).
+constexpr int kFewBlocks = 512;
+template <typename XT, int MAXC, int GROUPS>
 // dH may be the same buffer as dXn or dres (every thread writes only the chunks it has read, and a
 // row is written after its row sum is complete): those three carry no __restrict__.
-__global__ __launch_bounds__(kNormThreads) void rmsnorm_bwd_kernel(const XT* dXn, const XT* __restrict__ h,
+__global__ __launch_bounds__(kNormThreads* GROUPS) void rmsnorm_bwd_kernel(const XT* dXn, const XT* __restrict__ h,
                                                                    const float* __restrict__ gain,
                                                                    const float* __restrict__ rstd, const XT* dres, int T,
                                                                    int d, XT* dH, float* __restrict__ part) {
-  __shared__ float s_part[kNormThreads / kWave][4];
-  __shared__ float s_coef[4];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  constexpr int kGroupWaves = kNormThreads / kWave;
+  __shared__ float s_part[GROUPS][kGroupWaves][4];
+  __shared__ float s_coef[GROUPS][4];
+  __shared__ float s_cols[GROUPS > 1 ? GROUPS - 1 : 1][GROUPS > 1 ? kNormThreads : 1][8];
+  const int grp = threadIdx.x / kNormThreads, tid = threadIdx.x % kNormThreads;
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int t0 = blockIdx.x * kNormTok;
   float gacc[MAXC][8] = {};
-  for (int tq = 0; tq < kNormTok && t0 + tq < T; tq += 4) {
+  // the barriers inside are met by every group: one whose tokens lie past T works on clamped rows and drops them
+  for (int tq0 = 0; tq0 < kNormTok && t0 + tq0 < T; tq0 += 4 * GROUPS) {
+    const int tq = tq0 + 4 * grp;
     // ---- pass 1: S[q] = sum_c gain_c dXn[t,c] h[t,c]
     float sq[4] = {};
 #pragma unroll
     for (int m = 0; m < MAXC; ++m) {
-      const int c0 = (m * kNormThreads + threadIdx.x) * 8;
+      const int c0 = (m * kNormThreads + tid) * 8;
       if (c0 < d) {
         float gv[8];
         RowVec<float, 8>::ld(gain + c0, gv);
@@ -51,21 +62,21 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_bwd_kernel(const XT* dXn
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float s = wave_sum(sq[q]);
-      if (lane == 0) s_part[wave][q] = s;
+      if (lane == 0) s_part[grp][wave][q] = s;
     }
     __syncthreads();
-    if (threadIdx.x < 4) {
+    if (tid < 4) {
       float s = 0.f;
 #pragma unroll
-      for (int w = 0; w < kNormThreads / kWave; ++w) s += s_part[w][threadIdx.x];
-      const float r = rstd[min(t0 + tq + (int)threadIdx.x, T - 1)];
-      s_coef[threadIdx.x] = r * r * r * s / (float)d;
+      for (int w = 0; w < kGroupWaves; ++w) s += s_part[grp][w][tid];
+      const float r = rstd[min(t0 + tq + tid, T - 1)];
+      s_coef[grp][tid] = r * r * r * s / (float)d;
     }
     __syncthreads();
     // ---- pass 2: dH and the column sums
 #pragma unroll
     for (int m = 0; m < MAXC; ++m) {
-      const int c0 = (m * kNormThreads + threadIdx.x) * 8;
+      const int c0 = (m * kNormThreads + tid) * 8;
       if (c0 < d) {
         float gv[8];
         RowVec<float, 8>::ld(gain + c0, gv);
@@ -74,7 +85,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_bwd_kernel(const XT* dXn
           const int t = t0 + tq + q;
           if (t < T) {
             const size_t row = (size_t)t * d + c0;
-            const float r = rstd[t], coef = s_coef[q];
+            const float r = rstd[t], coef = s_coef[grp][q];
             float a[8], b[8], o[8];
             RowVec<XT, 8>::ld(dXn + row, a);
             RowVec<XT, 8>::ld(h + row, b);
@@ -98,8 +109,22 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_bwd_kernel(const XT* dXn
   }
 #pragma unroll
   for (int m = 0; m < MAXC; ++m) {
-    const int c0 = (m * kNormThreads + threadIdx.x) * 8;
-    if (c0 < d) RowVec<float, 8>::st(part + (size_t)blockIdx.x * d + c0, gacc[m]);
+    const int c0 = (m * kNormThreads + tid) * 8;
+    if constexpr (GROUPS > 1) {
+      if (grp > 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_cols[grp - 1][tid][i] = gacc[m][i];
+      }
+      __syncthreads();
+      if (grp == 0) {
+#pragma unroll
+        for (int g = 0; g < GROUPS - 1; ++g)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) gacc[m][i] += s_cols[g][tid][i];
+      }
+      __syncthreads();
+    }
+    if (grp == 0 && c0 < d) RowVec<float, 8>::st(part + (size_t)blockIdx.x * d + c0, gacc[m]);
   }
 }
 
@@ -125,16 +150,21 @@ template <typename XT>
 int launch_typed(const void* dXn, const void* h, const float* gain, const float* rstd, const void* dres, int T, int d,
                  void* dH, float* part, hipStream_t s) {
   const int nblk = ceil_div(T, kNormTok);
-#define BTX_NORM_LAUNCH(MAXC)                                                                                      \
-  rmsnorm_bwd_kernel<XT, MAXC><<<nblk, kNormThreads, 0, s>>>(static_cast<const XT*>(dXn), static_cast<const XT*>(h), \
-                                                             gain, rstd, static_cast<const XT*>(dres), T, d,         \
-                                                             static_cast<XT*>(dH), part)
-  if (d <= 2048) BTX_NORM_LAUNCH(1);
-  else if (d <= 4096) BTX_NORM_LAUNCH(2);
-  else if (d <= 8192) BTX_NORM_LAUNCH(4);
-  else if (d <= 16384) BTX_NORM_LAUNCH(8);
+  auto run = [&](auto maxc, auto groups) {
+    constexpr int G = decltype(groups)::value;
+    rmsnorm_bwd_kernel<XT, decltype(maxc)::value, G><<<nblk, kNormThreads * G, 0, s>>>(
+        static_cast<const XT*>(dXn), static_cast<const XT*>(h), gain, rstd, static_cast<const XT*>(dres), T, d,
+        static_cast<XT*>(dH), part);
+  };
+  auto by_blocks = [&](auto maxc) {
+    if (nblk < kFewBlocks) run(maxc, std::integral_constant<int, 4>{});
+    else run(maxc, std::integral_constant<int, 1>{});
+  };
+  if (d <= 2048) by_blocks(std::integral_constant<int, 1>{});
+  else if (d <= 4096) by_blocks(std::integral_constant<int, 2>{});
+  else if (d <= 8192) by_blocks(std::integral_constant<int, 4>{});
+  else if (d <= 16384) run(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{});
   else return BTX_ERR_UNSUPPORTED;
-#undef BTX_NORM_LAUNCH
   BTX_LAUNCH_CHECK();
   return BTX_OK;
 }

@@ -10,7 +10,7 @@
 //   0. transpose_wr   W_router [d,E] -> [E,d] in the workspace: a lane then reads its 8 columns of
 //                     an expert as 32 contiguous bytes and a wavefront's load covers 2 KB in one
 //                     piece, where the [d,E] form costs one cache line per lane and load.
-//   1. route_tokens   one wavefront handles kTokPerWave tokens at a time: fp32 dot
+//   1. route_tokens   one wavefront handles a few tokens at a time: fp32 dot
 //                     products of the token row with W_router (lanes split the row,
 //                     butterfly reduction; with more than 8 experts fp32 matrix instructions
 //                     on 16 tokens x 16 experts instead), then softmax / selection / gates
@@ -30,9 +30,8 @@
 namespace btx {
 namespace {
 
-constexpr int kTokPerWave = 4;
-constexpr int kWavesPerBlock = 4;
-constexpr int kTokPerBlock = kTokPerWave * kWavesPerBlock;  // 16 consecutive tokens per workgroup
+constexpr int kTokPerBlock = 16;                            // consecutive tokens per workgroup
+constexpr int kWavesPerBlock = 4;                           // of the scatter kernel, and of route_tokens with many tokens
 constexpr int kScanThreads = 1024;
 // blocks of kTokPerBlock tokens per workgroup when the logits run on the matrix cores: they share each
 // load of W_router (1: 130 us, 2: 112 us, 4: 204 us for 16384 tokens x 32 experts; with 4 the launch has
@@ -375,10 +374,14 @@ int launch_route_small(const RouteArgs& a, hipStream_t s) {
 }
 
 // ---- many tokens ---------------------------------------------------------------------------------------------
-// EC experts are accumulated per pass over the row; kTokPerWave tokens share each
+// EC experts are accumulated per pass over the row; the 16 / NW tokens of a wavefront share each
 // load of the (transposed) W_router.
-template <typename XT, int EC, bool NORM, int MG = 1, int NS = 1>
-__global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
+// NW: wavefronts of a workgroup.  4 while the workgroups alone fill the chip; with fewer than kFewBlocks of them every
+// row's latency shows and 16 (8 with the matrix cores, whose partial sums take LDS) split the same 16 tokens: 4001
+// tokens of 2048 columns with the normalisation, 8 experts: 33 -> 24 us; 1501 tokens, 64 experts: 62 -> 49 us.
+constexpr int kFewBlocks = 512;
+template <typename XT, int EC, bool NORM, int NW, int MG = 1, int NS = 1>
+__global__ __launch_bounds__(NW* kWave) void route_tokens_kernel(
     const XT* __restrict__ x, const float* __restrict__ WrT, const float* __restrict__ br,
     const float* __restrict__ U, int T, int d, int E, int k, int mode, float inv_tau, int32_t* __restrict__ topk_idx,
     float* __restrict__ gates, float* __restrict__ probs, int32_t* __restrict__ blk_counts,
@@ -389,8 +392,9 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
   // the matrix variant covers G blocks of kTokPerBlock tokens per workgroup (they share every load of
   // W_router); the statistics stay per block of kTokPerBlock tokens either way
   constexpr int G = MATRIX ? MG : 1;
-  __shared__ float s_logit[kWavesPerBlock][kTokPerWave][kMaxExperts];
-  __shared__ float s_stat[kWavesPerBlock][3][kMaxExperts];
+  constexpr int kTokPerWave = kTokPerBlock / NW;
+  __shared__ float s_logit[NW][kTokPerWave][kMaxExperts];
+  __shared__ float s_stat[NW][3][kMaxExperts];
   extern __shared__ float s_part[];                     // MATRIX: [wavefront][G * kTokPerBlock tokens][16 NS experts]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
   // ---- logits -------------------------------------------------------------
   if constexpr (MATRIX) {
     // fp32 16x16x4 matrix products: the workgroup's 16 tokens are the rows, 16 experts at a time the
-    // columns; wavefront w takes the 32-column pieces w, w + 4, ... of the rows and the four partial
+    // columns; wavefront w takes the 32-column pieces w, w + NW, ... of the rows and the NW partial
     // sums are added in that order below.  A lane supplies A[token = lane % 16][k] and
     // B[k][expert = lane % 16] for the 8 columns k = 32 piece + 8 (lane / 16) + i, one product per i,
     // and receives the sums of expert lane % 16 for the tokens 4 (lane / 16) + v.
@@ -440,7 +444,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
     // the lanes of the experts past E read expert E - 1; their sums are never looked at
 #pragma unroll
     for (int u = 0; u < NS; ++u) wrow[u] = WrT + (size_t)min(u * 16 + row, E - 1) * d;
-    // Trip `it` of this wavefront covers columns 32 (wave + 4 it) ... + 31.  The loads of kAhead trips are
+    // Trip `it` of this wavefront covers columns 32 (wave + NW it) ... + 31.  The loads of kAhead trips are
     // in flight ahead of the products, and nothing in the loop is conditional (the matrix instructions
     // take all 64 lanes, and a branch would make the compiler wait for every load): a trip past the
     // last one repeats the last one's loads, and a lane whose 8 columns lie past the row's end reads the
@@ -448,9 +452,9 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
     constexpr int kAhead = 3;
     struct Piece { Raw8<XT> xr[G]; Raw8<float> wr[NS]; };
     Piece buf[kAhead];
-    const int n_it = max(0, (d - wave * 32 + kWavesPerBlock * 32 - 1) / (kWavesPerBlock * 32));
+    const int n_it = max(0, (d - wave * 32 + NW * 32 - 1) / (NW * 32));
     auto col0 = [&](int it, bool& live) {
-      const int c = (wave + kWavesPerBlock * min(it, max(n_it - 1, 0))) * 32 + kc * 8;
+      const int c = (wave + NW * min(it, max(n_it - 1, 0))) * 32 + kc * 8;
       live = it < n_it && c < d;
       return c < d ? c : 0;
     };
@@ -551,7 +555,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
         const int tok = g * kTokPerBlock + wave * kTokPerWave + q;
         float sum = s_part[tok * pitch + lane];
 #pragma unroll
-        for (int w = 1; w < kWavesPerBlock; ++w) sum += s_part[(w * G * kTokPerBlock + tok) * pitch + lane];
+        for (int w = 1; w < NW; ++w) sum += s_part[(w * G * kTokPerBlock + tok) * pitch + lane];
         s_logit[wave][q][lane] = sum;                     // read back by this lane only
       }
     }
@@ -574,7 +578,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_tokens_kernel(
       int c = 0;
       float gs = 0.f, p = 0.f;
 #pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) {
+      for (int w = 0; w < NW; ++w) {
         c += __float_as_int(s_stat[w][0][e]);
         gs += s_stat[w][1][e];
         p += s_stat[w][2][e];
@@ -728,15 +732,16 @@ __global__ __launch_bounds__(256) void transpose_wr_kernel(const float* __restri
 template <typename XT>
 void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, float* bg, float* bp, hipStream_t s) {
   const XT* x = static_cast<const XT*>(a.x);
-  dim3 grid(nblk), block(kWavesPerBlock * kWave);
-#define BTX_ROUTE_LAUNCH(EC)                                                                                       \
+  const bool few = nblk < kFewBlocks;
+#define BTX_ROUTE_LAUNCH(EC) do { if (few) BTX_ROUTE_LAUNCH_NW(EC, 16); else BTX_ROUTE_LAUNCH_NW(EC, kWavesPerBlock); } while (0)
+#define BTX_ROUTE_LAUNCH_NW(EC, NW)                                                                                \
   do {                                                                                                             \
     if (a.gain)                                                                                                    \
-      route_tokens_kernel<XT, EC, true><<<grid, block, 0, s>>>(                                                    \
+      route_tokens_kernel<XT, EC, true, NW><<<nblk, NW * kWave, 0, s>>>(                                                    \
           x, WrT, a.b_router, a.U, a.T, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx, a.gates, a.probs, bc,  \
           bg, bp, a.gain, a.eps, static_cast<XT*>(a.xn), a.rstd);                                                   \
     else                                                                                                           \
-      route_tokens_kernel<XT, EC, false><<<grid, block, 0, s>>>(                                                   \
+      route_tokens_kernel<XT, EC, false, NW><<<nblk, NW * kWave, 0, s>>>(                                                \
           x, WrT, a.b_router, a.U, a.T, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx, a.gates, a.probs, bc,  \
           bg, bp, nullptr, 0.f, nullptr, nullptr);                                                                  \
   } while (0)
@@ -744,19 +749,22 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
     // many experts: the dot products go to the matrix cores (fp32 16x16x4, 1024 multiply-adds per
     // instruction).  On the vector unit they took 172 us for 16384 tokens x 32 experts (64 M vector
     // instructions); the kernel now takes 85 us
-    auto go = [&](auto mg, auto ns) {
-      constexpr int MG = decltype(mg)::value, NS = decltype(ns)::value;
-      const size_t lds = (size_t)kWavesPerBlock * MG * kTokPerBlock * 16 * NS * sizeof(float);
-      route_tokens_kernel<XT, 0, false, MG, NS><<<ceil_div(nblk, MG), block, lds, s>>>(
+    auto go_nw = [&](auto nw, auto mg, auto ns) {
+      constexpr int NW = decltype(nw)::value, MG = decltype(mg)::value, NS = decltype(ns)::value;
+      const size_t lds = (size_t)NW * MG * kTokPerBlock * 16 * NS * sizeof(float);
+      route_tokens_kernel<XT, 0, false, NW, MG, NS><<<ceil_div(nblk, MG), NW * kWave, lds, s>>>(
           x, WrT, a.b_router, a.U, a.T, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx, a.gates, a.probs, bc,
           bg, bp, nullptr, 0.f, nullptr, nullptr);
     };
     using std::integral_constant;
-    const integral_constant<int, kMatrixGroups> mg;
-    if (a.E <= 16) go(mg, integral_constant<int, 1>{});
-    else if (a.E <= 32) go(mg, integral_constant<int, 2>{});
-    else if (a.E <= 48) go(mg, integral_constant<int, 3>{});
-    else go(mg, integral_constant<int, 4>{});
+    auto go = [&](auto ns) {
+      if (few) go_nw(integral_constant<int, 8>{}, integral_constant<int, 1>{}, ns);
+      else go_nw(integral_constant<int, kWavesPerBlock>{}, integral_constant<int, kMatrixGroups>{}, ns);
+    };
+    if (a.E <= 16) go(integral_constant<int, 1>{});
+    else if (a.E <= 32) go(integral_constant<int, 2>{});
+    else if (a.E <= 48) go(integral_constant<int, 3>{});
+    else go(integral_constant<int, 4>{});
     return;
   }
   if (a.E <= 1) BTX_ROUTE_LAUNCH(1);
@@ -764,6 +772,7 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
   else if (a.E <= 4) BTX_ROUTE_LAUNCH(4);
   else BTX_ROUTE_LAUNCH(8);   // 16 per pass was measured no faster at E = 32
 #undef BTX_ROUTE_LAUNCH
+#undef BTX_ROUTE_LAUNCH_NW
 }
 
 }  // namespace

@@ -125,6 +125,73 @@ __global__ __launch_bounds__(256) void dwr_partial_kernel(const XT* __restrict__
   }
 }
 
+// The same sums with the four wavefronts of a workgroup on the same 512 columns and a quarter of the chunk's tokens each,
+// added in wavefront order: four times the rows in flight and four times the workgroups, for batches whose (chunk, column
+// block, expert pass) grid would leave the chip idle (fewer than kFewBlocks: 1501 tokens of 4096 columns, 64 experts 65 ->
+// 27 us; 4001 of 2048, 8 experts 29 -> 12).
+constexpr int kFewBlocks = 512;
+template <typename XT, int KEC, int CHUNK>
+__global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restrict__ x, const float* __restrict__ ds, int T,
+                                                              int d, int E, float* __restrict__ part,
+                                                              float* __restrict__ db_part) {
+  constexpr int kQuarter = CHUNK / 4;
+  __shared__ float s_ds[CHUNK][KEC];
+  __shared__ f32x4 s_acc[KEC * 2][kWave];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int t0 = blockIdx.x * CHUNK, e0 = blockIdx.z * KEC;
+  const int nt = min(CHUNK, T - t0);
+  for (int i = threadIdx.x; i < CHUNK * KEC; i += 256) {
+    const int q = i / KEC, j = i % KEC;
+    s_ds[q][j] = (q < nt && e0 + j < E) ? ds[(size_t)(t0 + q) * E + e0 + j] : 0.f;
+  }
+  __syncthreads();
+  const int c0 = (blockIdx.y * kWave + lane) * kColsPerThread, cc = min(c0, d - kColsPerThread);
+  float acc[KEC][kColsPerThread] = {};
+  for (int q = wave * kQuarter; q < min(nt, (wave + 1) * kQuarter); q += 4) {   // rows past the end meet the zeros of s_ds
+    float xv[4][8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) RowVec<XT, 8>::ld_stream(x + (size_t)min(t0 + q + u, T - 1) * d + cc, xv[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < KEC; ++j) {
+        const float w = s_ds[q + u][j];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[j][i] = fmaf(xv[u][i], w, acc[j][i]);
+      }
+  }
+  for (int w = 1; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int j = 0; j < KEC; ++j) {
+        s_acc[2 * j][lane] = f32x4{acc[j][0], acc[j][1], acc[j][2], acc[j][3]};
+        s_acc[2 * j + 1][lane] = f32x4{acc[j][4], acc[j][5], acc[j][6], acc[j][7]};
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int j = 0; j < KEC; ++j) {
+        const f32x4 a = s_acc[2 * j][lane], b = s_acc[2 * j + 1][lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { acc[j][i] += a[i]; acc[j][4 + i] += b[i]; }
+      }
+    }
+    __syncthreads();
+  }
+  if (wave == 0 && c0 < d) {
+#pragma unroll
+    for (int j = 0; j < KEC; ++j)
+      if (e0 + j < E) RowVec<float, 8>::st(part + ((size_t)blockIdx.x * E + e0 + j) * d + c0, acc[j]);
+  }
+  if (blockIdx.y == 0 && threadIdx.x < KEC && e0 + threadIdx.x < E) {
+    float a = 0.f;
+    for (int q = 0; q < nt; ++q) a += s_ds[q][threadIdx.x];
+    db_part[(size_t)blockIdx.x * E + e0 + threadIdx.x] = a;
+  }
+}
+
 // 64 sums per block, taken in the partials' expert-major order (coalesced reads) and written to
 // dW_router's [d,E] place; 16 thread groups each add every 16th partial, then the 16 sums are
 // added in group order (a fixed order, like everything else here).
@@ -155,9 +222,7 @@ __global__ __launch_bounds__(64 * kRedGroups) void dwr_reduce_kernel(const float
 
 // dX[t] = sum_j dxs[inv_pos[t,j]] + ds[t] W_router^T.  A wavefront owns 512 columns (8 per lane)
 // for TOK tokens, 4 of them in flight at a time; its slice of W_router (read from the [E,d]
-// copy) stays in registers when E <= EC, so the kernel streams dxs and dX and little else.
-// With more experts the slice is reloaded in pieces of EC per 4 tokens (cache hits): 4 columns
-// per lane with the whole slice resident was measured slower (8-byte row loads).
+// copy, E <= EC) stays in registers, so the kernel streams dxs and dX and little else.
 template <typename XT, int EC, int TOK>
 __global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos,
                                                         const float* __restrict__ ds, const float* __restrict__ WrT,
@@ -166,20 +231,16 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ d
   const int c0 = ((blockIdx.y * 4 + wave) * kWave + lane) * 8;
   const int t0 = blockIdx.x * TOK;
   if (c0 >= d) return;                      // no cross-lane traffic below
-  const int n_ch = (E + EC - 1) / EC;
   float wr[EC][8];
-  auto load_wr = [&](int e0) {
 #pragma unroll
-    for (int j = 0; j < EC; ++j) {
-      if (e0 + j < E) {
-        RowVec<float, 8>::ld(WrT + (size_t)(e0 + j) * d + c0, wr[j]);
-      } else {
+  for (int j = 0; j < EC; ++j) {
+    if (j < E) {
+      RowVec<float, 8>::ld(WrT + (size_t)j * d + c0, wr[j]);
+    } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) wr[j][i] = 0.f;
-      }
+      for (int i = 0; i < 8; ++i) wr[j][i] = 0.f;
     }
-  };
-  if (n_ch == 1) load_wr(0);
+  }
   for (int tq = 0; tq < TOK; tq += 4) {
     float acc[4][8] = {};
     // slot by slot, the four tokens' rows in flight together; a dropped pair (or a token past
@@ -200,19 +261,15 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ d
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[q][i] += have[q] ? v[q][i] : 0.f;
     }
-    for (int ch = 0; ch < n_ch; ++ch) {
-      if (n_ch > 1) load_wr(ch * EC);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = t0 + tq + q;
-        if (t >= T) break;
+    for (int q = 0; q < 4; ++q) {
+      const int t = t0 + tq + q;
+      if (t >= T) break;
 #pragma unroll
-        for (int j = 0; j < EC; ++j) {
-          const int e = ch * EC + j;
-          const float w = e < E ? ds[(size_t)t * E + e] : 0.f;
+      for (int j = 0; j < EC; ++j) {
+        const float w = j < E ? ds[(size_t)t * E + j] : 0.f;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) acc[q][i] = fmaf(w, wr[j][i], acc[q][i]);
-        }
+        for (int i = 0; i < 8; ++i) acc[q][i] = fmaf(w, wr[j][i], acc[q][i]);
       }
     }
 #pragma unroll
@@ -221,14 +278,13 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ d
   }
 }
 
-// The same for 9 to 32 experts, where the slice of W_router no longer fits the registers and reloading it
+// The same for more than 8 experts, where the slice of W_router no longer fits the registers and reloading it
 // per 4 tokens (from the caches) cost 110 of the kernel's 337 us at 32 experts: the 8 wavefronts of a
 // workgroup share one slice of kDxCols columns, staged once in LDS ([expert][half][lane] 16-byte
-// pieces, so that consecutive lanes read consecutive pieces), and split the workgroup's tokens, 4 in
-// flight per wavefront.
+// pieces, so that consecutive lanes read consecutive pieces; 128 KB at 64 experts), and split the workgroup's
+// tokens, 4 in flight per wavefront.  1501 tokens of 4096 columns, 64 experts, 8 slots: 152 us reloading, 50 now.
 constexpr int kDxCols = kWave * 8;                      // columns of a workgroup: 8 per lane
 constexpr int kDxWaves = 8;
-constexpr int kDxLdsMaxE = 32;                          // 32 experts x 512 columns x 4 bytes = 64 KB
 template <typename XT>
 __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT* __restrict__ dxs,
                                                                         const int32_t* __restrict__ inv_pos,
@@ -286,7 +342,24 @@ __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT
   }
 }
 
+// More dynamic LDS than the default limit from 33 experts on: raised once per device, which may not happen inside a
+// stream capture (router_bwd_prepare() does it up front); threads racing here store the same value.
+int raise_dx_lds_limit() {
+  static bool done[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BTX_ERR_HIP;
+  if (done[dev]) return BTX_OK;
+  const int bytes = kMaxExperts * kDxCols * (int)sizeof(float);
+  for (const void* kernel : {reinterpret_cast<const void*>(dx_finish_lds_kernel<bf16_t>),
+                             reinterpret_cast<const void*>(dx_finish_lds_kernel<float>)})
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return BTX_ERR_HIP;
+  done[dev] = true;
+  return BTX_OK;
+}
+
 }  // namespace
+
+int router_bwd_prepare() { return raise_dx_lds_limit(); }
 
 // token chunk of the dW_router partial sums: longer chunks for many experts keep the partials
 // (chunks * d * E floats) small next to x
@@ -312,6 +385,8 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
   w += align_up((size_t)nch * a.E * sizeof(float), 256);
   float* WrT = reinterpret_cast<float*>(w);
 
+  if (a.E > 32)
+    if (int rc = raise_dx_lds_limit()) return rc;
   if (int rc = launch_transpose_wr(a.W_router, a.d, a.E, WrT, s)) return rc;
   router_ds_kernel<<<ceil_div(a.T, 4), 256, 0, s>>>(a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
                                                    a.flags, a.noise, a.noise ? 1.f / a.tau : 1.f, a.topk_idx, a.gates,
@@ -322,7 +397,14 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
     using XT = decltype(tag);
     const XT* x = static_cast<const XT*>(a.x);
     const int col_blocks = ceil_div(a.d, 256 * kColsPerThread);
-    if (a.E <= 8)
+    const int few_cols = ceil_div(a.d, kWave * kColsPerThread);
+    const bool few = (int64_t)nch * col_blocks * ceil_div(a.E, a.E <= 8 ? 8 : 16) < kFewBlocks;
+    if (a.E <= 8 && few)
+      dwr_partial_few_kernel<XT, 8, 64><<<dim3(nch, few_cols, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
+    else if (few)
+      dwr_partial_few_kernel<XT, 16, 128><<<dim3(nch, few_cols, ceil_div(a.E, 16)), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part,
+                                                                                               dbp);
+    else if (a.E <= 8)
       dwr_partial_kernel<XT, 8, 64><<<dim3(nch, col_blocks, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
     else
       dwr_partial_kernel<XT, 16, 128><<<dim3(nch, col_blocks, ceil_div(a.E, 16)), 256, 0, s>>>(x, ds, a.T, a.d, a.E,
@@ -342,14 +424,16 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
   dx_finish_kernel<XT, EC, TOK><<<dim3(ceil_div(a.T, TOK), ceil_div(a.d, 4 * kWave * 8)), 256, 0, s>>>(dxs, a.inv_pos, \
                                                                                                       ds, WrT, a.T, a.d, \
                                                                                                       a.E, a.k, dX)
-    if (a.E <= 4) BTX_DX_LAUNCH(4, 16);
-    else if (a.E <= 8) BTX_DX_LAUNCH(8, 16);
-    else if (a.E <= kDxLdsMaxE) {
-      const int tok = 128;                              // tokens per workgroup: the slice is staged once for them
-      dx_finish_lds_kernel<XT><<<dim3(ceil_div(a.T, tok), ceil_div(a.d, kDxCols)), kDxWaves * kWave,
+    const bool few = ceil_div(a.T, 16) * ceil_div(a.d, 4 * kWave * 8) < kFewBlocks;   // then 4 tokens per wavefront, not 16
+    if (a.E <= 4) { if (few) BTX_DX_LAUNCH(4, 4); else BTX_DX_LAUNCH(4, 16); }
+    else if (a.E <= 8) { if (few) BTX_DX_LAUNCH(8, 4); else BTX_DX_LAUNCH(8, 16); }
+    else {
+      // tokens per workgroup, for which the slice is staged once: fewer where the chip would be left idle
+      const int cols = ceil_div(a.d, kDxCols), tok = ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
+      dx_finish_lds_kernel<XT><<<dim3(ceil_div(a.T, tok), cols), kDxWaves * kWave,
                                  (size_t)a.E * kDxCols * sizeof(float), s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k,
                                                                               tok, dX);
-    } else BTX_DX_LAUNCH(16, 32);
+    }
 #undef BTX_DX_LAUNCH
   };
   if (a.dtype == BTX_BF16) dx_launch(bf16_t{});
