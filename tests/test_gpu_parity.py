@@ -681,3 +681,20 @@ def test_adamw_steps_follow_the_oracle(gdtype, n, beta2):
     assert_close(V.cpu().numpy(), vo, 1e-5, "v")
     # working copy: the fp32 result rounded once
     assert torch.equal(low, P.to(BF16))
+
+
+@pytest.mark.parametrize("n", [11184810, 11184813])     # both sides of 128 MB of P, M and V; no multiple of 4
+def test_adamw_past_the_caches_gives_the_same_numbers(n):
+    """The update is elementwise: a tensor must come out as its pieces do."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    P, M = (torch.randn(n, generator=g, device="cuda") for _ in range(2))
+    V = torch.rand(n, generator=g, device="cuda")
+    grad = torch.randn(n, generator=g, device="cuda").to(BF16)
+    whole, low = [t.clone() for t in (P, M, V)], torch.empty(n, dtype=BF16, device="cuda")
+    B.btx_adamw_step(*whole, grad, 3, 1e-3, weight_decay=0.1, lowp=low)
+    for lo in range(0, n, 4000000):
+        piece = [t[lo:lo + 4000000].clone() for t in (P, M, V, grad)]
+        low_p = torch.empty_like(piece[3])
+        B.btx_adamw_step(*piece, 3, 1e-3, weight_decay=0.1, lowp=low_p)
+        for got, want in zip([t[lo:lo + 4000000] for t in (*whole, low)], (*piece[:3], low_p)):
+            assert torch.equal(got, want)
