@@ -72,6 +72,7 @@ struct MArgs {
   int total_ids;                        // tile ids of the launch (a few name no tile: padding of the id space)
   // UP / DOWN / BWD_DX: the tiles of the last, partly filled round are cut along K (see Gemm::split_plan)
   f32x4* partial; int cus;              // fp32 accumulators of the slices (NULL: never cut); compute units
+  int strip;                            // weight-gradient strips: column tiles of a workgroup
   // small tiles: every tile of the launch is cut into `slices` K ranges; slices > 1: fp32 sums in slice_sums,
   // [slice][panel][R][N]
   int slices; float* slice_sums;
@@ -129,13 +130,14 @@ __device__ __forceinline__ u32x4 swap_halves(u32x4 v, bool yes) {
 // Epilogue stores.  STREAM: marked non-temporal, so that the written tile does not push the operand panels
 // that the other compute units are streaming out of the XCD's L2.  Measured per product: BWD_ACT (three
 // tensors out per tile, the lowest L2 hit rate of the six) -5 %, DOWN -0.3 % (-3.7 % with 32 narrow experts);
-// BWD_DX +0.6 % / -2 %, UP and DW13 +1 %: those keep plain stores.
+// BWD_DX +0.6 % / -2 %, UP and DW13 +1 %: those keep plain stores.  DW2: see launch_dw().
 template <bool STREAM, typename V> __device__ __forceinline__ void store_out(V* p, V v) {
   if constexpr (STREAM) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
+          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 struct Gemm {
   // K index contiguous in memory?  A always is.  In the dW products K is the grouped-row index:
   // x (dW1/dW3) and ga, dY (dW2) arrive transposed, [columns][padded rows], every expert's rows
@@ -144,7 +146,6 @@ struct Gemm {
   static constexpr bool B_KC = (MODE != UP && MODE != DOWN && MODE != DW13);
   static constexpr bool DUAL = (MODE == UP || MODE == DW13);
   static constexpr bool GROUP_K = (MODE == DW13 || MODE == DW2);
-  static constexpr bool STREAM_OUT = (MODE == BWD_ACT || MODE == DOWN);
   // 128-column tiles: one pipeline for all wavefronts, two workgroups of four per compute unit; 256: ping-pong
   static constexpr bool SMALL = BN == 128;
   static constexpr int NW = WM * WN, NT = NW * kWave;
@@ -819,8 +820,8 @@ struct Gemm {
           const u32x4 v3 = *reinterpret_cast<const u32x4*>(bufB + o);
           if (mb + r < row_end && cn < g.N) {
             const size_t idx = (size_t)(mb + r) * g.ldc + cn;
-            store_out<STREAM_OUT>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + idx), v1);
-            store_out<STREAM_OUT>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + idx), v3);
+            store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + idx), v1);
+            store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + idx), v3);
           }
         }
         if (g.T2) {
@@ -863,7 +864,7 @@ struct Gemm {
               const bf16x8 w = *reinterpret_cast<const bf16x8*>(bufT + tc * 128 + ((qg ^ ((tc >> 1) & 7)) << 4));
               const int col = wcol0 + tc;
               if (col < g.N && m8 < pad_e)
-                store_out<STREAM_OUT>(reinterpret_cast<bf16x8*>(g.T2 + (size_t)col * g.ldt + kp_begin + m8), w);
+                store_out<STREAM>(reinterpret_cast<bf16x8*>(g.T2 + (size_t)col * g.ldt + kp_begin + m8), w);
             }
           }
         }
@@ -923,7 +924,7 @@ struct Gemm {
               const u32x4 val = swap_halves(
                   *reinterpret_cast<const u32x4*>(wb + pp * (32 * ROWB) + stage_off<ROWB, 4 * ES>(r, cc)),
                   half_flip<ROWB, ES>(r) != 0);
-              if (mb + r < row_end && cn < g.N) store_out<STREAM_OUT>(reinterpret_cast<u32x4*>(C + (size_t)(mb + r) * g.ldc + cn), val);
+              if (mb + r < row_end && cn < g.N) store_out<STREAM>(reinterpret_cast<u32x4*>(C + (size_t)(mb + r) * g.ldc + cn), val);
             }
           }
         }
@@ -960,10 +961,11 @@ struct Gemm {
   }
 };
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
+          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::run(g, smem);
+  Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM>::run(g, smem);
 }
 
 // small tiles: 4 wavefronts, two workgroups per compute unit
@@ -1013,6 +1015,161 @@ __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs 
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>::finish(g);
 }
 
+// Weight gradients of experts with few rows (dW1, dW3 = xs^T dh1, dh3; dW2 = ga^T dys): a contraction of a few k tiles
+// whose result, the size of the weights, has to be written.  With one 256 x 256 tile per workgroup a tile costs its
+// latencies one after another (finding it, the first copies, the products, turning the results around, the stores): 13 us
+// where its 128 KB take 6 to write.  Here a workgroup walks a strip of 128 x 128 tiles along the columns, the k tiles of
+// all of them one sequence: a tile's results are stored while the copies of the next one are in flight, and a second
+// workgroup on the compute unit fills the rest.  4 wavefronts of 64 x 64, two LDS stages of both operands and a staging
+// band per wavefront: 80 KB.  Used where a k tile is all there is (launch_dw()): with three, the two
+// LDS stages leave the copies too little time (188 rows: 356 us against 324).
+template <bool B_KC, typename ET, bool STREAM> struct DwStrip {
+  // for the LDS layouts: both operands K-contiguous (dW2), or B strided (dW1, dW3)
+  using H = Gemm<128, 128, 64, 2, 2, 2, 3, B_KC ? BWD_DX : DOWN>;
+  static constexpr int BT = 128, BK = 64, ES = sizeof(ET), STAGE = BT * BK * 2, BAND = 4096;
+  static constexpr int LDS_BYTES = 4 * STAGE + 4 * BAND;
+  static constexpr int ROWB = 64 * ES, BAND_ROWS = BAND / ROWB, FR = BAND_ROWS / 16;   // fragment rows per band
+  static constexpr int STORES = 4 / FR * (BAND / 1024);                                // of a wavefront per tile
+  static constexpr int PRODUCTS = B_KC ? 1 : 2;
+
+  static __device__ void run(const MArgs& g, char* smem) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wm = wave >> 1, wn = wave & 1, lane_m = lane & 15, lane_c = lane >> 4;
+    // every XCD takes one eighth of the strips, one after another, an expert's row panels fastest: they share B's columns
+    const int nx = g.tiles_n * PRODUCTS, n_strips = (nx + g.strip - 1) / g.strip, per_e = g.tiles_m * n_strips;
+    const int total = g.E * per_e, share = (total + 7) / 8, pos = (int)(blockIdx.x / 8);
+    const int id = (int)(blockIdx.x % 8) * share + pos;
+    if (pos >= share || id >= total) return;
+    const int e = id / per_e, local = id - e * per_e;
+    const int row0 = (local % g.tiles_m) * BT, first = local / g.tiles_m * g.strip, last = min(first + g.strip, nx);
+    const int k_begin = g.offsets[e], k_end = g.offsets[e + 1], kp_begin = H::padded_rows_before(g, e, lane);
+    const int nk = (k_end - k_begin + BK - 1) / BK;
+    const bool rows_full = row0 + BT <= g.M;
+
+    int a_row[4], a_off[4], b_major[4], b_minor[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      int minor;
+      H::template copy_coords<true, BT>(wave * 4 + q, lane, a_row[q], minor);
+      a_off[q] = ((min(row0 + a_row[q], g.M - 1) - row0) * g.lda + minor) * 2;
+      H::template copy_coords<B_KC, BT>(wave * 4 + q, lane, b_major[q], b_minor[q]);
+    }
+    const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
+    auto tile_of = [&](int ct, bool& second, int& col0) {
+      second = !B_KC && ct >= g.tiles_n;
+      col0 = (ct - (second ? g.tiles_n : 0)) * BT;
+    };
+    // copies of k tile kt of column tile ct into LDS stage st
+    auto issue = [&](int ct, int kt, int st) {
+      bool second;
+      int col0;
+      tile_of(ct, second, col0);
+      const bf16_t* A = g.A0 + (size_t)row0 * g.lda + kp_begin + kt * BK;
+      const int k0 = k_begin + kt * BK;
+      const bf16_t* B = B_KC ? g.B0 + (size_t)col0 * g.ldb + kp_begin + kt * BK : (second ? g.B1 : g.B0) + (size_t)k0 * g.ldb;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) copy16_to_lds(A, (uint32_t)a_off[q], smem_base + st * STAGE + (wave * 4 + q) * 1024);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // strided: k rows past the expert's last one repeat it (they meet the zero fill of A, so must be finite)
+        const uint32_t off = B_KC ? (uint32_t)((min(col0 + b_major[q], g.N - 1) - col0) * g.ldb + b_minor[q]) * 2u
+                                  : (uint32_t)((min(k0 + b_major[q], k_end - 1) - k0) * g.ldb + min(col0 + b_minor[q], g.N - 8)) * 2u;
+        copy16_to_lds(B, off, smem_base + (2 + st) * STAGE + (wave * 4 + q) * 1024);
+      }
+    };
+
+    f32x4 acc[4][4];
+    auto clear = [&]() {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    char* band = smem + 4 * STAGE + wave * BAND;
+    // results of column tile ct through the wavefront's band, whole row segments per store (see Gemm's epilogue)
+    auto store = [&](int ct) {
+      bool second;
+      int col0;
+      tile_of(ct, second, col0);
+      ET* C = static_cast<ET*>(second ? g.C1 : g.C0) + (size_t)e * g.strideC_e;
+      constexpr int CPR = ROWB / 16, RPI = 64 / CPR, NI = BAND_ROWS / RPI;
+      const int cr = lane / CPR, cc = lane % CPR, cn = col0 + wn * 64 + cc * (16 / ES);
+#pragma unroll
+      for (int ib = 0; ib < 4 / FR; ++ib) {
+#pragma unroll
+        for (int i2 = 0; i2 < FR; ++i2)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int byte = (j * 16 + 4 * lane_c) * ES, r = i2 * 16 + lane_m;
+            char* dst = band + stage_off<ROWB, 4 * ES>(r, byte >> 4) + ((byte & 15) ^ half_flip<ROWB, ES>(r));
+            const f32x4 v = acc[ib * FR + i2][j];
+            if constexpr (ES == 2) *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            else *reinterpret_cast<f32x4*>(dst) = v;
+          }
+#pragma unroll
+        for (int t = 0; t < NI; ++t) {
+          const int r = t * RPI + cr, m = row0 + wm * 64 + ib * BAND_ROWS + r;
+          const u32x4 val = swap_halves(*reinterpret_cast<const u32x4*>(band + stage_off<ROWB, 4 * ES>(r, cc)), half_flip<ROWB, ES>(r) != 0);
+          if (m < g.M && cn < g.N) store_out<STREAM>(reinterpret_cast<u32x4*>(C + (size_t)m * g.ldc + cn), val);
+        }
+      }
+    };
+
+    clear();
+    if (nk == 0) {                                       // an expert without rows: zeros
+      for (int ct = first; ct < last; ++ct) store(ct);
+      return;
+    }
+    issue(first, 0, 0);
+    bool stores_behind = false;                          // STORES stores were issued after the copies now waited for
+    int st = 0;
+    for (int ct = first; ct < last; ++ct) {
+#pragma unroll 1
+      for (int kt = 0; kt < nk; ++kt, st ^= 1) {
+        if (stores_behind) wait_vmcnt<STORES>(); else wait_vmcnt<0>();
+        stores_behind = false;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();                    // this k tile published; everybody is done with the last one
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + 1 < nk) issue(ct, kt + 1, st ^ 1);
+        else if (ct + 1 < last) issue(ct + 1, 0, st ^ 1);
+        const char* At = smem + st * STAGE;
+        const char* Bt = smem + (2 + st) * STAGE;
+        bf16x8 fa[2][4], fb[2][4];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fa[ks][i] = H::read_kc(At, wm * 64 + i * 16, ks, lane);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            fb[ks][j] = B_KC ? H::read_kc(Bt, wn * 64 + j * 16, ks, lane) : H::template read_tr<BT>(Bt, wn * 64 + j * 16, ks, lane);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+      }
+      bool second;
+      int col0;
+      tile_of(ct, second, col0);
+      __builtin_amdgcn_sched_barrier(0);
+      store(ct);
+      clear();
+      __builtin_amdgcn_sched_barrier(0);
+      // only a whole tile is sure to have issued every one of its stores: vmcnt counts instructions in order
+      stores_behind = rows_full && col0 + BT <= g.N;
+    }
+  }
+};
+
+template <bool B_KC, typename ET, bool STREAM> __global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs g) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  DwStrip<B_KC, ET, STREAM>::run(g, smem);
+}
+
 // compute units of the current device (looked up once per device)
 int compute_units() {
   static int n[64] = {};
@@ -1042,10 +1199,11 @@ template <void (*Kernel)(MArgs), int LDS_BYTES> int raise_lds_limit() {
   return BTX_OK;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
+          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 int launch(MArgs g, bool prepare_only, hipStream_t s) {
   using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
-  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
+  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM>;
   if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
   constexpr int BNH = G::DUAL ? BN / 2 : BN;
@@ -1170,6 +1328,56 @@ template <int MODE> int prepare_rows() {
   return BTX_OK;
 }
 
+template <bool B_KC, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool prepare_only, hipStream_t s) {
+  using D = DwStrip<B_KC, ET, STREAM>;
+  constexpr auto kernel = dw_strip_kernel<B_KC, ET, STREAM>;
+  if (int rc = raise_lds_limit<kernel, D::LDS_BYTES>()) return rc;
+  if (prepare_only) return BTX_OK;
+  g.tiles_n = ceil_div(g.N, D::BT);
+  g.tiles_m = ceil_div(g.M, D::BT);
+  const int nx = g.tiles_n * D::PRODUCTS;
+  // long strips, but four for every workgroup that runs at a time (64 experts of 4096 x 688: strips of 1, 4, 8, 16 tiles
+  // 258, 198, 193, 196 us for dW1 and dW3)
+  const int64_t want = (int64_t)4 * 2 * kSplitMaxCus;
+  g.strip = (int)std::min<int64_t>(std::max<int64_t>((int64_t)g.E * g.tiles_m * nx / want, 1), nx);
+  const int64_t blocks = (int64_t)g.E * g.tiles_m * ceil_div(nx, g.strip);
+  if (blocks > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
+  kernel<<<(unsigned)align_up((size_t)blocks, 8), 256, D::LDS_BYTES, s>>>(g);
+  BTX_LAUNCH_CHECK();
+  return BTX_OK;
+}
+
+// Weight gradients.  Strips up to 64 rows per expert (one k tile), 256 x 256 tiles above.  us for (dW1, dW3) / dW2, strips
+// against tiles: 37 rows, 64 experts of 4096 x 688: 195 / 96 against 210 / 111; 48 rows, 64 of 1032 x 264: 33 / 21, 51 / 39;
+// 125 rows, 8 of 2048 x 5504: 122 / 79, 124 / 67; 150 rows, 4 of 4096 x 11008: 295 / 142, 271 / 125.
+// Streamed stores want whole lines: 64 experts of 4096 x 688, 188 rows, dW2 (rows of 4096 columns) 173 -> 151 us, 32 of
+// 4096 x 1376, 4096 rows 1236 -> 1208.  dW1 and dW3 leave a 256 x 256 tile in halves of lines and keep plain stores (64
+// experts of 4096 x 688, 37 rows: 210 us, streamed 356); with the two panels side by side, which makes them whole, the
+// transposing reads cost what the stores gain (8192 rows 4346 -> 4450 us, 1000 rows 357 -> 367).
+template <int MODE> int launch_dw(const MArgs& g, bool strip, bool stream, bool prepare_only, hipStream_t s) {
+  constexpr bool KC = MODE == DW2;
+  if (strip && g.c_is_f32)
+    return stream ? launch_dw_strip<KC, float, true>(g, prepare_only, s) : launch_dw_strip<KC, float, false>(g, prepare_only, s);
+  if (strip)
+    return stream ? launch_dw_strip<KC, bf16_t, true>(g, prepare_only, s) : launch_dw_strip<KC, bf16_t, false>(g, prepare_only, s);
+  if constexpr (KC)
+    if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, true>(g, prepare_only, s);
+  return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false>(g, prepare_only, s);
+}
+template <int MODE> int launch_dw(const MArgs& g, hipStream_t s) {
+  return launch_dw<MODE>(g, g.R / g.E <= 64, g.N % (g.c_is_f32 ? 32 : 64) == 0, false, s);
+}
+template <int MODE> int prepare_dw() {
+  MArgs g{};
+  for (int f32 : {0, 1})
+    for (bool strip : {false, true})
+      for (bool stream : {false, true}) {
+        g.c_is_f32 = f32;
+        if (int rc = launch_dw<MODE>(g, strip, stream, true, nullptr)) return rc;
+      }
+  return BTX_OK;
+}
+
 }  // namespace
 
 int mfma_prepare() {
@@ -1178,8 +1386,8 @@ int mfma_prepare() {
   if (int rc = prepare_rows<DOWN>()) return rc;
   if (int rc = prepare_rows<BWD_ACT>()) return rc;
   if (int rc = prepare_rows<BWD_DX>()) return rc;
-  if (int rc = launch<256, 256, 64, 2, 4, 3, 2, DW13>(MArgs{}, true, nullptr)) return rc;
-  return launch<256, 256, 64, 2, 4, 3, 2, DW2>(MArgs{}, true, nullptr);
+  if (int rc = prepare_dw<DW13>()) return rc;
+  return prepare_dw<DW2>();
 }
 // one dg partial per column tile of BWD_ACT
 int mfma_bwd_act_partials(const FfShapes& sh) {
@@ -1240,7 +1448,7 @@ int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh
   g.A0 = (const bf16_t*)xsT; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
   g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
   g.strideC_e = sh.s13; g.R = sh.R; g.c_is_f32 = dW_dtype == BTX_F32;
-  return launch<256, 256, 64, 2, 4, 3, 2, DW13>(g, false, s);
+  return launch_dw<DW13>(g, s);
 }
 
 int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t* off, const FfShapes& sh, void* dW2,
@@ -1249,7 +1457,7 @@ int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t*
   h.A0 = (const bf16_t*)gaT; h.B0 = (const bf16_t*)dysT; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
-  return launch<256, 256, 64, 2, 4, 3, 2, DW2>(h, false, s);
+  return launch_dw<DW2>(h, s);
 }
 
 }  // namespace btx

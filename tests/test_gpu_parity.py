@@ -332,6 +332,18 @@ def test_bf16_row_tiles(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [
+    # strips: no rows at all for some experts, one k tile, several k tiles (skewed), partial row panels and column tiles
+    (3, 136, 264, 64, 2, {}), (64, 256, 192, 8, 2, {}), (100, 264, 136, 8, 4, dict(bias=[3.0] + [0.0] * 7)),
+    (250, 512, 320, 16, 4, dict(cf=0.8, poison=True)), (256, 264, 1032, 4, 1, {}),
+    # the same widths past the strips' limit of 64 rows per expert, whole lines and not
+    (300, 256, 192, 4, 1, {}), (300, 264, 136, 4, 1, {}),
+])
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_of_few_rows(T, d, f, E, k, kw, dW_dtype):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
+
+
 @pytest.mark.parametrize("T,d,E,k,kw", [
     # both sides of the limits of the two-launch routing: tokens, pairs, tokens x columns x experts
     (512, 64, 8, 8, {}), (513, 64, 8, 2, {}), (512, 72, 9, 8, dict(cf=0.8)), (456, 64, 9, 9, {}), (512, 1024, 64, 3, {}),
