@@ -22,7 +22,7 @@ inline int esize(int dtype) { return dtype == BTX_BF16 ? 2 : 4; }
 inline bool dtype_ok(int dtype) { return dtype == BTX_F32 || dtype == BTX_BF16; }
 
 struct FwdWs { void *xs, *act, *y, *partial; size_t bytes; };
-FwdWs carve_forward(void* ws, int T, int d, int f, int k, int dtype) {
+FwdWs carve_forward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const size_t R = (size_t)T * k, es = esize(dtype);
   Carver c(ws);
   FwdWs w;
@@ -30,7 +30,7 @@ FwdWs carve_forward(void* ws, int T, int d, int f, int k, int dtype) {
   w.xs = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   w.act = c.take(R * f * es);
   w.y = c.take(R * d * es);
-  const size_t split = ff_split_bytes(dtype);            // K slices of DOWN's last round
+  const size_t split = ff_forward_split_bytes(dtype, FfShapes{(int)R, d, f, E, 0, 0});   // sums of K slices
   w.partial = split ? c.take(split) : nullptr;
   w.bytes = c.used;
   return w;
@@ -39,6 +39,7 @@ FwdWs carve_forward(void* ws, int T, int d, int f, int k, int dtype) {
 struct BwdWs { void *xsT, *dysT, *dys, *dh1, *dh3, *ga, *dxs, *router, *partial; float* dg_part; size_t bytes; };
 BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const size_t R = (size_t)T * k, es = esize(dtype);
+  const FfShapes sh{(int)R, d, f, E, 0, 0};
   Carver c(ws);
   BwdWs w;
   // the bf16 dW products take x and dY transposed and padded
@@ -52,9 +53,9 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   // transposed path: dW2 reads ga as [f][padded rows]
   w.ga = c.take(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : R * f * es);
   w.dxs = c.take(R * d * es);
-  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials(dtype, FfShapes{(int)R, d, f, E, 0, 0}) * sizeof(float)));
+  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials(dtype, sh) * sizeof(float)));
   w.router = c.take(router_bwd_workspace_bytes(T, d, E));
-  const size_t split = ff_split_bytes(dtype);            // K slices of BWD_DX's last round
+  const size_t split = ff_backward_split_bytes(dtype, sh);   // sums of K slices
   w.partial = split ? c.take(split) : nullptr;
   w.bytes = c.used;
   return w;
@@ -245,7 +246,7 @@ int btx_rmsnorm_backward(const void* dXn, const void* h, const float* gain, cons
 
 size_t btx_moe_ff_forward_workspace_bytes(int T, int d, int f, int E, int k, int dtype) {
   if (!dtype_ok(dtype) || !shapes_ok(T, d, f, E, k) || T == 0) return 0;
-  return carve_forward(nullptr, T, d, f, k, dtype).bytes;
+  return carve_forward(nullptr, T, d, f, E, k, dtype).bytes;
 }
 
 int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void* W2, int dtype,
@@ -262,7 +263,7 @@ int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void
     return BTX_ERR_INVALID_ARG;
   if (!aligned16(x, W1, W3, W2, residual, out, save_h1, save_h3, workspace) || w13_expert_stride % 8 || w2_expert_stride % 8)
     return BTX_ERR_INVALID_ARG;
-  const FwdWs w = carve_forward(workspace, T, d, f, k, dtype);
+  const FwdWs w = carve_forward(workspace, T, d, f, E, k, dtype);
   if (workspace_bytes < w.bytes) return BTX_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int R = T * k;

@@ -255,10 +255,12 @@ bool ff_gather_fused(int dtype, int T, int d);
 // a = silu(xs W1) * (xs W3); h1/h3 stored when non-null.
 int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void* W3, const int32_t* offsets,
                      const FfShapes& sh, void* h1, void* h3, void* act, void* partial, hipStream_t s);
-// partial (here, in launch_down and in launch_bwd_dx): ff_split_bytes() of scratch (the bf16 MFMA path cuts the
-// tiles of a partly filled last round along K and adds the slices in a second kernel); may be NULL when
-// ff_split_bytes() is 0.  Products that follow each other on a stream may share it.
-size_t ff_split_bytes(int dtype);
+// partial (here, in launch_down and in launch_bwd_dx): ff_forward_split_bytes() / ff_backward_split_bytes() of scratch
+// for the sums of products that are cut along K (the tiles of a partly filled last round, or all tiles of a small
+// product; a second kernel adds the slices); may be NULL when that is 0.  Products that follow each other on a
+// stream may share it.
+size_t ff_forward_split_bytes(int dtype, const FfShapes& sh);
+size_t ff_backward_split_bytes(int dtype, const FfShapes& sh);
 // y = act W2
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, hipStream_t s);

@@ -23,7 +23,15 @@ int bwd_act_partials(int dtype, const FfShapes& sh) {
   return dtype == BTX_BF16 ? mfma_bwd_act_partials(sh) : f32_bwd_act_partials(sh.f);
 }
 
-size_t ff_split_bytes(int dtype) { return dtype == BTX_BF16 ? mfma_split_bytes() : 0; }
+static size_t f32_sums_bytes(const FfShapes& sh, int slices) {
+  return slices > 1 ? (size_t)slices * sh.R * sh.d * sizeof(float) : 0;
+}
+size_t ff_forward_split_bytes(int dtype, const FfShapes& sh) {
+  return dtype == BTX_BF16 ? mfma_split_bytes() : f32_sums_bytes(sh, f32_down_slices(sh));
+}
+size_t ff_backward_split_bytes(int dtype, const FfShapes& sh) {
+  return dtype == BTX_BF16 ? mfma_split_bytes() : f32_sums_bytes(sh, f32_bwd_dx_slices(sh));
+}
 
 int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void* W3, const int32_t* offsets,
                      const FfShapes& sh, void* h1, void* h3, void* act, void* partial, hipStream_t s) {
@@ -33,7 +41,7 @@ int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void*
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, hipStream_t s) {
   if (dtype == BTX_BF16) return mfma_down(act, W2, offsets, sh, y, partial, s);
-  return f32_down(act, W2, offsets, sh, y, s);
+  return f32_down(act, W2, offsets, sh, y, partial, s);
 }
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
@@ -45,7 +53,7 @@ int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* 
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s) {
   if (dtype == BTX_BF16) return mfma_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, partial, s);
-  return f32_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, s);
+  return f32_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, partial, s);
 }
 int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
                     const FfShapes& sh, void* dW1, void* dW3, hipStream_t s) {

@@ -41,6 +41,7 @@ struct FArgs {
   int M, N, K;                           // row-grouped: M unused; grouped along K: K unused
   int lda, ldb, ldc;
   int64_t strideB_e, strideC_e;
+  int slices; float* sums; int R;        // DOWN, BWD_DX: K ranges of every tile; their sums [slice][R][N] (slices > 1)
   int tiles_n, tiles_m;                  // column tiles of one product; row tiles of an expert (grouped along K)
   // p / k for 0 <= p < 2^31 without a division (which would cost a third of the vector work of a dW tile):
   // with s = 31 + ceil(log2 k) and div_mul = ceil(2^s / k) < 2^32 the product is off by less than one in 2^31
@@ -61,6 +62,7 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
   static constexpr bool GROUP_K = MODE == DW13 || MODE == DW2;
   static constexpr bool A_KC = !GROUP_K, B_KC = MODE == BWD_ACT || MODE == BWD_DX;   // k contiguous in memory
   static constexpr bool A_GATHER = MODE == UP || MODE == BWD_ACT || MODE == DW13, B_GATHER = MODE == DW2;
+  static constexpr bool SLICED = MODE == DOWN || MODE == BWD_DX;
   static constexpr bool DUAL = MODE == UP;                       // two B panels side by side in one tile
   static constexpr int BNH = DUAL ? BN / 2 : BN;                 // output columns of a tile
   static constexpr int TM = BM / 32, TN = BN / 32, TNH = DUAL ? TN / 2 : TN;
@@ -188,17 +190,22 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
     int e = 0, row0, row_end, k_begin = 0, k_end = g.K;
     const int nx = MODE == DW13 ? 2 * g.tiles_n : g.tiles_n;
     RowTiles row_tiles(g.offsets, GROUP_K ? 1 : g.E, BM, lane);
-    const int total = GROUP_K ? g.E * g.tiles_m * nx : row_tiles.count() * nx;
+    const int per_row_tile = SLICED ? nx * g.slices : nx;
+    const int total = GROUP_K ? g.E * g.tiles_m * nx : row_tiles.count() * per_row_tile;
     const int share = (total + 7) / 8, id = (int)(blockIdx.x % 8) * share + (int)(blockIdx.x / 8);
     if ((int)(blockIdx.x / 8) >= share || id >= total) return;
-    int tile_m, tile_n, n_rows;
+    int tile_m, tile_n, n_rows, slice = 0;
     bool second_product = false;
     if (GROUP_K) {
       e = id / (g.tiles_m * nx);
       n_rows = g.tiles_m;
       tile_m = id - e * n_rows * nx;
     } else {
-      row_tiles.expert_of(id, nx, e, n_rows, tile_m);
+      row_tiles.expert_of(id, per_row_tile, e, n_rows, tile_m);
+      if (SLICED) {
+        slice = tile_m / (nx * n_rows);
+        tile_m -= slice * nx * n_rows;
+      }
     }
     const int band = tile_m / (kBand * nx), in_band = tile_m - band * kBand * nx, h = min(kBand, n_rows - band * kBand);
     tile_m = band * kBand + in_band % h;
@@ -213,25 +220,38 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
       row_tiles.rows_of(e, tile_m, row0, row_end);
     }
     const int col0 = tile_n * BNH;
+    const float* A0 = g.A0;
     const float* B0 = second_product ? g.B1 : g.B0;
     const float* B1 = g.B1;
+    bool two_passes = MODE == BWD_DX;
+    if (SLICED && g.slices > 1) {                        // k tiles s nk / n .. (s + 1) nk / n of this slice's pass
+      int n = g.slices;
+      if (MODE == BWD_DX) {
+        two_passes = false;
+        n /= 2;
+        if (slice >= n) { A0 = g.A1; B0 = g.B1; }
+      }
+      const int s = slice % n, nk = (g.K + BK - 1) / BK;
+      k_begin = s * nk / n * BK;
+      k_end = min((s + 1) * nk / n * BK, g.K);
+    }
     if (!GROUP_K) { B0 += e * g.strideB_e; if (B1) B1 += e * g.strideB_e; }
 
     Operand<A_KC, BM, A_PITCH, NA, A_GATHER> a;
     Operand<B_KC, BN, B_PITCH, NB, B_GATHER> b;
-    if constexpr (A_KC) a.rows(g.A0, row0, row_end, g.lda, g);
+    if constexpr (A_KC) a.rows(A0 + k_begin, row0, row_end, g.lda, g);
     else a.cols(g.A0, nullptr, row0, g.M, g.lda, k_begin);
-    if constexpr (B_KC) b.rows(B0, col0, g.N, g.ldb, g);
+    if constexpr (B_KC) b.rows(B0 + k_begin, col0, g.N, g.ldb, g);
     else b.cols(B0, B1, col0, g.N, g.ldb, k_begin);
 
-    const int nk1 = (k_end - k_begin + BK - 1) / BK, nk = MODE == BWD_DX ? 2 * nk1 : nk1;
+    const int nk1 = (k_end - k_begin + BK - 1) / BK, nk = two_passes ? 2 * nk1 : nk1;
     auto look_up = [&](int kt) {
       if constexpr (!A_KC && A_GATHER) a.look_up(g, k_begin + kt * BK, k_end);
       if constexpr (!B_KC && B_GATHER) b.look_up(g, k_begin + kt * BK, k_end);
     };
-    auto k_left = [&](int kt) { return k_end - k_begin - (MODE == BWD_DX && kt >= nk1 ? kt - nk1 : kt) * BK; };
+    auto k_left = [&](int kt) { return k_end - k_begin - (two_passes && kt >= nk1 ? kt - nk1 : kt) * BK; };
     auto fetch = [&](auto set, int kt) {
-      if (MODE == BWD_DX && kt == nk1) {                 // second K pass
+      if (two_passes && kt == nk1) {                 // second K pass
         a.rows(g.A1, row0, row_end, g.lda, g);
         b.rows(B1, col0, g.N, g.ldb, g);
       }
@@ -303,6 +323,7 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
     const int m_wave = row0 + wm * (BM / 2), n_wave = col0 + wn * (BNH / 2);
     float* C = second_product ? g.C1 : g.C0;
     if (GROUP_K) C += e * g.strideC_e;
+    if (SLICED && g.slices > 1) C = g.sums + (int64_t)slice * g.R * g.ldc;
     float dot[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -370,19 +391,60 @@ template <int BM, int BN, int BK, int MODE> __global__ __launch_bounds__(kThread
 // 128 x 128 and 128 x 64 tiles of the same form (half the operand traffic per product, half the workgroups) were
 // slower on this library's fp32 shapes: with 4006 rows, d = 512, f = 1376 DOWN 115 / 111 us against 84, DW13 151 / 142
 // against 138.
-constexpr int kTile = 64, kTileK = 32;
+constexpr int kTile = 64, kTileK = 32, kMaxSlices = 8;
+
+// The K slices of a product added in slice order, 4 columns of a row per thread.
+__global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N,
+                                                                     const int32_t* __restrict__ offsets, int E,
+                                                                     float* __restrict__ C) {
+  const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4, all = (int64_t)R * N;
+  if (i >= (int64_t)offsets[E] * N) return;              // rows past the kept ones do not exist
+  f32x4 a = *reinterpret_cast<const f32x4*>(sums + i);
+  for (int s = 1; s < slices; ++s) {
+    const f32x4 b = *reinterpret_cast<const f32x4*>(sums + s * all + i);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) a[x] += b[x];
+  }
+  *reinterpret_cast<f32x4*>(C + i) = a;
+}
+
+// K slices of DOWN and BWD_DX.  Few tiles of many k tiles leave compute units idle, or some with a tile more than others.
+// Measured on 64 x 64 tiles of 32 k: with r tiles on a compute unit a k tile takes about 0.35 us for every four of them and
+// 0.55 us each; the slices' sums pass through memory once more, in a launch of its own.  64 tokens, 8 experts of 512 x
+// 1376, top-2: DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: what the caller's scratch holds.
+int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
+  const int busy = std::max(std::min(E, R), 1);
+  const int64_t tiles = (int64_t)busy * ceil_div(ceil_div(R, busy), kTile) * ceil_div(N, kTile);
+  const double nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
+  int best = 1;
+  double best_us = 0;
+  for (int n = 1; n <= std::min(most, kMaxSlices); ++n) {
+    if (n > 1 && ((two_passes && n % 2) || n > nk / 2)) continue;
+    const double r = (double)ceil_div(tiles * n, 256), per_k = 0.35 * std::ceil(r / 4) + 0.55 * r;
+    const double us = per_k * (nk / n + 1) + (n > 1 ? 5.0 + 8e-6 / 4 * n * (double)R * N : 0.0);
+    if (n == 1 || us < best_us) { best = n; best_us = us; }
+  }
+  return best;
+}
 
 template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
   constexpr int BM = kTile, BN = kTile, BK = kTileK;
   using G = F32Gemm<BM, BN, BK, MODE>;
   g.tiles_n = ceil_div(g.N, G::BNH);
   g.tiles_m = ceil_div(g.M, BM);
-  const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) *
+  if (!G::SLICED) g.slices = 1;
+  g.R = R;
+  const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
                         (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, BM) + g.E);   // at most this many
   if (tiles > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
   const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
   f32_gemm_kernel<BM, BN, BK, MODE><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
+  if (g.slices > 1) {
+    f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets,
+                                                                                         g.E, g.C0);
+    BTX_LAUNCH_CHECK();
+  }
   return BTX_OK;
 }
 
@@ -390,6 +452,9 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
 
 bool f32_rows_ok(int R, int E) { return ceil_div(R, 64) + E <= 65535; }
 int f32_bwd_act_partials(int f) { return ceil_div(f, kTile); }
+// no more scratch than two rows of d and three of f per grouped row
+int f32_down_slices(const FfShapes& sh) { return f32_slices(sh.R, sh.E, sh.d, sh.f, false, 1 + 2 * sh.f / sh.d); }
+int f32_bwd_dx_slices(const FfShapes& sh) { return f32_slices(sh.R, sh.E, sh.d, sh.f, true, 2 + sh.f / sh.d); }
 
 int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh, void* h1,
                   void* h3, void* act, hipStream_t s) {
@@ -399,8 +464,9 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f; g.strideB_e = sh.s13;
   return launch<UP>(g, sh.R, s);
 }
-int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, hipStream_t s) {
+int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, hipStream_t s) {
   FArgs g{};
+  g.slices = f32_down_slices(sh); g.sums = (float*)sums;
   g.A0 = (const float*)act; g.B0 = (const float*)W2; g.C0 = (float*)y;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideB_e = sh.s2;
   return launch<DOWN>(g, sh.R, s);
@@ -417,8 +483,9 @@ int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void
   return launch<BWD_ACT>(g, sh.R, s);
 }
 int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
-               void* dxs, hipStream_t s) {
+               void* dxs, void* sums, hipStream_t s) {
   FArgs g{};
+  g.slices = f32_bwd_dx_slices(sh); g.sums = (float*)sums;
   g.A0 = (const float*)dh1; g.A1 = (const float*)dh3; g.B0 = (const float*)W1; g.B1 = (const float*)W3; g.C0 = (float*)dxs;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d; g.strideB_e = sh.s13;
   return launch<BWD_DX>(g, sh.R, s);

@@ -46,6 +46,12 @@ def test_fp32_tiles(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, F32, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [(64, 512, 1376, 8, 2, {}), (40, 72, 1032, 4, 2, {}), (1, 64, 2056, 3, 2, {}),
+                                          (130, 136, 776, 4, 2, dict(cf=0.8, poison=True)), (300, 264, 1384, 2, 1, {})])
+def test_fp32_products_cut_along_k(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, F32, **kw)
+
+
 @pytest.mark.parametrize("mode", [B.BTX_ROUTE_SWITCH_TOP1, B.BTX_ROUTE_SAMPLE_TOP1])
 @pytest.mark.parametrize("lb_mode,flags", [(B.BTX_LB_TOKEN_FRAC, 0), (B.BTX_LB_GATE_MEAN, 0),
                                            (B.BTX_LB_GATE_MEAN, B.BTX_FLAG_LB_GRAD_THROUGH_U)])
