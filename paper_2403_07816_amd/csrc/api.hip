@@ -325,12 +325,8 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   if (n_dw == 3) {
     RowSource dw_x{x, perm, k}, dw_dy{dY, perm, k};
     if (ff_dw_transposed(dtype)) {
-      auto gather_dw_operands = [&]() -> int {
-        const int pitch = ff_dw_pitch(R, E);
-        if (int rc = launch_gather_rows_t(x, w.xsT, perm, offsets, R, k, d, E, pitch, s)) return rc;
-        return launch_gather_rows_t(dY, w.dysT, perm, offsets, R, k, d, E, pitch, s);
-      };
-      BTX_STAGE(BTX_STAGE_GATHER_X_BWD, gather_dw_operands());
+      BTX_STAGE(BTX_STAGE_GATHER_X_BWD,
+                launch_gather_rows_t(x, w.xsT, dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
       dw_x = RowSource{w.xsT, nullptr, 1};
       dw_dy = RowSource{w.dysT, nullptr, 1};
     }

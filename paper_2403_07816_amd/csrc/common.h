@@ -230,15 +230,13 @@ size_t rmsnorm_bwd_workspace_bytes(int T, int d);
 int launch_rmsnorm_bwd(const void* dXn, const void* h, const float* gain, const float* rstd, const void* dres,
                        int dtype, int T, int d, void* dH, float* dgain, void* workspace, hipStream_t s);
 int launch_route(const RouteArgs& a, hipStream_t s);
-// WrT[e][c] = Wr[c][e]: the router kernels read W_router expert-major
-int launch_transpose_wr(const float* Wr, int d, int E, float* WrT, hipStream_t s);
 
 // rows: dst[r] = src[perm[r] / k]  (k = 1 with perm = NULL copies nothing; perm required)
 int launch_gather_rows(const void* src, void* dst, const int32_t* perm, int R, int k, int d, int dtype, hipStream_t s);
 // bf16 only: dst[c][P_e + i] = src[perm[o_e + i] / k][c], every expert's rows padded with zeros to a
-// multiple of 64 (P_e = padded rows of the experts before e); dst is [d][pitch]
-int launch_gather_rows_t(const void* src, void* dst, const int32_t* perm, const int32_t* offsets, int R, int k, int d,
-                         int E, int pitch, hipStream_t s);
+// multiple of 64 (P_e = padded rows of the experts before e); dst is [d][pitch].  Two such matrices in one launch.
+int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* dst1, const int32_t* perm,
+                         const int32_t* offsets, int R, int k, int d, int E, int pitch, hipStream_t s);
 // out[t] = sum_j gates[t,j] * y[inv_pos[t,j]]   (gates NULL => unit weights; inv_pos < 0: dropped pair, skipped)
 // residual (may be NULL): [T,d] added to the sum in fp32 before the one rounding
 int launch_combine(const void* y, const float* gates, const int32_t* inv_pos, const void* residual, void* out, int T,

@@ -4,7 +4,8 @@
 //   gather_rows_t  the same rows, transposed and padded for the weight-gradient products,
 //                whose contraction runs over grouped rows: dst[c][P_e + i] = src[perm[o_e + i] / k][c]
 //                for row i of expert e, with P_e = sum over e' < e of n_e' rounded up to 64 and
-//                zeros from P_e + n_e to P_(e+1).  64 rows x 128 columns are turned around in LDS.
+//                zeros from P_e + n_e to P_(e+1).  64 rows x 128 columns are turned around in LDS; x and dY in one
+//                launch.
 //   combine      out[t] = (residual[t] +) sum_j gates[t,j] * y[inv_pos[t,j]]: the gate-weighted sum of the
 //                layer equation (Sec. 3.2), one wavefront per token row, slots summed in
 //                ascending j in fp32, one rounding.  No atomics: every output row has
@@ -37,11 +38,14 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(const u32x4* __re
 }
 
 constexpr int kTRows = 64, kTCols = 128;
-__global__ __launch_bounds__(kThreads) void gather_rows_t_kernel(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst,
+__global__ __launch_bounds__(kThreads) void gather_rows_t_kernel(const bf16_t* __restrict__ src0, bf16_t* __restrict__ dst0,
+                                                                 const bf16_t* __restrict__ src1, bf16_t* __restrict__ dst1,
                                                                  const int32_t* __restrict__ perm,
                                                                  const int32_t* __restrict__ offsets, int E, int k,
                                                                  int d, int pitch) {
   __shared__ uint32_t tile[kTRows][kTCols / 2 + 1];     // +1 dword: the column reads below hit distinct banks
+  const bf16_t* __restrict__ src = blockIdx.z ? src1 : src0;
+  bf16_t* __restrict__ dst = blockIdx.z ? dst1 : dst0;
   const int pb = blockIdx.x * kTRows;                   // first padded row of this block
   int e = 0, P = 0, base = 0, n = 0;
   for (; e < E; ++e) {
@@ -169,11 +173,12 @@ int launch_gather_rows(const void* src, void* dst, const int32_t* perm, int R, i
   return BTX_OK;
 }
 
-int launch_gather_rows_t(const void* src, void* dst, const int32_t* perm, const int32_t* offsets, int R, int k, int d,
-                         int E, int pitch, hipStream_t s) {
+int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* dst1, const int32_t* perm,
+                         const int32_t* offsets, int R, int k, int d, int E, int pitch, hipStream_t s) {
   if (pitch % 8 != 0 || pitch < (int)align_up((size_t)R, kTRows) + kTRows * E) return BTX_ERR_INVALID_ARG;
-  const dim3 grid(ceil_div(R, kTRows) + E, ceil_div(d, kTCols));
-  gather_rows_t_kernel<<<grid, kThreads, 0, s>>>(static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), perm,
+  const dim3 grid(ceil_div(R, kTRows) + E, ceil_div(d, kTCols), 2);
+  gather_rows_t_kernel<<<grid, kThreads, 0, s>>>(static_cast<const bf16_t*>(src0), static_cast<bf16_t*>(dst0),
+                                                 static_cast<const bf16_t*>(src1), static_cast<bf16_t*>(dst1), perm,
                                                  offsets, E, k, d, pitch);
   BTX_LAUNCH_CHECK();
   return BTX_OK;

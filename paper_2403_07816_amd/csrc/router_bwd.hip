@@ -17,13 +17,24 @@ namespace {
 
 constexpr int kColsPerThread = 8;
 
+// The workgroups behind the tokens' lay W_router out expert-major for dx_finish (a launch less, 5 us).
 __global__ __launch_bounds__(256) void router_ds_kernel(
+    const float* __restrict__ Wr, int d, float* __restrict__ WrT,
     int T, int E, int k, int mode, int lb_mode, float lb_alpha, float lam, unsigned flags,
     const float* __restrict__ noise, float inv_tau,
     const int32_t* __restrict__ topk_idx, const float* __restrict__ gates, const float* __restrict__ probs,
     const int32_t* __restrict__ inv_pos, const float* __restrict__ gate_sum, const float* __restrict__ prob_sum,
     const int32_t* __restrict__ counts, const float* __restrict__ dg_part, int n_part, float* __restrict__ ds) {
   const int lane = threadIdx.x & (kWave - 1);
+  const int token_blocks = (T + 3) / 4;
+  if ((int)blockIdx.x >= token_blocks) {
+    const int64_t i = (int64_t)((int)blockIdx.x - token_blocks) * 256 + threadIdx.x;
+    if (i < (int64_t)d * E) {
+      const int e = (int)(i / d), c = (int)(i - (int64_t)e * d);
+      WrT[i] = Wr[(size_t)c * E + e];
+    }
+    return;
+  }
   const int t = blockIdx.x * 4 + threadIdx.x / kWave;
   if (t >= T) return;
   const bool live = lane < E;
@@ -133,7 +144,8 @@ constexpr int kFewBlocks = 512;
 template <typename XT, int KEC, int CHUNK>
 __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restrict__ x, const float* __restrict__ ds, int T,
                                                               int d, int E, float* __restrict__ part,
-                                                              float* __restrict__ db_part) {
+                                                              float* __restrict__ db_part, float* __restrict__ dWr,
+                                                              float* __restrict__ db) {
   constexpr int kQuarter = CHUNK / 4;
   __shared__ float s_ds[CHUNK][KEC];
   __shared__ f32x4 s_acc[KEC * 2][kWave];
@@ -182,13 +194,24 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
   }
   if (wave == 0 && c0 < d) {
 #pragma unroll
-    for (int j = 0; j < KEC; ++j)
-      if (e0 + j < E) RowVec<float, 8>::st(part + ((size_t)blockIdx.x * E + e0 + j) * d + c0, acc[j]);
+    for (int j = 0; j < KEC; ++j) {
+      if (e0 + j >= E) continue;
+      if (dWr) {                                        // the only chunk: its sums are the result
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dWr[(size_t)(c0 + i) * E + e0 + j] = acc[j][i];
+      } else {
+        RowVec<float, 8>::st(part + ((size_t)blockIdx.x * E + e0 + j) * d + c0, acc[j]);
+      }
+    }
   }
   if (blockIdx.y == 0 && threadIdx.x < KEC && e0 + threadIdx.x < E) {
     float a = 0.f;
     for (int q = 0; q < nt; ++q) a += s_ds[q][threadIdx.x];
-    db_part[(size_t)blockIdx.x * E + e0 + threadIdx.x] = a;
+    if (dWr) {
+      if (db) db[e0 + threadIdx.x] = a;
+    } else {
+      db_part[(size_t)blockIdx.x * E + e0 + threadIdx.x] = a;
+    }
   }
 }
 
@@ -387,23 +410,28 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
 
   if (a.E > 32)
     if (int rc = raise_dx_lds_limit()) return rc;
-  if (int rc = launch_transpose_wr(a.W_router, a.d, a.E, WrT, s)) return rc;
-  router_ds_kernel<<<ceil_div(a.T, 4), 256, 0, s>>>(a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
+  if ((int64_t)a.d * a.E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
+  router_ds_kernel<<<ceil_div(a.T, 4) + ceil_div(a.d * a.E, 256), 256, 0, s>>>(
+                                                   a.W_router, a.d, WrT, a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
                                                    a.flags, a.noise, a.noise ? 1.f / a.tau : 1.f, a.topk_idx, a.gates,
                                                    a.probs, a.inv_pos, a.gate_sum,
                                                    a.prob_sum, a.counts, a.dg_part, a.n_part, ds);
   BTX_LAUNCH_CHECK();
+  bool reduce = nch > 1;                                // a single chunk's sums need no second kernel
   auto typed = [&](auto tag) {
     using XT = decltype(tag);
     const XT* x = static_cast<const XT*>(a.x);
     const int col_blocks = ceil_div(a.d, 256 * kColsPerThread);
     const int few_cols = ceil_div(a.d, kWave * kColsPerThread);
     const bool few = (int64_t)nch * col_blocks * ceil_div(a.E, a.E <= 8 ? 8 : 16) < kFewBlocks;
+    if (!few) reduce = true;
+    float* direct = reduce ? nullptr : a.dW_router;
     if (a.E <= 8 && few)
-      dwr_partial_few_kernel<XT, 8, 64><<<dim3(nch, few_cols, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
+      dwr_partial_few_kernel<XT, 8, 64><<<dim3(nch, few_cols, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp, direct,
+                                                                               a.db_router);
     else if (few)
       dwr_partial_few_kernel<XT, 16, 128><<<dim3(nch, few_cols, ceil_div(a.E, 16)), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part,
-                                                                                               dbp);
+                                                                                               dbp, direct, a.db_router);
     else if (a.E <= 8)
       dwr_partial_kernel<XT, 8, 64><<<dim3(nch, col_blocks, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
     else
@@ -413,9 +441,11 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
   if (a.dtype == BTX_BF16) typed(bf16_t{});
   else typed(float{});
   BTX_LAUNCH_CHECK();
-  dwr_reduce_kernel<<<ceil_div(a.d * a.E, 64), 64 * kRedGroups, 0, s>>>(part, dbp, nch, a.d, a.E, a.dW_router,
-                                                                       a.db_router);
-  BTX_LAUNCH_CHECK();
+  if (reduce) {
+    dwr_reduce_kernel<<<ceil_div(a.d * a.E, 64), 64 * kRedGroups, 0, s>>>(part, dbp, nch, a.d, a.E, a.dW_router,
+                                                                         a.db_router);
+    BTX_LAUNCH_CHECK();
+  }
   auto dx_launch = [&](auto tag) {
     using XT = decltype(tag);
     const XT* dxs = static_cast<const XT*>(a.dxs);
