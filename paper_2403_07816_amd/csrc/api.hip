@@ -188,8 +188,7 @@ int btx_moe_route(const void* x, int x_dtype, const float* W_router, const float
 int btx_init(void) {
   void* p = nullptr;
   if (int rc = static_scratch(&p)) return rc;   // also looks up this device's copy of the fixed workspace
-  if (int rc = ff_prepare()) return rc;
-  return router_bwd_prepare();
+  return ff_prepare();
 }
 
 size_t btx_moe_route_noalloc_max_workspace_bytes(void) { return kStaticRouteBytes; }

@@ -304,8 +304,10 @@ __global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ d
 // The same for more than 8 experts, where the slice of W_router no longer fits the registers and reloading it
 // per 4 tokens (from the caches) cost 110 of the kernel's 337 us at 32 experts: the 8 wavefronts of a
 // workgroup share one slice of kDxCols columns, staged once in LDS ([expert][half][lane] 16-byte
-// pieces, so that consecutive lanes read consecutive pieces; 128 KB at 64 experts), and split the workgroup's
-// tokens, 4 in flight per wavefront.  1501 tokens of 4096 columns, 64 experts, 8 slots: 152 us reloading, 50 now.
+// pieces, so that consecutive lanes read consecutive pieces), and split the workgroup's tokens, 4 in flight per
+// wavefront.  More than kDxLdsE experts take turns in the same 64 KB, for one pass of 32 tokens per workgroup.  1501
+// tokens of 4096 columns, 64 experts, 8 slots: 152 us reloading, 44 now.
+constexpr int kDxLdsE = 32;                             // 32 experts x 512 columns x 4 bytes = 64 KB
 constexpr int kDxCols = kWave * 8;                      // columns of a workgroup: 8 per lane
 constexpr int kDxWaves = 8;
 template <typename XT>
@@ -314,20 +316,24 @@ __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT
                                                                         const float* __restrict__ ds,
                                                                         const float* __restrict__ WrT, int T, int d, int E,
                                                                         int k, int tok_per_block, XT* __restrict__ dX) {
-  extern __shared__ f32x4 s_wr[];                       // [E][2][kWave]
+  extern __shared__ f32x4 s_wr[];                       // [min(E, kDxLdsE)][2][kWave]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int cb = blockIdx.y * kDxCols, c0 = cb + lane * 8;
-  for (int i = threadIdx.x; i < E * (kDxCols / 4); i += kDxWaves * kWave) {
-    const int e = i / (kDxCols / 4), c4 = i % (kDxCols / 4);      // 16-byte piece c4 of expert e's slice
-    f32x4 w{0.f, 0.f, 0.f, 0.f};
-    if (cb + 4 * c4 < d) w = *reinterpret_cast<const f32x4*>(WrT + (size_t)e * d + cb + 4 * c4);
-    s_wr[(e * 2 + (c4 & 1)) * kWave + (c4 >> 1)] = w;
-  }
-  __syncthreads();
-  if (c0 >= d) return;                      // no barrier and no cross-lane traffic below
-  const int t_end = min(T, (int)(blockIdx.x + 1) * tok_per_block);
-  for (int t0 = blockIdx.x * tok_per_block + wave * 4; t0 < t_end; t0 += kDxWaves * 4) {
+  const int cb = blockIdx.y * kDxCols, c0 = cb + lane * 8, cc = min(c0, d - 8);
+  auto stage = [&](int e0) {
+    for (int i = threadIdx.x; i < min(E - e0, kDxLdsE) * (kDxCols / 4); i += kDxWaves * kWave) {
+      const int e = i / (kDxCols / 4), c4 = i % (kDxCols / 4);    // 16-byte piece c4 of expert e0 + e's slice
+      f32x4 w{0.f, 0.f, 0.f, 0.f};
+      if (cb + 4 * c4 < d) w = *reinterpret_cast<const f32x4*>(WrT + (size_t)(e0 + e) * d + cb + 4 * c4);
+      s_wr[(e * 2 + (c4 & 1)) * kWave + (c4 >> 1)] = w;
+    }
+    __syncthreads();
+  };
+  stage(0);
+  const int t_first = blockIdx.x * tok_per_block, t_end = min(T, t_first + tok_per_block);
+  // every wavefront makes every trip (there are barriers below); tokens past the end and columns past d are not stored
+  for (int tb = t_first; tb < t_end; tb += kDxWaves * 4) {
+    const int t0 = tb + wave * 4;
     float acc[4][8] = {};
     // slot by slot, the four tokens' rows in flight together; a dropped pair (or a token past
     // the end) reads row 0 and adds zero
@@ -340,49 +346,38 @@ __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT
         const int t = t0 + q;
         const int r = t < t_end ? inv_pos[(size_t)t * k + j] : -1;
         have[q] = r >= 0;
-        RowVec<XT, 8>::ld_stream(dxs + (size_t)max(r, 0) * d + c0, v[q]);
+        RowVec<XT, 8>::ld_stream(dxs + (size_t)max(r, 0) * d + cc, v[q]);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[q][i] += have[q] ? v[q][i] : 0.f;
     }
-    for (int e = 0; e < E; ++e) {
-      const f32x4 wa = s_wr[(e * 2) * kWave + lane], wb = s_wr[(e * 2 + 1) * kWave + lane];
+    for (int e0 = 0; e0 < E; e0 += kDxLdsE) {
+      if (e0 > 0) {                                     // only with one trip per workgroup (tok_per_block = 32)
+        __syncthreads();                                // everybody is done with the slice in place
+        stage(e0);
+      }
+      for (int e = 0; e < min(E - e0, kDxLdsE); ++e) {
+        const f32x4 wa = s_wr[(e * 2) * kWave + lane], wb = s_wr[(e * 2 + 1) * kWave + lane];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float w = ds[(size_t)min(t0 + q, T - 1) * E + e];   // uniform across the wavefront
+        for (int q = 0; q < 4; ++q) {
+          const float w = ds[(size_t)min(t0 + q, T - 1) * E + e0 + e];   // uniform across the wavefront
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[q][i] = fmaf(w, wa[i], acc[q][i]);
-          acc[q][4 + i] = fmaf(w, wb[i], acc[q][4 + i]);
+          for (int i = 0; i < 4; ++i) {
+            acc[q][i] = fmaf(w, wa[i], acc[q][i]);
+            acc[q][4 + i] = fmaf(w, wb[i], acc[q][4 + i]);
+          }
         }
       }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (t0 + q < t_end) RowVec<XT, 8>::st_stream(dX + (size_t)(t0 + q) * d + c0, acc[q]);
+      if (t0 + q < t_end && c0 < d) RowVec<XT, 8>::st_stream(dX + (size_t)(t0 + q) * d + c0, acc[q]);
   }
 }
 
-// More dynamic LDS than the default limit from 33 experts on: raised once per device, which may not happen inside a
-// stream capture (router_bwd_prepare() does it up front); threads racing here store the same value.
-int raise_dx_lds_limit() {
-  static bool done[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BTX_ERR_HIP;
-  if (done[dev]) return BTX_OK;
-  const int bytes = kMaxExperts * kDxCols * (int)sizeof(float);
-  for (const void* kernel : {reinterpret_cast<const void*>(dx_finish_lds_kernel<bf16_t>),
-                             reinterpret_cast<const void*>(dx_finish_lds_kernel<float>)})
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return BTX_ERR_HIP;
-  done[dev] = true;
-  return BTX_OK;
-}
-
 }  // namespace
-
-int router_bwd_prepare() { return raise_dx_lds_limit(); }
 
 // token chunk of the dW_router partial sums: longer chunks for many experts keep the partials
 // (chunks * d * E floats) small next to x
@@ -408,8 +403,6 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
   w += align_up((size_t)nch * a.E * sizeof(float), 256);
   float* WrT = reinterpret_cast<float*>(w);
 
-  if (a.E > 32)
-    if (int rc = raise_dx_lds_limit()) return rc;
   if ((int64_t)a.d * a.E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
   router_ds_kernel<<<ceil_div(a.T, 4) + ceil_div(a.d * a.E, 256), 256, 0, s>>>(
                                                    a.W_router, a.d, WrT, a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
@@ -459,9 +452,10 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
     else if (a.E <= 8) { if (few) BTX_DX_LAUNCH(8, 4); else BTX_DX_LAUNCH(8, 16); }
     else {
       // tokens per workgroup, for which the slice is staged once: fewer where the chip would be left idle
-      const int cols = ceil_div(a.d, kDxCols), tok = ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
+      const int cols = ceil_div(a.d, kDxCols);
+      const int tok = a.E <= kDxLdsE && ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
       dx_finish_lds_kernel<XT><<<dim3(ceil_div(a.T, tok), cols), kDxWaves * kWave,
-                                 (size_t)a.E * kDxCols * sizeof(float), s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k,
+                                 (size_t)std::min(a.E, kDxLdsE) * kDxCols * sizeof(float), s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k,
                                                                               tok, dX);
     }
 #undef BTX_DX_LAUNCH
