@@ -122,11 +122,12 @@ __device__ __forceinline__ void select_experts(float s, bool live, int lane, int
   if (live) probs[(size_t)t * E + lane] = p;
   psum += p;
   if (mode == BTX_ROUTE_TOPK_RENORM) {
-    float cand = s;
+    // k different experts whatever the logits are, so that every slot is written: a NaN counts as -infinity, and an
+    // expert that is taken (or does not exist) comes after every other one of that value
+    Best mine = live && s == s ? Best{s, lane} : Best{-INFINITY, live ? lane : lane + kWave};
     int my_slot = -1;
     for (int j = 0; j < k; ++j) {
-      const Best b = wave_best(Best{cand, lane});
-      if (lane == b.i) { my_slot = j; cand = -INFINITY; }
+      if (wave_best(mine).i == lane) { my_slot = j; mine = Best{-INFINITY, lane + kWave}; }
     }
     const float zsel = wave_sum(my_slot >= 0 ? z : 0.f);
     if (my_slot >= 0) {
@@ -248,8 +249,7 @@ __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
 }
 
 // One workgroup: statistics, offsets and lb_loss, and the stable grouping of the pairs.  The rank of a pair among its
-// expert's comes from ballots, 1024 pairs a round; it waits in inv_pos until the offsets are known.  A slot that no
-// expert was written to (rows with NaN logits leave such slots) is nobody's pair and gets row 0.
+// expert's comes from ballots, 1024 pairs a round; it waits in inv_pos until the offsets are known.
 __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
     int T, int E, int k, int cap, int lb_mode, float lb_alpha, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ gates, const float* __restrict__ probs, int32_t* __restrict__ counts,
@@ -269,8 +269,7 @@ __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
     for (int i = threadIdx.x; i < n * E; i += kGroupThreads) s_dense[i] = 0.f;
     __syncthreads();
     for (int i = threadIdx.x; i < n * k; i += kGroupThreads) {
-      const int e = topk_idx[t0 * k + i];
-      if ((unsigned)e < (unsigned)E) s_dense[(i / k) * E + e] = gates[t0 * k + i];
+      s_dense[(i / k) * E + topk_idx[t0 * k + i]] = gates[t0 * k + i];
     }
     __syncthreads();
     if (lane < E)
@@ -286,7 +285,7 @@ __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
   // ---- ranks
   int running = 0;                                      // wavefront 0, lane e: pairs of expert e so far
   for (int i0 = 0; i0 < R; i0 += kGroupThreads) {
-    const int i = i0 + threadIdx.x, idx = i < R ? topk_idx[i] : -1, e = (unsigned)idx < (unsigned)E ? idx : -1;
+    const int i = i0 + threadIdx.x, e = i < R ? topk_idx[i] : -1;
     int local = 0, mine = 0;
     for (int q = 0; q < E; ++q) {
       const unsigned long long m = __ballot(e == q);
@@ -329,13 +328,11 @@ __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
   }
   __syncthreads();
   for (int i = threadIdx.x; i < R; i += kGroupThreads) {          // the thread that left the rank reads it back
-    const int e = topk_idx[i];
-    const bool known = (unsigned)e < (unsigned)E;
-    const int rank = known ? inv_pos[i] : 0;
+    const int rank = inv_pos[i];
     if (cap > 0 && rank >= cap) {
       inv_pos[i] = -1;                                  // beyond the expert's capacity: dropped
     } else {
-      const int pos = known ? s_first[e] + rank : 0;
+      const int pos = s_first[topk_idx[i]] + rank;
       perm[pos] = i;
       inv_pos[i] = pos;
     }

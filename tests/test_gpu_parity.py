@@ -373,6 +373,37 @@ def test_routing_takes_a_router_matrix_at_any_float(E):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("T", [300, 1500])               # two launches, four launches
+@pytest.mark.parametrize("E,k", [(4, 2), (12, 5)])
+@pytest.mark.parametrize("broken", ["row", "expert"])
+def test_routing_of_nan_logits_fills_every_slot(T, E, k, broken):
+    """A row (or one expert's column of W_router) that holds NaN: its gates mean nothing, but k different experts are chosen,
+    whatever the output buffers held before, and the other rows are routed as ever."""
+    L = to_dev(synth.make_layer(T, 64, 64, E, dtype=F32))
+    clean = B.btx_moe_route(L["x"], L["W_router"], None, None, k)
+    if broken == "row":
+        L["x"][7] = float("nan")
+    else:
+        L["W_router"][:, 1] = float("nan")
+    runs = []
+    for fill in (1, 3):
+        r = B.alloc_routing(T, E, k, "cuda")
+        for t in vars(r).values():
+            t.fill_(fill)
+        B.btx_moe_route(L["x"], L["W_router"], None, None, k, out=r)
+        runs.append(r)
+    for a, b in zip(vars(runs[0]).values(), vars(runs[1]).values()):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    idx = runs[0].topk_idx.long()
+    assert bool(((idx >= 0) & (idx < E)).all()) and bool((idx.sort(dim=1).values.diff(dim=1) > 0).all())
+    assert torch.equal(runs[0].counts.long(), torch.bincount(idx.flatten(), minlength=E))
+    assert torch.equal(runs[0].perm.sort().values, torch.arange(T * k, dtype=torch.int32, device="cuda"))
+    assert torch.equal(runs[0].perm[runs[0].inv_pos.flatten().long()], torch.arange(T * k, dtype=torch.int32, device="cuda"))
+    if broken == "row":
+        rest = torch.arange(T, device="cuda") != 7
+        assert torch.equal(idx[rest], clean.topk_idx.long()[rest]) and torch.equal(runs[0].gates[rest], clean.gates[rest])
+
+
 def test_bf16_unrelated_experts_meet_the_plain_bar_on_router_gradients():
     """With experts that share nothing the gate Jacobian has no cancellation and
     dW_router / db_router must meet 2e-2 without any amplification factor."""
