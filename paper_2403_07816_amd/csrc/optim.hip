@@ -77,21 +77,20 @@ int launch_adamw(float* P, float* M, float* V, const void* G, int grad_dtype, vo
                  float beta1, float beta2, float eps, float wd, hipStream_t s) {
   AdamArgs a{lr, beta1, beta2, eps, wd, (float)(1.0 / (1.0 - std::pow((double)beta1, step))),
              (float)(1.0 / (1.0 - std::pow((double)beta2, step)))};
-  const int64_t blocks = std::max<int64_t>((n / 4 + 255) / 256, 1);
-  if (blocks > 0x7fffffff) return BTX_ERR_UNSUPPORTED;
-  auto go = [&](auto tag, auto stream) {
+  // A launch holds fewer than 2^32 threads: longer tensors (2^34 elements, 240 GB of state and gradients) take several.
+  constexpr int64_t kPiece = (((int64_t)1 << 24) - 1) * 256 * 4;
+  auto go = [&](auto tag, auto stream) -> int {
     using GT = decltype(tag);
-    adamw_kernel<GT, decltype(stream)::value><<<(unsigned)blocks, 256, 0, s>>>(P, M, V, static_cast<const GT*>(G),
-                                                                             static_cast<bf16_t*>(lowp), n, a);
+    for (int64_t i = 0; i < n; i += kPiece) {
+      const int64_t left = std::min(n - i, kPiece), blocks = std::max<int64_t>((left / 4 + 255) / 256, 1);
+      adamw_kernel<GT, decltype(stream)::value><<<(unsigned)blocks, 256, 0, s>>>(
+          P + i, M + i, V + i, static_cast<const GT*>(G) + i, lowp ? static_cast<bf16_t*>(lowp) + i : nullptr, left, a);
+      BTX_LAUNCH_CHECK();
+    }
+    return BTX_OK;
   };
-  auto by_size = [&](auto tag) {
-    if (n * 12 >= kStreamFrom) go(tag, std::true_type{});
-    else go(tag, std::false_type{});
-  };
-  if (grad_dtype == BTX_BF16) by_size(bf16_t{});
-  else by_size(float{});
-  BTX_LAUNCH_CHECK();
-  return BTX_OK;
+  auto by_size = [&](auto tag) { return n * 12 >= kStreamFrom ? go(tag, std::true_type{}) : go(tag, std::false_type{}); };
+  return grad_dtype == BTX_BF16 ? by_size(bf16_t{}) : by_size(float{});
 }
 
 }  // namespace btx
