@@ -53,7 +53,7 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   // transposed path: dW2 reads ga as [f][padded rows]
   w.ga = c.take(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : R * f * es);
   w.dxs = c.take(R * d * es);
-  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials(dtype, sh) * sizeof(float)));
+  w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials_most(dtype, f) * sizeof(float)));
   w.router = c.take(router_bwd_workspace_bytes(T, d, E));
   const size_t split = ff_backward_split_bytes(dtype, sh);   // sums of K slices
   w.partial = split ? c.take(split) : nullptr;

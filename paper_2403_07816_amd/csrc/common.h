@@ -255,8 +255,8 @@ int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void*
                      const FfShapes& sh, void* h1, void* h3, void* act, void* partial, hipStream_t s);
 // partial (here, in launch_down and in launch_bwd_dx): ff_forward_split_bytes() / ff_backward_split_bytes() of scratch
 // for the sums of products that are cut along K (the tiles of a partly filled last round, or all tiles of a small
-// product; a second kernel adds the slices); may be NULL when that is 0.  Products that follow each other on a
-// stream may share it.
+// product; a second kernel adds the slices); may be NULL when that is 0.  Never less for more rows.  Products that follow
+// each other on a stream may share it.
 size_t ff_forward_split_bytes(int dtype, const FfShapes& sh);
 size_t ff_backward_split_bytes(int dtype, const FfShapes& sh);
 // y = act W2
@@ -265,8 +265,10 @@ int launch_down(int dtype, const void* act, const void* W2, const int32_t* offse
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.
 // dh1, dh3: [R,f].  When ff_dw_transposed() holds, `ga` receives g*a transposed and padded
 // ([f][ff_dw_pitch()]), or nothing at all when want_dw is false; otherwise ga is [R,f].
-// bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile)
+// bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile), and the
+// most that any number of rows gets (fewer rows may run with narrower tiles)
 int bwd_act_partials(int dtype, const FfShapes& sh);
+int bwd_act_partials_most(int dtype, int f);
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
                    bool want_dw, float* dg_part, hipStream_t s);

@@ -23,6 +23,7 @@
 // LDS writes and reads 8 % each.
 #include "gemm_f32.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace btx {
@@ -392,6 +393,9 @@ template <int BM, int BN, int BK, int MODE> __global__ __launch_bounds__(kThread
 // slower on this library's fp32 shapes: with 4006 rows, d = 512, f = 1376 DOWN 115 / 111 us against 84, DW13 151 / 142
 // against 138.
 constexpr int kTile = 64, kTileK = 32, kMaxSlices = 8;
+// (tile, slice) pairs of a product that is cut, 16 for a compute unit: no product that gains from the cut has more (2304 seen
+// over d, f up to 512, 1376), and the sums' scratch has a bound of its own, 64 MB
+constexpr int64_t kMaxSliceTiles = 4096;
 
 // The K slices of a product added in slice order, 4 columns of a row per thread.
 __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N,
@@ -411,20 +415,35 @@ __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float
 // K slices of DOWN and BWD_DX.  Few tiles of many k tiles leave compute units idle, or some with a tile more than others.
 // Measured on 64 x 64 tiles of 32 k: with r tiles on a compute unit a k tile takes about 0.35 us for every four of them and
 // 0.55 us each; the slices' sums pass through memory once more, in a launch of its own.  64 tokens, 8 experts of 512 x
-// 1376, top-2: DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: what the caller's scratch holds.
+// 1376, top-2: DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: see most_slices().
 int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
   const int busy = std::max(std::min(E, R), 1);
   const int64_t tiles = (int64_t)busy * ceil_div(ceil_div(R, busy), kTile) * ceil_div(N, kTile);
   const double nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
   int best = 1;
   double best_us = 0;
-  for (int n = 1; n <= std::min(most, kMaxSlices); ++n) {
-    if (n > 1 && ((two_passes && n % 2) || n > nk / 2)) continue;
+  for (int n = 1; n <= most; ++n) {
+    if (n > 1 && ((two_passes && n % 2) || n > nk / 2 || n * tiles > kMaxSliceTiles)) continue;
     const double r = (double)ceil_div(tiles * n, 256), per_k = 0.35 * std::ceil(r / 4) + 0.55 * r;
     const double us = per_k * (nk / n + 1) + (n > 1 ? 5.0 + 8e-6 / 4 * n * (double)R * N : 0.0);
     if (n == 1 || us < best_us) { best = n; best_us = us; }
   }
   return best;
+}
+
+// No more scratch than two rows of d and three of f per grouped row.
+int most_slices(const FfShapes& sh, bool two_passes) {
+  const int by_k = ceil_div(sh.f, kTileK) * (two_passes ? 2 : 1) / 2, by_scratch = two_passes ? 2 + sh.f / sh.d : 1 + 2 * sh.f / sh.d;
+  return std::min({kMaxSlices, by_k, by_scratch});
+}
+// Scratch of the sums for up to sh.R rows: what any number of rows up to that asks for, so that a workspace of a large batch
+// serves every smaller one (fewer rows may be cut into more slices).
+size_t sums_bytes(const FfShapes& sh, bool two_passes) {
+  const int most = most_slices(sh, two_passes);
+  return most < 2 ? 0 : std::min((size_t)most * sh.R * sh.d, (size_t)kMaxSliceTiles * kTile * kTile) * sizeof(float);
+}
+int slices_of(const FfShapes& sh, bool two_passes) {
+  return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
 }
 
 template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
@@ -452,9 +471,8 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
 
 bool f32_rows_ok(int R, int E) { return ceil_div(R, 64) + E <= 65535; }
 int f32_bwd_act_partials(int f) { return ceil_div(f, kTile); }
-// no more scratch than two rows of d and three of f per grouped row
-int f32_down_slices(const FfShapes& sh) { return f32_slices(sh.R, sh.E, sh.d, sh.f, false, 1 + 2 * sh.f / sh.d); }
-int f32_bwd_dx_slices(const FfShapes& sh) { return f32_slices(sh.R, sh.E, sh.d, sh.f, true, 2 + sh.f / sh.d); }
+size_t f32_down_sums_bytes(const FfShapes& sh) { return sums_bytes(sh, false); }
+size_t f32_bwd_dx_sums_bytes(const FfShapes& sh) { return sums_bytes(sh, true); }
 
 int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh, void* h1,
                   void* h3, void* act, hipStream_t s) {
@@ -466,7 +484,7 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
 }
 int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, hipStream_t s) {
   FArgs g{};
-  g.slices = f32_down_slices(sh); g.sums = (float*)sums;
+  g.slices = slices_of(sh, false); g.sums = (float*)sums;
   g.A0 = (const float*)act; g.B0 = (const float*)W2; g.C0 = (float*)y;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideB_e = sh.s2;
   return launch<DOWN>(g, sh.R, s);
@@ -485,7 +503,7 @@ int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void
 int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                void* dxs, void* sums, hipStream_t s) {
   FArgs g{};
-  g.slices = f32_bwd_dx_slices(sh); g.sums = (float*)sums;
+  g.slices = slices_of(sh, true); g.sums = (float*)sums;
   g.A0 = (const float*)dh1; g.A1 = (const float*)dh3; g.B0 = (const float*)W1; g.B1 = (const float*)W3; g.C0 = (float*)dxs;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d; g.strideB_e = sh.s13;
   return launch<BWD_DX>(g, sh.R, s);

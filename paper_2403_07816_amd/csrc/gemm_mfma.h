@@ -8,6 +8,7 @@ int mfma_prepare();
 // the weight-gradient products address 255 rows of the transposed, padded operands with 32-bit byte offsets
 bool mfma_rows_ok(int R, int E);
 int mfma_bwd_act_partials(const FfShapes& sh);
+int mfma_bwd_act_partials_most(int f);
 // gathered A rows need every byte offset inside the source to fit 32 bits
 bool mfma_gather_ok(int T, int d);
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,

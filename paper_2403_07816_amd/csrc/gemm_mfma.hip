@@ -1395,6 +1395,7 @@ int mfma_bwd_act_partials(const FfShapes& sh) {
   g.R = sh.R; g.E = sh.E; g.N = sh.f; g.K = sh.d;
   return ceil_div(sh.f, row_tile<BWD_ACT>(g) == 256 ? 256 : 128);
 }
+int mfma_bwd_act_partials_most(int f) { return ceil_div(f, 128); }
 
 bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 < ((int64_t)1 << 32); }
 

@@ -35,3 +35,16 @@ def test_adamw_takes_tensors_of_any_length(record, n, dtype):
         assert launch.first == P + 4 * done and done % 4 == 0       # the master weights of this piece
         done += launch.grid[0] * 1024                               # at most; the last workgroup may hold fewer
     assert done - 1024 < n <= done + 3                              # (up to 3 trailing elements go to the first workgroup)
+
+
+def test_a_workspace_for_many_tokens_serves_fewer(record):
+    """Programs size their workspace for the largest batch: no query may fall as the number of tokens grows."""
+    shapes = [(512, 1376, 8, 2), (64, 2056, 3, 2), (4096, 688, 64, 8), (2048, 5504, 8, 2), (72, 96, 4, 1), (1032, 264, 64, 4)]
+    tokens = sorted({1, 2, 3, 17, 40, 64, 100, 255, 256, 440, 700, 768, 769, 880, 881, 882, 1000, 1345, 1500, 2003, 2304, 2305, 2561,
+                     3000, 4001, 4096, 16384, *range(216, 232), *range(840, 884)})
+    calls = [(f"btx_moe_ff_{which}_workspace_bytes", [T, d, f, E, k, dtype])
+             for which in ("forward", "backward") for d, f, E, k in shapes for dtype in (B.BTX_F32, B.BTX_BF16) for T in tokens]
+    sizes = [rc for rc, _ in record(*calls)]
+    for (name, args), size, (next_name, next_args), next_size in zip(calls, sizes, calls[1:], sizes[1:]):
+        if name == next_name and args[1:] == next_args[1:]:
+            assert size <= next_size, f"{name}: {args} {size} bytes, {next_args} {next_size}"
