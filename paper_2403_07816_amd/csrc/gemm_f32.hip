@@ -393,9 +393,9 @@ template <int BM, int BN, int BK, int MODE> __global__ __launch_bounds__(kThread
 // slower on this library's fp32 shapes: with 4006 rows, d = 512, f = 1376 DOWN 115 / 111 us against 84, DW13 151 / 142
 // against 138.
 constexpr int kTile = 64, kTileK = 32, kMaxSlices = 8;
-// (tile, slice) pairs of a product that is cut, 16 for a compute unit: no product that gains from the cut has more (2304 seen
-// over d, f up to 512, 1376), and the sums' scratch has a bound of its own, 64 MB
-constexpr int64_t kMaxSliceTiles = 4096;
+// floats that the slices' sums of a product may take (128 MB): the cut pays while tiles are few, and the scratch has a bound of
+// its own
+constexpr int64_t kMaxSums = (int64_t)1 << 25;
 
 // The K slices of a product added in slice order, 4 columns of a row per thread.
 __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N,
@@ -423,7 +423,7 @@ int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
   int best = 1;
   double best_us = 0;
   for (int n = 1; n <= most; ++n) {
-    if (n > 1 && ((two_passes && n % 2) || n > nk / 2 || n * tiles > kMaxSliceTiles)) continue;
+    if (n > 1 && ((two_passes && n % 2) || n > nk / 2 || (int64_t)n * R * N > kMaxSums)) continue;
     const double r = (double)ceil_div(tiles * n, 256), per_k = 0.35 * std::ceil(r / 4) + 0.55 * r;
     const double us = per_k * (nk / n + 1) + (n > 1 ? 5.0 + 8e-6 / 4 * n * (double)R * N : 0.0);
     if (n == 1 || us < best_us) { best = n; best_us = us; }
@@ -440,7 +440,7 @@ int most_slices(const FfShapes& sh, bool two_passes) {
 // serves every smaller one (fewer rows may be cut into more slices).
 size_t sums_bytes(const FfShapes& sh, bool two_passes) {
   const int most = most_slices(sh, two_passes);
-  return most < 2 ? 0 : std::min((size_t)most * sh.R * sh.d, (size_t)kMaxSliceTiles * kTile * kTile) * sizeof(float);
+  return most < 2 ? 0 : std::min((size_t)most * sh.R * sh.d, (size_t)kMaxSums) * sizeof(float);
 }
 int slices_of(const FfShapes& sh, bool two_passes) {
   return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
