@@ -26,10 +26,10 @@ int bwd_act_partials(int dtype, const FfShapes& sh) {
 int bwd_act_partials_most(int dtype, int f) { return dtype == BTX_BF16 ? mfma_bwd_act_partials_most(f) : f32_bwd_act_partials(f); }
 
 size_t ff_forward_split_bytes(int dtype, const FfShapes& sh) {
-  return dtype == BTX_BF16 ? mfma_split_bytes() : f32_down_sums_bytes(sh);
+  return dtype == BTX_BF16 ? mfma_forward_split_bytes(sh) : f32_down_sums_bytes(sh);
 }
 size_t ff_backward_split_bytes(int dtype, const FfShapes& sh) {
-  return dtype == BTX_BF16 ? mfma_split_bytes() : f32_bwd_dx_sums_bytes(sh);
+  return dtype == BTX_BF16 ? mfma_backward_split_bytes(sh) : f32_bwd_dx_sums_bytes(sh);
 }
 
 int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void* W3, const int32_t* offsets,

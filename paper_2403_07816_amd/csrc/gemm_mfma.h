@@ -11,10 +11,12 @@ int mfma_bwd_act_partials(const FfShapes& sh);
 int mfma_bwd_act_partials_most(int f);
 // gathered A rows need every byte offset inside the source to fit 32 bits
 bool mfma_gather_ok(int T, int d);
+// partial: scratch for the sums of K slices, of mfma_forward_split_bytes() (mfma_backward_split_bytes() in mfma_bwd_dx); NULL
+// when that is 0
+size_t mfma_forward_split_bytes(const FfShapes& sh);
+size_t mfma_backward_split_bytes(const FfShapes& sh);
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                    void* h1, void* h3, void* act, void* partial, hipStream_t s);
-// partial: mfma_split_bytes() of scratch for the K slices of the last round (NULL: tiles are never cut)
-size_t mfma_split_bytes();
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
               hipStream_t s);
 // dh1, dh3: [R,f]; gaT: [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to multiples of 64

@@ -39,10 +39,10 @@
 namespace btx {
 
 // fp32 accumulators of the K slices of the last round of UP / DOWN / BWD_DX: at most cus + 8 * 8 (tile, slice) pairs
-// of 256 x 256 floats.  Small tiles keep their slices' sums here too, as many as fit.
+// of 256 x 256 floats.  Small tiles keep their slices' sums here too, as many as fit (see split_bytes()).
 constexpr int kSplitMaxSlices = 8;
 constexpr int kSplitMaxCus = 256;   // compute units the K-cut of a last round is laid out for (see Gemm::split_plan)
-size_t mfma_split_bytes() { return (size_t)(kSplitMaxCus + 8 * kSplitMaxSlices) * 256 * 256 * sizeof(float); }
+constexpr size_t kSplitBytes = (size_t)(kSplitMaxCus + 8 * kSplitMaxSlices) * 256 * 256 * sizeof(float);
 
 namespace {
 
@@ -1247,7 +1247,7 @@ int even_row_tiles(const MArgs& g, int BM) {
 // at least 8 k tiles, and no more than the caller's scratch holds.  DOWN of 16 tokens (4 experts of 11008 x 4096, 128
 // tiles): 2 slices 68 us, 4 (two workgroups per unit) 73.
 int small_slices(int64_t tiles, int nk, size_t bytes_per_slice) {
-  const int64_t fill = kSplitMaxCus / std::max<int64_t>(tiles, 1), fit = (int64_t)(mfma_split_bytes() / bytes_per_slice);
+  const int64_t fill = kSplitMaxCus / std::max<int64_t>(tiles, 1), fit = (int64_t)(kSplitBytes / bytes_per_slice);
   return (int)std::max<int64_t>(std::min({fill, fit, (int64_t)(nk / 8), (int64_t)kSplitMaxSlices}), 1);
 }
 
@@ -1290,17 +1290,31 @@ template <int BM, int MODE, int TAIL> int launch_small(MArgs g, bool prepare_onl
 // A product of few 256-row tiles that are also too short to be cut along K into pieces of 32 k tiles leaves compute
 // units idle (1200 rows, 4 experts of 4096 x 1376: UP 76 us, DOWN 39, BWD_ACT 88, BWD_DX 68); with 128-row tiles 58, 34,
 // 55, 50; with 64-row tiles 67, 38, 37, 60: the smaller ones are taken, of 64 rows where those of 128 are too few as well.
+constexpr int kSmallRows = 110;                          // rows per expert up to which a product takes small tiles
+constexpr int64_t kEnough = 192;                         // workgroups of three quarters of the compute units
 template <int MODE> int row_tile(const MArgs& g) {
   constexpr bool DUAL = MODE == UP;
-  constexpr int64_t kEnough = 192;                       // workgroups of three quarters of the compute units
   const int64_t avg = g.R / std::max(g.E, 1);
   if (avg <= 48) return 64;
-  if (avg <= 110) return 128;
+  if (avg <= kSmallRows) return 128;
   const int64_t tiles = (int64_t)even_row_tiles(g, 256) * ceil_div(g.N, DUAL ? 128 : 256);
   const int64_t pieces = MODE == BWD_ACT || !g.partial ? 1 : ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1) / 32;
   if (tiles * std::max<int64_t>(std::min(pieces, kSplitMaxCus / std::max<int64_t>(tiles, 1)), 1) >= kEnough)
     return MODE != BWD_ACT && avg <= 168 ? 192 : 256;
   return (int64_t)even_row_tiles(g, 128) * ceil_div(g.N, DUAL ? 64 : 128) >= kEnough ? 128 : 64;
+}
+
+// Scratch for the K slices of a product of up to R rows, or of any smaller number of them.  Small tiles (at most one (tile,
+// slice) pair of 128 x 128 sums for a compute unit; small_slices()) may be cut at any number of rows; the last round of larger
+// tiles only with rows enough for those and K for two slices (row_tile(), split_plan()).
+template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
+  MArgs g{};
+  g.R = R; g.E = E;
+  const int nk = ceil_div(K, 64) * (MODE == BWD_DX ? 2 : 1), slices = std::min(nk / 8, kSplitMaxSlices);
+  if (R / std::max(E, 1) > kSmallRows && nk >= 2 * Gemm<256, 256, 64, 2, 4, 3, 2, MODE>::kMinSliceTiles &&
+      even_row_tiles(g, 256) * (int64_t)ceil_div(N, MODE == UP ? 128 : 256) * (nk / 32) >= kEnough)
+    return kSplitBytes;
+  return slices < 2 ? 0 : std::min((size_t)slices * R * N * (MODE == UP ? 8 : 4), (size_t)kSplitMaxCus * 128 * 128 * sizeof(float));
 }
 
 // the instantiation for this K (see TAIL) and row tile
@@ -1396,6 +1410,11 @@ int mfma_bwd_act_partials(const FfShapes& sh) {
   return ceil_div(sh.f, row_tile<BWD_ACT>(g) == 256 ? 256 : 128);
 }
 int mfma_bwd_act_partials_most(int f) { return ceil_div(f, 128); }
+
+size_t mfma_forward_split_bytes(const FfShapes& sh) {
+  return std::max(split_bytes<UP>(sh.R, sh.E, sh.f, sh.d), split_bytes<DOWN>(sh.R, sh.E, sh.d, sh.f));
+}
+size_t mfma_backward_split_bytes(const FfShapes& sh) { return split_bytes<BWD_DX>(sh.R, sh.E, sh.d, sh.f); }
 
 bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 < ((int64_t)1 << 32); }
 

@@ -338,6 +338,28 @@ def test_bf16_row_tiles(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,dtype", [
+    (16, 4096, 1024, 4, 2, BF16), (301, 1032, 4104, 4, 2, BF16), (33, 72, 2056, 4, 2, BF16), (40, 2056, 72, 5, 2, BF16),
+    (900, 256, 2048, 4, 1, BF16), (210, 2056, 520, 4, 2, BF16), (260, 4104, 768, 16, 8, BF16), (2050, 1032, 8192, 2, 1, BF16),
+    (64, 512, 1376, 8, 2, F32), (768, 512, 1376, 8, 2, F32), (1, 64, 2056, 3, 2, F32), (2003, 264, 1376, 4, 2, F32)])
+def test_nothing_is_written_behind_the_workspace(T, d, f, E, k, dtype):
+    """Workspaces of exactly the size that the queries return, products cut along K of every kind."""
+    lib, code = B.load_library(), B.BTX_BF16 if dtype == BF16 else B.BTX_F32
+    L = synth.make_layer(T, d, f, E, dtype=dtype, device="cuda", unit_rms=True, with_dY=True)
+    r = B.btx_moe_route(L["x"], L["W_router"], None, None, k)
+    behind = 128 << 20
+
+    def workspace(nbytes):
+        whole = torch.full((nbytes + behind,), 0xA5, dtype=torch.uint8, device="cuda")
+        return whole[:nbytes], whole[nbytes:]
+    ws, after = workspace(lib.btx_moe_ff_forward_workspace_bytes(T, d, f, E, k, code))
+    out, h1, h3 = B.btx_moe_ff_forward(L["x"], L["W1"], L["W3"], L["W2"], r, workspace=ws)
+    assert bool((after == 0xA5).all())
+    ws, after = workspace(lib.btx_moe_ff_backward_workspace_bytes(T, d, f, E, k, code))
+    B.btx_moe_ff_backward(L["dY"], L["x"], L["W_router"], L["W1"], L["W3"], L["W2"], r, h1, h3, workspace=ws)
+    assert bool((after == 0xA5).all())
+
+
 @pytest.mark.parametrize("T,d,f,E,k,kw", [
     # strips: no rows at all for some experts, one k tile, several k tiles (skewed), partial row panels and column tiles
     (3, 136, 264, 64, 2, {}), (64, 256, 192, 8, 2, {}), (100, 264, 136, 8, 4, dict(bias=[3.0] + [0.0] * 7)),

@@ -48,3 +48,13 @@ def test_a_workspace_for_many_tokens_serves_fewer(record):
     for (name, args), size, (next_name, next_args), next_size in zip(calls, sizes, calls[1:], sizes[1:]):
         if name == next_name and args[1:] == next_args[1:]:
             assert size <= next_size, f"{name}: {args} {size} bytes, {next_args} {next_size}"
+
+
+@pytest.mark.parametrize("T,d,f,E,k,forward_kb,backward_kb", [(1, 1032, 264, 64, 4, 64, 22000), (16, 264, 200, 4, 2, 64, 700),
+                                                              (70, 8, 8, 2, 1, 64, 64), (301, 520, 392, 4, 2, 3000, 6000)])
+def test_bf16_workspaces_of_small_layers_are_small(record, T, d, f, E, k, forward_kb, backward_kb):
+    """The sums of K slices take what these products can need, not the 84 MB of the largest ones."""
+    (forward, _), (backward, _) = record(*((f"btx_moe_ff_{which}_workspace_bytes", [T, d, f, E, k, B.BTX_BF16])
+                                           for which in ("forward", "backward")))
+    assert 0 < forward <= forward_kb << 10
+    assert 0 < backward <= backward_kb << 10
