@@ -1379,7 +1379,11 @@ template <int MODE> int launch_dw(const MArgs& g, bool strip, bool stream, bool 
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false>(g, prepare_only, s);
 }
 template <int MODE> int launch_dw(const MArgs& g, hipStream_t s) {
-  return launch_dw<MODE>(g, g.R / g.E <= 64, g.N % (g.c_is_f32 ? 32 : 64) == 0, false, s);
+  const bool strip = g.R / g.E <= 64, rows_of_lines = g.N % (g.c_is_f32 ? 32 : 64) == 0;
+  // strips: streamed from half lines on (300 tokens, 64 experts of 4096 x 688, dW2 shifted by 64 bytes: the backward pass 748
+  // us with plain stores, 729 streamed), not from any 16-byte piece (761, 862); tiles: streamed anyhow (1501 tokens: 1066, 1054)
+  const bool halves = ((uintptr_t)g.C0 % 64 | (uintptr_t)g.C1 % 64 | (uintptr_t)(g.strideC_e * (g.c_is_f32 ? 4 : 2)) % 64) == 0;
+  return launch_dw<MODE>(g, strip, rows_of_lines && (!strip || halves), false, s);
 }
 template <int MODE> int prepare_dw() {
   MArgs g{};

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2403_07816_amd import binding as B
 
-from launches import P, adamw_call, launches
+from launches import P, adamw_call, backward_call, launches
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -58,3 +58,17 @@ def test_bf16_workspaces_of_small_layers_are_small(record, T, d, f, E, k, forwar
                                            for which in ("forward", "backward")))
     assert 0 < forward <= forward_kb << 10
     assert 0 < backward <= backward_kb << 10
+
+
+@pytest.mark.parametrize("dW_dtype", [B.BTX_F32, B.BTX_BF16])
+def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_dtype):
+    """The strips' stores go past the caches where every row starts on 64 bytes: not for a stack that starts on any other 16-byte
+    piece, nor with an expert stride that shifts the others there."""
+    def streamed(T, dW2=P, stride=None):
+        (rc, found), = record(backward_call(T, 256, 192, 8, 2, B.BTX_BF16, dW_dtype=dW_dtype, dW2=dW2, stride=stride))
+        last = [n.kernel for n in found if "dw_strip" in n.kernel or ", 5, 0, " in n.kernel][-1]
+        assert rc == 0 and ("strip" in last) == (T == 100)
+        return last.endswith("true>")
+    assert streamed(100) and streamed(100, dW2=P + 64) and streamed(100, stride=256 * 192 + 32)
+    assert not streamed(100, dW2=P + 16) and not streamed(100, stride=256 * 192 + 8)
+    assert streamed(1500) and streamed(1500, dW2=P + 16)          # 256 x 256 tiles: from anywhere
