@@ -206,6 +206,8 @@ struct RowTiles {
 };
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+// a launch holds fewer than 2^32 threads in each direction of its grid
+inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < (int64_t)1 << 32; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 #define BTX_LAUNCH_CHECK()                                   \

@@ -455,7 +455,7 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
   g.R = R;
   const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
                         (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, BM) + g.E);   // at most this many
-  if (tiles > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
+  if (!grid_fits(tiles + 7, kThreads)) return BTX_ERR_UNSUPPORTED;
   const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
   f32_gemm_kernel<BM, BN, BK, MODE><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();

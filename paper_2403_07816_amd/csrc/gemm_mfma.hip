@@ -1267,7 +1267,7 @@ template <int BM, int MODE, int TAIL> int launch_small(MArgs g, bool prepare_onl
     g.slices = small_slices((int64_t)even_row_tiles(g, BM) * g.tiles_n, ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1),
                             (size_t)g.R * g.N * (MODE == UP ? 8 : 4));
   const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * g.slices;
-  if (blocks > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
+  if (!grid_fits(blocks + 7, 256)) return BTX_ERR_UNSUPPORTED;
   kernel<<<(unsigned)align_up((size_t)blocks, 8), G::NT, G::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
   if (g.slices > 1) {
@@ -1355,7 +1355,7 @@ template <bool B_KC, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool
   const int64_t want = (int64_t)4 * 2 * kSplitMaxCus;
   g.strip = (int)std::min<int64_t>(std::max<int64_t>((int64_t)g.E * g.tiles_m * nx / want, 1), nx);
   const int64_t blocks = (int64_t)g.E * g.tiles_m * ceil_div(nx, g.strip);
-  if (blocks > 0x7fffff00) return BTX_ERR_UNSUPPORTED;
+  if (!grid_fits(blocks + 7, 256)) return BTX_ERR_UNSUPPORTED;
   kernel<<<(unsigned)align_up((size_t)blocks, 8), 256, D::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
   return BTX_OK;

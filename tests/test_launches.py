@@ -5,7 +5,7 @@ import pytest
 
 from paper_2403_07816_amd import binding as B
 
-from launches import P, adamw_call, backward_call, launches
+from launches import P, adamw_call, backward_call, forward_call, launches
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -72,3 +72,11 @@ def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_d
     assert streamed(100) and streamed(100, dW2=P + 64) and streamed(100, stride=256 * 192 + 32)
     assert not streamed(100, dW2=P + 16) and not streamed(100, stride=256 * 192 + 8)
     assert streamed(1500) and streamed(1500, dW2=P + 16)          # 256 x 256 tiles: from anywhere
+
+
+def test_fp32_products_of_too_many_tiles_are_refused(record):
+    """2^24 tiles of 256 threads are more than a launch can hold (137 GB of activations)."""
+    (rc, found), = record(forward_call(4_000_000, 64, 8704, 4, 1, B.BTX_F32, save=False))
+    assert rc == 2 and not found
+    (rc, found), = record(forward_call(4_000_000, 64, 8448, 4, 1, B.BTX_F32, save=False))
+    assert rc == 0 and found and all(threads_fit(launch) for launch in found)
