@@ -172,6 +172,8 @@ __global__ __launch_bounds__(256) void merge_weighted_f32_kernel(Ptrs in, Weight
   }
 }
 
+constexpr int64_t kMostBlocks = ((int64_t)1 << 24) - 1;   // of 256 threads: a launch holds fewer than 2^32 threads
+
 }  // namespace
 
 int launch_merge_weighted(const void* const* inputs, const float* weights, int N, void* out, int64_t numel, int dtype,
@@ -181,8 +183,8 @@ int launch_merge_weighted(const void* const* inputs, const float* weights, int N
   for (int n = 0; n < N; ++n) { p.p[n] = inputs[n]; w.w[n] = weights[n]; }
   const int per = dtype == BTX_BF16 ? 8 : 4;
   const int64_t chunks = numel / per;
-  // one chunk per thread wherever the grid allows it (a loop over fewer workgroups streams slower)
-  const int grid = (int)std::min<int64_t>(std::max<int64_t>((chunks + 255) / 256, 1), 0x7fffffff);
+  // one chunk per thread wherever a launch can hold them (a loop over fewer workgroups streams slower)
+  const int grid = (int)std::min<int64_t>(std::max<int64_t>((chunks + 255) / 256, 1), kMostBlocks);
   if (dtype == BTX_BF16) merge_weighted_bf16_kernel<<<grid, 256, 0, s>>>(p, w, N, static_cast<bf16_t*>(out), numel);
   else merge_weighted_f32_kernel<<<grid, 256, 0, s>>>(p, w, N, static_cast<float*>(out), numel);
   BTX_LAUNCH_CHECK();
@@ -196,9 +198,9 @@ int launch_merge_average(const void* const* inputs, int N, void* out, int64_t nu
   const int64_t chunks = numel / per;
   const int64_t bf16_run = (numel / 8 + kMergeUnroll - 1) / kMergeUnroll;   // chunks per run, one thread each
   const int64_t bf16_blocks = std::max<int64_t>((bf16_run + 255) / 256, 1);
-  if (dtype == BTX_BF16 && bf16_blocks > 0x7fffffff) return BTX_ERR_UNSUPPORTED;
+  if (dtype == BTX_BF16 && bf16_blocks > kMostBlocks) return BTX_ERR_UNSUPPORTED;
   const int grid = dtype == BTX_BF16 ? (int)bf16_blocks
-                                     : (int)std::min<int64_t>(std::max<int64_t>((chunks + 255) / 256, 1), 0x7fffffff);
+                                     : (int)std::min<int64_t>(std::max<int64_t>((chunks + 255) / 256, 1), kMostBlocks);
   if (dtype == BTX_BF16) {
     bf16_t* o = static_cast<bf16_t*>(out);
     switch (N) {

@@ -63,7 +63,8 @@ out = []
 for name, args in json.load(sys.stdin):
     fn = getattr(lib, name)
     fn.restype = ctypes.c_size_t if name.endswith("bytes") else ctypes.c_int
-    rc = fn(*[ctypes.c_float(a) if isinstance(a, float) else ctypes.c_int64(a) for a in args])
+    rc = fn(*[(ctypes.c_float if isinstance(a[0], float) else ctypes.c_void_p).__mul__(len(a))(*a) if isinstance(a, list) else
+              ctypes.c_float(a) if isinstance(a, float) else ctypes.c_int64(a) for a in args])
     out.append((rc, log.taken().decode()))
 print(json.dumps(out))
 """
@@ -90,7 +91,8 @@ def _short(name):
 
 
 def launches(calls, tmp_path):
-    """calls: (entry point, arguments) with pointers as integers and floats as floats; per call its status and its launches."""
+    """calls: (entry point, arguments) with pointers as integers, floats as floats and host arrays as lists; per call its status
+    and its launches."""
     source, stand_in = os.path.join(tmp_path, "stand_in.cpp"), os.path.join(tmp_path, "stand_in.so")
     if not os.path.exists(stand_in):
         with open(source, "w") as f:

@@ -80,3 +80,14 @@ def test_fp32_products_of_too_many_tiles_are_refused(record):
     assert rc == 2 and not found
     (rc, found), = record(forward_call(4_000_000, 64, 8448, 4, 1, B.BTX_F32, save=False))
     assert rc == 0 and found and all(threads_fit(launch) for launch in found)
+
+
+@pytest.mark.parametrize("n", [1, 1 << 20, (1 << 34) + 5])
+def test_merges_of_any_length_fit_a_launch(record, n):
+    """The kernels walk over the grid, so fewer threads than chunks are fine."""
+    for name, args in (("btx_merge_average", [[P, P], 2, P, n, B.BTX_F32, 0]),
+                       ("btx_merge_average", [[P, P], 2, P, n, B.BTX_BF16, 0]),
+                       ("btx_merge_weighted", [[P, P], [0.5, 0.5], 2, P, n, B.BTX_F32, 0]),
+                       ("btx_merge_weighted", [[P, P], [0.5, 0.5], 2, P, n, B.BTX_BF16, 0])):
+        (rc, found), = record((name, args))
+        assert rc == 0 and len(found) == 1 and threads_fit(found[0])
