@@ -1034,15 +1034,44 @@ template <bool B_KC, typename ET, bool STREAM> struct DwStrip {
 
   static __device__ void run(const MArgs& g, char* smem) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int wm = wave >> 1, wn = wave & 1, lane_m = lane & 15, lane_c = lane >> 4;
     // every XCD takes one eighth of the strips, one after another, an expert's row panels fastest: they share B's columns
     const int nx = g.tiles_n * PRODUCTS, n_strips = (nx + g.strip - 1) / g.strip, per_e = g.tiles_m * n_strips;
-    const int total = g.E * per_e, share = (total + 7) / 8, pos = (int)(blockIdx.x / 8);
-    const int id = (int)(blockIdx.x % 8) * share + pos;
-    if (pos >= share || id >= total) return;
-    const int e = id / per_e, local = id - e * per_e;
-    const int row0 = (local % g.tiles_m) * BT, first = local / g.tiles_m * g.strip, last = min(first + g.strip, nx);
+    const int total = g.E * per_e, share = (total + 7) / 8, xcd = blockIdx.x % 8, nth = blockIdx.x / 8, id = xcd * share + nth;
+    const int xe = min(lane, g.E - 1), x0 = g.offsets[xe], x1 = g.offsets[xe + 1];   // not looked at before the strip is done
+    if (nth < share && id < total) {
+      const int e = id / per_e, local = id - e * per_e, first = local / g.tiles_m * g.strip;
+      if (g.offsets[e + 1] - g.offsets[e] <= kLong) strip(g, smem, threadIdx.x, e, local % g.tiles_m * BT, first, min(first + g.strip, nx));
+    }
+    // Experts with more than kLong rows: their column tiles in strips that are the shorter, the more k tiles there are, shared out
+    // over all workgroups.  A routing that has collapsed would leave the products to a few of them otherwise (4096 rows on one
+    // of 64 experts of 4096 x 704: dW1 and dW3 638 -> 191 us, dW2 366 -> 111; 256 on one of four of 4096 x 11008: 259 -> 164,
+    // 158 -> 99).
+    const int x_rows = x1 - x0;
+    if (__ballot(x_rows > kLong) == 0) return;
+    const int x_len = max(1, 4 * g.strip / (2 + (x_rows + BK - 1) / BK));
+    const int x_strips = lane < g.E && x_rows > kLong ? (nx + x_len - 1) / x_len : 0, incl = wave_incl_scan_i32(x_strips, lane);
+    const int n_long = __builtin_amdgcn_readlane(incl, kWave - 1) * g.tiles_m, share_long = (n_long + 7) / 8;
+    for (int pos = nth; pos < share_long; pos += gridDim.x / 8) {
+      const int i = xcd * share_long + pos;
+      if (i >= n_long) break;
+      const int e = __ffsll((long long)__ballot((int64_t)incl * g.tiles_m > i)) - 1, len = __builtin_amdgcn_readlane(x_len, e);
+      const int local = i - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(x_strips, e)) * g.tiles_m;
+      const int first = local / g.tiles_m * len;
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();                      // everybody is done with what the first copies overwrite
+      __builtin_amdgcn_sched_barrier(0);
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));                      // keeps this copy's address arithmetic out of the other one's registers
+      strip(g, smem, tid, e, local % g.tiles_m * BT, first, min(first + len, nx));
+    }
+  }
+  static constexpr int kLong = 2 * BK;
+
+  // column tiles first .. last - 1 of the rows row0 .. row0 + 127 of expert e's gradient
+  static __device__ __forceinline__ void strip(const MArgs& g, char* smem, int tid, int e, int row0, int first, int last) {
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wm = wave >> 1, wn = wave & 1, lane_m = lane & 15, lane_c = lane >> 4;
     const int k_begin = g.offsets[e], k_end = g.offsets[e + 1], kp_begin = H::padded_rows_before(g, e, lane);
     const int nk = (k_end - k_begin + BK - 1) / BK;
     const bool rows_full = row0 + BT <= g.M;

@@ -372,6 +372,17 @@ def test_bf16_weight_gradients_of_few_rows(T, d, f, E, k, kw, dW_dtype):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,bias", [
+    (500, 264, 136, 8, 1, [6.0]), (512, 520, 264, 16, 2, [6.0, 6.0]),          # nearly everything on one expert, on two
+    (800, 1032, 1032, 64, 2, [4.0, 3.5, 3.0, 3.0, 2.5]),                        # strips of several tiles, shorter for some
+    (4000, 72, 136, 64, 1, [6.0]),
+])
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_of_few_rows_with_overloaded_experts(T, d, f, E, k, bias, dW_dtype):
+    """Up to 64 rows per expert on average, but far more on some: their strips are shared out over all workgroups."""
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, bias=bias + [0.0] * (E - len(bias)), poison=True)
+
+
 @pytest.mark.parametrize("T,d,E,k,kw", [
     # both sides of the limits of the two-launch routing: tokens, pairs, tokens x columns x experts
     (512, 64, 8, 8, {}), (513, 64, 8, 2, {}), (512, 72, 9, 8, dict(cf=0.8)), (456, 64, 9, 9, {}), (512, 1024, 64, 3, {}),
