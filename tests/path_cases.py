@@ -1,0 +1,40 @@
+"""Shapes that take the bf16 products along named paths: the GPU tests run them against the oracle, test_launches.py checks on
+the CPU that today's choice of kernels takes each of them there.  A case is (T, d, f, E, k, options of run_layer_and_check);
+the paths are {product: (rows of a tile, form of the last k tile, K slices of the last round)}, the slices for rows spread evenly
+over the experts (and cut off by the capacity limit)."""
+from paper_2403_07816_amd import binding as B
+
+UP, DOWN, BWD_ACT, BWD_DX, DW13, DW2 = range(6)
+SWITCH = dict(mode=B.BTX_ROUTE_SWITCH_TOP1)
+WHOLE, HALF, ANY = 0, 1, 2          # K a multiple of 64; 32 more; any other multiple of 8
+
+LAST_ROUND_CUT = [
+    # DOWN and both K passes of BWD_DX
+    ((2050, 1032, 8192, 2, 1, SWITCH), {DOWN: (256, WHOLE, 5), BWD_DX: (256, WHOLE, 5)}),
+    ((2050, 1032, 8224, 2, 1, SWITCH), {DOWN: (256, HALF, 5), BWD_DX: (256, HALF, 5)}),
+    ((2050, 1032, 8232, 2, 1, dict(SWITCH, cf=0.9, bias=[0.5, 0.0])), {DOWN: (256, ANY, 6), BWD_DX: (256, ANY, 6)}),
+    ((1200, 2056, 4104, 12, 2, dict(cf=1.0)), {DOWN: (256, ANY, 2), BWD_DX: (256, ANY, 2)}),
+    # UP, whose finishing kernel applies the SwiGLU
+    ((2050, 4096, 1160, 2, 1, SWITCH), {UP: (256, WHOLE, 2)}),
+    ((2050, 4128, 1160, 2, 1, SWITCH), {UP: (256, HALF, 2)}),
+    ((2050, 4104, 1160, 2, 1, dict(SWITCH, cf=0.9, bias=[0.5, 0.0])), {UP: (256, ANY, 3)}),
+    # 192 rows, the third LDS stage on the weights
+    ((260, 4096, 768, 16, 8, {}), {UP: (192, WHOLE, 2)}),
+    ((260, 4104, 768, 16, 8, {}), {UP: (192, ANY, 2)}),
+    ((260, 1536, 4096, 16, 8, dict(cf=0.9)), {DOWN: (192, WHOLE, 2), BWD_DX: (192, WHOLE, 2)}),
+    ((260, 1544, 4104, 16, 8, {}), {DOWN: (192, ANY, 2), BWD_DX: (192, ANY, 2)}),
+    ((280, 4104, 1160, 16, 8, {}), {BWD_DX: (192, ANY, 2)}),
+]
+
+
+def whole_tile_case(i):
+    """Seeded random shapes whose row-grouped products all run 256-row tiles; BWD_DX cuts its last round."""
+    import numpy as np
+    rng = np.random.default_rng(2000 + i)
+    E, k = [(2, 1), (3, 2), (3, 1)][i % 3]
+    T = int(rng.integers(10300, 13000)) // k
+    d, f = (8 * int(rng.integers(130, 160)) for _ in range(2))
+    return T, d, f, E, k
+
+
+WHOLE_TILE_CASES = 6

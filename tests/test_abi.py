@@ -195,9 +195,9 @@ def test_shapes_beyond_the_kernels_limits_are_refused_before_any_launch(lib):
         return lib.btx_moe_ff_forward(p, p, p, p, dt, d * f, d * f, T, d, f, E, k, p, p, p, p, null, p, p, p, p,
                                       1 << 62, null)
     unsupported = 2
-    assert fwd(8_400_000, 64, 64, 4, 1, 1) == unsupported     # bf16 MFMA path: padded rows * 512 bytes overflow 32 bits
-    assert fwd(4_200_000, 64, 64, 4, 1, 0) == unsupported     # plain path: more row tiles than the grid's y dimension
-    assert fwd(4_200_000, 64, 72, 4, 1, 1) == unsupported     # bf16 with an f the MFMA kernels do not take
+    assert fwd(8_400_000, 64, 64, 4, 1, 1) == unsupported     # bf16: padded rows * 512 bytes overflow 32 bits
+    assert fwd(4_200_000, 64, 64, 4, 1, 0) == unsupported     # fp32: the documented limit of 65535 row tiles
+    assert fwd(4_200_000, 64, 72, 4, 1, 1) == unsupported     # bf16 off the grid of 32: the same limit
 
 
 def test_missing_library_raises(monkeypatch):

@@ -10,6 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
+from path_cases import LAST_ROUND_CUT, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -264,7 +265,7 @@ def test_empty_batch_is_a_noop():
 # ------------------------------------------------------------------ bf16 path
 @pytest.mark.parametrize("T,d,f,E,k", [(512, 256, 384, 4, 2), (333, 264, 200, 4, 2), (1500, 512, 1376, 8, 4),
                                        (40, 64, 72, 4, 1),
-                                       # MFMA path at its edges: fewer rows than one k tile, many (mostly tiny or
+                                       # the products at their edges: fewer rows than one k tile, many (mostly tiny or
                                        # empty) experts, d and f that are multiples of 32 but not of 64
                                        (5, 64, 64, 4, 2), (700, 96, 160, 64, 8), (257, 320, 96, 3, 3),
                                        (300, 128, 96, 17, 3)])
@@ -273,21 +274,20 @@ def test_bf16_forward_backward(T, d, f, E, k):
 
 
 @pytest.mark.parametrize("T,d,f,E,k", [(313, 120, 264, 4, 2), (200, 264, 520, 3, 1), (150, 72, 776, 5, 3)])
-def test_bf16_off_the_mfma_path_with_wide_experts(T, d, f, E, k):
-    """bf16 shapes that the MFMA kernels do not take (d or f not a multiple of 32) with f > 256: the plain
-    kernels leave one sum of D * act per grouped row, not one per 256 columns as the MFMA path does."""
+def test_bf16_widths_off_the_32_grid_with_wide_experts(T, d, f, E, k):
+    """d or f not a multiple of 32, and f > 256: several column tiles, the last one partial, each with its own sum of D * act."""
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True)
 
 
 @pytest.mark.parametrize("T,d,f,E,k", [(70, 8, 8, 2, 1), (300, 56, 40, 3, 2), (261, 72, 88, 4, 2), (190, 104, 120, 5, 3),
-                                       # K ranges of a cut last round that end in a partial k tile (f, d = 40, 8 mod 64)
+                                       # K slices of small tiles that end in a partial k tile (f, d = 40, 8 mod 64)
                                        (700, 328, 2088, 3, 2), (300, 1096, 312, 2, 1)])
 def test_bf16_contractions_that_end_inside_a_k_tile(T, d, f, E, k):
     """d and f that are multiples of 8 only: the last k tile holds 1 to 7 chunks of 8, in both operand layouts."""
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True)
 
 
-def _random_mfma_case(i):
+def _random_small_tile_case(i):
     rng = np.random.default_rng(1000 + i)
     E = int(rng.choice([1, 2, 3, 4, 6, 8, 16]))
     k = int(rng.integers(1, min(E, 4) + 1))
@@ -298,27 +298,39 @@ def _random_mfma_case(i):
 
 
 @pytest.mark.parametrize("case", range(12))
-def test_bf16_random_shapes_on_the_mfma_path(case):
-    """Seeded random shapes (d, f multiples of 32; 1-16 experts; ragged groups of every size):
-    tile edges, padded groups, the ragged strips of the tile order, BK = 32 and 64 variants."""
-    T, d, f, E, k = _random_mfma_case(case)
+def test_bf16_random_shapes_of_small_tiles(case):
+    """Seeded random shapes (d, f multiples of 32; 1-16 experts; ragged groups of every size): 64- and 128-row tiles,
+    tile edges, padded groups, last k tiles that are half full."""
+    T, d, f, E, k = _random_small_tile_case(case)
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, seed=synth.BASE_SEED + case,
                         dW_dtype=F32 if case % 3 == 0 else None)
 
 
+@pytest.mark.parametrize("case", range(WHOLE_TILE_CASES))
+def test_bf16_random_shapes_of_whole_tiles(case):
+    """Seeded random shapes large enough for 256-row tiles in all four row-grouped products: partial row and column tiles,
+    ragged strips of the tile order, every form of the last k tile."""
+    T, d, f, E, k = whole_tile_case(case)
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, seed=synth.BASE_SEED + case)
+
+
+@pytest.mark.parametrize("case,paths", LAST_ROUND_CUT)
+def test_bf16_last_round_cut_along_k(case, paths):
+    """256- and 192-row tiles of a partly filled last round in K ranges of their own, whose sums a second kernel adds: every product
+    that is cut, every form of the last k tile, dropped pairs.  That the shapes take these paths is checked on the CPU."""
+    T, d, f, E, k, options = case
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True, **options)
+
+
 @pytest.mark.parametrize("T,d,f,E,k,kw", [
-    # 12 tiles in a round of 256 workgroups, f = 32.5 k tiles: the down projection is cut in two, the
-    # input-gradient product (two K passes, 66 k tiles, a half-empty tile at the end of each) in four
     (700, 320, 2080, 3, 2, {}),
     # top-1 with dropped pairs: rows of the output nothing writes, tiles of unequal height
     (900, 256, 2048, 4, 1, dict(mode=B.BTX_ROUTE_SWITCH_TOP1, bias=[2.0, 0, 0, 0], cf=1.5)),
-    # 96 tiles left over: two slices; 192 left over: too many to cut (the extra workgroups find nothing to do)
     (600, 4096, 1024, 3, 2, {}),
     (1100, 4096, 1024, 4, 2, {}),
 ])
-def test_bf16_last_round_cut_along_k(T, d, f, E, k, kw):
-    """DOWN and BWD_DX cut the tiles of a partly filled last round along K when K is long enough
-    (f >= 2048 / f >= 1024) and add the slices in a second kernel."""
+def test_bf16_few_tiles_of_long_contractions(T, d, f, E, k, kw):
+    """Too few 256-row tiles for the chip: 64- or 128-row tiles in their place, most of them cut along K."""
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True, **kw)
 
 

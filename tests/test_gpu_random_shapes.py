@@ -1,8 +1,9 @@
 """Seeded random configurations of the whole layer (route, forward, backward) against the oracle:
 both storage types, every routing mode, both forms of the load-balancing loss, capacity limits,
-router biases, 1 to 64 experts, shapes on and off the MFMA path, poisoned workspaces.  The same
-generator with other seeds found the cases that tests elsewhere now pin by name (wide experts off the
-MFMA path, the capacity limit at an exact product, gradients whose sum over the tokens cancels)."""
+router biases, 1 to 64 experts, widths on and off the grid of 32 (in bf16 all of them on 64- and 128-row
+tiles), poisoned workspaces.  The same generator with other seeds found the cases that tests elsewhere now
+pin by name (wide experts off that grid, the capacity limit at an exact product, gradients whose sum over
+the tokens cancels)."""
 import numpy as np
 import pytest
 import torch

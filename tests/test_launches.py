@@ -1,11 +1,14 @@
 """What the library launches for given sizes, without a GPU (see launches.py)."""
+import math
 import os
+import re
 
 import pytest
 
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -91,3 +94,47 @@ def test_merges_of_any_length_fit_a_launch(record, n):
                        ("btx_merge_weighted", [[P, P], [0.5, 0.5], 2, P, n, B.BTX_BF16, 0])):
         (rc, found), = record((name, args))
         assert rc == 0 and len(found) == 1 and threads_fit(found[0])
+
+
+def bf16_products(record, T, d, f, E, k):
+    """{product: (rows of a tile, form of the last k tile, a last round of it can be cut)} of a forward and a backward pass."""
+    paths = {}
+    for rc, found in record(forward_call(T, d, f, E, k, B.BTX_BF16), backward_call(T, d, f, E, k, B.BTX_BF16)):
+        assert rc == 0
+        names = [launch.kernel for launch in found]
+        for name, following in zip(names, names[1:] + [""]):
+            numbers = [int(n) for n in re.findall(r"[<,] ?(\d+)(?=[,>])", name)]
+            if name.startswith("mfma_gemm_kernel"):
+                paths[numbers[7]] = numbers[0], numbers[8], following.startswith("mfma_split_finish")
+            elif name.startswith("mfma_small_kernel"):
+                paths[numbers[5]] = numbers[0], numbers[6], False
+    return paths
+
+
+def slices_of_last_round(rows, E, N, K, product, tile):
+    """Gemm::split_plan for `rows` rows on each of E experts and 256 compute units."""
+    tiles = E * math.ceil(rows / tile) * math.ceil(N / (128 if product == UP else 256))
+    left, k_tiles = tiles % 256, math.ceil(K / 64) * (2 if product == BWD_DX else 1)
+    return max(1, min(8, 256 // left, k_tiles // 16)) if left else 1
+
+
+@pytest.mark.parametrize("case,paths", LAST_ROUND_CUT)
+def test_shapes_of_the_cut_last_round_take_that_path(record, case, paths):
+    T, d, f, E, k, options = case
+    taken = bf16_products(record, T, d, f, E, k)
+    rows = math.ceil(T * k / E)
+    if options.get("cf"):
+        rows = min(rows, math.ceil(options["cf"] * T * k / E))
+    for product, (tile, tail, slices) in paths.items():
+        N, K = (f, d) if product == UP else (d, f)
+        assert taken[product] == (tile, tail, True)
+        # 192-row tiles know no HALF: a last k tile of 32 takes the general form there
+        assert tail == (WHOLE if K % 64 == 0 else HALF if K % 64 == 32 and tile == 256 else ANY)
+        assert slices_of_last_round(rows, E, N, K, product, tile) == slices > 1
+
+
+@pytest.mark.parametrize("case", range(WHOLE_TILE_CASES))
+def test_random_shapes_of_whole_tiles_take_that_path(record, case):
+    T, d, f, E, k = whole_tile_case(case)
+    taken = bf16_products(record, T, d, f, E, k)
+    assert all(taken[product][0] == 256 for product in (UP, DOWN, BWD_ACT, BWD_DX)) and taken[BWD_DX][2]
