@@ -20,8 +20,9 @@ constexpr int kNormThreads = 256;
 // MAXC: 8-column chunks a thread owns (d <= MAXC * 2048); its column sums stay in registers.
 // GROUPS: groups of kNormThreads threads that share the workgroup's tokens, 4 at a time each; their column sums are
 // added in group order.  1 while the workgroups alone fill the chip, 4 with fewer than kFewBlocks of them (4001 tokens
-// of 2048 columns: 43 -> 22 us).
-constexpr int kFewBlocks = 512;
+// of 2048 columns: 43 -> 22 us); fp32 rows of more than 1024 columns already fill it with two workgroups on some compute
+// units (4500 tokens of 8192 columns: 192 us with one group, 230 with four; 4001 tokens 163, 155).
+constexpr int kFewBlocks = 512, kComputeUnits = 256;
 template <typename XT, int MAXC, int GROUPS>
 // dH may be the same buffer as dXn or dres (every thread writes only the chunks it has read, and a
 // row is written after its row sum is complete): those three carry no __restrict__.
@@ -33,7 +34,10 @@ __global__ __launch_bounds__(kNormThreads* GROUPS) void rmsnorm_bwd_kernel(const
   __shared__ float s_part[GROUPS][kGroupWaves][4];
   __shared__ float s_coef[GROUPS][4];
   __shared__ float s_cols[GROUPS > 1 ? GROUPS - 1 : 1][GROUPS > 1 ? kNormThreads : 1][8];
-  const int grp = threadIdx.x / kNormThreads, tid = threadIdx.x % kNormThreads;
+  // MAXC 8 (never grouped) says so itself: where the compiler had to find it out, it kept fewer loads in flight (bf16, 700
+  // tokens of 16384 columns: 171 us against 111); the narrower rows gain from that, 8 % with 12000 tokens of 4096 columns
+  static_assert(MAXC < 8 || GROUPS == 1, "groups");
+  const int grp = MAXC == 8 ? 0 : threadIdx.x / kNormThreads, tid = MAXC == 8 ? threadIdx.x : threadIdx.x % kNormThreads;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int t0 = blockIdx.x * kNormTok;
   float gacc[MAXC][8] = {};
@@ -157,7 +161,8 @@ int launch_typed(const void* dXn, const void* h, const float* gain, const float*
         static_cast<XT*>(dH), part);
   };
   auto by_blocks = [&](auto maxc) {
-    if (nblk < kFewBlocks) run(maxc, std::integral_constant<int, 4>{});
+    const bool few = nblk < kFewBlocks && (sizeof(XT) == 2 || nblk <= kComputeUnits || d <= 1024);
+    if (few) run(maxc, std::integral_constant<int, 4>{});
     else run(maxc, std::integral_constant<int, 1>{});
   };
   if (d <= 2048) by_blocks(std::integral_constant<int, 1>{});

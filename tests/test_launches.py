@@ -138,3 +138,10 @@ def test_random_shapes_of_whole_tiles_take_that_path(record, case):
     T, d, f, E, k = whole_tile_case(case)
     taken = bf16_products(record, T, d, f, E, k)
     assert all(taken[product][0] == 256 for product in (UP, DOWN, BWD_ACT, BWD_DX)) and taken[BWD_DX][2]
+
+
+@pytest.mark.parametrize("dtype,T,d,threads", [(B.BTX_BF16, 8000, 8192, 1024), (B.BTX_BF16, 8192, 8192, 256), (B.BTX_F32, 4096, 8192, 1024),
+                                               (B.BTX_F32, 4097, 8192, 256), (B.BTX_F32, 4097, 1024, 1024), (B.BTX_BF16, 100, 16384, 256)])
+def test_normalisation_backward_groups_threads_where_that_is_faster(record, dtype, T, d, threads):
+    (rc, found), = record(("btx_rmsnorm_backward", [P, P, P, P, P, dtype, T, d, P, P, P, 1 << 62, 0]))
+    assert rc == 0 and found[0].block[0] == threads
