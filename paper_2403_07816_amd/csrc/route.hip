@@ -373,12 +373,10 @@ int launch_route_small(const RouteArgs& a, hipStream_t s) {
 // ---- many tokens ---------------------------------------------------------------------------------------------
 // EC experts are accumulated per pass over the row; the 16 / NW tokens of a wavefront share each
 // load of the (transposed) W_router.
-// NW: wavefronts of a workgroup.  4 while the workgroups alone fill the chip; with fewer than kFewBlocks of them every
-// row's latency shows and 16 (8 with the matrix cores, whose partial sums take LDS) split the same 16 tokens: 4001
-// tokens of 2048 columns with the normalisation, 8 experts: 33 -> 24 us; 1501 tokens, 64 experts: 62 -> 49 us.
-constexpr int kFewBlocks = 512;
+// NW: wavefronts of a workgroup, see token_waves().
 template <typename XT, int EC, bool NORM, int NW, int MG = 1, int NS = 1>
-__global__ __launch_bounds__(NW* kWave) void route_tokens_kernel(
+__global__ __launch_bounds__(NW* kWave, NW == 8 && EC > 0 ? 4 : 1)   // 8: two workgroups on a compute unit
+void route_tokens_kernel(
     const XT* __restrict__ x, const float* __restrict__ WrT, const float* __restrict__ br,
     const float* __restrict__ U, int T, int d, int E, int k, int mode, float inv_tau, int32_t* __restrict__ topk_idx,
     float* __restrict__ gates, float* __restrict__ probs, int32_t* __restrict__ blk_counts,
@@ -390,8 +388,9 @@ __global__ __launch_bounds__(NW* kWave) void route_tokens_kernel(
   // W_router); the statistics stay per block of kTokPerBlock tokens either way
   constexpr int G = MATRIX ? MG : 1;
   constexpr int kTokPerWave = kTokPerBlock / NW;
+  constexpr int kGroup = kTokPerBlock / kWavesPerBlock, kTokPerSlot = kTokPerWave == kGroup ? kGroup : 1, kSlots = kTokPerBlock / kTokPerSlot;
   __shared__ float s_logit[NW][kTokPerWave][kMaxExperts];
-  __shared__ float s_stat[NW][3][kMaxExperts];
+  __shared__ float s_stat[kSlots][3][kMaxExperts];
   extern __shared__ float s_part[];                     // MATRIX: [wavefront][G * kTokPerBlock tokens][16 NS experts]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -558,27 +557,39 @@ __global__ __launch_bounds__(NW* kWave) void route_tokens_kernel(
     }
 
     // ---- per token: softmax, selection, gates; lane e owns expert e ----------
-    int cnt = 0;
-    float gsum = 0.f, psum = 0.f;
-    for (int q = 0; q < kTokPerWave; ++q) {
-      const int t = t0 + q;
-      if (t >= T) break;  // uniform across the wave
-      const float s = live ? s_logit[wave][q][lane] + (br ? br[lane] : 0.f) : -INFINITY;
-      select_experts(s, live, lane, t, E, k, mode, inv_tau, U, topk_idx, gates, probs, psum, gsum, cnt);
+    // the statistics are sums over groups of kGroup tokens, then over the groups, whatever NW is: the same bits as with any
+    // other number of wavefronts
+#pragma unroll 1
+    for (int q0 = 0; q0 < kTokPerWave; q0 += kTokPerSlot) {
+      int cnt = 0;
+      float gsum = 0.f, psum = 0.f;
+      for (int q = q0; q < q0 + kTokPerSlot; ++q) {
+        const int t = t0 + q;
+        if (t >= T) break;  // uniform across the wave
+        const float s = live ? s_logit[wave][q][lane] + (br ? br[lane] : 0.f) : -INFINITY;
+        select_experts(s, live, lane, t, E, k, mode, inv_tau, U, topk_idx, gates, probs, psum, gsum, cnt);
+      }
+      const int slot = (wave * kTokPerWave + q0) / kTokPerSlot;
+      s_stat[slot][0][lane] = __int_as_float(cnt);
+      s_stat[slot][1][lane] = gsum;
+      s_stat[slot][2][lane] = psum;
     }
-    s_stat[wave][0][lane] = __int_as_float(cnt);
-    s_stat[wave][1][lane] = gsum;
-    s_stat[wave][2][lane] = psum;
     __syncthreads();
     if (threadIdx.x < E) {
       const int e = threadIdx.x;
       int c = 0;
       float gs = 0.f, p = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        c += __float_as_int(s_stat[w][0][e]);
-        gs += s_stat[w][1][e];
-        p += s_stat[w][2][e];
+      for (int w = 0; w < kSlots; w += kGroup / kTokPerSlot) {
+        float group_gs = 0.f, group_p = 0.f;
+#pragma unroll
+        for (int x = w; x < w + kGroup / kTokPerSlot; ++x) {
+          c += __float_as_int(s_stat[x][0][e]);
+          group_gs += s_stat[x][1][e];
+          group_p += s_stat[x][2][e];
+        }
+        gs += group_gs;
+        p += group_p;
       }
       blk_counts[(size_t)blk * E + e] = c;
       blk_gsum[(size_t)blk * E + e] = gs;
@@ -726,11 +737,41 @@ __global__ __launch_bounds__(256) void transpose_wr_kernel(const float* __restri
   WrT[i] = Wr[(size_t)c * E + e];
 }
 
+// Wavefronts of a route_tokens workgroup.  4 while the workgroups alone fill the chip (kFewBlocks).  With fewer of them every
+// row's latency shows, and 8 or 16 split the same 16 tokens; but every wavefront reads all of W_router, and that traffic
+// decides wherever W_router is large or two workgroups share a compute unit.  us with 4 / 8 / 16:
+//   plain, up to 256 blocks: bf16 1500 tokens of 4096 columns, 8 experts 32 / 27 / 34, of 8192 41 / 36 / 49; more: 4500 of
+//   4096 34 / 38 / 54, of 8192 49 / 56 / 86; fp32 4500 of 2048 31 / 31 / 39, 8000 37 / 33 / 41, 4500 of 8192 60 / 68 / 96
+//   normalising, bf16: 4001 of 4096, 4 experts 55 / 43 / 39, 64 experts 281 / 197 / 213; of 512, 64 experts 87 / 64 / 60; 4500
+//   of 4096, 4 experts 58 / 49 / 57, 64 experts 303 / 256 / 366
+//   normalising, fp32: 1500 of 4096, 64 experts 152 / 136 / 193; of 512 70 / 56 / 55; of 16384, 8 experts 110 / 105 / 142, 4001
+//   187 / 208 / 270; 4500 of 512, 64 experts 80 / 71 / 83, of 4096 235 / 263 / 392
+// Logits on the matrix cores: 8 wavefronts that share W_router's columns, for one block of tokens instead of kMatrixGroups.
+// 4001 tokens of 4096 columns, 64 experts 87 -> 74 us; past one workgroup on a compute unit 4500 tokens 88 -> 119, and only
+// few experts of few columns gain (4500 of 1024, 16 experts 35 -> 31, of 8192 59 -> 66; 32 of 4096 66 -> 71).
+constexpr int kFewBlocks = 512, kComputeUnits = 256;
+int token_waves(int nblk, int d, int E, bool f32, bool norm) {
+  if (nblk >= kFewBlocks) return kWavesPerBlock;
+  if (nblk <= kComputeUnits) {
+    if (f32 && d > 8192) return kWavesPerBlock;
+    return norm && (f32 ? d <= 512 : d <= 1024 || E <= 4) ? 16 : 8;
+  }
+  return (f32 ? d <= 4096 && d * E <= 32768 : norm) ? 8 : kWavesPerBlock;
+}
+bool matrix_few(int nblk, int d, int E) {
+  return nblk <= kComputeUnits || (nblk < kFewBlocks && E <= 32 && d * E <= 65536);
+}
+
 template <typename XT>
 void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, float* bg, float* bp, hipStream_t s) {
   const XT* x = static_cast<const XT*>(a.x);
-  const bool few = nblk < kFewBlocks;
-#define BTX_ROUTE_LAUNCH(EC) do { if (few) BTX_ROUTE_LAUNCH_NW(EC, 16); else BTX_ROUTE_LAUNCH_NW(EC, kWavesPerBlock); } while (0)
+  const int waves = token_waves(nblk, a.d, a.E, std::is_same<XT, float>::value, a.gain != nullptr);
+#define BTX_ROUTE_LAUNCH(EC)                                      \
+  do {                                                            \
+    if (waves == 16) BTX_ROUTE_LAUNCH_NW(EC, 16);                 \
+    else if (waves == 8) BTX_ROUTE_LAUNCH_NW(EC, 8);              \
+    else BTX_ROUTE_LAUNCH_NW(EC, kWavesPerBlock);                 \
+  } while (0)
 #define BTX_ROUTE_LAUNCH_NW(EC, NW)                                                                                \
   do {                                                                                                             \
     if (a.gain)                                                                                                    \
@@ -755,7 +796,7 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
     };
     using std::integral_constant;
     auto go = [&](auto ns) {
-      if (few) go_nw(integral_constant<int, 8>{}, integral_constant<int, 1>{}, ns);
+      if (matrix_few(nblk, a.d, a.E)) go_nw(integral_constant<int, 8>{}, integral_constant<int, 1>{}, ns);
       else go_nw(integral_constant<int, kWavesPerBlock>{}, integral_constant<int, kMatrixGroups>{}, ns);
     };
     if (a.E <= 16) go(integral_constant<int, 1>{});

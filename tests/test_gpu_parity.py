@@ -531,6 +531,22 @@ def test_block_rmsnorm_route_forward_backward(T, d, f, E, k, dtype):
     run_block_and_check(T, d, f, E, k, dtype)
 
 
+@pytest.mark.parametrize("T,d,E,k,dtype", [
+    # 16, 8 and 4 wavefronts for 16 tokens, up to one workgroup of them on a compute unit and past that; ragged last blocks
+    (601, 136, 3, 2, BF16), (523, 1032, 40, 4, BF16), (601, 136, 40, 3, F32), (530, 1032, 5, 2, F32), (515, 8200, 3, 2, F32),
+    (4203, 72, 33, 2, BF16), (4203, 72, 9, 2, F32), (4203, 4104, 3, 1, F32), (8190, 72, 5, 3, BF16),
+])
+def test_block_rmsnorm_route_wavefronts(T, d, E, k, dtype):
+    run_block_and_check(T, d, 64, E, k, dtype)
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", [(601, 136, 3, 2, BF16), (4203, 1032, 7, 2, F32), (4203, 136, 7, 2, BF16), (600, 8200, 2, 1, F32),
+                                           (4203, 72, 12, 3, F32), (4203, 2056, 40, 2, BF16), (8190, 72, 17, 2, BF16)])
+def test_routing_wavefronts(T, d, E, k, dtype):
+    """Without the normalisation: the vector unit up to 8 experts, the matrix cores beyond."""
+    run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False)
+
+
 def test_block_rmsnorm_with_switch_routing_and_capacity():
     run_block_and_check(900, 256, 256, 4, 1, BF16, mode=B.BTX_ROUTE_SWITCH_TOP1, bias=[2.0, 0, 0, 0], cf=1.5)
 
@@ -545,6 +561,19 @@ def test_block_rmsnorm_route_matches_plain_route_on_the_normalised_rows():
     r2 = B.btx_moe_route(xn, Wr, k=2, lb_alpha=0.01)
     for name in ("topk_idx", "gates", "probs", "counts", "offsets", "perm", "inv_pos", "gate_sum", "prob_sum", "lb_loss"):
         assert torch.equal(getattr(r1, name), getattr(r2, name)), name
+
+
+@pytest.mark.parametrize("T,d,E,dtype", [(600, 4096, 4, BF16), (3001, 1032, 7, BF16), (4201, 2048, 8, BF16), (700, 512, 8, F32), (4201, 512, 3, F32),
+                                         (530, 8200, 2, F32)])
+def test_block_rmsnorm_route_gives_the_same_bits_with_other_wavefronts(T, d, E, dtype):
+    """Sizes where the fused kernel and btx_moe_route split the tokens of a block over different numbers of wavefronts."""
+    h = (synth.make_layer(T, d, 64, E, dtype=dtype)["x"].float() * 3.0).to(dtype).cuda()
+    gain = torch.linspace(0.5, 1.5, d).cuda()
+    Wr = 0.02 * torch.randn((d, E), generator=torch.Generator().manual_seed(E)).cuda()
+    r1, xn, _ = B.btx_moe_norm_route(h, gain, 1e-5, Wr, k=2, lb_alpha=0.01)
+    r2 = B.btx_moe_route(xn, Wr, k=2, lb_alpha=0.01)
+    for a, b in zip(vars(r1).values(), vars(r2).values()):
+        assert torch.equal(a, b)
 
 
 # ---------------------------------------------------------------------- merge

@@ -145,3 +145,28 @@ def test_random_shapes_of_whole_tiles_take_that_path(record, case):
 def test_normalisation_backward_groups_threads_where_that_is_faster(record, dtype, T, d, threads):
     (rc, found), = record(("btx_rmsnorm_backward", [P, P, P, P, P, dtype, T, d, P, P, P, 1 << 62, 0]))
     assert rc == 0 and found[0].block[0] == threads
+
+
+@pytest.mark.parametrize("dtype,norm,T,d,E,waves", [
+    # one workgroup of 16 tokens on a compute unit
+    (B.BTX_BF16, False, 4096, 8192, 8, 8), (B.BTX_F32, False, 4096, 8200, 8, 4), (B.BTX_BF16, True, 4096, 4096, 4, 16),
+    (B.BTX_BF16, True, 4096, 4096, 8, 8), (B.BTX_BF16, True, 4096, 1024, 64, 16), (B.BTX_F32, True, 4096, 512, 64, 16),
+    (B.BTX_F32, True, 4096, 4096, 64, 8), (B.BTX_F32, True, 600, 16384, 64, 4),
+    # two
+    (B.BTX_BF16, False, 4097, 4096, 8, 4), (B.BTX_F32, False, 4097, 4096, 8, 8), (B.BTX_F32, False, 4097, 4096, 16, None),
+    (B.BTX_BF16, True, 8176, 16384, 64, 8), (B.BTX_F32, True, 8176, 4096, 64, 4), (B.BTX_F32, True, 8176, 512, 64, 8),
+    (B.BTX_BF16, True, 8177, 4096, 4, 4),
+    # logits on the matrix cores: 8 wavefronts and one block of tokens, or 4 and two
+    (B.BTX_BF16, False, 4096, 4096, 64, 8), (B.BTX_BF16, False, 4097, 512, 64, 4), (B.BTX_BF16, False, 4097, 2048, 32, 8),
+    (B.BTX_BF16, False, 4097, 4096, 32, 4)])
+def test_wavefronts_that_share_16_tokens(record, dtype, norm, T, d, E, waves):
+    k = min(E, 2)
+    lead = [P, dtype, P, 1e-5, 2 * P, P] if norm else [P, dtype]
+    args = lead + [P, 0, 0, T, d, E, k, 0, 0, 0.01, 1.0, 0.0] + [P] * 10 + [P, 1 << 62, 0]
+    (rc, found), = record(("btx_moe_norm_route" if norm else "btx_moe_route", args))
+    tokens, = [launch for launch in found if launch.kernel.startswith("route_tokens")]
+    assert rc == 0
+    if waves is None:           # fp32 rows, 16 experts: the matrix cores
+        assert "0, false, 8, 1, 1>" in tokens.kernel
+    else:
+        assert tokens.block[0] == 64 * waves and f", {waves}, " in tokens.kernel
