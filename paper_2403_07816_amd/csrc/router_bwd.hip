@@ -146,7 +146,6 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
                                                               int d, int E, float* __restrict__ part,
                                                               float* __restrict__ db_part, float* __restrict__ dWr,
                                                               float* __restrict__ db) {
-  constexpr int kQuarter = CHUNK / 4;
   __shared__ float s_ds[CHUNK][KEC];
   __shared__ f32x4 s_acc[KEC * 2][kWave];
   const int lane = threadIdx.x & (kWave - 1);
@@ -160,7 +159,8 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
   __syncthreads();
   const int c0 = (blockIdx.y * kWave + lane) * kColsPerThread, cc = min(c0, d - kColsPerThread);
   float acc[KEC][kColsPerThread] = {};
-  for (int q = wave * kQuarter; q < min(nt, (wave + 1) * kQuarter); q += 4) {   // rows past the end meet the zeros of s_ds
+  const int quarter = (nt + 15) / 16 * 4;               // of the tokens there are, whole groups of four
+  for (int q = wave * quarter; q < min(nt, (wave + 1) * quarter); q += 4) {     // rows past the end meet the zeros of s_ds
     float xv[4][8];
 #pragma unroll
     for (int u = 0; u < 4; ++u) RowVec<XT, 8>::ld_stream(x + (size_t)min(t0 + q + u, T - 1) * d + cc, xv[u]);
