@@ -34,6 +34,7 @@
 //     up to 8 slices whose fp32 accumulators a second small kernel adds in ascending order and stores
 //     (UP: with the SwiGLU applied to the sums), so that the round fills the chip (Gemm::split_plan).
 #include "gemm_mfma.h"
+#include <cmath>
 #include <type_traits>
 
 namespace btx {
@@ -1315,12 +1316,43 @@ template <int BM, int MODE, int TAIL> int launch_small(MArgs g, bool prepare_onl
 //   128                  144 /  71       150 /  74   154 /  82   222 / 125   227 / 129   235 / 133
 //   192 (3 stages of B)                              160 /  90   170 / 101   179 / 104   290 / 148
 // (how many rows an expert has is only known on the device: the average decides, and a routing that is far from it pays
-// with a second row tile for the experts that have more.)
-// A product of few 256-row tiles that are also too short to be cut along K into pieces of 32 k tiles leaves compute
-// units idle (1200 rows, 4 experts of 4096 x 1376: UP 76 us, DOWN 39, BWD_ACT 88, BWD_DX 68); with 128-row tiles 58, 34,
-// 55, 50; with 64-row tiles 67, 38, 37, 60: the smaller ones are taken, of 64 rows where those of 128 are too few as well.
+// with a second row tile for the experts that have more.  192 rows stop at 168 on average, not where the table crosses: an
+// expert that has more than 192 costs a second tile, the jump from 179 to 290, and random routing spreads by sqrt(rows).)
+// A product of few 256-row tiles, even when cut along K into pieces of 32 k tiles, leaves compute units idle, and 128-row tiles
+// (64 where those are too few as well) may fill them: 480 rows on each of 4 experts of 4096 x 1376: DOWN 33 us with 256 rows,
+// 28 with 128; BWD_DX 66, 58; BWD_ACT 83, 43 with 64.  Or need a second round: 200 rows, 2 experts of 4096 x 11008: UP 82 with
+// 256 rows, 107 with 128.  There tile_us() decides.
 constexpr int kSmallRows = 110;                          // rows per expert up to which a product takes small tiles
-constexpr int64_t kEnough = 192;                         // workgroups of three quarters of the compute units
+constexpr int64_t kEnough = 192;                         // workgroups of three quarters of the compute units: 256-row tiles without question
+// row tiles to expect of rows that are spread at random over the experts
+double random_row_tiles(const MArgs& g, int BM) {
+  const double rows = (double)g.R / g.E, m = std::ceil(rows / BM), spread = std::sqrt(2.0 * rows * (1.0 - 1.0 / g.E));
+  if (spread == 0) return g.E * m;
+  return g.E * m + std::round(g.E * 0.5 * std::erfc((m * BM - rows) / spread)) -
+         (m > 1 ? std::round(g.E * 0.5 * std::erfc((rows - (m - 1) * BM) / spread)) : 0.0);
+}
+// Rounds of workgroups times what a k tile takes, us: small tiles with one workgroup on a compute unit and with two, large ones
+// whole and in a last round that is cut.  Fitted to 741 shapes (1 to 64 experts, 115 to 2300 rows each, 128 x 512 to 8192 x
+// 4096).  With "fewer than kEnough: small" a product was more than 5 % slower than with 256 rows at 159 of these 2964 (by up to
+// half), now at 30, near a full round where single rows decide; on average 3 % behind the best tile.
+template <int MODE> double tile_us(const MArgs& g, int BM) {
+  constexpr bool ACT = MODE == BWD_ACT;
+  const bool small = BM <= 128;
+  const int cols = ceil_div(g.N, (small ? 128 : 256) / (MODE == UP ? 2 : 1)), nk = ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1);
+  const int64_t tiles = (int64_t)(random_row_tiles(g, BM) * cols);
+  const bool cut = !ACT && g.partial;
+  if (small) {
+    const double one = BM == 64 ? 0.44 : 0.655, pair = BM == 64 ? 0.66 : 0.95, fixed = (BM == 64 ? 2.5 : 4.0) + (ACT ? 7.0 : 0.0);
+    const int slices = cut ? small_slices((int64_t)even_row_tiles(g, BM) * cols, nk, (size_t)g.R * g.N * (MODE == UP ? 8 : 4)) : 1;
+    const double k = (double)nk / slices;
+    const int64_t wgs = tiles * slices, rest = wgs % (2 * kSplitMaxCus), pairs = wgs / (2 * kSplitMaxCus) + (rest > kSplitMaxCus);
+    return pairs * (fixed + k * pair) + (rest > 0 && rest <= kSplitMaxCus ? fixed + k * one : 0.0) + (slices > 1 ? 4.0 : 0.0);
+  }
+  const double fixed = 9.0 + (ACT ? 20.0 : 0.0);
+  const int64_t rounds = tiles / kSplitMaxCus, left = tiles % kSplitMaxCus;
+  const int64_t slices = cut && left > 0 ? std::max<int64_t>(std::min<int64_t>({kSplitMaxSlices, kSplitMaxCus / left, nk / 16}), 1) : 1;
+  return rounds * (fixed + nk * 1.4) + (left > 0 ? fixed + (double)nk / slices * 1.05 : 0.0) + (slices > 1 ? 4.0 + 0.09 * left * slices : 0.0);
+}
 template <int MODE> int row_tile(const MArgs& g) {
   constexpr bool DUAL = MODE == UP;
   const int64_t avg = g.R / std::max(g.E, 1);
@@ -1328,21 +1360,18 @@ template <int MODE> int row_tile(const MArgs& g) {
   if (avg <= kSmallRows) return 128;
   const int64_t tiles = (int64_t)even_row_tiles(g, 256) * ceil_div(g.N, DUAL ? 128 : 256);
   const int64_t pieces = MODE == BWD_ACT || !g.partial ? 1 : ceil_div(g.K, 64) * (MODE == BWD_DX ? 2 : 1) / 32;
-  if (tiles * std::max<int64_t>(std::min(pieces, kSplitMaxCus / std::max<int64_t>(tiles, 1)), 1) >= kEnough)
-    return MODE != BWD_ACT && avg <= 168 ? 192 : 256;
-  return (int64_t)even_row_tiles(g, 128) * ceil_div(g.N, DUAL ? 64 : 128) >= kEnough ? 128 : 64;
+  const int large = MODE != BWD_ACT && avg <= 168 ? 192 : 256;
+  if (tiles * std::max<int64_t>(std::min(pieces, kSplitMaxCus / std::max<int64_t>(tiles, 1)), 1) >= kEnough) return large;
+  const int small = (int64_t)even_row_tiles(g, 128) * ceil_div(g.N, DUAL ? 64 : 128) >= kEnough ? 128 : 64;
+  return tile_us<MODE>(g, large) < tile_us<MODE>(g, small) ? large : small;
 }
 
 // Scratch for the K slices of a product of up to R rows, or of any smaller number of them.  Small tiles (at most one (tile,
 // slice) pair of 128 x 128 sums for a compute unit; small_slices()) may be cut at any number of rows; the last round of larger
 // tiles only with rows enough for those and K for two slices (row_tile(), split_plan()).
 template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
-  MArgs g{};
-  g.R = R; g.E = E;
   const int nk = ceil_div(K, 64) * (MODE == BWD_DX ? 2 : 1), slices = std::min(nk / 8, kSplitMaxSlices);
-  if (R / std::max(E, 1) > kSmallRows && nk >= 2 * Gemm<256, 256, 64, 2, 4, 3, 2, MODE>::kMinSliceTiles &&
-      even_row_tiles(g, 256) * (int64_t)ceil_div(N, MODE == UP ? 128 : 256) * (nk / 32) >= kEnough)
-    return kSplitBytes;
+  if (R / std::max(E, 1) > kSmallRows && nk >= 2 * Gemm<256, 256, 64, 2, 4, 3, 2, MODE>::kMinSliceTiles) return kSplitBytes;
   return slices < 2 ? 0 : std::min((size_t)slices * R * N * (MODE == UP ? 8 : 4), (size_t)kSplitMaxCus * 128 * 128 * sizeof(float));
 }
 

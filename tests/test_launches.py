@@ -170,3 +170,15 @@ def test_wavefronts_that_share_16_tokens(record, dtype, norm, T, d, E, waves):
         assert "0, false, 8, 1, 1>" in tokens.kernel
     else:
         assert tokens.block[0] == 64 * waves and f", {waves}, " in tokens.kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,product,tile", [
+    # one round of 256- or 192-row tiles where smaller ones would need a second round (us there: 256 / 128 rows)
+    (400, 4096, 11008, 2, UP, 256), (480, 4096, 11008, 1, UP, 256), (6000, 4096, 688, 4, UP, 256), (320, 4096, 11008, 2, UP, 192),
+    (2300, 4096, 11008, 1, DOWN, 256), (600, 2048, 5504, 1, BWD_DX, 256), (4600, 2048, 5504, 2, BWD_DX, 256), (2300, 8192, 4096, 1, BWD_ACT, 256),
+    # compute units that large tiles would leave idle
+    (1200, 4096, 1376, 4, BWD_DX, 128), (1200, 4096, 1376, 4, DOWN, 128), (1200, 4096, 1376, 4, BWD_ACT, 64), (600, 512, 1376, 4, UP, 64),
+    # enough large tiles
+    (16384, 4096, 11008, 4, DOWN, 256), (4001 * 2, 2048, 5504, 8, BWD_DX, 256)])
+def test_row_tiles_of_products_with_few_tiles(record, T, d, f, E, product, tile):
+    assert bf16_products(record, T, d, f, E, 1)[product][0] == tile
