@@ -24,14 +24,18 @@
  *     Arguments are validated before anything is launched; on an error status
  *     no kernel has been enqueued.
  *   - T == 0 is a valid no-op (BTX_OK).
+ *   - A workspace query never falls as T grows: a workspace sized for the largest batch
+ *     serves every smaller one.
  *   - Rows move as 16-byte pieces: every tensor of rows (x, the expert weights and their
  *     gradients, saved activations, outputs, workspaces) starts on a 16-byte boundary, and
  *     the expert strides are multiples of 8 elements; BTX_ERR_INVALID_ARG otherwise.
  *   - Every kernel is free of atomics: results are bit-identical run to run.  The order
  *     of every sum is fixed by the shapes, the routing counts and the number of compute
  *     units of the device (the bf16 up-projection, down-projection and input-gradient
- *     products cut the tiles of a partly filled last round of workgroups into up to eight K
- *     ranges, added in ascending order by a second kernel).
+ *     products cut the tiles of a partly filled last round of workgroups, or with few rows per
+ *     expert every tile, into up to eight K ranges; fp32 does so with the tiles of the
+ *     down-projection and the input gradient when they are few; a second kernel adds the
+ *     ranges in ascending order).
  *   - Outputs must not alias inputs unless stated.  NaN/Inf inputs give
  *     unspecified results.
  */
@@ -102,15 +106,17 @@ int btx_init(void);
  * kernels on the caller's stream, so that single kernels can be timed inside the real
  * sequence.  n_pairs = 0 switches it off.  Stage ids: */
 enum {
-  BTX_STAGE_ROUTE = 0,        /* btx_moe_route: all three kernels                  */
-  BTX_STAGE_GATHER_X = 1,     /* forward: x -> expert-grouped rows                 */
+  BTX_STAGE_ROUTE = 0,        /* btx_moe_route: its two or four kernels            */
+  BTX_STAGE_GATHER_X = 1,     /* forward: x -> expert-grouped rows (bf16, only when
+                                  x has 2^32 bytes or more: else UP reads x itself)  */
   BTX_STAGE_UP = 2,           /* forward: xs W1, xs W3, SwiGLU                     */
   BTX_STAGE_DOWN = 3,         /* forward: act W2                                   */
   BTX_STAGE_COMBINE = 4,      /* forward: gate-weighted un-permute                 */
-  BTX_STAGE_GATHER_DY = 5,    /* backward: dY -> grouped rows                      */
+  BTX_STAGE_GATHER_DY = 5,    /* backward: dY -> grouped rows (as GATHER_X)        */
   BTX_STAGE_BWD_ACT = 6,      /* backward: dys W2^T + SwiGLU backward              */
   BTX_STAGE_BWD_DX = 7,       /* backward: dh1 W1^T + dh3 W3^T                     */
-  BTX_STAGE_GATHER_X_BWD = 8, /* backward: x -> grouped rows (for dW1, dW3)        */
+  BTX_STAGE_GATHER_X_BWD = 8, /* backward: x and dY -> transposed grouped rows for
+                                  the weight gradients (bf16; none with frozen experts) */
   BTX_STAGE_DW13 = 9,         /* backward: dW1, dW3                                */
   BTX_STAGE_DW2 = 10,         /* backward: dW2                                     */
   BTX_STAGE_ROUTER_BWD = 11,  /* backward: router gradients and final dX           */
@@ -250,7 +256,7 @@ int btx_rmsnorm_backward(const void* dXn, const void* h, const float* gain, cons
  *                        the backward pass.  Both NULL = forward only.
  * dtype BTX_BF16: bf16 storage, bf16 MFMA products, fp32 accumulation; the
  * activation silu(h1)*h3 and the expert output are rounded to bf16 once each.
- * dtype BTX_F32: plain fp32 FMA kernels (parity path, not the fast path).
+ * dtype BTX_F32: fp32 matrix-instruction products (exact products, fp32 accumulation), fp32 storage.
  * Requirements: d % 8 == 0, f % 8 == 0, strides >= d*f and multiples of 8.
  * Limits (BTX_ERR_UNSUPPORTED beyond them; also for btx_moe_ff_backward): the bf16 kernels address the
  * padded grouped rows with 32-bit byte offsets, ceil(R/64)*64 + 64*E < 2^23 (about 8.3 M routed rows);

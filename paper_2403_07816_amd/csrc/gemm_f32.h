@@ -3,7 +3,7 @@
 #include "common.h"
 
 namespace btx {
-// the row tiles of the row-grouped products, at the smaller tile height
+// the number of rows that the interface documents for fp32 (R/64 + E <= 65535); the kernels' grids would take more
 bool f32_rows_ok(int R, int E);
 // partial sums of dg per grouped row that f32_bwd_act leaves (one per column tile)
 int f32_bwd_act_partials(int f);

@@ -17,10 +17,9 @@
 //   * token rows (x, dY) are read through perm wherever they are an operand, the SwiGLU and its backward are
 //     epilogues on the accumulators: nothing is gathered, and no product is stored only to be read again.
 // Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP): with plain FMA
-// tiles, gathered operands and separate elementwise kernels 1.62 ms, now 0.71; the products run at 65 to 90 of the
-// 153 TFLOP/s this instruction sustains (matrix pipe busy 45 - 63 %).  Timing builds: the products alone, without any
-// operand traffic, would take 0.50 of their 0.66 ms (ragged rounds of 64 x 64 tiles), the global loads add 12 %, the
-// LDS writes and reads 8 % each.
+// tiles, gathered operands and separate elementwise kernels 1.64 ms, now 0.60; the products run at 70 to 94 of the
+// 153 TFLOP/s this instruction sustains (matrix pipe busy 46 - 66 %): UP 120 us, DOWN 81, BWD_ACT 72, BWD_DX 131 + 5,
+// DW13 123, DW2 67.  What is left is ragged rounds of 64 x 64 tiles and the operands' way through registers into LDS.
 #include "gemm_f32.h"
 
 #include <algorithm>
@@ -391,7 +390,7 @@ template <int BM, int BN, int BK, int MODE> __global__ __launch_bounds__(kThread
 
 // 128 x 128 and 128 x 64 tiles of the same form (half the operand traffic per product, half the workgroups) were
 // slower on this library's fp32 shapes: with 4006 rows, d = 512, f = 1376 DOWN 115 / 111 us against 84, DW13 151 / 142
-// against 138.
+// against 138 (of the loads then; 123 now).
 constexpr int kTile = 64, kTileK = 32, kMaxSlices = 8;
 // floats that the slices' sums of a product may take (128 MB): the cut pays while tiles are few, and the scratch has a bound of
 // its own

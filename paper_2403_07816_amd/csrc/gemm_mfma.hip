@@ -506,7 +506,7 @@ struct Gemm {
     // TAIL is a template parameter: 0 the common shapes, which pay nothing for it; 1 K = 32 mod 64, where only the
     // second half of the tile has to be looked at (with 2 in its place the step with 32 split experts, where DOWN and
     // BWD_DX run 21.5 k tiles, lost 0.7 %); 2 any other multiple of 8.  The shapes of 2 ran on plain fp32 FMA kernels
-    // before: fwd + bwd of 1501 tokens, 64 experts of 4096 x 688, top-8: 13.9 -> 1.73 ms.
+    // before: fwd + bwd of 1501 tokens, 64 experts of 4096 x 688, top-8: 13.9 -> 1.44 ms.
     static_assert(!(TAIL && GROUP_K), "the dW products have no K tail");
     // in the slice's own count of k tiles: where the second K pass begins, and the two possible tail tiles
     const int pass2_at = nk1 - kb, tail1_at = nk1 - 1 - kb, tail2_at = nk_all - 1 - kb;

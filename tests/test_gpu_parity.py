@@ -523,7 +523,7 @@ def test_bf16_expert_without_tokens():
 @pytest.mark.parametrize("T,d,f,E,k,dtype", [
     (300, 64, 176, 4, 2, F32),          # fp32, ragged last token block
     (77, 2056, 64, 3, 1, F32),          # d not a multiple of the 2048-column thread stride, E < 4
-    (1000, 512, 1376, 8, 2, BF16),      # MFMA path
+    (1000, 512, 1376, 8, 2, BF16),      # 250 rows per expert
     (515, 4096, 256, 4, 2, BF16),       # the benchmark's d
     (130, 4608, 128, 16, 4, BF16),      # E > 8: several expert passes over the rows; d > 4096
 ])
