@@ -16,13 +16,14 @@ import csv
 import sys
 
 MODES = {0: "up_swiglu", 1: "down", 2: "bwd_act", 3: "bwd_dx", 4: "dw13", 5: "dw2"}
+MODE_AT = {"mfma_gemm_kernel": 7, "mfma_small_kernel": 5, "f32_gemm_kernel": 3}   # template arguments in front of MODE
 
 
 def short(name: str) -> str:
     name = name.replace("btx::(anonymous namespace)::", "").replace("void ", "").split("(")[0]
-    if name.startswith("mfma_gemm_kernel<"):
-        args = name[len("mfma_gemm_kernel<"):-1].split(",")   # BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL
-        name += " " + MODES.get(int(args[7]), "?")
+    for kernel, mode_at in MODE_AT.items():
+        if name.startswith(kernel + "<"):
+            name += " " + MODES.get(int(name[len(kernel) + 1:-1].split(",")[mode_at]), "?")
     return name
 
 
