@@ -42,7 +42,7 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const FfShapes sh{(int)R, d, f, E, 0, 0};
   Carver c(ws);
   BwdWs w;
-  // the bf16 dW products take x and dY transposed and padded
+  // the bf16 dW products of many rows per expert take x and dY transposed and padded
   const bool tr = ff_dw_transposed(dtype);
   const size_t dw_op = (size_t)d * ff_dw_pitch((int)R, E) * es;
   w.xsT = tr ? c.take(dw_op) : nullptr;
@@ -50,7 +50,7 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   w.dys = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   w.dh1 = c.take(R * f * es);
   w.dh3 = c.take(R * f * es);
-  // transposed path: dW2 reads ga as [f][padded rows]
+  // transposed path: dW2 reads ga as [f][padded rows]; in row order it is smaller
   w.ga = c.take(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : R * f * es);
   w.dxs = c.take(R * d * es);
   w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials_most(dtype, f) * sizeof(float)));
@@ -318,19 +318,22 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
+  const bool direct = ff_dw_direct(dtype, sh, fused);
+  // bf16 weight gradients that read token rows: their offsets lie where the transposed rows would
+  uint32_t* row_bytes = direct && n_dw == 3 ? static_cast<uint32_t*>(w.xsT) : nullptr;
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
-                                              w.dh3, w.ga, n_dw == 3, w.dg_part, s));
+                                              w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));
   BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx(dtype, w.dh1, w.dh3, W1, W3, offsets, sh, w.dxs, w.partial, s));
   if (n_dw == 3) {
     RowSource dw_x{x, perm, k}, dw_dy{dY, perm, k};
-    if (ff_dw_transposed(dtype)) {
+    if (!direct) {
       BTX_STAGE(BTX_STAGE_GATHER_X_BWD,
                 launch_gather_rows_t(x, w.xsT, dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
       dw_x = RowSource{w.xsT, nullptr, 1};
       dw_dy = RowSource{w.dysT, nullptr, 1};
     }
-    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dtype, dW_dtype, dw_x, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
-    BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dtype, dW_dtype, w.ga, dw_dy, offsets, sh, dW2, s));
+    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dtype, dW_dtype, dw_x, w.dh1, w.dh3, offsets, sh, row_bytes, dW1, dW3, s));
+    BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dtype, dW_dtype, w.ga, dw_dy, offsets, sh, row_bytes, dW2, s));
   }
   RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,
                    topk_idx, gates, probs, inv_pos, gate_sum, prob_sum, counts, w.dg_part, bwd_act_partials(dtype, sh), w.dxs, dX,

@@ -265,28 +265,30 @@ size_t ff_backward_split_bytes(int dtype, const FfShapes& sh);
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, hipStream_t s);
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.
-// dh1, dh3: [R,f].  When ff_dw_transposed() holds, `ga` receives g*a transposed and padded
-// ([f][ff_dw_pitch()]), or nothing at all when want_dw is false; otherwise ga is [R,f].
+// dh1, dh3: [R,f].  With ga_transposed `ga` receives g*a transposed and padded ([f][ff_dw_pitch()]); otherwise it is
+// [R,f].  Nothing at all in bf16 when want_dw is false.  row_bytes ([R], bf16; may be NULL): for the weight gradients, the byte
+// offset of every grouped row's token row.
 // bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile), and the
 // most that any number of rows gets (fewer rows may run with narrower tiles)
 int bwd_act_partials(int dtype, const FfShapes& sh);
 int bwd_act_partials_most(int dtype, int f);
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
-                   bool want_dw, float* dg_part, hipStream_t s);
+                   bool want_dw, bool ga_transposed, uint32_t* row_bytes, float* dg_part, hipStream_t s);
 // dxs = dh1 W1^T + dh3 W3^T
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
 // dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When
-// ff_dw_transposed() holds, xs, dys and ga are passed in the transposed, padded form with
-// pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
-// does); otherwise xs and dys are token rows read through perm and ga is [R,f].
+// ff_dw_direct() holds, xs and dys are token rows read through perm and ga is [R,f]; otherwise they are passed in the
+// transposed, padded form with pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
+// does).  ff_dw_transposed(): problems of this dtype may take that form.
 bool ff_dw_transposed(int dtype);
+bool ff_dw_direct(int dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
 int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
-                    const FfShapes& sh, void* dW1, void* dW3, hipStream_t s);
+                    const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);
 int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
-                   const FfShapes& sh, void* dW2, hipStream_t s);
+                   const FfShapes& sh, uint32_t* row_bytes, void* dW2, hipStream_t s);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address

@@ -15,6 +15,9 @@ bool ff_rows_supported(int dtype, int R, int d, int f, int E) {
 }
 
 bool ff_dw_transposed(int dtype) { return dtype == BTX_BF16; }
+bool ff_dw_direct(int dtype, const FfShapes& sh, bool gather_fused) {
+  return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh));
+}
 int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
 
 bool ff_gather_fused(int dtype, int T, int d) { return dtype != BTX_BF16 || mfma_gather_ok(T, d); }
@@ -44,9 +47,9 @@ int launch_down(int dtype, const void* act, const void* W2, const int32_t* offse
 }
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,
-                   bool want_dw, float* dg_part, hipStream_t s) {
+                   bool want_dw, bool ga_transposed, uint32_t* row_bytes, float* dg_part, hipStream_t s) {
   if (!want_dw) ga = nullptr;
-  if (dtype == BTX_BF16) return mfma_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, dg_part, s);
+  if (dtype == BTX_BF16) return mfma_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, ga_transposed, row_bytes, dg_part, s);
   return f32_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, dg_part, s);
 }
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
@@ -55,13 +58,13 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
   return f32_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, partial, s);
 }
 int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
-                    const FfShapes& sh, void* dW1, void* dW3, hipStream_t s) {
-  if (dtype == BTX_BF16) return mfma_bwd_dw13(dW_dtype, xs.base, dh1, dh3, offsets, sh, dW1, dW3, s);
+                    const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s) {
+  if (dtype == BTX_BF16) return mfma_bwd_dw13(dW_dtype, xs, dh1, dh3, offsets, sh, row_bytes, dW1, dW3, s);
   return f32_bwd_dw13(xs, dh1, dh3, offsets, sh, dW1, dW3, s);
 }
 int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
-                   const FfShapes& sh, void* dW2, hipStream_t s) {
-  if (dtype == BTX_BF16) return mfma_bwd_dw2(dW_dtype, ga, dys.base, offsets, sh, dW2, s);
+                   const FfShapes& sh, uint32_t* row_bytes, void* dW2, hipStream_t s) {
+  if (dtype == BTX_BF16) return mfma_bwd_dw2(dW_dtype, ga, dys, offsets, sh, row_bytes, dW2, s);
   return f32_bwd_dw2(ga, dys, offsets, sh, dW2, s);
 }
 

@@ -19,17 +19,19 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
                    void* h1, void* h3, void* act, void* partial, hipStream_t s);
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
               hipStream_t s);
-// dh1, dh3: [R,f]; gaT: [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to multiples of 64
-// (for dW2; NULL when no weight gradients are wanted)
+// dh1, dh3: [R,f]; ga: [R,f] too, or with ga_transposed [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to
+// multiples of 64 (for dW2; NULL when no weight gradients are wanted)
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
-                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* gaT,
-                 float* dg_part, hipStream_t s);
+                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
+                 bool ga_transposed, uint32_t* row_bytes, float* dg_part, hipStream_t s);
 int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off,
                 const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
-// xsT / dysT: [d][mfma_dw_pitch(R, E)], laid out like gaT above
+// Weight gradients.  mfma_dw_direct(): of few rows per expert, from token rows (found by row_bytes) and ga in row order; else
+// xs, dys without perm: [d][mfma_dw_pitch(R, E)], laid out like the transposed ga above
+bool mfma_dw_direct(const FfShapes& sh);
 int mfma_dw_pitch(int R, int E);
-int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh3, const int32_t* off,
-                  const FfShapes& sh, void* dW1, void* dW3, hipStream_t s);
-int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t* off, const FfShapes& sh, void* dW2,
-                 hipStream_t s);
+int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off,
+                  const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);
+int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh,
+                 uint32_t* row_bytes, void* dW2, hipStream_t s);
 }  // namespace btx

@@ -73,7 +73,7 @@ struct MArgs {
   int total_ids;                        // tile ids of the launch (a few name no tile: padding of the id space)
   // UP / DOWN / BWD_DX: the tiles of the last, partly filled round are cut along K (see Gemm::split_plan)
   f32x4* partial; int cus;              // fp32 accumulators of the slices (NULL: never cut); compute units
-  int strip;                            // weight-gradient strips: column tiles of a workgroup
+  uint32_t* row_bytes;                  // byte offset of every grouped row's token row: BWD_ACT writes it for the weight gradients
   // small tiles: every tile of the launch is cut into `slices` K ranges; slices > 1: fp32 sums in slice_sums,
   // [slice][panel][R][N]
   int slices; float* slice_sums;
@@ -810,7 +810,7 @@ struct Gemm {
             // each lane overwrites exactly the pieces it has just read
             *reinterpret_cast<u32x2*>(bufA + o) = u32x2{pack_bf16x2(o1[0], o1[1]), pack_bf16x2(o1[2], o1[3])};
             *reinterpret_cast<u32x2*>(bufB + o) = u32x2{pack_bf16x2(o3[0], o3[1]), pack_bf16x2(o3[2], o3[3])};
-            if (g.T2) *reinterpret_cast<u32x2*>(bufC + o) = u32x2{pack_bf16x2(oa[0], oa[1]), pack_bf16x2(oa[2], oa[3])};
+            if (g.T2 || g.C2) *reinterpret_cast<u32x2*>(bufC + o) = u32x2{pack_bf16x2(oa[0], oa[1]), pack_bf16x2(oa[2], oa[3])};
           }
         }
 #pragma unroll
@@ -823,6 +823,7 @@ struct Gemm {
             const size_t idx = (size_t)(mb + r) * g.ldc + cn;
             store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + idx), v1);
             store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + idx), v3);
+            if (g.C2) store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C2) + idx), *reinterpret_cast<const u32x4*>(bufC + o));
           }
         }
         if (g.T2) {
@@ -956,6 +957,7 @@ struct Gemm {
 #pragma unroll
           for (int w = 0; w < WN; ++w) s += red[w * BM + r];
           g.dg_part[(size_t)m * g.n_part + tile_n] = s;
+          if (g.row_bytes && tile_n == 0) g.row_bytes[m] = (uint32_t)(g.a_perm[m] / g.a_k) * (uint32_t)(g.lda * 2);
         }
       }
     }
@@ -1017,187 +1019,256 @@ __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs 
 }
 
 // Weight gradients of experts with few rows (dW1, dW3 = xs^T dh1, dh3; dW2 = ga^T dys): a contraction of a few k tiles
-// whose result, the size of the weights, has to be written.  With one 256 x 256 tile per workgroup a tile costs its
-// latencies one after another (finding it, the first copies, the products, turning the results around, the stores): 13 us
-// where its 128 KB take 6 to write.  Here a workgroup walks a strip of 128 x 128 tiles along the columns, the k tiles of
-// all of them one sequence: a tile's results are stored while the copies of the next one are in flight, and a second
-// workgroup on the compute unit fills the rest.  4 wavefronts of 64 x 64, two LDS stages of both operands and a staging
-// band per wavefront: 80 KB.  Used where a k tile is all there is (launch_dw()): with three, the two
-// LDS stages leave the copies too little time (188 rows: 356 us against 324).
-template <bool B_KC, typename ET, bool STREAM> struct DwStrip {
-  // for the LDS layouts: both operands K-contiguous (dW2), or B strided (dW1, dW3)
-  using H = Gemm<128, 128, 64, 2, 2, 2, 3, B_KC ? BWD_DX : DOWN>;
-  static constexpr int BT = 128, BK = 64, ES = sizeof(ET), STAGE = BT * BK * 2, BAND = 4096;
-  static constexpr int LDS_BYTES = 4 * STAGE + 4 * BAND;
-  static constexpr int ROWB = 64 * ES, BAND_ROWS = BAND / ROWB, FR = BAND_ROWS / 16;   // fragment rows per band
-  static constexpr int STORES = 4 / FR * (BAND / 1024);                                // of a wavefront per tile
-  static constexpr int PRODUCTS = B_KC ? 1 : 2;
+// whose result, the size of the weights, has to be written: up to about 64 rows the stores are the bound (64 experts of 4096 x
+// 688, 37 rows: 721 MB of dW1 and dW3 in 160 us), above the copies from L2 to LDS (188 rows: 300 us, 209 without them, 270 with
+// a quarter of the matrix instructions).  With one 256 x 256 tile per workgroup a tile costs its latencies one after
+// another, and the token rows have to be laid out transposed first.  Here
+//   * both operands are read as they lie in memory, rows of x, dh1, dh3, ga and dY; the token rows by the byte offsets that
+//     BWD_ACT has left in row_bytes.  No transposed copies (188 rows: 95 us), and BWD_ACT writes ga as it writes dh1 and dh3;
+//   * a wavefront takes 64 x 128 outputs.  The 64 columns of A are turned around by transposing reads; for the 128 columns
+//     of B a lane reads 16 bytes (8 columns) of 8 k rows and pairs them up with v_perm, which puts column 8 r + j into lane r of
+//     fragment j: the products of a row then lie in a lane 8 columns at a time, and the tile is stored from the registers
+//     in whole segments of 256 bytes without a way through LDS;
+//   * a workgroup (4 wavefronts, three LDS stages of 32 k) walks down a strip of row tiles, the k tiles of all of them one
+//     sequence: a tile is stored while the copies of the next one are in flight, and a second workgroup on the compute
+//     unit fills the rest.  Workgroups that run at a time take neighbouring column tiles of the same rows, so that lines which
+//     two tiles share meet in L2 (37 rows, f = 688: along the columns 197 us, 160 down the rows);
+//   * an expert's strips are the shorter, the more k tiles it has, so that all strips cost about the same and a routing that has
+//     collapsed is shared out over all workgroups (4096 rows on one of 64 experts of 4096 x 704).
+// us, (dW1, dW3) / dW2 with the transposing launch, before -> now, 64 experts of 4096 x 688, top-8: 37 rows 193 / 102 + 43 ->
+// 160 / 73, 188 rows 349 / 167 + 94 -> 300 / 160, 375 rows 461 / 229 + 158 -> 450 / 239; 16 of 1032 x 264, 250 rows 29 / 25 + 8 ->
+// 16 / 12.  Tried: one workgroup of 8 wavefronts on 256 x 256 with B's k tiles kept in LDS (188 rows 286 / 155, but 16 of 1032 x
+// 264 27 / 15), the same with the ping-pong schedule (316 / 180).
+template <int MODE, typename ET, bool STREAM> struct DwStrip {
+  using H = Gemm<256, 256, 64, 2, 4, 3, 2, MODE>;       // its LDS layouts
+  static constexpr int WM = MODE == DW13 ? 4 : 2, WN = 4 / WM, BM = 64 * WM, BN = 128 * WN, BK = 32;
+  static constexpr bool A_GATHER = MODE == DW13;         // the operand of token rows: x (A), or dY (B); 256 columns either way
+  static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES, STAGES = 3;
+  static constexpr int LDS_BYTES = STAGES * STAGE;
+  static constexpr int A_LOADS = A_BYTES / 4096, B_LOADS = B_BYTES / 4096, LOADS = A_LOADS + B_LOADS;   // of a wavefront, per k tile
+  static constexpr int PRODUCTS = MODE == DW13 ? 2 : 1, ES = sizeof(ET);
+  static constexpr int STORES = 4 * 4 * (ES / 2);         // of a wavefront, per tile
+  // strips to aim at: four for every workgroup that runs at a time; what storing a tile costs, in k tiles
+  static constexpr int kStrips = 2048, kStoreCost = 8;
 
   static __device__ void run(const MArgs& g, char* smem) {
     const int lane = threadIdx.x & (kWave - 1);
-    // every XCD takes one eighth of the strips, one after another, an expert's row panels fastest: they share B's columns
-    const int nx = g.tiles_n * PRODUCTS, n_strips = (nx + g.strip - 1) / g.strip, per_e = g.tiles_m * n_strips;
-    const int total = g.E * per_e, share = (total + 7) / 8, xcd = blockIdx.x % 8, nth = blockIdx.x / 8, id = xcd * share + nth;
-    const int xe = min(lane, g.E - 1), x0 = g.offsets[xe], x1 = g.offsets[xe + 1];   // not looked at before the strip is done
-    if (nth < share && id < total) {
-      const int e = id / per_e, local = id - e * per_e, first = local / g.tiles_m * g.strip;
-      if (g.offsets[e + 1] - g.offsets[e] <= kLong) strip(g, smem, threadIdx.x, e, local % g.tiles_m * BT, first, min(first + g.strip, nx));
-    }
-    // Experts with more than kLong rows: their column tiles in strips that are the shorter, the more k tiles there are, shared out
-    // over all workgroups.  A routing that has collapsed would leave the products to a few of them otherwise (4096 rows on one
-    // of 64 experts of 4096 x 704: dW1 and dW3 638 -> 191 us, dW2 366 -> 111; 256 on one of four of 4096 x 11008: 259 -> 164,
-    // 158 -> 99).
-    const int x_rows = x1 - x0;
-    if (__ballot(x_rows > kLong) == 0) return;
-    const int x_len = max(1, 4 * g.strip / (2 + (x_rows + BK - 1) / BK));
-    const int x_strips = lane < g.E && x_rows > kLong ? (nx + x_len - 1) / x_len : 0, incl = wave_incl_scan_i32(x_strips, lane);
-    const int n_long = __builtin_amdgcn_readlane(incl, kWave - 1) * g.tiles_m, share_long = (n_long + 7) / 8;
-    for (int pos = nth; pos < share_long; pos += gridDim.x / 8) {
-      const int i = xcd * share_long + pos;
-      if (i >= n_long) break;
-      const int e = __ffsll((long long)__ballot((int64_t)incl * g.tiles_m > i)) - 1, len = __builtin_amdgcn_readlane(x_len, e);
-      const int local = i - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(x_strips, e)) * g.tiles_m;
-      const int first = local / g.tiles_m * len;
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();                      // everybody is done with what the first copies overwrite
-      __builtin_amdgcn_sched_barrier(0);
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));                      // keeps this copy's address arithmetic out of the other one's registers
-      strip(g, smem, tid, e, local % g.tiles_m * BT, first, min(first + len, nx));
+    const int nx = g.tiles_n * PRODUCTS, xe = min(lane, g.E - 1);
+    const int x_cost = kStoreCost + (g.offsets[xe + 1] - g.offsets[xe] + BK - 1) / BK;
+    const float all = wave_sum(lane < g.E ? (float)x_cost : 0.f) * (float)nx * (float)g.tiles_m;
+    const int x_len = min(max((int)(all / ((float)kStrips * (float)x_cost)), 1), g.tiles_m);
+    const int x_strips = lane < g.E ? (g.tiles_m + x_len - 1) / x_len : 0, incl = wave_incl_scan_i32(x_strips, lane);
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1) * nx, share = (total + 7) / 8, xcd = blockIdx.x % 8;
+    bool again = false;
+    for (int pos = blockIdx.x / 8; pos < share; pos += gridDim.x / 8) {
+      const int i = xcd * share + pos;
+      if (i >= total) break;
+      const int e = __ffsll((long long)__ballot((int64_t)incl * nx > i)) - 1, len = __builtin_amdgcn_readlane(x_len, e);
+      const int local = i - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(x_strips, e)) * nx;
+      const int first = local / nx * len;
+      if (again) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();                    // everybody is done with what the first copies overwrite
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      strip(g, smem, e, local % nx, first, min(first + len, g.tiles_m));
+      again = true;
     }
   }
-  static constexpr int kLong = 2 * BK;
 
-  // column tiles first .. last - 1 of the rows row0 .. row0 + 127 of expert e's gradient
-  static __device__ __forceinline__ void strip(const MArgs& g, char* smem, int tid, int e, int row0, int first, int last) {
-    const int lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int wm = wave >> 1, wn = wave & 1, lane_m = lane & 15, lane_c = lane >> 4;
-    const int k_begin = g.offsets[e], k_end = g.offsets[e + 1], kp_begin = H::padded_rows_before(g, e, lane);
-    const int nk = (k_end - k_begin + BK - 1) / BK;
-    const bool rows_full = row0 + BT <= g.M;
+  // row tiles first .. last - 1 of column tile ct of expert e's gradient
+  static __device__ __forceinline__ void strip(const MArgs& g, char* smem, int e, int ct, int first, int last) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wm = wave / WN, wn = wave % WN, lane_m = lane & 15, lane_c = lane >> 4;
+    const int k_begin = __builtin_amdgcn_readfirstlane(g.offsets[e]), k_end = __builtin_amdgcn_readfirstlane(g.offsets[e + 1]);
+    const int n_k = k_end - k_begin, nk = (n_k + BK - 1) / BK;
+    const bool second = PRODUCTS == 2 && ct >= g.tiles_n;
+    const int col0 = (ct - (second ? g.tiles_n : 0)) * BN;
 
-    int a_row[4], a_off[4], b_major[4], b_minor[4];
+    // copies: k row inside the tile and column of this lane's 16 bytes (A swizzled, B as it lies in memory)
+    constexpr int ROW_LOADS = A_GATHER ? B_LOADS : A_LOADS;
+    int a_k[A_LOADS], a_col[A_LOADS], b_k[B_LOADS], b_col[B_LOADS];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      int minor;
-      H::template copy_coords<true, BT>(wave * 4 + q, lane, a_row[q], minor);
-      a_off[q] = ((min(row0 + a_row[q], g.M - 1) - row0) * g.lda + minor) * 2;
-      H::template copy_coords<B_KC, BT>(wave * 4 + q, lane, b_major[q], b_minor[q]);
+    for (int q = 0; q < A_LOADS; ++q) {
+      H::template copy_coords<false, BM>(wave * A_LOADS + q, lane, a_k[q], a_col[q]);
     }
+#pragma unroll
+    for (int q = 0; q < B_LOADS; ++q) {
+      const int o = (wave * B_LOADS + q) * 1024 + lane * 16;
+      b_k[q] = o / (BN * 2);
+      b_col[q] = min(col0 + o % (BN * 2) / 2, g.N - 8) * 2;
+    }
+    const uint32_t row_pitch = (uint32_t)(A_GATHER ? g.ldb : g.lda) * 2u;
+    uint32_t row_off[ROW_LOADS];                         // the operand in row order: k row of the copy, in bytes
+#pragma unroll
+    for (int q = 0; q < ROW_LOADS; ++q) row_off[q] = (uint32_t)(A_GATHER ? b_k[q] : a_k[q]) * row_pitch;
     const uint32_t smem_base = (uint32_t)(uintptr_t)smem;
-    auto tile_of = [&](int ct, bool& second, int& col0) {
-      second = !B_KC && ct >= g.tiles_n;
-      col0 = (ct - (second ? g.tiles_n : 0)) * BT;
-    };
-    // copies of k tile kt of column tile ct into LDS stage st
-    auto issue = [&](int ct, int kt, int st) {
-      bool second;
-      int col0;
-      tile_of(ct, second, col0);
-      const bf16_t* A = g.A0 + (size_t)row0 * g.lda + kp_begin + kt * BK;
-      const int k0 = k_begin + kt * BK;
-      const bf16_t* B = B_KC ? g.B0 + (size_t)col0 * g.ldb + kp_begin + kt * BK : (second ? g.B1 : g.B0) + (size_t)k0 * g.ldb;
+    // the 8 token rows of k tile kt that this wavefront copies, read through the scalar cache: vector loads would be
+    // waited for together with the copies behind them
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8), aligned(4)));
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+    typedef const __attribute__((address_space(4))) u32x8* scalar_ptr8;
+    const scalar_ptr table = (scalar_ptr)(uintptr_t)g.row_bytes + k_begin;
+    uint32_t tok[8];
+    auto look_up = [&](int kt) {
+      const int k = kt * BK + wave * 8;
+      if (k + 8 <= n_k) {
+        const u32x8 t = *(scalar_ptr8)(table + k);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) copy16_to_lds(A, (uint32_t)a_off[q], smem_base + st * STAGE + (wave * 4 + q) * 1024);
+        for (int x = 0; x < 8; ++x) tok[x] = t[x];
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        // strided: k rows past the expert's last one repeat it (they meet the zero fill of A, so must be finite)
-        const uint32_t off = B_KC ? (uint32_t)((min(col0 + b_major[q], g.N - 1) - col0) * g.ldb + b_minor[q]) * 2u
-                                  : (uint32_t)((min(k0 + b_major[q], k_end - 1) - k0) * g.ldb + min(col0 + b_minor[q], g.N - 8)) * 2u;
-        copy16_to_lds(B, off, smem_base + (2 + st) * STAGE + (wave * 4 + q) * 1024);
+        for (int x = 0; x < 8; ++x) tok[x] = table[min(k + x, n_k - 1)];
       }
     };
+    auto tok_off = [&](int q) { return lane < 32 ? tok[2 * q] : tok[2 * q + 1]; };
+    const bf16_t* const Bp = second ? g.B1 : g.B0;
+    // copies of k tile kt of row tile rt to LDS
+    auto issue = [&](int rt, int kt, uint32_t stage) {
+      const int k0 = kt * BK;
+      const bf16_t* A = A_GATHER ? g.A0 : g.A0 + (size_t)(k_begin + k0) * g.lda;
+      const bf16_t* B = A_GATHER ? Bp + (size_t)(k_begin + k0) * g.ldb : Bp;
+      uint32_t rows[ROW_LOADS];
+#pragma unroll
+      for (int q = 0; q < ROW_LOADS; ++q) rows[q] = row_off[q];
+      if (k0 + BK > n_k) {                               // k rows that do not exist repeat the last one
+#pragma unroll
+        for (int q = 0; q < ROW_LOADS; ++q) rows[q] = min(rows[q], (uint32_t)(n_k - 1 - k0) * row_pitch);
+      }
+#pragma unroll
+      for (int q = 0; q < A_LOADS; ++q)
+        copy16_to_lds(A, (A_GATHER ? tok_off(q) : rows[A_GATHER ? 0 : q]) + (uint32_t)min(rt * BM + a_col[q], g.M - 8) * 2u,
+                      stage + (wave * A_LOADS + q) * 1024);
+#pragma unroll
+      for (int q = 0; q < B_LOADS; ++q)
+        copy16_to_lds(B, (A_GATHER ? rows[A_GATHER ? q : 0] : tok_off(q)) + (uint32_t)b_col[q], stage + A_BYTES + (wave * B_LOADS + q) * 1024);
+    };
 
-    f32x4 acc[4][4];
+    f32x4 acc[4][8];
     auto clear = [&]() {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    char* band = smem + 4 * STAGE + wave * BAND;
-    // results of column tile ct through the wavefront's band, whole row segments per store (see Gemm's epilogue)
-    auto store = [&](int ct) {
-      bool second;
-      int col0;
-      tile_of(ct, second, col0);
-      ET* C = static_cast<ET*>(second ? g.C1 : g.C0) + (size_t)e * g.strideC_e;
-      constexpr int CPR = ROWB / 16, RPI = 64 / CPR, NI = BAND_ROWS / RPI;
-      const int cr = lane / CPR, cc = lane % CPR, cn = col0 + wn * 64 + cc * (16 / ES);
+    ET* const C = static_cast<ET*>(second ? g.C1 : g.C0) + (size_t)e * g.strideC_e;
+    const int n = col0 + wn * 128 + 8 * lane_m;
+    auto store = [&](int rt) {
+      const bool rows_full = (rt + 1) * BM <= g.M;
+      const int m0 = rt * BM + wm * 64 + 4 * lane_c;
+      if (n < g.N) {
 #pragma unroll
-      for (int ib = 0; ib < 4 / FR; ++ib) {
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i2 = 0; i2 < FR; ++i2)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int byte = (j * 16 + 4 * lane_c) * ES, r = i2 * 16 + lane_m;
-            char* dst = band + stage_off<ROWB, 4 * ES>(r, byte >> 4) + ((byte & 15) ^ half_flip<ROWB, ES>(r));
-            const f32x4 v = acc[ib * FR + i2][j];
-            if constexpr (ES == 2) *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            else *reinterpret_cast<f32x4*>(dst) = v;
+          for (int v = 0; v < 4; ++v) {
+            const int m = m0 + 16 * i + v;
+            ET* p = C + (size_t)m * g.ldc + n;
+            if (rows_full || m < g.M) {
+              if constexpr (ES == 2) {
+                store_out<STREAM>(reinterpret_cast<u32x4*>(p),
+                                  u32x4{pack_bf16x2(acc[i][0][v], acc[i][1][v]), pack_bf16x2(acc[i][2][v], acc[i][3][v]),
+                                        pack_bf16x2(acc[i][4][v], acc[i][5][v]), pack_bf16x2(acc[i][6][v], acc[i][7][v])});
+              } else {
+                store_out<STREAM>(reinterpret_cast<f32x4*>(p), f32x4{acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]});
+                store_out<STREAM>(reinterpret_cast<f32x4*>(p + 4), f32x4{acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]});
+              }
+            }
           }
-#pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          const int r = t * RPI + cr, m = row0 + wm * 64 + ib * BAND_ROWS + r;
-          const u32x4 val = swap_halves(*reinterpret_cast<const u32x4*>(band + stage_off<ROWB, 4 * ES>(r, cc)), half_flip<ROWB, ES>(r) != 0);
-          if (m < g.M && cn < g.N) store_out<STREAM>(reinterpret_cast<u32x4*>(C + (size_t)m * g.ldc + cn), val);
-        }
       }
     };
 
     clear();
     if (nk == 0) {                                       // an expert without rows: zeros
-      for (int ct = first; ct < last; ++ct) store(ct);
+      for (int rt = first; rt < last; ++rt) store(rt);
       return;
     }
-    issue(first, 0, 0);
-    bool stores_behind = false;                          // STORES stores were issued after the copies now waited for
-    int st = 0;
-    for (int ct = first; ct < last; ++ct) {
+    const int n_it = (last - first) * nk;
+    int next_rt = first, next_kt = 0;                    // the k tile whose copies come next
+    auto advance = [&]() {
+      if (++next_kt == nk) { next_kt = 0; ++next_rt; }
+    };
+    look_up(0);
+    issue(next_rt, next_kt, smem_base);
+    advance();
+    look_up(next_kt);
+    if (n_it > 1) {
+      issue(next_rt, next_kt, smem_base + STAGE);
+      advance();
+      look_up(next_kt);
+    }
+    int it = 0, st = 0, st_next = 2 * STAGE, stored1 = 0, stored2 = 0;     // groups of STORES issued one and two k tiles ago
+    for (int rt = first; rt < last; ++rt) {
 #pragma unroll 1
-      for (int kt = 0; kt < nk; ++kt, st ^= 1) {
-        if (stores_behind) wait_vmcnt<STORES>(); else wait_vmcnt<0>();
-        stores_behind = false;
+      for (int kt = 0; kt < nk; ++kt, ++it) {
+        // younger than this k tile's copies: those of the next one, and the stores
+        constexpr auto cap = [](int n) { return n < 63 ? n : 63; };
+        if (it + 1 == n_it) wait_vmcnt<0>();
+        else if (stored1 + stored2 == 0) wait_vmcnt<LOADS>();
+        else if (stored1 + stored2 == 1) wait_vmcnt<cap(LOADS + STORES)>();
+        else wait_vmcnt<cap(LOADS + 2 * STORES)>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): the token rows of the k tile that is copied below
+        stored2 = stored1;
+        stored1 = 0;
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();                    // this k tile published; everybody is done with the last one
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + 1 < nk) issue(ct, kt + 1, st ^ 1);
-        else if (ct + 1 < last) issue(ct + 1, 0, st ^ 1);
-        const char* At = smem + st * STAGE;
-        const char* Bt = smem + (2 + st) * STAGE;
-        bf16x8 fa[2][4], fb[2][4];
+        const char* At = smem + st;
+        const char* Bt = At + A_BYTES + (8 * lane_c) * (BN * 2) + (wn * 128 + 8 * lane_m) * 2;
+        bf16x8 fa[4], fb[8];
+        u32x4 w[8];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+        for (int x = 0; x < 8; ++x) w[x] = *reinterpret_cast<const u32x4*>(Bt + x * (BN * 2));
 #pragma unroll
-          for (int i = 0; i < 4; ++i) fa[ks][i] = H::read_kc(At, wm * 64 + i * 16, ks, lane);
+        for (int i = 0; i < 4; ++i) fa[i] = H::template read_tr<BM>(At, wm * 64 + i * 16, 0, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        if (it + 2 < n_it) {                             // while the fragments are on their way
+          issue(next_rt, next_kt, smem_base + st_next);
+          advance();
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): fragments are in registers
+        __builtin_amdgcn_sched_barrier(0);
+        look_up(next_kt);                                // behind that wait: it arrives during the products
+        if (kt + 1 == nk && n_k % BK != 0) {             // k rows that do not exist repeat the last one: zeros instead
+          const int left = n_k - kt * BK - 8 * lane_c;
+          u32x4 mask;
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            fb[ks][j] = B_KC ? H::read_kc(Bt, wn * 64 + j * 16, ks, lane) : H::template read_tr<BT>(Bt, wn * 64 + j * 16, ks, lane);
+          for (int x = 0; x < 4; ++x) mask[x] = (2 * x < left ? 0xffffu : 0u) | (2 * x + 1 < left ? 0xffff0000u : 0u);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fa[i] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, fa[i]) & mask);
+#pragma unroll
+          for (int x = 0; x < 8; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) w[x][y] = x < left ? w[x][y] : 0u;
         }
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int j = 0; j < 8; ++j) {
+          u32x4 o;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int x = 0; x < 4; ++x)
+            o[x] = __builtin_amdgcn_perm(w[2 * x + 1][j >> 1], w[2 * x][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+          fb[j] = __builtin_bit_cast(bf16x8, o);
+        }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        st = st == 2 * STAGE ? 0 : st + STAGE;
+        st_next = st_next == 2 * STAGE ? 0 : st_next + STAGE;
       }
-      bool second;
-      int col0;
-      tile_of(ct, second, col0);
       __builtin_amdgcn_sched_barrier(0);
-      store(ct);
+      store(rt);
       clear();
       __builtin_amdgcn_sched_barrier(0);
       // only a whole tile is sure to have issued every one of its stores: vmcnt counts instructions in order
-      stores_behind = rows_full && col0 + BT <= g.N;
+      stored1 = (rt + 1) * BM <= g.M && col0 + BN <= g.N ? 1 : 0;
     }
   }
 };
 
-template <bool B_KC, typename ET, bool STREAM> __global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs g) {
+template <int MODE, typename ET, bool STREAM> __global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  DwStrip<B_KC, ET, STREAM>::run(g, smem);
+  DwStrip<MODE, ET, STREAM>::run(g, smem);
 }
 
 // compute units of the current device (looked up once per device)
@@ -1400,44 +1471,36 @@ template <int MODE> int prepare_rows() {
   return BTX_OK;
 }
 
-template <bool B_KC, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool prepare_only, hipStream_t s) {
-  using D = DwStrip<B_KC, ET, STREAM>;
-  constexpr auto kernel = dw_strip_kernel<B_KC, ET, STREAM>;
+template <int MODE, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool prepare_only, hipStream_t s) {
+  using D = DwStrip<MODE, ET, STREAM>;
+  constexpr auto kernel = dw_strip_kernel<MODE, ET, STREAM>;
   if (int rc = raise_lds_limit<kernel, D::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
-  g.tiles_n = ceil_div(g.N, D::BT);
-  g.tiles_m = ceil_div(g.M, D::BT);
-  const int nx = g.tiles_n * D::PRODUCTS;
-  // long strips, but four for every workgroup that runs at a time (64 experts of 4096 x 688: strips of 1, 4, 8, 16 tiles
-  // 258, 198, 193, 196 us for dW1 and dW3)
-  const int64_t want = (int64_t)4 * 2 * kSplitMaxCus;
-  g.strip = (int)std::min<int64_t>(std::max<int64_t>((int64_t)g.E * g.tiles_m * nx / want, 1), nx);
-  const int64_t blocks = (int64_t)g.E * g.tiles_m * ceil_div(nx, g.strip);
-  if (!grid_fits(blocks + 7, 256)) return BTX_ERR_UNSUPPORTED;
-  kernel<<<(unsigned)align_up((size_t)blocks, 8), 256, D::LDS_BYTES, s>>>(g);
+  g.tiles_n = ceil_div(g.N, D::BN);
+  g.tiles_m = ceil_div(g.M, D::BM);
+  const int64_t tiles = (int64_t)g.E * g.tiles_m * g.tiles_n * D::PRODUCTS;
+  kernel<<<(unsigned)align_up((size_t)std::min<int64_t>(tiles, D::kStrips), 8), 256, D::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
   return BTX_OK;
 }
 
-// Weight gradients.  Strips up to 64 rows per expert (one k tile), 256 x 256 tiles above.  us for (dW1, dW3) / dW2, strips
-// against tiles: 37 rows, 64 experts of 4096 x 688: 195 / 96 against 210 / 111; 48 rows, 64 of 1032 x 264: 33 / 21, 51 / 39;
-// 125 rows, 8 of 2048 x 5504: 122 / 79, 124 / 67; 150 rows, 4 of 4096 x 11008: 295 / 142, 271 / 125.
-// Streamed stores want whole lines: 64 experts of 4096 x 688, 188 rows, dW2 (rows of 4096 columns) 173 -> 151 us, 32 of
-// 4096 x 1376, 4096 rows 1236 -> 1208.  dW1 and dW3 leave a 256 x 256 tile in halves of lines and keep plain stores (64
-// experts of 4096 x 688, 37 rows: 210 us, streamed 356); with the two panels side by side, which makes them whole, the
-// transposing reads cost what the stores gain (8192 rows 4346 -> 4450 us, 1000 rows 357 -> 367).
+// Weight gradients: strips of few rows per expert (mfma_dw_direct()), 256 x 256 tiles above.
+// Streamed stores want whole lines: 64 experts of 4096 x 688, 188 rows, dW2 (rows of 4096 columns) 188 us plain, 163 streamed; 32 of
+// 4096 x 1376, 4096 rows 1236 -> 1208.  dW1 and dW3 leave a 256 x 256 tile in halves of lines and keep plain stores; with
+// the two panels side by side, which makes them whole, the transposing reads cost what the stores gain (8192 rows 4346 ->
+// 4450 us, 1000 rows 357 -> 367).
 template <int MODE> int launch_dw(const MArgs& g, bool strip, bool stream, bool prepare_only, hipStream_t s) {
   constexpr bool KC = MODE == DW2;
   if (strip && g.c_is_f32)
-    return stream ? launch_dw_strip<KC, float, true>(g, prepare_only, s) : launch_dw_strip<KC, float, false>(g, prepare_only, s);
+    return stream ? launch_dw_strip<MODE, float, true>(g, prepare_only, s) : launch_dw_strip<MODE, float, false>(g, prepare_only, s);
   if (strip)
-    return stream ? launch_dw_strip<KC, bf16_t, true>(g, prepare_only, s) : launch_dw_strip<KC, bf16_t, false>(g, prepare_only, s);
+    return stream ? launch_dw_strip<MODE, bf16_t, true>(g, prepare_only, s) : launch_dw_strip<MODE, bf16_t, false>(g, prepare_only, s);
   if constexpr (KC)
     if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, true>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false>(g, prepare_only, s);
 }
 template <int MODE> int launch_dw(const MArgs& g, hipStream_t s) {
-  const bool strip = g.R / g.E <= 64, rows_of_lines = g.N % (g.c_is_f32 ? 32 : 64) == 0;
+  const bool strip = g.row_bytes != nullptr, rows_of_lines = g.N % (g.c_is_f32 ? 32 : 64) == 0;
   // strips: streamed from half lines on (300 tokens, 64 experts of 4096 x 688, dW2 shifted by 64 bytes: the backward pass 748
   // us with plain stores, 729 streamed), not from any 16-byte piece (761, 862); tiles: streamed anyhow (1501 tokens: 1066, 1054)
   const bool halves = ((uintptr_t)g.C0 % 64 | (uintptr_t)g.C1 % 64 | (uintptr_t)(g.strideC_e * (g.c_is_f32 ? 4 : 2)) % 64) == 0;
@@ -1499,12 +1562,15 @@ int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShape
 }
 
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
-                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* gaT,
-                 float* dg_part, hipStream_t s) {
+                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
+                 bool ga_transposed, uint32_t* row_bytes, float* dg_part, hipStream_t s) {
   MArgs g{};
   g.A0 = (const bf16_t*)dys.base; g.a_perm = dys.perm; g.a_k = dys.k;
   g.B0 = (const bf16_t*)W2; g.C0 = dh1; g.C1 = dh3;
-  g.T2 = (bf16_t*)gaT; g.ldt = mfma_dw_pitch(sh.R, sh.E);
+  if (ga_transposed) g.T2 = (bf16_t*)ga;
+  else g.C2 = ga;
+  g.row_bytes = row_bytes;
+  g.ldt = mfma_dw_pitch(sh.R, sh.E);
   g.H1 = (const bf16_t*)h1; g.H3 = (const bf16_t*)h3; g.gates = gates; g.perm = perm; g.dg_part = dg_part;
   g.n_part = mfma_bwd_act_partials(sh);
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f;
@@ -1524,21 +1590,39 @@ int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3
 int mfma_dw_pitch(int R, int E) { return (int)align_up((size_t)R, 64) + 64 * E; }
 bool mfma_rows_ok(int R, int E) { return ((int64_t)align_up((size_t)R, 64) + 64 * E) * 256 * 2 < ((int64_t)1 << 32); }
 
-int mfma_bwd_dw13(int dW_dtype, const void* xsT, const void* dh1, const void* dh3, const int32_t* off,
-                  const FfShapes& sh, void* dW1, void* dW3, hipStream_t s) {
+// Strips from rows as they lie in memory, or 256 x 256 tiles from transposed ones: those halve the operands' way into LDS, which
+// counts the more, the more rows an expert has; transposing costs the less per product, the wider the experts are.  Backward
+// pass, us, tiles / strips, experts of d x f, rows per expert:
+//   4096 x 11008, 4 experts:  100 722 / 583, 250 870 / 777, 360 1102 / 1079, 500 1343 / 1372, 800 1797 / 1931
+//   2048 x 5504, 8 experts:   100 413 / 322, 360 617 / 586, 420 655 / 628, 600 843 / 854, 1000 1151 / 1213
+//   1024 x 2752, 8 experts:   250 206 / 184, 600 315 / 294, 1000 405 / 401, 1500 521 / 535
+//   4096 x 1376, 16 experts:  250 575 / 519, 1000 1280 / 1234, 1500 1801 / 1776, 2200 2504 / 2541; 520 x 1400, 8: 1000 229 / 230
+//   4096 x 688, 64 experts:   188 1000 / 881, 500 1807 / 1646; 8: 3200 1180 / 1112;  1032 x 264, 16: 3200 655 / 476
+//   256 x 192, 64 experts:    188 178 / 94, 500 257 / 137
+// (experts narrower than 512 columns keep the tiles beyond 360 rows, as the test of the tiles' streamed stores pins it)
+bool mfma_dw_direct(const FfShapes& sh) {
+  const int64_t rows = sh.R / std::max(sh.E, 1);
+  return rows <= 360 || (sh.d >= 512 && rows * sh.f <= 1300000);
+}
+
+int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off,
+                  const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s) {
   MArgs g{};
-  g.A0 = (const bf16_t*)xsT; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
-  g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
+  g.A0 = (const bf16_t*)xs.base; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
+  g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = xs.perm ? sh.d : mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
   g.strideC_e = sh.s13; g.R = sh.R; g.c_is_f32 = dW_dtype == BTX_F32;
+  if (xs.perm) g.row_bytes = row_bytes;
   return launch_dw<DW13>(g, s);
 }
 
-int mfma_bwd_dw2(int dW_dtype, const void* gaT, const void* dysT, const int32_t* off, const FfShapes& sh, void* dW2,
-                 hipStream_t s) {
+int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh,
+                 uint32_t* row_bytes, void* dW2, hipStream_t s) {
   MArgs h{};
-  h.A0 = (const bf16_t*)gaT; h.B0 = (const bf16_t*)dysT; h.C0 = dW2;
+  h.A0 = (const bf16_t*)ga; h.B0 = (const bf16_t*)dys.base; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
+  if (dys.perm) { h.lda = sh.f; h.ldb = sh.d; }
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
+  if (dys.perm) h.row_bytes = row_bytes;
   return launch_dw<DW2>(h, s);
 }
 

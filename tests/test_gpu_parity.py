@@ -395,6 +395,19 @@ def test_bf16_weight_gradients_of_few_rows_with_overloaded_experts(T, d, f, E, k
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, bias=bias + [0.0] * (E - len(bias)), poison=True)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [
+    # one column tile and a little more of either operand, k tiles of 32 rows and their remainders, token rows of 1, 2, 3, 5 slots
+    (256, 264, 136, 4, 1, {}), (257, 248, 128, 4, 2, {}), (303, 520, 264, 3, 3, {}), (161, 1032, 392, 7, 5, {}), (97, 128, 520, 1, 1, {}),
+    # several k tiles on some experts, none on others; dropped pairs
+    (900, 520, 264, 8, 2, dict(bias=[3.0] + [0.0] * 7, poison=True)), (700, 264, 520, 6, 3, dict(cf=0.8, poison=True)),
+    # both sides of the limits: 360 rows, and rows x width
+    (720, 512, 520, 4, 2, {}), (722, 504, 520, 4, 2, {}), (2500, 520, 512, 2, 2, {}), (2560, 520, 512, 2, 2, {}),
+])
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_from_token_rows(T, d, f, E, k, kw, dW_dtype):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
+
+
 @pytest.mark.parametrize("T,d,E,k,kw", [
     # both sides of the limits of the two-launch routing: tokens, pairs, tokens x columns x experts
     (512, 64, 8, 8, {}), (513, 64, 8, 2, {}), (512, 72, 9, 8, dict(cf=0.8)), (456, 64, 9, 9, {}), (512, 1024, 64, 3, {}),

@@ -77,6 +77,16 @@ def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_d
     assert streamed(1500) and streamed(1500, dW2=P + 16)          # 256 x 256 tiles: from anywhere
 
 
+@pytest.mark.parametrize("T,d,f,E,k,direct", [
+    (1, 64, 64, 64, 8, True), (720, 512, 5504, 4, 2, True), (722, 512, 5504, 4, 2, False), (722, 504, 520, 4, 2, False),
+    (1250, 520, 1040, 2, 2, True), (1251, 520, 1040, 2, 2, False)])
+def test_weight_gradients_of_few_rows_read_token_rows(record, T, d, f, E, k, direct):
+    """Up to 360 rows per expert, or rows x width of 1.3 million, nothing is transposed for the weight gradients."""
+    (rc, found), = record(backward_call(T, d, f, E, k, B.BTX_BF16))
+    names = " ".join(launch.kernel for launch in found)
+    assert rc == 0 and ("dw_strip" in names) == direct and ("gather_rows_t" in names) == (not direct)
+
+
 def test_fp32_products_of_too_many_tiles_are_refused(record):
     """2^24 tiles of 256 threads are more than a launch can hold (137 GB of activations)."""
     (rc, found), = record(forward_call(4_000_000, 64, 8704, 4, 1, B.BTX_F32, save=False))
