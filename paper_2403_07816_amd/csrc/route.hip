@@ -167,8 +167,8 @@ __device__ __forceinline__ void select_experts(float s, bool live, int lane, int
 // A decoding step or a prompt is latency: the kernels below gave it one wavefront per 4 tokens, which walked its rows
 // twice, and three more launches (16 tokens of 4096 columns with the normalisation: 66 us).  Here every token has a
 // workgroup whose threads share its columns and read W_router as it lies, and one workgroup does the grouping:
-// 16 tokens of 4096 columns with the normalisation 16 us, 301 tokens 21, 512 tokens 25.  The one workgroup takes over
-// from there: 1024 tokens of 256 to 1024 columns 31 to 37 us, against 28 to 34 with the four launches.
+// 16 tokens of 4096 columns with the normalisation 11 us, 301 tokens 15, 512 tokens 16.  From there on it depends, see
+// route_is_small().
 constexpr int kSmallTokens = 512, kSmallPairs = 4096;
 constexpr int64_t kSmallTraffic = (int64_t)1 << 25;     // T * d * E: every token reads the whole W_router (128 MB in all)
 constexpr int kSmallThreads = 256, kGroupThreads = 1024;
@@ -248,69 +248,104 @@ __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
   select_experts(s, live, lane, t, E, k, mode, inv_tau, U, topk_idx, gates, probs, psum, gsum, cnt);
 }
 
-// One workgroup: statistics, offsets and lb_loss, and the stable grouping of the pairs.  The rank of a pair among its
-// expert's comes from ballots, 1024 pairs a round; it waits in inv_pos until the offsets are known.
-__global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
+// One workgroup: statistics, offsets and lb_loss, and the stable grouping of the pairs.  Latency is all it costs: what the
+// token kernel left is requested at once (up to four pairs a thread), ranks stay in registers, and a wavefront finds the
+// lanes of the same expert with a ballot for every bit of the index.  With a ballot per expert, three barriers for every 1024
+// pairs and ranks that waited in inv_pos: 512 tokens, 4 experts, top-2
+// 12.4 us, now 6; 64 experts, top-8 38, now 16.
+// ROUNDS: pairs a thread can have; PIECE: floats of [token][expert] that LDS holds of gates and of probabilities.  (The large
+// form's code alone costs a decoding step 0.9 us.)
+template <int ROUNDS, int PIECE> __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
     int T, int E, int k, int cap, int lb_mode, float lb_alpha, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ gates, const float* __restrict__ probs, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_pos,
     float* __restrict__ gate_sum, float* __restrict__ prob_sum, float* __restrict__ lb_loss) {
-  constexpr int kWaves = kGroupThreads / kWave, kDense = 8192;
-  __shared__ int s_cnt[kWaves][kMaxExperts], s_first[kMaxExperts], s_kept;
-  __shared__ float s_dense[kDense], s_sum[2][kWaves][kMaxExperts];
+  constexpr int kWaves = kGroupThreads / kWave, kLoads = PIECE / kGroupThreads;
+  static_assert(PIECE % kGroupThreads == 0 && PIECE / kMaxExperts >= kWaves, "a piece holds kWaves tokens of any number of experts");
+  __shared__ int s_cnt[ROUNDS * kWaves][kMaxExperts], s_first[kMaxExperts], s_kept;
+  __shared__ float s_gate[PIECE], s_prob[PIECE], s_sum[2][kWaves][kMaxExperts];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, R = T * k;
 
+  int e[ROUNDS], local[ROUNDS];
+  float gate[ROUNDS];
+#pragma unroll
+  for (int j = 0; j < ROUNDS; ++j) {
+    const int i = j * kGroupThreads + threadIdx.x;
+    e[j] = i < R ? topk_idx[i] : -1;
+    gate[j] = i < R ? gates[i] : 0.f;
+    if (j * kGroupThreads < R) s_cnt[j * kWaves + wave][lane] = 0;
+  }
+
   // ---- gate and probability sums: thread (expert lane, group wave) adds every kWaves-th token, groups in order.  The
-  // gates are laid out [token][expert] first, as many tokens at a time as the LDS piece holds.
+  // gates are laid out [token][expert] first, as many tokens at a time as the LDS pieces hold.
   float g = 0.f, p = 0.f;
-  const int span = min(T, kDense / E);
+  const int span = min(T, PIECE / E / kWaves * kWaves);
   for (int t0 = 0; t0 < T; t0 += span) {
     const int n = min(span, T - t0);
-    for (int i = threadIdx.x; i < n * E; i += kGroupThreads) s_dense[i] = 0.f;
+    float v[kLoads];
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x) {
+      const int i = x * kGroupThreads + threadIdx.x;
+      v[x] = i < n * E ? probs[(size_t)t0 * E + i] : 0.f;
+    }
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x)
+      if (x * kGroupThreads < n * E) s_gate[x * kGroupThreads + threadIdx.x] = 0.f;
     __syncthreads();
-    for (int i = threadIdx.x; i < n * k; i += kGroupThreads) {
-      s_dense[(i / k) * E + topk_idx[t0 * k + i]] = gates[t0 * k + i];
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x)
+      if (x * kGroupThreads < n * E) s_prob[x * kGroupThreads + threadIdx.x] = v[x];
+#pragma unroll
+    for (int j = 0; j < ROUNDS; ++j) {
+      const int i = j * kGroupThreads + threadIdx.x - t0 * k;      // pair of the span
+      if (e[j] >= 0 && i >= 0 && i < n * k) s_gate[i / k * E + e[j]] = gate[j];
+    }
+    if (t0 == 0) {                                      // ranks inside a wavefront's 64 pairs, and how many each expert has of them
+#pragma unroll
+      for (int j = 0; j < ROUNDS; ++j) {
+        local[j] = 0;
+        if (j * kGroupThreads >= R) continue;
+        unsigned long long same = __ballot(e[j] >= 0);
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+          const unsigned long long ones = __ballot((e[j] >> b) & 1);
+          same &= (e[j] >> b) & 1 ? ones : ~ones;
+        }
+        local[j] = __popcll(same & ((1ull << lane) - 1ull));
+        if (e[j] >= 0 && local[j] == 0) s_cnt[j * kWaves + wave][e[j]] = __popcll(same);
+      }
     }
     __syncthreads();
-    if (lane < E)
+    if (lane < E) {
+#pragma unroll 8
       for (int q = wave; q < n; q += kWaves) {
-        g += s_dense[q * E + lane];
-        p += probs[(size_t)(t0 + q) * E + lane];
+        g += s_gate[q * E + lane];
+        p += s_prob[q * E + lane];
       }
-    __syncthreads();
+    }
+    if (t0 + span < T) __syncthreads();
   }
   s_sum[0][wave][lane] = g;
   s_sum[1][wave][lane] = p;
-
-  // ---- ranks
-  int running = 0;                                      // wavefront 0, lane e: pairs of expert e so far
-  for (int i0 = 0; i0 < R; i0 += kGroupThreads) {
-    const int i = i0 + threadIdx.x, e = i < R ? topk_idx[i] : -1;
-    int local = 0, mine = 0;
-    for (int q = 0; q < E; ++q) {
-      const unsigned long long m = __ballot(e == q);
-      if (e == q) local = __popcll(m & ((1ull << lane) - 1ull));
-      if (lane == q) mine = __popcll(m);
-    }
-    s_cnt[wave][lane] = mine;
-    __syncthreads();
-    if (wave == 0) {
-      for (int w = 0; w < kWaves; ++w) {
-        const int c = s_cnt[w][lane];
-        s_cnt[w][lane] = running;
-        running += c;
-      }
-    }
-    __syncthreads();
-    if (e >= 0) inv_pos[i] = s_cnt[wave][e] + local;
-    __syncthreads();
-  }
+  __syncthreads();
 
   // ---- what every expert ends with
   if (wave == 0) {
+    int running = 0;                                    // lane e: pairs of expert e so far
+    for (int w0 = 0; w0 * kWave < R; w0 += kWaves) {
+      int c[kWaves];
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) c[w] = s_cnt[w0 + w][lane];
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        s_cnt[w0 + w][lane] = running;
+        running += c[w];
+      }
+    }
     const int kept = cap > 0 ? min(running, cap) : running;
     const int incl = wave_incl_scan_i32(kept, lane);
     float gs = 0.f, ps = 0.f, term = 0.f;
+#pragma unroll
     for (int w = 0; w < kWaves; ++w) { gs += s_sum[0][w][lane]; ps += s_sum[1][w][lane]; }
     s_first[lane] = incl - kept;
     if (lane == kWave - 1) { s_kept = incl; offsets[E] = incl; }
@@ -323,16 +358,19 @@ __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
       term = u * (ps / (float)T);
     }
     float loss = 0.f;
-    for (int e = 0; e < E; ++e) loss += __shfl(term, e, kWave);   // expert order
+    for (int x = 0; x < E; ++x) loss += lane_f32(term, x);         // expert order
     if (lane == 0) *lb_loss = lb_alpha * (float)E * loss;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < R; i += kGroupThreads) {          // the thread that left the rank reads it back
-    const int rank = inv_pos[i];
+#pragma unroll
+  for (int j = 0; j < ROUNDS; ++j) {
+    const int i = j * kGroupThreads + threadIdx.x;
+    if (e[j] < 0) continue;
+    const int rank = s_cnt[j * kWaves + wave][e[j]] + local[j];
     if (cap > 0 && rank >= cap) {
       inv_pos[i] = -1;                                  // beyond the expert's capacity: dropped
     } else {
-      const int pos = s_first[topk_idx[i]] + rank;
+      const int pos = s_first[e[j]] + rank;
       perm[pos] = i;
       inv_pos[i] = pos;
     }
@@ -340,8 +378,14 @@ __global__ __launch_bounds__(kGroupThreads) void route_small_group_kernel(
   for (int r = s_kept + threadIdx.x; r < R; r += kGroupThreads) perm[r] = 0;   // no such rows: any valid pair
 }
 
+// us, four launches / two (see kSmallTokens): 4 experts, top-2, 1024 tokens of 1024 columns 14.4 / 13.6, with the normalisation
+// 17.2 / 15.5, of 4096 18.1 / 19.1 and 29.8 / 22.6; 16 experts, top-4, of 1024 600 tokens 20.5 / 19.0, 800 20.7 / 22.8; 64
+// experts, top-4, of 512 512 tokens 31 / 31, 600 31 / 34
 bool route_is_small(const RouteArgs& a) {
-  return a.T <= kSmallTokens && (int64_t)a.T * a.k <= kSmallPairs && (int64_t)a.T * a.d * a.E <= kSmallTraffic;
+  const int64_t traffic = (int64_t)a.T * a.d * a.E;
+  if ((int64_t)a.T * a.k > kSmallPairs || traffic > kSmallTraffic) return false;
+  if (a.T <= kSmallTokens) return true;
+  return a.T <= (a.E <= 4 ? 1024 : a.E <= 16 ? 640 : 0) && (a.gain || traffic <= 12000000);
 }
 
 int launch_route_small(const RouteArgs& a, hipStream_t s) {
@@ -363,9 +407,15 @@ int launch_route_small(const RouteArgs& a, hipStream_t s) {
   if (a.x_dtype == BTX_BF16) by_norm(bf16_t{});
   else by_norm(float{});
   BTX_LAUNCH_CHECK();
-  route_small_group_kernel<<<1, kGroupThreads, 0, s>>>(a.T, a.E, a.k, a.cap, a.lb_mode, a.lb_alpha, a.topk_idx, a.gates,
-                                                       a.probs, a.counts, a.offsets, a.perm, a.inv_pos, a.gate_sum,
-                                                       a.prob_sum, a.lb_loss);
+  auto group = [&](auto rounds, auto piece) {
+    route_small_group_kernel<decltype(rounds)::value, decltype(piece)::value><<<1, kGroupThreads, 0, s>>>(
+        a.T, a.E, a.k, a.cap, a.lb_mode, a.lb_alpha, a.topk_idx, a.gates, a.probs, a.counts, a.offsets, a.perm, a.inv_pos,
+        a.gate_sum, a.prob_sum, a.lb_loss);
+  };
+  const std::integral_constant<int, 1> one_round;
+  if (a.T * a.k <= kGroupThreads && a.T * a.E <= kGroupThreads) group(one_round, std::integral_constant<int, kGroupThreads>{});
+  else if (a.T * a.k <= kGroupThreads) group(one_round, std::integral_constant<int, 4 * kGroupThreads>{});
+  else group(std::integral_constant<int, kSmallPairs / kGroupThreads>{}, std::integral_constant<int, 4 * kGroupThreads>{});
   BTX_LAUNCH_CHECK();
   return BTX_OK;
 }

@@ -419,6 +419,17 @@ def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
+@pytest.mark.parametrize("T,d,E,k,kw", [
+    # one, two and four pairs a thread; all probabilities at once, in several pieces; 1024 tokens and one more
+    (256, 64, 4, 4, {}), (257, 64, 4, 4, {}), (301, 64, 64, 2, {}), (64, 64, 17, 16, dict(cf=0.8)), (512, 72, 64, 8, dict(cf=1.25)),
+    (1024, 64, 4, 4, {}), (1025, 64, 4, 2, {}), (1024, 2936, 4, 2, {}), (640, 72, 16, 6, {}), (641, 72, 16, 6, {}), (1000, 64, 1, 1, {}),
+    (999, 72, 3, 1, dict(mode=B.BTX_ROUTE_SWITCH_TOP1, cf=0.5, bias=[2.0, 0.0, 0.0])),
+])
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_routing_by_one_workgroup(T, d, E, k, kw, dtype):
+    run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
+
+
 @pytest.mark.parametrize("E", [2, 4, 8, 12])
 def test_routing_takes_a_router_matrix_at_any_float(E):
     T, d, k = 50, 264, 2
