@@ -92,6 +92,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // completion is awaited explicitly with wait_vmcnt() before the barrier that publishes a tile.
 // `base` and `lds_base` are wave-uniform by construction; readfirstlane states that to the
 // compiler where its divergence analysis cannot see it.
+// STREAM: past the L1 and marked for early eviction in the L2, for bytes that are read once.
+template <bool STREAM = false>
 __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_off, uint32_t lds_base) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
   // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
@@ -99,10 +101,16 @@ __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_of
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
   const uint64_t sp = (uint64_t)lo | ((uint64_t)hi << 32);
   const uint32_t sl = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(sl), "v"(byte_off), "s"(sp)
-               : "memory");
+  if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 sc1 nt"
+                 :
+                 : "s"(sl), "v"(byte_off), "s"(sp)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(sl), "v"(byte_off), "s"(sp)
+                 : "memory");
 }
 
 // Epilogue staging band: 32 rows of ROWB bytes in LDS, 16-byte chunks XOR-swizzled by row so
@@ -137,7 +145,8 @@ template <bool STREAM, typename V> __device__ __forceinline__ void store_out(V* 
   else *p = v;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
+// STREAM_B: the weights past the caches (stream_weights())
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0, bool STREAM_B = false,
           bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 struct Gemm {
   // K index contiguous in memory?  A always is.  In the dW products K is the grouped-row index:
@@ -554,7 +563,7 @@ struct Gemm {
           else off = (uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u;
         }
         const bool second = MODE == BWD_DX ? pass2 : (DUAL && b_second[q]);
-        copy16_to_lds(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
+        copy16_to_lds<STREAM_B>(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
       }
     };
 
@@ -964,18 +973,17 @@ struct Gemm {
   }
 };
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
-          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL, bool STREAM_B, bool STREAM>
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM>::run(g, smem);
+  Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>::run(g, smem);
 }
 
 // small tiles: 4 wavefronts, two workgroups per compute unit
-template <int BM, int WM, int WN, int NSA, int NSB, int MODE, int TAIL>
+template <int BM, int WM, int WN, int NSA, int NSB, int MODE, int TAIL, bool STREAM_B>
 __global__ __launch_bounds__(WM* WN* kWave, 2) void mfma_small_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL>::run(g, smem);
+  Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B>::run(g, smem);
 }
 
 // The K slices of small tiles added in slice order, 8 columns of a row per thread; SWIGLU: [slice][2][R][N], the
@@ -1300,11 +1308,11 @@ template <void (*Kernel)(MArgs), int LDS_BYTES> int raise_lds_limit() {
   return BTX_OK;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0,
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0, bool STREAM_B = false,
           bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 int launch(MArgs g, bool prepare_only, hipStream_t s) {
   using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
-  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM>;
+  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>;
   if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
   constexpr int BNH = G::DUAL ? BN / 2 : BN;
@@ -1352,12 +1360,12 @@ int small_slices(int64_t tiles, int nk, size_t bytes_per_slice) {
   return (int)std::max<int64_t>(std::min({fill, fit, (int64_t)(nk / 8), (int64_t)kSplitMaxSlices}), 1);
 }
 
-template <int BM, int MODE, int TAIL> int launch_small(MArgs g, bool prepare_only, hipStream_t s) {
+template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, bool prepare_only, hipStream_t s) {
   // 64 rows: three stages of both operands (72 KB); 128: two of A and three of B (80 KB, half of a compute unit's LDS)
   constexpr int WM = MODE == BWD_ACT && BM == 64 ? 1 : 2, WN = 4 / WM;
   constexpr int NSA = BM == 64 ? 3 : 2, NSB = 3;
-  using G = Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL>;
-  constexpr auto kernel = mfma_small_kernel<BM, WM, WN, NSA, NSB, MODE, TAIL>;
+  using G = Gemm<BM, 128, 64, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B>;
+  constexpr auto kernel = mfma_small_kernel<BM, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B>;
   if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
   g.tiles_n = ceil_div(g.N, G::BNH);
@@ -1446,27 +1454,50 @@ template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
   return slices < 2 ? 0 : std::min((size_t)slices * R * N * (MODE == UP ? 8 : 4), (size_t)kSplitMaxCus * 128 * 128 * sizeof(float));
 }
 
-// the instantiation for this K (see TAIL) and row tile
-template <int MODE> int launch_rows(const MArgs& g, int tile, bool prepare_only, hipStream_t s) {
+// the instantiation for this row tile, way of reading the weights (stream_weights()) and K (see TAIL)
+template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, bool prepare_only, hipStream_t s) {
   const bool whole = g.K % 64 == 0;
-  if (tile == 64) return whole ? launch_small<64, MODE, 0>(g, prepare_only, s) : launch_small<64, MODE, 2>(g, prepare_only, s);
-  if (tile == 128) return whole ? launch_small<128, MODE, 0>(g, prepare_only, s) : launch_small<128, MODE, 2>(g, prepare_only, s);
+  auto go = [&](auto stream) {
+    constexpr bool S = decltype(stream)::value;
+    if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, s);
+    if constexpr (MODE != BWD_ACT)
+      if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 0, S>(g, prepare_only, s);
+    return launch_small<128, MODE, 0, S>(g, prepare_only, s);
+  };
+  if (stream_b) return go(std::true_type{});
+  if (whole && tile <= 192) return go(std::false_type{});
+  if (tile == 64) return launch_small<64, MODE, 2, false>(g, prepare_only, s);
+  if (tile == 128) return launch_small<128, MODE, 2, false>(g, prepare_only, s);
   if constexpr (MODE != BWD_ACT)
-    if (tile == 192)
-      return whole ? launch<192, 256, 64, 2, 4, 2, 3, MODE, 0>(g, prepare_only, s)
-                   : launch<192, 256, 64, 2, 4, 2, 3, MODE, 2>(g, prepare_only, s);
+    if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 2>(g, prepare_only, s);
   if (whole) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0>(g, prepare_only, s);
   if (g.K % 64 == 32) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 1>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 2>(g, prepare_only, s);
 }
-template <int MODE> int launch_rows(const MArgs& g, hipStream_t s) { return launch_rows<MODE>(g, row_tile<MODE>(g), false, s); }
+// Weights streamed past the caches: products of one row tile per expert read them once.  Where the layer's weights are larger
+// than the memory-side cache (256 MB; smaller ones stay there from pass to pass: 135 MB, 30 rows 39 us plain, 42 streamed), with
+// room for experts that have more rows than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293), and where a row
+// of B is whole lines: else every line is fetched for two tiles (32 x 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
+//   4 x 4096 x 11008: 4 rows 200 / 180, 30 206 / 187, 64 244 / 232, 150 277 / 265;  8 x 2048 x 5504: 16 106 / 93, 64 127 / 122
+//   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143;  32 x 2048 x 2752: 30 208 / 186;  backward 468 / 441
+bool stream_weights(const MArgs& g, int tile) {
+  const int64_t avg = g.R / std::max(g.E, 1);
+  const uintptr_t at = (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)(g.strideB_e * 2) | (uintptr_t)g.ldb * 2;
+  return tile <= 192 && avg <= (tile == 128 ? 96 : tile) && (int64_t)6 * g.E * g.N * g.K >= 400000000 && at % 128 == 0 && g.K % 64 == 0;
+}
+template <int MODE> int launch_rows(const MArgs& g, hipStream_t s) {
+  const int tile = row_tile<MODE>(g);
+  return launch_rows<MODE>(g, tile, stream_weights(g, tile), false, s);
+}
 
 template <int MODE> int prepare_rows() {
   MArgs g{};
   for (int tile : {64, 128, 192, 256})
     for (int k : {64, 32, 8}) {
       g.K = k;
-      if (int rc = launch_rows<MODE>(g, tile, true, nullptr)) return rc;
+      if (int rc = launch_rows<MODE>(g, tile, false, true, nullptr)) return rc;
+      if (tile <= 192 && k == 64)
+        if (int rc = launch_rows<MODE>(g, tile, true, true, nullptr)) return rc;
     }
   return BTX_OK;
 }
@@ -1496,8 +1527,8 @@ template <int MODE> int launch_dw(const MArgs& g, bool strip, bool stream, bool 
   if (strip)
     return stream ? launch_dw_strip<MODE, bf16_t, true>(g, prepare_only, s) : launch_dw_strip<MODE, bf16_t, false>(g, prepare_only, s);
   if constexpr (KC)
-    if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, true>(g, prepare_only, s);
-  return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false>(g, prepare_only, s);
+    if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, true>(g, prepare_only, s);
+  return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, false>(g, prepare_only, s);
 }
 template <int MODE> int launch_dw(const MArgs& g, hipStream_t s) {
   const bool strip = g.row_bytes != nullptr, rows_of_lines = g.N % (g.c_is_f32 ? 32 : 64) == 0;

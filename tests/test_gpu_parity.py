@@ -419,6 +419,23 @@ def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
+@pytest.mark.parametrize("T", [16, 160, 301])          # 64-, 128- and 192-row tiles
+def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T):
+    """1.1 GB of expert weights, read past the caches where their rows start on whole lines; shifted by 64 bytes they are not."""
+    d, f, E, k = 4096, 11008, 4, 2
+    L = synth.make_layer(T, d, f, E, dtype=BF16, device="cuda", unit_rms=True, with_dY=True)
+    r = B.btx_moe_route(L["x"], L["W_router"], None, None, k)
+
+    def shifted(W):
+        return torch.empty(W.numel() + 64, dtype=W.dtype, device="cuda")[32:32 + W.numel()].view(W.shape).copy_(W)
+    results = []
+    for W1, W3, W2 in ((L["W1"], L["W3"], L["W2"]), tuple(shifted(L[n]) for n in ("W1", "W3", "W2"))):
+        out, h1, h3 = B.btx_moe_ff_forward(L["x"], W1, W3, W2, r)
+        g = B.btx_moe_ff_backward(L["dY"], L["x"], L["W_router"], W1, W3, W2, r, h1, h3)
+        results.append((out, h1, h3, g.dX, g.dW_router, g.dW1, g.dW3, g.dW2))
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
 @pytest.mark.parametrize("T,d,E,k,kw", [
     # one, two and four pairs a thread; all probabilities at once, in several pieces; 1024 tokens and one more
     (256, 64, 4, 4, {}), (257, 64, 4, 4, {}), (301, 64, 64, 2, {}), (64, 64, 17, 16, dict(cf=0.8)), (512, 72, 64, 8, dict(cf=1.25)),
