@@ -1460,17 +1460,16 @@ template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, boo
   auto go = [&](auto stream) {
     constexpr bool S = decltype(stream)::value;
     if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, s);
+    if (tile == 128) return launch_small<128, MODE, 0, S>(g, prepare_only, s);
     if constexpr (MODE != BWD_ACT)
       if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 0, S>(g, prepare_only, s);
-    return launch_small<128, MODE, 0, S>(g, prepare_only, s);
+    return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, S>(g, prepare_only, s);
   };
-  if (stream_b) return go(std::true_type{});
-  if (whole && tile <= 192) return go(std::false_type{});
+  if (whole) return stream_b ? go(std::true_type{}) : go(std::false_type{});
   if (tile == 64) return launch_small<64, MODE, 2, false>(g, prepare_only, s);
   if (tile == 128) return launch_small<128, MODE, 2, false>(g, prepare_only, s);
   if constexpr (MODE != BWD_ACT)
     if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 2>(g, prepare_only, s);
-  if (whole) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0>(g, prepare_only, s);
   if (g.K % 64 == 32) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 1>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 2>(g, prepare_only, s);
 }
@@ -1479,11 +1478,12 @@ template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, boo
 // room for experts that have more rows than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293), and where a row
 // of B is whole lines: else every line is fetched for two tiles (32 x 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
 //   4 x 4096 x 11008: 4 rows 200 / 180, 30 206 / 187, 64 244 / 232, 150 277 / 265;  8 x 2048 x 5504: 16 106 / 93, 64 127 / 122
-//   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143;  32 x 2048 x 2752: 30 208 / 186;  backward 468 / 441
+//   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143, 200 173 / 158;  32 x 2048 x 2752: 30 208 / 186, 200 294 / 283;  backward 30
+//   468 / 441, 200 746 / 718
 bool stream_weights(const MArgs& g, int tile) {
   const int64_t avg = g.R / std::max(g.E, 1);
   const uintptr_t at = (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)(g.strideB_e * 2) | (uintptr_t)g.ldb * 2;
-  return tile <= 192 && avg <= (tile == 128 ? 96 : tile) && (int64_t)6 * g.E * g.N * g.K >= 400000000 && at % 128 == 0 && g.K % 64 == 0;
+  return avg <= (tile == 128 ? 96 : tile == 256 ? 236 : tile) && (int64_t)6 * g.E * g.N * g.K >= 400000000 && at % 128 == 0 && g.K % 64 == 0;
 }
 template <int MODE> int launch_rows(const MArgs& g, hipStream_t s) {
   const int tile = row_tile<MODE>(g);
@@ -1496,7 +1496,7 @@ template <int MODE> int prepare_rows() {
     for (int k : {64, 32, 8}) {
       g.K = k;
       if (int rc = launch_rows<MODE>(g, tile, false, true, nullptr)) return rc;
-      if (tile <= 192 && k == 64)
+      if (k == 64)
         if (int rc = launch_rows<MODE>(g, tile, true, true, nullptr)) return rc;
     }
   return BTX_OK;

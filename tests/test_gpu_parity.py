@@ -419,7 +419,7 @@ def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
-@pytest.mark.parametrize("T", [16, 160, 301])          # 64-, 128- and 192-row tiles
+@pytest.mark.parametrize("T", [16, 160, 301, 420])     # 64-, 128-, 192- and 256-row tiles
 def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T):
     """1.1 GB of expert weights, read past the caches where their rows start on whole lines; shifted by 64 bytes they are not."""
     d, f, E, k = 4096, 11008, 4, 2
