@@ -41,9 +41,9 @@ int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void*
   return f32_up_swiglu(xs, W1, W3, offsets, sh, h1, h3, act, s);
 }
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
-                void* partial, hipStream_t s) {
-  if (dtype == BTX_BF16) return mfma_down(act, W2, offsets, sh, y, partial, s);
-  return f32_down(act, W2, offsets, sh, y, partial, s);
+                void* partial, int* slices, hipStream_t s) {
+  if (dtype == BTX_BF16) return mfma_down(act, W2, offsets, sh, y, partial, slices, s);
+  return f32_down(act, W2, offsets, sh, y, partial, slices, s);
 }
 int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                    const int32_t* perm, const int32_t* offsets, const FfShapes& sh, void* dh1, void* dh3, void* ga,

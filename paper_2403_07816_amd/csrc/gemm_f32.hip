@@ -445,7 +445,8 @@ int slices_of(const FfShapes& sh, bool two_passes) {
   return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
 }
 
-template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
+// left (may be NULL): K slices whose sums the caller adds himself, in g.sums
+template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
   constexpr int BM = kTile, BN = kTile, BK = kTileK;
   using G = F32Gemm<BM, BN, BK, MODE>;
   g.tiles_n = ceil_div(g.N, G::BNH);
@@ -458,7 +459,9 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s) {
   const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
   f32_gemm_kernel<BM, BN, BK, MODE><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
-  if (g.slices > 1) {
+  if (left) {
+    *left = g.slices;
+  } else if (g.slices > 1) {
     f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets,
                                                                                          g.E, g.C0);
     BTX_LAUNCH_CHECK();
@@ -481,12 +484,12 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f; g.strideB_e = sh.s13;
   return launch<UP>(g, sh.R, s);
 }
-int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, hipStream_t s) {
+int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices, hipStream_t s) {
   FArgs g{};
   g.slices = slices_of(sh, false); g.sums = (float*)sums;
   g.A0 = (const float*)act; g.B0 = (const float*)W2; g.C0 = (float*)y;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideB_e = sh.s2;
-  return launch<DOWN>(g, sh.R, s);
+  return launch<DOWN>(g, sh.R, s, slices);
 }
 int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,

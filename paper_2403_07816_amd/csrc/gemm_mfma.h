@@ -17,8 +17,9 @@ size_t mfma_forward_split_bytes(const FfShapes& sh);
 size_t mfma_backward_split_bytes(const FfShapes& sh);
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                    void* h1, void* h3, void* act, void* partial, hipStream_t s);
+// slices: see launch_down()
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
-              hipStream_t s);
+              int* slices, hipStream_t s);
 // dh1, dh3: [R,f]; ga: [R,f] too, or with ga_transposed [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to
 // multiples of 64 (for dW2; NULL when no weight gradients are wanted)
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,

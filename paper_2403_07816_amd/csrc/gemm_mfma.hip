@@ -1360,7 +1360,8 @@ int small_slices(int64_t tiles, int nk, size_t bytes_per_slice) {
   return (int)std::max<int64_t>(std::min({fill, fit, (int64_t)(nk / 8), (int64_t)kSplitMaxSlices}), 1);
 }
 
-template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, bool prepare_only, hipStream_t s) {
+// left (may be NULL): K slices whose sums the caller adds himself, in slice_sums
+template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, bool prepare_only, int* left, hipStream_t s) {
   // 64 rows: three stages of both operands (72 KB); 128: two of A and three of B (80 KB, half of a compute unit's LDS)
   constexpr int WM = MODE == BWD_ACT && BM == 64 ? 1 : 2, WN = 4 / WM;
   constexpr int NSA = BM == 64 ? 3 : 2, NSB = 3;
@@ -1379,7 +1380,9 @@ template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, b
   if (!grid_fits(blocks + 7, 256)) return BTX_ERR_UNSUPPORTED;
   kernel<<<(unsigned)align_up((size_t)blocks, 8), G::NT, G::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
-  if (g.slices > 1) {
+  if (left) {
+    *left = g.slices;
+  } else if (g.slices > 1) {
     slices_finish_kernel<MODE == UP><<<ceil_div((int64_t)g.R * (g.N / 8), 256), 256, 0, s>>>(
         g.slice_sums, g.slices, g.R, g.N, g.offsets, g.E, (bf16_t*)g.C0, (bf16_t*)g.C1, (bf16_t*)g.C2);
     BTX_LAUNCH_CHECK();
@@ -1455,19 +1458,19 @@ template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
 }
 
 // the instantiation for this row tile, way of reading the weights (stream_weights()) and K (see TAIL)
-template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, bool prepare_only, hipStream_t s) {
+template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, bool prepare_only, int* left, hipStream_t s) {
   const bool whole = g.K % 64 == 0;
   auto go = [&](auto stream) {
     constexpr bool S = decltype(stream)::value;
-    if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, s);
-    if (tile == 128) return launch_small<128, MODE, 0, S>(g, prepare_only, s);
+    if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, left, s);
+    if (tile == 128) return launch_small<128, MODE, 0, S>(g, prepare_only, left, s);
     if constexpr (MODE != BWD_ACT)
       if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 0, S>(g, prepare_only, s);
     return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, S>(g, prepare_only, s);
   };
   if (whole) return stream_b ? go(std::true_type{}) : go(std::false_type{});
-  if (tile == 64) return launch_small<64, MODE, 2, false>(g, prepare_only, s);
-  if (tile == 128) return launch_small<128, MODE, 2, false>(g, prepare_only, s);
+  if (tile == 64) return launch_small<64, MODE, 2, false>(g, prepare_only, left, s);
+  if (tile == 128) return launch_small<128, MODE, 2, false>(g, prepare_only, left, s);
   if constexpr (MODE != BWD_ACT)
     if (tile == 192) return launch<192, 256, 64, 2, 4, 2, 3, MODE, 2>(g, prepare_only, s);
   if (g.K % 64 == 32) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 1>(g, prepare_only, s);
@@ -1485,9 +1488,9 @@ bool stream_weights(const MArgs& g, int tile) {
   const uintptr_t at = (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)(g.strideB_e * 2) | (uintptr_t)g.ldb * 2;
   return avg <= (tile == 128 ? 96 : tile == 256 ? 236 : tile) && (int64_t)6 * g.E * g.N * g.K >= 400000000 && at % 128 == 0 && g.K % 64 == 0;
 }
-template <int MODE> int launch_rows(const MArgs& g, hipStream_t s) {
+template <int MODE> int launch_rows(const MArgs& g, hipStream_t s, int* left = nullptr) {
   const int tile = row_tile<MODE>(g);
-  return launch_rows<MODE>(g, tile, stream_weights(g, tile), false, s);
+  return launch_rows<MODE>(g, tile, stream_weights(g, tile), false, left, s);
 }
 
 template <int MODE> int prepare_rows() {
@@ -1495,9 +1498,9 @@ template <int MODE> int prepare_rows() {
   for (int tile : {64, 128, 192, 256})
     for (int k : {64, 32, 8}) {
       g.K = k;
-      if (int rc = launch_rows<MODE>(g, tile, false, true, nullptr)) return rc;
+      if (int rc = launch_rows<MODE>(g, tile, false, true, nullptr, nullptr)) return rc;
       if (k == 64)
-        if (int rc = launch_rows<MODE>(g, tile, true, true, nullptr)) return rc;
+        if (int rc = launch_rows<MODE>(g, tile, true, true, nullptr, nullptr)) return rc;
     }
   return BTX_OK;
 }
@@ -1584,12 +1587,13 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
 }
 
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
-              hipStream_t s) {
+              int* slices, hipStream_t s) {
+  *slices = 1;
   MArgs g{};
   g.A0 = (const bf16_t*)act; g.B0 = (const bf16_t*)W2; g.C0 = y; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d;
   g.strideB_e = sh.s2; g.R = sh.R;
-  return launch_rows<DOWN>(g, s);
+  return launch_rows<DOWN>(g, s, slices);
 }
 
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,

@@ -419,6 +419,16 @@ def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,kw", [
+    # 1, 2, 3 and 8 slots in registers and more than that; an odd number of slices, dropped pairs
+    (9, 264, 2056, 4, 1, {}), (20, 72, 2056, 5, 2, {}), (17, 264, 1544, 6, 3, dict(cf=0.8, poison=True)), (20, 264, 2056, 12, 12, {}),
+    (5, 1032, 1096, 8, 8, {}),
+])
+@pytest.mark.parametrize("dtype", [BF16, F32])
+def test_combine_adds_the_slices_of_the_down_projection(T, d, f, E, k, kw, dtype):
+    run_layer_and_check(T, d, f, E, k, dtype, unit_rms=True, backward=False, **kw)
+
+
 @pytest.mark.parametrize("T", [16, 160, 301, 420])     # 64-, 128-, 192- and 256-row tiles
 def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T):
     """1.1 GB of expert weights, read past the caches where their rows start on whole lines; shifted by 64 bytes they are not."""
