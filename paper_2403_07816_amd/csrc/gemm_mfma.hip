@@ -456,6 +456,10 @@ struct Gemm {
     const int e = tile.e, row0 = tile.row0, row_end = tile.row_end, k_begin = tile.k_begin, k_end = tile.k_end;
     const int kp_begin = tile.kp_begin, tile_n = tile.tile_n;
     const int col0 = tile_n * BNH;
+    // small tiles: an expert with more rows than expected reads its weights through the caches, where its row tiles share
+    // them (320 tokens, top-1, 4 experts of 4096 x 11008, the favoured one with more than 128 rows: forward pass 322 us with every
+    // weight streamed, 306 with none, 293 like this)
+    const bool read_once = !SMALL || row_end - tile.exp_row0 <= BM;
 
     const bf16_t* Bp0 = g.B0;
     const bf16_t* Bp1 = g.B1;
@@ -549,22 +553,26 @@ struct Gemm {
       const uint32_t stage = smem_base + B_BASE + (kt % NSB) * B_BYTES;
       const bf16_t* B0b = Bp0 + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb);
       const bf16_t* B1b = Bp1 ? Bp1 + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb) : nullptr;
+      auto copy = [&](auto stream) {
 #pragma unroll
-      for (int q = 0; q < B_LOADS; ++q) {
-        uint32_t off = b_off[q];
-        // grouped-K, strided operand: a k row past the expert's last grouped row is re-pointed at that last
-        // row.  It meets the zero fill of the transposed operand, so it must hold finite numbers: the
-        // expert's own rows were written by BWD_ACT in this call, whereas the rows behind them belong to
-        // the next expert or, past the last kept row when a capacity limit dropped pairs, to nobody
-        // (workspace bytes nothing has written, possibly NaN patterns).
-        if (GROUP_K && !B_KC) off = (uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u;
-        if (is_tail(kt)) {
-          if (B_KC) { if (b_kc[q] >= k_tail) off -= (uint32_t)(b_kc[q] * 2); }
-          else off = (uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u;
+        for (int q = 0; q < B_LOADS; ++q) {
+          uint32_t off = b_off[q];
+          // grouped-K, strided operand: a k row past the expert's last grouped row is re-pointed at that last
+          // row.  It meets the zero fill of the transposed operand, so it must hold finite numbers: the
+          // expert's own rows were written by BWD_ACT in this call, whereas the rows behind them belong to
+          // the next expert or, past the last kept row when a capacity limit dropped pairs, to nobody
+          // (workspace bytes nothing has written, possibly NaN patterns).
+          if (GROUP_K && !B_KC) off = (uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u;
+          if (is_tail(kt)) {
+            if (B_KC) { if (b_kc[q] >= k_tail) off -= (uint32_t)(b_kc[q] * 2); }
+            else off = (uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u;
+          }
+          const bool second = MODE == BWD_DX ? pass2 : (DUAL && b_second[q]);
+          copy16_to_lds<decltype(stream)::value>(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
         }
-        const bool second = MODE == BWD_DX ? pass2 : (DUAL && b_second[q]);
-        copy16_to_lds<STREAM_B>(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
-      }
+      };
+      if (STREAM_B && read_once) copy(std::bool_constant<STREAM_B>{});
+      else copy(std::false_type{});
     };
 
     f32x4 acc[TM][TN];
@@ -1478,7 +1486,7 @@ template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, boo
 }
 // Weights streamed past the caches: products of one row tile per expert read them once.  Where the layer's weights are larger
 // than the memory-side cache (256 MB; smaller ones stay there from pass to pass: 135 MB, 30 rows 39 us plain, 42 streamed), with
-// room for experts that have more rows than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293), and where a row
+// room for experts that have more rows than the average (small tiles look at the true number as well, see read_once; 128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293), and where a row
 // of B is whole lines: else every line is fetched for two tiles (32 x 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
 //   4 x 4096 x 11008: 4 rows 200 / 180, 30 206 / 187, 64 244 / 232, 150 277 / 265;  8 x 2048 x 5504: 16 106 / 93, 64 127 / 122
 //   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143, 200 173 / 158;  32 x 2048 x 2752: 30 208 / 186, 200 294 / 283;  backward 30

@@ -429,12 +429,13 @@ def test_combine_adds_the_slices_of_the_down_projection(T, d, f, E, k, kw, dtype
     run_layer_and_check(T, d, f, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
-@pytest.mark.parametrize("T", [16, 160, 301, 420])     # 64-, 128-, 192- and 256-row tiles
-def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T):
+# 64-, 128-, 192- and 256-row tiles; small tiles, one expert with several of them
+@pytest.mark.parametrize("T,k,bias", [(16, 2, 0.0), (160, 2, 0.0), (301, 2, 0.0), (420, 2, 0.0), (160, 1, 2.0), (320, 1, 2.0)])
+def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T, k, bias):
     """1.1 GB of expert weights, read past the caches where their rows start on whole lines; shifted by 64 bytes they are not."""
-    d, f, E, k = 4096, 11008, 4, 2
-    L = synth.make_layer(T, d, f, E, dtype=BF16, device="cuda", unit_rms=True, with_dY=True)
-    r = B.btx_moe_route(L["x"], L["W_router"], None, None, k)
+    d, f, E = 4096, 11008, 4
+    L = synth.make_layer(T, d, f, E, dtype=BF16, device="cuda", unit_rms=True, with_dY=True, router_bias=[bias, 0.0, 0.0, 0.0])
+    r = B.btx_moe_route(L["x"], L["W_router"], L["b_router"], None, k)
 
     def shifted(W):
         return torch.empty(W.numel() + 64, dtype=W.dtype, device="cuda")[32:32 + W.numel()].view(W.shape).copy_(W)
