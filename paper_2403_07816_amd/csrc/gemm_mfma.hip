@@ -1486,8 +1486,9 @@ template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, boo
 }
 // Weights streamed past the caches: products of one row tile per expert read them once.  Where the layer's weights are larger
 // than the memory-side cache (256 MB; smaller ones stay there from pass to pass: 135 MB, 30 rows 39 us plain, 42 streamed), with
-// room for experts that have more rows than the average (small tiles look at the true number as well, see read_once; 128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293), and where a row
-// of B is whole lines: else every line is fetched for two tiles (32 x 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
+// room for experts that have more rows than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293; small tiles look at
+// the true number as well, see read_once), and where a row of B is whole lines: else every line is fetched for two tiles (32 x
+// 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
 //   4 x 4096 x 11008: 4 rows 200 / 180, 30 206 / 187, 64 244 / 232, 150 277 / 265;  8 x 2048 x 5504: 16 106 / 93, 64 127 / 122
 //   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143, 200 173 / 158;  32 x 2048 x 2752: 30 208 / 186, 200 294 / 283;  backward 30
 //   468 / 441, 200 746 / 718
