@@ -128,5 +128,11 @@ def backward_call(T, d, f, E, k, dtype, dW_dtype=None, dW2=P, stride=None):
             [p, p, p, p, p, dW2, dtype if dW_dtype is None else dW_dtype, p, PLENTY, 0])
 
 
+def route_call(T, d, E, k, dtype, norm=False):
+    lead = [P, dtype, P, 1e-5, 2 * P, P] if norm else [P, dtype]
+    return ("btx_moe_norm_route" if norm else "btx_moe_route",
+            lead + [P, 0, 0, T, d, E, k, 0, 0, 0.01, 1.0, 0.0] + [P] * 10 + [P, PLENTY, 0])
+
+
 def adamw_call(n, dtype=B.BTX_BF16, lowp=P, master=P):
     return ("btx_adamw_step", [master, P, P, P, dtype, lowp, n, 3, 1e-4, 0.9, 0.95, 1e-8, 0.1, 0])

@@ -616,9 +616,10 @@ def test_block_rmsnorm_route_matches_plain_route_on_the_normalised_rows():
 
 
 @pytest.mark.parametrize("T,d,E,dtype", [(600, 4096, 4, BF16), (3001, 1032, 7, BF16), (4201, 2048, 8, BF16), (700, 512, 8, F32), (4201, 512, 3, F32),
-                                         (530, 8200, 2, F32)])
+                                         (530, 8200, 2, F32), (1024, 4096, 4, BF16), (640, 4096, 8, BF16), (1024, 8200, 4, F32), (520, 4104, 7, F32)])
 def test_block_rmsnorm_route_gives_the_same_bits_with_other_wavefronts(T, d, E, dtype):
-    """Sizes where the fused kernel and btx_moe_route split the tokens of a block over different numbers of wavefronts."""
+    """Sizes where the fused kernel and btx_moe_route split the tokens of a block over different numbers of wavefronts, and sizes
+    between those that few tokens' kernels take and those that they do not."""
     h = (synth.make_layer(T, d, 64, E, dtype=dtype)["x"].float() * 3.0).to(dtype).cuda()
     gain = torch.linspace(0.5, 1.5, d).cuda()
     Wr = 0.02 * torch.randn((d, E), generator=torch.Generator().manual_seed(E)).cuda()

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2403_07816_amd import binding as B
 
-from launches import P, adamw_call, backward_call, forward_call, launches
+from launches import P, adamw_call, backward_call, forward_call, launches, route_call
 from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
@@ -180,6 +180,18 @@ def test_wavefronts_that_share_16_tokens(record, dtype, norm, T, d, E, waves):
         assert "0, false, 8, 1, 1>" in tokens.kernel
     else:
         assert tokens.block[0] == 64 * waves and f", {waves}, " in tokens.kernel
+
+
+@pytest.mark.parametrize("dtype", [B.BTX_F32, B.BTX_BF16])
+@pytest.mark.parametrize("E", [1, 2, 3, 4, 5, 8, 9, 12, 16, 17, 64])
+def test_routing_takes_the_same_way_with_and_without_the_normalisation(record, E, dtype):
+    """btx_moe_norm_route routes exactly as btx_moe_route does from the rows it wrote: few tokens go to the same kernels in both, as
+    the kernels for few and for many tokens add up a logit in different orders."""
+    shapes = [(T, d) for T in (1, 500, 512, 513, 600, 640, 641, 750, 1000, 1024, 1025) for d in (64, 256, 512, 1024, 1040, 2048, 2936, 4096, 8192)]
+    found = record(*(route_call(T, d, E, min(E, 2), dtype, norm) for T, d in shapes for norm in (False, True)))
+    for shape, (rc, plain), (norm_rc, norm) in zip(shapes, found[::2], found[1::2]):
+        assert rc == norm_rc == 0
+        assert ("route_small" in plain[0].kernel) == ("route_small" in norm[0].kernel), shape
 
 
 @pytest.mark.parametrize("T,d,f,E,product,tile", [
