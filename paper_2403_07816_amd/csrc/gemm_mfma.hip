@@ -1044,7 +1044,10 @@ __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs 
 //   * a wavefront takes 64 x 128 outputs.  The 64 columns of A are turned around by transposing reads; for the 128 columns
 //     of B a lane reads 16 bytes (8 columns) of 8 k rows and pairs them up with v_perm, which puts column 8 r + j into lane r of
 //     fragment j: the products of a row then lie in a lane 8 columns at a time, and the tile is stored from the registers
-//     in whole segments of 256 bytes without a way through LDS;
+//     in whole segments of 256 bytes without a way through LDS.  fp32 gradients: two times 8 bytes, which makes it columns 4 r + j
+//     and 64 + 4 r + j, so that 16 lanes store 256 bytes in a row as well.  With 8 columns to a lane every store left half of each
+//     64 bytes out, which is what streamed stores pay for (backward pass with fp32 gradients, transposed tiles / 8 columns /
+//     now: 128 tokens, 4 experts of 4096 x 11008 814 / 1410 / 684 us, 1024 tokens, 32 of 4096 x 1376 772 / 1413 / 698);
 //   * a workgroup (4 wavefronts, three LDS stages of 32 k) walks down a strip of row tiles, the k tiles of all of them one
 //     sequence: a tile is stored while the copies of the next one are in flight, and a second workgroup on the compute
 //     unit fills the rest.  Workgroups that run at a time take neighbouring column tiles of the same rows, so that lines which
@@ -1064,6 +1067,7 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
   static constexpr int A_LOADS = A_BYTES / 4096, B_LOADS = B_BYTES / 4096, LOADS = A_LOADS + B_LOADS;   // of a wavefront, per k tile
   static constexpr int PRODUCTS = MODE == DW13 ? 2 : 1, ES = sizeof(ET);
   static constexpr int STORES = 4 * 4 * (ES / 2);         // of a wavefront, per tile
+  static constexpr int LANE_COLS = 16 / ES;               // columns of B in a row that a lane reads and stores: 16 bytes of the result
   // strips to aim at: four for every workgroup that runs at a time; what storing a tile costs, in k tiles
   static constexpr int kStrips = 2048, kStoreCost = 8;
 
@@ -1169,7 +1173,7 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
         for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     ET* const C = static_cast<ET*>(second ? g.C1 : g.C0) + (size_t)e * g.strideC_e;
-    const int n = col0 + wn * 128 + 8 * lane_m;
+    const int n = col0 + wn * 128 + LANE_COLS * lane_m;
     auto store = [&](int rt) {
       const bool rows_full = (rt + 1) * BM <= g.M;
       const int m0 = rt * BM + wm * 64 + 4 * lane_c;
@@ -1187,7 +1191,8 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
                                         pack_bf16x2(acc[i][4][v], acc[i][5][v]), pack_bf16x2(acc[i][6][v], acc[i][7][v])});
               } else {
                 store_out<STREAM>(reinterpret_cast<f32x4*>(p), f32x4{acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]});
-                store_out<STREAM>(reinterpret_cast<f32x4*>(p + 4), f32x4{acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]});
+                if (n + 64 < g.N)
+                  store_out<STREAM>(reinterpret_cast<f32x4*>(p + 64), f32x4{acc[i][4][v], acc[i][5][v], acc[i][6][v], acc[i][7][v]});
               }
             }
           }
@@ -1230,11 +1235,19 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
         __builtin_amdgcn_s_barrier();                    // this k tile published; everybody is done with the last one
         __builtin_amdgcn_sched_barrier(0);
         const char* At = smem + st;
-        const char* Bt = At + A_BYTES + (8 * lane_c) * (BN * 2) + (wn * 128 + 8 * lane_m) * 2;
+        const char* Bt = At + A_BYTES + (8 * lane_c) * (BN * 2) + (wn * 128 + LANE_COLS * lane_m) * 2;
         bf16x8 fa[4], fb[8];
         u32x4 w[8];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) w[x] = *reinterpret_cast<const u32x4*>(Bt + x * (BN * 2));
+        for (int x = 0; x < 8; ++x) {
+          const char* row = Bt + x * (BN * 2);
+          if constexpr (ES == 2) {
+            w[x] = *reinterpret_cast<const u32x4*>(row);
+          } else {
+            const u32x2 lo = *reinterpret_cast<const u32x2*>(row), hi = *reinterpret_cast<const u32x2*>(row + 128);
+            w[x] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+          }
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) fa[i] = H::template read_tr<BM>(At, wm * 64 + i * 16, 0, lane);
         __builtin_amdgcn_sched_barrier(0);

@@ -408,6 +408,13 @@ def test_bf16_weight_gradients_from_token_rows(T, d, f, E, k, kw, dW_dtype):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [(90, 72, 72, 3, 2), (70, 120, 200, 2, 1), (100, 184, 184, 5, 2), (64, 200, 64, 2, 2), (77, 264, 8, 3, 1), (65, 320, 136, 2, 1),
+                                       (130, 328, 192, 4, 2), (40, 376, 248, 4, 3), (33, 456, 256, 1, 1)])
+def test_bf16_fp32_weight_gradients_of_few_rows_at_every_column_remainder(T, d, f, E, k):
+    """fp32 strips: a lane holds 4 columns in each half of a 128-column piece; the last piece ends before, in and behind the halves."""
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=F32, poison=True)
+
+
 @pytest.mark.parametrize("T,d,E,k,kw", [
     # both sides of the limits of the two-launch routing: tokens, pairs, tokens x columns x experts
     (512, 64, 8, 8, {}), (513, 64, 8, 2, {}), (512, 72, 9, 8, dict(cf=0.8)), (456, 64, 9, 9, {}), (512, 1024, 64, 3, {}),
