@@ -1052,8 +1052,9 @@ __global__ __launch_bounds__(WM* WN* kWave) void mfma_split_finish_kernel(MArgs 
 //     sequence: a tile is stored while the copies of the next one are in flight, and a second workgroup on the compute
 //     unit fills the rest.  Workgroups that run at a time take neighbouring column tiles of the same rows, so that lines which
 //     two tiles share meet in L2 (37 rows, f = 688: along the columns 197 us, 160 down the rows);
-//   * an expert's strips are the shorter, the more k tiles it has, so that all strips cost about the same and a routing that has
-//     collapsed is shared out over all workgroups (4096 rows on one of 64 experts of 4096 x 704).
+//   * an expert's strips are the shorter, the more k tiles it has, so that all strips cost about the same, and those of an expert
+//     with far more rows than the average go to all XCDs: a routing that has collapsed is shared out over all workgroups (3953 of 4096
+//     rows on one of 64 experts of 4096 x 704: backward pass 758 us; 1054 with its strips on one XCD after another).
 // us, (dW1, dW3) / dW2 with the transposing launch, before -> now, 64 experts of 4096 x 688, top-8: 37 rows 193 / 102 + 43 ->
 // 160 / 73, 188 rows 349 / 167 + 94 -> 300 / 160, 375 rows 461 / 229 + 158 -> 450 / 239; 16 of 1032 x 264, 250 rows 29 / 25 + 8 ->
 // 16 / 12.  Tried: one workgroup of 8 wavefronts on 256 x 256 with B's k tiles kept in LDS (188 rows 286 / 155, but 16 of 1032 x
@@ -1070,20 +1071,34 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
   static constexpr int LANE_COLS = 16 / ES;               // columns of B in a row that a lane reads and stores: 16 bytes of the result
   // strips to aim at: four for every workgroup that runs at a time; what storing a tile costs, in k tiles
   static constexpr int kStrips = 2048, kStoreCost = 8;
+  static constexpr int kXcdStrips = 32;                   // compute units of an XCD
+  static constexpr float kLong = 1.5f;                    // a long expert's tiles cost more than so many average ones
 
   static __device__ void run(const MArgs& g, char* smem) {
     const int lane = threadIdx.x & (kWave - 1);
     const int nx = g.tiles_n * PRODUCTS, xe = min(lane, g.E - 1);
     const int x_cost = kStoreCost + (g.offsets[xe + 1] - g.offsets[xe] + BK - 1) / BK;
-    const float all = wave_sum(lane < g.E ? (float)x_cost : 0.f) * (float)nx * (float)g.tiles_m;
+    const float costs = wave_sum(lane < g.E ? (float)x_cost : 0.f), all = costs * (float)nx * (float)g.tiles_m;
     const int x_len = min(max((int)(all / ((float)kStrips * (float)x_cost)), 1), g.tiles_m);
-    const int x_strips = lane < g.E ? (g.tiles_m + x_len - 1) / x_len : 0, incl = wave_incl_scan_i32(x_strips, lane);
-    const int total = __builtin_amdgcn_readlane(incl, kWave - 1) * nx, share = (total + 7) / 8, xcd = blockIdx.x % 8;
+    const int x_strips = lane < g.E ? (g.tiles_m + x_len - 1) / x_len : 0, xcd = blockIdx.x % 8;
+    // The strips of long experts, then the others', each dealt to the XCDs in eighths: a long expert's cost products, the others'
+    // stores, and an XCD that has one sort only leaves the other half of its means idle (experts in order, top-1 with one favoured
+    // expert, backward pass: 1016 of 1600 rows on one of 8 experts of 2048 x 5504 660 us, 434 like this, 516 with tiles; 2282 of 6400
+    // on one of 32 of 1024 x 2752 757, 530, 582)
+    const bool x_long = lane < g.E && (float)x_cost * (float)g.E > kLong * costs;
+    const int incl_long = wave_incl_scan_i32(x_long ? x_strips : 0, lane);
+    int n_long = __builtin_amdgcn_readlane(incl_long, kWave - 1) * nx;
+    if (n_long <= kXcdStrips) n_long = 0;                // an XCD has a unit for each and reads their rows once (16 of 1024 x 64, one with
+                                                         // 8000 of 16000 rows: 424, dealt out 433)
+    const int incl_rest = wave_incl_scan_i32(x_long && n_long ? 0 : x_strips, lane);
+    const int share_long = (n_long + 7) / 8, shares = share_long + (__builtin_amdgcn_readlane(incl_rest, kWave - 1) * nx + 7) / 8;
     bool again = false;
-    for (int pos = blockIdx.x / 8; pos < share; pos += gridDim.x / 8) {
-      const int i = xcd * share + pos;
-      if (i >= total) break;
-      const int e = __ffsll((long long)__ballot((int64_t)incl * nx > i)) - 1, len = __builtin_amdgcn_readlane(x_len, e);
+    for (int pos = blockIdx.x / 8; pos < shares; pos += gridDim.x / 8) {
+      const bool in_long = pos < share_long;
+      const int i = in_long ? xcd * share_long + pos : xcd * (shares - share_long) + pos - share_long, incl = in_long ? incl_long : incl_rest;
+      const unsigned long long owners = __ballot((int64_t)incl * nx > i);
+      if (owners == 0) continue;                         // past the last strip of that sort
+      const int e = __ffsll((long long)owners) - 1, len = __builtin_amdgcn_readlane(x_len, e);
       const int local = i - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(x_strips, e)) * nx;
       const int first = local / nx * len;
       if (again) {

@@ -395,6 +395,17 @@ def test_bf16_weight_gradients_of_few_rows_with_overloaded_experts(T, d, f, E, k
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, bias=bias + [0.0] * (E - len(bias)), poison=True)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,bias", [
+    # one, two and most of the experts long; fewer strips than XCDs, shares that do not come out even, more strips than workgroups
+    (400, 72, 72, 2, 1, [4.0]), (900, 264, 392, 7, 1, [0.0, 4.0]), (600, 1032, 264, 33, 2, [5.0, 0.0, 0.0, 5.0]), (1200, 264, 136, 5, 2, [3.0, 3.0, 3.0, 0.0, -60.0]),
+    (700, 2056, 1096, 16, 1, [4.0, 0.0, 3.0]), (300, 520, 136, 64, 1, [7.0]),
+])
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_of_long_experts_reach_every_tile(T, d, f, E, k, bias, dW_dtype):
+    """The strips of experts with more rows than the average are dealt out first, to all XCDs: nothing is left as it was handed over."""
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, bias=bias + [0.0] * (E - len(bias)), poison=True)
+
+
 @pytest.mark.parametrize("T,d,f,E,k,kw", [
     # one column tile and a little more of either operand, k tiles of 32 rows and their remainders, token rows of 1, 2, 3, 5 slots
     (256, 264, 136, 4, 1, {}), (257, 248, 128, 4, 2, {}), (303, 520, 264, 3, 3, {}), (161, 1032, 392, 7, 5, {}), (97, 128, 520, 1, 1, {}),
