@@ -456,10 +456,13 @@ struct Gemm {
     const int e = tile.e, row0 = tile.row0, row_end = tile.row_end, k_begin = tile.k_begin, k_end = tile.k_end;
     const int kp_begin = tile.kp_begin, tile_n = tile.tile_n;
     const int col0 = tile_n * BNH;
-    // small tiles: an expert with more rows than expected reads its weights through the caches, where its row tiles share
-    // them (320 tokens, top-1, 4 experts of 4096 x 11008, the favoured one with more than 128 rows: forward pass 322 us with every
-    // weight streamed, 306 with none, 293 like this)
-    const bool read_once = !SMALL || row_end - tile.exp_row0 <= BM;
+    // an expert with more rows than expected reads its weights through the caches, where its row tiles share them: small tiles (320
+    // tokens, top-1, 4 experts of 4096 x 11008, the favoured one with more than 128 rows: forward pass 322 us with every weight
+    // streamed, 306 with none, 293 like this) and the backward products (backward pass with every weight streamed / like this, top-1
+    // with a favoured expert: 480 tokens 655 / 626, 600 tokens 681 / 662, 1200 tokens, 8 experts of 2048 x 5504 403 / 389; even loads the
+    // same).  The forward products of larger tiles do not look: it costs their loop 1 % (even loads, 600 tokens 260 / 263, 420
+    // tokens, top-2, 294 / 298) and gives as much at times (favoured experts 221 / 218, but 333 / 336).
+    const bool read_once = (!SMALL && (MODE == UP || MODE == DOWN)) || row_end - tile.exp_row0 <= BM;
 
     const bf16_t* Bp0 = g.B0;
     const bf16_t* Bp1 = g.B1;

@@ -447,8 +447,8 @@ def test_combine_adds_the_slices_of_the_down_projection(T, d, f, E, k, kw, dtype
     run_layer_and_check(T, d, f, E, k, dtype, unit_rms=True, backward=False, **kw)
 
 
-# 64-, 128-, 192- and 256-row tiles; small tiles, one expert with several of them
-@pytest.mark.parametrize("T,k,bias", [(16, 2, 0.0), (160, 2, 0.0), (301, 2, 0.0), (420, 2, 0.0), (160, 1, 2.0), (320, 1, 2.0)])
+# 64-, 128-, 192- and 256-row tiles; the same, one expert with several of them
+@pytest.mark.parametrize("T,k,bias", [(16, 2, 0.0), (160, 2, 0.0), (301, 2, 0.0), (420, 2, 0.0), (160, 1, 2.0), (320, 1, 2.0), (600, 1, 2.0), (900, 1, 2.0)])
 def test_bf16_weights_streamed_past_the_caches_give_the_same_bits(T, k, bias):
     """1.1 GB of expert weights, read past the caches where their rows start on whole lines; shifted by 64 bytes they are not."""
     d, f, E = 4096, 11008, 4
