@@ -378,15 +378,25 @@ template <int ROUNDS, int PIECE> __global__ __launch_bounds__(kGroupThreads) voi
   for (int r = s_kept + threadIdx.x; r < R; r += kGroupThreads) perm[r] = 0;   // no such rows: any valid pair
 }
 
-// us, four launches / two (see kSmallTokens): 4 experts, top-2, 1024 tokens of 1024 columns 14.4 / 13.6, with the normalisation
-// 17.2 / 15.5, of 4096 18.1 / 19.1 and 29.8 / 22.6; 16 experts, top-4, of 1024 600 tokens 20.5 / 19.0, 800 20.7 / 22.8; 64
-// experts, top-4, of 512 512 tokens 31 / 31, 600 31 / 34.  The normalisation is not asked: a logit's sum has another order in
-// two launches than in four, and routing with it is routing without it on the rows it writes, bit for bit.
+// Two launches win up to kSmallTokens tokens; above, route_small_tokens and the one grouping workgroup lose ground to four launches with
+// every token.  us, four launches / two:
+//   whole vector loads of W_router (4, 8, 16 experts; 9, where one column is left over): 1024 tokens of 1024 columns, 4 experts, top-2
+//     14.3 / 13.3, of 2048 15.5 / 15.2, of 4096 17.7 / 19; top-3 853 of 1024 14.8 / 14.0, top-4 1024 of 2048 16.7 / 17.6; 640 of 1024, 8
+//     experts 16.5 / 14.2, of 2336 19.4 / 17.8; 9 experts, 640 of 1024 17.0 / 14.3, of 1600 17.3 / 16.9; 16 experts, top-4, 640 of 392
+//     17.0 / 16.2, of 776 17.3 / 17.9, of 1024 20.3 / 18.9, of 1072 18.6 / 20.5 (with the normalisation 26.4 / 20.2 for 776)
+//   other numbers of experts, whose last columns are loaded one by one: 1024 of 256, 2 experts 11.8 / 9.6, of 512 12.5 / 12.8, of 4096
+//     15.7 / 25; 3 experts of 512 13.6 / 14.0; 640 of 256, 7 experts 15.2 / 14.2, of 448 15.3 / 15.8; 520 of 4096, 5 experts 19.5 / 42; 640
+//     of 256, 13 experts 17.7 / 16.6, 12 of 1024 19.3 / 20.7
+//   64 experts, top-4, of 512 columns: 512 tokens 31 / 31, 600 31 / 34
+// The normalisation is not asked, though it gains more (1024 of 2048, 4 experts 20.9 / 17.3): a logit's sum has another order in two
+// launches than in four, and routing with it is routing without it on the rows it writes, bit for bit.
 bool route_is_small(const RouteArgs& a) {
-  const int64_t traffic = (int64_t)a.T * a.d * a.E;
-  if ((int64_t)a.T * a.k > kSmallPairs || traffic > kSmallTraffic) return false;
+  const int64_t traffic = (int64_t)a.T * a.d * a.E, pairs = (int64_t)a.T * a.k;
+  if (pairs > kSmallPairs || traffic > kSmallTraffic) return false;
   if (a.T <= kSmallTokens) return true;
-  return a.T <= (a.E <= 4 ? 1024 : a.E <= 16 ? 640 : 0) && traffic <= 12000000;
+  if (a.E <= 4) return a.T <= 1024 && pairs <= 2560 && traffic <= (a.E == 4 ? 12000000 : 500000);
+  if (a.E <= 8) return a.T <= 640 && traffic <= (a.E == 8 ? 12000000 : 800000);
+  return a.E <= 16 && a.T <= 640 && traffic <= (a.E == 9 || (a.E == 16 && a.d <= 1024) ? 10500000 : 2500000);
 }
 
 int launch_route_small(const RouteArgs& a, hipStream_t s) {

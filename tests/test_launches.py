@@ -194,6 +194,20 @@ def test_routing_takes_the_same_way_with_and_without_the_normalisation(record, E
         assert ("route_small" in plain[0].kernel) == ("route_small" in norm[0].kernel), shape
 
 
+@pytest.mark.parametrize("T,d,E,k,launches", [
+    (512, 4096, 5, 2, 2), (512, 8192, 8, 2, 2), (512, 8200, 8, 2, 4),
+    # above 512 tokens: whole vector loads of W_router
+    (1024, 1024, 4, 2, 2), (732, 4096, 4, 2, 2), (733, 4096, 4, 2, 4), (1025, 64, 4, 2, 4), (640, 64, 4, 4, 2), (641, 64, 4, 4, 4), (640, 2336, 8, 2, 2),
+    (640, 2352, 8, 2, 4), (641, 64, 8, 2, 4), (640, 1024, 16, 4, 2), (520, 1032, 16, 4, 4), (640, 1816, 9, 2, 2), (640, 1832, 9, 2, 4),
+    # columns of W_router that are loaded one by one
+    (1024, 4096, 1, 1, 4), (1024, 480, 1, 1, 2), (1024, 512, 2, 2, 4), (1024, 240, 2, 2, 2), (1024, 1024, 3, 2, 4), (600, 256, 3, 2, 2), (520, 4096, 5, 2, 4),
+    (640, 2048, 5, 2, 4), (640, 248, 5, 2, 2), (640, 176, 7, 2, 2), (640, 448, 7, 2, 4), (640, 1536, 12, 4, 4), (640, 256, 15, 4, 2), (640, 1024, 14, 4, 4), (513, 64, 17, 2, 4)])
+@pytest.mark.parametrize("norm", [False, True])
+def test_routing_launches(record, T, d, E, k, launches, norm):
+    (rc, found), = record(route_call(T, d, E, k, B.BTX_BF16, norm))
+    assert rc == 0 and len(found) == launches
+
+
 @pytest.mark.parametrize("T,d,f,E,product,tile", [
     # one round of 256- or 192-row tiles where smaller ones would need a second round (us there: 256 / 128 rows)
     (400, 4096, 11008, 2, UP, 256), (480, 4096, 11008, 1, UP, 256), (6000, 4096, 688, 4, UP, 256), (320, 4096, 11008, 2, UP, 192),
