@@ -445,7 +445,7 @@ int slices_of(const FfShapes& sh, bool two_passes) {
   return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
 }
 
-// left (may be NULL): K slices whose sums the caller adds himself, in g.sums
+// left (may be NULL): in, K slices that the caller can add himself; out, those whose sums he finds in g.sums (1: none)
 template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
   constexpr int BM = kTile, BN = kTile, BK = kTileK;
   using G = F32Gemm<BM, BN, BK, MODE>;
@@ -459,9 +459,9 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullpt
   const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
   f32_gemm_kernel<BM, BN, BK, MODE><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
-  if (left) {
-    *left = g.slices;
-  } else if (g.slices > 1) {
+  const bool leave = left && g.slices <= *left;
+  if (left) *left = leave ? g.slices : 1;
+  if (g.slices > 1 && !leave) {
     f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets,
                                                                                          g.E, g.C0);
     BTX_LAUNCH_CHECK();

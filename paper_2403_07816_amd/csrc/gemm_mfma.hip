@@ -1399,7 +1399,7 @@ int small_slices(int64_t tiles, int nk, size_t bytes_per_slice) {
   return (int)std::max<int64_t>(std::min({fill, fit, (int64_t)(nk / 8), (int64_t)kSplitMaxSlices}), 1);
 }
 
-// left (may be NULL): K slices whose sums the caller adds himself, in slice_sums
+// left (may be NULL): in, K slices that the caller can add himself; out, those whose sums he finds in slice_sums (1: none)
 template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, bool prepare_only, int* left, hipStream_t s) {
   // 64 rows: three stages of both operands (72 KB); 128: two of A and three of B (80 KB, half of a compute unit's LDS)
   constexpr int WM = MODE == BWD_ACT && BM == 64 ? 1 : 2, WN = 4 / WM;
@@ -1419,9 +1419,9 @@ template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, b
   if (!grid_fits(blocks + 7, 256)) return BTX_ERR_UNSUPPORTED;
   kernel<<<(unsigned)align_up((size_t)blocks, 8), G::NT, G::LDS_BYTES, s>>>(g);
   BTX_LAUNCH_CHECK();
-  if (left) {
-    *left = g.slices;
-  } else if (g.slices > 1) {
+  const bool leave = left && g.slices <= *left;
+  if (left) *left = leave ? g.slices : 1;
+  if (g.slices > 1 && !leave) {
     slices_finish_kernel<MODE == UP><<<ceil_div((int64_t)g.R * (g.N / 8), 256), 256, 0, s>>>(
         g.slice_sums, g.slices, g.R, g.N, g.offsets, g.E, (bf16_t*)g.C0, (bf16_t*)g.C1, (bf16_t*)g.C2);
     BTX_LAUNCH_CHECK();
@@ -1499,6 +1499,7 @@ template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
 // the instantiation for this row tile, way of reading the weights (stream_weights()) and K (see TAIL)
 template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, bool prepare_only, int* left, hipStream_t s) {
   const bool whole = g.K % 64 == 0;
+  if (left && tile > 128) *left = 1;                     // large tiles finish their slices themselves
   auto go = [&](auto stream) {
     constexpr bool S = decltype(stream)::value;
     if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, left, s);
@@ -1628,7 +1629,6 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
 
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
               int* slices, hipStream_t s) {
-  *slices = 1;
   MArgs g{};
   g.A0 = (const bf16_t*)act; g.B0 = (const bf16_t*)W2; g.C0 = y; g.partial = (f32x4*)partial;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d;

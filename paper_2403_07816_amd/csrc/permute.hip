@@ -117,7 +117,8 @@ constexpr int kFewRows = 8192;
 // KMAX: slots whose grouped rows and gates a wavefront keeps in registers; the rows of those slots are
 // requested together for every 16-byte column chunk (k > KMAX: the remaining slots are looked up as they come).
 // SLICED: y is still the fp32 sums of a product cut along K, [slice][row][column]; they are added in slice order and rounded to
-// ET as a finishing kernel of the product would have (forward pass, 16 tokens, 4 experts of 4096 x 11008 197.4 -> 195.7 us).
+// ET as a finishing kernel of the product would have (forward pass, 16 tokens, 4 experts of 4096 x 11008 197.4 -> 195.7 us); no more
+// than combine_most_slices().
 template <typename ET, int KMAX, bool SLICED>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restrict__ y_rows, int slices, int64_t slice_stride, const float* __restrict__ gates,
                                                            const int32_t* __restrict__ inv_pos,
@@ -128,17 +129,6 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restric
   const int t = blockIdx.x * (kThreads / kWave) + wave;
   if (t >= T) return;
   const u32x4* y = static_cast<const u32x4*>(y_rows);
-  // chunk c of a row of y out of its slices
-  auto slice_sum = [&](int r, int c) {
-    float v[N] = {};
-    for (int s = 0; s < slices; ++s) {
-      float u[N];
-      RowVec<float, N>::ld(static_cast<const float*>(y_rows) + s * slice_stride + ((int64_t)r * chunks_per_row + c) * N, u);
-#pragma unroll
-      for (int i = 0; i < N; ++i) v[i] = s ? v[i] + u[i] : u[i];
-    }
-    return Chunk<ET>::pack(v);
-  };
   int row[KMAX];
   float gate[KMAX];
 #pragma unroll
@@ -164,6 +154,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restric
           for (int j = 0; j < KMAX; ++j)
             RowVec<float, N>::ld(static_cast<const float*>(y_rows) + min(s0 + b, slices - 1) * slice_stride +
                                      ((int64_t)max(row[j], 0) * chunks_per_row + c) * N, u[b][j]);
+        __builtin_amdgcn_sched_barrier(0);                // no sum in front of a load (30 tokens, top-3, 4 experts of 1024 x 5504: 36.1 us, 34.8)
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
@@ -185,12 +176,12 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restric
         for (int i = 0; i < N; ++i) acc[i] = fmaf(gate[j], v[i], acc[i]);
       }
     }
-    for (int j = KMAX; j < k; ++j) {
+    for (int j = KMAX; j < k && !SLICED; ++j) {
       const int r = inv_pos[(size_t)t * k + j];
       if (r < 0) continue;                  // pair dropped at its expert's capacity
       const float g = gates ? gates[(size_t)t * k + j] : 1.f;
       float v[N];
-      Chunk<ET>::unpack(SLICED ? slice_sum(r, c) : y[(size_t)r * chunks_per_row + c], v);
+      Chunk<ET>::unpack(y[(size_t)r * chunks_per_row + c], v);
 #pragma unroll
       for (int i = 0; i < N; ++i) acc[i] = fmaf(g, v[i], acc[i]);
     }
@@ -218,6 +209,16 @@ int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* d
                                                  offsets, E, k, d, pitch);
   BTX_LAUNCH_CHECK();
   return BTX_OK;
+}
+
+// K slices of a row that launch_combine() may be given.  A wavefront adds the slices of a token's slots; the more of them there are,
+// the longer it takes, where a finishing kernel has a thread for every 8 columns of a row.  Forward pass, us, finishing kernel /
+// added here: bf16, 40 tokens, 8 experts of 512 x 5504, 8 slices: top-2 34.1 / 31.5, top-4 34.6 / 33.8, top-5 35.9 / 36.3, top-8 35.6 /
+// 37.2; 100 tokens, top-8, 16 experts of 512 x 1376, 2 slices 30.3 / 29.4; fp32, 10 tokens, 16 of 128 x 1024, top-8 19.0 / 18.6.  Slots
+// that are looked up as they come: 10 tokens, top-12 20.6 / 27.1.
+int combine_most_slices(int T, int k, int dtype) {
+  if (k > (T < kFewRows ? 8 : 4)) return 1;
+  return (dtype == BTX_BF16 ? 32 : 64) / k;
 }
 
 int launch_combine(const void* y, const float* y_sums, int slices, const float* gates, const int32_t* inv_pos, const void* residual, void* out, int T,

@@ -208,6 +208,23 @@ def test_routing_launches(record, T, d, E, k, launches, norm):
     assert rc == 0 and len(found) == launches
 
 
+@pytest.mark.parametrize("dtype,T,d,f,E,k,sliced", [
+    (B.BTX_BF16, 16, 4096, 11008, 4, 2, True), (B.BTX_BF16, 40, 512, 5504, 8, 4, True), (B.BTX_BF16, 100, 512, 1376, 16, 8, True),
+    (B.BTX_F32, 64, 512, 1376, 8, 8, True), (B.BTX_F32, 10, 128, 1024, 16, 8, True),
+    # too many slices of too many slots; slots that are looked up as they come; products that are not cut
+    (B.BTX_BF16, 40, 512, 5504, 8, 5, False), (B.BTX_BF16, 40, 512, 5504, 8, 8, False), (B.BTX_BF16, 7, 256, 4096, 12, 12, False),
+    (B.BTX_F32, 10, 128, 1024, 16, 12, False), (B.BTX_BF16, 301, 4096, 11008, 4, 2, False), (B.BTX_F32, 2003, 512, 1376, 8, 2, False)])
+def test_slices_of_the_down_projection_are_added_once(record, dtype, T, d, f, E, k, sliced):
+    """By the combine, or by a finishing kernel of the product."""
+    (rc, found), = record(forward_call(T, d, f, E, k, dtype))
+    names = [launch.kernel for launch in found]
+    assert rc == 0 and names[-1].startswith("combine_kernel") and names[-1].endswith("true>") == sliced
+    if sliced:
+        assert "finish" not in names[-2]
+    elif T < 100:
+        assert "slices_finish" in names[-2]
+
+
 @pytest.mark.parametrize("T,d,f,E,product,tile", [
     # one round of 256- or 192-row tiles where smaller ones would need a second round (us there: 256 / 128 rows)
     (400, 4096, 11008, 2, UP, 256), (480, 4096, 11008, 1, UP, 256), (6000, 4096, 688, 4, UP, 256), (320, 4096, 11008, 2, UP, 192),
