@@ -1075,7 +1075,7 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
   // strips to aim at: four for every workgroup that runs at a time; what storing a tile costs, in k tiles
   static constexpr int kStrips = 2048, kStoreCost = 8;
   static constexpr int kXcdStrips = 32;                   // compute units of an XCD
-  static constexpr float kLong = 1.5f;                    // a long expert's tiles cost more than so many average ones
+  static constexpr float kLong = 1.15f;                   // a long expert's tiles cost more than so many average ones
 
   static __device__ void run(const MArgs& g, char* smem) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -1087,7 +1087,8 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
     // The strips of long experts, then the others', each dealt to the XCDs in eighths: a long expert's cost products, the others'
     // stores, and an XCD that has one sort only leaves the other half of its means idle (experts in order, top-1 with one favoured
     // expert, backward pass: 1016 of 1600 rows on one of 8 experts of 2048 x 5504 660 us, 434 like this, 516 with tiles; 2282 of 6400
-    // on one of 32 of 1024 x 2752 757, 530, 582)
+    // on one of 32 of 1024 x 2752 757, 530, 582; milder, kLong 1.5 / 1.15: 523 of 1300 rows on one of 4 of 2048 x 5504 392 / 331, tiles
+    // 359; 730 of 3600 on one of 8 of 1024 x 2752 268 / 237, 260; 391 of 2400 on one of 8 of 1024 x 1376 141 / 146, 150)
     const bool x_long = lane < g.E && (float)x_cost * (float)g.E > kLong * costs;
     const int incl_long = wave_incl_scan_i32(x_long ? x_strips : 0, lane);
     int n_long = __builtin_amdgcn_readlane(incl_long, kWave - 1) * nx;
