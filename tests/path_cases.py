@@ -38,3 +38,10 @@ def whole_tile_case(i):
 
 
 WHOLE_TILE_CASES = 6
+
+# weight gradients from transposed rows: more than 8 experts, experts without rows, dropped pairs; dW2 streamed and not
+TRANSPOSED_ROWS = [
+    (2200, 264, 2056, 12, 2, dict(cf=0.8, poison=True)), (2200, 320, 2056, 12, 2, dict(cf=0.8, poison=True)),
+    (1100, 136, 2056, 3, 1, dict(bias=[0.0, -60.0, 0.0], poison=True)), (6100, 64, 2056, 33, 2, dict(bias=[0.0] * 32 + [-60.0], poison=True)),
+    (1500, 520, 3608, 4, 1, dict(bias=[3.0, 0.0, 0.0, 0.0], poison=True)),
+]

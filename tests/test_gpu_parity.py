@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import LAST_ROUND_CUT, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import LAST_ROUND_CUT, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -411,11 +411,18 @@ def test_bf16_weight_gradients_of_long_experts_reach_every_tile(T, d, f, E, k, b
     (256, 264, 136, 4, 1, {}), (257, 248, 128, 4, 2, {}), (303, 520, 264, 3, 3, {}), (161, 1032, 392, 7, 5, {}), (97, 128, 520, 1, 1, {}),
     # several k tiles on some experts, none on others; dropped pairs
     (900, 520, 264, 8, 2, dict(bias=[3.0] + [0.0] * 7, poison=True)), (700, 264, 520, 6, 3, dict(cf=0.8, poison=True)),
-    # both sides of the limits: 360 rows, and rows x width
+    # both sides of the limits: 360 rows, rows x width, and rows of few strips
     (720, 512, 520, 4, 2, {}), (722, 504, 520, 4, 2, {}), (2500, 520, 512, 2, 2, {}), (2560, 520, 512, 2, 2, {}),
+    (720, 264, 5504, 2, 1, {}), (724, 264, 5504, 2, 1, {}), (1400, 72, 136, 4, 2, {}), (1404, 72, 136, 4, 2, {}), (1500, 256, 192, 8, 2, {}),
 ])
 @pytest.mark.parametrize("dW_dtype", [BF16, F32])
 def test_bf16_weight_gradients_from_token_rows(T, d, f, E, k, kw, dW_dtype):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", TRANSPOSED_ROWS)
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_from_transposed_rows(T, d, f, E, k, kw, dW_dtype):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
 
 

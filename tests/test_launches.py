@@ -8,7 +8,7 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -67,24 +67,35 @@ def test_bf16_workspaces_of_small_layers_are_small(record, T, d, f, E, k, forwar
 def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_dtype):
     """The strips' stores go past the caches where every row starts on 64 bytes: not for a stack that starts on any other 16-byte
     piece, nor with an expert stride that shifts the others there."""
-    def streamed(T, dW2=P, stride=None):
-        (rc, found), = record(backward_call(T, 256, 192, 8, 2, B.BTX_BF16, dW_dtype=dW_dtype, dW2=dW2, stride=stride))
+    def streamed(T, dW2=P, stride=None, d=256, f=192):
+        (rc, found), = record(backward_call(T, d, f, 8, 2, B.BTX_BF16, dW_dtype=dW_dtype, dW2=dW2, stride=stride))
         last = [n.kernel for n in found if "dw_strip" in n.kernel or ", 5, 0, " in n.kernel][-1]
         assert rc == 0 and ("strip" in last) == (T == 100)
         return last.endswith("true>")
     assert streamed(100) and streamed(100, dW2=P + 64) and streamed(100, stride=256 * 192 + 32)
     assert not streamed(100, dW2=P + 16) and not streamed(100, stride=256 * 192 + 8)
-    assert streamed(1500) and streamed(1500, dW2=P + 16)          # 256 x 256 tiles: from anywhere
+    wide = dict(d=2048, f=5504)                                    # 256 x 256 tiles: from anywhere
+    assert streamed(1500, **wide) and streamed(1500, dW2=P + 16, **wide)
 
 
 @pytest.mark.parametrize("T,d,f,E,k,direct", [
-    (1, 64, 64, 64, 8, True), (720, 512, 5504, 4, 2, True), (722, 512, 5504, 4, 2, False), (722, 504, 520, 4, 2, False),
-    (1250, 520, 1040, 2, 2, True), (1251, 520, 1040, 2, 2, False)])
+    (1, 64, 64, 64, 8, True), (720, 512, 5504, 4, 2, True), (722, 512, 5504, 4, 2, False), (722, 504, 520, 4, 2, True),
+    (1250, 520, 1040, 2, 2, True), (1251, 520, 1040, 2, 2, False),
+    # few strips: 700 rows of fewer than 512 columns, 2500 of more; from d x E = 4096 on any number of rows; 700 thousand below 512 columns
+    (1500, 256, 192, 8, 2, True), (1400, 504, 520, 4, 2, True), (1402, 504, 520, 4, 2, False), (5000, 512, 352, 4, 2, True), (5002, 512, 352, 4, 2, False),
+    (20000, 504, 64, 8, 2, False), (20000, 512, 64, 8, 2, True), (160000, 64, 64, 64, 2, True), (6000, 504, 1400, 24, 2, True), (6012, 504, 1400, 24, 2, False)])
 def test_weight_gradients_of_few_rows_read_token_rows(record, T, d, f, E, k, direct):
-    """Up to 360 rows per expert, or rows x width of 1.3 million, nothing is transposed for the weight gradients."""
+    """Up to 360 rows per expert, or rows x width of 1.3 million where there are strips enough, nothing is transposed for the weight
+    gradients."""
     (rc, found), = record(backward_call(T, d, f, E, k, B.BTX_BF16))
     names = " ".join(launch.kernel for launch in found)
     assert rc == 0 and ("dw_strip" in names) == direct and ("gather_rows_t" in names) == (not direct)
+
+
+@pytest.mark.parametrize("case", TRANSPOSED_ROWS)
+def test_shapes_of_transposed_rows_take_that_path(record, case):
+    (rc, found), = record(backward_call(*case[:5], B.BTX_BF16))
+    assert rc == 0 and any("gather_rows_t" in launch.kernel for launch in found)
 
 
 def test_fp32_products_of_too_many_tiles_are_refused(record):
