@@ -320,7 +320,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
-  const bool direct = ff_dw_direct(dtype, sh, fused);
+  const bool direct = ff_dw_direct(dtype, dW_dtype, sh, fused);
   // bf16 weight gradients that read token rows: their offsets lie where the transposed rows would
   uint32_t* row_bytes = direct && n_dw == 3 ? static_cast<uint32_t*>(w.xsT) : nullptr;
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,

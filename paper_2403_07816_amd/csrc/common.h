@@ -293,7 +293,7 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
 // transposed, padded form with pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
 // does).  ff_dw_transposed(): problems of this dtype may take that form.
 bool ff_dw_transposed(int dtype);
-bool ff_dw_direct(int dtype, const FfShapes& sh, bool gather_fused);
+bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
 int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
                     const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);

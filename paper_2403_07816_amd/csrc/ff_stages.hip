@@ -15,8 +15,8 @@ bool ff_rows_supported(int dtype, int R, int d, int f, int E) {
 }
 
 bool ff_dw_transposed(int dtype) { return dtype == BTX_BF16; }
-bool ff_dw_direct(int dtype, const FfShapes& sh, bool gather_fused) {
-  return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh));
+bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused) {
+  return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh, dW_dtype));
 }
 int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
 

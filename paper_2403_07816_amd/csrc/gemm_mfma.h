@@ -29,7 +29,7 @@ int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3
                 const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
 // Weight gradients.  mfma_dw_direct(): of few rows per expert, from token rows (found by row_bytes) and ga in row order; else
 // xs, dys without perm: [d][mfma_dw_pitch(R, E)], laid out like the transposed ga above
-bool mfma_dw_direct(const FfShapes& sh);
+bool mfma_dw_direct(const FfShapes& sh, int dW_dtype);
 int mfma_dw_pitch(int R, int E);
 int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off,
                   const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);

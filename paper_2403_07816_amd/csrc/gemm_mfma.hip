@@ -1676,17 +1676,18 @@ bool mfma_rows_ok(int R, int E) { return ((int64_t)align_up((size_t)R, 64) + 64 
 //   4096 x 688, 64 experts:   188 1000 / 881, 500 1807 / 1646; 8: 3200 1180 / 1112;  1032 x 264, 16: 3200 655 / 476
 //   256 x 192, 64 experts:    188 178 / 94, 500 251 / 154, 5000 2284 / 1555;  8: 375 77 / 60, 1500 137 / 131, 2500 199 / 200, 5000 335 / 350
 // Few strips, those of few experts of few columns, leave a long contraction to few workgroups, the more so when the 256 columns of a
-// row tile are not all there; from d * E = 4096 on nothing is lost at any number of rows:
+// row tile are not all there; from d * E = 4096 on nothing is lost at any number of rows (8192 with fp32 gradients, whose k tiles take
+// more reads from LDS: 512 x 64, 8 experts of 5290 rows 342 / 361, 1024 x 128, 8 of 2567 238 / 227):
 //   512 x 64:  1 expert 1800 118 / 117, 3700 190 / 200, 20000 814 / 903;  4: 2566 162 / 160, 5043 273 / 282;  8: 5290 344 / 337, 21361 1311 /
 //   1263;  512 x 352, 4: 2566 176 / 176;  1024 x 64, 4: 20165 1133 / 1100
 //   64 x 64:  4 experts 742 69 / 68, 2569 140 / 153;  64: 9442 2119 / 1789;  128 x 352:  16: 700 129 / 119, 3061 283 / 292;  32: 3354 589 / 492
 // The average decides, and a favoured expert's rows are more: half of all rows on one of 8, average as given: 512 x 520 1300 313 / 326,
 // 256 x 192 375 119 / 113, 700 173 / 172, 1000 220 / 230, 504 x 1400 750 247 / 265.  Below 512 columns, where the chain is the larger part,
 // the limits are tighter for that.
-bool mfma_dw_direct(const FfShapes& sh) {
+bool mfma_dw_direct(const FfShapes& sh, int dW_dtype) {
   const int64_t rows = sh.R / std::max(sh.E, 1);
   if (rows <= 360) return true;
-  if ((int64_t)sh.d * sh.E < 4096 && rows > (sh.d < 512 ? 700 : 2500)) return false;
+  if ((int64_t)sh.d * sh.E < (dW_dtype == BTX_F32 ? 8192 : 4096) && rows > (sh.d < 512 ? 700 : 2500)) return false;
   return rows * sh.f <= (sh.d < 512 ? 700000 : 1300000);
 }
 

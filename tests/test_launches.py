@@ -92,6 +92,12 @@ def test_weight_gradients_of_few_rows_read_token_rows(record, T, d, f, E, k, dir
     assert rc == 0 and ("dw_strip" in names) == direct and ("gather_rows_t" in names) == (not direct)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,direct", [(720, 512, 5504, 4, 2, True), (10000, 512, 64, 8, 2, True), (10004, 512, 64, 8, 2, False), (20000, 1024, 64, 8, 2, True)])
+def test_fp32_weight_gradients_of_few_strips_transpose_earlier(record, T, d, f, E, k, direct):
+    (rc, found), = record(backward_call(T, d, f, E, k, B.BTX_BF16, dW_dtype=B.BTX_F32))
+    assert rc == 0 and any("gather_rows_t" in launch.kernel for launch in found) == (not direct)
+
+
 @pytest.mark.parametrize("case", TRANSPOSED_ROWS)
 def test_shapes_of_transposed_rows_take_that_path(record, case):
     (rc, found), = record(backward_call(*case[:5], B.BTX_BF16))
