@@ -1517,18 +1517,19 @@ template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, boo
   if (g.K % 64 == 32) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 1>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 2>(g, prepare_only, s);
 }
-// Weights streamed past the caches: products of one row tile per expert read them once.  Where the layer's weights are larger
-// than the memory-side cache (256 MB; smaller ones stay there from pass to pass: 135 MB, 30 rows 39 us plain, 42 streamed), with
-// room for experts that have more rows than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293; small tiles look at
-// the true number as well, see read_once), and where a row of B is whole lines: else every line is fetched for two tiles (32 x
-// 4096 x 1376, UP 137, 139).  Forward pass, us, plain / streamed:
+// Weights streamed past the caches: products of one row tile per expert read them once.  Where the layer's three weights are more than
+// the memory-side cache (256 MB) keeps from pass to pass, which shows from 300 MB on (plain / streamed, forward pass, us: 4 experts of 2048
+// x 5504, 271 MB, 16 tokens 55 / 55, 60 tokens 56 / 59; 16 of 1024 x 2752, 271 MB, 640 tokens 66 / 69; 3 of 3072 x 5504, 304 MB, 16 tokens 73
+// / 70, 120 tokens 96 / 94; 7 of 2048 x 4096, 352 MB, 16 tokens 81 / 72, 280 tokens 94 / 91), with room for experts that have more rows
+// than the average (128-row tiles of 32 x 4096 x 1376, 110 rows: 274, 293; see read_once), and where a row of B is whole lines: else
+// every line is fetched for two tiles (32 x 4096 x 1376, UP 137, 139).  K is whole k tiles: the forms with a K tail are not built twice.
 //   4 x 4096 x 11008: 4 rows 200 / 180, 30 206 / 187, 64 244 / 232, 150 277 / 265;  8 x 2048 x 5504: 16 106 / 93, 64 127 / 122
 //   32 x 1024 x 2752: 16 106 / 90, 130 168 / 143, 200 173 / 158;  32 x 2048 x 2752: 30 208 / 186, 200 294 / 283;  backward 30
 //   468 / 441, 200 746 / 718
 bool stream_weights(const MArgs& g, int tile) {
-  const int64_t avg = g.R / std::max(g.E, 1);
+  const int64_t avg = g.R / std::max(g.E, 1), layer_bytes = (int64_t)6 * g.E * g.N * g.K;
   const uintptr_t at = (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)(g.strideB_e * 2) | (uintptr_t)g.ldb * 2;
-  return avg <= (tile == 128 ? 96 : tile == 256 ? 236 : tile) && (int64_t)6 * g.E * g.N * g.K >= 400000000 && at % 128 == 0 && g.K % 64 == 0;
+  return avg <= (tile == 128 ? 96 : tile == 256 ? 236 : tile) && layer_bytes >= 300000000 && at % 128 == 0 && g.K % 64 == 0;
 }
 template <int MODE> int launch_rows(const MArgs& g, hipStream_t s, int* left = nullptr) {
   const int tile = row_tile<MODE>(g);

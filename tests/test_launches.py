@@ -242,6 +242,31 @@ def test_slices_of_the_down_projection_are_added_once(record, dtype, T, d, f, E,
         assert "slices_finish" in names[-2]
 
 
+@pytest.mark.parametrize("T,d,f,E,kw,streamed", [
+    # rows per expert: what a tile of 64, 128 (96), 192 and 256 (236) rows has room for
+    (4 * 48, 4096, 11008, 4, {}, "UP DOWN"), (4 * 96, 4096, 11008, 4, {}, "UP DOWN"), (4 * 97, 4096, 11008, 4, {}, ""), (4 * 111, 4096, 11008, 4, {}, "UP DOWN"),
+    (4 * 168, 4096, 11008, 4, {}, "UP DOWN"), (4 * 236, 4096, 11008, 4, {}, "UP DOWN"), (4 * 237, 4096, 11008, 4, {}, ""),
+    # 300 million bytes of weights
+    (16, 3072, 5504, 3, {}, "UP DOWN"), (16, 2560, 6528, 3, {}, "UP DOWN"), (16, 2560, 6464, 3, {}, ""), (16, 2048, 5504, 4, {}, ""),
+    # rows of whole lines, from the first expert's to the last one's
+    (16, 4096, 11008, 4, dict(p=P + 64), ""), (16, 4096, 11008, 4, dict(stride=4096 * 11008 + 32), ""), (16, 4096, 11008, 4, dict(stride=4096 * 11008 + 64), "UP DOWN"),
+    # K of whole k tiles, rows of whole lines: W2 has K = f rows of d columns
+    (16, 4096, 11040, 4, {}, ""), (16, 4096, 688, 64, {}, ""), (16, 4128, 11008, 4, {}, ""), (64, 1024, 2752, 32, {}, "UP DOWN")])
+def test_weights_are_streamed_where_they_are_read_once(record, T, d, f, E, kw, streamed):
+    (rc, found), = record(forward_call(T, d, f, E, 1, B.BTX_BF16, **kw))
+    assert rc == 0
+    for launch in found:
+        if launch.kernel.startswith("mfma_small"):
+            *numbers, stream = launch.kernel[:-1].split(", ")
+            product = int(numbers[5])
+        elif launch.kernel.startswith("mfma_gemm"):
+            *numbers, stream, _ = launch.kernel[:-1].split(", ")
+            product = int(numbers[7])
+        else:
+            continue
+        assert (stream == "true") == ({UP: "UP", DOWN: "DOWN"}[product] in streamed.split()), launch.kernel
+
+
 @pytest.mark.parametrize("T,d,f,E,product,tile", [
     # one round of 256- or 192-row tiles where smaller ones would need a second round (us there: 256 / 128 rows)
     (400, 4096, 11008, 2, UP, 256), (480, 4096, 11008, 1, UP, 256), (6000, 4096, 688, 4, UP, 256), (320, 4096, 11008, 2, UP, 192),
