@@ -45,3 +45,18 @@ TRANSPOSED_ROWS = [
     (1100, 136, 2056, 3, 1, dict(bias=[0.0, -60.0, 0.0], poison=True)), (6100, 64, 2056, 33, 2, dict(bias=[0.0] * 32 + [-60.0], poison=True)),
     (1500, 520, 3608, 4, 1, dict(bias=[3.0, 0.0, 0.0, 0.0], poison=True)),
 ]
+
+# many tokens' routing: (T, d, E, k, dtype, with the normalisation) -> experts of a pass over the columns, wavefronts that share 16
+# tokens.  Ragged last blocks; one workgroup on a compute unit, two, more.
+ROUTE_MANY = [
+    ((1030, 136, 1, 1, B.BTX_BF16, True), (1, 16)), ((1030, 136, 2, 2, B.BTX_BF16, True), (2, 16)), ((1030, 4104, 3, 2, B.BTX_BF16, True), (4, 16)),
+    ((1035, 4096, 4, 2, B.BTX_BF16, True), (4, 16)), ((1030, 1032, 5, 2, B.BTX_BF16, True), (8, 8)), ((1030, 520, 40, 3, B.BTX_BF16, True), (8, 16)),
+    ((4203, 136, 3, 2, B.BTX_BF16, True), (4, 8)), ((8190, 72, 2, 1, B.BTX_BF16, True), (2, 4)),
+    ((1030, 136, 1, 1, B.BTX_F32, True), (1, 16)), ((1030, 520, 2, 1, B.BTX_F32, True), (2, 8)), ((1030, 136, 3, 2, B.BTX_F32, True), (4, 16)),
+    ((1030, 1032, 5, 2, B.BTX_F32, True), (8, 8)), ((1030, 8200, 2, 1, B.BTX_F32, True), (2, 4)), ((1030, 8200, 3, 2, B.BTX_F32, True), (4, 4)),
+    ((1030, 8200, 7, 2, B.BTX_F32, True), (8, 4)), ((4203, 4104, 8, 2, B.BTX_F32, True), (8, 4)),
+    ((1030, 136, 1, 1, B.BTX_BF16, False), (1, 8)), ((1030, 1032, 2, 1, B.BTX_BF16, False), (2, 8)), ((1030, 136, 3, 2, B.BTX_BF16, False), (4, 8)),
+    ((4203, 72, 2, 2, B.BTX_BF16, False), (2, 4)), ((1030, 136, 1, 1, B.BTX_F32, False), (1, 8)), ((1030, 520, 2, 1, B.BTX_F32, False), (2, 8)),
+    ((1030, 8200, 2, 1, B.BTX_F32, False), (2, 4)), ((1030, 8200, 3, 2, B.BTX_F32, False), (4, 4)), ((1030, 8200, 7, 2, B.BTX_F32, False), (8, 4)),
+    ((520, 4096, 5, 2, B.BTX_BF16, False), (8, 8)), ((520, 4096, 5, 2, B.BTX_BF16, True), (8, 8)), ((1024, 4096, 1, 1, B.BTX_F32, False), (1, 8)),
+]

@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import LAST_ROUND_CUT, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -445,7 +445,7 @@ def test_routing_of_few_tokens(T, d, E, k, kw, dtype):
 
 
 @pytest.mark.parametrize("T,d,f,E,k,kw", [
-    # 1, 2, 3 and 8 slots in registers and more than that; an odd number of slices, dropped pairs
+    # 1, 2, 3 and 8 slots in registers (12: a finishing kernel adds them); an odd number of slices, dropped pairs
     (9, 264, 2056, 4, 1, {}), (20, 72, 2056, 5, 2, {}), (17, 264, 1544, 6, 3, dict(cf=0.8, poison=True)), (20, 264, 2056, 12, 12, {}),
     (5, 1032, 1096, 8, 8, {}),
 ])
@@ -609,7 +609,7 @@ def test_block_rmsnorm_route_forward_backward(T, d, f, E, k, dtype):
 
 
 @pytest.mark.parametrize("T,d,E,k,dtype", [
-    # 16, 8 and 4 wavefronts for 16 tokens, up to one workgroup of them on a compute unit and past that; ragged last blocks
+    # few experts go to the two launches up to 1024 tokens, to 16 or 4 wavefronts for 16 tokens above (see ROUTE_MANY); ragged last blocks
     (601, 136, 3, 2, BF16), (523, 1032, 40, 4, BF16), (601, 136, 40, 3, F32), (530, 1032, 5, 2, F32), (515, 8200, 3, 2, F32),
     (4203, 72, 33, 2, BF16), (4203, 72, 9, 2, F32), (4203, 4104, 3, 1, F32), (8190, 72, 5, 3, BF16),
 ])
@@ -622,6 +622,17 @@ def test_block_rmsnorm_route_wavefronts(T, d, E, k, dtype):
 def test_routing_wavefronts(T, d, E, k, dtype):
     """Without the normalisation: the vector unit up to 8 experts, the matrix cores beyond."""
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False)
+
+
+@pytest.mark.parametrize("case,taken", ROUTE_MANY)
+def test_routing_of_many_tokens(case, taken):
+    """Every number of experts in a pass and of wavefronts that share 16 tokens, above the sizes that two launches take."""
+    T, d, E, k, code, norm = case
+    dtype = BF16 if code == B.BTX_BF16 else F32
+    if norm:
+        run_block_and_check(T, d, 64, E, k, dtype)
+    else:
+        run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False)
 
 
 def test_block_rmsnorm_with_switch_routing_and_capacity():
@@ -641,7 +652,8 @@ def test_block_rmsnorm_route_matches_plain_route_on_the_normalised_rows():
 
 
 @pytest.mark.parametrize("T,d,E,dtype", [(600, 4096, 4, BF16), (3001, 1032, 7, BF16), (4201, 2048, 8, BF16), (700, 512, 8, F32), (4201, 512, 3, F32),
-                                         (530, 8200, 2, F32), (1024, 4096, 4, BF16), (640, 4096, 8, BF16), (1024, 8200, 4, F32), (520, 4104, 7, F32)])
+                                         (530, 8200, 2, F32), (1024, 4096, 4, BF16), (640, 4096, 8, BF16), (1024, 8200, 4, F32), (520, 4104, 7, F32),
+                                         (1030, 8200, 2, F32), (1100, 1032, 3, BF16), (1035, 4096, 4, BF16)])
 def test_block_rmsnorm_route_gives_the_same_bits_with_other_wavefronts(T, d, E, dtype):
     """Sizes where the fused kernel and btx_moe_route split the tokens of a block over different numbers of wavefronts, and sizes
     between those that few tokens' kernels take and those that they do not."""

@@ -8,7 +8,7 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -209,6 +209,15 @@ def test_routing_takes_the_same_way_with_and_without_the_normalisation(record, E
     for shape, (rc, plain), (norm_rc, norm) in zip(shapes, found[::2], found[1::2]):
         assert rc == norm_rc == 0
         assert ("route_small" in plain[0].kernel) == ("route_small" in norm[0].kernel), shape
+
+
+@pytest.mark.parametrize("case,taken", ROUTE_MANY)
+def test_shapes_of_many_tokens_routing_take_that_path(record, case, taken):
+    T, d, E, k, dtype, norm = case
+    (rc, found), = record(route_call(*case))
+    tokens, = [launch.kernel for launch in found if launch.kernel.startswith("route_tokens")]
+    experts, with_norm, waves = re.search(r", (\d+), (true|false), (\d+), ", tokens).groups()
+    assert rc == 0 and (int(experts), int(waves)) == taken and with_norm == str(norm).lower()
 
 
 @pytest.mark.parametrize("T,d,E,k,launches", [
