@@ -34,8 +34,8 @@
  *     units of the device (the bf16 up-projection, down-projection and input-gradient
  *     products cut the tiles of a partly filled last round of workgroups, or with few rows per
  *     expert every tile, into up to eight K ranges; fp32 does so with the tiles of the
- *     down-projection and the input gradient when they are few; a second kernel adds the
- *     ranges in ascending order).
+ *     down-projection and the input gradient when they are few; a second kernel, after the
+ *     down-projection of few rows the one that combines them, adds the ranges in ascending order).
  *   - Outputs must not alias inputs unless stated.  NaN/Inf inputs give
  *     unspecified results.
  */
@@ -116,7 +116,8 @@ enum {
   BTX_STAGE_BWD_ACT = 6,      /* backward: dys W2^T + SwiGLU backward              */
   BTX_STAGE_BWD_DX = 7,       /* backward: dh1 W1^T + dh3 W3^T                     */
   BTX_STAGE_GATHER_X_BWD = 8, /* backward: x and dY -> transposed grouped rows for
-                                  the weight gradients (bf16; none with frozen experts) */
+                                  the weight gradients (bf16 and experts of many rows; none
+                                  with frozen experts)                              */
   BTX_STAGE_DW13 = 9,         /* backward: dW1, dW3                                */
   BTX_STAGE_DW2 = 10,         /* backward: dW2                                     */
   BTX_STAGE_ROUTER_BWD = 11,  /* backward: router gradients and final dX           */
@@ -207,7 +208,8 @@ int btx_moe_route_noalloc(const void* x, int x_dtype, const float* W_router, con
  *   xn     [T,d]  x_dtype   out; must not alias h
  *   rstd   [T]    fp32      out
  * Mean square, rstd and the product are evaluated in fp64 and xn is rounded once to x_dtype;
- * the logits are computed from those rounded values, exactly as btx_moe_route would from xn.
+ * the logits are computed from those rounded values, exactly as btx_moe_route would from xn (more
+ * than 8 experts and 512 tokens: to the rounding of fp32 sums, which may run in another order).
  * Everything else as btx_moe_route (same workspace size).
  */
 int btx_moe_norm_route(const void* h, int x_dtype, const float* gain, float eps, void* xn, float* rstd,

@@ -250,8 +250,8 @@ int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* d
 // residual (may be NULL): [T,d] added to the sum in fp32 before the one rounding
 // slices > 1: y is not there yet, y_sums [slices][T*k, d] are to be added first (see launch_down); at most combine_most_slices()
 int combine_most_slices(int T, int k, int dtype);
-int launch_combine(const void* y, const float* y_sums, int slices, const float* gates, const int32_t* inv_pos, const void* residual, void* out, int T,
-                   int k, int d, int dtype, hipStream_t s);
+int launch_combine(const void* y, const float* y_sums, int slices, const float* gates, const int32_t* inv_pos,
+                   const void* residual, void* out, int T, int k, int d, int dtype, hipStream_t s);
 
 // Expert GEMM stages.  `offsets` = E+1 grouped-row offsets on the device.
 struct FfShapes { int R, d, f, E; int64_t s13, s2; };
@@ -270,8 +270,8 @@ int launch_up_swiglu(int dtype, const RowSource& xs, const void* W1, const void*
 // each other on a stream may share it.
 size_t ff_forward_split_bytes(int dtype, const FfShapes& sh);
 size_t ff_backward_split_bytes(int dtype, const FfShapes& sh);
-// y = act W2.  *slices: in, how many K slices of a row whoever reads y can add up; out, 1, or the number of slices whose sums [slices][R, d]
-// are left for it in `partial`.
+// y = act W2.  *slices: in, how many K slices of a row whoever reads y can add up; out, 1, or the number of slices whose
+// sums [slices][R, d] are left for it in `partial`.
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, int* slices, hipStream_t s);
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.

@@ -13,7 +13,9 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
 // sums: scratch for the sums of K slices, of f32_down_sums_bytes() (f32_bwd_dx_sums_bytes() in f32_bwd_dx); NULL when that is 0
 size_t f32_down_sums_bytes(const FfShapes& sh);
 size_t f32_bwd_dx_sums_bytes(const FfShapes& sh);
-int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices, hipStream_t s);   // slices: see launch_down()
+// slices: see launch_down()
+int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices,
+             hipStream_t s);
 int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
                 float* dg_part, hipStream_t s);

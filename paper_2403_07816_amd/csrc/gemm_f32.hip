@@ -413,8 +413,9 @@ __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float
 
 // K slices of DOWN and BWD_DX.  Few tiles of many k tiles leave compute units idle, or some with a tile more than others.
 // Measured on 64 x 64 tiles of 32 k: with r tiles on a compute unit a k tile takes about 0.35 us for every four of them and
-// 0.55 us each; the slices' sums pass through memory once more, in a launch of its own.  64 tokens, 8 experts of 512 x
-// 1376, top-2: DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: see most_slices().
+// 0.55 us each; the slices' sums pass through memory once more, BWD_DX's in a launch of its own.  (DOWN's are added by the combine where
+// combine_most_slices() allows it; the launch that this saves is charged all the same.)  64 tokens, 8 experts of 512 x 1376, top-2:
+// DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: see most_slices().
 int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
   const int busy = std::max(std::min(E, R), 1);
   const int64_t tiles = (int64_t)busy * ceil_div(ceil_div(R, busy), kTile) * ceil_div(N, kTile);

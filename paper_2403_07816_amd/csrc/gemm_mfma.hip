@@ -16,9 +16,9 @@
 //   * an operand whose K index is contiguous in memory is stored [row][BK] with a 16-byte
 //     chunk XOR swizzle and read with ds_read_b128; an operand whose K index is strided
 //     (the weights in UP and DOWN, dh1/dh3 in DW13) is stored as it lies in memory, [BK][cols],
-//     and read with the transposing ds_read_b64_tr_b16; x, dY and ga reach the dW products
-//     transposed and zero-padded per expert (x and dY from a gather kernel, ga written that way
-//     by BWD_ACT's epilogue).  The swizzles are applied by choosing which
+//     and read with the transposing ds_read_b64_tr_b16; x, dY and ga reach the dW products of
+//     many rows per expert transposed and zero-padded (x and dY from a gather kernel, ga written
+//     that way by BWD_ACT's epilogue; see DwStrip for few rows).  The swizzles are applied by choosing which
 //     global chunk each lane fetches, since a direct copy fixes the LDS position per lane;
 //   * v_mfma_f32_16x16x32_bf16 (on this chip it sustains a seventh more than the 32x32x16 form
 //     under the same power limit) with the roles of the operands swapped (the N-side fragment
@@ -57,9 +57,9 @@ enum Mode { UP = 0, DOWN = 1, BWD_ACT = 2, BWD_DX = 3, DW13 = 4, DW2 = 5 };
 struct MArgs {
   const bf16_t* A0; const bf16_t* A1;   // A1: second K pass (BWD_DX)
   const bf16_t* B0; const bf16_t* B1;   // B1: second panel (UP, DW13) or second K pass (BWD_DX)
-  void* C0; void* C1; void* C2;         // UP: h1,h3,act; BWD_ACT: dh1,dh3 (ga goes to T2); DW13: dW1,dW3; else C0
+  void* C0; void* C1; void* C2;         // UP: h1,h3,act; BWD_ACT: dh1,dh3,ga (or NULL, see T2); DW13: dW1,dW3; else C0
   const bf16_t* H1; const bf16_t* H3;   // BWD_ACT inputs
-  bf16_t* T2; int ldt;                  // BWD_ACT: ga transposed [N][ldt], experts' rows padded to 64 (NULL: not wanted)
+  bf16_t* T2; int ldt;                  // BWD_ACT: ga transposed [N][ldt], experts' rows padded to 64 (NULL: ga goes to C2, if at all)
   const float* gates; const int32_t* perm; float* dg_part; int n_part;
   const int32_t* a_perm; int a_k;       // UP / BWD_ACT: A row r is row a_perm[r] / a_k of A0 (NULL: row r)
   const int32_t* offsets; int E;
@@ -150,7 +150,7 @@ template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, in
           bool STREAM = MODE == BWD_ACT || MODE == DOWN>
 struct Gemm {
   // K index contiguous in memory?  A always is.  In the dW products K is the grouped-row index:
-  // x (dW1/dW3) and ga, dY (dW2) arrive transposed, [columns][padded rows], every expert's rows
+  // x (dW1/dW3) and ga, dY (dW2) arrive here transposed, [columns][padded rows], every expert's rows
   // starting at a multiple of 64 and zero-filled up to the next one; dh1/dh3 stay row-major.
   static constexpr bool A_KC = true;
   static constexpr bool B_KC = (MODE != UP && MODE != DOWN && MODE != DW13);

@@ -120,7 +120,8 @@ constexpr int kFewRows = 8192;
 // ET as a finishing kernel of the product would have (forward pass, 16 tokens, 4 experts of 4096 x 11008 197.4 -> 195.7 us); no more
 // than combine_most_slices().
 template <typename ET, int KMAX, bool SLICED>
-__global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restrict__ y_rows, int slices, int64_t slice_stride, const float* __restrict__ gates,
+__global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restrict__ y_rows, int slices, int64_t slice_stride,
+                                                           const float* __restrict__ gates,
                                                            const int32_t* __restrict__ inv_pos,
                                                            const u32x4* __restrict__ residual, u32x4* __restrict__ out,
                                                            int T, int k, int chunks_per_row) {
@@ -154,7 +155,8 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const void* __restric
           for (int j = 0; j < KMAX; ++j)
             RowVec<float, N>::ld(static_cast<const float*>(y_rows) + min(s0 + b, slices - 1) * slice_stride +
                                      ((int64_t)max(row[j], 0) * chunks_per_row + c) * N, u[b][j]);
-        __builtin_amdgcn_sched_barrier(0);                // no sum in front of a load (30 tokens, top-3, 4 experts of 1024 x 5504: 36.1 us, 34.8)
+        // no sum in front of a load (30 tokens, top-3, 4 experts of 1024 x 5504: 36.1 us, 34.8)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
@@ -221,8 +223,8 @@ int combine_most_slices(int T, int k, int dtype) {
   return (dtype == BTX_BF16 ? 32 : 64) / k;
 }
 
-int launch_combine(const void* y, const float* y_sums, int slices, const float* gates, const int32_t* inv_pos, const void* residual, void* out, int T,
-                   int k, int d, int dtype, hipStream_t s) {
+int launch_combine(const void* y, const float* y_sums, int slices, const float* gates, const int32_t* inv_pos,
+                   const void* residual, void* out, int T, int k, int d, int dtype, hipStream_t s) {
   const int esz = dtype == BTX_BF16 ? 2 : 4;
   const int chunks = d * esz / 16;
   const bool few = T < kFewRows;
@@ -232,8 +234,8 @@ int launch_combine(const void* y, const float* y_sums, int slices, const float* 
     const bool sliced = slices > 1;
     auto kernel = sliced ? combine_kernel<ET, decltype(kmax)::value, true> : combine_kernel<ET, decltype(kmax)::value, false>;
     kernel<<<grid, kThreads, 0, s>>>(
-        sliced ? static_cast<const void*>(y_sums) : y, slices, (int64_t)T * k * d, gates, inv_pos, static_cast<const u32x4*>(residual), static_cast<u32x4*>(out), T, k,
-        chunks);
+        sliced ? static_cast<const void*>(y_sums) : y, slices, (int64_t)T * k * d, gates, inv_pos,
+        static_cast<const u32x4*>(residual), static_cast<u32x4*>(out), T, k, chunks);
   };
   auto by_k = [&](auto tag) {
     if (k <= 1) run(tag, std::integral_constant<int, 1>{});
