@@ -384,9 +384,9 @@ template <int ROUNDS, int PIECE> __global__ __launch_bounds__(kGroupThreads) voi
 //     14.3 / 13.3, of 2048 15.5 / 15.2, of 4096 17.7 / 19; top-3 853 of 1024 14.8 / 14.0, top-4 1024 of 2048 16.7 / 17.6; 640 of 1024, 8
 //     experts 16.5 / 14.2, of 2336 19.4 / 17.8; 9 experts, 640 of 1024 17.0 / 14.3, of 1600 17.3 / 16.9; 16 experts, top-4, 640 of 392
 //     17.0 / 16.2, of 776 17.3 / 17.9, of 1024 20.3 / 18.9, of 1072 18.6 / 20.5 (with the normalisation 26.4 / 20.2 for 776)
-//   other numbers of experts, whose last columns are loaded one by one: 1024 of 256, 2 experts 11.8 / 9.6, of 512 12.5 / 12.8, of 4096
-//     15.7 / 25; 3 experts of 512 13.6 / 14.0; 640 of 256, 7 experts 15.2 / 14.2, of 448 15.3 / 15.8; 520 of 4096, 5 experts 19.5 / 42; 640
-//     of 256, 13 experts 17.7 / 16.6, 12 of 1024 19.3 / 20.7
+//   other numbers of experts, whose last columns are loaded one by one: 1024 of 256, 2 experts 11.8 / 9.6, of 384 12.6 / 12.6, of 4096
+//     15.7 / 25; 3 experts of 512 13.6 / 14.0; 640 of 256, 7 experts 15.2 / 14.2, of 448 15.3 / 15.8; 5 experts 640 of 512 14.4 / 13.8, 520
+//     of 4096 19.5 / 42; 640 of 256, 13 experts 17.7 / 16.6, 12 of 1024 19.3 / 20.7
 //   64 experts, top-4, of 512 columns: 512 tokens 31 / 31, 600 31 / 34
 // The normalisation is not asked, though it gains more (1024 of 2048, 4 experts 20.9 / 17.3): a logit's sum has another order in two
 // launches than in four, and routing with it is routing without it on the rows it writes, bit for bit.
@@ -394,8 +394,9 @@ bool route_is_small(const RouteArgs& a) {
   const int64_t traffic = (int64_t)a.T * a.d * a.E, pairs = (int64_t)a.T * a.k;
   if (pairs > kSmallPairs || traffic > kSmallTraffic) return false;
   if (a.T <= kSmallTokens) return true;
-  if (a.E <= 4) return a.T <= 1024 && pairs <= 2560 && traffic <= (a.E == 4 ? 12000000 : 500000);
-  if (a.E <= 8) return a.T <= 640 && traffic <= (a.E == 8 ? 12000000 : 800000);
+  if (a.E <= 8)
+    return a.T <= (a.E <= 4 ? 1024 : 640) && (a.E > 4 || pairs <= 2560) &&
+           traffic <= (a.E % 4 == 0 ? 12000000 : a.E < 4 ? 800000 : 1300000);
   return a.E <= 16 && a.T <= 640 && traffic <= (a.E == 9 || (a.E == 16 && a.d <= 1024) ? 10500000 : 2500000);
 }
 
