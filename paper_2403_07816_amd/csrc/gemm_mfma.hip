@@ -1090,8 +1090,11 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
     // on one of 32 of 1024 x 2752 757, 530, 582; milder, kLong 1.5 / 1.15: 523 of 1300 rows on one of 4 of 2048 x 5504 392 / 331, tiles
     // 359; 730 of 3600 on one of 8 of 1024 x 2752 268 / 237, 260; 391 of 2400 on one of 8 of 1024 x 1376 141 / 146, 150)
     const bool x_long = lane < g.E && (float)x_cost * (float)g.E > kLong * costs;
-    const int incl_long = wave_incl_scan_i32(x_long ? x_strips : 0, lane);
-    int n_long = __builtin_amdgcn_readlane(incl_long, kWave - 1) * nx;
+    int incl_long = 0, n_long = 0;
+    if (__builtin_expect(__ballot(x_long) != 0, 0)) {
+      incl_long = wave_incl_scan_i32(x_long ? x_strips : 0, lane);
+      n_long = __builtin_amdgcn_readlane(incl_long, kWave - 1) * nx;
+    }
     if (n_long <= kXcdStrips) n_long = 0;                // an XCD has a unit for each and reads their rows once (16 of 1024 x 64, one with
                                                          // 8000 of 16000 rows: 424, dealt out 433)
     const int incl_rest = wave_incl_scan_i32(x_long && n_long ? 0 : x_strips, lane);
