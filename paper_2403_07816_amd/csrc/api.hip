@@ -36,7 +36,7 @@ FwdWs carve_forward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   return w;
 }
 
-struct BwdWs { void *xsT, *dysT, *dys, *dh1, *dh3, *ga, *dxs, *router, *partial; float* dg_part; size_t bytes; };
+struct BwdWs { uint32_t* row_bytes; void *xsT, *dysT, *dys, *dh1, *dh3, *ga, *dxs, *router, *partial; float* dg_part; size_t bytes; };
 BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const size_t R = (size_t)T * k, es = esize(dtype);
   const FfShapes sh{(int)R, d, f, E, 0, 0};
@@ -47,6 +47,8 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const size_t dw_op = (size_t)d * ff_dw_pitch((int)R, E) * es;
   w.xsT = tr ? c.take(dw_op) : nullptr;
   w.dysT = tr ? c.take(dw_op) : nullptr;
+  // byte offsets of the token rows, for weight gradients that read them: bf16, where the transposed rows would lie
+  w.row_bytes = static_cast<uint32_t*>(tr ? w.xsT : c.take(R * sizeof(uint32_t)));
   w.dys = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   w.dh1 = c.take(R * f * es);
   w.dh3 = c.take(R * f * es);
@@ -321,8 +323,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
   const bool direct = ff_dw_direct(dtype, dW_dtype, sh, fused);
-  // bf16 weight gradients that read token rows: their offsets lie where the transposed rows would
-  uint32_t* row_bytes = direct && n_dw == 3 ? static_cast<uint32_t*>(w.xsT) : nullptr;
+  uint32_t* row_bytes = direct && n_dw == 3 ? w.row_bytes : nullptr;   // of weight gradients that read token rows
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));
   BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx(dtype, w.dh1, w.dh3, W1, W3, offsets, sh, w.dxs, w.partial, s));

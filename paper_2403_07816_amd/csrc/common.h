@@ -276,7 +276,7 @@ int launch_down(int dtype, const void* act, const void* W2, const int32_t* offse
                 void* partial, int* slices, hipStream_t s);
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.
 // dh1, dh3: [R,f].  With ga_transposed `ga` receives g*a transposed and padded ([f][ff_dw_pitch()]); otherwise it is
-// [R,f].  Nothing at all in bf16 when want_dw is false.  row_bytes ([R], bf16; may be NULL): for the weight gradients, the byte
+// [R,f].  Nothing at all in bf16 when want_dw is false.  row_bytes ([R]; may be NULL): for the weight gradients, the byte
 // offset of every grouped row's token row.
 // bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile), and the
 // most that any number of rows gets (fewer rows may run with narrower tiles)

@@ -50,7 +50,7 @@ int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* 
                    bool want_dw, bool ga_transposed, uint32_t* row_bytes, float* dg_part, hipStream_t s) {
   if (!want_dw) ga = nullptr;
   if (dtype == BTX_BF16) return mfma_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, ga_transposed, row_bytes, dg_part, s);
-  return f32_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, dg_part, s);
+  return f32_bwd_act(dys, W2, h1, h3, gates, perm, offsets, sh, dh1, dh3, ga, row_bytes, dg_part, s);
 }
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s) {
@@ -60,12 +60,12 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
 int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
                     const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s) {
   if (dtype == BTX_BF16) return mfma_bwd_dw13(dW_dtype, xs, dh1, dh3, offsets, sh, row_bytes, dW1, dW3, s);
-  return f32_bwd_dw13(xs, dh1, dh3, offsets, sh, dW1, dW3, s);
+  return f32_bwd_dw13(xs, dh1, dh3, offsets, sh, row_bytes, dW1, dW3, s);
 }
 int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
                    const FfShapes& sh, uint32_t* row_bytes, void* dW2, hipStream_t s) {
   if (dtype == BTX_BF16) return mfma_bwd_dw2(dW_dtype, ga, dys, offsets, sh, row_bytes, dW2, s);
-  return f32_bwd_dw2(ga, dys, offsets, sh, dW2, s);
+  return f32_bwd_dw2(ga, dys, offsets, sh, row_bytes, dW2, s);
 }
 
 }  // namespace btx

@@ -3,23 +3,29 @@
 // operands, fp32 matrix instructions (v_mfma_f32_16x16x4_f32: exact products, fp32 sums) and fp32 storage.
 //
 // The matrix pipe bounds it: 256 FLOP per clock and compute unit, a sixteenth of bf16, while a fragment
-// feeds as many output tiles, so LDS and L2 have room to spare.  The tiles are therefore kept simple:
-//   * 64 x 64 x 32, 4 wavefronts as 2 x 2, operands global -> registers -> LDS, two LDS stages, the loads of the
-//     next two k tiles in flight during a k tile's products, one barrier per k tile; four workgroups per compute unit
-//     cover each other's barriers.
+// feeds as many output tiles, so LDS and L2 have room to spare.  What keeps the pipe from being busy is the other
+// instructions: each vector or scalar one costs it 2 to 4 clocks, whichever wavefront of the SIMD issues it.  So the tiles are
+// kept simple and the loop short:
+//   * 64 x 64 x 32, 4 wavefronts as 2 x 2, two LDS stages, one barrier per k tile; five workgroups per compute unit cover
+//     each other's barriers and memory latency (three stages and three workgroups: 4 % slower, 9 % with four and two).
+//   * operands go straight from global memory to LDS, four copies per wavefront and k tile in one block: one setting of m0,
+//     bases in scalar registers, 32-bit lane offsets that stay the same from k tile to k tile.  With copies from 64-bit addresses in
+//     vector registers the compute unit's other wavefronts lose the matrix pipe to them: 4096 rows, one expert of 1024 x 4096: DOWN
+//     319 us, 249 like this.  Those only serve operands that 32 bits do not reach (wide_offsets()).
 //   * within 16 consecutive k a lane of k group g supplies k = 4 g + i to instruction i (the order of k inside
 //     a sum is free as long as both operands agree), so that an operand whose k is contiguous in memory is kept
-//     as [row][BK] and read 16 bytes at a time; an operand whose k is strided (the weights in UP and DOWN,
-//     everything in the dW products) stays as it lies in memory, [BK][columns], and a wavefront's fragments are
-//     interleaved columns, one read for all of them.  Pitches of BK + 4 and columns + 8 floats against bank conflicts.
-//   * addresses are pointers that move on by a k tile; only a last, partial k tile is masked.
+//     as rows of k and read 16 bytes at a time; an operand whose k is strided (the weights in UP and DOWN,
+//     everything in the dW products) stays as it lies in memory, and a wavefront's fragments are interleaved columns, one
+//     read for all of them.
+//   * only a last, partial k tile is masked; a branch leads there.
 //   * the operands' roles are swapped, so that a lane ends up with 4 consecutive columns of one row.
-//   * token rows (x, dY) are read through perm wherever they are an operand, the SwiGLU and its backward are
-//     epilogues on the accumulators: nothing is gathered, and no product is stored only to be read again.
-// Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP): with plain FMA
-// tiles, gathered operands and separate elementwise kernels 1.64 ms, now 0.60; the products run at 70 to 94 of the
-// 153 TFLOP/s this instruction sustains (matrix pipe busy 46 - 66 %): UP 120 us, DOWN 81, BWD_ACT 72, BWD_DX 131 + 5,
-// DW13 123, DW2 67.  What is left is ragged rounds of 64 x 64 tiles and the operands' way through registers into LDS.
+//   * token rows (x, dY) are read through perm wherever they are an operand (the weight gradients: by byte offsets that BWD_ACT
+//     leaves behind, found through the scalar cache), the SwiGLU and its backward are epilogues on the accumulators: nothing is
+//     gathered, and no product is stored only to be read again.
+// Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP), operands through registers /
+// now: 601 / 559 us: UP 114 / 107 us, DOWN 77 / 58, BWD_ACT 68 / 66, BWD_DX 128 / 112, DW13 115 / 112, DW2 64 / 64, at 76 to 105 of the
+// 153 TFLOP/s this instruction sustains; 4096 rows, one expert of 1024 x 4096: 2598 / 2435, at 124 to 138.  What is left is
+// ragged rounds of 64 x 64 tiles and what starting and storing a tile takes.
 #include "gemm_f32.h"
 
 #include <algorithm>
@@ -35,7 +41,8 @@ struct FArgs {
   const float* B0; const float* B1;      // B1: second panel (UP), second product (DW13), second K pass (BWD_DX)
   float* C0; float* C1; float* C2;       // UP: h1, h3 (NULL: not kept), act; BWD_ACT: dh1, dh3, ga; DW13: dW1, dW3
   const float* H1; const float* H3; const float* gates; float* dg_part; int n_part;   // BWD_ACT
-  const int32_t* perm; uint32_t div_mul, div_shift;   // gathered operand: row r is token perm[r] / k
+  const int32_t* perm; uint32_t div_mul, div_shift; int k;   // gathered operand: row r is token perm[r] / k
+  uint32_t* row_bytes;                   // byte offset of every grouped row's token row: BWD_ACT writes it for the weight gradients (NULL: none wanted)
   const int32_t* perm_pairs;             // BWD_ACT: perm, for the gates
   const int32_t* offsets; int E;
   int M, N, K;                           // row-grouped: M unused; grouped along K: K unused
@@ -48,6 +55,7 @@ struct FArgs {
   __device__ __forceinline__ int token(int p) const { return (int)(((uint64_t)(uint32_t)p * div_mul) >> div_shift); }
   void gather(const RowSource& r) {
     perm = r.perm;
+    k = r.k;
     int l = 0;
     while ((1 << l) < r.k) ++l;
     div_shift = 31 + l;
@@ -56,128 +64,175 @@ struct FArgs {
 };
 
 constexpr int kThreads = 256;
+constexpr int kTile = 64, kTileK = 32;   // rows and columns of a tile, and k of a k tile
 constexpr int kBand = 8;                 // row tiles of a band in the tile order
 
-template <int BM, int BN, int BK, int MODE> struct F32Gemm {
+// at most N vector memory operations outstanding (vmcnt = bits [3:0] and [15:14]; expcnt and lgkmcnt left at max)
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ uint64_t uniform64(const float* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+// Four copies of 1 KB, 16 bytes per lane, from global memory straight into LDS, to lds, lds + 1024, ... : copies 0 and 1 from
+// a + off, 2 from b0 + off, 3 from b1 + off.  The offset of the instruction counts in memory as in LDS, so the lanes' offsets make up
+// for it (Operand::kBias), and all four share one setting of m0.  Inline assembly, so that the compiler does not wait for the
+// copies in flight before every LDS read; wait_vmcnt() awaits them.
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, const float* a, const float* b0, const float* b1, const uint32_t* oa, const uint32_t* ob) {
+  const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+               "global_load_lds_dwordx4 %3, %6 offset:2048\n\tglobal_load_lds_dwordx4 %4, %7 offset:3072"
+               :
+               : "s"(at), "v"(oa[0]), "v"(oa[1]), "v"(ob[0]), "v"(ob[1]), "s"(uniform64(a)), "s"(uniform64(b0)), "s"(uniform64(b1))
+               : "memory");
+}
+__device__ __forceinline__ void copy_to_lds(uint32_t lds, const float* a, const float* b0, const float* b1, const uint64_t* oa, const uint64_t* ob) {
+  const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
+  const uint64_t A = reinterpret_cast<uint64_t>(a), B0 = reinterpret_cast<uint64_t>(b0), B1 = reinterpret_cast<uint64_t>(b1);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\tglobal_load_lds_dwordx4 %2, off offset:1024\n\t"
+               "global_load_lds_dwordx4 %3, off offset:2048\n\tglobal_load_lds_dwordx4 %4, off offset:3072"
+               :
+               : "s"(at), "v"(A + oa[0]), "v"(A + oa[1]), "v"(B0 + ob[0]), "v"(B1 + ob[1])
+               : "memory");
+}
+
+// WIDE: byte offsets inside an operand need more than 32 bits (wide_offsets())
+template <int MODE, bool WIDE> struct F32Gemm {
+  typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
   static constexpr bool GROUP_K = MODE == DW13 || MODE == DW2;
   static constexpr bool A_KC = !GROUP_K, B_KC = MODE == BWD_ACT || MODE == BWD_DX;   // k contiguous in memory
   static constexpr bool A_GATHER = MODE == UP || MODE == BWD_ACT || MODE == DW13, B_GATHER = MODE == DW2;
   static constexpr bool SLICED = MODE == DOWN || MODE == BWD_DX;
-  static constexpr bool DUAL = MODE == UP;                       // two B panels side by side in one tile
-  static constexpr int BNH = DUAL ? BN / 2 : BN;                 // output columns of a tile
-  static constexpr int TM = BM / 32, TN = BN / 32, TNH = DUAL ? TN / 2 : TN;
-  static constexpr int A_PITCH = A_KC ? BK + 4 : BM + 8, B_PITCH = B_KC ? BK + 4 : BN + 8;
-  static constexpr int A_SIZE = (A_KC ? BM : BK) * A_PITCH, B_SIZE = (B_KC ? BN : BK) * B_PITCH;
-  static constexpr int NA = BM * BK / 4 / kThreads, NB = BN * BK / 4 / kThreads;      // 16-byte chunks per thread
-  static_assert(NA >= 1 && NB >= 1 && BK % 16 == 0 && (!DUAL || TN % 2 == 0), "tile");
+  static constexpr bool DUAL = MODE == UP;                       // two B panels in one tile
+  static constexpr int BNH = DUAL ? kTile / 2 : kTile;           // output columns of a tile
+  static constexpr int STAGE = 2 * kTile * kTileK, PIECE = STAGE / 4;   // floats of a stage, and of it those that one wavefront copies
 
-  // One operand of a tile: this thread's chunks of it, fetched to registers and put into LDS.
-  // contiguous: chunk (row, 4 k);  strided: chunk (k row, 4 columns).  Rows and columns past the matrix repeat
-  // its last ones: their results are never stored.
-  template <bool KC, int ROWS_OR_COLS, int PITCH, int NQ, bool GATHER> struct Operand {
-    const float* p[NQ];                  // the chunk in the k tile that is fetched next (gathered and strided: its column in row 0)
-    int kk[NQ], lds[NQ];                 // k of the chunk inside the tile; its place in LDS
-    int src[NQ];                         // gathered and strided: token row of the k row that is fetched next
-    f32x4 v[2][NQ];                      // two k tiles in flight
-    // the k tile in register set S, of which n_k k exist (the rest becomes zeros), to LDS
-    template <int S> __device__ __forceinline__ void put(float* tile, int n_k) {
-      if (n_k < BK) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int x = 0; x < 4; ++x) v[S][q][x] = kk[q] < n_k ? v[S][q][x] : 0.f;
-      }
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(tile + lds[q]) = v[S][q];
+  // LDS: a stage is four pieces of 4 KB, each two copies of A and two of B by one wavefront.  An operand whose k is contiguous: 16
+  // rows of 32 k to a piece, 8 chunks of 16 bytes to a row, the chunk index XORed with row / 2.  One whose k is strided: 8 k rows of 64
+  // columns, as it lies in memory, the halves of the row exchanged in every other group of four k.  Two panels (UP): 8 k rows
+  // of 32 columns of the one, then of the other, there odd and even k rows exchanged, and the halves of the row as above.  All of it
+  // makes the reads below free of bank conflicts.  A copy fixes where a lane's 16 bytes land, so a lane chooses which chunk of
+  // global memory it fetches.
+  static __device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 7; }
+  static __device__ __forceinline__ int tr_swz(bool panels, int k) { return ((k >> 2) & 1) << (panels ? 2 : 3); }
+
+  // One operand of a tile: this lane's chunks of it.  Rows and columns past the matrix repeat its last ones: their results are never
+  // stored.  SLOT: its first copy's place in the piece.
+  template <bool KC, bool GATHER, bool PANELS, int SLOT> struct Operand {
+    static constexpr bool LOOK_UP = !KC && GATHER;
+    static constexpr int kBias = 4096;   // bytes that `base` lies ahead of the data (see copy_to_lds())
+    const float* base;                   // uniform: first row and k (strided: k row and column) of the k tile that is copied next
+    const float* base2;                  // PANELS: the same of the second panel
+    Off off[2];                          // bytes from there to this lane's chunk of either copy (LOOK_UP: to its column)
+    uint32_t tok[LOOK_UP ? 8 : 1];       // LOOK_UP: byte offsets (WIDE: token rows) of this wavefront's k rows of the k tile that is copied next
+    // contiguous: the row, strided: the k row of this lane's chunk of copy q
+    static __device__ __forceinline__ int major_of(int q, int wave, int lane) {
+      return KC ? 16 * wave + 8 * q + (lane >> 3) : PANELS ? 8 * wave + ((lane >> 3) ^ q) : 8 * wave + 4 * q + (lane >> 4);
     }
-    static __device__ __forceinline__ void coords(int q, int& major, int& minor) {
-      constexpr int PER = (KC ? BK : ROWS_OR_COLS) / 4;
-      const int c = threadIdx.x + q * kThreads;
-      major = c / PER;
-      minor = 4 * (c % PER);
+    // contiguous: its k, strided: its column
+    static __device__ __forceinline__ int minor_of(int q, int wave, int lane) {
+      const int m = major_of(q, wave, lane);
+      return KC ? 4 * ((lane & 7) ^ kc_swz(m)) : PANELS ? 4 * ((lane & 7) ^ tr_swz(true, m)) : 4 * ((lane & 15) ^ tr_swz(false, m));
     }
-    // rows row0 .. of an operand whose k is contiguous, from k0 on
-    __device__ __forceinline__ void rows(const float* base, int row0, int row_end, int ld, const FArgs& g) {
+    static __device__ __forceinline__ Off bytes(int q, Off floats) { return floats * 4 + (Off)(kBias - 1024 * (SLOT + q)); }
+    // rows row0 .. of an operand whose k is contiguous, from `from` on
+    __device__ __forceinline__ void rows(const float* from, int row0, int row_end, int ld, int wave, int lane, const FArgs& g) {
+      base = from + ((GATHER ? (int64_t)0 : (int64_t)row0 * ld) - kBias / 4);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        int major, minor;
-        coords(q, major, minor);
-        const int r = min(row0 + major, row_end - 1);
-        p[q] = base + (int64_t)(GATHER ? g.token(g.perm[r]) : r) * ld + minor;
-        kk[q] = minor;
-        lds[q] = major * PITCH + minor;
-      }
-    }
-    // columns col0 .. of an operand whose k is strided, from row k0 on; DUAL: the second half of them is base2's
-    __device__ __forceinline__ void cols(const float* base, const float* base2, int col0, int n, int ld, int k0) {
-      constexpr int PANEL = DUAL ? ROWS_OR_COLS / 2 : ROWS_OR_COLS;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        int major, minor;
-        coords(q, major, minor);
-        const bool second = minor >= PANEL;
-        p[q] = (second ? base2 : base) + (GATHER ? (int64_t)0 : (int64_t)(k0 + major) * ld) +
-               min(col0 + minor - (second ? PANEL : 0), n - 4);
-        kk[q] = major;
-        lds[q] = major * PITCH + minor;
+      for (int q = 0; q < 2; ++q) {
+        const int r = min(row0 + major_of(q, wave, lane), row_end - 1);
+        off[q] = bytes(q, (Off)(GATHER ? g.token(g.perm[r]) : r - row0) * (Off)ld + (Off)minor_of(q, wave, lane));
       }
     }
-    // gathered and strided: look up the token rows of the k tile that is fetched next
-    __device__ __forceinline__ void look_up(const FArgs& g, int k0, int k_end) {
+    // columns col0 .. of an operand whose k is strided, from row k0 on; PANELS: as many of `from2` as well
+    __device__ __forceinline__ void cols(const float* from, const float* from2, int col0, int n, int ld, int k0, int wave, int lane) {
+      const int64_t first = (GATHER ? (int64_t)0 : (int64_t)k0 * ld) + col0 - kBias / 4;
+      base = from + first;
+      base2 = PANELS ? from2 + first : base;
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) src[q] = g.token(g.perm[min(k0 + kk[q], k_end - 1)]);
+      for (int q = 0; q < 2; ++q)
+        off[q] = bytes(q, (Off)(GATHER ? 0 : major_of(q, wave, lane)) * (Off)ld + (Off)(min(col0 + minor_of(q, wave, lane), n - 4) - col0));
     }
-    // request the next k tile, of which n_k k exist, and move on to the one after it
-    template <int S> __device__ __forceinline__ void fetch(int ld, int n_k) {
-      if (n_k < BK && !(!KC && GATHER)) {          // the last one of a pass: what lies past its end repeats its first k
+    // LOOK_UP: the token rows of the k tile from k0 on, through the scalar cache (vector loads would be waited for together with
+    // the copies behind them); rows past k_end repeat the last one
+    __device__ __forceinline__ void look_up(const FArgs& g, int k0, int k_end, int wave) {
+      typedef uint32_t u32x8 __attribute__((ext_vector_type(8), aligned(4)));
+      typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+      typedef const __attribute__((address_space(4))) u32x8* scalar_ptr8;
+      const scalar_ptr table = (scalar_ptr)(uintptr_t)(WIDE ? reinterpret_cast<const uint32_t*>(g.perm) : g.row_bytes);
+      const int k = k0 + 8 * wave;
+      if (k + 8 <= k_end) {
+        const u32x8 t = *(scalar_ptr8)(table + k);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-          if (kk[q] >= n_k) p[q] -= KC ? (int64_t)kk[q] : (int64_t)kk[q] * ld;
+        for (int x = 0; x < 8; ++x) tok[x] = t[x];
+      } else {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) tok[x] = table[min(k + x, k_end - 1)];
       }
+    }
+    // offsets of the copies of a k tile of which n_k k exist; k that do not exist repeat the tile's first (last) k
+    __device__ __forceinline__ void offsets(Off (&o)[2], int ld, int n_k, int wave, int lane, const FArgs& g) const {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q)
-        v[S][q] = *reinterpret_cast<const f32x4*>(p[q] + (!KC && GATHER ? (int64_t)src[q] * ld : (int64_t)0));
-      if (!(!KC && GATHER)) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) p[q] += KC ? (int64_t)BK : (int64_t)BK * ld;
+      for (int q = 0; q < 2; ++q) {
+        o[q] = off[q];
+        if constexpr (LOOK_UP) {
+          const int x = lane >> 4;
+          const uint32_t lo = x & 1 ? tok[4 * q + 1] : tok[4 * q], hi = x & 1 ? tok[4 * q + 3] : tok[4 * q + 2];
+          const uint32_t t = x & 2 ? hi : lo;
+          o[q] += WIDE ? (Off)g.token((int)t) * (Off)ld * 4 : (Off)t;
+        } else if (n_k < kTileK) {
+          const int k = KC ? minor_of(q, wave, lane) : major_of(q, wave, lane);
+          o[q] -= KC ? (Off)(k >= n_k ? 4 * k : 0) : (Off)max(k - n_k + 1, 0) * (Off)ld * 4;
+        }
       }
+    }
+    __device__ __forceinline__ void advance(int ld) {
+      if (LOOK_UP) return;
+      const int64_t step = KC ? (int64_t)kTileK : (int64_t)kTileK * ld;
+      base += step;
+      base2 += step;
     }
   };
 
   // Fragments of 16 rows (columns) x 16 k: element x of f[i] feeds instruction x, k = 16 s + 4 (lane / 16) + x.
-  // contiguous: fragment i is rows base + 16 i + lane % 16; strided: rows base + N (lane % 16) + i, so that one read
-  // of N consecutive floats serves all N fragments.
-  template <bool KC, int PITCH, int N>
-  static __device__ __forceinline__ void frags(const float* tile, int base, int s, int lane, f32x4* f) {
-    const int r = lane & 15, k = 16 * s + 4 * (lane >> 4);
+  // contiguous: fragment i is rows 32 w + 16 i + lane % 16 of the tile; strided: columns 32 w + 2 (lane % 16) + i, one read for both
+  // fragments.  PANELS: 16 columns of either panel, two pairs of columns from the first, two of the second, and so on, so that
+  // a lane of the result holds both products of its outputs.
+  template <bool KC, bool PANELS>
+  static __device__ __forceinline__ void frags(const float* tile, int w, int s, int lane, f32x4* f) {
+    const int r = lane & 15, g4 = lane >> 4;
     if constexpr (KC) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) f[i] = *reinterpret_cast<const f32x4*>(tile + (base + 16 * i + r) * PITCH + k);
+      for (int i = 0; i < 2; ++i)
+        f[i] = *reinterpret_cast<const f32x4*>(tile + (2 * w + i) * PIECE + r * kTileK + (((4 * s + g4) ^ kc_swz(r)) << 2));
     } else {
-      typedef float __attribute__((ext_vector_type(N))) vec;
+      typedef float __attribute__((ext_vector_type(2))) vec;
+      const int k = 4 * g4, p = (r >> 1) & 1;            // of 16 s + k + x: piece 2 s + k / 8
+      const int col = (PANELS ? 16 * w + 2 * ((r & 1) + 2 * (r >> 2)) : 32 * w + 2 * r) ^ (tr_swz(PANELS, k) << 2);
+      const float* at = tile + (2 * s + (k >> 3)) * PIECE + col + (PANELS ? 256 * p : 0);
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const vec w = *reinterpret_cast<const vec*>(tile + (k + x) * PITCH + base + N * r);
-#pragma unroll
-        for (int i = 0; i < N; ++i) f[i][x] = w[i];
+        const vec v = *reinterpret_cast<const vec*>(at + (PANELS ? (((k & 7) + x) ^ p) * 32 : ((k & 7) + x) * 64));
+        f[0][x] = v[0];
+        f[1][x] = v[1];
       }
     }
   }
   // row of fragment i (A) that this lane's results belong to, relative to the wavefront's first
   static __device__ __forceinline__ int out_row(int i, int lane) {
-    return A_KC ? 16 * i + (lane & 15) : TM * (lane & 15) + i;
+    return A_KC ? 16 * i + (lane & 15) : 2 * (lane & 15) + i;
   }
-  // group q (of TNH) of 4 consecutive output columns of a panel: the first one, relative to the wavefront's first ...
+  // group q of 4 consecutive output columns (UP: one, of each panel): the first one, relative to the wavefront's first ...
   static __device__ __forceinline__ int out_col(int q, int lane) {
-    return B_KC ? 16 * q + 4 * (lane >> 4) : 4 * (TNH * (lane >> 4) + q);
+    return DUAL ? 4 * (lane >> 4) : B_KC ? 16 * q + 4 * (lane >> 4) : 4 * (2 * (lane >> 4) + q);
   }
-  // ... and the four results of one fragment row
+  // ... and the four results of one fragment row (UP: of panel q)
   static __device__ __forceinline__ f32x4 out4(const f32x4* acc, int q) {
-    if constexpr (B_KC) return acc[q];
-    f32x4 r;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) r[x] = acc[(4 * q + x) % TNH][(4 * q + x) / TNH];
-    return r;
+    if constexpr (!DUAL && B_KC) return acc[q];
+    return f32x4{acc[0][2 * q], acc[1][2 * q], acc[0][2 * q + 1], acc[1][2 * q + 1]};
   }
 
   static __device__ void run(const FArgs& g, float* smem) {
@@ -189,7 +244,7 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
     // about as high as it is wide, its L2 keeps the band's rows, and the columns of the weights pass through it once.
     int e = 0, row0, row_end, k_begin = 0, k_end = g.K;
     const int nx = MODE == DW13 ? 2 * g.tiles_n : g.tiles_n;
-    RowTiles row_tiles(g.offsets, GROUP_K ? 1 : g.E, BM, lane);
+    RowTiles row_tiles(g.offsets, GROUP_K ? 1 : g.E, kTile, lane);
     const int per_row_tile = SLICED ? nx * g.slices : nx;
     const int total = GROUP_K ? g.E * g.tiles_m * nx : row_tiles.count() * per_row_tile;
     const int share = (total + 7) / 8, id = (int)(blockIdx.x % 8) * share + (int)(blockIdx.x / 8);
@@ -211,7 +266,7 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
     tile_m = band * kBand + in_band % h;
     tile_n = in_band / h;
     if (GROUP_K) {
-      row0 = tile_m * BM;
+      row0 = tile_m * kTile;
       row_end = g.M;
       k_begin = g.offsets[e];
       k_end = g.offsets[e + 1];
@@ -231,113 +286,134 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
         n /= 2;
         if (slice >= n) { A0 = g.A1; B0 = g.B1; }
       }
-      const int s = slice % n, nk = (g.K + BK - 1) / BK;
-      k_begin = s * nk / n * BK;
-      k_end = min((s + 1) * nk / n * BK, g.K);
+      const int s = slice % n, nk = (g.K + kTileK - 1) / kTileK;
+      k_begin = s * nk / n * kTileK;
+      k_end = min((s + 1) * nk / n * kTileK, g.K);
     }
     if (!GROUP_K) { B0 += e * g.strideB_e; if (B1) B1 += e * g.strideB_e; }
 
-    Operand<A_KC, BM, A_PITCH, NA, A_GATHER> a;
-    Operand<B_KC, BN, B_PITCH, NB, B_GATHER> b;
-    if constexpr (A_KC) a.rows(A0 + k_begin, row0, row_end, g.lda, g);
-    else a.cols(g.A0, nullptr, row0, g.M, g.lda, k_begin);
-    if constexpr (B_KC) b.rows(B0 + k_begin, col0, g.N, g.ldb, g);
-    else b.cols(B0, B1, col0, g.N, g.ldb, k_begin);
+    Operand<A_KC, A_GATHER, false, 0> a;
+    Operand<B_KC, B_GATHER, DUAL, 2> b;
+    if constexpr (A_KC) a.rows(A0 + k_begin, row0, row_end, g.lda, wave, lane, g);
+    else a.cols(g.A0, nullptr, row0, g.M, g.lda, k_begin, wave, lane);
+    if constexpr (B_KC) b.rows(B0 + k_begin, col0, g.N, g.ldb, wave, lane, g);
+    else b.cols(B0, B1, col0, g.N, g.ldb, k_begin, wave, lane);
 
-    const int nk1 = (k_end - k_begin + BK - 1) / BK, nk = two_passes ? 2 * nk1 : nk1;
+    const int n_k1 = k_end - k_begin, nk1 = (n_k1 + kTileK - 1) / kTileK, nk = two_passes ? 2 * nk1 : nk1;
+    const int k_tail = n_k1 - (nk1 - 1) * kTileK;        // k that exist in the last k tile of a pass
+    constexpr bool LOOK_UP = GROUP_K;
     auto look_up = [&](int kt) {
-      if constexpr (!A_KC && A_GATHER) a.look_up(g, k_begin + kt * BK, k_end);
-      if constexpr (!B_KC && B_GATHER) b.look_up(g, k_begin + kt * BK, k_end);
+      if constexpr (!A_KC && A_GATHER) a.look_up(g, k_begin + kt * kTileK, k_end, wave);
+      if constexpr (!B_KC && B_GATHER) b.look_up(g, k_begin + kt * kTileK, k_end, wave);
     };
-    auto k_left = [&](int kt) { return k_end - k_begin - (two_passes && kt >= nk1 ? kt - nk1 : kt) * BK; };
-    auto fetch = [&](auto set, int kt) {
-      if (two_passes && kt == nk1) {                 // second K pass
-        a.rows(g.A1, row0, row_end, g.lda, g);
-        b.rows(B1, col0, g.N, g.ldb, g);
+    const uint32_t lds = (uint32_t)(uintptr_t)smem + wave * (PIECE * 4);
+    int next = 0, last = nk1 - 1;                        // the k tile that is copied next; the last one of its pass
+    auto request = [&](int stage, int n_k) {
+      Off oa[2], ob[2];
+      a.offsets(oa, g.lda, n_k, wave, lane, g);
+      b.offsets(ob, g.ldb, n_k, wave, lane, g);
+      copy_to_lds(lds + stage * (STAGE * 4), a.base, b.base, DUAL ? b.base2 : b.base, oa, ob);
+    };
+    auto copy = [&](int stage) {
+      if (next != last) {                                // a branch, so that the rare case costs nothing else
+        request(stage, kTileK);
+      } else {
+        request(stage, k_tail);
+        last = nk - 1;
       }
-      a.template fetch<decltype(set)::value>(g.lda, k_left(kt));
-      b.template fetch<decltype(set)::value>(g.ldb, k_left(kt));
+      ++next;
+      a.advance(g.lda);
+      b.advance(g.ldb);
+      if (MODE == BWD_DX && next == nk1 && two_passes) { // second K pass
+        a.rows(g.A1, row0, row_end, g.lda, wave, lane, g);
+        b.rows(B1, col0, g.N, g.ldb, wave, lane, g);
+      }
     };
 
-    f32x4 acc[TM][TN];
+    f32x4 acc[2][2];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    float* const As = smem;                              // two stages of A, then two of B
-    float* const Bs = smem + 2 * A_SIZE;
-    auto put = [&](auto set, int kt) {
-      a.template put<decltype(set)::value>(As + (kt & 1) * A_SIZE, k_left(kt));
-      b.template put<decltype(set)::value>(Bs + (kt & 1) * B_SIZE, k_left(kt));
-    };
-    const std::integral_constant<int, 0> set0;
-    const std::integral_constant<int, 1> set1;
-    if (nk > 0) {
-      look_up(0);
-      fetch(set0, 0);
-      if (nk > 1) { look_up(1); fetch(set1, 1); }
-      if (nk > 2) look_up(2);
-      put(set0, 0);
-      __syncthreads();
-    }
-    // k tile kt: request tile kt + 2, multiply, put tile kt + 1 into the other stage.  More than three tiles from the end
-    // (MORE) no load is conditional: behind a branch that may have issued loads the compiler can only wait for all of
-    // them, and every k tile waited for the one requested in it (4096 rows, one expert of 512 x 1376: DOWN 65 -> 60 us, DW13 196 -> 167, DW2 157 -> 115).
-    auto step = [&](auto more, auto mine, auto other, int kt) {
-      constexpr bool MORE = decltype(more)::value;
-      if (MORE || kt + 2 < nk) {
-        fetch(mine, kt + 2);
-        if (MORE || kt + 3 < nk) look_up(kt + 3);
+    // k tile kt, in LDS stage `stage`; more: another one follows
+    auto step = [&](auto stage_tag, auto more_tag, int kt) {
+      constexpr int stage = decltype(stage_tag)::value;
+      constexpr bool more = decltype(more_tag)::value;
+      wait_vmcnt<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();                      // k tile kt published; everybody is done with the last one
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) copy(stage ^ 1);
+      const float* T = smem + stage * STAGE;
+      f32x4 af[2][2], bf[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        frags<A_KC, false>(T, wm, s, lane, af[s]);
+        frags<B_KC, DUAL>(T + PIECE / 2, wn, s, lane, bf[s]);
       }
-      const float* At = As + (kt & 1) * A_SIZE;
-      const float* Bt = Bs + (kt & 1) * B_SIZE;
+      if (more && LOOK_UP) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): scalar loads behind the fragments would be waited for with them
+        __builtin_amdgcn_sched_barrier(0);
+        look_up(kt + 2);
+      }
+      // k that do not exist repeat others: zeros instead
+      if (k_tail < kTileK && (!more || (MODE == BWD_DX && two_passes && kt == nk1 - 1))) {
 #pragma unroll
-      for (int s = 0; s < BK / 16; ++s) {
-        f32x4 af[TM], bf[TN];
-        frags<A_KC, A_PITCH, TM>(At, wm * (BM / 2), s, lane, af);
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int h = 0; h < TN / TNH; ++h)
-          frags<B_KC, B_PITCH, TNH>(Bt, h * BNH + wn * (BNH / 2), s, lane, bf + h * TNH);
+          for (int x = 0; x < 4; ++x) {
+            const bool in = 16 * s + 4 * (lane >> 4) + x < k_tail;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              af[s][i][x] = in ? af[s][i][x] : 0.f;
+              bf[s][i][x] = in ? bf[s][i][x] : 0.f;
+            }
+          }
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int x = 0; x < 4; ++x)
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[j][x], af[i][x], acc[i][j], 0, 0, 0);
-      }
-      if (MORE || kt + 1 < nk) put(other, kt + 1);
-      __syncthreads();
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[s][j][x], af[s][i][x], acc[i][j], 0, 0, 0);
     };
-    int kt = 0;
-    for (; kt + 3 < nk; kt += 2) {
-      step(std::true_type{}, set0, set1, kt);
-      step(std::true_type{}, set1, set0, kt + 1);
-    }
-    for (; kt < nk; kt += 2) {
-      step(std::false_type{}, set0, set1, kt);
-      if (kt + 1 < nk) step(std::false_type{}, set1, set0, kt + 1);
+    const std::integral_constant<int, 0> stage0;
+    const std::integral_constant<int, 1> stage1;
+    if (nk > 0) {
+      look_up(0);
+      copy(0);
+      look_up(1);
+      for (int kt = 0;; kt += 2) {
+        if (kt + 1 >= nk) { step(stage0, std::false_type{}, kt); break; }
+        step(stage0, std::true_type{}, kt);
+        if (kt + 2 >= nk) { step(stage1, std::false_type{}, kt + 1); break; }
+        step(stage1, std::true_type{}, kt + 1);
+      }
     }
 
-    const int m_wave = row0 + wm * (BM / 2), n_wave = col0 + wn * (BNH / 2);
+    const int m_wave = row0 + wm * 32, n_wave = col0 + wn * (BNH / 2);
+    constexpr int GROUPS = DUAL ? 1 : 2;                 // of 4 consecutive columns that a lane holds of a row
     float* C = second_product ? g.C1 : g.C0;
     if (GROUP_K) C += e * g.strideC_e;
     if (SLICED && g.slices > 1) C = g.sums + (int64_t)slice * g.R * g.ldc;
-    float dot[TM];
+    float dot[2];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < 2; ++i) {
       const int m = m_wave + out_row(i, lane);
       dot[i] = 0.f;
       const float gate = MODE == BWD_ACT ? g.gates[g.perm_pairs[min(m, row_end - 1)]] : 0.f;
       if (m < row_end) {
 #pragma unroll
-        for (int q = 0; q < TNH; ++q) {
+        for (int q = 0; q < GROUPS; ++q) {
           const int n = n_wave + out_col(q, lane);
           if (n >= g.N) continue;
           const int64_t at = (int64_t)m * g.ldc + n;
           if constexpr (MODE == UP) {
-            const f32x4 h1 = out4(acc[i], q), h3 = out4(acc[i] + TNH, q);
+            const f32x4 h1 = out4(acc[i], 0), h3 = out4(acc[i], 1);
             f32x4 act;
 #pragma unroll
             for (int x = 0; x < 4; ++x) act[x] = silu_f(h1[x]) * h3[x];
@@ -368,30 +444,35 @@ template <int BM, int BN, int BK, int MODE> struct F32Gemm {
       }
     }
     if constexpr (MODE == BWD_ACT) {                     // dg partial of this column tile, summed in a fixed order
-      float* red = smem;                                 // [2][BM]; the operand stages are dead
+      __syncthreads();                                   // everybody is done with the operand stages
+      float* red = smem;                                 // [2][kTile]
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
+      for (int i = 0; i < 2; ++i) {
         float s = dot[i] + __shfl_xor(dot[i], 16, kWave);
         s += __shfl_xor(s, 32, kWave);
-        if (lane < 16) red[wn * BM + wm * (BM / 2) + 16 * i + lane] = s;
+        if (lane < 16) red[wn * kTile + wm * 32 + 16 * i + lane] = s;
       }
       __syncthreads();
-      for (int r = threadIdx.x; r < BM; r += kThreads)
-        if (row0 + r < row_end) g.dg_part[(size_t)(row0 + r) * g.n_part + tile_n] = red[r] + red[BM + r];
+      const int r = threadIdx.x, row = row0 + r;
+      if (r < kTile && row < row_end) {
+        g.dg_part[(size_t)row * g.n_part + tile_n] = red[r] + red[kTile + r];
+        if (g.row_bytes && tile_n == 0) g.row_bytes[row] = (uint32_t)g.token(g.perm[row]) * (uint32_t)(g.lda * 4);
+      }
     }
   }
 };
 
-template <int BM, int BN, int BK, int MODE> __global__ __launch_bounds__(kThreads) void f32_gemm_kernel(FArgs g) {
-  using G = F32Gemm<BM, BN, BK, MODE>;
-  __shared__ __attribute__((aligned(16))) float smem[2 * (G::A_SIZE + G::B_SIZE)];
+template <int MODE, bool WIDE> __global__ __launch_bounds__(kThreads, 5) void f32_gemm_kernel(FArgs g) {
+  using G = F32Gemm<MODE, WIDE>;
+  __shared__ __attribute__((aligned(1024))) float smem[2 * G::STAGE];
   G::run(g, smem);
 }
 
-// 128 x 128 and 128 x 64 tiles of the same form (half the operand traffic per product, half the workgroups) were
-// slower on this library's fp32 shapes: with 4006 rows, d = 512, f = 1376 DOWN 115 / 111 us against 84, DW13 151 / 142
-// against 138 (of the loads then; 123 now).
-constexpr int kTile = 64, kTileK = 32, kMaxSlices = 8;
+// Tried: 128 x 128 and 128 x 64 tiles (half the operand traffic per product, half the workgroups): 4006 rows, d = 512, f = 1376, operands
+// through registers: DOWN 115 / 111 us against 84, DW13 151 / 142 against 138.  64 x 64 per wavefront, the wavefronts taking turns along
+// K, each with stages of its own and no barrier (half the reads from LDS): DOWN 76, DW13 140, and 268 against 249 with long K.  The first two
+// k tiles requested at once: UP 2 % slower, DW13 2 % faster.
+constexpr int kMaxSlices = 8;
 // floats that the slices' sums of a product may take (128 MB): the cut pays while tiles are few, and the scratch has a bound of
 // its own
 constexpr int64_t kMaxSums = (int64_t)1 << 25;
@@ -412,20 +493,23 @@ __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float
 }
 
 // K slices of DOWN and BWD_DX.  Few tiles of many k tiles leave compute units idle, or some with a tile more than others.
-// Measured on 64 x 64 tiles of 32 k: with r tiles on a compute unit a k tile takes about 0.35 us for every four of them and
-// 0.55 us each; the slices' sums pass through memory once more, BWD_DX's in a launch of its own.  (DOWN's are added by the combine where
-// combine_most_slices() allows it; the launch that this saves is charged all the same.)  64 tokens, 8 experts of 512 x 1376, top-2:
-// DOWN 35 -> 17 us, BWD_DX 66 -> 26.  most: see most_slices().
+// Measured on 64 x 64 tiles of 32 k (64 to 2003 tokens, 8 experts of 512 x 1376, 1 to 4 slices): with r tiles on a compute unit a k
+// tile takes 0.5 us for each of them, 0.7 us for a single one, which waits for memory; the slices' sums pass through memory once
+// more, at about 8 TB/s, BWD_DX's in a launch of its own, DOWN's in the combine, to which a cut for less than a seventh is not
+// worth it.  An expert's last row tile is half full on average.  (DOWN + combine, us, without slices / as chosen here: 64 tokens 45 /
+// 22, 512 45 / 29, 1024 57 / 43, 1536 58 / 58; BWD_DX 66 / 25, 66 / 45, 100 / 68, 104 / 90, 2003 tokens 136 / 112.)
 int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
   const int busy = std::max(std::min(E, R), 1);
-  const int64_t tiles = (int64_t)busy * ceil_div(ceil_div(R, busy), kTile) * ceil_div(N, kTile);
+  const double tiles = busy * std::max((double)R / busy / kTile + 0.5, 1.0) * ceil_div(N, kTile);
   const double nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
   int best = 1;
-  double best_us = 0;
+  double best_us = 0, uncut_us = 0;
   for (int n = 1; n <= most; ++n) {
     if (n > 1 && ((two_passes && n % 2) || n > nk / 2 || (int64_t)n * R * N > kMaxSums)) continue;
-    const double r = (double)ceil_div(tiles * n, 256), per_k = 0.35 * std::ceil(r / 4) + 0.55 * r;
-    const double us = per_k * (nk / n + 1) + (n > 1 ? 5.0 + 8e-6 / 4 * n * (double)R * N : 0.0);
+    const double per_k = std::max(0.5 * std::ceil(tiles * n / 256), 0.7);
+    const double us = per_k * (nk / n + 1) + (n > 1 ? (two_passes ? 5.0 : 1.0) + 5e-7 * n * (double)R * N : 0.0);
+    if (n == 1) uncut_us = us;
+    else if (!two_passes && us * 1.15 > uncut_us) continue;
     if (n == 1 || us < best_us) { best = n; best_us = us; }
   }
   return best;
@@ -446,19 +530,25 @@ int slices_of(const FfShapes& sh, bool two_passes) {
   return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
 }
 
+// Do byte offsets from a tile's first row (gathered: from token 0) need more than 32 bits?  A tile spans 64 rows.
+bool wide_offsets(const FArgs& g, int R) {
+  const int64_t rows = g.perm ? std::max(ceil_div(R, g.k), kTile) : kTile;
+  return rows * std::max(g.lda, g.ldb) >= ((int64_t)1 << 30) - 4096;
+}
+
 // left (may be NULL): in, K slices that the caller can add himself; out, those whose sums he finds in g.sums (1: none)
 template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
-  constexpr int BM = kTile, BN = kTile, BK = kTileK;
-  using G = F32Gemm<BM, BN, BK, MODE>;
+  using G = F32Gemm<MODE, false>;
   g.tiles_n = ceil_div(g.N, G::BNH);
-  g.tiles_m = ceil_div(g.M, BM);
+  g.tiles_m = ceil_div(g.M, kTile);
   if (!G::SLICED) g.slices = 1;
   g.R = R;
   const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
-                        (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, BM) + g.E);   // at most this many
+                        (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, kTile) + g.E);   // at most this many
   if (!grid_fits(tiles + 7, kThreads)) return BTX_ERR_UNSUPPORTED;
   const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
-  f32_gemm_kernel<BM, BN, BK, MODE><<<grid, kThreads, 0, s>>>(g);
+  if (wide_offsets(g, R)) f32_gemm_kernel<MODE, true><<<grid, kThreads, 0, s>>>(g);
+  else f32_gemm_kernel<MODE, false><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
   const bool leave = left && g.slices <= *left;
   if (left) *left = leave ? g.slices : 1;
@@ -494,8 +584,9 @@ int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes
 }
 int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
-                float* dg_part, hipStream_t s) {
+                uint32_t* row_bytes, float* dg_part, hipStream_t s) {
   FArgs g{};
+  g.row_bytes = row_bytes;
   g.A0 = (const float*)dys.base; g.gather(dys); g.B0 = (const float*)W2;
   g.C0 = (float*)dh1; g.C1 = (float*)dh3; g.C2 = (float*)ga;
   g.H1 = (const float*)h1; g.H3 = (const float*)h3; g.gates = gates; g.perm_pairs = perm; g.dg_part = dg_part;
@@ -511,16 +602,19 @@ int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3,
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d; g.strideB_e = sh.s13;
   return launch<BWD_DX>(g, sh.R, s);
 }
-int f32_bwd_dw13(const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1,
-                 void* dW3, hipStream_t s) {
+int f32_bwd_dw13(const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes,
+                 void* dW1, void* dW3, hipStream_t s) {
   FArgs g{};
+  g.row_bytes = row_bytes;
   g.A0 = (const float*)xs.base; g.gather(xs); g.B0 = (const float*)dh1; g.B1 = (const float*)dh3;
   g.C0 = (float*)dW1; g.C1 = (float*)dW3;
   g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f; g.strideC_e = sh.s13;
   return launch<DW13>(g, sh.R, s);
 }
-int f32_bwd_dw2(const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, void* dW2, hipStream_t s) {
+int f32_bwd_dw2(const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW2,
+                hipStream_t s) {
   FArgs g{};
+  g.row_bytes = row_bytes;
   g.A0 = (const float*)ga; g.B0 = (const float*)dys.base; g.gather(dys); g.C0 = (float*)dW2;
   g.offsets = off; g.E = sh.E; g.M = sh.f; g.N = sh.d; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideC_e = sh.s2;
   return launch<DW2>(g, sh.R, s);

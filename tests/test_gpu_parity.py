@@ -53,6 +53,34 @@ def test_fp32_products_cut_along_k(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, F32, **kw)
 
 
+def test_fp32_token_rows_past_4_gib():
+    """Token rows whose byte offsets need more than 32 bits: as the same rows give in batches that stay below.  Without a
+    load-balancing loss the tokens do not see each other; the weight gradients add up."""
+    T, d, f, E = (1 << 17) + 104, 1 << 13, 16, 2
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, dY = (torch.randn((T, d), generator=g, device="cuda") for _ in range(2))
+    W1, W3 = (torch.randn((E, d, f), generator=g, device="cuda") / d ** 0.5 for _ in range(2))
+    W2, Wr = torch.randn((E, f, d), generator=g, device="cuda") / f ** 0.5, torch.randn((d, E), generator=g, device="cuda") * 0.02
+
+    def step(x, dY):
+        r = B.btx_moe_route(x, Wr, None, None, 1, B.BTX_ROUTE_SWITCH_TOP1)
+        out, h1, h3 = B.btx_moe_ff_forward(x, W1, W3, W2, r)
+        b = B.btx_moe_ff_backward(dY, x, Wr, W1, W3, W2, r, h1, h3, B.BTX_ROUTE_SWITCH_TOP1)
+        return out, b.dX, [t.double() for t in (b.dW1, b.dW3, b.dW2, b.dW_router)]
+
+    out, dX, sums = step(x, dY)
+    parts = [0.0] * len(sums)
+    for at in range(0, T, T // 4):
+        rows = slice(at, at + T // 4)
+        part_out, part_dX, dW = step(x[rows], dY[rows])
+        # fp32 sums of at most 8192 terms, each in the order of the whole batch; the routing's of any order
+        for got, want in ((out[rows], part_out), (dX[rows], part_dX)):
+            assert float((got - want).norm() / want.norm()) < 1e-6
+        parts = [a + b for a, b in zip(parts, dW)]
+    for got, want in zip(sums, parts):          # 65 thousand terms of random signs, in two orders
+        assert float((got - want).norm() / want.norm()) < TOL[F32] / 4
+
+
 @pytest.mark.parametrize("mode", [B.BTX_ROUTE_SWITCH_TOP1, B.BTX_ROUTE_SAMPLE_TOP1])
 @pytest.mark.parametrize("lb_mode,flags", [(B.BTX_LB_TOKEN_FRAC, 0), (B.BTX_LB_GATE_MEAN, 0),
                                            (B.BTX_LB_GATE_MEAN, B.BTX_FLAG_LB_GRAD_THROUGH_U)])
