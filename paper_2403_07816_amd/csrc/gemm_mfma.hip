@@ -113,6 +113,38 @@ __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_of
                  : "memory");
 }
 
+// N copies of 1 KB by one wavefront, to lds, lds + 1024, ... : the offset of the instruction counts in memory as in LDS, so that
+// all of them share one setting of m0 and one base, and the lanes' offsets make up for it: copy q of bytes at `off` from the
+// operand is given base - kCopyBias and copy_off(off, q).  (A setting of m0 and a base of their own took each copy 8 scalar
+// instructions, which the other wavefront's products wait for.)
+constexpr uint32_t kCopyBias = 4096;
+__device__ __forceinline__ constexpr uint32_t copy_off(uint32_t off, int q) { return off + (kCopyBias - 1024u * q); }
+__device__ __forceinline__ uint64_t uniform64(const void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+#define BTX_COPY(q, reg, flags) "\n\tglobal_load_lds_dwordx4 %" #reg ", %1 offset:" #q flags
+#define BTX_COPIES(flags)                                                                                                           \
+  static_assert(N >= 2 && N <= 4, "copies");                                                                                        \
+  if constexpr (N == 2)                                                                                                             \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" BTX_COPY(0, 2, flags) BTX_COPY(1024, 3, flags)                                       \
+                 : : "s"(lds), "s"(base), "v"(off[0]), "v"(off[1]) : "memory");                                                     \
+  else if constexpr (N == 3)                                                                                                        \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" BTX_COPY(0, 2, flags) BTX_COPY(1024, 3, flags) BTX_COPY(2048, 4, flags)              \
+                 : : "s"(lds), "s"(base), "v"(off[0]), "v"(off[1]), "v"(off[2]) : "memory");                                        \
+  else                                                                                                                              \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" BTX_COPY(0, 2, flags) BTX_COPY(1024, 3, flags) BTX_COPY(2048, 4, flags)              \
+                     BTX_COPY(3072, 5, flags)                                                                                       \
+                 : : "s"(lds), "s"(base), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]) : "memory")
+template <int N, bool STREAM> __device__ __forceinline__ void copies_to_lds(uint64_t base, const uint32_t* off, uint32_t lds) {
+  if constexpr (STREAM) { BTX_COPIES(" sc1 nt"); } else { BTX_COPIES(""); }
+}
+#undef BTX_COPIES
+#undef BTX_COPY
+
 // Epilogue staging band: 32 rows of ROWB bytes in LDS, 16-byte chunks XOR-swizzled by row so
 // that both the piece writes (PIECE bytes per lane, 32 rows at one column) and the
 // row-contiguous 16-byte reads are free of bank conflicts.
@@ -205,22 +237,28 @@ struct Gemm {
   }
 
   // fragment of 16 rows x 32 k: lane l holds row l % 16, k = 32 ks + 8 (l / 16) .. + 7
-  static __device__ __forceinline__ bf16x8 read_kc(const char* tile, int row, int ks, int lane) {
+  static __device__ __forceinline__ uint32_t kc_at(int row, int ks, int lane) {
     const int r = row + (lane & 15);
     const int chunk = 4 * ks + (lane >> 4);
-    return *reinterpret_cast<const bf16x8*>(tile + r * (BK * 2) + ((chunk ^ kc_swz(r)) << 4));
+    return (uint32_t)(r * (BK * 2) + ((chunk ^ kc_swz(r)) << 4));
   }
-  template <int COLS>
-  static __device__ __forceinline__ bf16x8 read_tr(const char* tile, int col, int ks, int lane) {
+  static __device__ __forceinline__ bf16x8 read_kc(const char* tile, int row, int ks, int lane) {
+    return *reinterpret_cast<const bf16x8*>(tile + kc_at(row, ks, lane));
+  }
+  template <int COLS> static __device__ __forceinline__ uint32_t tr_at(int col, int ks, int lane) {
     // a transposing read hands lane 4a+b of a 16-lane group element b of what lanes a, a+4, a+8,
     // a+12 fetched (4 consecutive columns each): lane r fetches k row r/4 at columns 4 (r%4) ..
     const int g = lane >> 4, r = lane & 15;
     const int k = 32 * ks + 8 * g + (r >> 2);
     const int c = col + 4 * (r & 3);
-    const int off = k * (COLS * 2) + ((((c >> 3) ^ tr_swz<COLS>(k)) << 4) | ((c & 7) << 1));
+    return (uint32_t)(k * (COLS * 2) + ((((c >> 3) ^ tr_swz<COLS>(k)) << 4) | ((c & 7) << 1)));
+  }
+  template <int COLS>
+  static __device__ __forceinline__ bf16x8 read_tr(const char* tile, int col, int ks, int lane) {
     typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + off));
-    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + off + 4 * COLS * 2));
+    const char* at = tile + tr_at<COLS>(col, ks, lane);
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)at);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(at + 4 * COLS * 2));
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   }
 
@@ -473,7 +511,6 @@ struct Gemm {
     // strided operand: base = P + k0*ld,         offset = k_in_tile*ld + clamp(col)
     uint32_t a_off[A_LOADS], b_off[B_LOADS];
     int b_k[B_LOADS], b_c[B_LOADS];                               // strided layout: k row / column
-    bool b_second[B_LOADS];
     int a_k[A_LOADS], b_kc[B_LOADS];                              // KC layouts: the chunk's first k inside the tile
 #pragma unroll
     for (int q = 0; q < A_LOADS; ++q) {
@@ -481,30 +518,28 @@ struct Gemm {
       copy_coords<A_KC, BM>(wave * A_LOADS + q, lane, major, minor);
       const int gr = min(row0 + major, row_end - 1);
       // gathered rows: the offset is taken from the first row of A0 (it fits 32 bits, checked on the host)
-      a_off[q] = g.a_perm ? (uint32_t)(g.a_perm[gr] / g.a_k) * (uint32_t)(g.lda * 2) + (uint32_t)(minor * 2)
-                          : (uint32_t)((gr - row0) * g.lda + minor) * 2u;
+      a_off[q] = copy_off(g.a_perm ? (uint32_t)(g.a_perm[gr] / g.a_k) * (uint32_t)(g.lda * 2) + (uint32_t)(minor * 2)
+                                   : (uint32_t)((gr - row0) * g.lda + minor) * 2u, q);
       a_k[q] = minor;
     }
 #pragma unroll
     for (int q = 0; q < B_LOADS; ++q) {
       int major, minor;
-      // DUAL: the B tile is two panels [BK][BNH] back to back, so one wave copy (1 KB) never
-      // straddles W1 and W3 and its base pointer stays uniform
+      // DUAL: the B tile is two panels [BK][BNH] back to back, and half of the wavefronts copy either
       constexpr int SEGS_PER_PANEL = B_BYTES / 1024 / (DUAL ? 2 : 1);
+      static_assert(SEGS_PER_PANEL % B_LOADS == 0, "a wavefront's copies have one base");
       const int seg = wave * B_LOADS + q;
       copy_coords<B_KC, BNH>(seg % SEGS_PER_PANEL, lane, major, minor);
       if (B_KC) {
         // tile rows are output columns (DUAL: BNH of the first panel, then BNH of the second)
-        b_off[q] = (uint32_t)((min(col0 + major, g.N - 1) - col0) * g.ldb + minor) * 2u;
+        b_off[q] = copy_off((uint32_t)((min(col0 + major, g.N - 1) - col0) * g.ldb + minor) * 2u, q);
         b_k[q] = b_c[q] = 0;
-        b_second[q] = DUAL && seg >= SEGS_PER_PANEL;
         b_kc[q] = minor;
       } else {
         b_kc[q] = 0;
         b_k[q] = major;
         b_c[q] = min(col0 + minor, g.N - 8);
-        b_off[q] = (uint32_t)(major * g.ldb + b_c[q]) * 2u;
-        b_second[q] = DUAL && seg >= SEGS_PER_PANEL;     // uniform across the wavefront
+        b_off[q] = copy_off((uint32_t)(major * g.ldb + b_c[q]) * 2u, q);
       }
     }
 
@@ -537,45 +572,52 @@ struct Gemm {
       pass2 = MODE == BWD_DX && kt >= pass2_at;
       return (GROUP_K && kc ? kp_first : (pass2 ? k_first2 : k_first1)) + kt * BK;
     };
-    auto issueA = [&](int kt) {
+    // where this wavefront's copies of tile kt come from and go to
+    auto sourceA = [&](int kt) {
       bool pass2;
       const int k0 = tile_k0(kt, A_KC, pass2);
-      const uint32_t stage = smem_base + (kt % NSA) * A_BYTES;
-      const bf16_t* Ab = pass2 ? g.A1 : g.A0;
-      Ab += (g.a_perm ? (size_t)0 : (size_t)row0 * g.lda) + k0;
+      return uniform64((pass2 ? g.A1 : g.A0) + (g.a_perm ? (size_t)0 : (size_t)row0 * g.lda) + k0) - kCopyBias;
+    };
+    const bool b_second = DUAL && wave >= NW / 2;        // DUAL: whose columns this wavefront copies
+    auto sourceB = [&](int kt) {
+      bool pass2;
+      const int k0 = tile_k0(kt, B_KC, pass2);
+      return uniform64(((MODE == BWD_DX ? pass2 : b_second) ? Bp1 : Bp0) + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb)) - kCopyBias;
+    };
+    const uint32_t ldsA = smem_base + wave * (A_LOADS * 1024), ldsB = smem_base + B_BASE + wave * (B_LOADS * 1024);
+    auto put_a = [&](uint64_t from, const uint32_t* off, uint32_t to) { copies_to_lds<A_LOADS, false>(from, off, to); };
+    auto put_b = [&](uint64_t from, const uint32_t* off, uint32_t to) {
+      if (STREAM_B && read_once) copies_to_lds<B_LOADS, STREAM_B>(from, off, to);
+      else copies_to_lds<B_LOADS, false>(from, off, to);
+    };
+    auto issueA = [&](int kt) {
+      uint32_t off[A_LOADS];
 #pragma unroll
       for (int q = 0; q < A_LOADS; ++q) {
-        uint32_t off = a_off[q];
-        if (is_tail(kt) && a_k[q] >= k_tail) off -= (uint32_t)(a_k[q] * 2);
-        copy16_to_lds(Ab, off, stage + (wave * A_LOADS + q) * 1024);
+        off[q] = a_off[q];
+        if (is_tail(kt) && a_k[q] >= k_tail) off[q] -= (uint32_t)(a_k[q] * 2);
       }
+      put_a(sourceA(kt), off, ldsA + (kt % NSA) * A_BYTES);
     };
     auto issueB = [&](int kt) {
       bool pass2;
       const int k0 = tile_k0(kt, B_KC, pass2);
-      const uint32_t stage = smem_base + B_BASE + (kt % NSB) * B_BYTES;
-      const bf16_t* B0b = Bp0 + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb);
-      const bf16_t* B1b = Bp1 ? Bp1 + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb) : nullptr;
-      auto copy = [&](auto stream) {
+      uint32_t off[B_LOADS];
 #pragma unroll
-        for (int q = 0; q < B_LOADS; ++q) {
-          uint32_t off = b_off[q];
-          // grouped-K, strided operand: a k row past the expert's last grouped row is re-pointed at that last
-          // row.  It meets the zero fill of the transposed operand, so it must hold finite numbers: the
-          // expert's own rows were written by BWD_ACT in this call, whereas the rows behind them belong to
-          // the next expert or, past the last kept row when a capacity limit dropped pairs, to nobody
-          // (workspace bytes nothing has written, possibly NaN patterns).
-          if (GROUP_K && !B_KC) off = (uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u;
-          if (is_tail(kt)) {
-            if (B_KC) { if (b_kc[q] >= k_tail) off -= (uint32_t)(b_kc[q] * 2); }
-            else off = (uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u;
-          }
-          const bool second = MODE == BWD_DX ? pass2 : (DUAL && b_second[q]);
-          copy16_to_lds<decltype(stream)::value>(second ? B1b : B0b, off, stage + (wave * B_LOADS + q) * 1024);
+      for (int q = 0; q < B_LOADS; ++q) {
+        off[q] = b_off[q];
+        // grouped-K, strided operand: a k row past the expert's last grouped row is re-pointed at that last
+        // row.  It meets the zero fill of the transposed operand, so it must hold finite numbers: the
+        // expert's own rows were written by BWD_ACT in this call, whereas the rows behind them belong to
+        // the next expert or, past the last kept row when a capacity limit dropped pairs, to nobody
+        // (workspace bytes nothing has written, possibly NaN patterns).
+        if (GROUP_K && !B_KC) off[q] = copy_off((uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u, q);
+        if (is_tail(kt)) {
+          if (B_KC) { if (b_kc[q] >= k_tail) off[q] -= (uint32_t)(b_kc[q] * 2); }
+          else off[q] = copy_off((uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u, q);
         }
-      };
-      if (STREAM_B && read_once) copy(std::bool_constant<STREAM_B>{});
-      else copy(std::false_type{});
+      }
+      put_b(sourceB(kt), off, ldsB + (kt % NSB) * B_BYTES);
     };
 
     f32x4 acc[TM][TN];
@@ -684,34 +726,116 @@ struct Gemm {
         __builtin_amdgcn_s_barrier();                // tile 0 published
       }
       if (grp == 1 && nk > 0) __builtin_amdgcn_s_barrier();   // idle during group 0's first memory phase
-      // one k tile per trip: unrolled by two (the compiler's choice for some instantiations) the loop ran 2 to
-      // 4 % slower
-#pragma unroll 1
-      for (int kt = 0; kt < nk; ++kt) {
+      // One k tile.  fast: not one of the last of a pass, whose copies and fragments need a look: sources, stages and the lanes' LDS
+      // addresses move on by additions, made while the second half's fragments are on their way.  In front of its copies and
+      // reads a memory phase then issues one setting of m0.  With everything worked out from kt, 90 scalar and vector instructions and
+      // 10 branches per k tile, the phase was as long as the products of the other group (fwd + bwd of 16384 tokens, 4 experts
+      // of 4096 x 11008, top-2: 19.73 ms / 19.01 like this; 32 of 4096 x 1376, top-8: 12.74 / 12.23; one sequence forward 1.79 / 1.72); with
+      // the additions made during the products 19.31, which wait for them.
+      constexpr int NRB = B_KC ? KSTEPS : TNH;       // B_KC: an address for each k step, else one for each column of fragments
+      struct Moving { uint64_t a, b; uint32_t to_a, to_b, at_a, at_b, ra[KSTEPS], rb[NRB]; } mv{};
+      auto read_fast = [&](int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
+        typedef const __attribute__((address_space(3))) bf16x8* ptr8;
+        typedef __attribute__((address_space(3))) bf16x4* ptr4;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) af[i] = *(ptr8)(uintptr_t)(mv.ra[ks] + i * (16 * BK * 2));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if constexpr (B_KC) {
+            bfr[j] = *(ptr8)(uintptr_t)(mv.rb[ks] + ((j / TNH) * BNH + (j % TNH) * 16) * (BK * 2));
+          } else {
+            const uint32_t at = mv.rb[j % TNH] + (j / TNH) * (BK * BNH * 2) + ks * (32 * BNH * 2);
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((ptr4)(uintptr_t)at);
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((ptr4)(uintptr_t)(at + 4 * BNH * 2));
+            bfr[j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          }
+        }
+      };
+      const uint64_t step_b = B_KC ? (uint64_t)(BK * 2) : (uint64_t)g.ldb * (BK * 2);
+      auto start_moving = [&](int kt) {
+        const int ta = kt + (DEEP_B ? 1 : 2), tb = kt + (DEEP_B ? 2 : 1);
+        mv.a = sourceA(ta); mv.b = sourceB(tb);
+        mv.to_a = ldsA + (ta % NSA) * A_BYTES; mv.to_b = ldsB + (tb % NSB) * B_BYTES;
+        mv.at_a = (kt % NSA) * A_BYTES; mv.at_b = (kt % NSB) * B_BYTES;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) mv.ra[ks] = smem_base + mv.at_a + kc_at(wm * (TM * 16), ks, lane);
+#pragma unroll
+        for (int x = 0; x < NRB; ++x)
+          mv.rb[x] = smem_base + B_BASE + mv.at_b + (B_KC ? kc_at(wn * (TNH * 16), x, lane) : tr_at<BNH>(wn * (TNH * 16) + x * 16, 0, lane));
+      };
+      auto move_on = [&]() {
+        auto next = [](uint32_t x, uint32_t first, uint32_t bytes, int n) { return x == first + (n - 1) * bytes ? first : x + bytes; };
+        mv.a += BK * 2;
+        mv.b += step_b;
+        mv.to_a = next(mv.to_a, ldsA, A_BYTES, NSA);
+        mv.to_b = next(mv.to_b, ldsB, B_BYTES, NSB);
+        const uint32_t a = next(mv.at_a, 0, A_BYTES, NSA), b = next(mv.at_b, 0, B_BYTES, NSB);
+#pragma unroll
+        for (int x = 0; x < KSTEPS; ++x) {
+          mv.ra[x] += a - mv.at_a;
+          asm volatile("" : "+v"(mv.ra[x]));         // here, not where it is used
+        }
+#pragma unroll
+        for (int x = 0; x < NRB; ++x) {
+          mv.rb[x] += b - mv.at_b;
+          asm volatile("" : "+v"(mv.rb[x]));
+        }
+        mv.at_a = a;
+        mv.at_b = b;
+      };
+      auto k_tile = [&](auto fast_tag, int kt) {
+        constexpr bool fast = decltype(fast_tag)::value;
+        auto landed = [&]() {
+          if (fast || kt + 2 < nk) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>();
+        };
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          // ---- memory phase
+          // ---- memory phase: copies first, they take longer
+          if constexpr (fast) {
+            if ((h == 0) == DEEP_B) put_a(mv.a, a_off, mv.to_a);
+            else put_b(mv.b, b_off, mv.to_b);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int x = 0; x < HS; ++x) load_frags(kt, h * HS + x, fa[x], fb[x]);
-          if (h == 0 && kt + 1 < nk) issue_near(kt + 1);
-          if (h == 1 && kt + 2 < nk) issue_deep(kt + 2);
+            for (int x = 0; x < HS; ++x) read_fast(h * HS + x, fa[x], fb[x]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (h == 1) move_on();                   // while the reads are on their way
+          } else {
+#pragma unroll
+            for (int x = 0; x < HS; ++x) load_frags(kt, h * HS + x, fa[x], fb[x]);
+            if (h == 0 && kt + 1 < nk) issue_near(kt + 1);
+            if (h == 1 && kt + 2 < nk) issue_deep(kt + 2);
+          }
           __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0): fragments are in registers
-          if ((TAIL == 2 || h == 1) && is_tail(kt)) {   // the part of the last k tile that lies past K
+          if (!fast && (TAIL == 2 || h == 1) && is_tail(kt)) {   // the part of the last k tile that lies past K
 #pragma unroll
             for (int x = 0; x < HS; ++x) zero_past(fa[x], h * HS + x);
           }
-          if (h == 1 && grp == 1) { if (kt + 2 < nk) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>(); }
+          if (h == 1 && grp == 1) landed();
           __builtin_amdgcn_sched_barrier(0);
           __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
           // ---- compute phase
 #pragma unroll
           for (int x = 0; x < HS; ++x) mfma_step(fa[x], fb[x]);
-          if (h == 1 && grp == 0) { if (kt + 2 < nk) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>(); }
+          if (h == 1 && grp == 0) landed();
           __builtin_amdgcn_sched_barrier(0);
-          if (!(grp == 1 && h == 1 && kt + 1 == nk)) __builtin_amdgcn_s_barrier();
+          if (fast || !(grp == 1 && h == 1 && kt + 1 == nk)) __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
         }
+      };
+      for (int kt = 0; kt < nk;) {
+        // the tiles in front of the last two of this pass (three, where the copies of its last one are special)
+        const int pass_end = MODE == BWD_DX && kt < pass2_at && pass2_at < nk ? pass2_at : nk;
+        if (const int stop = pass_end - (TAIL ? 3 : 2); kt < stop) {
+          start_moving(kt);
+          // one k tile per trip: unrolled by two (the compiler's choice for some instantiations) the loop ran 2 to
+          // 4 % slower
+#pragma unroll 1
+          do k_tile(std::true_type{}, kt);
+          while (++kt < stop);
+        }
+#pragma unroll 1
+        for (; kt < pass_end; ++kt) k_tile(std::false_type{}, kt);
       }
     }
 
@@ -1621,7 +1745,7 @@ size_t mfma_forward_split_bytes(const FfShapes& sh) {
 }
 size_t mfma_backward_split_bytes(const FfShapes& sh) { return split_bytes<BWD_DX>(sh.R, sh.E, sh.d, sh.f); }
 
-bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 < ((int64_t)1 << 32); }
+bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 + kCopyBias < ((int64_t)1 << 32); }
 
 int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                    void* h1, void* h3, void* act, void* partial, hipStream_t s) {

@@ -39,6 +39,11 @@ def whole_tile_case(i):
 
 WHOLE_TILE_CASES = 6
 
+# contractions of 1 to 6 k tiles in 256-row tiles, where the main loop gives way to its last k tiles: UP and BWD_ACT (few columns of x),
+# DOWN and both passes of BWD_DX (narrow experts)
+FEW_K_TILES = [((12300, d, 1032, 2, 1, SWITCH), (UP, BWD_ACT)) for d in (64, 72, 128, 160, 192, 248, 256, 384)] + \
+              [((12300, 1032, f, 2, 1, SWITCH), (DOWN, BWD_DX)) for f in (64, 72, 128, 160, 192, 248, 256, 320)]
+
 # weight gradients from transposed rows: more than 8 experts, experts without rows, dropped pairs; dW2 streamed and not
 TRANSPOSED_ROWS = [
     (2200, 264, 2056, 12, 2, dict(cf=0.8, poison=True)), (2200, 320, 2056, 12, 2, dict(cf=0.8, poison=True)),

@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import FEW_K_TILES, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -340,6 +340,12 @@ def test_bf16_random_shapes_of_whole_tiles(case):
     ragged strips of the tile order, every form of the last k tile."""
     T, d, f, E, k = whole_tile_case(case)
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, seed=synth.BASE_SEED + case)
+
+
+@pytest.mark.parametrize("case,products", FEW_K_TILES)
+def test_bf16_few_k_tiles_of_large_row_tiles(case, products):
+    T, d, f, E, k, options = case
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True, **options)
 
 
 @pytest.mark.parametrize("case,paths", LAST_ROUND_CUT)

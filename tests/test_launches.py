@@ -8,7 +8,7 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, HALF, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, FEW_K_TILES, HALF, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -165,6 +165,13 @@ def test_random_shapes_of_whole_tiles_take_that_path(record, case):
     T, d, f, E, k = whole_tile_case(case)
     taken = bf16_products(record, T, d, f, E, k)
     assert all(taken[product][0] == 256 for product in (UP, DOWN, BWD_ACT, BWD_DX)) and taken[BWD_DX][2]
+
+
+@pytest.mark.parametrize("case,products", FEW_K_TILES)
+def test_shapes_of_few_k_tiles_take_large_row_tiles(record, case, products):
+    T, d, f, E, k, _ = case
+    taken = bf16_products(record, T, d, f, E, k)
+    assert all(taken[product][0] == 256 for product in products)
 
 
 @pytest.mark.parametrize("dtype,T,d,threads", [(B.BTX_BF16, 8000, 8192, 1024), (B.BTX_BF16, 8192, 8192, 256), (B.BTX_F32, 4096, 8192, 1024),
