@@ -5,8 +5,9 @@
 //   router_ds       one wavefront per token, lane e = expert e: dg (summed partials of
 //                   <dY, expert output>), gate Jacobian, load-balancing term -> ds[T,E]
 //   dwr_partial     dW_router = x^T ds as per-token-chunk partial sums
+//   dx_finish       dX[t] = sum_j dxs[inv_pos[t,j]] + ds[t] W_router^T, W_router slice kept in registers; in batches that are not
+//                   large one launch with dwr_partial (dx_and_dwr)
 //   dwr_reduce      fixed-order sum of the partials (and of db_router)
-//   dx_finish       dX[t] = sum_j dxs[inv_pos[t,j]] + ds[t] W_router^T, W_router slice kept in registers
 // The rows these kernels stream (x, dxs, dX) are touched once per kernel and go past the caches.
 // dwr_partial and dx_finish work expert-major (partials [chunk][E][d], W_router as [E,d]): a
 // lane's 8 columns of one expert are then 32 contiguous bytes instead of 8 pieces E floats apart.
@@ -24,7 +25,7 @@ __global__ __launch_bounds__(256) void router_ds_kernel(
     const float* __restrict__ noise, float inv_tau,
     const int32_t* __restrict__ topk_idx, const float* __restrict__ gates, const float* __restrict__ probs,
     const int32_t* __restrict__ inv_pos, const float* __restrict__ gate_sum, const float* __restrict__ prob_sum,
-    const int32_t* __restrict__ counts, const float* __restrict__ dg_part, int n_part, float* __restrict__ ds) {
+    const int32_t* __restrict__ counts, const float* __restrict__ dg_part, int n_part, int slots_log2, float* __restrict__ ds) {
   const int lane = threadIdx.x & (kWave - 1);
   const int token_blocks = (T + 3) / 4;
   if ((int)blockIdx.x >= token_blocks) {
@@ -46,12 +47,17 @@ __global__ __launch_bounds__(256) void router_ds_kernel(
   if (lane < k) {
     my_e = topk_idx[(size_t)t * k + lane];
     g = gates[(size_t)t * k + lane];
-    const int r = inv_pos[(size_t)t * k + lane];
-    if (r >= 0) {                            // a dropped pair produced no output: dg = 0
-      const float* part = dg_part + (size_t)r * n_part;
-      for (int p = 0; p < n_part; ++p) dg += part[p];
-    }
   }
+  // its dg: the partial sums of slot j by lanes j, j + slots, ..., so that they are requested together (22 of them one after
+  // another: 8.6 us)
+  const int slots = 1 << slots_log2, j = lane & (slots - 1);
+  const int r = j < k ? inv_pos[(size_t)t * k + j] : -1;
+  if (r >= 0) {                              // a dropped pair produced no output: dg = 0
+    const float* part = dg_part + (size_t)r * n_part;
+    for (int p = lane >> slots_log2; p < n_part; p += kWave >> slots_log2) dg += part[p];
+  }
+  for (int step = slots; step < kWave; step *= 2) dg += __shfl_xor(dg, step, kWave);
+  if (lane >= k) dg = 0.f;
   if (flags & BTX_FLAG_LB_GRAD_THROUGH_U) {
     const float pb = __shfl(pbar, my_e < 0 ? 0 : my_e, kWave);
     if (lane < k) dg += lam * lbc * pb;
@@ -136,36 +142,37 @@ __global__ __launch_bounds__(256) void dwr_partial_kernel(const XT* __restrict__
   }
 }
 
-// The same sums with the four wavefronts of a workgroup on the same 512 columns and a quarter of the chunk's tokens each,
-// added in wavefront order: four times the rows in flight and four times the workgroups, for batches whose (chunk, column
+// The same sums with the WAVES wavefronts of a workgroup on the same 512 columns and their share of the chunk's tokens each,
+// added in wavefront order: as many times the rows in flight and the workgroups, for batches whose (chunk, column
 // block, expert pass) grid would leave the chip idle (fewer than kFewBlocks: 1501 tokens of 4096 columns, 64 experts 65 ->
 // 27 us; 4001 of 2048, 8 experts 29 -> 12).
 constexpr int kFewBlocks = 512;
-template <typename XT, int KEC, int CHUNK>
-__global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restrict__ x, const float* __restrict__ ds, int T,
-                                                              int d, int E, float* __restrict__ part,
-                                                              float* __restrict__ db_part, float* __restrict__ dWr,
-                                                              float* __restrict__ db) {
-  __shared__ float s_ds[CHUNK][KEC];
-  __shared__ f32x4 s_acc[KEC * 2][kWave];
+template <int KEC, int CHUNK> constexpr int dwr_few_lds_bytes() { return (CHUNK * KEC + KEC * 8 * kWave) * (int)sizeof(float); }
+template <typename XT, int KEC, int CHUNK, int WAVES>
+__device__ __forceinline__ void dwr_partial_few(const XT* __restrict__ x, const float* __restrict__ ds, int T, int d, int E,
+                                                float* __restrict__ part, float* __restrict__ db_part, float* __restrict__ dWr,
+                                                float* __restrict__ db, int chunk, int cols, int pass, float* smem) {
+  float (*s_ds)[KEC] = reinterpret_cast<float (*)[KEC]>(smem);                  // [CHUNK][KEC]
+  f32x4 (*s_acc)[kWave] = reinterpret_cast<f32x4 (*)[kWave]>(smem + CHUNK * KEC);    // [KEC * 2][kWave]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int t0 = blockIdx.x * CHUNK, e0 = blockIdx.z * KEC;
+  const int t0 = chunk * CHUNK, e0 = pass * KEC;
   const int nt = min(CHUNK, T - t0);
-  for (int i = threadIdx.x; i < CHUNK * KEC; i += 256) {
+  for (int i = threadIdx.x; i < CHUNK * KEC; i += WAVES * kWave) {
     const int q = i / KEC, j = i % KEC;
     s_ds[q][j] = (q < nt && e0 + j < E) ? ds[(size_t)(t0 + q) * E + e0 + j] : 0.f;
   }
   __syncthreads();
-  const int c0 = (blockIdx.y * kWave + lane) * kColsPerThread, cc = min(c0, d - kColsPerThread);
+  const int c0 = (cols * kWave + lane) * kColsPerThread, cc = min(c0, d - kColsPerThread);
   float acc[KEC][kColsPerThread] = {};
-  const int quarter = (nt + 15) / 16 * 4;               // of the tokens there are, whole groups of four
-  for (int q = wave * quarter; q < min(nt, (wave + 1) * quarter); q += 4) {     // rows past the end meet the zeros of s_ds
-    float xv[4][8];
+  constexpr int U = WAVES == 4 ? 4 : 2;                 // rows in flight: more do not fit the registers of 16 wavefronts
+  const int share = (nt + 4 * WAVES - 1) / (4 * WAVES) * 4;               // of the tokens there are, whole groups of four
+  for (int q = wave * share; q < min(nt, (wave + 1) * share); q += U) {   // rows past the end meet the zeros of s_ds
+    float xv[U][8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) RowVec<XT, 8>::ld_stream(x + (size_t)min(t0 + q + u, T - 1) * d + cc, xv[u]);
+    for (int u = 0; u < U; ++u) RowVec<XT, 8>::ld_stream(x + (size_t)min(t0 + q + u, T - 1) * d + cc, xv[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int j = 0; j < KEC; ++j) {
         const float w = s_ds[q + u][j];
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
         for (int i = 0; i < 8; ++i) acc[j][i] = fmaf(xv[u][i], w, acc[j][i]);
       }
   }
-  for (int w = 1; w < 4; ++w) {
+  for (int w = 1; w < WAVES; ++w) {
     if (wave == w) {
 #pragma unroll
       for (int j = 0; j < KEC; ++j) {
@@ -185,9 +192,9 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
     if (wave == 0) {
 #pragma unroll
       for (int j = 0; j < KEC; ++j) {
-        const f32x4 a = s_acc[2 * j][lane], b = s_acc[2 * j + 1][lane];
+        const f32x4 u = s_acc[2 * j][lane], v = s_acc[2 * j + 1][lane];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { acc[j][i] += a[i]; acc[j][4 + i] += b[i]; }
+        for (int i = 0; i < 4; ++i) { acc[j][i] += u[i]; acc[j][4 + i] += v[i]; }
       }
     }
     __syncthreads();
@@ -200,17 +207,17 @@ __global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restri
 #pragma unroll
         for (int i = 0; i < 8; ++i) dWr[(size_t)(c0 + i) * E + e0 + j] = acc[j][i];
       } else {
-        RowVec<float, 8>::st(part + ((size_t)blockIdx.x * E + e0 + j) * d + c0, acc[j]);
+        RowVec<float, 8>::st(part + ((size_t)chunk * E + e0 + j) * d + c0, acc[j]);
       }
     }
   }
-  if (blockIdx.y == 0 && threadIdx.x < KEC && e0 + threadIdx.x < E) {
-    float a = 0.f;
-    for (int q = 0; q < nt; ++q) a += s_ds[q][threadIdx.x];
+  if (cols == 0 && threadIdx.x < KEC && e0 + threadIdx.x < E) {
+    float b = 0.f;
+    for (int q = 0; q < nt; ++q) b += s_ds[q][threadIdx.x];
     if (dWr) {
-      if (db) db[e0 + threadIdx.x] = a;
+      if (db) db[e0 + threadIdx.x] = b;
     } else {
-      db_part[(size_t)blockIdx.x * E + e0 + threadIdx.x] = a;
+      db_part[(size_t)chunk * E + e0 + threadIdx.x] = b;
     }
   }
 }
@@ -247,12 +254,11 @@ __global__ __launch_bounds__(64 * kRedGroups) void dwr_reduce_kernel(const float
 // for TOK tokens, 4 of them in flight at a time; its slice of W_router (read from the [E,d]
 // copy, E <= EC) stays in registers, so the kernel streams dxs and dX and little else.
 template <typename XT, int EC, int TOK>
-__global__ __launch_bounds__(256) void dx_finish_kernel(const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos,
-                                                        const float* __restrict__ ds, const float* __restrict__ WrT,
-                                                        int T, int d, int E, int k, XT* __restrict__ dX) {
+__device__ __forceinline__ void dx_finish(const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos, const float* __restrict__ ds,
+                                          const float* __restrict__ WrT, int T, int d, int E, int k, XT* __restrict__ dX, int tokens, int cols) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int c0 = ((blockIdx.y * 4 + wave) * kWave + lane) * 8;
-  const int t0 = blockIdx.x * TOK;
+  const int c0 = ((cols * 4 + wave) * kWave + lane) * 8;
+  const int t0 = tokens * TOK;
   if (c0 >= d) return;                      // no cross-lane traffic below
   float wr[EC][8];
 #pragma unroll
@@ -311,15 +317,13 @@ constexpr int kDxLdsE = 32;                             // 32 experts x 512 colu
 constexpr int kDxCols = kWave * 8;                      // columns of a workgroup: 8 per lane
 constexpr int kDxWaves = 8;
 template <typename XT>
-__global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT* __restrict__ dxs,
-                                                                        const int32_t* __restrict__ inv_pos,
-                                                                        const float* __restrict__ ds,
-                                                                        const float* __restrict__ WrT, int T, int d, int E,
-                                                                        int k, int tok_per_block, XT* __restrict__ dX) {
-  extern __shared__ f32x4 s_wr[];                       // [min(E, kDxLdsE)][2][kWave]
+__device__ __forceinline__ void dx_finish_lds(const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos, const float* __restrict__ ds,
+                                              const float* __restrict__ WrT, int T, int d, int E, int k, int tok_per_block,
+                                              XT* __restrict__ dX, int tokens, int cols, float* smem) {
+  f32x4* const s_wr = reinterpret_cast<f32x4*>(smem);   // [min(E, kDxLdsE)][2][kWave]
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int cb = blockIdx.y * kDxCols, c0 = cb + lane * 8, cc = min(c0, d - 8);
+  const int cb = cols * kDxCols, c0 = cb + lane * 8, cc = min(c0, d - 8);
   auto stage = [&](int e0) {
     for (int i = threadIdx.x; i < min(E - e0, kDxLdsE) * (kDxCols / 4); i += kDxWaves * kWave) {
       const int e = i / (kDxCols / 4), c4 = i % (kDxCols / 4);    // 16-byte piece c4 of expert e0 + e's slice
@@ -330,7 +334,7 @@ __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT
     __syncthreads();
   };
   stage(0);
-  const int t_first = blockIdx.x * tok_per_block, t_end = min(T, t_first + tok_per_block);
+  const int t_first = tokens * tok_per_block, t_end = min(T, t_first + tok_per_block);
   // every wavefront makes every trip (there are barriers below); tokens past the end and columns past d are not stored
   for (int tb = t_first; tb < t_end; tb += kDxWaves * 4) {
     const int t0 = tb + wave * 4;
@@ -377,6 +381,39 @@ __global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(const XT
   }
 }
 
+// Both read ds and nothing of each other: one launch, whose first dx_blocks workgroups finish dX (dx_x of them to a column block) and
+// whose others sum dW_router's partials (chunks x column blocks x expert passes of them; none where a kernel of its own does).
+// In two launches one waited for the other's last workgroups, and small ones for their launch.  The router's whole backward pass,
+// us, two launches / one: 500 tokens of 512, 4 experts 22.4 / 17.7; 100 of 1000, 16 experts 38.4 / 21.2; 300 of 4096, 4 experts 26.8
+// / 17.8; 1501 of 4096, 64 experts 87 / 78; 4001 of 2048, 8 experts 46.9 / 36.2.
+template <typename XT, int EC, int TOK>
+__global__ __launch_bounds__(256) void dx_and_dwr_kernel(
+    const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos, const float* __restrict__ ds, const float* __restrict__ WrT, int T,
+    int d, int E, int k, XT* __restrict__ dX, int dx_blocks, int dx_x, const XT* __restrict__ x, float* __restrict__ part,
+    float* __restrict__ db_part, float* __restrict__ dWr, float* __restrict__ db, int chunks) {
+  __shared__ __attribute__((aligned(16))) float smem[dwr_few_lds_bytes<8, 64>() / sizeof(float)];
+  const int b = blockIdx.x, p = b - dx_blocks;
+  if (b < dx_blocks) dx_finish<XT, EC, TOK>(dxs, inv_pos, ds, WrT, T, d, E, k, dX, b % dx_x, b / dx_x);
+  else dwr_partial_few<XT, 8, 64, 4>(x, ds, T, d, E, part, db_part, dWr, db, p % chunks, p / chunks, 0, smem);
+}
+template <typename XT>
+__global__ __launch_bounds__(kDxWaves* kWave) void dx_finish_lds_kernel(
+    const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos, const float* __restrict__ ds, const float* __restrict__ WrT, int T,
+    int d, int E, int k, int tok_per_block, XT* __restrict__ dX, int dx_x) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  dx_finish_lds<XT>(dxs, inv_pos, ds, WrT, T, d, E, k, tok_per_block, dX, blockIdx.x % dx_x, blockIdx.x / dx_x, lds);
+}
+template <typename XT>
+__global__ __launch_bounds__(kDxWaves* kWave, 4) void dx_and_dwr_lds_kernel(
+    const XT* __restrict__ dxs, const int32_t* __restrict__ inv_pos, const float* __restrict__ ds, const float* __restrict__ WrT, int T,
+    int d, int E, int k, int tok_per_block, XT* __restrict__ dX, int dx_blocks, int dx_x, const XT* __restrict__ x,
+    float* __restrict__ part, float* __restrict__ db_part, float* __restrict__ dWr, float* __restrict__ db, int chunks, int cols) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int b = blockIdx.x, p = b - dx_blocks;
+  if (b < dx_blocks) dx_finish_lds<XT>(dxs, inv_pos, ds, WrT, T, d, E, k, tok_per_block, dX, b % dx_x, b / dx_x, lds);
+  else dwr_partial_few<XT, 8, 128, kDxWaves>(x, ds, T, d, E, part, db_part, dWr, db, p % chunks, p / chunks % cols, p / (chunks * cols), lds);
+}
+
 }  // namespace
 
 // token chunk of the dW_router partial sums: longer chunks for many experts keep the partials
@@ -404,65 +441,62 @@ int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
   float* WrT = reinterpret_cast<float*>(w);
 
   if ((int64_t)a.d * a.E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
+  int slots_log2 = 0;                                   // a power of two of lanes for a token's slots
+  while ((1 << slots_log2) < a.k) ++slots_log2;
   router_ds_kernel<<<ceil_div(a.T, 4) + ceil_div(a.d * a.E, 256), 256, 0, s>>>(
                                                    a.W_router, a.d, WrT, a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
                                                    a.flags, a.noise, a.noise ? 1.f / a.tau : 1.f, a.topk_idx, a.gates,
                                                    a.probs, a.inv_pos, a.gate_sum,
-                                                   a.prob_sum, a.counts, a.dg_part, a.n_part, ds);
+                                                   a.prob_sum, a.counts, a.dg_part, a.n_part, slots_log2, ds);
   BTX_LAUNCH_CHECK();
-  bool reduce = nch > 1;                                // a single chunk's sums need no second kernel
-  auto typed = [&](auto tag) {
+  const int passes = ceil_div(a.E, a.E <= 8 ? 8 : 16);
+  const bool few = (int64_t)nch * ceil_div(a.d, 256 * kColsPerThread) * passes < kFewBlocks;
+  const bool reduce = nch > 1 || !few;                  // a single chunk's sums need no further kernel
+  float *const dWr = reduce ? nullptr : a.dW_router, *const db = reduce ? nullptr : a.db_router;
+  const int few_cols = ceil_div(a.d, kWave * kColsPerThread), dwr_blocks = few ? nch * few_cols * ceil_div(a.E, 8) : 0;
+  auto typed = [&](auto tag) -> int {
     using XT = decltype(tag);
-    const XT* x = static_cast<const XT*>(a.x);
-    const int col_blocks = ceil_div(a.d, 256 * kColsPerThread);
-    const int few_cols = ceil_div(a.d, kWave * kColsPerThread);
-    const bool few = (int64_t)nch * col_blocks * ceil_div(a.E, a.E <= 8 ? 8 : 16) < kFewBlocks;
-    if (!few) reduce = true;
-    float* direct = reduce ? nullptr : a.dW_router;
-    if (a.E <= 8 && few)
-      dwr_partial_few_kernel<XT, 8, 64><<<dim3(nch, few_cols, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp, direct,
-                                                                               a.db_router);
-    else if (few)
-      dwr_partial_few_kernel<XT, 16, 128><<<dim3(nch, few_cols, ceil_div(a.E, 16)), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part,
-                                                                                               dbp, direct, a.db_router);
-    else if (a.E <= 8)
-      dwr_partial_kernel<XT, 8, 64><<<dim3(nch, col_blocks, 1), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
-    else
-      dwr_partial_kernel<XT, 16, 128><<<dim3(nch, col_blocks, ceil_div(a.E, 16)), 256, 0, s>>>(x, ds, a.T, a.d, a.E,
-                                                                                             part, dbp);
+    const XT *const x = static_cast<const XT*>(a.x), *const dxs = static_cast<const XT*>(a.dxs);
+    XT* const dX = static_cast<XT*>(a.dX);
+    if (!few) {
+      const dim3 grid(nch, ceil_div(a.d, 256 * kColsPerThread), passes);
+      if (a.E <= 8) dwr_partial_kernel<XT, 8, 64><<<grid, 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
+      else dwr_partial_kernel<XT, 16, 128><<<grid, 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp);
+      BTX_LAUNCH_CHECK();
+    }
+    if (a.E <= 8) {
+      const int cols = ceil_div(a.d, 4 * kWave * 8);
+      const int tok = ceil_div(a.T, 16) * cols < kFewBlocks ? 4 : 16;     // tokens of a wavefront
+      const int dx_x = ceil_div(a.T, tok);
+      const int64_t blocks = (int64_t)dx_x * cols + dwr_blocks;
+      if (!grid_fits(blocks, 256)) return BTX_ERR_UNSUPPORTED;
+#define BTX_DX_LAUNCH(EC, TOK) dx_and_dwr_kernel<XT, EC, TOK><<<(unsigned)blocks, 256, 0, s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, dX, dx_x * cols, dx_x, x, part, dbp, dWr, db, nch)
+      if (a.E <= 4) { if (tok == 4) BTX_DX_LAUNCH(4, 4); else BTX_DX_LAUNCH(4, 16); }
+      else { if (tok == 4) BTX_DX_LAUNCH(8, 4); else BTX_DX_LAUNCH(8, 16); }
+#undef BTX_DX_LAUNCH
+    } else {
+      // tokens per workgroup, for which the slice is staged once: fewer where the chip would be left idle
+      const int cols = ceil_div(a.d, kDxCols);
+      const int tok = a.E <= kDxLdsE && ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
+      const int dx_x = ceil_div(a.T, tok);
+      const int64_t blocks = (int64_t)dx_x * cols + dwr_blocks;
+      if (!grid_fits(blocks, kDxWaves * kWave)) return BTX_ERR_UNSUPPORTED;
+      const int lds = std::min(a.E, kDxLdsE) * kDxCols * (int)sizeof(float);
+      if (few)
+        dx_and_dwr_lds_kernel<XT><<<(unsigned)blocks, kDxWaves * kWave, std::max(lds, dwr_few_lds_bytes<8, 128>()), s>>>(
+            dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, tok, dX, dx_x * cols, dx_x, x, part, dbp, dWr, db, nch, few_cols);
+      else
+        dx_finish_lds_kernel<XT><<<(unsigned)blocks, kDxWaves * kWave, lds, s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, tok, dX, dx_x);
+    }
+    BTX_LAUNCH_CHECK();
+    return BTX_OK;
   };
-  if (a.dtype == BTX_BF16) typed(bf16_t{});
-  else typed(float{});
-  BTX_LAUNCH_CHECK();
+  if (int rc = a.dtype == BTX_BF16 ? typed(bf16_t{}) : typed(float{})) return rc;
   if (reduce) {
     dwr_reduce_kernel<<<ceil_div(a.d * a.E, 64), 64 * kRedGroups, 0, s>>>(part, dbp, nch, a.d, a.E, a.dW_router,
                                                                          a.db_router);
     BTX_LAUNCH_CHECK();
   }
-  auto dx_launch = [&](auto tag) {
-    using XT = decltype(tag);
-    const XT* dxs = static_cast<const XT*>(a.dxs);
-    XT* dX = static_cast<XT*>(a.dX);
-#define BTX_DX_LAUNCH(EC, TOK)                                                                                       \
-  dx_finish_kernel<XT, EC, TOK><<<dim3(ceil_div(a.T, TOK), ceil_div(a.d, 4 * kWave * 8)), 256, 0, s>>>(dxs, a.inv_pos, \
-                                                                                                      ds, WrT, a.T, a.d, \
-                                                                                                      a.E, a.k, dX)
-    const bool few = ceil_div(a.T, 16) * ceil_div(a.d, 4 * kWave * 8) < kFewBlocks;   // then 4 tokens per wavefront, not 16
-    if (a.E <= 4) { if (few) BTX_DX_LAUNCH(4, 4); else BTX_DX_LAUNCH(4, 16); }
-    else if (a.E <= 8) { if (few) BTX_DX_LAUNCH(8, 4); else BTX_DX_LAUNCH(8, 16); }
-    else {
-      // tokens per workgroup, for which the slice is staged once: fewer where the chip would be left idle
-      const int cols = ceil_div(a.d, kDxCols);
-      const int tok = a.E <= kDxLdsE && ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
-      dx_finish_lds_kernel<XT><<<dim3(ceil_div(a.T, tok), cols), kDxWaves * kWave,
-                                 (size_t)std::min(a.E, kDxLdsE) * kDxCols * sizeof(float), s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k,
-                                                                              tok, dX);
-    }
-#undef BTX_DX_LAUNCH
-  };
-  if (a.dtype == BTX_BF16) dx_launch(bf16_t{});
-  else dx_launch(float{});
-  BTX_LAUNCH_CHECK();
   return BTX_OK;
 }
 

@@ -631,6 +631,14 @@ def test_bf16_expert_without_tokens():
 
 
 # ------------------------------------------------- the sublayer in its block
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,d,E,k", [(3, 72, 8, 3), (64, 520, 4, 2), (65, 2056, 5, 2), (128, 1032, 9, 4), (129, 64, 33, 5), (257, 1544, 64, 2),
+                                     (4100, 136, 24, 12)])
+def test_router_gradients_and_dX_in_one_launch(T, d, E, k, dtype):
+    """One and several chunks of tokens, column blocks that end early, experts that take turns in LDS, more slots than eight."""
+    run_layer_and_check(T, d, 72, E, k, dtype, unit_rms=True, poison=True)
+
+
 @pytest.mark.parametrize("T,d,f,E,k,dtype", [
     (300, 64, 176, 4, 2, F32),          # fp32, ragged last token block
     (77, 2056, 64, 3, 1, F32),          # d not a multiple of the 2048-column thread stride, E < 4
