@@ -291,14 +291,18 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
 // dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When
 // ff_dw_direct() holds, xs and dys are token rows read through perm and ga is [R,f]; otherwise they are passed in the
 // transposed, padded form with pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
-// does).  ff_dw_transposed(): problems of this dtype may take that form.
+// does).  ff_dw_transposed(): problems of this dtype may take that form.  bf16; fp32: launch_bwd_dx_dw() does these two and
+// launch_bwd_dx() at once, always direct.
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
-int launch_bwd_dw13(int dtype, int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
+int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
                     const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);
-int launch_bwd_dw2(int dtype, int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
+int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
                    const FfShapes& sh, uint32_t* row_bytes, void* dW2, hipStream_t s);
+int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
+                     const void* W3, const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* partial,
+                     void* dW1, void* dW3, void* dW2, hipStream_t s);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address

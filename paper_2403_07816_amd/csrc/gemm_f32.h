@@ -10,7 +10,7 @@ int f32_bwd_act_partials(int f);
 // xs / dys: token rows, read through perm.  row_bytes: [R], scratch that f32_bwd_act fills for the weight gradients (NULL: none wanted)
 int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh, void* h1,
                   void* h3, void* act, hipStream_t s);
-// sums: scratch for the sums of K slices, of f32_down_sums_bytes() (f32_bwd_dx_sums_bytes() in f32_bwd_dx); NULL when that is 0
+// sums: scratch for the sums of K slices, of f32_down_sums_bytes() (f32_bwd_dx_sums_bytes() in the backward pass); NULL when that is 0
 size_t f32_down_sums_bytes(const FfShapes& sh);
 size_t f32_bwd_dx_sums_bytes(const FfShapes& sh);
 // slices: see launch_down()
@@ -21,8 +21,8 @@ int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void
                 uint32_t* row_bytes, float* dg_part, hipStream_t s);
 int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
                void* dxs, void* sums, hipStream_t s);
-int f32_bwd_dw13(const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes,
-                 void* dW1, void* dW3, hipStream_t s);
-int f32_bwd_dw2(const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW2,
-                hipStream_t s);
+// the same with the weight gradients
+int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
+                  const void* W3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* sums, void* dW1,
+                  void* dW3, void* dW2, hipStream_t s);
 }  // namespace btx

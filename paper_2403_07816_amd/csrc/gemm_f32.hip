@@ -235,7 +235,8 @@ template <int MODE, bool WIDE> struct F32Gemm {
     return f32x4{acc[0][2 * q], acc[1][2 * q], acc[0][2 * q + 1], acc[1][2 * q + 1]};
   }
 
-  static __device__ void run(const FArgs& g, float* smem) {
+  // block: of the `total` ones of this product
+  static __device__ void run(const FArgs& g, unsigned block, float* smem) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wm = wave >> 1, wn = wave & 1;
@@ -247,8 +248,8 @@ template <int MODE, bool WIDE> struct F32Gemm {
     RowTiles row_tiles(g.offsets, GROUP_K ? 1 : g.E, kTile, lane);
     const int per_row_tile = SLICED ? nx * g.slices : nx;
     const int total = GROUP_K ? g.E * g.tiles_m * nx : row_tiles.count() * per_row_tile;
-    const int share = (total + 7) / 8, id = (int)(blockIdx.x % 8) * share + (int)(blockIdx.x / 8);
-    if ((int)(blockIdx.x / 8) >= share || id >= total) return;
+    const int share = (total + 7) / 8, id = (int)(block % 8) * share + (int)(block / 8);
+    if ((int)(block / 8) >= share || id >= total) return;
     int tile_m, tile_n, n_rows, slice = 0;
     bool second_product = false;
     if (GROUP_K) {
@@ -465,7 +466,21 @@ template <int MODE, bool WIDE> struct F32Gemm {
 template <int MODE, bool WIDE> __global__ __launch_bounds__(kThreads, 5) void f32_gemm_kernel(FArgs g) {
   using G = F32Gemm<MODE, WIDE>;
   __shared__ __attribute__((aligned(1024))) float smem[2 * G::STAGE];
-  G::run(g, smem);
+  G::run(g, blockIdx.x, smem);
+}
+// The input's and the weights' gradients need what BWD_ACT has left and nothing of each other: one launch, first the tiles of BWD_DX,
+// whose contraction is the longest in small batches (last: 279 us for a whole pass of 700 tokens, first 252), then DW13's, then DW2's;
+// each number a multiple of 8, as they are dealt to the XCDs.  A product fills what the one before it leaves idle at its end, and in
+// small batches two launches count.  Whole backward products, us, three launches / one: 256 tokens of 256, f = 688, 4 experts 34 / 23;
+// 100 of 512, f = 1376, 8 experts 67 / 50; 2003 of them 290 / 263.  BWD_DX uncut there would take 249, but its sums would be longer chains, and not
+// those of a pass with frozen experts.
+template <bool WIDE>
+__global__ __launch_bounds__(kThreads, 5) void f32_dx_dw_kernel(FArgs dx, unsigned dx_blocks, FArgs dw13, unsigned dw13_blocks, FArgs dw2) {
+  __shared__ __attribute__((aligned(1024))) float smem[2 * F32Gemm<BWD_DX, WIDE>::STAGE];
+  const unsigned b = blockIdx.x;
+  if (b < dx_blocks) F32Gemm<BWD_DX, WIDE>::run(dx, b, smem);
+  else if (b < dx_blocks + dw13_blocks) F32Gemm<DW13, WIDE>::run(dw13, b - dx_blocks, smem);
+  else F32Gemm<DW2, WIDE>::run(dw2, b - dx_blocks - dw13_blocks, smem);
 }
 
 // Tried: 128 x 128 and 128 x 64 tiles (half the operand traffic per product, half the workgroups): 4006 rows, d = 512, f = 1376, operands
@@ -536,8 +551,8 @@ bool wide_offsets(const FArgs& g, int R) {
   return rows * std::max(g.lda, g.ldb) >= ((int64_t)1 << 30) - 4096;
 }
 
-// left (may be NULL): in, K slices that the caller can add himself; out, those whose sums he finds in g.sums (1: none)
-template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
+// Completes the arguments of a product; its workgroups, 0: more than a launch can hold
+template <int MODE> unsigned blocks_of(FArgs& g, int R) {
   using G = F32Gemm<MODE, false>;
   g.tiles_n = ceil_div(g.N, G::BNH);
   g.tiles_m = ceil_div(g.M, kTile);
@@ -545,19 +560,23 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullpt
   g.R = R;
   const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
                         (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, kTile) + g.E);   // at most this many
-  if (!grid_fits(tiles + 7, kThreads)) return BTX_ERR_UNSUPPORTED;
-  const unsigned grid = (unsigned)align_up((size_t)tiles, 8);
+  return grid_fits(tiles + 7, kThreads) ? (unsigned)align_up((size_t)tiles, 8) : 0;
+}
+int finish_slices(const FArgs& g, int R, hipStream_t s) {
+  f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets, g.E, g.C0);
+  BTX_LAUNCH_CHECK();
+  return BTX_OK;
+}
+// left (may be NULL): in, K slices that the caller can add himself; out, those whose sums he finds in g.sums (1: none)
+template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
+  const unsigned grid = blocks_of<MODE>(g, R);
+  if (grid == 0) return BTX_ERR_UNSUPPORTED;
   if (wide_offsets(g, R)) f32_gemm_kernel<MODE, true><<<grid, kThreads, 0, s>>>(g);
   else f32_gemm_kernel<MODE, false><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
   const bool leave = left && g.slices <= *left;
   if (left) *left = leave ? g.slices : 1;
-  if (g.slices > 1 && !leave) {
-    f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets,
-                                                                                         g.E, g.C0);
-    BTX_LAUNCH_CHECK();
-  }
-  return BTX_OK;
+  return g.slices > 1 && !leave ? finish_slices(g, R, s) : BTX_OK;
 }
 
 }  // namespace
@@ -594,30 +613,43 @@ int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void
   g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f; g.strideB_e = sh.s2;
   return launch<BWD_ACT>(g, sh.R, s);
 }
-int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
-               void* dxs, void* sums, hipStream_t s) {
+namespace {
+FArgs bwd_dx_args(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh, void* dxs,
+                  void* sums) {
   FArgs g{};
   g.slices = slices_of(sh, true); g.sums = (float*)sums;
   g.A0 = (const float*)dh1; g.A1 = (const float*)dh3; g.B0 = (const float*)W1; g.B1 = (const float*)W3; g.C0 = (float*)dxs;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d; g.strideB_e = sh.s13;
-  return launch<BWD_DX>(g, sh.R, s);
+  return g;
 }
-int f32_bwd_dw13(const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes,
-                 void* dW1, void* dW3, hipStream_t s) {
-  FArgs g{};
-  g.row_bytes = row_bytes;
-  g.A0 = (const float*)xs.base; g.gather(xs); g.B0 = (const float*)dh1; g.B1 = (const float*)dh3;
-  g.C0 = (float*)dW1; g.C1 = (float*)dW3;
-  g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f; g.strideC_e = sh.s13;
-  return launch<DW13>(g, sh.R, s);
+}  // namespace
+int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* off, const FfShapes& sh,
+               void* dxs, void* sums, hipStream_t s) {
+  return launch<BWD_DX>(bwd_dx_args(dh1, dh3, W1, W3, off, sh, dxs, sums), sh.R, s);
 }
-int f32_bwd_dw2(const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW2,
-                hipStream_t s) {
-  FArgs g{};
-  g.row_bytes = row_bytes;
-  g.A0 = (const float*)ga; g.B0 = (const float*)dys.base; g.gather(dys); g.C0 = (float*)dW2;
-  g.offsets = off; g.E = sh.E; g.M = sh.f; g.N = sh.d; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideC_e = sh.s2;
-  return launch<DW2>(g, sh.R, s);
+int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
+                  const void* W3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* sums, void* dW1,
+                  void* dW3, void* dW2, hipStream_t s) {
+  FArgs dx = bwd_dx_args(dh1, dh3, W1, W3, off, sh, dxs, sums), dw13{}, dw2{};
+  dw13.row_bytes = dw2.row_bytes = row_bytes;
+  dw13.A0 = (const float*)xs.base; dw13.gather(xs); dw13.B0 = (const float*)dh1; dw13.B1 = (const float*)dh3;
+  dw13.C0 = (float*)dW1; dw13.C1 = (float*)dW3;
+  dw13.offsets = off; dw13.E = sh.E; dw13.M = sh.d; dw13.N = sh.f; dw13.lda = sh.d; dw13.ldb = sh.f; dw13.ldc = sh.f; dw13.strideC_e = sh.s13;
+  dw2.A0 = (const float*)ga; dw2.B0 = (const float*)dys.base; dw2.gather(dys); dw2.C0 = (float*)dW2;
+  dw2.offsets = off; dw2.E = sh.E; dw2.M = sh.f; dw2.N = sh.d; dw2.lda = sh.f; dw2.ldb = sh.d; dw2.ldc = sh.d; dw2.strideC_e = sh.s2;
+  const unsigned n_dx = blocks_of<BWD_DX>(dx, sh.R), n13 = blocks_of<DW13>(dw13, sh.R), n2 = blocks_of<DW2>(dw2, sh.R);
+  if (n_dx == 0 || n13 == 0 || n2 == 0) return BTX_ERR_UNSUPPORTED;
+  if (!grid_fits((int64_t)n_dx + n13 + n2, kThreads)) {
+    if (int rc = launch<BWD_DX>(dx, sh.R, s)) return rc;
+    if (int rc = launch<DW13>(dw13, sh.R, s)) return rc;
+    return launch<DW2>(dw2, sh.R, s);
+  }
+  if (wide_offsets(dx, sh.R) || wide_offsets(dw13, sh.R) || wide_offsets(dw2, sh.R))
+    f32_dx_dw_kernel<true><<<n_dx + n13 + n2, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2);
+  else
+    f32_dx_dw_kernel<false><<<n_dx + n13 + n2, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2);
+  BTX_LAUNCH_CHECK();
+  return dx.slices > 1 ? finish_slices(dx, sh.R, s) : BTX_OK;
 }
 
 }  // namespace btx

@@ -283,6 +283,19 @@ def test_frozen_experts_skip_weight_gradients():
     assert torch.equal(full.dX, frozen.dX) and torch.equal(full.dW_router, frozen.dW_router)
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 8, 8, 4, 1), (65, 72, 136, 3, 2), (64, 512, 1376, 8, 2), (1501, 136, 1032, 5, 2)])
+def test_fp32_gradients_of_frozen_and_trained_experts(T, d, f, E, k):
+    """The products of the backward pass in one launch: few and many tiles of each, cut along K and not; the input's gradients are
+    those of the product alone, the weights' those of the oracle."""
+    run_layer_and_check(T, d, f, E, k, F32, poison=True)
+    L = to_dev(synth.make_layer(T, d, f, E, dtype=F32, with_dY=True))
+    r = B.btx_moe_route(L["x"], L["W_router"], None, None, k)
+    _, h1, h3 = B.btx_moe_ff_forward(L["x"], L["W1"], L["W3"], L["W2"], r)
+    full, frozen = (B.btx_moe_ff_backward(L["dY"], L["x"], L["W_router"], L["W1"], L["W3"], L["W2"], r, h1, h3, frozen_experts=z)
+                    for z in (False, True))
+    assert torch.equal(full.dX, frozen.dX) and torch.equal(full.dW_router, frozen.dW_router)
+
+
 def test_empty_batch_is_a_noop():
     x = torch.empty((0, 64), device="cuda")
     Wr = torch.zeros((64, 4), device="cuda")
