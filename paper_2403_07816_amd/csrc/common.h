@@ -288,18 +288,19 @@ int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* 
 // dxs = dh1 W1^T + dh3 W3^T
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
-// dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When
-// ff_dw_direct() holds, xs and dys are token rows read through perm and ga is [R,f]; otherwise they are passed in the
-// transposed, padded form with pitch ff_dw_pitch() (xs and dys as launch_gather_rows_t writes them, ga as launch_bwd_act
-// does).  ff_dw_transposed(): problems of this dtype may take that form.  bf16; fp32: launch_bwd_dx_dw() does these two and
-// launch_bwd_dx() at once, always direct.
+// dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When ff_dw_direct() holds, xs and dys are token rows read
+// through perm, ga is [R,f], and one launch does all three (bf16) or them and launch_bwd_dx's (fp32, launch_bwd_dx_dw()).  Otherwise
+// (bf16: ff_dw_transposed()) they are passed in the transposed, padded form with pitch ff_dw_pitch() (xs and dys as
+// launch_gather_rows_t writes them, ga as launch_bwd_act does).
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
-int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets,
-                    const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s);
-int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets,
-                   const FfShapes& sh, uint32_t* row_bytes, void* dW2, hipStream_t s);
+int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets, const FfShapes& sh,
+                    void* dW1, void* dW3, hipStream_t s);
+int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets, const FfShapes& sh, void* dW2,
+                   hipStream_t s);
+int launch_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
+                         const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2, hipStream_t s);
 int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
                      const void* W3, const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* partial,
                      void* dW1, void* dW3, void* dW2, hipStream_t s);

@@ -1201,13 +1201,14 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
   static constexpr int kXcdStrips = 32;                   // compute units of an XCD
   static constexpr float kLong = 1.15f;                   // a long expert's tiles cost more than so many average ones
 
-  static __device__ void run(const MArgs& g, char* smem) {
+  // block: of `blocks`, a multiple of 8
+  static __device__ void run(const MArgs& g, unsigned block, unsigned blocks, char* smem) {
     const int lane = threadIdx.x & (kWave - 1);
     const int nx = g.tiles_n * PRODUCTS, xe = min(lane, g.E - 1);
     const int x_cost = kStoreCost + (g.offsets[xe + 1] - g.offsets[xe] + BK - 1) / BK;
     const float costs = wave_sum(lane < g.E ? (float)x_cost : 0.f), all = costs * (float)nx * (float)g.tiles_m;
     const int x_len = min(max((int)(all / ((float)kStrips * (float)x_cost)), 1), g.tiles_m);
-    const int x_strips = lane < g.E ? (g.tiles_m + x_len - 1) / x_len : 0, xcd = blockIdx.x % 8;
+    const int x_strips = lane < g.E ? (g.tiles_m + x_len - 1) / x_len : 0, xcd = block % 8;
     // The strips of long experts, then the others', each dealt to the XCDs in eighths: a long expert's cost products, the others'
     // stores, and an XCD that has one sort only leaves the other half of its means idle (experts in order, top-1 with one favoured
     // expert, backward pass: 1016 of 1600 rows on one of 8 experts of 2048 x 5504 660 us, 434 like this, 516 with tiles; 2282 of 6400
@@ -1224,7 +1225,7 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
     const int incl_rest = wave_incl_scan_i32(x_long && n_long ? 0 : x_strips, lane);
     const int share_long = (n_long + 7) / 8, shares = share_long + (__builtin_amdgcn_readlane(incl_rest, kWave - 1) * nx + 7) / 8;
     bool again = false;
-    for (int pos = blockIdx.x / 8; pos < shares; pos += gridDim.x / 8) {
+    for (int pos = block / 8; pos < shares; pos += blocks / 8) {
       const bool in_long = pos < share_long;
       const int i = in_long ? xcd * share_long + pos : xcd * (shares - share_long) + pos - share_long, incl = in_long ? incl_long : incl_rest;
       const unsigned long long owners = __ballot((int64_t)incl * nx > i);
@@ -1441,9 +1442,15 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
   }
 };
 
-template <int MODE, typename ET, bool STREAM> __global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs g) {
+// Neither product needs anything of the other: one launch, the workgroups of dW1 and dW3 first.  A launch less in small batches, and
+// dW2's stores fill what the others' last strips leave idle.  us, two launches / one, training passes: 64 tokens of 256, f = 688, 4 experts
+// 70.4 / 67.1; 500 of 2056, f = 136, 4 experts 99.8 / 89.8; 600 of 4096, f = 5504, 8 experts 878 / 870; 1501 of 4096, f = 688, 64 experts, top-8
+// 1294 / 1273; 1200 of 2048, f = 344, 64 experts 405 / 406.
+template <typename ET, bool STREAM13, bool STREAM2>
+__global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs dw13, unsigned blocks13, MArgs dw2) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  DwStrip<MODE, ET, STREAM>::run(g, smem);
+  if (blockIdx.x < blocks13) DwStrip<DW13, ET, STREAM13>::run(dw13, blockIdx.x, blocks13, smem);
+  else DwStrip<DW2, ET, STREAM2>::run(dw2, blockIdx.x - blocks13, gridDim.x - blocks13, smem);
 }
 
 // compute units of the current device (looked up once per device)
@@ -1462,7 +1469,7 @@ int compute_units() {
 // The kernels use more dynamic LDS than the default limit allows: the limit is raised once per
 // device and instantiation (idempotent, so a race between threads is harmless).  This must not
 // happen inside a stream capture; mfma_prepare() does it for every instantiation up front.
-template <void (*Kernel)(MArgs), int LDS_BYTES> int raise_lds_limit() {
+template <auto Kernel, int LDS_BYTES> int raise_lds_limit() {
   static bool attr_set[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BTX_ERR_HIP;
@@ -1675,17 +1682,29 @@ template <int MODE> int prepare_rows() {
   return BTX_OK;
 }
 
-template <int MODE, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool prepare_only, hipStream_t s) {
-  using D = DwStrip<MODE, ET, STREAM>;
-  constexpr auto kernel = dw_strip_kernel<MODE, ET, STREAM>;
-  if (int rc = raise_lds_limit<kernel, D::LDS_BYTES>()) return rc;
+template <typename ET, bool STREAM13, bool STREAM2> int launch_dw_strips(MArgs dw13, MArgs dw2, bool prepare_only, hipStream_t s) {
+  using D13 = DwStrip<DW13, ET, STREAM13>;
+  using D2 = DwStrip<DW2, ET, STREAM2>;
+  static_assert(D13::LDS_BYTES == D2::LDS_BYTES);
+  constexpr auto kernel = dw_strip_kernel<ET, STREAM13, STREAM2>;
+  if (int rc = raise_lds_limit<kernel, D2::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
-  g.tiles_n = ceil_div(g.N, D::BN);
-  g.tiles_m = ceil_div(g.M, D::BM);
-  const int64_t tiles = (int64_t)g.E * g.tiles_m * g.tiles_n * D::PRODUCTS;
-  kernel<<<(unsigned)align_up((size_t)std::min<int64_t>(tiles, D::kStrips), 8), 256, D::LDS_BYTES, s>>>(g);
+  auto blocks = [](MArgs& g, auto tag) {
+    using D = decltype(tag);
+    g.tiles_n = ceil_div(g.N, D::BN);
+    g.tiles_m = ceil_div(g.M, D::BM);
+    const int64_t tiles = (int64_t)g.E * g.tiles_m * g.tiles_n * D::PRODUCTS;
+    return (unsigned)align_up((size_t)std::min<int64_t>(tiles, D::kStrips), 8);
+  };
+  const unsigned blocks13 = blocks(dw13, D13{}), blocks2 = blocks(dw2, D2{});
+  kernel<<<blocks13 + blocks2, 256, D2::LDS_BYTES, s>>>(dw13, blocks13, dw2);
   BTX_LAUNCH_CHECK();
   return BTX_OK;
+}
+template <typename ET> int launch_dw_strips(const MArgs& dw13, const MArgs& dw2, bool stream13, bool stream2, bool prepare_only, hipStream_t s) {
+  if (stream13)
+    return stream2 ? launch_dw_strips<ET, true, true>(dw13, dw2, prepare_only, s) : launch_dw_strips<ET, true, false>(dw13, dw2, prepare_only, s);
+  return stream2 ? launch_dw_strips<ET, false, true>(dw13, dw2, prepare_only, s) : launch_dw_strips<ET, false, false>(dw13, dw2, prepare_only, s);
 }
 
 // Weight gradients: strips of few rows per expert (mfma_dw_direct()), 256 x 256 tiles above.
@@ -1693,31 +1712,27 @@ template <int MODE, typename ET, bool STREAM> int launch_dw_strip(MArgs g, bool 
 // 4096 x 1376, 4096 rows 1236 -> 1208.  dW1 and dW3 leave a 256 x 256 tile in halves of lines and keep plain stores; with
 // the two panels side by side, which makes them whole, the transposing reads cost what the stores gain (8192 rows 4346 ->
 // 4450 us, 1000 rows 357 -> 367).
-template <int MODE> int launch_dw(const MArgs& g, bool strip, bool stream, bool prepare_only, hipStream_t s) {
-  constexpr bool KC = MODE == DW2;
-  if (strip && g.c_is_f32)
-    return stream ? launch_dw_strip<MODE, float, true>(g, prepare_only, s) : launch_dw_strip<MODE, float, false>(g, prepare_only, s);
-  if (strip)
-    return stream ? launch_dw_strip<MODE, bf16_t, true>(g, prepare_only, s) : launch_dw_strip<MODE, bf16_t, false>(g, prepare_only, s);
-  if constexpr (KC)
+bool rows_of_lines(const MArgs& g) { return g.N % (g.c_is_f32 ? 32 : 64) == 0; }
+// strips: streamed from half lines on (300 tokens, 64 experts of 4096 x 688, dW2 shifted by 64 bytes: the backward pass 748
+// us with plain stores, 729 streamed), not from any 16-byte piece (761, 862); tiles: streamed anyhow (1501 tokens: 1066, 1054)
+bool stream_strips(const MArgs& g) {
+  return rows_of_lines(g) && ((uintptr_t)g.C0 % 64 | (uintptr_t)g.C1 % 64 | (uintptr_t)(g.strideC_e * (g.c_is_f32 ? 4 : 2)) % 64) == 0;
+}
+template <int MODE> int launch_dw(const MArgs& g, bool stream, bool prepare_only, hipStream_t s) {
+  if constexpr (MODE == DW2)
     if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, true>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, false>(g, prepare_only, s);
 }
-template <int MODE> int launch_dw(const MArgs& g, hipStream_t s) {
-  const bool strip = g.row_bytes != nullptr, rows_of_lines = g.N % (g.c_is_f32 ? 32 : 64) == 0;
-  // strips: streamed from half lines on (300 tokens, 64 experts of 4096 x 688, dW2 shifted by 64 bytes: the backward pass 748
-  // us with plain stores, 729 streamed), not from any 16-byte piece (761, 862); tiles: streamed anyhow (1501 tokens: 1066, 1054)
-  const bool halves = ((uintptr_t)g.C0 % 64 | (uintptr_t)g.C1 % 64 | (uintptr_t)(g.strideC_e * (g.c_is_f32 ? 4 : 2)) % 64) == 0;
-  return launch_dw<MODE>(g, strip, rows_of_lines && (!strip || halves), false, s);
-}
-template <int MODE> int prepare_dw() {
-  MArgs g{};
-  for (int f32 : {0, 1})
-    for (bool strip : {false, true})
-      for (bool stream : {false, true}) {
-        g.c_is_f32 = f32;
-        if (int rc = launch_dw<MODE>(g, strip, stream, true, nullptr)) return rc;
-      }
+int prepare_dw() {
+  const MArgs g{};
+  for (bool stream : {false, true}) {
+    if (int rc = launch_dw<DW13>(g, stream, true, nullptr)) return rc;
+    if (int rc = launch_dw<DW2>(g, stream, true, nullptr)) return rc;
+    for (bool stream2 : {false, true}) {
+      if (int rc = launch_dw_strips<float>(g, g, stream, stream2, true, nullptr)) return rc;
+      if (int rc = launch_dw_strips<bf16_t>(g, g, stream, stream2, true, nullptr)) return rc;
+    }
+  }
   return BTX_OK;
 }
 
@@ -1729,8 +1744,7 @@ int mfma_prepare() {
   if (int rc = prepare_rows<DOWN>()) return rc;
   if (int rc = prepare_rows<BWD_ACT>()) return rc;
   if (int rc = prepare_rows<BWD_DX>()) return rc;
-  if (int rc = prepare_dw<DW13>()) return rc;
-  return prepare_dw<DW2>();
+  return prepare_dw();
 }
 // one dg partial per column tile of BWD_ACT
 int mfma_bwd_act_partials(const FfShapes& sh) {
@@ -1819,25 +1833,39 @@ bool mfma_dw_direct(const FfShapes& sh, int dW_dtype) {
   return rows * sh.f <= (sh.d < 512 ? 700000 : 1300000);
 }
 
-int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off,
-                  const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, hipStream_t s) {
+namespace {
+MArgs dw13_args(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1, void* dW3) {
   MArgs g{};
   g.A0 = (const bf16_t*)xs.base; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
   g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = xs.perm ? sh.d : mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
   g.strideC_e = sh.s13; g.R = sh.R; g.c_is_f32 = dW_dtype == BTX_F32;
-  if (xs.perm) g.row_bytes = row_bytes;
-  return launch_dw<DW13>(g, s);
+  return g;
 }
-
-int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh,
-                 uint32_t* row_bytes, void* dW2, hipStream_t s) {
+MArgs dw2_args(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, void* dW2) {
   MArgs h{};
   h.A0 = (const bf16_t*)ga; h.B0 = (const bf16_t*)dys.base; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
   if (dys.perm) { h.lda = sh.f; h.ldb = sh.d; }
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
-  if (dys.perm) h.row_bytes = row_bytes;
-  return launch_dw<DW2>(h, s);
+  return h;
+}
+}  // namespace
+
+int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1,
+                  void* dW3, hipStream_t s) {
+  const MArgs g = dw13_args(dW_dtype, xs, dh1, dh3, off, sh, dW1, dW3);
+  return launch_dw<DW13>(g, rows_of_lines(g), false, s);
+}
+int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, void* dW2, hipStream_t s) {
+  const MArgs g = dw2_args(dW_dtype, ga, dys, off, sh, dW2);
+  return launch_dw<DW2>(g, rows_of_lines(g), false, s);
+}
+int mfma_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
+                       const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2, hipStream_t s) {
+  MArgs g = dw13_args(dW_dtype, xs, dh1, dh3, off, sh, dW1, dW3), h = dw2_args(dW_dtype, ga, dys, off, sh, dW2);
+  g.row_bytes = h.row_bytes = row_bytes;
+  if (g.c_is_f32) return launch_dw_strips<float>(g, h, stream_strips(g), stream_strips(h), false, s);
+  return launch_dw_strips<bf16_t>(g, h, stream_strips(g), stream_strips(h), false, s);
 }
 
 }  // namespace btx

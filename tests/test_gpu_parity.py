@@ -639,6 +639,13 @@ def test_nothing_depends_on_unwritten_workspace(case):
         run_layer_and_check(300, 128, 256, 4, 2, BF16, dW_dtype=F32, cf=0.7, **kw)
 
 
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 64, 64, 2, 1), (3, 64, 72, 2, 1), (40, 72, 64, 3, 2), (33, 136, 264, 9, 2), (130, 264, 72, 64, 8), (70, 8, 2056, 4, 2)])
+def test_strips_of_all_weight_gradients_in_one_launch(T, d, f, E, k, dW_dtype):
+    """Fewer tiles than XCDs and more, either product's stores past the caches, both and neither."""
+    run_layer_and_check(T, d, f, E, k, BF16, dW_dtype=dW_dtype, poison=True)
+
+
 def test_bf16_expert_without_tokens():
     run_layer_and_check(300, 128, 256, 4, 2, BF16, bias=[0, -60.0, 0, 0], unit_rms=True)
 
