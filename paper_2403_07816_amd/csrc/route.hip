@@ -9,7 +9,8 @@
 //   out for the expert GEMMs and are what the logits are computed from.
 //   0. transpose_wr   W_router [d,E] -> [E,d] in the workspace: a lane then reads its 8 columns of
 //                     an expert as 32 contiguous bytes and a wavefront's load covers 2 KB in one
-//                     piece, where the [d,E] form costs one cache line per lane and load.
+//                     piece, where the [d,E] form costs one cache line per lane and load.  (For the matrix cores
+//                     wr_fragments, the order of their loads.)
 //   1. route_tokens   one wavefront handles a few tokens at a time: fp32 dot
 //                     products of the token row with W_router (lanes split the row,
 //                     butterfly reduction; with more than 8 experts fp32 matrix instructions
@@ -491,7 +492,6 @@ void route_tokens_kernel(
     // and receives the sums of expert lane % 16 for the tokens 4 (lane / 16) + v.
     const int row = lane & 15, kc = lane >> 4;
     const XT* xrow[G];
-    const float* wrow[NS];
     f32x4 acc[G][NS];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -499,15 +499,14 @@ void route_tokens_kernel(
 #pragma unroll
       for (int u = 0; u < NS; ++u) acc[g][u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // the lanes of the experts past E read expert E - 1; their sums are never looked at
-#pragma unroll
-    for (int u = 0; u < NS; ++u) wrow[u] = WrT + (size_t)min(u * 16 + row, E - 1) * d;
+    // experts of a set, and the one of this lane (past E: expert E - 1 again, whose sums are never looked at)
+    auto of_set = [&](int u) { return u + 1 < NS ? 16 : E - 16 * (NS - 1); };
     // Trip `it` of this wavefront covers columns 32 (wave + NW it) ... + 31.  The loads of kAhead trips are
     // in flight ahead of the products, and nothing in the loop is conditional (the matrix instructions
     // take all 64 lanes, and a branch would make the compiler wait for every load): a trip past the
     // last one repeats the last one's loads, and a lane whose 8 columns lie past the row's end reads the
     // row's first 8; both supply zeros for the tokens.
-    constexpr int kAhead = 3;
+    constexpr int kAhead = 2;                           // 3: a trip more than the columns need, 2 to 4 us; 4: as 3
     struct Piece { Raw8<XT> xr[G]; Raw8<float> wr[NS]; };
     Piece buf[kAhead];
     const int n_it = max(0, (d - wave * 32 + NW * 32 - 1) / (NW * 32));
@@ -521,8 +520,15 @@ void route_tokens_kernel(
       const int c0 = col0(it, live);
 #pragma unroll
       for (int g = 0; g < G; ++g) pc.xr[g].load(xrow[g] + c0);
+      const int p0 = (wave + NW * min(it, max(n_it - 1, 0))) * 32, chunks = max(min((d - p0) / 8, 4), 1);   // see wr_fragments_kernel
+      const float* w0 = WrT + (p0 < d ? (size_t)p0 * E : 0);
+      const int c = kc < chunks ? kc : 0, half = chunks * 4 * E;
 #pragma unroll
-      for (int u = 0; u < NS; ++u) pc.wr[u].load(wrow[u] + c0);
+      for (int u = 0; u < NS; ++u) {
+        const float* w = w0 + u * 64 * chunks + (c * of_set(u) + min(row, of_set(u) - 1)) * 4;
+        pc.wr[u].a = *reinterpret_cast<const f32x4*>(w);
+        pc.wr[u].b = *reinterpret_cast<const f32x4*>(w + half);
+      }
     };
     auto multiply = [&](const Piece& pc, int it) {
       bool live;
@@ -800,6 +806,26 @@ __global__ __launch_bounds__(256) void transpose_wr_kernel(const float* __restri
   const int e = i / d, c = i - e * d;
   WrT[i] = Wr[(size_t)c * E + e];
 }
+// W_router [d,E] in the order in which the matrix-core logits take it: 32 columns, of these the first four of every 8 and then the
+// others, 16 experts, 8 columns, expert, column; the last 32 columns and the last 16 experts are what is left.  A wavefront's load
+// is then one piece of 1 KB: from [E,d] it touched 16 lines at 64 places, and those lookups were what the kernel took its time for.
+// Routing as a whole, us, [E,d] / like this: 1501 tokens of 4096 columns, 64 experts 67 / 50; 700 of 512 37 / 30; 2000 of 1024, 16 experts 24.8 /
+// 22.0; 16384 of 4096, 32 experts 95 / 91; 5000 of 1032, 33 experts 48.6 / 50; fp32 4500 of 4096, 64 experts 87 / 78.
+__global__ __launch_bounds__(256) void wr_fragments_kernel(const float* __restrict__ Wr, int d, int E, float* __restrict__ out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= d * E) return;
+  const int p0 = i / (32 * E) * 32, chunks = min((d - p0) / 8, 4);
+  int r = i - p0 * E;
+  const int half = r / (chunks * 4 * E);
+  r -= half * chunks * 4 * E;
+  const int set = r / (64 * chunks), of_set = min(E - 16 * set, 16);
+  r -= set * 64 * chunks;
+  const int chunk = r / (4 * of_set), e = 16 * set + r / 4 % of_set;
+  out[i] = Wr[(size_t)(p0 + 8 * chunk + 4 * half + r % 4) * E + e];
+}
+
+// Logits of more than 8 experts go to the matrix cores, of rows that are as they are.
+bool matrix_logits(const RouteArgs& a) { return a.E > 8 && !a.gain; }
 
 // Wavefronts of a route_tokens workgroup.  4 while the workgroups alone fill the chip (kFewBlocks).  With fewer of them every
 // row's latency shows, and 8 or 16 split the same 16 tokens; but every wavefront reads all of W_router, and that traffic
@@ -811,8 +837,9 @@ __global__ __launch_bounds__(256) void transpose_wr_kernel(const float* __restri
 //   normalising, fp32: 1500 of 4096, 64 experts 152 / 136 / 193; of 512 70 / 56 / 55; of 16384, 8 experts 110 / 105 / 142, 4001
 //   187 / 208 / 270; 4500 of 512, 64 experts 80 / 71 / 83, of 4096 235 / 263 / 392
 // Logits on the matrix cores: 8 wavefronts that share W_router's columns, for one block of tokens instead of kMatrixGroups.
-// 4001 tokens of 4096 columns, 64 experts 87 -> 74 us; past one workgroup on a compute unit 4500 tokens 88 -> 119, and only
-// few experts of few columns gain (4500 of 1024, 16 experts 35 -> 31, of 8192 59 -> 66; 32 of 4096 66 -> 71).
+// 4001 tokens of 4096 columns, 64 experts 67 -> 44 us; past one workgroup on a compute unit few experts of few columns 4500 of 1024, 16
+// experts 30 -> 24, of 2048, 32 experts 38 -> 33.  (Others would gain as well, 4500 of 8192, 16 experts 56 -> 49, 32 of 4096 48 -> 44, 64 of
+// them 66 -> 65, but not while W_router was read as [E,d], and a logit's sum has another order with other wavefronts.)
 constexpr int kFewBlocks = 512, kComputeUnits = 256;
 int token_waves(int nblk, int d, int E, bool f32, bool norm) {
   if (nblk >= kFewBlocks) return kWavesPerBlock;
@@ -847,7 +874,7 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
           x, WrT, a.b_router, a.U, a.T, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx, a.gates, a.probs, bc,  \
           bg, bp, nullptr, 0.f, nullptr, nullptr);                                                                  \
   } while (0)
-  if (a.E > 8 && !a.gain) {
+  if (matrix_logits(a)) {
     // many experts: the dot products go to the matrix cores (fp32 16x16x4, 1024 multiply-adds per
     // instruction).  On the vector unit they took 172 us for 16384 tokens x 32 experts (64 M vector
     // instructions); the kernel now takes 85 us
@@ -879,10 +906,12 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
 
 }  // namespace
 
-// WrT[e][c] = Wr[c][e]
-static int launch_transpose_wr(const float* Wr, int d, int E, float* WrT, hipStream_t s) {
+// WrT: what route_tokens reads, [E,d] or fragments
+static int launch_transpose_wr(const RouteArgs& a, float* WrT, hipStream_t s) {
+  const int d = a.d, E = a.E;
   if ((int64_t)d * E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
-  transpose_wr_kernel<<<ceil_div(d * E, 256), 256, 0, s>>>(Wr, d, E, WrT);
+  if (matrix_logits(a)) wr_fragments_kernel<<<ceil_div(d * E, 256), 256, 0, s>>>(a.W_router, d, E, WrT);
+  else transpose_wr_kernel<<<ceil_div(d * E, 256), 256, 0, s>>>(a.W_router, d, E, WrT);
   BTX_LAUNCH_CHECK();
   return BTX_OK;
 }
@@ -906,7 +935,7 @@ int launch_route(const RouteArgs& a, hipStream_t s) {
   float* bg = reinterpret_cast<float*>(bb + n);
   float* bp = bg + n;
   float* WrT = reinterpret_cast<float*>(static_cast<char*>(a.workspace) + block_stats_bytes(a.T, a.E));
-  if (int rc = launch_transpose_wr(a.W_router, a.d, a.E, WrT, s)) return rc;
+  if (int rc = launch_transpose_wr(a, WrT, s)) return rc;
   if (a.x_dtype == BTX_BF16) launch_tokens<bf16_t>(a, WrT, nblk, bc, bg, bp, s);
   else launch_tokens<float>(a, WrT, nblk, bc, bg, bp, s);
   BTX_LAUNCH_CHECK();

@@ -686,6 +686,14 @@ def test_routing_wavefronts(T, d, E, k, dtype):
     run_layer_and_check(T, d, 64, E, k, dtype, unit_rms=True, backward=False)
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,d,E", [(700, 8, 9), (700, 40, 16), (4203, 48, 17), (700, 56, 31), (4203, 64, 32), (700, 136, 33), (8200, 144, 48), (700, 264, 49),
+                                   (4203, 1032, 63), (700, 1048, 64)])
+def test_routing_reads_every_column_of_every_expert(T, d, E, dtype):
+    """More than 8 experts: W_router in pieces of 32 columns (the last of 8, 16 or 24) and 16 experts (the last of 1, 15 or 16)."""
+    run_layer_and_check(T, d, 8, E, 2, dtype, unit_rms=True, backward=False, poison=True)
+
+
 @pytest.mark.parametrize("case,taken", ROUTE_MANY)
 def test_routing_of_many_tokens(case, taken):
     """Every number of experts in a pass and of wavefronts that share 16 tokens, above the sizes that two launches take."""
