@@ -122,7 +122,9 @@ enum {
   BTX_STAGE_DW13 = 9,         /* backward: dW1, dW3; bf16 without GATHER_X_BWD: and
                                   dW2, DW2 is then empty                            */
   BTX_STAGE_DW2 = 10,         /* backward: dW2                                     */
-  BTX_STAGE_ROUTER_BWD = 11,  /* backward: router gradients and final dX           */
+  BTX_STAGE_ROUTER_BWD = 11,  /* backward: router gradients and final dX (small
+                                  batches: its first part runs beside the weight
+                                  gradients)                                        */
   BTX_STAGE_NORM_BWD = 12,    /* btx_rmsnorm_backward: both kernels                */
   BTX_STAGE_COUNT = 13
 };

@@ -3,6 +3,7 @@
 #include <cmath>
 
 #include "common.h"
+#include "router_ds.h"
 
 using namespace btx;
 
@@ -326,27 +327,30 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   uint32_t* row_bytes = direct && n_dw == 3 ? w.row_bytes : nullptr;   // of weight gradients that read token rows
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));
+  RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,
+                   topk_idx, gates, probs, inv_pos, gate_sum, prob_sum, counts, w.dg_part, bwd_act_partials(dtype, sh), w.dxs, dX,
+                   dW_router, db_router, w.router};
+  const bool ds_rides = n_dw == 3 && direct && router_ds_rides(T, d, E, dtype == BTX_F32);
+  const RouterDs rd = ds_rides ? router_ds_args(ra) : RouterDs{};
+  const RouterDs* const ds = ds_rides ? &rd : nullptr;
   const RowSource dw_x{x, perm, k}, dw_dy{dY, perm, k};
   if (n_dw == 3 && dtype == BTX_F32) {
     BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx_dw(dw_x, dw_dy, w.dh1, w.dh3, w.ga, W1, W3, offsets, sh, row_bytes, w.dxs, w.partial,
-                                                 dW1, dW3, dW2, s));
+                                                 dW1, dW3, dW2, ds, s));
     BTX_STAGE(BTX_STAGE_DW13, BTX_OK);                   // events with nothing between them
     BTX_STAGE(BTX_STAGE_DW2, BTX_OK);
   } else {
     BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx(dtype, w.dh1, w.dh3, W1, W3, offsets, sh, w.dxs, w.partial, s));
   }
   if (n_dw == 3 && dtype == BTX_BF16 && direct) {
-    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw_direct(dW_dtype, dw_x, dw_dy, w.dh1, w.dh3, w.ga, offsets, sh, row_bytes, dW1, dW3, dW2, s));
+    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw_direct(dW_dtype, dw_x, dw_dy, w.dh1, w.dh3, w.ga, offsets, sh, row_bytes, dW1, dW3, dW2, ds, s));
     BTX_STAGE(BTX_STAGE_DW2, BTX_OK);
   } else if (n_dw == 3 && dtype == BTX_BF16) {
     BTX_STAGE(BTX_STAGE_GATHER_X_BWD, launch_gather_rows_t(x, w.xsT, dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
     BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dW_dtype, {w.xsT, nullptr, 1}, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
     BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dW_dtype, w.ga, {w.dysT, nullptr, 1}, offsets, sh, dW2, s));
   }
-  RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,
-                   topk_idx, gates, probs, inv_pos, gate_sum, prob_sum, counts, w.dg_part, bwd_act_partials(dtype, sh), w.dxs, dX,
-                   dW_router, db_router, w.router};
-  BTX_STAGE(BTX_STAGE_ROUTER_BWD, launch_router_bwd(ra, s));
+  BTX_STAGE(BTX_STAGE_ROUTER_BWD, launch_router_bwd(ra, ds_rides, s));
   return BTX_OK;
 }
 

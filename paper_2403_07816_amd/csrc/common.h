@@ -291,7 +291,9 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
 // dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When ff_dw_direct() holds, xs and dys are token rows read
 // through perm, ga is [R,f], and one launch does all three (bf16) or them and launch_bwd_dx's (fp32, launch_bwd_dx_dw()).  Otherwise
 // (bf16: ff_dw_transposed()) they are passed in the transposed, padded form with pitch ff_dw_pitch() (xs and dys as
-// launch_gather_rows_t writes them, ga as launch_bwd_act does).
+// launch_gather_rows_t writes them, ga as launch_bwd_act does).  ds (may be NULL): router_ds() for the direct forms' launch to run beside
+// them.
+struct RouterDs;
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
@@ -300,10 +302,11 @@ int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const vo
 int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets, const FfShapes& sh, void* dW2,
                    hipStream_t s);
 int launch_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
-                         const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2, hipStream_t s);
+                         const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2,
+                         const RouterDs* ds, hipStream_t s);
 int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
                      const void* W3, const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* partial,
-                     void* dW1, void* dW3, void* dW2, hipStream_t s);
+                     void* dW1, void* dW3, void* dW2, const RouterDs* ds, hipStream_t s);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address
@@ -316,7 +319,8 @@ struct RouterBwdArgs {
   const void* dxs; void* dX; float* dW_router; float* db_router; void* workspace;
 };
 size_t router_bwd_workspace_bytes(int T, int d, int E);
-int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s);
+// ds_done: router_ds() has run in another launch
+int launch_router_bwd(const RouterBwdArgs& a, bool ds_done, hipStream_t s);
 
 int launch_mix_experts(const void* W1, const void* W3, const void* W2, int dtype, int N, int d, int f, int mode, int C,
                        void* oW1, void* oW3, void* oW2, hipStream_t s);

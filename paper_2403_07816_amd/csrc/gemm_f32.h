@@ -24,5 +24,5 @@ int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3,
 // the same with the weight gradients
 int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
                   const void* W3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* sums, void* dW1,
-                  void* dW3, void* dW2, hipStream_t s);
+                  void* dW3, void* dW2, const RouterDs* ds, hipStream_t s);
 }  // namespace btx

@@ -27,6 +27,7 @@
 // 153 TFLOP/s this instruction sustains; 4096 rows, one expert of 1024 x 4096: 2598 / 2435, at 124 to 138.  What is left is
 // ragged rounds of 64 x 64 tiles and what starting and storing a tile takes.
 #include "gemm_f32.h"
+#include "router_ds.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -475,12 +476,13 @@ template <int MODE, bool WIDE> __global__ __launch_bounds__(kThreads, 5) void f3
 // 100 of 512, f = 1376, 8 experts 67 / 50; 2003 of them 290 / 263.  BWD_DX uncut there would take 249, but its sums would be longer chains, and not
 // those of a pass with frozen experts.
 template <bool WIDE>
-__global__ __launch_bounds__(kThreads, 5) void f32_dx_dw_kernel(FArgs dx, unsigned dx_blocks, FArgs dw13, unsigned dw13_blocks, FArgs dw2) {
+__global__ __launch_bounds__(kThreads, 5) void f32_dx_dw_kernel(FArgs dx, unsigned dx_blocks, FArgs dw13, unsigned dw13_blocks, FArgs dw2, unsigned dw2_blocks, RouterDs ds) {
   __shared__ __attribute__((aligned(1024))) float smem[2 * F32Gemm<BWD_DX, WIDE>::STAGE];
   const unsigned b = blockIdx.x;
   if (b < dx_blocks) F32Gemm<BWD_DX, WIDE>::run(dx, b, smem);
   else if (b < dx_blocks + dw13_blocks) F32Gemm<DW13, WIDE>::run(dw13, b - dx_blocks, smem);
-  else F32Gemm<DW2, WIDE>::run(dw2, b - dx_blocks - dw13_blocks, smem);
+  else if (b < dx_blocks + dw13_blocks + dw2_blocks) F32Gemm<DW2, WIDE>::run(dw2, b - dx_blocks - dw13_blocks, smem);
+  else router_ds(ds, b - dx_blocks - dw13_blocks - dw2_blocks);
 }
 
 // Tried: 128 x 128 and 128 x 64 tiles (half the operand traffic per product, half the workgroups): 4006 rows, d = 512, f = 1376, operands
@@ -629,7 +631,7 @@ int f32_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3,
 }
 int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
                   const void* W3, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* sums, void* dW1,
-                  void* dW3, void* dW2, hipStream_t s) {
+                  void* dW3, void* dW2, const RouterDs* ds, hipStream_t s) {
   FArgs dx = bwd_dx_args(dh1, dh3, W1, W3, off, sh, dxs, sums), dw13{}, dw2{};
   dw13.row_bytes = dw2.row_bytes = row_bytes;
   dw13.A0 = (const float*)xs.base; dw13.gather(xs); dw13.B0 = (const float*)dh1; dw13.B1 = (const float*)dh3;
@@ -639,15 +641,18 @@ int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, co
   dw2.offsets = off; dw2.E = sh.E; dw2.M = sh.f; dw2.N = sh.d; dw2.lda = sh.f; dw2.ldb = sh.d; dw2.ldc = sh.d; dw2.strideC_e = sh.s2;
   const unsigned n_dx = blocks_of<BWD_DX>(dx, sh.R), n13 = blocks_of<DW13>(dw13, sh.R), n2 = blocks_of<DW2>(dw2, sh.R);
   if (n_dx == 0 || n13 == 0 || n2 == 0) return BTX_ERR_UNSUPPORTED;
-  if (!grid_fits((int64_t)n_dx + n13 + n2, kThreads)) {
+  const RouterDs rd = ds ? *ds : RouterDs{};
+  const unsigned nds = ds ? router_ds_blocks(rd) : 0;
+  if (!grid_fits((int64_t)n_dx + n13 + n2 + nds, kThreads)) {
+    if (ds) return BTX_ERR_UNSUPPORTED;                  // nobody asks for both
     if (int rc = launch<BWD_DX>(dx, sh.R, s)) return rc;
     if (int rc = launch<DW13>(dw13, sh.R, s)) return rc;
     return launch<DW2>(dw2, sh.R, s);
   }
   if (wide_offsets(dx, sh.R) || wide_offsets(dw13, sh.R) || wide_offsets(dw2, sh.R))
-    f32_dx_dw_kernel<true><<<n_dx + n13 + n2, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2);
+    f32_dx_dw_kernel<true><<<n_dx + n13 + n2 + nds, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2, n2, rd);
   else
-    f32_dx_dw_kernel<false><<<n_dx + n13 + n2, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2);
+    f32_dx_dw_kernel<false><<<n_dx + n13 + n2 + nds, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2, n2, rd);
   BTX_LAUNCH_CHECK();
   return dx.slices > 1 ? finish_slices(dx, sh.R, s) : BTX_OK;
 }

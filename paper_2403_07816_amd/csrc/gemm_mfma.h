@@ -35,5 +35,6 @@ int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void
                   void* dW3, hipStream_t s);
 int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, void* dW2, hipStream_t s);
 int mfma_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
-                       const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2, hipStream_t s);
+                       const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2,
+                       const RouterDs* ds, hipStream_t s);
 }  // namespace btx

@@ -34,6 +34,7 @@
 //     up to 8 slices whose fp32 accumulators a second small kernel adds in ascending order and stores
 //     (UP: with the SwiGLU applied to the sums), so that the round fills the chip (Gemm::split_plan).
 #include "gemm_mfma.h"
+#include "router_ds.h"
 #include <cmath>
 #include <type_traits>
 
@@ -1447,10 +1448,11 @@ template <int MODE, typename ET, bool STREAM> struct DwStrip {
 // 70.4 / 67.1; 500 of 2056, f = 136, 4 experts 99.8 / 89.8; 600 of 4096, f = 5504, 8 experts 878 / 870; 1501 of 4096, f = 688, 64 experts, top-8
 // 1294 / 1273; 1200 of 2048, f = 344, 64 experts 405 / 406.
 template <typename ET, bool STREAM13, bool STREAM2>
-__global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs dw13, unsigned blocks13, MArgs dw2) {
+__global__ __launch_bounds__(256, 2) void dw_strip_kernel(MArgs dw13, unsigned blocks13, MArgs dw2, unsigned blocks_ds, RouterDs ds) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if (blockIdx.x < blocks13) DwStrip<DW13, ET, STREAM13>::run(dw13, blockIdx.x, blocks13, smem);
-  else DwStrip<DW2, ET, STREAM2>::run(dw2, blockIdx.x - blocks13, gridDim.x - blocks13, smem);
+  else if (blockIdx.x < blocks13 + blocks_ds) router_ds(ds, blockIdx.x - blocks13);
+  else DwStrip<DW2, ET, STREAM2>::run(dw2, blockIdx.x - blocks13 - blocks_ds, gridDim.x - blocks13 - blocks_ds, smem);
 }
 
 // compute units of the current device (looked up once per device)
@@ -1682,7 +1684,7 @@ template <int MODE> int prepare_rows() {
   return BTX_OK;
 }
 
-template <typename ET, bool STREAM13, bool STREAM2> int launch_dw_strips(MArgs dw13, MArgs dw2, bool prepare_only, hipStream_t s) {
+template <typename ET, bool STREAM13, bool STREAM2> int launch_dw_strips(MArgs dw13, MArgs dw2, const RouterDs* ds, bool prepare_only, hipStream_t s) {
   using D13 = DwStrip<DW13, ET, STREAM13>;
   using D2 = DwStrip<DW2, ET, STREAM2>;
   static_assert(D13::LDS_BYTES == D2::LDS_BYTES);
@@ -1697,14 +1699,15 @@ template <typename ET, bool STREAM13, bool STREAM2> int launch_dw_strips(MArgs d
     return (unsigned)align_up((size_t)std::min<int64_t>(tiles, D::kStrips), 8);
   };
   const unsigned blocks13 = blocks(dw13, D13{}), blocks2 = blocks(dw2, D2{});
-  kernel<<<blocks13 + blocks2, 256, D2::LDS_BYTES, s>>>(dw13, blocks13, dw2);
+  const unsigned blocks_ds = ds ? (unsigned)align_up(router_ds_blocks(*ds), 8) : 0;   // the strips' are dealt to the XCDs
+  kernel<<<blocks13 + blocks_ds + blocks2, 256, D2::LDS_BYTES, s>>>(dw13, blocks13, dw2, blocks_ds, ds ? *ds : RouterDs{});
   BTX_LAUNCH_CHECK();
   return BTX_OK;
 }
-template <typename ET> int launch_dw_strips(const MArgs& dw13, const MArgs& dw2, bool stream13, bool stream2, bool prepare_only, hipStream_t s) {
+template <typename ET> int launch_dw_strips(const MArgs& dw13, const MArgs& dw2, const RouterDs* ds, bool stream13, bool stream2, bool prepare_only, hipStream_t s) {
   if (stream13)
-    return stream2 ? launch_dw_strips<ET, true, true>(dw13, dw2, prepare_only, s) : launch_dw_strips<ET, true, false>(dw13, dw2, prepare_only, s);
-  return stream2 ? launch_dw_strips<ET, false, true>(dw13, dw2, prepare_only, s) : launch_dw_strips<ET, false, false>(dw13, dw2, prepare_only, s);
+    return stream2 ? launch_dw_strips<ET, true, true>(dw13, dw2, ds, prepare_only, s) : launch_dw_strips<ET, true, false>(dw13, dw2, ds, prepare_only, s);
+  return stream2 ? launch_dw_strips<ET, false, true>(dw13, dw2, ds, prepare_only, s) : launch_dw_strips<ET, false, false>(dw13, dw2, ds, prepare_only, s);
 }
 
 // Weight gradients: strips of few rows per expert (mfma_dw_direct()), 256 x 256 tiles above.
@@ -1729,8 +1732,8 @@ int prepare_dw() {
     if (int rc = launch_dw<DW13>(g, stream, true, nullptr)) return rc;
     if (int rc = launch_dw<DW2>(g, stream, true, nullptr)) return rc;
     for (bool stream2 : {false, true}) {
-      if (int rc = launch_dw_strips<float>(g, g, stream, stream2, true, nullptr)) return rc;
-      if (int rc = launch_dw_strips<bf16_t>(g, g, stream, stream2, true, nullptr)) return rc;
+      if (int rc = launch_dw_strips<float>(g, g, nullptr, stream, stream2, true, nullptr)) return rc;
+      if (int rc = launch_dw_strips<bf16_t>(g, g, nullptr, stream, stream2, true, nullptr)) return rc;
     }
   }
   return BTX_OK;
@@ -1861,11 +1864,12 @@ int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32
   return launch_dw<DW2>(g, rows_of_lines(g), false, s);
 }
 int mfma_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
-                       const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2, hipStream_t s) {
+                       const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2,
+                       const RouterDs* ds, hipStream_t s) {
   MArgs g = dw13_args(dW_dtype, xs, dh1, dh3, off, sh, dW1, dW3), h = dw2_args(dW_dtype, ga, dys, off, sh, dW2);
   g.row_bytes = h.row_bytes = row_bytes;
-  if (g.c_is_f32) return launch_dw_strips<float>(g, h, stream_strips(g), stream_strips(h), false, s);
-  return launch_dw_strips<bf16_t>(g, h, stream_strips(g), stream_strips(h), false, s);
+  if (g.c_is_f32) return launch_dw_strips<float>(g, h, ds, stream_strips(g), stream_strips(h), false, s);
+  return launch_dw_strips<bf16_t>(g, h, ds, stream_strips(g), stream_strips(h), false, s);
 }
 
 }  // namespace btx

@@ -3,7 +3,8 @@
 // load-balancing loss of Sec. 3.3).  All reductions run in a fixed order; no atomics.
 //
 //   router_ds       one wavefront per token, lane e = expert e: dg (summed partials of
-//                   <dY, expert output>), gate Jacobian, load-balancing term -> ds[T,E]
+//                   <dY, expert output>), gate Jacobian, load-balancing term -> ds[T,E]; in batches that are not
+//                   large part of the weight gradients' launch (see router_ds_rides())
 //   dwr_partial     dW_router = x^T ds as per-token-chunk partial sums
 //   dx_finish       dX[t] = sum_j dxs[inv_pos[t,j]] + ds[t] W_router^T, W_router slice kept in registers; in batches that are not
 //                   large one launch with dwr_partial (dx_and_dwr)
@@ -12,92 +13,14 @@
 // dwr_partial and dx_finish work expert-major (partials [chunk][E][d], W_router as [E,d]): a
 // lane's 8 columns of one expert are then 32 contiguous bytes instead of 8 pieces E floats apart.
 #include "common.h"
+#include "router_ds.h"
 
 namespace btx {
 namespace {
 
 constexpr int kColsPerThread = 8;
 
-// The workgroups behind the tokens' lay W_router out expert-major for dx_finish (a launch less, 5 us).
-__global__ __launch_bounds__(256) void router_ds_kernel(
-    const float* __restrict__ Wr, int d, float* __restrict__ WrT,
-    int T, int E, int k, int mode, int lb_mode, float lb_alpha, float lam, unsigned flags,
-    const float* __restrict__ noise, float inv_tau,
-    const int32_t* __restrict__ topk_idx, const float* __restrict__ gates, const float* __restrict__ probs,
-    const int32_t* __restrict__ inv_pos, const float* __restrict__ gate_sum, const float* __restrict__ prob_sum,
-    const int32_t* __restrict__ counts, const float* __restrict__ dg_part, int n_part, int slots_log2, float* __restrict__ ds) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int token_blocks = (T + 3) / 4;
-  if ((int)blockIdx.x >= token_blocks) {
-    const int64_t i = (int64_t)((int)blockIdx.x - token_blocks) * 256 + threadIdx.x;
-    if (i < (int64_t)d * E) {
-      const int e = (int)(i / d), c = (int)(i - (int64_t)e * d);
-      WrT[i] = Wr[(size_t)c * E + e];
-    }
-    return;
-  }
-  const int t = blockIdx.x * 4 + threadIdx.x / kWave;
-  if (t >= T) return;
-  const bool live = lane < E;
-  const float lbc = lb_alpha * (float)E / (float)T;
-  const float pbar = live ? prob_sum[lane] / (float)T : 0.f;
-  // lane j < k: slot j of this token
-  int my_e = -1;
-  float g = 0.f, dg = 0.f;
-  if (lane < k) {
-    my_e = topk_idx[(size_t)t * k + lane];
-    g = gates[(size_t)t * k + lane];
-  }
-  // its dg: the partial sums of slot j by lanes j, j + slots, ..., so that they are requested together (22 of them one after
-  // another: 8.6 us)
-  const int slots = 1 << slots_log2, j = lane & (slots - 1);
-  const int r = j < k ? inv_pos[(size_t)t * k + j] : -1;
-  if (r >= 0) {                              // a dropped pair produced no output: dg = 0
-    const float* part = dg_part + (size_t)r * n_part;
-    for (int p = lane >> slots_log2; p < n_part; p += kWave >> slots_log2) dg += part[p];
-  }
-  for (int step = slots; step < kWave; step *= 2) dg += __shfl_xor(dg, step, kWave);
-  if (lane >= k) dg = 0.f;
-  if (flags & BTX_FLAG_LB_GRAD_THROUGH_U) {
-    const float pb = __shfl(pbar, my_e < 0 ? 0 : my_e, kWave);
-    if (lane < k) dg += lam * lbc * pb;
-  }
-  const float p = live ? probs[(size_t)t * E + lane] : 0.f;
-  float dsv = 0.f;
-  if (mode == BTX_ROUTE_TOPK_RENORM) {
-    const float inner = wave_sum(g * dg);  // lanes >= k contribute 0
-    const float mine = g * (dg - inner);
-    for (int j = 0; j < k; ++j) {
-      const int e = __shfl(my_e, j, kWave);
-      const float v = __shfl(mine, j, kWave);
-      if (lane == e) dsv = v;
-    }
-  } else if (mode == BTX_ROUTE_GUMBEL_TOP1) {
-    // gate = y_e, y = softmax((logits + noise) / tau), rebuilt from log p (= logits up to a
-    // constant per token): d gate / d logit_j = y_e (delta_ej - y_j) / tau
-    const int e = __shfl(my_e, 0, kWave);
-    const float dg0 = __shfl(dg, 0, kWave);
-    const float v = live ? (__logf(p) + noise[(size_t)t * E + lane]) * inv_tau : -INFINITY;
-    const float vmax = wave_max(v);
-    const float z = live ? __expf(v - vmax) : 0.f;
-    const float y = z / wave_sum(z);
-    const float ye = __shfl(y, e, kWave);
-    dsv = dg0 * ye * ((lane == e ? 1.f : 0.f) - y) * inv_tau;
-  } else {
-    const int e = __shfl(my_e, 0, kWave);
-    const float dg0 = __shfl(dg, 0, kWave);
-    const float pe = __shfl(p, e, kWave);
-    dsv = dg0 * pe * ((lane == e ? 1.f : 0.f) - p);
-  }
-  if (lam != 0.f) {
-    const float u = !live ? 0.f
-                    : lb_mode == BTX_LB_TOKEN_FRAC ? (float)counts[lane] / ((float)T * (float)k)
-                                                   : gate_sum[lane] / (float)T;
-    const float up = wave_sum(u * p);
-    dsv += lam * lbc * p * (u - up);
-  }
-  if (live) ds[(size_t)t * E + lane] = dsv;
-}
+__global__ __launch_bounds__(256) void router_ds_kernel(RouterDs a) { router_ds(a, blockIdx.x); }
 
 // grid: (token chunks of CHUNK, column blocks of 256*8, expert passes of KEC).  The partial sums
 // are stored expert-major ([chunk][E][d]): a thread's 8 columns of an expert are 32 contiguous bytes.
@@ -429,26 +352,43 @@ size_t router_bwd_workspace_bytes(int T, int d, int E) {
   return ds + part + dbp + wrt;
 }
 
-int launch_router_bwd(const RouterBwdArgs& a, hipStream_t s) {
+namespace {
+struct Parts { float *ds, *part, *dbp, *WrT; };
+Parts parts_of(const RouterBwdArgs& a) {
   const int nch = n_chunks(a.T, a.E);
   char* w = static_cast<char*>(a.workspace);
-  float* ds = reinterpret_cast<float*>(w);
+  Parts p;
+  p.ds = reinterpret_cast<float*>(w);
   w += align_up((size_t)a.T * a.E * sizeof(float), 256);
-  float* part = reinterpret_cast<float*>(w);
+  p.part = reinterpret_cast<float*>(w);
   w += align_up((size_t)nch * a.d * a.E * sizeof(float), 256);
-  float* dbp = reinterpret_cast<float*>(w);
+  p.dbp = reinterpret_cast<float*>(w);
   w += align_up((size_t)nch * a.E * sizeof(float), 256);
-  float* WrT = reinterpret_cast<float*>(w);
+  p.WrT = reinterpret_cast<float*>(w);
+  return p;
+}
+}  // namespace
 
-  if ((int64_t)a.d * a.E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
+RouterDs router_ds_args(const RouterBwdArgs& a) {
+  const Parts p = parts_of(a);
   int slots_log2 = 0;                                   // a power of two of lanes for a token's slots
   while ((1 << slots_log2) < a.k) ++slots_log2;
-  router_ds_kernel<<<ceil_div(a.T, 4) + ceil_div(a.d * a.E, 256), 256, 0, s>>>(
-                                                   a.W_router, a.d, WrT, a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale,
-                                                   a.flags, a.noise, a.noise ? 1.f / a.tau : 1.f, a.topk_idx, a.gates,
-                                                   a.probs, a.inv_pos, a.gate_sum,
-                                                   a.prob_sum, a.counts, a.dg_part, a.n_part, slots_log2, ds);
-  BTX_LAUNCH_CHECK();
+  return RouterDs{a.W_router, a.d, p.WrT, a.T, a.E, a.k, a.route_mode, a.lb_mode, a.lb_alpha, a.lb_grad_scale, a.flags, a.noise,
+                  a.noise ? 1.f / a.tau : 1.f, a.topk_idx, a.gates, a.probs, a.inv_pos, a.gate_sum, a.prob_sum, a.counts, a.dg_part,
+                  a.n_part, slots_log2, p.ds};
+}
+
+int launch_router_bwd(const RouterBwdArgs& a, bool ds_done, hipStream_t s) {
+  const int nch = n_chunks(a.T, a.E);
+  const Parts w = parts_of(a);
+  float *const ds = w.ds, *const part = w.part, *const dbp = w.dbp, *const WrT = w.WrT;
+
+  if ((int64_t)a.d * a.E >= (int64_t)1 << 31) return BTX_ERR_UNSUPPORTED;   // the kernels index W_router with 32 bits
+  if (!ds_done) {
+    const RouterDs rd = router_ds_args(a);
+    router_ds_kernel<<<router_ds_blocks(rd), 256, 0, s>>>(rd);
+    BTX_LAUNCH_CHECK();
+  }
   const int passes = ceil_div(a.E, a.E <= 8 ? 8 : 16);
   const bool few = (int64_t)nch * ceil_div(a.d, 256 * kColsPerThread) * passes < kFewBlocks;
   const bool reduce = nch > 1 || !few;                  // a single chunk's sums need no further kernel

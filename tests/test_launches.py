@@ -104,6 +104,14 @@ def test_shapes_of_transposed_rows_take_that_path(record, case):
     assert rc == 0 and any("gather_rows_t" in launch.kernel for launch in found)
 
 
+@pytest.mark.parametrize("dtype,T,d,E,beside", [(B.BTX_BF16, 64, 256, 4, True), (B.BTX_BF16, 1792, 1024, 16, True), (B.BTX_BF16, 1793, 1024, 16, False),
+                                                (B.BTX_F32, 4864, 2048, 8, True), (B.BTX_F32, 4865, 2048, 8, False)])
+def test_router_gradient_beside_the_weight_gradients(record, dtype, T, d, E, beside):
+    """As long as its workgroups (4 tokens, or 256 weights of the router) are no more than run at a time: 512, fp32 1280."""
+    (rc, found), = record(backward_call(T, d, 64, E, 2, dtype))
+    assert rc == 0 and any("router_ds_kernel" in launch.kernel for launch in found) != beside
+
+
 def test_fp32_products_of_too_many_tiles_are_refused(record):
     """2^24 tiles of 256 threads are more than a launch can hold (137 GB of activations)."""
     (rc, found), = record(forward_call(4_000_000, 64, 8704, 4, 1, B.BTX_F32, save=False))
