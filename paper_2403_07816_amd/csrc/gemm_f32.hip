@@ -644,7 +644,8 @@ int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, co
   const RouterDs rd = ds ? *ds : RouterDs{};
   const unsigned nds = ds ? router_ds_blocks(rd) : 0;
   if (!grid_fits((int64_t)n_dx + n13 + n2 + nds, kThreads)) {
-    if (ds) return BTX_ERR_UNSUPPORTED;                  // nobody asks for both
+    if (ds) f32_dx_dw_kernel<false><<<nds, kThreads, 0, s>>>(dx, 0, dw13, 0, dw2, 0, rd);
+    BTX_LAUNCH_CHECK();
     if (int rc = launch<BWD_DX>(dx, sh.R, s)) return rc;
     if (int rc = launch<DW13>(dw13, sh.R, s)) return rc;
     return launch<DW2>(dw2, sh.R, s);

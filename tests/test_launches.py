@@ -112,6 +112,14 @@ def test_router_gradient_beside_the_weight_gradients(record, dtype, T, d, E, bes
     assert rc == 0 and any("router_ds_kernel" in launch.kernel for launch in found) != beside
 
 
+@pytest.mark.parametrize("f,launches", [(1_000_000, 1), (8_000_000, 4)])
+def test_fp32_backward_products_that_fit_no_launch_together(record, f, launches):
+    """Each of them fits: the router's gradient, dX, dW1 and dW3, dW2."""
+    (rc, found), = record(backward_call(64, 8, f, 64, 2, B.BTX_F32))
+    assert rc == 0 and all(threads_fit(launch) for launch in found)
+    assert sum(launch.kernel.startswith(("f32_dx_dw", "f32_gemm_kernel<3", "f32_gemm_kernel<4", "f32_gemm_kernel<5")) for launch in found) == launches
+
+
 def test_fp32_products_of_too_many_tiles_are_refused(record):
     """2^24 tiles of 256 threads are more than a launch can hold (137 GB of activations)."""
     (rc, found), = record(forward_call(4_000_000, 64, 8704, 4, 1, B.BTX_F32, save=False))
