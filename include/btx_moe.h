@@ -267,7 +267,8 @@ int btx_rmsnorm_backward(const void* dXn, const void* h, const float* gain, cons
  * Limits (BTX_ERR_UNSUPPORTED beyond them; also for btx_moe_ff_backward): the bf16 kernels address the
  * padded grouped rows with 32-bit byte offsets, ceil(R/64)*64 + 64*E < 2^23 (about 8.3 M routed rows);
  * fp32, and bf16 with a d or f that is no multiple of 32 (or below 64), take R/64 + E <= 65535 row tiles
- * (about 4.1 M routed rows).
+ * (about 4.1 M routed rows).  Weight gradients in bf16 address 32 or 64 grouped rows of f elements with 32 bits: f <= 2^25 - 24
+ * (few routed rows: min(R, 32) * f <= 2^31 is enough).
  */
 size_t btx_moe_ff_forward_workspace_bytes(int T, int d, int f, int E, int k, int dtype);
 int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void* W2, int dtype,

@@ -309,6 +309,10 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   if (n_dw != 0 && n_dw != 3) return BTX_ERR_INVALID_ARG;
   if (T == 0) return BTX_OK;
   if (!shapes_supported(dtype, T, d, f, E, k)) return BTX_ERR_UNSUPPORTED;
+  const int R = T * k;
+  const FfShapes sh{R, d, f, E, w13_expert_stride, w2_expert_stride};
+  const bool fused = ff_gather_fused(dtype, T, d), direct = ff_dw_direct(dtype, dW_dtype, sh, fused);
+  if (n_dw == 3 && !ff_dw_supported(dtype, sh, direct)) return BTX_ERR_UNSUPPORTED;
   if (!dY || !x || !W_router || !W1 || !W3 || !W2 || !topk_idx || !gates || !probs || !offsets || !perm || !inv_pos ||
       !gate_sum || !prob_sum || !counts || !save_h1 || !save_h3 || !dX || !dW_router || !workspace)
     return BTX_ERR_INVALID_ARG;
@@ -318,12 +322,8 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const BwdWs w = carve_backward(workspace, T, d, f, E, k, dtype);
   if (workspace_bytes < w.bytes) return BTX_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int R = T * k;
-  const FfShapes sh{R, d, f, E, w13_expert_stride, w2_expert_stride};
-  const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
-  const bool direct = ff_dw_direct(dtype, dW_dtype, sh, fused);
   uint32_t* row_bytes = direct && n_dw == 3 ? w.row_bytes : nullptr;   // of weight gradients that read token rows
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));

@@ -311,6 +311,8 @@ int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1,
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address
 bool ff_rows_supported(int dtype, int R, int d, int f, int E);
+// false when experts are wider than the weight gradients' kernels can address (direct: ff_dw_direct())
+bool ff_dw_supported(int dtype, const FfShapes& sh, bool direct);
 
 struct RouterBwdArgs {
   const void* x; int dtype; const float* W_router; int T, d, E, k, route_mode, lb_mode; float lb_alpha, lb_grad_scale;

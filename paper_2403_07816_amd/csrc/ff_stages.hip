@@ -14,6 +14,8 @@ bool ff_rows_supported(int dtype, int R, int d, int f, int E) {
   return mfma_rows_ok(R, E) && ((d % 32 == 0 && f % 32 == 0 && d >= 64 && f >= 64) || f32_rows_ok(R, E));
 }
 
+bool ff_dw_supported(int dtype, const FfShapes& sh, bool direct) { return dtype != BTX_BF16 || mfma_dw_ok(sh.R, sh.f, direct); }
+
 bool ff_dw_transposed(int dtype) { return dtype == BTX_BF16; }
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused) {
   return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh, dW_dtype));

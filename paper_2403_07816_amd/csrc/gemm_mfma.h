@@ -7,6 +7,8 @@ namespace btx {
 int mfma_prepare();
 // the weight-gradient products address 255 rows of the transposed, padded operands with 32-bit byte offsets
 bool mfma_rows_ok(int R, int E);
+// and the k rows of a k tile of the operands in row order likewise (direct: mfma_dw_direct())
+bool mfma_dw_ok(int R, int f, bool direct);
 int mfma_bwd_act_partials(const FfShapes& sh);
 int mfma_bwd_act_partials_most(int f);
 // gathered A rows need every byte offset inside the source to fit 32 bits

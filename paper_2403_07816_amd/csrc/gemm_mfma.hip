@@ -116,10 +116,11 @@ __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_of
 
 // N copies of 1 KB by one wavefront, to lds, lds + 1024, ... : the offset of the instruction counts in memory as in LDS, so that
 // all of them share one setting of m0 and one base, and the lanes' offsets make up for it: copy q of bytes at `off` from the
-// operand is given base - kCopyBias and copy_off(off, q).  (A setting of m0 and a base of their own took each copy 8 scalar
+// operand is given base - copy_bias(N) and copy_off<N>(off, q).  (A setting of m0 and a base of their own took each copy 8 scalar
 // instructions, which the other wavefront's products wait for.)
-constexpr uint32_t kCopyBias = 4096;
-__device__ __forceinline__ constexpr uint32_t copy_off(uint32_t off, int q) { return off + (kCopyBias - 1024u * q); }
+constexpr uint32_t copy_bias(int n) { return 1024u * (n - 1); }
+constexpr uint32_t kCopyBias = copy_bias(4);             // of the most copies
+template <int N, typename Off> __device__ __forceinline__ constexpr Off copy_off(Off off, int q) { return off + (copy_bias(N) - 1024u * q); }
 __device__ __forceinline__ uint64_t uniform64(const void* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
@@ -145,6 +146,14 @@ template <int N, bool STREAM> __device__ __forceinline__ void copies_to_lds(uint
 }
 #undef BTX_COPIES
 #undef BTX_COPY
+// The same with offsets of 64 bits (wide_offsets())
+template <int N, bool STREAM> __device__ __forceinline__ void copies_to_lds(uint64_t base, const uint64_t* off, uint32_t lds) {
+  static_assert(!STREAM, "copies");
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 : : "s"(lds + 1024u * q), "v"(base + off[q] + 1024u * q) : "memory");
+}
 
 // Epilogue staging band: 32 rows of ROWB bytes in LDS, 16-byte chunks XOR-swizzled by row so
 // that both the piece writes (PIECE bytes per lane, 32 rows at one column) and the
@@ -178,6 +187,8 @@ template <bool STREAM, typename V> __device__ __forceinline__ void store_out(V* 
   else *p = v;
 }
 
+// TAIL: see run(); kWideTail: any K, and operands whose rows lie too far apart for 32-bit offsets inside a tile
+constexpr int kWideTail = 3;
 // STREAM_B: the weights past the caches (stream_weights())
 template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0, bool STREAM_B = false,
           bool STREAM = MODE == BWD_ACT || MODE == DOWN>
@@ -189,6 +200,8 @@ struct Gemm {
   static constexpr bool B_KC = (MODE != UP && MODE != DOWN && MODE != DW13);
   static constexpr bool DUAL = (MODE == UP || MODE == DW13);
   static constexpr bool GROUP_K = (MODE == DW13 || MODE == DW2);
+  typedef std::conditional_t<TAIL == kWideTail, uint64_t, uint32_t> Off;   // bytes from the base of a tile's copies on
+  static_assert(TAIL != kWideTail || (BN == 128 && !STREAM_B), "only small tiles come in this form");
   // 128-column tiles: one pipeline for all wavefronts, two workgroups of four per compute unit; 256: ping-pong
   static constexpr bool SMALL = BN == 128;
   static constexpr int NW = WM * WN, NT = NW * kWave;
@@ -510,7 +523,7 @@ struct Gemm {
     // ---- per-lane byte offsets of the direct copies, relative to a per-tile uniform base --
     // KC operand:      base = P + row0*ld + k0,  offset = (clamp(row) - row0)*ld + k_in_tile
     // strided operand: base = P + k0*ld,         offset = k_in_tile*ld + clamp(col)
-    uint32_t a_off[A_LOADS], b_off[B_LOADS];
+    Off a_off[A_LOADS], b_off[B_LOADS];
     int b_k[B_LOADS], b_c[B_LOADS];                               // strided layout: k row / column
     int a_k[A_LOADS], b_kc[B_LOADS];                              // KC layouts: the chunk's first k inside the tile
 #pragma unroll
@@ -519,8 +532,8 @@ struct Gemm {
       copy_coords<A_KC, BM>(wave * A_LOADS + q, lane, major, minor);
       const int gr = min(row0 + major, row_end - 1);
       // gathered rows: the offset is taken from the first row of A0 (it fits 32 bits, checked on the host)
-      a_off[q] = copy_off(g.a_perm ? (uint32_t)(g.a_perm[gr] / g.a_k) * (uint32_t)(g.lda * 2) + (uint32_t)(minor * 2)
-                                   : (uint32_t)((gr - row0) * g.lda + minor) * 2u, q);
+      a_off[q] = copy_off<A_LOADS>(g.a_perm ? (Off)(g.a_perm[gr] / g.a_k) * ((Off)g.lda * 2u) + (Off)minor * 2u
+                                            : ((Off)(gr - row0) * (Off)g.lda + (Off)minor) * 2u, q);
       a_k[q] = minor;
     }
 #pragma unroll
@@ -533,14 +546,14 @@ struct Gemm {
       copy_coords<B_KC, BNH>(seg % SEGS_PER_PANEL, lane, major, minor);
       if (B_KC) {
         // tile rows are output columns (DUAL: BNH of the first panel, then BNH of the second)
-        b_off[q] = copy_off((uint32_t)((min(col0 + major, g.N - 1) - col0) * g.ldb + minor) * 2u, q);
+        b_off[q] = copy_off<B_LOADS>(((Off)(min(col0 + major, g.N - 1) - col0) * (Off)g.ldb + (Off)minor) * 2u, q);
         b_k[q] = b_c[q] = 0;
         b_kc[q] = minor;
       } else {
         b_kc[q] = 0;
         b_k[q] = major;
         b_c[q] = min(col0 + minor, g.N - 8);
-        b_off[q] = copy_off((uint32_t)(major * g.ldb + b_c[q]) * 2u, q);
+        b_off[q] = copy_off<B_LOADS>(((Off)major * (Off)g.ldb + (Off)b_c[q]) * 2u, q);
       }
     }
 
@@ -577,33 +590,33 @@ struct Gemm {
     auto sourceA = [&](int kt) {
       bool pass2;
       const int k0 = tile_k0(kt, A_KC, pass2);
-      return uniform64((pass2 ? g.A1 : g.A0) + (g.a_perm ? (size_t)0 : (size_t)row0 * g.lda) + k0) - kCopyBias;
+      return uniform64((pass2 ? g.A1 : g.A0) + (g.a_perm ? (size_t)0 : (size_t)row0 * g.lda) + k0) - copy_bias(A_LOADS);
     };
     const bool b_second = DUAL && wave >= NW / 2;        // DUAL: whose columns this wavefront copies
     auto sourceB = [&](int kt) {
       bool pass2;
       const int k0 = tile_k0(kt, B_KC, pass2);
-      return uniform64(((MODE == BWD_DX ? pass2 : b_second) ? Bp1 : Bp0) + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb)) - kCopyBias;
+      return uniform64(((MODE == BWD_DX ? pass2 : b_second) ? Bp1 : Bp0) + (B_KC ? (size_t)col0 * g.ldb + k0 : (size_t)k0 * g.ldb)) - copy_bias(B_LOADS);
     };
     const uint32_t ldsA = smem_base + wave * (A_LOADS * 1024), ldsB = smem_base + B_BASE + wave * (B_LOADS * 1024);
-    auto put_a = [&](uint64_t from, const uint32_t* off, uint32_t to) { copies_to_lds<A_LOADS, false>(from, off, to); };
-    auto put_b = [&](uint64_t from, const uint32_t* off, uint32_t to) {
+    auto put_a = [&](uint64_t from, const Off* off, uint32_t to) { copies_to_lds<A_LOADS, false>(from, off, to); };
+    auto put_b = [&](uint64_t from, const Off* off, uint32_t to) {
       if (STREAM_B && read_once) copies_to_lds<B_LOADS, STREAM_B>(from, off, to);
       else copies_to_lds<B_LOADS, false>(from, off, to);
     };
     auto issueA = [&](int kt) {
-      uint32_t off[A_LOADS];
+      Off off[A_LOADS];
 #pragma unroll
       for (int q = 0; q < A_LOADS; ++q) {
         off[q] = a_off[q];
-        if (is_tail(kt) && a_k[q] >= k_tail) off[q] -= (uint32_t)(a_k[q] * 2);
+        if (is_tail(kt) && a_k[q] >= k_tail) off[q] -= (Off)(a_k[q] * 2);
       }
       put_a(sourceA(kt), off, ldsA + (kt % NSA) * A_BYTES);
     };
     auto issueB = [&](int kt) {
       bool pass2;
       const int k0 = tile_k0(kt, B_KC, pass2);
-      uint32_t off[B_LOADS];
+      Off off[B_LOADS];
 #pragma unroll
       for (int q = 0; q < B_LOADS; ++q) {
         off[q] = b_off[q];
@@ -612,10 +625,10 @@ struct Gemm {
         // expert's own rows were written by BWD_ACT in this call, whereas the rows behind them belong to
         // the next expert or, past the last kept row when a capacity limit dropped pairs, to nobody
         // (workspace bytes nothing has written, possibly NaN patterns).
-        if (GROUP_K && !B_KC) off[q] = copy_off((uint32_t)((min(k0 + b_k[q], k_end - 1) - k0) * g.ldb + b_c[q]) * 2u, q);
+        if (GROUP_K && !B_KC) off[q] = copy_off<B_LOADS>(((Off)(min(k0 + b_k[q], k_end - 1) - k0) * (Off)g.ldb + (Off)b_c[q]) * 2u, q);
         if (is_tail(kt)) {
-          if (B_KC) { if (b_kc[q] >= k_tail) off[q] -= (uint32_t)(b_kc[q] * 2); }
-          else off[q] = copy_off((uint32_t)(min(b_k[q], k_tail - 1) * g.ldb + b_c[q]) * 2u, q);
+          if (B_KC) { if (b_kc[q] >= k_tail) off[q] -= (Off)(b_kc[q] * 2); }
+          else off[q] = copy_off<B_LOADS>(((Off)min(b_k[q], k_tail - 1) * (Off)g.ldb + (Off)b_c[q]) * 2u, q);
         }
       }
       put_b(sourceB(kt), off, ldsB + (kt % NSB) * B_BYTES);
@@ -1611,8 +1624,14 @@ template <int MODE> double tile_us(const MArgs& g, int BM) {
   const int64_t slices = cut && left > 0 ? std::max<int64_t>(std::min<int64_t>({kSplitMaxSlices, kSplitMaxCus / left, nk / 16}), 1) : 1;
   return rounds * (fixed + nk * 1.4) + (left > 0 ? fixed + (double)nk / slices * 1.05 : 0.0) + (slices > 1 ? 4.0 + 0.09 * left * slices : 0.0);
 }
+// Do byte offsets from a tile's first row (of A, and of B where its K is contiguous) or k row (of B elsewhere) need more than 32 bits?
+template <int MODE> bool wide_offsets(const MArgs& g) {
+  const int64_t rows = (int64_t)255 * g.K + 64, k_rows = MODE == UP || MODE == DOWN ? (int64_t)64 * g.N : 0;
+  return std::max(rows, k_rows) * 2 + kCopyBias > (int64_t)1 << 32;
+}
 template <int MODE> int row_tile(const MArgs& g) {
   constexpr bool DUAL = MODE == UP;
+  if (wide_offsets<MODE>(g)) return 64;
   const int64_t avg = g.R / std::max(g.E, 1);
   if (avg <= 48) return 64;
   if (avg <= kSmallRows) return 128;
@@ -1637,6 +1656,7 @@ template <int MODE> size_t split_bytes(int R, int E, int N, int K) {
 template <int MODE> int launch_rows(const MArgs& g, int tile, bool stream_b, bool prepare_only, int* left, hipStream_t s) {
   const bool whole = g.K % 64 == 0;
   if (left && tile > 128) *left = 1;                     // large tiles finish their slices themselves
+  if (tile == 64 && wide_offsets<MODE>(g)) return launch_small<64, MODE, kWideTail, false>(g, prepare_only, left, s);
   auto go = [&](auto stream) {
     constexpr bool S = decltype(stream)::value;
     if (tile == 64) return launch_small<64, MODE, 0, S>(g, prepare_only, left, s);
@@ -1675,7 +1695,7 @@ template <int MODE> int launch_rows(const MArgs& g, hipStream_t s, int* left = n
 template <int MODE> int prepare_rows() {
   MArgs g{};
   for (int tile : {64, 128, 192, 256})
-    for (int k : {64, 32, 8}) {
+    for (int k : {64, 32, 8, 1 << 30}) {                 // whole k tiles, half a last one, any other, wide_offsets()
       g.K = k;
       if (int rc = launch_rows<MODE>(g, tile, false, true, nullptr, nullptr)) return rc;
       if (k == 64)
@@ -1761,6 +1781,11 @@ size_t mfma_forward_split_bytes(const FfShapes& sh) {
   return std::max(split_bytes<UP>(sh.R, sh.E, sh.f, sh.d), split_bytes<DOWN>(sh.R, sh.E, sh.d, sh.f));
 }
 size_t mfma_backward_split_bytes(const FfShapes& sh) { return split_bytes<BWD_DX>(sh.R, sh.E, sh.d, sh.f); }
+
+// Bytes from a k tile's first k row of dh1, dh3 or ga on, rows of f elements: strips of 32 k rows, 256 x 256 tiles of 64
+bool mfma_dw_ok(int R, int f, bool direct) {
+  return (int64_t)std::min(R, direct ? 32 : 64) * f * 2 + (direct ? 0 : kCopyBias) <= (int64_t)1 << 32;
+}
 
 bool mfma_gather_ok(int T, int d) { return (int64_t)T * d * 2 + kCopyBias < ((int64_t)1 << 32); }
 

@@ -81,6 +81,46 @@ def test_fp32_token_rows_past_4_gib():
         assert float((got - want).norm() / want.norm()) < TOL[F32] / 4
 
 
+def test_bf16_experts_whose_rows_need_64_bit_offsets():
+    """256 rows of f elements span 4 GiB: the down-projection and the input gradient find them with 64-bit offsets.  One expert, whose
+    gate is 1; against fp32 products, a piece of the columns at a time."""
+    T, d, f, pieces = 257, 264, 8421504, 16
+    g = torch.Generator(device="cuda").manual_seed(6)
+    def draw(*shape, scale=1.0):
+        return torch.randn(shape, generator=g, device="cuda", dtype=BF16).mul_(scale)
+    x, dY, W1, W3, W2 = draw(T, d), draw(T, d), draw(1, d, f, scale=d ** -0.5), draw(1, d, f, scale=d ** -0.5), draw(1, f, d, scale=f ** -0.5)
+    Wr = torch.zeros((d, 1), device="cuda")
+    r = B.btx_moe_route(x, Wr, None, None, 1, B.BTX_ROUTE_SWITCH_TOP1)
+    out, h1, h3 = B.btx_moe_ff_forward(x, W1, W3, W2, r)
+    b = B.btx_moe_ff_backward(dY, x, Wr, W1, W3, W2, r, h1, h3, B.BTX_ROUTE_SWITCH_TOP1)
+
+    def check(got, want, what):
+        err = float((got.float() - want).norm() / want.norm())
+        assert err < TOL[BF16], f"{what}: {err:.2e}"
+    rows = torch.argsort(r.inv_pos.flatten().long())                # grouped row -> token
+    xf, dYf = x.float()[rows], dY.float()[rows]
+    want_out, want_dX = torch.zeros((T, d), device="cuda", dtype=torch.float64), torch.zeros((T, d), device="cuda", dtype=torch.float64)
+    for p in range(pieces):
+        c = slice(p * f // pieces, (p + 1) * f // pieces)
+        w1, w3, w2 = W1[0, :, c].float(), W3[0, :, c].float(), W2[0, c].float()
+        u1, u3 = xf @ w1, xf @ w3
+        check(h1[:, c], u1, f"h1, piece {p}")
+        check(h3[:, c], u3, f"h3, piece {p}")
+        want_out += ((torch.nn.functional.silu(u1) * u3).to(BF16).float() @ w2).double()
+        u1, u3 = h1[:, c].float(), h3[:, c].float()
+        s = torch.sigmoid(u1)
+        da = dYf @ w2.t().contiguous()
+        dh1, dh3, ga = ((v.to(BF16).float()) for v in (da * u3 * s * (1 + u1 * (1 - s)), da * u1 * s, u1 * s * u3))
+        want_dX += (dh1 @ w1.t().contiguous()).double() + (dh3 @ w3.t().contiguous()).double()
+        check(b.dW1[0, :, c], xf.t().contiguous() @ dh1, f"dW1, piece {p}")
+        check(b.dW3[0, :, c], xf.t().contiguous() @ dh3, f"dW3, piece {p}")
+        check(b.dW2[0, c], ga.t().contiguous() @ dYf, f"dW2, piece {p}")
+    check(out[rows], want_out, "out")
+    check(b.dX[rows], want_dX, "dX")
+    del out, h1, h3, b, W1, W3, W2
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("mode", [B.BTX_ROUTE_SWITCH_TOP1, B.BTX_ROUTE_SAMPLE_TOP1])
 @pytest.mark.parametrize("lb_mode,flags", [(B.BTX_LB_TOKEN_FRAC, 0), (B.BTX_LB_GATE_MEAN, 0),
                                            (B.BTX_LB_GATE_MEAN, B.BTX_FLAG_LB_GRAD_THROUGH_U)])

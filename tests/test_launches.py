@@ -161,6 +161,32 @@ def slices_of_last_round(rows, E, N, K, product, tile):
     return max(1, min(8, 256 // left, k_tiles // 16)) if left else 1
 
 
+@pytest.mark.parametrize("T,d,f,wide", [
+    # 255 rows of K elements and 64 of their own, and at most 3 KB by which copies share a base: 2^32 bytes
+    (257, 264, 8421496, ()), (257, 264, 8421504, (DOWN, BWD_DX)), (16, 8421504, 64, (UP, BWD_ACT)),
+    # 64 rows of W1 and W3, or of W2
+    (100, 8, (1 << 25) - 24, (DOWN, BWD_DX)), (100, 8, (1 << 25) - 16, (UP, DOWN, BWD_DX)), (8, (1 << 25) - 16, 8, (UP, DOWN, BWD_ACT))])
+def test_bf16_operands_of_far_rows_take_64_bit_offsets(record, T, d, f, wide):
+    taken = bf16_products(record, T, d, f, 1, 1)
+    for product, (tile, tail, _) in taken.items():
+        assert (tail == 3) == (product in wide) and (tile == 64 or tail != 3)
+        if tail != 3:
+            K = d if product in (UP, BWD_ACT) else f
+            N = f + d - K if product in (UP, DOWN) else 0
+            assert max((min(tile, T) - 1) * K + min(K, 64), min(64, K) * N) * 2 + 3072 <= 1 << 32
+
+
+@pytest.mark.parametrize("T,f,status", [(400, (1 << 25) - 24, 0), (400, (1 << 25) - 16, 2), (100, 1 << 26, 0), (100, (1 << 26) + 8, 2), (20, 1 << 26, 0)])
+def test_bf16_weight_gradients_of_rows_too_far_apart_are_refused(record, T, f, status):
+    """64 grouped rows of the products' operands (strips: 32) span up to 2^32 bytes; without weight gradients any width will do."""
+    name, args = backward_call(T, 8, f, 1, 1, B.BTX_BF16)
+    frozen = list(args)
+    frozen[-7:-4] = [0, 0, 0]
+    (rc, found), (frozen_rc, frozen_found) = record((name, args), (name, frozen))
+    assert rc == status and bool(found) == (status == 0)
+    assert frozen_rc == 0 and frozen_found
+
+
 @pytest.mark.parametrize("case,paths", LAST_ROUND_CUT)
 def test_shapes_of_the_cut_last_round_take_that_path(record, case, paths):
     T, d, f, E, k, options = case
