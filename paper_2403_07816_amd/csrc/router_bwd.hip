@@ -145,6 +145,14 @@ __device__ __forceinline__ void dwr_partial_few(const XT* __restrict__ x, const 
   }
 }
 
+template <typename XT, int KEC, int CHUNK>
+__global__ __launch_bounds__(256) void dwr_partial_few_kernel(const XT* __restrict__ x, const float* __restrict__ ds, int T, int d, int E,
+                                                              float* __restrict__ part, float* __restrict__ db_part,
+                                                              float* __restrict__ dWr, float* __restrict__ db) {
+  __shared__ __attribute__((aligned(16))) float smem[dwr_few_lds_bytes<KEC, CHUNK>() / sizeof(float)];
+  dwr_partial_few<XT, KEC, CHUNK, 4>(x, ds, T, d, E, part, db_part, dWr, db, blockIdx.x, blockIdx.y, blockIdx.z, smem);
+}
+
 // 64 sums per block, taken in the partials' expert-major order (coalesced reads) and written to
 // dW_router's [d,E] place; 16 thread groups each add every 16th partial, then the 16 sums are
 // added in group order (a fixed order, like everything else here).
@@ -369,6 +377,21 @@ Parts parts_of(const RouterBwdArgs& a) {
 }
 }  // namespace
 
+// More than 8 experts: the partial sums beside dX, or in a launch of their own with 16 experts to a pass?  Beside it they read x once
+// for every 8 experts, and fill what dX's last round of workgroups (two on a compute unit) leaves idle.  What is read again costs more
+// than that from about 84 MB of fp32 rows or 144 MB of bf16 ones on, and a long launch gains nothing where that round is nearly full by
+// itself.  Of 232 shapes (9 to 64 experts, 64 to 4096 columns) this leaves 0.2 % on average to the better form, 7 % at most; always beside: 2.4
+// and 28 %.  The router's backward pass, us, a launch of its own / beside:
+//   4096 columns: 609 tokens fp32, 33 experts 48 / 27; 1410, 48 experts 65 / 57; 2013, 64 experts (504 workgroups) 71 / 75, 2069 (520) 118 / 94
+//   3072: 3122 tokens, 64 experts 104 / 89;  2048: 6563, 12 experts 57 / 48; fp32 3200, 64 experts (105 MB) 88 / 94; 10701, 32 (175 MB) 127 / 154
+//   1032: 13616 tokens, 24 experts (1278) 122 / 106;  256: 19822, 32 experts 104 / 95; 65408, 12 experts (2044) 153 / 159
+constexpr int kDxRound = 512, kDxNearlyFull = 470, kShortBlocks = 1536;
+static bool dwr_beside_dx(const RouterBwdArgs& a, int64_t dx_blocks, int64_t blocks) {
+  const bool f32 = a.dtype == BTX_F32;
+  const int64_t last = dx_blocks % kDxRound, again = (int64_t)a.T * a.d * (f32 ? 4 : 2) * (ceil_div(a.E, 8) - ceil_div(a.E, 16));
+  return again <= (f32 ? 84000000 : 144000000) && (blocks <= kShortBlocks || (last > 0 && last <= kDxNearlyFull));
+}
+
 RouterDs router_ds_args(const RouterBwdArgs& a) {
   const Parts p = parts_of(a);
   int slots_log2 = 0;                                   // a power of two of lanes for a token's slots
@@ -393,7 +416,7 @@ int launch_router_bwd(const RouterBwdArgs& a, bool ds_done, hipStream_t s) {
   const bool few = (int64_t)nch * ceil_div(a.d, 256 * kColsPerThread) * passes < kFewBlocks;
   const bool reduce = nch > 1 || !few;                  // a single chunk's sums need no further kernel
   float *const dWr = reduce ? nullptr : a.dW_router, *const db = reduce ? nullptr : a.db_router;
-  const int few_cols = ceil_div(a.d, kWave * kColsPerThread), dwr_blocks = few ? nch * few_cols * ceil_div(a.E, 8) : 0;
+  const int few_cols = ceil_div(a.d, kWave * kColsPerThread), dwr_blocks = few ? nch * few_cols * ceil_div(a.E, 8) : 0;   // beside dX
   auto typed = [&](auto tag) -> int {
     using XT = decltype(tag);
     const XT *const x = static_cast<const XT*>(a.x), *const dxs = static_cast<const XT*>(a.dxs);
@@ -419,14 +442,19 @@ int launch_router_bwd(const RouterBwdArgs& a, bool ds_done, hipStream_t s) {
       const int cols = ceil_div(a.d, kDxCols);
       const int tok = a.E <= kDxLdsE && ceil_div(a.T, 128) * cols >= kFewBlocks ? 128 : 32;
       const int dx_x = ceil_div(a.T, tok);
-      const int64_t blocks = (int64_t)dx_x * cols + dwr_blocks;
+      const int64_t dx_blocks = (int64_t)dx_x * cols, blocks = dx_blocks + dwr_blocks;
       if (!grid_fits(blocks, kDxWaves * kWave)) return BTX_ERR_UNSUPPORTED;
       const int lds = std::min(a.E, kDxLdsE) * kDxCols * (int)sizeof(float);
-      if (few)
+      const bool beside = few && dwr_beside_dx(a, dx_blocks, blocks);
+      if (few && !beside) {
+        dwr_partial_few_kernel<XT, 16, 128><<<dim3(nch, few_cols, passes), 256, 0, s>>>(x, ds, a.T, a.d, a.E, part, dbp, dWr, db);
+        BTX_LAUNCH_CHECK();
+      }
+      if (beside)
         dx_and_dwr_lds_kernel<XT><<<(unsigned)blocks, kDxWaves * kWave, std::max(lds, dwr_few_lds_bytes<8, 128>()), s>>>(
             dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, tok, dX, dx_x * cols, dx_x, x, part, dbp, dWr, db, nch, few_cols);
       else
-        dx_finish_lds_kernel<XT><<<(unsigned)blocks, kDxWaves * kWave, lds, s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, tok, dX, dx_x);
+        dx_finish_lds_kernel<XT><<<(unsigned)dx_blocks, kDxWaves * kWave, lds, s>>>(dxs, a.inv_pos, ds, WrT, a.T, a.d, a.E, a.k, tok, dX, dx_x);
     }
     BTX_LAUNCH_CHECK();
     return BTX_OK;

@@ -699,6 +699,12 @@ def test_router_gradients_and_dX_in_one_launch(T, d, E, k, dtype):
     run_layer_and_check(T, d, 72, E, k, dtype, unit_rms=True, poison=True)
 
 
+@pytest.mark.parametrize("T,d,E,k", [(5400, 1032, 64, 2), (8000, 1544, 17, 1)])
+def test_router_gradients_of_many_experts_in_a_launch_of_their_own(T, d, E, k):
+    """The sizes for which the partial sums do not run beside dX: passes of 16 experts, the last one of 1 and of 16."""
+    run_layer_and_check(T, d, 8, E, k, BF16, unit_rms=True, poison=True)
+
+
 @pytest.mark.parametrize("T,d,f,E,k,dtype", [
     (300, 64, 176, 4, 2, F32),          # fp32, ragged last token block
     (77, 2056, 64, 3, 1, F32),          # d not a multiple of the 2048-column thread stride, E < 4

@@ -112,6 +112,18 @@ def test_router_gradient_beside_the_weight_gradients(record, dtype, T, d, E, bes
     assert rc == 0 and any("router_ds_kernel" in launch.kernel for launch in found) != beside
 
 
+@pytest.mark.parametrize("dtype,T,d,E,beside", [
+    (B.BTX_BF16, 1501, 4096, 64, True), (B.BTX_F32, 609, 4096, 33, True), (B.BTX_BF16, 3122, 3072, 64, True), (B.BTX_BF16, 13616, 1032, 24, True),
+    # 84 MB of fp32 rows that are read again, 144 MB of bf16 ones
+    (B.BTX_F32, 2563, 2048, 64, True), (B.BTX_F32, 2564, 2048, 64, False), (B.BTX_BF16, 4394, 4096, 64, True), (B.BTX_BF16, 4395, 4096, 64, False),
+    # dX's last round of workgroups nearly full, more than 1536 workgroups together
+    (B.BTX_BF16, 15872, 256, 64, True), (B.BTX_BF16, 5400, 1032, 64, False), (B.BTX_BF16, 8000, 1544, 17, False), (B.BTX_BF16, 7136, 1544, 17, True)])
+def test_partial_sums_of_many_experts_router_gradient_beside_dX(record, dtype, T, d, E, beside):
+    (rc, found), = record(backward_call(T, d, 64, E, 2, dtype))
+    names = " ".join(launch.kernel for launch in found)
+    assert rc == 0 and ("dx_and_dwr_lds" in names) == beside and ("dwr_partial_few" in names and "dx_finish_lds" in names) == (not beside)
+
+
 @pytest.mark.parametrize("f,launches", [(1_000_000, 1), (8_000_000, 4)])
 def test_fp32_backward_products_that_fit_no_launch_together(record, f, launches):
     """Each of them fits: the router's gradient, dX, dW1 and dW3, dW2."""
