@@ -699,6 +699,13 @@ def test_router_gradients_and_dX_in_one_launch(T, d, E, k, dtype):
     run_layer_and_check(T, d, 72, E, k, dtype, unit_rms=True, poison=True)
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("E,k", [(3, 2), (8, 1)])
+def test_router_gradients_of_large_batches(E, k, dtype):
+    """The last 16 tokens of a wavefront and the last chunk of 64 have one."""
+    run_layer_and_check(32705, 8, 8, E, k, dtype, unit_rms=True, poison=True)
+
+
 @pytest.mark.parametrize("T,d,E,k", [(5400, 1032, 64, 2), (8000, 1544, 17, 1)])
 def test_router_gradients_of_many_experts_in_a_launch_of_their_own(T, d, E, k):
     """The sizes for which the partial sums do not run beside dX: passes of 16 experts, the last one of 1 and of 16."""

@@ -112,6 +112,16 @@ def test_router_gradient_beside_the_weight_gradients(record, dtype, T, d, E, bes
     assert rc == 0 and any("router_ds_kernel" in launch.kernel for launch in found) != beside
 
 
+@pytest.mark.parametrize("dtype", [B.BTX_F32, B.BTX_BF16])
+@pytest.mark.parametrize("T,d,E,beside", [(64, 64, 1, True), (16320, 4096, 4, True), (16321, 4096, 4, False), (32704, 2048, 8, True), (32705, 2048, 8, False)])
+def test_large_batches_finish_dX_in_a_kernel_of_its_own(record, dtype, T, d, E, beside):
+    """512 blocks of 64 tokens and 2048 columns: nothing runs beside dX, and its kernel holds nothing for that."""
+    (rc, found), = record(backward_call(T, d, 64, E, 1, dtype))
+    names = " ".join(launch.kernel for launch in found)
+    assert rc == 0 and ("dx_and_dwr_kernel" in names) == beside
+    assert ("dx_finish_kernel" in names and "dwr_partial_kernel" in names) == (not beside)
+
+
 @pytest.mark.parametrize("dtype,T,d,E,beside", [
     (B.BTX_BF16, 1501, 4096, 64, True), (B.BTX_F32, 609, 4096, 33, True), (B.BTX_BF16, 3122, 3072, 64, True), (B.BTX_BF16, 13616, 1032, 24, True),
     # 84 MB of fp32 rows that are read again, 144 MB of bf16 ones
