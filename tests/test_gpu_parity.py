@@ -747,6 +747,14 @@ def test_routing_reads_every_column_of_every_expert(T, d, E, dtype):
     run_layer_and_check(T, d, 8, E, 2, dtype, unit_rms=True, backward=False, poison=True)
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("T,d,E", [(4203, 40, 33), (4203, 264, 33), (8200, 264, 24), (4203, 392, 49), (8200, 520, 9), (4203, 648, 40), (700, 904, 64),
+                                   (4203, 4104, 12), (4203, 4200, 20)])
+def test_routing_trips_that_are_no_whole_rounds(T, d, E, dtype):
+    """More than 8 experts: no trip, one to six and more for each wavefront, of which two or three are on their way at a time."""
+    run_layer_and_check(T, d, 8, E, 2, dtype, unit_rms=True, backward=False, poison=True)
+
+
 @pytest.mark.parametrize("case,taken", ROUTE_MANY)
 def test_routing_of_many_tokens(case, taken):
     """Every number of experts in a pass and of wavefronts that share 16 tokens, above the sizes that two launches take."""
