@@ -845,8 +845,10 @@ bool matrix_logits(const RouteArgs& a) { return a.E > 8 && !a.gain; }
 //   187 / 208 / 270; 4500 of 512, 64 experts 80 / 71 / 83, of 4096 235 / 263 / 392
 // Logits on the matrix cores: 8 wavefronts that share W_router's columns, for one block of tokens instead of kMatrixGroups.
 // 4001 tokens of 4096 columns, 64 experts 67 -> 44 us; past one workgroup on a compute unit few experts of few columns 4500 of 1024, 16
-// experts 30 -> 24, of 2048, 32 experts 38 -> 33.  (Others would gain as well, 4500 of 8192, 16 experts 56 -> 49, 32 of 4096 48 -> 44, 64 of
-// them 66 -> 65, but not while W_router was read as [E,d], and a logit's sum has another order with other wavefronts.)
+// experts 30 -> 24, of 2048, 32 experts 38 -> 33, and wide rows, where 4 wavefronts wait longer for every piece of a row: 4600 of 4608, 16
+// experts 43 -> 36, 28 experts 51 -> 47; of 10240 62 -> 54, 78 -> 74; 7000 of 16384, 12 experts 105 -> 90, but 24 experts 114 -> 115; fp32 5000
+// of 6144, 12 experts 61 -> 55, 24 experts 64 -> 67, of 16384 119 -> 113, 126 -> 139.  (More than 65536 weights of up to 4096 columns gain as well,
+// 4500 tokens, 32 experts 48 -> 44; left as they are.)
 constexpr int kFewBlocks = 512, kComputeUnits = 256;
 int token_waves(int nblk, int d, int E, bool f32, bool norm) {
   if (nblk >= kFewBlocks) return kWavesPerBlock;
@@ -856,8 +858,10 @@ int token_waves(int nblk, int d, int E, bool f32, bool norm) {
   }
   return (f32 ? d <= 4096 && d * E <= 32768 : norm) ? 8 : kWavesPerBlock;
 }
-bool matrix_few(int nblk, int d, int E) {
-  return nblk <= kComputeUnits || (nblk < kFewBlocks && E <= 32 && d * E <= 65536);
+bool matrix_few(int nblk, int d, int E, bool f32) {
+  if (nblk <= kComputeUnits) return true;
+  if (nblk >= kFewBlocks || E > 32) return false;
+  return d * E <= 65536 || (d > 4096 && (E <= 16 || (!f32 && d <= 10240)));
 }
 
 template <typename XT>
@@ -894,7 +898,7 @@ void launch_tokens(const RouteArgs& a, const float* WrT, int nblk, int32_t* bc, 
     };
     using std::integral_constant;
     auto go = [&](auto ns) {
-      if (matrix_few(nblk, a.d, a.E)) go_nw(integral_constant<int, 8>{}, integral_constant<int, 1>{}, ns);
+      if (matrix_few(nblk, a.d, a.E, std::is_same<XT, float>::value)) go_nw(integral_constant<int, 8>{}, integral_constant<int, 1>{}, ns);
       else go_nw(integral_constant<int, kWavesPerBlock>{}, integral_constant<int, kMatrixGroups>{}, ns);
     };
     if (a.E <= 16) go(integral_constant<int, 1>{});

@@ -270,6 +270,16 @@ def test_wavefronts_that_share_16_tokens(record, dtype, norm, T, d, E, waves):
         assert tokens.block[0] == 64 * waves and f", {waves}, " in tokens.kernel
 
 
+@pytest.mark.parametrize("dtype,T,d,E,waves", [
+    (B.BTX_BF16, 4097, 4096, 16, 8), (B.BTX_BF16, 4097, 4096, 17, 4), (B.BTX_BF16, 4097, 4104, 17, 8), (B.BTX_BF16, 8176, 10240, 32, 8),
+    (B.BTX_BF16, 8176, 10248, 17, 4), (B.BTX_BF16, 8176, 16384, 16, 8), (B.BTX_BF16, 8177, 16384, 16, 4), (B.BTX_BF16, 4097, 8192, 33, 4),
+    (B.BTX_F32, 4097, 4104, 16, 8), (B.BTX_F32, 4097, 4104, 17, 4)])
+def test_wide_rows_share_their_tokens_between_8_wavefronts(record, dtype, T, d, E, waves):
+    (rc, found), = record(route_call(T, d, E, 2, dtype))
+    tokens, = [launch for launch in found if launch.kernel.startswith("route_tokens")]
+    assert rc == 0 and tokens.block[0] == 64 * waves
+
+
 @pytest.mark.parametrize("dtype", [B.BTX_F32, B.BTX_BF16])
 @pytest.mark.parametrize("E", [1, 2, 3, 4, 5, 8, 9, 12, 16, 17, 64])
 def test_routing_takes_the_same_way_with_and_without_the_normalisation(record, E, dtype):
