@@ -100,8 +100,8 @@ __device__ __forceinline__ void copy_to_lds(uint32_t lds, const float* a, const 
                : "memory");
 }
 
-// WIDE: byte offsets inside an operand need more than 32 bits (wide_offsets())
-template <int MODE, bool WIDE> struct F32Gemm {
+// WIDE: byte offsets inside an operand need more than 32 bits (wide_offsets()).  STAGES: of LDS, three for weights_from_memory()
+template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
   typedef std::conditional_t<WIDE, uint64_t, uint32_t> Off;
   static constexpr bool GROUP_K = MODE == DW13 || MODE == DW2;
   static constexpr bool A_KC = !GROUP_K, B_KC = MODE == BWD_ACT || MODE == BWD_DX;   // k contiguous in memory
@@ -340,13 +340,13 @@ template <int MODE, bool WIDE> struct F32Gemm {
 
     // k tile kt, in LDS stage `stage`; more: another one follows
     auto step = [&](auto stage_tag, auto more_tag, int kt) {
-      constexpr int stage = decltype(stage_tag)::value;
+      const int stage = stage_tag;
       constexpr bool more = decltype(more_tag)::value;
-      wait_vmcnt<0>();
+      if (STAGES == 2 || kt + STAGES - 2 >= nk) wait_vmcnt<0>(); else wait_vmcnt<4 * (STAGES - 2)>();
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_barrier();                      // k tile kt published; everybody is done with the last one
       __builtin_amdgcn_sched_barrier(0);
-      if (more) copy(stage ^ 1);
+      if (STAGES == 2 ? more : kt + STAGES - 1 < nk) copy(STAGES == 2 ? stage ^ 1 : stage == 0 ? STAGES - 1 : stage - 1);
       const float* T = smem + stage * STAGE;
       f32x4 af[2][2], bf[2][2];
 #pragma unroll
@@ -385,7 +385,18 @@ template <int MODE, bool WIDE> struct F32Gemm {
     };
     const std::integral_constant<int, 0> stage0;
     const std::integral_constant<int, 1> stage1;
-    if (nk > 0) {
+    if (STAGES > 2 && nk > 0) {                          // STAGES - 1 k tiles on their way
+      static_assert(STAGES == 2 || !LOOK_UP, "token rows are looked up one k tile ahead");
+      for (int j = 0; j < STAGES - 1; ++j)
+        if (j < nk) copy(j);
+      int stage = 0;
+#pragma unroll 1
+      for (int kt = 0; kt < nk - 1; ++kt) {
+        step(stage, std::true_type{}, kt);
+        stage = stage == STAGES - 1 ? 0 : stage + 1;
+      }
+      step(stage, std::false_type{}, nk - 1);
+    } else if (nk > 0) {
       look_up(0);
       copy(0);
       look_up(1);
@@ -464,9 +475,9 @@ template <int MODE, bool WIDE> struct F32Gemm {
   }
 };
 
-template <int MODE, bool WIDE> __global__ __launch_bounds__(kThreads, 5) void f32_gemm_kernel(FArgs g) {
-  using G = F32Gemm<MODE, WIDE>;
-  __shared__ __attribute__((aligned(1024))) float smem[2 * G::STAGE];
+template <int MODE, bool WIDE, int STAGES> __global__ __launch_bounds__(kThreads, STAGES == 2 ? 5 : 3) void f32_gemm_kernel(FArgs g) {
+  using G = F32Gemm<MODE, WIDE, STAGES>;
+  __shared__ __attribute__((aligned(1024))) float smem[STAGES * G::STAGE];
   G::run(g, blockIdx.x, smem);
 }
 // The input's and the weights' gradients need what BWD_ACT has left and nothing of each other: one launch, first the tiles of BWD_DX,
@@ -509,16 +520,20 @@ __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float
   *reinterpret_cast<f32x4*>(C + i) = a;
 }
 
+// tiles of N columns (rows of tile_cols) to expect: an expert's last row tile is half full on average
+double expected_tiles(int R, int E, int N, int tile_cols) {
+  const int busy = std::max(std::min(E, R), 1);
+  return busy * std::max((double)R / busy / kTile + 0.5, 1.0) * ceil_div(N, tile_cols);
+}
+
 // K slices of DOWN and BWD_DX.  Few tiles of many k tiles leave compute units idle, or some with a tile more than others.
 // Measured on 64 x 64 tiles of 32 k (64 to 2003 tokens, 8 experts of 512 x 1376, 1 to 4 slices): with r tiles on a compute unit a k
 // tile takes 0.5 us for each of them, 0.7 us for a single one, which waits for memory; the slices' sums pass through memory once
 // more, at about 8 TB/s, BWD_DX's in a launch of its own, DOWN's in the combine, to which a cut for less than a seventh is not
-// worth it.  An expert's last row tile is half full on average.  (DOWN + combine, us, without slices / as chosen here: 64 tokens 45 /
+// worth it.  (DOWN + combine, us, without slices / as chosen here: 64 tokens 45 /
 // 22, 512 45 / 29, 1024 57 / 43, 1536 58 / 58; BWD_DX 66 / 25, 66 / 45, 100 / 68, 104 / 90, 2003 tokens 136 / 112.)
 int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
-  const int busy = std::max(std::min(E, R), 1);
-  const double tiles = busy * std::max((double)R / busy / kTile + 0.5, 1.0) * ceil_div(N, kTile);
-  const double nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
+  const double tiles = expected_tiles(R, E, N, kTile), nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
   int best = 1;
   double best_us = 0, uncut_us = 0;
   for (int n = 1; n <= most; ++n) {
@@ -553,6 +568,15 @@ bool wide_offsets(const FArgs& g, int R) {
   return rows * std::max(g.lda, g.ldb) >= ((int64_t)1 << 30) - 4096;
 }
 
+// UP with few workgroups on a compute unit and weights that come from memory, not from the memory-side cache (256 MB): one k tile on
+// its way is too little.  us, two stages / three (in brackets: through registers, with two k tiles on their way), by the bytes of W1 and W3:
+// 12 tokens of 5528, f = 216, 16 experts (153 MB) 141 / 117 (127); 37 of 3984, f = 216, 16 experts (110) 103 / 87 (94); 64 of 4096, f = 2048, 4
+// experts (268) 109 / 92 (98); 55 of 4096, f = 344, 8 experts (90) 99 / 91 (96); but 32 of 4448, f = 1104, 2 experts (79) 94 / 99, 94 of 2096, f =
+// 4072, 1 expert (68) 50 / 52, and with three workgroups on a unit 443 of 3824, f = 1488, 8 experts (752 tiles) 244 / 255.
+bool weights_from_memory(const FArgs& g, int R) {
+  return (int64_t)8 * std::min(g.E, R) * g.K * g.N >= 88000000 && expected_tiles(R, g.E, g.N, kTile / 2) <= 512;
+}
+
 // Completes the arguments of a product; its workgroups, 0: more than a launch can hold
 template <int MODE> unsigned blocks_of(FArgs& g, int R) {
   using G = F32Gemm<MODE, false>;
@@ -573,8 +597,9 @@ int finish_slices(const FArgs& g, int R, hipStream_t s) {
 template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullptr) {
   const unsigned grid = blocks_of<MODE>(g, R);
   if (grid == 0) return BTX_ERR_UNSUPPORTED;
-  if (wide_offsets(g, R)) f32_gemm_kernel<MODE, true><<<grid, kThreads, 0, s>>>(g);
-  else f32_gemm_kernel<MODE, false><<<grid, kThreads, 0, s>>>(g);
+  if (wide_offsets(g, R)) f32_gemm_kernel<MODE, true, 2><<<grid, kThreads, 0, s>>>(g);
+  else if (MODE == UP && weights_from_memory(g, R)) f32_gemm_kernel<MODE, false, MODE == UP ? 3 : 2><<<grid, kThreads, 0, s>>>(g);
+  else f32_gemm_kernel<MODE, false, 2><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
   const bool leave = left && g.slices <= *left;
   if (left) *left = leave ? g.slices : 1;

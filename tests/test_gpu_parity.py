@@ -53,6 +53,12 @@ def test_fp32_products_cut_along_k(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, F32, **kw)
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 680, 8192, 2, 2), (12, 5528, 216, 16, 2), (100, 4104, 344, 8, 1), (37, 3984, 216, 16, 2), (65, 2800, 4096, 1, 1)])
+def test_fp32_up_projection_with_three_stages(T, d, f, E, k):
+    """Last k tiles of 8, 16, 24 and 32, 22 to 173 of them, one and two row tiles to an expert."""
+    run_layer_and_check(T, d, f, E, k, F32, unit_rms=True, backward=False, poison=True)
+
+
 def test_fp32_token_rows_past_4_gib():
     """Token rows whose byte offsets need more than 32 bits: as the same rows give in batches that stay below.  Without a
     load-balancing loss the tokens do not see each other; the weight gradients add up."""

@@ -142,6 +142,16 @@ def test_fp32_backward_products_that_fit_no_launch_together(record, f, launches)
     assert sum(launch.kernel.startswith(("f32_dx_dw", "f32_gemm_kernel<3", "f32_gemm_kernel<4", "f32_gemm_kernel<5")) for launch in found) == launches
 
 
+@pytest.mark.parametrize("T,d,f,E,k,stages", [
+    (37, 3984, 216, 16, 2, 3), (4, 3896, 816, 64, 2, 3), (1, 680, 8192, 2, 2, 3),
+    # W1 and W3 of less than 88 MB; more than 512 tiles; tokens of fewer experts
+    (1, 664, 8192, 2, 2, 2), (512, 512, 1376, 8, 2, 2), (1, 680, 8224, 2, 2, 2), (443, 3824, 1488, 8, 2, 2), (1, 3896, 816, 64, 2, 2)])
+def test_fp32_up_projection_of_weights_from_memory_has_three_stages(record, T, d, f, E, k, stages):
+    (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32))
+    up, = [launch.kernel for launch in found if launch.kernel.startswith("f32_gemm_kernel<0")]
+    assert rc == 0 and up.endswith(f", {stages}>")
+
+
 def test_fp32_products_of_too_many_tiles_are_refused(record):
     """2^24 tiles of 256 threads are more than a launch can hold (137 GB of activations)."""
     (rc, found), = record(forward_call(4_000_000, 64, 8704, 4, 1, B.BTX_F32, save=False))
