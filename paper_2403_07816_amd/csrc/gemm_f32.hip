@@ -668,18 +668,22 @@ int f32_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, co
   if (n_dx == 0 || n13 == 0 || n2 == 0) return BTX_ERR_UNSUPPORTED;
   const RouterDs rd = ds ? *ds : RouterDs{};
   const unsigned nds = ds ? router_ds_blocks(rd) : 0;
-  if (!grid_fits((int64_t)n_dx + n13 + n2 + nds, kThreads)) {
-    if (ds) f32_dx_dw_kernel<false><<<nds, kThreads, 0, s>>>(dx, 0, dw13, 0, dw2, 0, rd);
+  const bool wide = wide_offsets(dx, sh.R) || wide_offsets(dw13, sh.R) || wide_offsets(dw2, sh.R);
+  auto go = [&](unsigned a, unsigned b, unsigned c, unsigned d) -> int {
+    if (a + b + c + d == 0) return BTX_OK;
+    if (wide) f32_dx_dw_kernel<true><<<a + b + c + d, kThreads, 0, s>>>(dx, a, dw13, b, dw2, c, rd);
+    else f32_dx_dw_kernel<false><<<a + b + c + d, kThreads, 0, s>>>(dx, a, dw13, b, dw2, c, rd);
     BTX_LAUNCH_CHECK();
-    if (int rc = launch<BWD_DX>(dx, sh.R, s)) return rc;
-    if (int rc = launch<DW13>(dw13, sh.R, s)) return rc;
-    return launch<DW2>(dw2, sh.R, s);
+    return BTX_OK;
+  };
+  if (grid_fits((int64_t)n_dx + n13 + n2 + nds, kThreads)) {
+    if (int rc = go(n_dx, n13, n2, nds)) return rc;
+  } else {                                               // one after another: each of them fits
+    if (int rc = go(0, 0, 0, nds)) return rc;
+    if (int rc = go(n_dx, 0, 0, 0)) return rc;
+    if (int rc = go(0, n13, 0, 0)) return rc;
+    if (int rc = go(0, 0, n2, 0)) return rc;
   }
-  if (wide_offsets(dx, sh.R) || wide_offsets(dw13, sh.R) || wide_offsets(dw2, sh.R))
-    f32_dx_dw_kernel<true><<<n_dx + n13 + n2 + nds, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2, n2, rd);
-  else
-    f32_dx_dw_kernel<false><<<n_dx + n13 + n2 + nds, kThreads, 0, s>>>(dx, n_dx, dw13, n13, dw2, n2, rd);
-  BTX_LAUNCH_CHECK();
   return dx.slices > 1 ? finish_slices(dx, sh.R, s) : BTX_OK;
 }
 
