@@ -67,6 +67,15 @@ PMC_PROFILE = os.path.join(ROOT, "profiles", "layer_fwd_bwd_c2_pmc_counters.txt"
 GEMM_SOURCE = os.path.join(ROOT, "paper_2403_07816_amd", "csrc", "gemm_mfma.hip")
 
 
+def gemm_flops(stage_ms):
+    """{stage: flops / (d f R)} of the expert GEMM stages that did work.  Weight gradients that need no transposed rows (gather_x_bwd
+    did not run: few rows per expert) are one launch, whose time is dw13's; dw2 is an empty interval then."""
+    flops = {n: c for n, c in GEMM_STAGES.items() if stage_ms[n] > 0}
+    if "dw13" in flops and stage_ms["gather_x_bwd"] == 0:
+        flops["dw13"] += flops.pop("dw2", GEMM_STAGES["dw2"])
+    return flops
+
+
 def describe(V, T):
     passes = "forward only" if V.get("forward_only") else "fwd+bwd"
     return (f"llama2-7b-shaped MoE-FF layer, {passes}, T={T}, d={D_MODEL}, f={V['f']}, E={V['E']}, {V['name']}, bf16, "
@@ -149,7 +158,8 @@ def hbm_stages(stage_ms, T, d, E, k, s=2, block=False):
     """The streaming stages against the 8 TB/s HBM peak: algorithmic bytes per token (bf16 rows of d*s bytes) and
     the rate they were moved at.  route: x read once + indices, gates, probabilities written; combine: k rows read,
     one written; gather_x_bwd: x and dY each read once per routed slot and written once per slot, transposed;
-    router_bwd: x read (dW_router), k rows of dxs read and one row of dX written."""
+    router_bwd: x read (dW_router), k rows of dxs read and one row of dX written (small batches: its first part, which moves none
+    of these rows, runs beside the weight gradients)."""
     per_token = {"route": d * s + k * 8 + E * 4, "combine": d * s * (k + 1), "gather_x_bwd": 2 * d * s * 2 * k,
                  "router_bwd": d * s * (k + 2)}
     if block:   # route also writes the normalised rows; combine also reads the residual; norm_bwd: dXn, h, dY in, dH out
@@ -353,10 +363,11 @@ class Layer:
             stage_ms[name] = float(np.mean(v))
         events.destroy()
         R = int(self.routing.offsets[-1].item())   # grouped rows the expert GEMMs worked on (T*k unless pairs were dropped)
+        flops = gemm_flops(stage_ms)
         gemm = {n: {"ms": stage_ms[n], "tflops": c * d * f * R / (stage_ms[n] * 1e-3) / 1e12,
                     "frac_of_peak": c * d * f * R / (stage_ms[n] * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
-                for n, c in GEMM_STAGES.items() if stage_ms[n] > 0}
-        gemm_coef = float(sum(GEMM_STAGES[n] for n in gemm))    # 18 for forward + backward, 6 for forward
+                for n, c in flops.items()}
+        gemm_coef = float(sum(flops.values()))                  # 18 for forward + backward, 6 for forward
         gemm_ms = sum(v["ms"] for v in gemm.values())
         gemm_tflops = gemm_coef * d * f * R / (gemm_ms * 1e-3) / 1e12
         ms_per_step = elapsed / steps * 1e3
@@ -465,7 +476,7 @@ def main():
         "roofline": {"bound": "mfma", "kernel": f"mfma_gemm_kernel ({dominant})", "achieved": gemm[dominant]["tflops"],
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": gemm[dominant]["tflops"] / PEAK_BF16_TFLOPS,
                      "traffic": traffic, "traffic_source": traffic_src,
-                     "algorithmic_flops": GEMM_STAGES[dominant] * D_MODEL * V["f"] * r["routed_rows"]},
+                     "algorithmic_flops": gemm_flops(r["stage_ms"])[dominant] * D_MODEL * V["f"] * r["routed_rows"]},
         "expert_gemms": r["expert_gemms"], "stage_ms": r["stage_ms"], "step_ms": r["step_ms"],
         "hbm_stages": r["hbm_stages"],
         "parity_checked": None if parity is None else parity["ok"], "parity": parity, "deterministic": det,
