@@ -3,6 +3,8 @@
 #include <cmath>
 
 #include "common.h"
+#include "gemm_f32.h"
+#include "gemm_mfma.h"
 #include "router_ds.h"
 
 using namespace btx;
@@ -335,7 +337,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   const RouterDs* const ds = ds_rides ? &rd : nullptr;
   const RowSource dw_x{x, perm, k}, dw_dy{dY, perm, k};
   if (n_dw == 3 && dtype == BTX_F32) {
-    BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx_dw(dw_x, dw_dy, w.dh1, w.dh3, w.ga, W1, W3, offsets, sh, row_bytes, w.dxs, w.partial,
+    BTX_STAGE(BTX_STAGE_BWD_DX, f32_bwd_dx_dw(dw_x, dw_dy, w.dh1, w.dh3, w.ga, W1, W3, offsets, sh, row_bytes, w.dxs, w.partial,
                                                  dW1, dW3, dW2, ds, s));
     BTX_STAGE(BTX_STAGE_DW13, BTX_OK);                   // events with nothing between them
     BTX_STAGE(BTX_STAGE_DW2, BTX_OK);
@@ -343,12 +345,12 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
     BTX_STAGE(BTX_STAGE_BWD_DX, launch_bwd_dx(dtype, w.dh1, w.dh3, W1, W3, offsets, sh, w.dxs, w.partial, s));
   }
   if (n_dw == 3 && dtype == BTX_BF16 && direct) {
-    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw_direct(dW_dtype, dw_x, dw_dy, w.dh1, w.dh3, w.ga, offsets, sh, row_bytes, dW1, dW3, dW2, ds, s));
+    BTX_STAGE(BTX_STAGE_DW13, mfma_bwd_dw_direct(dW_dtype, dw_x, dw_dy, w.dh1, w.dh3, w.ga, offsets, sh, row_bytes, dW1, dW3, dW2, ds, s));
     BTX_STAGE(BTX_STAGE_DW2, BTX_OK);
   } else if (n_dw == 3 && dtype == BTX_BF16) {
     BTX_STAGE(BTX_STAGE_GATHER_X_BWD, launch_gather_rows_t(x, w.xsT, dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
-    BTX_STAGE(BTX_STAGE_DW13, launch_bwd_dw13(dW_dtype, {w.xsT, nullptr, 1}, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
-    BTX_STAGE(BTX_STAGE_DW2, launch_bwd_dw2(dW_dtype, w.ga, {w.dysT, nullptr, 1}, offsets, sh, dW2, s));
+    BTX_STAGE(BTX_STAGE_DW13, mfma_bwd_dw13(dW_dtype, {w.xsT, nullptr, 1}, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
+    BTX_STAGE(BTX_STAGE_DW2, mfma_bwd_dw2(dW_dtype, w.ga, {w.dysT, nullptr, 1}, offsets, sh, dW2, s));
   }
   BTX_STAGE(BTX_STAGE_ROUTER_BWD, launch_router_bwd(ra, ds_rides, s));
   return BTX_OK;

@@ -212,6 +212,21 @@ struct RowTiles {
   }
 };
 
+// at most N vector memory operations outstanding (gfx9 encoding: vmcnt = bits [3:0] and [15:14]; expcnt [6:4] and
+// lgkmcnt [11:8] left at max)
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+// states to the compiler that a pointer is the same in all lanes
+__device__ __forceinline__ uint64_t uniform64(const void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // a launch holds fewer than 2^32 threads in each direction of its grid
 inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < (int64_t)1 << 32; }
@@ -289,24 +304,14 @@ int launch_bwd_act(int dtype, const RowSource& dys, const void* W2, const void* 
 int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, const void* W3, const int32_t* offsets,
                   const FfShapes& sh, void* dxs, void* partial, hipStream_t s);
 // dW1 = xs^T dh1, dW3 = xs^T dh3, dW2 = ga^T dys, per expert over its rows.  When ff_dw_direct() holds, xs and dys are token rows read
-// through perm, ga is [R,f], and one launch does all three (bf16) or them and launch_bwd_dx's (fp32, launch_bwd_dx_dw()).  Otherwise
-// (bf16: ff_dw_transposed()) they are passed in the transposed, padded form with pitch ff_dw_pitch() (xs and dys as
-// launch_gather_rows_t writes them, ga as launch_bwd_act does).  ds (may be NULL): router_ds() for the direct forms' launch to run beside
-// them.
+// through perm, ga is [R,f], and one launch does all three (mfma_bwd_dw_direct()) or them and launch_bwd_dx's (f32_bwd_dx_dw()).  Otherwise
+// (bf16: ff_dw_transposed(); mfma_bwd_dw13(), mfma_bwd_dw2()) they are passed in the transposed, padded form with pitch ff_dw_pitch() (xs and
+// dys as launch_gather_rows_t writes them, ga as launch_bwd_act does).  ds (may be NULL): router_ds() for the direct forms' launch to run
+// beside them.
 struct RouterDs;
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
-int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets, const FfShapes& sh,
-                    void* dW1, void* dW3, hipStream_t s);
-int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets, const FfShapes& sh, void* dW2,
-                   hipStream_t s);
-int launch_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
-                         const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2,
-                         const RouterDs* ds, hipStream_t s);
-int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
-                     const void* W3, const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* partial,
-                     void* dW1, void* dW3, void* dW2, const RouterDs* ds, hipStream_t s);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address

@@ -59,23 +59,5 @@ int launch_bwd_dx(int dtype, const void* dh1, const void* dh3, const void* W1, c
   if (dtype == BTX_BF16) return mfma_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, partial, s);
   return f32_bwd_dx(dh1, dh3, W1, W3, offsets, sh, dxs, partial, s);
 }
-int launch_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* offsets, const FfShapes& sh,
-                    void* dW1, void* dW3, hipStream_t s) {
-  return mfma_bwd_dw13(dW_dtype, xs, dh1, dh3, offsets, sh, dW1, dW3, s);
-}
-int launch_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* offsets, const FfShapes& sh, void* dW2,
-                   hipStream_t s) {
-  return mfma_bwd_dw2(dW_dtype, ga, dys, offsets, sh, dW2, s);
-}
-int launch_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,
-                         const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dW1, void* dW3, void* dW2,
-                         const RouterDs* ds, hipStream_t s) {
-  return mfma_bwd_dw_direct(dW_dtype, xs, dys, dh1, dh3, ga, offsets, sh, row_bytes, dW1, dW3, dW2, ds, s);
-}
-int launch_bwd_dx_dw(const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga, const void* W1,
-                     const void* W3, const int32_t* offsets, const FfShapes& sh, uint32_t* row_bytes, void* dxs, void* partial,
-                     void* dW1, void* dW3, void* dW2, const RouterDs* ds, hipStream_t s) {
-  return f32_bwd_dx_dw(xs, dys, dh1, dh3, ga, W1, W3, offsets, sh, row_bytes, dxs, partial, dW1, dW3, dW2, ds, s);
-}
 
 }  // namespace btx

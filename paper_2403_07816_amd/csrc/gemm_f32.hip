@@ -68,16 +68,6 @@ constexpr int kThreads = 256;
 constexpr int kTile = 64, kTileK = 32;   // rows and columns of a tile, and k of a k tile
 constexpr int kBand = 8;                 // row tiles of a band in the tile order
 
-// at most N vector memory operations outstanding (vmcnt = bits [3:0] and [15:14]; expcnt and lgkmcnt left at max)
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ uint64_t uniform64(const float* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return (uint64_t)lo | ((uint64_t)hi << 32);
-}
 // Four copies of 1 KB, 16 bytes per lane, from global memory straight into LDS, to lds, lds + 1024, ... : copies 0 and 1 from
 // a + off, 2 from b0 + off, 3 from b1 + off.  The offset of the instruction counts in memory as in LDS, so the lanes' offsets make up
 // for it (Operand::kBias), and all four share one setting of m0.  Inline assembly, so that the compiler does not wait for the

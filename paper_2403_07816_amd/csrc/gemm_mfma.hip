@@ -80,13 +80,6 @@ struct MArgs {
   int slices; float* slice_sums;
 };
 
-// at most N vector memory operations outstanding (gfx9 encoding: vmcnt = bits [3:0] and [15:14]; expcnt [6:4] and
-// lgkmcnt [11:8] left at max)
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
 // Direct global -> LDS copy of 16 bytes per lane: lane l's data lands at lds_base + 16*l.
 // Written as inline assembly so that the compiler does not serialise later LDS reads of
 // *other* stages behind it (it cannot tell the stages apart and would wait for vmcnt(0));
@@ -96,11 +89,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // STREAM: past the L1 and marked for early eviction in the L2, for bytes that are read once.
 template <bool STREAM = false>
 __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_off, uint32_t lds_base) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
-  const uint64_t sp = (uint64_t)lo | ((uint64_t)hi << 32);
+  const uint64_t sp = uniform64(base);
   const uint32_t sl = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
   if constexpr (STREAM)
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 sc1 nt"
@@ -121,13 +110,6 @@ __device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t byte_of
 constexpr uint32_t copy_bias(int n) { return 1024u * (n - 1); }
 constexpr uint32_t kCopyBias = copy_bias(4);             // of the most copies
 template <int N, typename Off> __device__ __forceinline__ constexpr Off copy_off(Off off, int q) { return off + (copy_bias(N) - 1024u * q); }
-__device__ __forceinline__ uint64_t uniform64(const void* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  // readfirstlane returns int: go through uint32_t so that the halves are not sign-extended
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return (uint64_t)lo | ((uint64_t)hi << 32);
-}
 #define BTX_COPY(q, reg, flags) "\n\tglobal_load_lds_dwordx4 %" #reg ", %1 offset:" #q flags
 #define BTX_COPIES(flags)                                                                                                           \
   static_assert(N >= 2 && N <= 4, "copies");                                                                                        \
