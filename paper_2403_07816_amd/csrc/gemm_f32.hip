@@ -7,7 +7,8 @@
 // instructions: each vector or scalar one costs it 2 to 4 clocks, whichever wavefront of the SIMD issues it.  So the tiles are
 // kept simple and the loop short:
 //   * 64 x 64 x 32, 4 wavefronts as 2 x 2, two LDS stages, one barrier per k tile; five workgroups per compute unit cover
-//     each other's barriers and memory latency (three stages and three workgroups: 4 % slower, 9 % with four and two).
+//     each other's barriers and memory latency (three stages and three workgroups: 4 % slower, 9 % with four and two;
+//     where one or two tiles are all that a unit gets, see weights_from_memory()).
 //   * operands go straight from global memory to LDS, four copies per wavefront and k tile in one block: one setting of m0,
 //     bases in scalar registers, 32-bit lane offsets that stay the same from k tile to k tile.  With copies from 64-bit addresses in
 //     vector registers the compute unit's other wavefronts lose the matrix pipe to them: 4096 rows, one expert of 1024 x 4096: DOWN
@@ -22,10 +23,10 @@
 //   * token rows (x, dY) are read through perm wherever they are an operand (the weight gradients: by byte offsets that BWD_ACT
 //     leaves behind, found through the scalar cache), the SwiGLU and its backward are epilogues on the accumulators: nothing is
 //     gathered, and no product is stored only to be read again.
-// Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP), operands through registers /
-// now: 601 / 559 us: UP 114 / 107 us, DOWN 77 / 58, BWD_ACT 68 / 66, BWD_DX 128 / 112, DW13 115 / 112, DW2 64 / 64, at 76 to 105 of the
-// 153 TFLOP/s this instruction sustains; 4096 rows, one expert of 1024 x 4096: 2598 / 2435, at 124 to 138.  What is left is
-// ragged rounds of 64 x 64 tiles and what starting and storing a tile takes.
+// Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP), operands through registers and
+// every product by itself / now: 600 / 528 us (16 of it the router's backward pass): UP 114 / 107 us, DOWN 77 / 69, BWD_ACT 68 / 66, BWD_DX 127, DW13 114 and DW2 64 / 263
+// in one launch, at 82 to 107 of the 153 TFLOP/s this instruction sustains; 4096 rows, one expert of 1024 x 4096: 2598 / 2404, at 115
+// to 137.  What is left is ragged rounds of 64 x 64 tiles and what starting and storing a tile takes.
 #include "gemm_f32.h"
 #include "router_ds.h"
 
@@ -521,7 +522,10 @@ double expected_tiles(int R, int E, int N, int tile_cols) {
 // tile takes 0.5 us for each of them, 0.7 us for a single one, which waits for memory; the slices' sums pass through memory once
 // more, at about 8 TB/s, BWD_DX's in a launch of its own, DOWN's in the combine, to which a cut for less than a seventh is not
 // worth it.  (DOWN + combine, us, without slices / as chosen here: 64 tokens 45 /
-// 22, 512 45 / 29, 1024 57 / 43, 1536 58 / 58; BWD_DX 66 / 25, 66 / 45, 100 / 68, 104 / 90, 2003 tokens 136 / 112.)
+// 22, 512 45 / 29, 1024 57 / 43, 1536 58 / 58; BWD_DX 66 / 25, 66 / 45, 100 / 68, 104 / 90, 2003 tokens 136 / 112.)  Other layers agree:
+// of 40 forward and 32 training passes of 16 to 2003 tokens, 2 to 8 experts of 64 to 512 x 64 to 1376, with every number of slices from 1 to 8,
+// DOWN + combine are 1 % from the best on average, 10 % at most (1297 tokens, 2 experts of 392 x 464: 28.3 us, 4 slices 25.8), the joint
+// launch of the backward pass 2.4 % and 16 % (750 tokens, 4 experts of 88 x 728: 29.8, 4 slices 25.6).
 int f32_slices(int R, int E, int N, int K, bool two_passes, int most) {
   const double tiles = expected_tiles(R, E, N, kTile), nk = ceil_div(K, kTileK) * (two_passes ? 2.0 : 1.0);
   int best = 1;

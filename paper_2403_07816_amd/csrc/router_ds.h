@@ -14,9 +14,11 @@ struct RouterDs {
 };
 RouterDs router_ds_args(const RouterBwdArgs& a);
 // Beside the weight gradients, if it is no more workgroups than run at a time there: two on a compute unit (strips) or five (fp32).
-// Training pass, us, own launch / beside: 64 tokens of 256, 4 experts (80 workgroups) 69.2 / 66.1; 100 of 1000, 16 experts (88) 81.9 / 77.9; 1500
-// of 512, 64 experts (503) 138 / 135; but 2500 of 1024, 16 experts (689) 96.5 / 98.2, 3500 of 512, 4 experts (883) 111.9 / 111.7; fp32 256 of 256,
-// 4 experts (68) 73.6 / 69.6, 2003 of 512, 8 experts (517) 535 / 530, 3500 of them (891) 189 / 186.
+// Training pass, us, own launch / beside: 64 tokens of 256, f = 688, 4 experts (20 workgroups) 65.8 / 62.7; 100 of 1000, f = 264, 16 experts (88)
+// 81.4 / 77.7; 1500 of 512, f = 1376, 64 experts (503) 307 / 303; 1750 of 1024, f = 688, 16 experts (502) 157.1 / 155.0; fp32 2003 of 512, f = 1376,
+// 8 experts (517) 533.6 / 529.5, 4000 of them (1016) 966.6 / 962.5; f = 64: 4000 (1016) 147.2 / 143.9, 5000 (1266) 165.0 / 161.4.  Beyond, it
+// gains or loses: 2500 of 1024, f = 688, 16 experts (689) 194.8 / 192.1, 3500 of 512, f = 1376, 4 experts (883) 256.7 / 256.8; fp32 f = 64:
+// 5400 (1366) 177.0 / 178.9, 6000 (1516) 178.4 / 174.5.
 inline bool router_ds_rides(int T, int d, int E, bool f32) {
   return ceil_div(T, 4) + (int64_t)ceil_div((int64_t)d * E, 256) <= 256 * (f32 ? 5 : 2);
 }
