@@ -87,10 +87,10 @@ def test_fp32_token_rows_past_4_gib():
         assert float((got - want).norm() / want.norm()) < TOL[F32] / 4
 
 
-def test_bf16_experts_whose_rows_need_64_bit_offsets():
-    """256 rows of f elements span 4 GiB: the down-projection and the input gradient find them with 64-bit offsets.  One expert, whose
-    gate is 1; against fp32 products, a piece of the columns at a time."""
-    T, d, f, pieces = 257, 264, 8421504, 16
+@pytest.mark.parametrize("T,d,f,pieces", [(257, 264, 8421504, 16), (66, 136, 34087048, 56)])
+def test_bf16_experts_whose_rows_need_64_bit_offsets(T, d, f, pieces):
+    """256 rows of f elements, or 64 of them, span 4 GiB: the down-projection and the input gradient (and the up-projection with 64 rows of
+    its weights) find them with 64-bit offsets.  One expert, whose gate is 1; against fp32 products, a piece of the columns at a time."""
     g = torch.Generator(device="cuda").manual_seed(6)
     def draw(*shape, scale=1.0):
         return torch.randn(shape, generator=g, device="cuda", dtype=BF16).mul_(scale)
@@ -125,6 +125,42 @@ def test_bf16_experts_whose_rows_need_64_bit_offsets():
     check(b.dX[rows], want_dX, "dX")
     del out, h1, h3, b, W1, W3, W2
     torch.cuda.empty_cache()
+
+
+def test_bf16_token_rows_that_need_64_bit_offsets():
+    """255 token rows of d elements would span 4 GiB: the up-projection and the activation's gradient run with 64-bit offsets.  Otherwise as above."""
+    T, d, f, pieces = 70, 8421504, 72, 16
+    g = torch.Generator(device="cuda").manual_seed(7)
+    def draw(*shape, scale=1.0):
+        return torch.randn(shape, generator=g, device="cuda", dtype=BF16).mul_(scale)
+    x, dY, W1, W3, W2 = draw(T, d), draw(T, d), draw(1, d, f, scale=d ** -0.5), draw(1, d, f, scale=d ** -0.5), draw(1, f, d, scale=f ** -0.5)
+    r = B.btx_moe_route(x, torch.zeros((d, 1), device="cuda"), None, None, 1, B.BTX_ROUTE_SWITCH_TOP1)
+    out, h1, h3 = B.btx_moe_ff_forward(x, W1, W3, W2, r)
+    b = B.btx_moe_ff_backward(dY, x, torch.zeros((d, 1), device="cuda"), W1, W3, W2, r, h1, h3, B.BTX_ROUTE_SWITCH_TOP1)
+
+    def check(got, want, what):
+        err = float((got.float() - want).norm() / want.norm())
+        assert err < TOL[BF16], f"{what}: {err:.2e}"
+    rows = torch.argsort(r.inv_pos.flatten().long())                # grouped row -> token
+    columns = [slice(p * d // pieces, (p + 1) * d // pieces) for p in range(pieces)]
+    want1, want3, da = (torch.zeros((T, f), device="cuda", dtype=torch.float64) for _ in range(3))
+    for c in columns:
+        xf, dYf = x[:, c].float()[rows], dY[:, c].float()[rows]
+        want1 += (xf @ W1[0, c].float()).double()
+        want3 += (xf @ W3[0, c].float()).double()
+        da += (dYf @ W2[0, :, c].float().t().contiguous()).double()
+    check(h1, want1, "h1")
+    check(h3, want3, "h3")
+    u1, u3 = h1.float(), h3.float()
+    s = torch.sigmoid(u1)
+    act, dh1, dh3 = (v.to(BF16).float() for v in (u1 * s * u3, da.float() * u3 * s * (1 + u1 * (1 - s)), da.float() * u1 * s))
+    for p, c in enumerate(columns):
+        w1, w3, xf, dYf = W1[0, c].float(), W3[0, c].float(), x[:, c].float()[rows], dY[:, c].float()[rows]
+        check(out[:, c][rows], act @ W2[0, :, c].float(), f"out, piece {p}")
+        check(b.dX[:, c][rows], dh1 @ w1.t().contiguous() + dh3 @ w3.t().contiguous(), f"dX, piece {p}")
+        check(b.dW1[0, c], xf.t().contiguous() @ dh1, f"dW1, piece {p}")
+        check(b.dW3[0, c], xf.t().contiguous() @ dh3, f"dW3, piece {p}")
+        check(b.dW2[0, :, c], act.t().contiguous() @ dYf, f"dW2, piece {p}")
 
 
 @pytest.mark.parametrize("mode", [B.BTX_ROUTE_SWITCH_TOP1, B.BTX_ROUTE_SAMPLE_TOP1])
