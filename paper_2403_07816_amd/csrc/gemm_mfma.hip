@@ -425,28 +425,46 @@ struct Gemm {
     Tile tile;
     if (!locate(g, experts, plan.id_full + j, tile)) return;
     const int col0 = tile.tile_n * BNH;
-    auto slices_sum = [&](int jj) {
-      const size_t at = (size_t)wave * (TM * TN * kWave) + (i * TN + jj) * kWave + lane;
-      f32x4 sum = __builtin_nontemporal_load(partial_slot(g, plan, j, 0) + at);
-      for (int sl = 1; sl < plan.n_slices; ++sl) {
-        const f32x4 v = __builtin_nontemporal_load(partial_slot(g, plan, j, sl) + at);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) sum[x] += v[x];
-      }
-      return sum;
-    };
     auto put = [&](void* C, size_t idx, const f32x4& v) {
       *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(C) + idx) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     };
     const int m0 = tile.row0 + wm * (TM * 16) + i * 16, m = m0 + (lane & 15);
     if (m0 >= tile.row_end) return;                      // 16 rows that do not exist: the slices left nothing there
+    // Latency: all fragments of up to four slices are requested together, and they were stored through the caches, which still hold
+    // most of them.  With streamed sums, a load waited for after another, us: 301 tokens, 4 experts of 4096 x 11008, UP (88 tiles of 2
+    // slices) 10.0, DOWN (64 of 4) 14.5, now 9.0 and 10.4; 4001 tokens, 8 of 2048 x 5504, DOWN 12.4, BWD_DX 19.0, now 6.4 and 8.0;
+    // 1501, 64 of 4096 x 688, UP 21.1, now 14.9; batches of four alone, streamed, 12.8 and 12.5, 9.5 and 9.7, 23.
+    f32x4 sum[TN] = {};
+    int sl = 0;
+    auto add = [&](auto batch) {
+      constexpr int B = decltype(batch)::value;
+      for (; sl + B <= plan.n_slices; sl += B) {
+        f32x4 v[B][TN];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+          const f32x4* from = partial_slot(g, plan, j, sl + b) + (size_t)wave * (TM * TN * kWave) + i * TN * kWave + lane;
+#pragma unroll
+          for (int jj = 0; jj < TN; ++jj) v[b][jj] = from[jj * kWave];
+        }
+        __builtin_amdgcn_sched_barrier(0);               // no sum in front of a load
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+          for (int jj = 0; jj < TN; ++jj)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sum[jj][x] = sl + b == 0 ? v[b][jj][x] : sum[jj][x] + v[b][jj][x];
+      }
+    };
+    add(std::integral_constant<int, 4>{});
+    add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 1>{});
 #pragma unroll
     for (int jj = 0; jj < TNH; ++jj) {
       const int n = col0 + wn * (TNH * 16) + jj * 16 + 4 * (lane >> 4);
       const bool inside = m < tile.row_end && n < g.N;
       const size_t idx = (size_t)m * g.ldc + n;
       if constexpr (MODE == UP) {                        // fragment jj holds x W1, fragment jj + TNH x W3 of the same outputs
-        const f32x4 h1 = slices_sum(jj), h3 = slices_sum(jj + TNH);
+        const f32x4 h1 = sum[jj], h3 = sum[jj + TNH];
         f32x4 a;
 #pragma unroll
         for (int x = 0; x < 4; ++x) a[x] = silu_f(h1[x]) * h3[x];
@@ -455,8 +473,7 @@ struct Gemm {
           put(g.C2, idx, a);
         }
       } else {
-        const f32x4 sum = slices_sum(jj);
-        if (inside) put(g.C0, idx, sum);
+        if (inside) put(g.C0, idx, sum[jj]);
       }
     }
   }
@@ -855,7 +872,7 @@ struct Gemm {
       for (int i = 0; i < TM; ++i) {
         if (row0 + wm * (TM * 16) + i * 16 >= row_end) break;          // finish() does not look at these rows
 #pragma unroll
-        for (int j = 0; j < TN; ++j) __builtin_nontemporal_store(acc[i][j], slot + (i * TN + j) * kWave + lane);
+        for (int j = 0; j < TN; ++j) slot[(i * TN + j) * kWave + lane] = acc[i][j];   // plain: they are read back at once
       }
       return;
     }
