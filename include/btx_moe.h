@@ -109,7 +109,8 @@ enum {
   BTX_STAGE_ROUTE = 0,        /* btx_moe_route: its two or four kernels            */
   BTX_STAGE_GATHER_X = 1,     /* forward: x -> expert-grouped rows (bf16, only when
                                   x has 2^32 bytes or more: else UP reads x itself)  */
-  BTX_STAGE_UP = 2,           /* forward: xs W1, xs W3, SwiGLU                     */
+  BTX_STAGE_UP = 2,           /* forward: xs W1, xs W3, SwiGLU; small fp32 layers:
+                                  and the work of DOWN, which is then empty          */
   BTX_STAGE_DOWN = 3,         /* forward: act W2                                   */
   BTX_STAGE_COMBINE = 4,      /* forward: gate-weighted un-permute                 */
   BTX_STAGE_GATHER_DY = 5,    /* backward: dY -> grouped rows (as GATHER_X)        */

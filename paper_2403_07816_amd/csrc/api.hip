@@ -1,5 +1,6 @@
 // C ABI of the library: argument validation, workspace carving, and the order in which
 // the stages of the layer are enqueued.  See include/btx_moe.h for the contract.
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
@@ -275,11 +276,22 @@ int btx_moe_ff_forward(const void* x, const void* W1, const void* W3, const void
   const bool fused = ff_gather_fused(dtype, T, d);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_X, launch_gather_rows(x, w.xs, perm, R, k, d, dtype, s));
   const RowSource xs = fused ? RowSource{x, perm, k} : RowSource{w.xs, nullptr, 1};
-  BTX_STAGE(BTX_STAGE_UP, launch_up_swiglu(dtype, xs, W1, W3, offsets, sh, save_h1, save_h3, w.act, w.partial, s));
   int y_slices = combine_most_slices(T, k, dtype);
-  BTX_STAGE(BTX_STAGE_DOWN, launch_down(dtype, w.act, W2, offsets, sh, w.y, w.partial, &y_slices, s));
-  BTX_STAGE(BTX_STAGE_COMBINE, launch_combine(w.y, static_cast<const float*>(w.partial), y_slices, gates, inv_pos,
-                                              residual, out, T, k, d, dtype, s));
+  // a small fp32 layer keeps no act: the sums of its slices lie where act, y and the sums of y's slices would, as many as fit there
+  const int64_t room = (static_cast<char*>(workspace) + w.bytes - static_cast<char*>(w.act)) / ((int64_t)R * d * 4);
+  const int ff_slices = dtype == BTX_F32 ? f32_ff_slices(sh, std::min<int64_t>(y_slices, room)) : 0;
+  const void* y = w.y;
+  const void* y_sums = w.partial;
+  if (ff_slices) {
+    BTX_STAGE(BTX_STAGE_UP, f32_ff(xs, W1, W3, W2, offsets, sh, save_h1, save_h3, w.act, s));
+    BTX_STAGE(BTX_STAGE_DOWN, BTX_OK);                   // events with nothing between them
+    y = y_sums = w.act;
+    y_slices = ff_slices;
+  } else {
+    BTX_STAGE(BTX_STAGE_UP, launch_up_swiglu(dtype, xs, W1, W3, offsets, sh, save_h1, save_h3, w.act, w.partial, s));
+    BTX_STAGE(BTX_STAGE_DOWN, launch_down(dtype, w.act, W2, offsets, sh, w.y, w.partial, &y_slices, s));
+  }
+  BTX_STAGE(BTX_STAGE_COMBINE, launch_combine(y, static_cast<const float*>(y_sums), y_slices, gates, inv_pos, residual, out, T, k, d, dtype, s));
   return BTX_OK;
 }
 

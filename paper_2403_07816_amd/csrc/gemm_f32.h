@@ -16,6 +16,11 @@ size_t f32_bwd_dx_sums_bytes(const FfShapes& sh);
 // slices: see launch_down()
 int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices,
              hipStream_t s);
+// Both products of a small layer in one launch: y is left as the sums of slices of f, [slice][R, d], f32_ff_slices() of them (0: not
+// such a layer, or more than `most`)
+int f32_ff_slices(const FfShapes& sh, int64_t most);
+int f32_ff(const RowSource& xs, const void* W1, const void* W3, const void* W2, const int32_t* off, const FfShapes& sh, void* h1, void* h3,
+           void* sums, hipStream_t s);
 int f32_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                 const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
                 uint32_t* row_bytes, float* dg_part, hipStream_t s);

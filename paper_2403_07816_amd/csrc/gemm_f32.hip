@@ -600,7 +600,145 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullpt
   return g.slices > 1 && !leave ? finish_slices(g, R, s) : BTX_OK;
 }
 
+// The whole feed-forward of a small layer (f32_ff_slices()) in one launch: UP and DOWN are two launches of about 5 us there, each a
+// few k tiles long and bound by its waits for memory.  A workgroup of 4 wavefronts takes 16 grouped rows and 64 of the f columns: its piece
+// of act stays in LDS, its products with the same 64 rows of W2 are a slice of y, which the combine adds up as it adds K slices.
+// Weights go straight from memory to the registers as each is used once for the 16 rows, all of a piece requested together, W2's
+// first while W1's and W3's are on their way; the wavefronts share the k of both products and add up their sums in LDS, in their
+// order.  512 tokens of 64 columns, f = 176, 4 experts: the two launches and the combine 10.9 us, with this 7.7.
+struct FfArgs {
+  const float* x; const float* W1; const float* W3; const float* W2;
+  const int32_t* perm; int k;            // row r is token perm[r] / k
+  const int32_t* offsets; int E, d, f;
+  int64_t s13, s2;                       // expert strides
+  float* h1; float* h3;                  // [R, f] (NULL: not kept)
+  float* sums; int R, slices;            // [slice][R, d]: of 64 f columns each, whoever reads them adds them up
+};
+constexpr int kFfRows = 16, kFfCols = 64;
+
+__global__ __launch_bounds__(kThreads, 4) void f32_ff_kernel(FfArgs g) {
+  constexpr int PITCH = kFfCols + 4;                     // floats of a row in LDS: 16 lanes of as many rows reach all banks
+  __shared__ __attribute__((aligned(16))) float part[2][4][kFfRows * PITCH], act[kFfRows * PITCH];
+  const int lane = threadIdx.x & (kWave - 1), r = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  // each XCD takes one eighth of the ids: of an expert's 64 columns all row tiles, so that its L2 keeps their weights
+  const RowTiles rt(g.offsets, g.E, kFfRows, lane);
+  const int total = rt.count() * g.slices, share = (total + 7) / 8, pos = (int)(blockIdx.x / 8), id = (int)(blockIdx.x % 8) * share + pos;
+  if (pos >= share || id >= total) return;
+  int e, n_rows, local, row0, row_end;
+  rt.expert_of(id, g.slices, e, n_rows, local);
+  const int slice = local / n_rows, col0 = slice * kFfCols;
+  rt.rows_of(e, local - slice * n_rows, row0, row_end);
+  auto ld = [](const float* p, bool in) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+    return in ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // a lane's 4 columns of 4 k rows: k rows 4 g4 + x and columns 4 r + j go to instruction x of fragment j
+  const float* const W2 = g.W2 + e * g.s2;
+  const int k2 = col0 + 16 * wave + 4 * g4;              // rows of W2, the wavefronts sharing the 64 out
+  f32x4 w2[4];
+  auto load_w2 = [&](int c0) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) w2[x] = ld(W2 + (int64_t)min(k2 + x, g.f - 1) * g.d + min(c0 + 4 * r, g.d - 4), k2 < g.f);
+  };
+  load_w2(0);
+  const float* const xr = g.x + (int64_t)(g.perm[min(row0 + r, row_end - 1)] / g.k) * g.d;
+  const int64_t panel = e * g.s13 + min(col0 + 4 * r, g.f - 4);
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[p][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int s = wave; 16 * s < g.d; s += 4) {             // 16 k at a time, the wavefronts in turn
+    const bool in = 16 * s + 4 * g4 < g.d;
+    const int k = in ? 16 * s + 4 * g4 : 0;
+    const f32x4 a = ld(xr + k, in);
+    f32x4 b[2][4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      b[0][x] = ld(g.W1 + panel + (int64_t)(k + x) * g.f, in);
+      b[1][x] = ld(g.W3 + panel + (int64_t)(k + x) * g.f, in);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[p][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[p][x][j], a[x], acc[p][j], 0, 0, 0);
+  }
+  // this lane's sums of row r: columns 16 g4 + 4 v + j
+  auto put = [&](float* to, const f32x4 (&c)[4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) *reinterpret_cast<f32x4*>(to + r * PITCH + 16 * g4 + 4 * v) = f32x4{c[0][v], c[1][v], c[2][v], c[3][v]};
+  };
+  const int row = threadIdx.x >> 4, c4 = 4 * (threadIdx.x & 15), m = row0 + row;
+  auto sum = [&](const float (&from)[4][kFfRows * PITCH]) {   // the wavefronts' sums, in their order
+    f32x4 t = *reinterpret_cast<const f32x4*>(from[0] + row * PITCH + c4);
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const f32x4 u = *reinterpret_cast<const f32x4*>(from[w] + row * PITCH + c4);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) t[x] += u[x];
+    }
+    return t;
+  };
+  put(part[0][wave], acc[0]);
+  put(part[1][wave], acc[1]);
+  __syncthreads();
+  {
+    const f32x4 h1 = sum(part[0]), h3 = sum(part[1]);
+    const bool in = col0 + c4 < g.f;
+    f32x4 a;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) a[x] = in ? silu_f(h1[x]) * h3[x] : 0.f;
+    *reinterpret_cast<f32x4*>(act + row * PITCH + c4) = a;
+    if (g.h1 && in && m < row_end) {
+      const int64_t at = (int64_t)m * g.f + col0 + c4;
+      *reinterpret_cast<f32x4*>(g.h1 + at) = h1;
+      *reinterpret_cast<f32x4*>(g.h3 + at) = h3;
+    }
+  }
+  __syncthreads();
+  const f32x4 a = *reinterpret_cast<const f32x4*>(act + r * PITCH + 16 * wave + 4 * g4);
+  float* const out = g.sums + ((int64_t)slice * g.R + m) * g.d + c4;
+  for (int c0 = 0, buf = 0; c0 < g.d; c0 += kFfCols, buf ^= 1) {
+    f32x4 c[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[x][j], a[x], c[j], 0, 0, 0);
+    if (c0 + kFfCols < g.d) load_w2(c0 + kFfCols);
+    put(part[buf][wave], c);
+    __syncthreads();                                     // (the other half is free: its sums were read before this barrier)
+    const f32x4 y = sum(part[buf]);
+    if (m < row_end && c0 + c4 < g.d) *reinterpret_cast<f32x4*>(out + c0) = y;
+  }
+}
+
 }  // namespace
+
+// Small layers, up to 192 columns and 47 million products (rows x d x f), by 95 forward calls of 16 to 2003 tokens, 2 to 8 experts, on both
+// ways (us, UP and DOWN / joint): 512 tokens of 64, f = 176, 4 experts 10.9 / 7.7; 77 of 64, f = 208, 5 11.0 / 7.4; 1000 of 64, f = 128, 8, top-4
+// 13.1 / 9.1; 458 of 96, f = 208, 2 12.2 / 10.0; 249 of 128, f = 664, 4 (42 million) 14.0 / 12.9; 69 of 192, f = 192, 5 12.4 / 11.7.  Above, 16
+// rows to a tile read the weights too often, and wide rows are a chain of passes: 400 of 192, f = 320, 5 (49) 14.7 / 14.8; 547 of 232, f =
+// 240, 5 (61) 16.6 / 17.7; 1064 of 144, f = 208, 5 (64) 15.6 / 18.0; 1349 of 168, f = 416, 5 (189) 26.7 / 31.7; 100 of 504, f = 64, 2 19.2 / 22.7.
+int f32_ff_slices(const FfShapes& sh, int64_t most) {
+  const int slices = ceil_div(sh.f, kFfCols);
+  return sh.d <= 192 && (int64_t)sh.R * sh.d * sh.f <= 47000000 && slices <= most ? slices : 0;
+}
+int f32_ff(const RowSource& xs, const void* W1, const void* W3, const void* W2, const int32_t* off, const FfShapes& sh, void* h1, void* h3,
+           void* sums, hipStream_t s) {
+  FfArgs g{(const float*)xs.base, (const float*)W1, (const float*)W3, (const float*)W2, xs.perm, xs.k, off, sh.E, sh.d, sh.f, sh.s13, sh.s2,
+           (float*)h1, (float*)h3, (float*)sums, sh.R, ceil_div(sh.f, kFfCols)};
+  const int64_t blocks = ((int64_t)ceil_div(sh.R, kFfRows) + sh.E) * g.slices;
+  if (!grid_fits(blocks + 7, kThreads)) return BTX_ERR_UNSUPPORTED;
+  f32_ff_kernel<<<(unsigned)align_up((size_t)blocks, 8), kThreads, 0, s>>>(g);
+  BTX_LAUNCH_CHECK();
+  return BTX_OK;
+}
 
 bool f32_rows_ok(int R, int E) { return ceil_div(R, 64) + E <= 65535; }
 int f32_bwd_act_partials(int f) { return ceil_div(f, kTile); }

@@ -51,6 +51,14 @@ TRANSPOSED_ROWS = [
     (1500, 520, 3608, 4, 1, dict(bias=[3.0, 0.0, 0.0, 0.0], poison=True)),
 ]
 
+# small fp32 layers, both products of the forward pass in one launch: 1 to 17 rows of a tile of 16; widths below, at and past one and
+# several pieces of 64, contractions that end inside 16; dropped pairs, experts without rows; as many slices as the combine takes
+JOINT_FORWARD = [
+    (1, 8, 8, 1, 1, {}), (15, 64, 64, 1, 1, {}), (16, 72, 72, 1, 1, {}), (17, 56, 120, 1, 1, {}), (33, 192, 136, 2, 1, {}),
+    (64, 128, 56, 4, 2, dict(poison=True)), (512, 64, 176, 4, 2, dict(cf=0.8, poison=True)), (90, 136, 320, 64, 4, dict(poison=True)),
+    (40, 184, 776, 2, 2, dict(poison=True)), (100, 24, 1376, 3, 2, dict(bias=[4.0, 0.0, -60.0])), (1270, 192, 192, 3, 1, {}), (50, 40, 512, 8, 8, {}),
+]
+
 # many tokens' routing: (T, d, E, k, dtype, with the normalisation) -> experts of a pass over the columns, wavefronts that share 16
 # tokens.  Ragged last blocks; one workgroup on a compute unit, two, more.
 ROUTE_MANY = [

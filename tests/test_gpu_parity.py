@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import FEW_K_TILES, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +57,11 @@ def test_fp32_products_cut_along_k(T, d, f, E, k, kw):
 def test_fp32_up_projection_with_three_stages(T, d, f, E, k):
     """Last k tiles of 8, 16, 24 and 32, 22 to 173 of them, one and two row tiles to an expert."""
     run_layer_and_check(T, d, f, E, k, F32, unit_rms=True, backward=False, poison=True)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", JOINT_FORWARD)
+def test_fp32_small_layers_forward_in_one_launch(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, F32, **kw)
 
 
 def test_fp32_token_rows_past_4_gib():
