@@ -1,15 +1,17 @@
-"""Compile the HIP sources under csrc/ into libbtx_moe.so (gfx950 only), in-tree."""
+"""Compile the HIP sources under csrc/ into libbtx_moe.so (gfx950 only), and the binding's marshal.cpp into _marshal.so, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libbtx_moe.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,11 +32,26 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_marshal() -> None:
+    """Host code against the headers of Python and of the torch that is installed; their libraries are loaded wherever it is."""
+    import torch                                     # (where it lies; nothing of it runs)
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", INCLUDE,
+           "-I", os.path.join(base, "include"), "-I", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for marshal.cpp:\n{r.stderr}")
+
+
 def build(verbose: bool = True, jobs: int = 8) -> str:
     """Always recompiles every translation unit and relinks the library."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_compile_marshal)
         objs = list(ex.map(_compile, sources()))
+        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

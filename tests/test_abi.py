@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2403_07816_amd import binding as B
 
@@ -205,3 +206,33 @@ def test_missing_library_raises(monkeypatch):
     monkeypatch.setattr(B, "LIB_PATH", "/nonexistent/libbtx_moe.so")
     with pytest.raises(RuntimeError):
         B.load_library()
+
+
+def marshalled_calls():
+    """(call, arguments) of every entry point that _marshal serves, on host tensors: nothing is launched."""
+    T, d, f, E, k = 6, 16, 24, 3, 2
+    x, Wr = torch.zeros(T, d), torch.zeros(d, E)
+    W1, W3, W2 = torch.zeros(E, d, f), torch.zeros(E, d, f), torch.zeros(E, f, d)
+    r, h = B.alloc_routing(T, E, k, "cpu"), torch.zeros(T * k, f)
+    ws = torch.empty(1 << 20, dtype=torch.uint8)
+    return {"route": (B.btx_moe_route, [x, Wr], dict(out=r, workspace=ws)),
+            "norm_route": (B.btx_moe_norm_route, [x, torch.zeros(d), 1e-5, Wr], dict(out=r, workspace=ws)),
+            "forward": (B.btx_moe_ff_forward, [x, W1, W3, W2, r], dict(workspace=ws)),
+            "backward": (B.btx_moe_ff_backward, [x, x, Wr, W1, W3, W2, r, h, h], dict(workspace=ws))}
+
+
+@pytest.mark.parametrize("entry,position,wrong,error", [
+    # host memory, in all of them; then one argument at a time
+    *[(entry, None, None, AssertionError) for entry in ("route", "norm_route", "forward", "backward")],
+    ("route", 0, lambda x: x[0], ValueError), ("route", 0, lambda x: x.double(), TypeError), ("route", 1, lambda W: W.bfloat16(), AssertionError),
+    ("route", 1, lambda W: W[1:], AssertionError), ("route", 0, lambda x: 3, AttributeError),
+    ("norm_route", 1, lambda g: g[1:], AssertionError), ("norm_route", 1, lambda g: g.double(), AssertionError), ("norm_route", 2, lambda eps: "1", TypeError),
+    ("forward", 1, lambda W: W.transpose(1, 2), AssertionError), ("forward", 1, lambda W: W.bfloat16(), AssertionError),
+    ("forward", 2, lambda W: W[:, :, 8:], AssertionError), ("forward", 3, lambda W: W[:2], AssertionError), ("forward", 3, lambda W: W[0], AssertionError),
+    ("forward", 4, lambda r: None, AttributeError), ("backward", 3, lambda W: W[:, ::2], AssertionError), ("backward", 6, lambda r: None, AttributeError)])
+def test_arguments_that_do_not_fit_are_refused_in_the_binding(lib, entry, position, wrong, error):
+    call, args, options = marshalled_calls()[entry]
+    if position is not None:
+        args[position] = wrong(args[position])
+    with pytest.raises(error):
+        call(*args, **options)

@@ -484,6 +484,21 @@ def test_bf16_row_tiles(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, **kw)
 
 
+@pytest.mark.parametrize("nbytes", [None, 0, 300])
+def test_a_workspace_that_is_too_small_is_replaced(nbytes):
+    """The binding hands a workspace of its own to the calls, with the same results."""
+    T, d, f, E, k = 70, 64, 96, 4, 2
+    G = to_dev(synth.make_layer(T, d, f, E, dtype=F32, with_dY=True))
+    def run(ws):
+        r = B.btx_moe_route(G["x"], G["W_router"], k=k, workspace=ws)
+        out, h1, h3 = B.btx_moe_ff_forward(G["x"], G["W1"], G["W3"], G["W2"], r, workspace=ws)
+        g = B.btx_moe_ff_backward(G["dY"], G["x"], G["W_router"], G["W1"], G["W3"], G["W2"], r, h1, h3, workspace=ws)
+        return out, r.gates, g.dX, g.dW1, g.dW2
+    expected = run(torch.empty(1 << 24, dtype=torch.uint8, device="cuda"))
+    for a, b in zip(expected, run(None if nbytes is None else torch.empty(nbytes, dtype=torch.uint8, device="cuda"))):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("T,d,f,E,k,dtype", [
     (16, 4096, 1024, 4, 2, BF16), (301, 1032, 4104, 4, 2, BF16), (33, 72, 2056, 4, 2, BF16), (40, 2056, 72, 5, 2, BF16),
     (900, 256, 2048, 4, 1, BF16), (210, 2056, 520, 4, 2, BF16), (260, 4104, 768, 16, 8, BF16), (2050, 1032, 8192, 2, 1, BF16),
