@@ -117,7 +117,7 @@ enum {
   BTX_STAGE_BWD_ACT = 6,      /* backward: dys W2^T + SwiGLU backward              */
   BTX_STAGE_BWD_DX = 7,       /* backward: dh1 W1^T + dh3 W3^T; fp32: and the work of
                                   DW13 and DW2, which are then empty                */
-  BTX_STAGE_GATHER_X_BWD = 8, /* backward: x and dY -> transposed grouped rows for
+  BTX_STAGE_GATHER_X_BWD = 8, /* backward: x (and dY) -> transposed grouped rows for
                                   the weight gradients (bf16 and experts of many rows; none
                                   with frozen experts)                              */
   BTX_STAGE_DW13 = 9,         /* backward: dW1, dW3; bf16 without GATHER_X_BWD: and

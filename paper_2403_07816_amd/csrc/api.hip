@@ -338,7 +338,9 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
-  uint32_t* row_bytes = direct && n_dw == 3 ? w.row_bytes : nullptr;   // of weight gradients that read token rows
+  // of weight gradients that read token rows: all of them, or (tiles) dW2, where transposed rows of dY would lie
+  const bool dw2_rows = dtype == BTX_BF16 && !direct && fused && mfma_dw2_rows(f);
+  uint32_t* row_bytes = n_dw != 3 ? nullptr : direct ? w.row_bytes : dw2_rows ? static_cast<uint32_t*>(w.dysT) : nullptr;
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));
   RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,
@@ -360,9 +362,10 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
     BTX_STAGE(BTX_STAGE_DW13, mfma_bwd_dw_direct(dW_dtype, dw_x, dw_dy, w.dh1, w.dh3, w.ga, offsets, sh, row_bytes, dW1, dW3, dW2, ds, s));
     BTX_STAGE(BTX_STAGE_DW2, BTX_OK);
   } else if (n_dw == 3 && dtype == BTX_BF16) {
-    BTX_STAGE(BTX_STAGE_GATHER_X_BWD, launch_gather_rows_t(x, w.xsT, dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
+    BTX_STAGE(BTX_STAGE_GATHER_X_BWD,
+              launch_gather_rows_t(x, w.xsT, dw2_rows ? nullptr : dY, w.dysT, perm, offsets, R, k, d, E, ff_dw_pitch(R, E), s));
     BTX_STAGE(BTX_STAGE_DW13, mfma_bwd_dw13(dW_dtype, {w.xsT, nullptr, 1}, w.dh1, w.dh3, offsets, sh, dW1, dW3, s));
-    BTX_STAGE(BTX_STAGE_DW2, mfma_bwd_dw2(dW_dtype, w.ga, {w.dysT, nullptr, 1}, offsets, sh, dW2, s));
+    BTX_STAGE(BTX_STAGE_DW2, mfma_bwd_dw2(dW_dtype, w.ga, dw2_rows ? dw_dy : RowSource{w.dysT, nullptr, 1}, offsets, sh, row_bytes, dW2, s));
   }
   BTX_STAGE(BTX_STAGE_ROUTER_BWD, launch_router_bwd(ra, ds_rides, s));
   return BTX_OK;

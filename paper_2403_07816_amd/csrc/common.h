@@ -258,7 +258,7 @@ int launch_route(const RouteArgs& a, hipStream_t s);
 // rows: dst[r] = src[perm[r] / k]  (k = 1 with perm = NULL copies nothing; perm required)
 int launch_gather_rows(const void* src, void* dst, const int32_t* perm, int R, int k, int d, int dtype, hipStream_t s);
 // bf16 only: dst[c][P_e + i] = src[perm[o_e + i] / k][c], every expert's rows padded with zeros to a
-// multiple of 64 (P_e = padded rows of the experts before e); dst is [d][pitch].  Two such matrices in one launch.
+// multiple of 64 (P_e = padded rows of the experts before e); dst is [d][pitch].  Two such matrices in one launch (src1 NULL: one).
 int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* dst1, const int32_t* perm,
                          const int32_t* offsets, int R, int k, int d, int E, int pitch, hipStream_t s);
 // out[t] = sum_j gates[t,j] * y[inv_pos[t,j]]   (gates NULL => unit weights; inv_pos < 0: dropped pair, skipped)

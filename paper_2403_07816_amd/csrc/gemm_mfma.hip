@@ -171,15 +171,16 @@ template <bool STREAM, typename V> __device__ __forceinline__ void store_out(V* 
 
 // TAIL: see run(); kWideTail: any K, and operands whose rows lie too far apart for 32-bit offsets inside a tile
 constexpr int kWideTail = 3;
-// STREAM_B: the weights past the caches (stream_weights())
+// STREAM_B: the weights past the caches (stream_weights()); ROWS: DW2 whose B is token rows (mfma_dw2_rows())
 template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0, bool STREAM_B = false,
-          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
+          bool STREAM = MODE == BWD_ACT || MODE == DOWN, bool ROWS = false>
 struct Gemm {
   // K index contiguous in memory?  A always is.  In the dW products K is the grouped-row index:
   // x (dW1/dW3) and ga, dY (dW2) arrive here transposed, [columns][padded rows], every expert's rows
-  // starting at a multiple of 64 and zero-filled up to the next one; dh1/dh3 stay row-major.
+  // starting at a multiple of 64 and zero-filled up to the next one; dh1/dh3 stay row-major, and so do the token rows of ROWS.
   static constexpr bool A_KC = true;
-  static constexpr bool B_KC = (MODE != UP && MODE != DOWN && MODE != DW13);
+  static constexpr bool B_KC = (MODE != UP && MODE != DOWN && MODE != DW13 && !ROWS);
+  static_assert(!ROWS || MODE == DW2, "token rows as B");
   static constexpr bool DUAL = (MODE == UP || MODE == DW13);
   static constexpr bool GROUP_K = (MODE == DW13 || MODE == DW2);
   typedef std::conditional_t<TAIL == kWideTail, uint64_t, uint32_t> Off;   // bytes from the base of a tile's copies on
@@ -552,7 +553,7 @@ struct Gemm {
         b_kc[q] = 0;
         b_k[q] = major;
         b_c[q] = min(col0 + minor, g.N - 8);
-        b_off[q] = copy_off<B_LOADS>(((Off)major * (Off)g.ldb + (Off)b_c[q]) * 2u, q);
+        b_off[q] = copy_off<B_LOADS>(((Off)(ROWS ? 0 : major) * (Off)g.ldb + (Off)b_c[q]) * 2u, q);
       }
     }
 
@@ -612,7 +613,34 @@ struct Gemm {
       }
       put_a(sourceA(kt), off, ldsA + (kt % NSA) * A_BYTES);
     };
+    // ROWS: the 8 token rows of k tile kt that this wavefront copies, by the byte offsets that BWD_ACT left, through the scalar cache
+    // (vector loads would be waited for together with the copies behind them); rows past the expert's last repeat it
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8), aligned(4)));
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+    typedef const __attribute__((address_space(4))) u32x8* scalar_ptr8;
+    uint32_t tok[8];
+    Off row_off[ROWS ? B_LOADS : 1];                     // of the k tile whose rows are copied next
+    auto look_up = [&](int kt) {
+      const int k = kt * BK + wave * 8;
+      const scalar_ptr table = (scalar_ptr)(uintptr_t)g.row_bytes + k_begin;
+      if (k + 8 <= k_len) {
+        const u32x8 t = *(scalar_ptr8)(table + k);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) tok[x] = t[x];
+      } else {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) tok[x] = table[min(k + x, k_len - 1)];
+      }
+    };
+    auto next_rows = [&]() {
+#pragma unroll
+      for (int q = 0; q < B_LOADS; ++q) row_off[q] = b_off[q] + (lane < 32 ? tok[2 * q] : tok[2 * q + 1]);
+    };
     auto issueB = [&](int kt) {
+      if constexpr (ROWS) {
+        put_b(uniform64(g.B0) - copy_bias(B_LOADS), row_off, ldsB + (kt % NSB) * B_BYTES);
+        return;
+      }
       bool pass2;
       const int k0 = tile_k0(kt, B_KC, pass2);
       Off off[B_LOADS];
@@ -675,6 +703,16 @@ struct Gemm {
       }
     };
 
+    // ROWS: token rows that repeat the expert's last one meet zeros, which an infinity there would not survive
+    auto zero_rows_past = [&](bf16x8 (&bfr)[TN], int kt, int ks) {
+      const int left = k_len - kt * BK - 32 * ks - 8 * (lane >> 4);
+      u32x4 mask;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) mask[x] = (2 * x < left ? 0xffffu : 0u) | (2 * x + 1 < left ? 0xffff0000u : 0u);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bfr[j] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, bfr[j]) & mask);
+    };
+
     if constexpr (SMALL) {
       // One pipeline for all wavefronts: A tiles are requested NSA - 1 k tiles ahead, B tiles NSB - 1, one barrier
       // per k tile.  A's copies are issued before B's, so that of what may be outstanding when tile kt is needed
@@ -732,9 +770,18 @@ struct Gemm {
       auto issue_near = [&](int kt) { if constexpr (DEEP_B) issueA(kt); else issueB(kt); };
       auto issue_deep = [&](int kt) { if constexpr (DEEP_B) issueB(kt); else issueA(kt); };
       if (nk > 0) {
+        if constexpr (ROWS) {
+          look_up(0);
+          next_rows();
+        }
         issue_deep(0);
         issue_near(0);
         if (nk > 1) issue_deep(1);
+        if constexpr (ROWS) {
+          look_up(1);
+          next_rows();
+          look_up(2);
+        }
         if (nk > 1) wait_vmcnt<DEEP_LOADS>(); else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();                // tile 0 published
       }
@@ -806,6 +853,7 @@ struct Gemm {
           // ---- memory phase: copies first, they take longer
           if constexpr (fast) {
             if ((h == 0) == DEEP_B) put_a(mv.a, a_off, mv.to_a);
+            else if constexpr (ROWS) put_b(uniform64(g.B0) - copy_bias(B_LOADS), row_off, mv.to_b);
             else put_b(mv.b, b_off, mv.to_b);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -823,11 +871,19 @@ struct Gemm {
 #pragma unroll
             for (int x = 0; x < HS; ++x) zero_past(fa[x], h * HS + x);
           }
+          if (ROWS && !fast && (kt + 1) * BK > k_len) {
+#pragma unroll
+            for (int x = 0; x < HS; ++x) zero_rows_past(fb[x], kt, h * HS + x);
+          }
           if (h == 1 && grp == 1) landed();
           __builtin_amdgcn_sched_barrier(0);
           __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
           // ---- compute phase
+          if constexpr (ROWS) {                          // looked up half a k tile before, waited for with the fragments
+            if (h == 0) next_rows();                     // of k tile kt + 2
+            else look_up(kt + 3);
+          }
 #pragma unroll
           for (int x = 0; x < HS; ++x) mfma_step(fa[x], fb[x]);
           if (h == 1 && grp == 0) landed();
@@ -1125,6 +1181,12 @@ template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, in
 __global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel(MArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>::run(g, smem);
+}
+// dW2 from token rows of dY (mfma_dw2_rows())
+template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL, bool STREAM_B, bool STREAM>
+__global__ __launch_bounds__(WM* WN* kWave) void mfma_gemm_kernel_rows(MArgs g) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM, true>::run(g, smem);
 }
 
 // small tiles: 4 wavefronts, two workgroups per compute unit
@@ -1497,10 +1559,13 @@ template <auto Kernel, int LDS_BYTES> int raise_lds_limit() {
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NSA, int NSB, int MODE, int TAIL = 0, bool STREAM_B = false,
-          bool STREAM = MODE == BWD_ACT || MODE == DOWN>
+          bool STREAM = MODE == BWD_ACT || MODE == DOWN, bool ROWS = false>
 int launch(MArgs g, bool prepare_only, hipStream_t s) {
-  using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL>;
-  constexpr auto kernel = mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>;
+  using G = Gemm<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM, ROWS>;
+  constexpr auto kernel = [] {
+    if constexpr (ROWS) return mfma_gemm_kernel_rows<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>;
+    else return mfma_gemm_kernel<BM, BN, BK, WM, WN, NSA, NSB, MODE, TAIL, STREAM_B, STREAM>;
+  }();
   if (int rc = raise_lds_limit<kernel, G::LDS_BYTES>()) return rc;
   if (prepare_only) return BTX_OK;
   constexpr int BNH = G::DUAL ? BN / 2 : BN;
@@ -1742,6 +1807,10 @@ bool stream_strips(const MArgs& g) {
 }
 template <int MODE> int launch_dw(const MArgs& g, bool stream, bool prepare_only, hipStream_t s) {
   if constexpr (MODE == DW2)
+    if (g.row_bytes)
+      return stream ? launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, true, true>(g, prepare_only, s)
+                    : launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, false, true>(g, prepare_only, s);
+  if constexpr (MODE == DW2)
     if (stream) return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, true>(g, prepare_only, s);
   return launch<256, 256, 64, 2, 4, 3, 2, MODE, 0, false, false>(g, prepare_only, s);
 }
@@ -1750,6 +1819,10 @@ int prepare_dw() {
   for (bool stream : {false, true}) {
     if (int rc = launch_dw<DW13>(g, stream, true, nullptr)) return rc;
     if (int rc = launch_dw<DW2>(g, stream, true, nullptr)) return rc;
+    MArgs rows{};
+    uint32_t any = 0;
+    rows.row_bytes = &any;
+    if (int rc = launch_dw<DW2>(rows, stream, true, nullptr)) return rc;
     for (bool stream2 : {false, true}) {
       if (int rc = launch_dw_strips<float>(g, g, nullptr, stream, stream2, true, nullptr)) return rc;
       if (int rc = launch_dw_strips<bf16_t>(g, g, nullptr, stream, stream2, true, nullptr)) return rc;
@@ -1860,6 +1933,14 @@ bool mfma_dw_direct(const FfShapes& sh, int dW_dtype) {
   return rows * sh.f <= (sh.d < 512 ? 700000 : 1300000);
 }
 
+// dW2 of 256 x 256 tiles from token rows of dY as they lie, turned around by transposing reads as dh1 and dh3 are, or from rows that the
+// gather has transposed with x's?  Rows spare half of that gather, the same for experts of any width, and take a quarter more reads from
+// LDS per product and the looking up of the rows.  Backward pass, us, transposed / rows: 16384 tokens, 32 experts of 4096 x 1376, top-8
+// 8364 / 8077 (the gather 677 / 341, dW2 1217 / 1290); 64 of 4096 x 688 5599 / 5266; 16 of 4096 x 2752, top-4 7274 / 7182; 32 of 1024 x 688,
+// top-8 1756 / 1626; 8 of 4096 x 4096, top-4, 8192 tokens 5041 / 5018; 8 of 4096 x 5504, top-4 13185 / 13078; but 4 of 4096 x 11008, top-2,
+// a training pass 19254 / 19357 (the gather 181 / 94, dW2 1977 / 2150), top-1 10068 / 10137.
+bool mfma_dw2_rows(int f) { return f <= 6144; }
+
 namespace {
 MArgs dw13_args(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1, void* dW3) {
   MArgs g{};
@@ -1872,7 +1953,7 @@ MArgs dw2_args(int dW_dtype, const void* ga, const RowSource& dys, const int32_t
   MArgs h{};
   h.A0 = (const bf16_t*)ga; h.B0 = (const bf16_t*)dys.base; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
-  if (dys.perm) { h.lda = sh.f; h.ldb = sh.d; }
+  if (dys.perm) { h.lda = sh.f; h.ldb = sh.d; }          // strips; tiles: mfma_bwd_dw2()
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
   return h;
 }
@@ -1883,8 +1964,11 @@ int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void
   const MArgs g = dw13_args(dW_dtype, xs, dh1, dh3, off, sh, dW1, dW3);
   return launch_dw<DW13>(g, rows_of_lines(g), false, s);
 }
-int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, void* dW2, hipStream_t s) {
-  const MArgs g = dw2_args(dW_dtype, ga, dys, off, sh, dW2);
+int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW2,
+                 hipStream_t s) {
+  MArgs g = dw2_args(dW_dtype, ga, dys, off, sh, dW2);
+  g.lda = mfma_dw_pitch(sh.R, sh.E);
+  g.row_bytes = row_bytes;
   return launch_dw<DW2>(g, rows_of_lines(g), false, s);
 }
 int mfma_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,

@@ -205,7 +205,7 @@ int launch_gather_rows(const void* src, void* dst, const int32_t* perm, int R, i
 int launch_gather_rows_t(const void* src0, void* dst0, const void* src1, void* dst1, const int32_t* perm,
                          const int32_t* offsets, int R, int k, int d, int E, int pitch, hipStream_t s) {
   if (pitch % 8 != 0 || pitch < (int)align_up((size_t)R, kTRows) + kTRows * E) return BTX_ERR_INVALID_ARG;
-  const dim3 grid(ceil_div(R, kTRows) + E, ceil_div(d, kTCols), 2);
+  const dim3 grid(ceil_div(R, kTRows) + E, ceil_div(d, kTCols), src1 ? 2 : 1);
   gather_rows_t_kernel<<<grid, kThreads, 0, s>>>(static_cast<const bf16_t*>(src0), static_cast<bf16_t*>(dst0),
                                                  static_cast<const bf16_t*>(src1), static_cast<bf16_t*>(dst1), perm,
                                                  offsets, E, k, d, pitch);

@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import DY_ROWS, DY_TRANSPOSED, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -567,6 +567,29 @@ def test_bf16_weight_gradients_of_long_experts_reach_every_tile(T, d, f, E, k, b
 @pytest.mark.parametrize("dW_dtype", [BF16, F32])
 def test_bf16_weight_gradients_from_token_rows(T, d, f, E, k, kw, dW_dtype):
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", DY_ROWS + DY_TRANSPOSED)
+@pytest.mark.parametrize("dW_dtype", [BF16, F32])
+def test_bf16_weight_gradients_of_tiles_from_token_rows_of_dY(T, d, f, E, k, kw, dW_dtype):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
+
+
+def test_bf16_an_infinity_in_the_last_row_of_dY_stays_in_its_column():
+    """The last k tile's rows past the expert's last one repeat it: they must not turn its infinity into NaN."""
+    T, d, f = 1001, 64, 1400
+    G = to_dev(synth.make_layer(T, d, f, 1, dtype=BF16, with_dY=True, unit_rms=True))
+    r = B.btx_moe_route(G["x"], G["W_router"], k=1)
+    _, h1, h3 = B.btx_moe_ff_forward(G["x"], G["W1"], G["W3"], G["W2"], r)
+    def dW2(dY):
+        return B.btx_moe_ff_backward(dY, G["x"], G["W_router"], G["W1"], G["W3"], G["W2"], r, h1, h3).dW2[0].float()
+    finite, broken = dW2(G["dY"]), G["dY"].clone()
+    broken[-1, 17] = float("inf")
+    got = dW2(broken)
+    others = [c for c in range(d) if c != 17]
+    assert torch.equal(got[:, others], finite[:, others])
+    act = torch.nn.functional.silu(h1[-1].float()) * h3[-1].float()
+    assert torch.equal(got[:, 17], torch.where(act > 0, torch.inf, -torch.inf))
 
 
 @pytest.mark.parametrize("T,d,f,E,k,kw", TRANSPOSED_ROWS)

@@ -8,7 +8,7 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -102,6 +102,16 @@ def test_fp32_weight_gradients_of_few_strips_transpose_earlier(record, T, d, f, 
 def test_shapes_of_transposed_rows_take_that_path(record, case):
     (rc, found), = record(backward_call(*case[:5], B.BTX_BF16))
     assert rc == 0 and any("gather_rows_t" in launch.kernel for launch in found)
+
+
+@pytest.mark.parametrize("case,rows", [(c, True) for c in DY_ROWS] + [(c, False) for c in DY_TRANSPOSED] +
+                         [((16384, 4096, 6144, 4, 2), True), ((16384, 4096, 6152, 4, 2), False), ((1 << 19, 4104, 1024, 4, 1), False)])
+def test_dW2_of_tiles_reads_token_rows_of_dY(record, case, rows):
+    """Experts of up to 6144 columns, unless the rows' offsets need more than 32 bits; x alone is transposed then."""
+    (rc, found), = record(backward_call(*case[:5], B.BTX_BF16))
+    gather, = [launch for launch in found if launch.kernel.startswith("gather_rows_t")]
+    dw2, = [launch for launch in found if ", 5, 0, " in launch.kernel]
+    assert rc == 0 and gather.grid[2] == (1 if rows else 2) and dw2.kernel.startswith("mfma_gemm_kernel_rows") == rows
 
 
 @pytest.mark.parametrize("dtype,T,d,E,beside", [(B.BTX_BF16, 64, 256, 4, True), (B.BTX_BF16, 1792, 1024, 16, True), (B.BTX_BF16, 1793, 1024, 16, False),
