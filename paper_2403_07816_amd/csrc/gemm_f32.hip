@@ -24,13 +24,14 @@
 //     leaves behind, found through the scalar cache), the SwiGLU and its backward are epilogues on the accumulators: nothing is
 //     gathered, and no product is stored only to be read again.
 // Measured, fwd + bwd of 2003 tokens through 8 experts of 512 x 1376, top-2 (the products 51 GFLOP), operands through registers and
-// every product by itself / now: 600 / 528 us (16 of it the router's backward pass): UP 114 / 107 us, DOWN 77 / 69, BWD_ACT 68 / 66, BWD_DX 127, DW13 114 and DW2 64 / 263
+// every product by itself / now: 600 / 522 us (16 of it the router's backward pass): UP 114 / 107 us, DOWN 77 / 61, BWD_ACT 68 / 66, BWD_DX 127, DW13 114 and DW2 64 / 263
 // in one launch, at 82 to 107 of the 153 TFLOP/s this instruction sustains; 4096 rows, one expert of 1024 x 4096: 2598 / 2404, at 115
 // to 137.  What is left is ragged rounds of 64 x 64 tiles and what starting and storing a tile takes.
 #include "gemm_f32.h"
 #include "router_ds.h"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace btx {
@@ -51,6 +52,7 @@ struct FArgs {
   int lda, ldb, ldc;
   int64_t strideB_e, strideC_e;
   int slices; float* sums; int R;        // DOWN, BWD_DX: K ranges of every tile; their sums [slice][R][N] (slices > 1)
+  float* cut;                            // DOWN: the last round's tiles in K slices (see Cut); their sums, [slot][64][64] (NULL: whole)
   int tiles_n, tiles_m;                  // column tiles of one product; row tiles of an expert (grouped along K)
   // p / k for 0 <= p < 2^31 without a division (which would cost a third of the vector work of a dW tile):
   // with s = 31 + ceil(log2 k) and div_mul = ceil(2^s / k) < 2^32 the product is off by less than one in 2^31
@@ -90,6 +92,20 @@ __device__ __forceinline__ void copy_to_lds(uint32_t lds, const float* a, const 
                : "s"(at), "v"(A + oa[0]), "v"(A + oa[1]), "v"(B0 + ob[0]), "v"(B1 + ob[1])
                : "memory");
 }
+
+// DOWN of few tiles: those of an XCD that its 32 compute units do not get evenly, the last ones of its `share`, are cut along K into as
+// many slices as give every unit one, and f32_cut_finish_kernel adds them in slice order.  A unit with one tile more than the others
+// held them all up (f32_cut()).
+struct Cut {
+  static constexpr int UNITS = 32, MOST = 8;
+  int whole, left, slices;
+  __device__ __forceinline__ explicit Cut(int share) {
+    left = share % UNITS;
+    slices = left ? min(UNITS / left, MOST) : 1;
+    if (slices < 2) left = 0;
+    whole = share - left;
+  }
+};
 
 // WIDE: byte offsets inside an operand need more than 32 bits (wide_offsets()).  STAGES: of LDS, three for weights_from_memory()
 template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
@@ -227,6 +243,13 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
     return f32x4{acc[0][2 * q], acc[1][2 * q], acc[0][2 * q + 1], acc[1][2 * q + 1]};
   }
 
+  // tile `tile` of those of an expert of n_rows row tiles, in bands: its row and column
+  static __device__ __forceinline__ void in_bands(int tile, int nx, int n_rows, int& tile_m, int& tile_n) {
+    const int band = tile / (kBand * nx), in_band = tile - band * kBand * nx, h = min(kBand, n_rows - band * kBand);
+    tile_m = band * kBand + in_band % h;
+    tile_n = in_band / h;
+  }
+
   // block: of the `total` ones of this product
   static __device__ void run(const FArgs& g, unsigned block, float* smem) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -240,9 +263,22 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
     RowTiles row_tiles(g.offsets, GROUP_K ? 1 : g.E, kTile, lane);
     const int per_row_tile = SLICED ? nx * g.slices : nx;
     const int total = GROUP_K ? g.E * g.tiles_m * nx : row_tiles.count() * per_row_tile;
-    const int share = (total + 7) / 8, id = (int)(block % 8) * share + (int)(block / 8);
-    if ((int)(block / 8) >= share || id >= total) return;
-    int tile_m, tile_n, n_rows, slice = 0;
+    const int share = (total + 7) / 8, xcd = (int)(block % 8);
+    int pos = (int)(block / 8), slice = 0, cut_slices = 1;
+    float* cut_sums = nullptr;
+    if (MODE == DOWN && g.cut) {
+      const Cut cut(share);
+      if (const int p = pos - cut.whole; p >= 0 && cut.left > 0) {
+        slice = p / cut.left;
+        if (slice >= cut.slices) return;
+        cut_slices = cut.slices;
+        cut_sums = g.cut + (int64_t)((xcd * cut.left + p % cut.left) * cut.slices + slice) * (kTile * kTile);
+        pos = cut.whole + p % cut.left;
+      }
+    }
+    const int id = xcd * share + pos;
+    if (pos >= share || id >= total) return;
+    int tile_m, tile_n, n_rows;
     bool second_product = false;
     if (GROUP_K) {
       e = id / (g.tiles_m * nx);
@@ -250,14 +286,12 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
       tile_m = id - e * n_rows * nx;
     } else {
       row_tiles.expert_of(id, per_row_tile, e, n_rows, tile_m);
-      if (SLICED) {
+      if (SLICED && g.slices > 1) {
         slice = tile_m / (nx * n_rows);
         tile_m -= slice * nx * n_rows;
       }
     }
-    const int band = tile_m / (kBand * nx), in_band = tile_m - band * kBand * nx, h = min(kBand, n_rows - band * kBand);
-    tile_m = band * kBand + in_band % h;
-    tile_n = in_band / h;
+    in_bands(tile_m, nx, n_rows, tile_m, tile_n);
     if (GROUP_K) {
       row0 = tile_m * kTile;
       row_end = g.M;
@@ -282,6 +316,10 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
       const int s = slice % n, nk = (g.K + kTileK - 1) / kTileK;
       k_begin = s * nk / n * kTileK;
       k_end = min((s + 1) * nk / n * kTileK, g.K);
+    } else if (MODE == DOWN && cut_slices > 1) {
+      const int nk = (g.K + kTileK - 1) / kTileK;
+      k_begin = slice * nk / cut_slices * kTileK;
+      k_end = min((slice + 1) * nk / cut_slices * kTileK, g.K);
     }
     if (!GROUP_K) { B0 += e * g.strideB_e; if (B1) B1 += e * g.strideB_e; }
 
@@ -441,6 +479,8 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
             *reinterpret_cast<f32x4*>(g.C0 + at) = d1;
             *reinterpret_cast<f32x4*>(g.C1 + at) = d3;
             if (g.C2) *reinterpret_cast<f32x4*>(g.C2 + at) = ga;
+          } else if (MODE == DOWN && cut_sums) {
+            *reinterpret_cast<f32x4*>(cut_sums + (m - row0) * kTile + n - col0) = out4(acc[i], q);
           } else {
             *reinterpret_cast<f32x4*>(C + at) = out4(acc[i], q);
           }
@@ -511,6 +551,31 @@ __global__ __launch_bounds__(kThreads) void f32_slices_finish_kernel(const float
   *reinterpret_cast<f32x4*>(C + i) = a;
 }
 
+// The K slices of the tiles that DOWN has cut (see Cut), four workgroups to a tile, in slice order.
+__global__ __launch_bounds__(kThreads) void f32_cut_finish_kernel(FArgs g) {
+  const int xcd = blockIdx.x % 8, p = blockIdx.x / 32, quarter = blockIdx.x / 8 % 4;
+  const RowTiles rt(g.offsets, g.E, kTile, threadIdx.x & (kWave - 1));
+  const int total = rt.count() * g.tiles_n, share = (total + 7) / 8;
+  const Cut cut(share);
+  const int id = xcd * share + cut.whole + p;
+  if (p >= cut.left || id >= total) return;
+  int e, n_rows, tile_m, tile_n, row0, row_end;
+  rt.expert_of(id, g.tiles_n, e, n_rows, tile_m);
+  F32Gemm<DOWN, false>::in_bands(tile_m, g.tiles_n, n_rows, tile_m, tile_n);
+  rt.rows_of(e, tile_m, row0, row_end);
+  const int row = 16 * quarter + threadIdx.x / 16, col = 4 * (threadIdx.x % 16), m = row0 + row, n = tile_n * kTile + col;
+  if (m >= row_end || n >= g.N) return;
+  const float* from = g.cut + (int64_t)((xcd * cut.left + p) * cut.slices) * (kTile * kTile) + row * kTile + col;
+  f32x4 v[Cut::MOST];
+#pragma unroll
+  for (int s = 0; s < Cut::MOST; ++s) v[s] = *reinterpret_cast<const f32x4*>(from + min(s, cut.slices - 1) * (kTile * kTile));
+#pragma unroll
+  for (int s = 1; s < Cut::MOST; ++s)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v[0][x] += s < cut.slices ? v[s][x] : 0.f;
+  *reinterpret_cast<f32x4*>(g.C0 + (int64_t)m * g.ldc + n) = v[0];
+}
+
 // tiles of N columns (rows of tile_cols) to expect: an expert's last row tile is half full on average
 double expected_tiles(int R, int E, int N, int tile_cols) {
   const int busy = std::max(std::min(E, R), 1);
@@ -556,6 +621,22 @@ int slices_of(const FfShapes& sh, bool two_passes) {
   return f32_slices(sh.R, sh.E, sh.d, sh.f, two_passes, most_slices(sh, two_passes));
 }
 
+// Is DOWN's last round worth a cut and the launch that adds it up (5 us)?  A unit that has one tile more than the others takes 0.5 us longer
+// for each of its k tiles, a slice's part of that when it is cut.  The number of tiles moves by a row tile's columns with the routing:
+// with fewer left than that there may be none.  us, whole / cut, forward call, top-2: 2003 tokens, 8 experts of 512 x 1376 (533 tiles) 159.5
+// / 145.3 (DOWN 70 / 55.7 and 4.8 for the sums; training pass 534.5 / 522.4); of 512 x 688 91.6 / 85.8; 4006 of 256 x 1376 (517) 165.0 / 151.1;
+// but 4 experts of 512 x 1376, 517 tiles expected and 512 there, 140.9 / 143.0.
+bool f32_cut(const FfShapes& sh) {
+  const double rows = (double)sh.R / sh.E, spread = std::sqrt(2.0 * rows * (1.0 - 1.0 / sh.E));
+  double row_tiles = 0;                                  // of an expert, for rows spread at random
+  for (int j = 0; j < ceil_div(sh.R, kTile) && kTile * j < rows + 8 * spread; ++j)
+    row_tiles += spread > 0 ? 0.5 * std::erfc((kTile * j + 0.5 - rows) / spread) : 1.0;
+  const double tiles = std::round(row_tiles * sh.E) * ceil_div(sh.d, kTile), rounds = std::floor(tiles / 256), left = tiles - 256 * rounds;
+  if (rounds < 1 || left < ceil_div(sh.d, kTile) || left > 120 || sums_bytes(sh, false) < (size_t)8 * Cut::UNITS * kTile * kTile * sizeof(float)) return false;
+  const double slices = std::min(std::floor(256 / left), (double)Cut::MOST);
+  return 0.5 * ceil_div(sh.f, kTileK) * (1.0 - 1.0 / slices) > 7.0;
+}
+
 // Do byte offsets from a tile's first row (gathered: from token 0) need more than 32 bits?  A tile spans 64 rows.
 bool wide_offsets(const FArgs& g, int R) {
   const int64_t rows = g.perm ? std::max(ceil_div(R, g.k), kTile) : kTile;
@@ -580,7 +661,8 @@ template <int MODE> unsigned blocks_of(FArgs& g, int R) {
   g.R = R;
   const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
                         (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, kTile) + g.E);   // at most this many
-  return grid_fits(tiles + 7, kThreads) ? (unsigned)align_up((size_t)tiles, 8) : 0;
+  const int64_t slices = MODE == DOWN && g.cut ? 8 * Cut::UNITS : 0;   // of the tiles that are cut
+  return grid_fits(tiles + slices + 7, kThreads) ? (unsigned)align_up((size_t)(tiles + slices), 8) : 0;
 }
 int finish_slices(const FArgs& g, int R, hipStream_t s) {
   f32_slices_finish_kernel<<<ceil_div((int64_t)R * g.N / 4, kThreads), kThreads, 0, s>>>(g.sums, g.slices, R, g.N, g.offsets, g.E, g.C0);
@@ -595,6 +677,10 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullpt
   else if (MODE == UP && weights_from_memory(g, R)) f32_gemm_kernel<MODE, false, MODE == UP ? 3 : 2><<<grid, kThreads, 0, s>>>(g);
   else f32_gemm_kernel<MODE, false, 2><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
+  if (MODE == DOWN && g.cut) {
+    f32_cut_finish_kernel<<<8 * 4 * (Cut::UNITS / 2), kThreads, 0, s>>>(g);   // at most half of an XCD's units have a tile that is cut
+    BTX_LAUNCH_CHECK();
+  }
   const bool leave = left && g.slices <= *left;
   if (left) *left = leave ? g.slices : 1;
   return g.slices > 1 && !leave ? finish_slices(g, R, s) : BTX_OK;
@@ -756,6 +842,7 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
 int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices, hipStream_t s) {
   FArgs g{};
   g.slices = slices_of(sh, false); g.sums = (float*)sums;
+  if (g.slices == 1 && f32_cut(sh)) g.cut = g.sums;
   g.A0 = (const float*)act; g.B0 = (const float*)W2; g.C0 = (float*)y;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideB_e = sh.s2;
   return launch<DOWN>(g, sh.R, s, slices);

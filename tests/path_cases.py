@@ -67,6 +67,13 @@ DY_ROWS = [
 ]
 DY_TRANSPOSED = [(500, 264, 6152, 1, 1, {}), (420, 72, 6400, 2, 2, dict(bias=[3.0, 0.0], poison=True))]
 
+# fp32 DOWN whose last round of tiles is cut along K: last k tiles of 8, 16 and 32, column tiles of 24 to 64; experts of uneven numbers of
+# rows (other numbers of tiles than expected: more slices, fewer, none), dropped pairs
+F32_LAST_ROUND = [
+    (592, 864, 552, 2, 2, {}), (634, 544, 528, 4, 3, dict(cf=0.9)), (808, 640, 552, 3, 2, dict(bias=[1.0, 0.0, 0.0])), (2176, 496, 576, 5, 1, {}),
+    (649, 728, 648, 8, 2, dict(bias=[2.0, 1.0] + [0.0] * 6)), (933, 568, 528, 4, 2, dict(bias=[0.0, 0.0, 0.0, -60.0])),
+]
+
 # many tokens' routing: (T, d, E, k, dtype, with the normalisation) -> experts of a pass over the columns, wavefronts that share 16
 # tokens.  Ragged last blocks; one workgroup on a compute unit, two, more.
 ROUTE_MANY = [

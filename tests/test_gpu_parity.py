@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import DY_ROWS, DY_TRANSPOSED, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
 
 pytestmark = pytest.mark.gpu
 
@@ -62,6 +62,11 @@ def test_fp32_up_projection_with_three_stages(T, d, f, E, k):
 @pytest.mark.parametrize("T,d,f,E,k,kw", JOINT_FORWARD)
 def test_fp32_small_layers_forward_in_one_launch(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, F32, **kw)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", F32_LAST_ROUND)
+def test_fp32_last_round_of_the_down_projection_cut_along_k(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, F32, backward=False, poison=True, **kw)
 
 
 def test_fp32_token_rows_past_4_gib():

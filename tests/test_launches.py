@@ -8,7 +8,7 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -160,6 +160,21 @@ def test_fp32_up_projection_of_weights_from_memory_has_three_stages(record, T, d
     (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32))
     up, = [launch.kernel for launch in found if launch.kernel.startswith("f32_gemm_kernel<0")]
     assert rc == 0 and up.endswith(f", {stages}>")
+
+
+@pytest.mark.parametrize("case,cut", [(c, True) for c in F32_LAST_ROUND] + [
+    # one tile more than others of a unit's, none, too many for two slices; few k tiles; fewer tiles than units
+    ((2003, 512, 1376, 8, 2), True), ((1900, 512, 1376, 8, 2), False), ((2003, 512, 416, 8, 2), False), ((64, 512, 1376, 8, 2), False)])
+def test_last_round_of_fp32_down_projections_is_cut(record, case, cut):
+    T, d, f, E, k = case[:5]
+    (size, _), (rc, found) = record(("btx_moe_ff_forward_workspace_bytes", [T, d, f, E, k, B.BTX_F32]), forward_call(T, d, f, E, k, B.BTX_F32))
+    names = [launch.kernel for launch in found]
+    assert rc == 0 and ("f32_cut_finish_kernel" in names) == cut
+    if cut:
+        down = found[names.index("f32_cut_finish_kernel") - 1]
+        tiles = (math.ceil(T * k / 64) + E) * math.ceil(d / 64)    # at most; of each XCD's, 32 workgroups more
+        assert down.kernel.startswith("f32_gemm_kernel<1") and down.grid[0] // 8 >= math.ceil(tiles / 8) + 32
+        assert size >= 4 * (T * k * (f + d) + 256 * 64 * 64)       # act, y, and a tile's sums for every workgroup that has a slice
 
 
 @pytest.mark.parametrize("T,d,f,E,k", [case[:5] for case in JOINT_FORWARD])
