@@ -32,7 +32,7 @@ FwdWs carve_forward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   FwdWs w;
   // gathered token rows, unless the GEMMs read them through perm themselves
   w.xs = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
-  w.act = c.take(R * f * es);
+  w.act = c.take(R * ff_act_pitch(dtype, f) * es);
   w.y = c.take(R * d * es);
   const size_t split = ff_forward_split_bytes(dtype, FfShapes{(int)R, d, f, E, 0, 0});   // sums of K slices
   w.partial = split ? c.take(split) : nullptr;
@@ -54,10 +54,11 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   // byte offsets of the token rows, for weight gradients that read them: bf16, where the transposed rows would lie
   w.row_bytes = static_cast<uint32_t*>(tr ? w.xsT : c.take(R * sizeof(uint32_t)));
   w.dys = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
-  w.dh1 = c.take(R * f * es);
-  w.dh3 = c.take(R * f * es);
+  const size_t rows_f = R * ff_act_pitch(dtype, f) * es;
+  w.dh1 = c.take(rows_f);
+  w.dh3 = c.take(rows_f);
   // transposed path: dW2 reads ga as [f][padded rows]; in row order it is smaller
-  w.ga = c.take(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : R * f * es);
+  w.ga = c.take(std::max(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : 0, rows_f));
   w.dxs = c.take(R * d * es);
   w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials_most(dtype, f) * sizeof(float)));
   w.router = c.take(router_bwd_workspace_bytes(T, d, E));

@@ -290,8 +290,8 @@ size_t ff_backward_split_bytes(int dtype, const FfShapes& sh);
 int launch_down(int dtype, const void* act, const void* W2, const int32_t* offsets, const FfShapes& sh, void* y,
                 void* partial, int* slices, hipStream_t s);
 // D = dys W2^T; dg_part[r,p] partial sums of D*a; da = g*D; dh1 = da*h3*silu'(h1); dh3 = da*silu(h1); ga = g*a.
-// dh1, dh3: [R,f].  With ga_transposed `ga` receives g*a transposed and padded ([f][ff_dw_pitch()]); otherwise it is
-// [R,f].  Nothing at all in bf16 when want_dw is false.  row_bytes ([R]; may be NULL): for the weight gradients, the byte
+// dh1, dh3: [R,f], rows ff_act_pitch() apart, as are those of act above.  With ga_transposed `ga` receives g*a transposed and padded
+// ([f][ff_dw_pitch()]); otherwise it is like them.  Nothing at all in bf16 when want_dw is false.  row_bytes ([R]; may be NULL): for the weight gradients, the byte
 // offset of every grouped row's token row.
 // bwd_act_partials: partial sums per grouped row that launch_bwd_act writes for these shapes (one per column tile), and the
 // most that any number of rows gets (fewer rows may run with narrower tiles)
@@ -312,6 +312,8 @@ struct RouterDs;
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
+// elements from a row of act, dh1, dh3 or (in row order) ga to the next: f, or more
+int ff_act_pitch(int dtype, int f);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)
 int ff_prepare();
 // false when R routed rows are more than the kernels of this dtype and shape can address

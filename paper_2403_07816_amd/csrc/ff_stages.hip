@@ -21,6 +21,7 @@ bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused
   return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh, dW_dtype));
 }
 int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
+int ff_act_pitch(int dtype, int f) { return dtype == BTX_BF16 ? mfma_act_pitch(f) : f; }
 
 bool ff_gather_fused(int dtype, int T, int d) { return dtype != BTX_BF16 || mfma_gather_ok(T, d); }
 

@@ -22,7 +22,7 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
 // slices: see launch_down()
 int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* partial,
               int* slices, hipStream_t s);
-// dh1, dh3: [R,f]; ga: [R,f] too, or with ga_transposed [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to
+// dh1, dh3: [R,f], rows mfma_act_pitch() apart; ga: like them, or with ga_transposed [f][mfma_dw_pitch(R, E)], experts' rows padded with zeros to
 // multiples of 64 (for dW2; NULL when no weight gradients are wanted)
 int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const void* h3, const float* gates,
                  const int32_t* perm, const int32_t* off, const FfShapes& sh, void* dh1, void* dh3, void* ga,
@@ -33,6 +33,8 @@ int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3
 // xs, dys without perm: [d][mfma_dw_pitch(R, E)], laid out like the transposed ga above
 bool mfma_dw_direct(const FfShapes& sh, int dW_dtype);
 int mfma_dw_pitch(int R, int E);
+// elements from a row of act, dh1, dh3 or ga (in row order) to the next
+int mfma_act_pitch(int f);
 int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1,
                   void* dW3, hipStream_t s);
 // row_bytes: dys are token rows, found by it (mfma_dw2_rows(); NULL: transposed like xs)

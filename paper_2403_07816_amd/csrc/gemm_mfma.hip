@@ -66,6 +66,7 @@ struct MArgs {
   const int32_t* offsets; int E;
   int M, N, K;                          // grouped-M: M unused; grouped-K: K unused
   int lda, ldb, ldc;                    // leading dimensions in elements
+  int ldp;                              // of the rows of f that stay inside the library: UP's act, BWD_ACT's dh1, dh3 and ga (mfma_act_pitch())
   int64_t strideB_e, strideC_e;         // per-expert strides in elements
   int R;                                // total grouped rows
   int tiles_n, tiles_m;                 // tile grid (tiles_m is the worst case for grouped-M)
@@ -463,7 +464,7 @@ struct Gemm {
     for (int jj = 0; jj < TNH; ++jj) {
       const int n = col0 + wn * (TNH * 16) + jj * 16 + 4 * (lane >> 4);
       const bool inside = m < tile.row_end && n < g.N;
-      const size_t idx = (size_t)m * g.ldc + n;
+      const size_t idx = (size_t)m * g.ldc + n, idx_act = (size_t)m * g.ldp + n;
       if constexpr (MODE == UP) {                        // fragment jj holds x W1, fragment jj + TNH x W3 of the same outputs
         const f32x4 h1 = sum[jj], h3 = sum[jj + TNH];
         f32x4 a;
@@ -471,7 +472,7 @@ struct Gemm {
         for (int x = 0; x < 4; ++x) a[x] = silu_f(h1[x]) * h3[x];
         if (inside) {
           if (g.C0) { put(g.C0, idx, h1); put(g.C1, idx, h3); }
-          put(g.C2, idx, a);
+          put(g.C2, idx_act, a);
         }
       } else {
         if (inside) put(g.C0, idx, sum[jj]);
@@ -1033,7 +1034,7 @@ struct Gemm {
           const u32x4 v1 = *reinterpret_cast<const u32x4*>(bufA + o);
           const u32x4 v3 = *reinterpret_cast<const u32x4*>(bufB + o);
           if (mb + r < row_end && cn < g.N) {
-            const size_t idx = (size_t)(mb + r) * g.ldc + cn;
+            const size_t idx = (size_t)(mb + r) * g.ldp + cn;
             store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C0) + idx), v1);
             store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C1) + idx), v3);
             if (g.C2) store_out<STREAM>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(g.C2) + idx), *reinterpret_cast<const u32x4*>(bufC + o));
@@ -1139,7 +1140,8 @@ struct Gemm {
               const u32x4 val = swap_halves(
                   *reinterpret_cast<const u32x4*>(wb + pp * (32 * ROWB) + stage_off<ROWB, 4 * ES>(r, cc)),
                   half_flip<ROWB, ES>(r) != 0);
-              if (mb + r < row_end && cn < g.N) store_out<STREAM>(reinterpret_cast<u32x4*>(C + (size_t)(mb + r) * g.ldc + cn), val);
+              const int ld = MODE == UP && pp == 2 ? g.ldp : g.ldc;
+              if (mb + r < row_end && cn < g.N) store_out<STREAM>(reinterpret_cast<u32x4*>(C + (size_t)(mb + r) * ld + cn), val);
             }
           }
         }
@@ -1199,7 +1201,7 @@ __global__ __launch_bounds__(WM* WN* kWave, 2) void mfma_small_kernel(MArgs g) {
 // The K slices of small tiles added in slice order, 8 columns of a row per thread; SWIGLU: [slice][2][R][N], the
 // activation (and the two products themselves, unless C0 is NULL) is stored.
 template <bool SWIGLU>
-__global__ __launch_bounds__(256) void slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N,
+__global__ __launch_bounds__(256) void slices_finish_kernel(const float* __restrict__ sums, int slices, int R, int N, int ldp,
                                                             const int32_t* __restrict__ offsets, int E,
                                                             bf16_t* __restrict__ C0, bf16_t* __restrict__ C1,
                                                             bf16_t* __restrict__ C2) {
@@ -1225,7 +1227,7 @@ __global__ __launch_bounds__(256) void slices_finish_kernel(const float* __restr
     if (C0) { RowVec<bf16_t, 8>::st(C0 + at, h1); RowVec<bf16_t, 8>::st(C1 + at, h3); }
 #pragma unroll
     for (int x = 0; x < 8; ++x) h1[x] = silu_f(h1[x]) * h3[x];
-    RowVec<bf16_t, 8>::st(C2 + at, h1);
+    RowVec<bf16_t, 8>::st(C2 + (size_t)row * ldp + c, h1);
   } else {
     RowVec<bf16_t, 8>::st(C0 + at, h1);
   }
@@ -1637,7 +1639,7 @@ template <int BM, int MODE, int TAIL, bool STREAM_B> int launch_small(MArgs g, b
   if (left) *left = leave ? g.slices : 1;
   if (g.slices > 1 && !leave) {
     slices_finish_kernel<MODE == UP><<<ceil_div((int64_t)g.R * (g.N / 8), 256), 256, 0, s>>>(
-        g.slice_sums, g.slices, g.R, g.N, g.offsets, g.E, (bf16_t*)g.C0, (bf16_t*)g.C1, (bf16_t*)g.C2);
+        g.slice_sums, g.slices, g.R, g.N, g.ldp, g.offsets, g.E, (bf16_t*)g.C0, (bf16_t*)g.C1, (bf16_t*)g.C2);
     BTX_LAUNCH_CHECK();
   }
   return BTX_OK;
@@ -1865,7 +1867,7 @@ int mfma_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const in
                    void* h1, void* h3, void* act, void* partial, hipStream_t s) {
   MArgs g{};
   g.A0 = (const bf16_t*)xs.base; g.a_perm = xs.perm; g.a_k = xs.k; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = h1; g.C1 = h3; g.C2 = act; g.partial = (f32x4*)partial;
-  g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f;
+  g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.f; g.ldc = sh.f; g.ldp = mfma_act_pitch(sh.f);
   g.strideB_e = sh.s13; g.R = sh.R;
   return launch_rows<UP>(g, s);
 }
@@ -1874,7 +1876,7 @@ int mfma_down(const void* act, const void* W2, const int32_t* off, const FfShape
               int* slices, hipStream_t s) {
   MArgs g{};
   g.A0 = (const bf16_t*)act; g.B0 = (const bf16_t*)W2; g.C0 = y; g.partial = (f32x4*)partial;
-  g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d;
+  g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = mfma_act_pitch(sh.f); g.ldb = sh.d; g.ldc = sh.d;
   g.strideB_e = sh.s2; g.R = sh.R;
   return launch_rows<DOWN>(g, s, slices);
 }
@@ -1891,7 +1893,7 @@ int mfma_bwd_act(const RowSource& dys, const void* W2, const void* h1, const voi
   g.ldt = mfma_dw_pitch(sh.R, sh.E);
   g.H1 = (const bf16_t*)h1; g.H3 = (const bf16_t*)h3; g.gates = gates; g.perm = perm; g.dg_part = dg_part;
   g.n_part = mfma_bwd_act_partials(sh);
-  g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f;
+  g.offsets = off; g.E = sh.E; g.N = sh.f; g.K = sh.d; g.lda = sh.d; g.ldb = sh.d; g.ldc = sh.f; g.ldp = mfma_act_pitch(sh.f);
   g.strideB_e = sh.s2; g.R = sh.R;
   return launch_rows<BWD_ACT>(g, s);
 }
@@ -1900,11 +1902,17 @@ int mfma_bwd_dx(const void* dh1, const void* dh3, const void* W1, const void* W3
                 const FfShapes& sh, void* dxs, void* partial, hipStream_t s) {
   MArgs g{};
   g.A0 = (const bf16_t*)dh1; g.A1 = (const bf16_t*)dh3; g.B0 = (const bf16_t*)W1; g.B1 = (const bf16_t*)W3; g.C0 = dxs; g.partial = (f32x4*)partial;
-  g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.f; g.ldc = sh.d;
+  g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = mfma_act_pitch(sh.f); g.ldb = sh.f; g.ldc = sh.d;
   g.strideB_e = sh.s13; g.R = sh.R;
   return launch_rows<BWD_DX>(g, s);
 }
 
+// Rows of act, dh1, dh3 and ga start on whole lines: of rows that do not, the 128 bytes of k that a copy takes lie in two lines, of which a
+// compute unit has at most 32 KB on their way, and streamed stores leave parts of lines.  Training pass, rows as wide as the expert /
+// padded: 16384 tokens, 32 experts of 4096 x 1376, top-8 12047 / 11870 us (BWD_DX 2430 / 2340); 64 of 1024 x 344 1554 / 1440; 16 of 2048 x 1376,
+// top-4 3394 / 3328; 64 of 1024 x 136 1062 / 1025; 1501 tokens, 64 of 4096 x 688 1251 / 1227; 800, 64 of 4040 x 616 1011 / 986; 100, 16 of
+// 1000 x 264 79.2 / 79.2.  Not where that nearly doubles the rows (8 of 256 x 72 295 / 298), nor where their offsets grow past 32 bits.
+int mfma_act_pitch(int f) { return f > 128 && f <= 65536 ? (int)align_up((size_t)f, 64) : f; }
 int mfma_dw_pitch(int R, int E) { return (int)align_up((size_t)R, 64) + 64 * E; }
 bool mfma_rows_ok(int R, int E) { return ((int64_t)align_up((size_t)R, 64) + 64 * E) * 256 * 2 < ((int64_t)1 << 32); }
 
@@ -1945,7 +1953,7 @@ namespace {
 MArgs dw13_args(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1, void* dW3) {
   MArgs g{};
   g.A0 = (const bf16_t*)xs.base; g.B0 = (const bf16_t*)dh1; g.B1 = (const bf16_t*)dh3; g.C0 = dW1; g.C1 = dW3;
-  g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = xs.perm ? sh.d : mfma_dw_pitch(sh.R, sh.E); g.ldb = sh.f; g.ldc = sh.f;
+  g.offsets = off; g.E = sh.E; g.M = sh.d; g.N = sh.f; g.lda = xs.perm ? sh.d : mfma_dw_pitch(sh.R, sh.E); g.ldb = mfma_act_pitch(sh.f); g.ldc = sh.f;
   g.strideC_e = sh.s13; g.R = sh.R; g.c_is_f32 = dW_dtype == BTX_F32;
   return g;
 }
@@ -1953,7 +1961,7 @@ MArgs dw2_args(int dW_dtype, const void* ga, const RowSource& dys, const int32_t
   MArgs h{};
   h.A0 = (const bf16_t*)ga; h.B0 = (const bf16_t*)dys.base; h.C0 = dW2;
   h.offsets = off; h.E = sh.E; h.M = sh.f; h.N = sh.d; h.lda = h.ldb = mfma_dw_pitch(sh.R, sh.E); h.ldc = sh.d;
-  if (dys.perm) { h.lda = sh.f; h.ldb = sh.d; }          // strips; tiles: mfma_bwd_dw2()
+  if (dys.perm) { h.lda = mfma_act_pitch(sh.f); h.ldb = sh.d; }          // strips; tiles: mfma_bwd_dw2()
   h.strideC_e = sh.s2; h.R = sh.R; h.c_is_f32 = dW_dtype == BTX_F32;
   return h;
 }
