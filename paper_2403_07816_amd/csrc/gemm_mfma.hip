@@ -15,10 +15,10 @@
 //     between a memory phase and a compute phase (see the main loop);
 //   * an operand whose K index is contiguous in memory is stored [row][BK] with a 16-byte
 //     chunk XOR swizzle and read with ds_read_b128; an operand whose K index is strided
-//     (the weights in UP and DOWN, dh1/dh3 in DW13) is stored as it lies in memory, [BK][cols],
-//     and read with the transposing ds_read_b64_tr_b16; x, dY and ga reach the dW products of
-//     many rows per expert transposed and zero-padded (x and dY from a gather kernel, ga written
-//     that way by BWD_ACT's epilogue; see DwStrip for few rows).  The swizzles are applied by choosing which
+//     (the weights in UP and DOWN, dh1/dh3 in DW13, token rows of dY in DW2) is stored as it lies in memory,
+//     [BK][cols], and read with the transposing ds_read_b64_tr_b16; x, ga and, for wide experts (mfma_dw2_rows()),
+//     dY reach the dW products of many rows per expert transposed and zero-padded (x and dY from a gather
+//     kernel, ga written that way by BWD_ACT's epilogue; see DwStrip for few rows).  The swizzles are applied by choosing which
 //     global chunk each lane fetches, since a direct copy fixes the LDS position per lane;
 //   * v_mfma_f32_16x16x32_bf16 (on this chip it sustains a seventh more than the 32x32x16 form
 //     under the same power limit) with the roles of the operands swapped (the N-side fragment

@@ -174,7 +174,12 @@ constexpr int kSmallTokens = 512, kSmallPairs = 4096;
 constexpr int64_t kSmallTraffic = (int64_t)1 << 25;     // T * d * E: every token reads the whole W_router (128 MB in all)
 constexpr int kSmallThreads = 256, kGroupThreads = 1024;
 
-template <typename XT, int EC, bool NORM>
+// AHEAD: pieces of a thread, 8 columns of the token, the first experts' weights and the gain, that are requested at once, in front of the
+// mean square's sum instead of behind it: two with the normalisation of more than 2048 columns.  us, the whole routing of 4096 columns, none
+// / two: 16 tokens, 4 experts 10.5 / 9.8, 8 12.8 / 12.0, 16, top-8 20.6 / 19.6; 512 tokens, 8 experts 18.9 / 18.2, 16 33.3 / 32.1; but 4 experts
+// 14.0 / 14.2, 301 tokens 13.0 / 13.1, where other workgroups cover the wait; of 1024 columns 16 tokens 8.2 / 8.3, 512 10.5 / 11.1; without the
+// normalisation 16 experts 15.6 / 16.4; 32 experts of 3072 26.2 / 26.8.
+template <typename XT, int EC, bool NORM, int AHEAD>
 __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
     const XT* __restrict__ x, const float* __restrict__ Wr, const float* __restrict__ br, const float* __restrict__ U,
     int d, int E, int k, int mode, float inv_tau, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
@@ -185,11 +190,8 @@ __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
   __shared__ double s_ss[kSmallThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, t = blockIdx.x;
   const XT* row = x + (size_t)t * d;
-  // 8 columns of this thread: the token's, the first experts' weights, and the gain.  Those of its first two pieces (4096 columns) are
-  // requested at once: in front of the mean square's sum, not behind it (16 tokens of 4096 columns, 4 experts, with the normalisation: 8.8
-  // us, now 8.0; 301 tokens 12.7, where the many readers of W_router count).
   struct Piece { Raw8<XT> x; float w[8][EC], g[NORM ? 8 : 1]; };
-  constexpr int AHEAD = 2, STEP = kSmallThreads * 8;
+  constexpr int STEP = kSmallThreads * 8;
   auto load_w = [&](float (&w)[8][EC], int c0, int e0) {
     const float* w0 = Wr + (size_t)c0 * E + e0;
     if (EC % 4 == 0 && e0 + EC <= E) {
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
     load_w(p.w, c0, e0);
     if constexpr (NORM) RowVec<float, 8>::ld(gain + c0, p.g);
   };
-  Piece first[AHEAD];
+  Piece first[AHEAD ? AHEAD : 1];
 #pragma unroll
   for (int q = 0; q < AHEAD; ++q)
     if (const int c0 = threadIdx.x * 8 + q * STEP; c0 < d) load(first[q], c0, 0);
@@ -436,7 +438,11 @@ bool route_is_small(const RouteArgs& a) {
 int launch_route_small(const RouteArgs& a, hipStream_t s) {
   auto tokens = [&](auto tag, auto ec, auto norm) {
     using XT = decltype(tag);
-    route_small_tokens_kernel<XT, decltype(ec)::value, decltype(norm)::value><<<a.T, kSmallThreads, 0, s>>>(
+    constexpr int EC = decltype(ec)::value;
+    constexpr bool NORM = decltype(norm)::value;
+    const bool ahead = NORM && a.d > 2048 && a.E <= 16 && (a.E > 4 || a.T <= 256);
+    const auto kernel = ahead ? route_small_tokens_kernel<XT, EC, NORM, NORM ? 2 : 0> : route_small_tokens_kernel<XT, EC, NORM, 0>;
+    kernel<<<a.T, kSmallThreads, 0, s>>>(
         static_cast<const XT*>(a.x), a.W_router, a.b_router, a.U, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx,
         a.gates, a.probs, a.gain, a.eps, static_cast<XT*>(a.xn), a.rstd);
   };

@@ -16,7 +16,7 @@ import csv
 import sys
 
 MODES = {0: "up_swiglu", 1: "down", 2: "bwd_act", 3: "bwd_dx", 4: "dw13", 5: "dw2"}
-MODE_AT = {"mfma_gemm_kernel": 7, "mfma_small_kernel": 5, "f32_gemm_kernel": 0}   # template arguments in front of MODE
+MODE_AT = {"mfma_gemm_kernel": 7, "mfma_gemm_kernel_rows": 7, "mfma_small_kernel": 5, "f32_gemm_kernel": 0}   # template arguments in front of MODE
 
 
 def short(name: str) -> str:

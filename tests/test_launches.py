@@ -337,6 +337,13 @@ def test_wavefronts_that_share_16_tokens(record, dtype, norm, T, d, E, waves):
         assert tokens.block[0] == 64 * waves and f", {waves}, " in tokens.kernel
 
 
+@pytest.mark.parametrize("T,d,E,norm,ahead", [(16, 4096, 4, True, 2), (16, 2056, 16, True, 2), (256, 8192, 4, True, 2), (512, 4096, 5, True, 2),
+                                              (257, 4096, 4, True, 0), (16, 2048, 4, True, 0), (16, 4096, 17, True, 0), (16, 4096, 4, False, 0)])
+def test_few_tokens_of_wide_rows_are_requested_ahead_of_the_normalisation(record, T, d, E, norm, ahead):
+    (rc, found), = record(route_call(T, d, E, 2, B.BTX_BF16, norm))
+    assert rc == 0 and found[0].kernel.startswith("route_small_tokens") and found[0].kernel.endswith(f", {ahead}>")
+
+
 @pytest.mark.parametrize("dtype,T,d,E,waves", [
     (B.BTX_BF16, 4097, 4096, 16, 8), (B.BTX_BF16, 4097, 4096, 17, 4), (B.BTX_BF16, 4097, 4104, 17, 8), (B.BTX_BF16, 8176, 10240, 32, 8),
     (B.BTX_BF16, 8176, 10248, 17, 4), (B.BTX_BF16, 8176, 16384, 16, 8), (B.BTX_BF16, 8177, 16384, 16, 4), (B.BTX_BF16, 4097, 8192, 33, 4),
