@@ -64,6 +64,19 @@ const at::Tensor& matrix(PyObject* o) {
   if (t.dim() != 2) fail(PyExc_ValueError, "a matrix is expected");
   return t;
 }
+// Shapes and strides of the experts that x goes through.  The library takes one expert stride for W1 and W3, and one dtype
+struct Experts {
+  int64_t T, d, E, f, s13, s2;
+  Experts(const at::Tensor& x, const at::Tensor& W1, const at::Tensor& W3, const at::Tensor& W2)
+      : T(x.size(0)), d(x.size(1)), E(0), f(0), s13(stacked(W1)), s2(stacked(W2)) {
+    E = W1.size(0);
+    f = W1.size(2);
+    require(W1.size(1) == d && W3.sizes() == W1.sizes() && W2.size(0) == E && W2.size(1) == f && W2.size(2) == d &&
+                W1.scalar_type() == x.scalar_type() && W3.scalar_type() == x.scalar_type() && W2.scalar_type() == x.scalar_type(),
+            "W1, W3 [E, d, f] and W2 [E, f, d] of x's dtype");
+    require(E == 1 || (is_stacked(W3) && W3.stride(0) == s13), "W3 is stacked like W1");
+  }
+};
 int64_t integer(PyObject* o) {
   const long long v = PyLong_AsLongLong(o);
   if (v == -1 && PyErr_Occurred()) throw PyError{};
@@ -174,18 +187,15 @@ PyObject* norm_route(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 11, [&] {
     const at::Tensor &x = matrix(a[0]), &W1 = tensor(a[1]), &W3 = tensor(a[2]), &W2 = tensor(a[3]);
-    const int64_t s13 = stacked(W1), s2 = stacked(W2);
-    const int64_t T = x.size(0), d = x.size(1), E = W1.size(0), f = W1.size(2);
-    require(W1.scalar_type() == x.scalar_type() && W3.sizes() == W1.sizes() && W2.size(0) == E && W2.size(1) == f && W2.size(2) == d,
-            "W1, W3 [E, d, f] and W2 [E, f, d] of x's dtype");
+    const Experts w(x, W1, W3, W2);
     static const char* const names[] = {"topk_idx", "gates", "offsets", "perm", "inv_pos"};
     const RoutingPtrs r(a[4], names, 5);
     const int dt = dtype_code(x), k = r.k;
     const void *xp = address(a[0]), *w1 = address(a[1], true), *w3 = address(a[2], true), *w2 = address(a[3], true), *res = address(a[5]);
     void *out = address(a[6]), *h1 = address(a[7]), *h3 = address(a[8]);
     void* const stream = reinterpret_cast<void*>(integer(a[10]));
-    return with_workspace(a[9], lib.forward_bytes((int)T, (int)d, (int)f, (int)E, k, dt), [&](void* ws, size_t bytes) {
-      return lib.forward(xp, w1, w3, w2, dt, s13, s2, (int)T, (int)d, (int)f, (int)E, k, (const float*)r.at[1], (const int32_t*)r.at[2],
+    return with_workspace(a[9], lib.forward_bytes((int)w.T, (int)w.d, (int)w.f, (int)w.E, k, dt), [&](void* ws, size_t bytes) {
+      return lib.forward(xp, w1, w3, w2, dt, w.s13, w.s2, (int)w.T, (int)w.d, (int)w.f, (int)w.E, k, (const float*)r.at[1], (const int32_t*)r.at[2],
                          (const int32_t*)r.at[3], (const int32_t*)r.at[4], res, out, h1, h3, ws, bytes, stream);
     });
   });
@@ -195,17 +205,18 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // dW1, dW3, dW2, weight gradients in fp32, workspace, stream
 PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 25, [&] {
-    const at::Tensor &x = matrix(a[1]), &W1 = tensor(a[3]), &W2 = tensor(a[5]);
-    const int64_t s13 = stacked(W1), s2 = stacked(W2);
-    const int64_t T = x.size(0), d = x.size(1), E = W1.size(0), f = W1.size(2);
+    const at::Tensor &x = matrix(a[1]), &W1 = tensor(a[3]), &W3 = tensor(a[4]), &W2 = tensor(a[5]);
+    const Experts w(x, W1, W3, W2);
+    const bool dw_f32 = PyObject_IsTrue(a[22]) == 1;
     for (int i = 0; i < 3; ++i) {
       if (a[19 + i] == Py_None) continue;
       const at::Tensor &dW = tensor(a[19 + i]), &W = tensor(a[3 + i]);
       require(dW.sizes() == W.sizes() && stacked(dW) == stacked(W), "dW is stacked like W");
+      require(dW.scalar_type() == (dw_f32 ? at::kFloat : at::kBFloat16), "dW is of dW_dtype");
     }
     static const char* const names[] = {"topk_idx", "gates", "probs", "offsets", "perm", "inv_pos", "gate_sum", "prob_sum", "counts"};
     const RoutingPtrs r(a[6], names, 9);
-    const int dt = dtype_code(x), k = r.k, mode = int32(a[9]), lb_mode = int32(a[10]), dw_dt = PyObject_IsTrue(a[22]) ? BTX_F32 : BTX_BF16;
+    const int dt = dtype_code(x), k = r.k, mode = int32(a[9]), lb_mode = int32(a[10]), dw_dt = dw_f32 ? BTX_F32 : BTX_BF16;
     const float alpha = real(a[11]), scale = real(a[12]), tau = real(a[15]);
     const unsigned flags = (unsigned)integer(a[13]);
     const void *dY = address(a[0]), *xp = address(a[1]), *w1 = address(a[3], true), *w3 = address(a[4], true), *w2 = address(a[5], true);
@@ -214,8 +225,8 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void *dX = address(a[16]), *dW1 = address(a[19], true), *dW3 = address(a[20], true), *dW2 = address(a[21], true);
     float *dWr = address_of<float>(a[17]), *dbr = address_of<float>(a[18]);
     void* const stream = reinterpret_cast<void*>(integer(a[24]));
-    return with_workspace(a[23], lib.backward_bytes((int)T, (int)d, (int)f, (int)E, k, dt), [&](void* ws, size_t bytes) {
-      return lib.backward(dY, xp, Wr, w1, w3, w2, dt, s13, s2, (int)T, (int)d, (int)f, (int)E, k, mode, lb_mode, alpha, scale, flags, noise,
+    return with_workspace(a[23], lib.backward_bytes((int)w.T, (int)w.d, (int)w.f, (int)w.E, k, dt), [&](void* ws, size_t bytes) {
+      return lib.backward(dY, xp, Wr, w1, w3, w2, dt, w.s13, w.s2, (int)w.T, (int)w.d, (int)w.f, (int)w.E, k, mode, lb_mode, alpha, scale, flags, noise,
                           tau, (const int32_t*)r.at[0], (const float*)r.at[1], (const float*)r.at[2], (const int32_t*)r.at[3],
                           (const int32_t*)r.at[4], (const int32_t*)r.at[5], (const float*)r.at[6], (const float*)r.at[7],
                           (const int32_t*)r.at[8], h1, h3, dX, dWr, dbr, dW1, dW3, dW2, dw_dt, ws, bytes, stream);

@@ -236,3 +236,44 @@ def test_arguments_that_do_not_fit_are_refused_in_the_binding(lib, entry, positi
         args[position] = wrong(args[position])
     with pytest.raises(error):
         call(*args, **options)
+
+
+def apart(W):
+    """The same matrices, 8 elements further apart."""
+    wide = torch.zeros(W.shape[0], W[0].numel() + 8, dtype=W.dtype)
+    return wide[:, :W[0].numel()].unflatten(1, W.shape[1:])
+
+
+# every check by its message: host tensors are refused whatever else is wrong with them
+@pytest.mark.parametrize("entry,position,wrong,message", [
+    ("route", 1, lambda W: W.bfloat16(), "W_router"), ("route", 1, lambda W: W[1:], "W_router"), ("norm_route", 3, lambda W: W[1:], "W_router"),
+    ("norm_route", 1, lambda g: g[1:], "gain"), ("norm_route", 1, lambda g: g.double(), "gain"),
+    *[(entry, at + 2 * (entry == "backward"), wrong, message) for entry in ("forward", "backward") for at, wrong, message in [
+        (1, lambda W: W.transpose(1, 2), "stacked"), (1, lambda W: W.bfloat16(), "of x's dtype"), (2, lambda W: W.bfloat16(), "of x's dtype"),
+        (3, lambda W: W.bfloat16(), "of x's dtype"), (2, lambda W: W[:, :, 8:], "of x's dtype"), (3, lambda W: W[:2], "of x's dtype"), (3, lambda W: W[0], "stacked"),
+        (1, apart, "W3 is stacked like W1"), (2, apart, "W3 is stacked like W1"), (3, apart, "device-resident")]]])
+def test_arguments_are_refused_for_what_is_wrong_with_them(lib, entry, position, wrong, message):
+    call, args, options = marshalled_calls()[entry]
+    args[position] = wrong(args[position])
+    frozen = dict(frozen_experts=True) if entry == "backward" else {}
+    with pytest.raises(AssertionError, match=message):
+        call(*args, **options, **frozen)
+
+
+@pytest.mark.parametrize("dtype,asked,message", [
+    (torch.float32, torch.float32, "device-resident"), (torch.float32, None, "device-resident"), (torch.bfloat16, torch.float32, "dW is of dW_dtype"),
+    (torch.bfloat16, None, "dW is of dW_dtype"), (torch.float32, torch.bfloat16, "dW is of dW_dtype")])
+def test_weight_gradients_of_another_dtype_than_asked_for_are_refused(lib, dtype, asked, message):
+    """They would be written past their end, or half."""
+    call, args, options = marshalled_calls()["backward"]
+    x, Wr, W1, W3, W2 = args[1:6]
+    grads = B.Grads(torch.empty_like(x), torch.empty_like(Wr), torch.empty(Wr.shape[1]), *[torch.empty_like(W, dtype=dtype) for W in (W1, W3, W2)])
+    with pytest.raises(AssertionError, match=message):
+        call(*args, **options, out=grads, dW_dtype=asked)
+
+
+def test_one_expert_may_have_any_stride(lib):
+    call, args, options = marshalled_calls()["forward"]
+    x, W1, W3, W2, r = args
+    with pytest.raises(AssertionError, match="device-resident"):
+        call(x, W1[:1], apart(W3)[:1], W2[:1], r, **options)
