@@ -806,14 +806,20 @@ __global__ __launch_bounds__(kThreads, 4) void f32_ff_kernel(FfArgs g) {
 
 }  // namespace
 
-// Small layers, up to 192 columns and 47 million products (rows x d x f), by 95 forward calls of 16 to 2003 tokens, 2 to 8 experts, on both
-// ways (us, UP and DOWN / joint): 512 tokens of 64, f = 176, 4 experts 10.9 / 7.7; 77 of 64, f = 208, 5 11.0 / 7.4; 1000 of 64, f = 128, 8, top-4
-// 13.1 / 9.1; 458 of 96, f = 208, 2 12.2 / 10.0; 249 of 128, f = 664, 4 (42 million) 14.0 / 12.9; 69 of 192, f = 192, 5 12.4 / 11.7.  Above, 16
-// rows to a tile read the weights too often, and wide rows are a chain of passes: 400 of 192, f = 320, 5 (49) 14.7 / 14.8; 547 of 232, f =
-// 240, 5 (61) 16.6 / 17.7; 1064 of 144, f = 208, 5 (64) 15.6 / 18.0; 1349 of 168, f = 416, 5 (189) 26.7 / 31.7; 100 of 504, f = 64, 2 19.2 / 22.7.
+// Small layers, up to 192 columns and 47 million products (rows x d x f, at least 64 columns of f, which a workgroup takes), by 95 forward
+// calls of 16 to 2003 tokens, 2 to 8 experts, on both ways (us, UP and DOWN / joint): 512 tokens of 64, f = 176, 4 experts 10.9 / 7.7; 77 of 64,
+// f = 208, 5 11.0 / 7.4; 1000 of 64, f = 128, 8, top-4 13.1 / 9.1; 458 of 96, f = 208, 2 12.2 / 10.0; 249 of 128, f = 664, 4 (42 million) 14.0 /
+// 12.9; 69 of 192, f = 192, 5 12.4 / 11.7.  Above, 16 rows to a tile read the weights too often, and wide rows are a chain of passes: 400 of
+// 192, f = 320, 5 (49) 14.7 / 14.8; 547 of 232, f = 240, 5 (61) 16.6 / 17.7; 1064 of 144, f = 208, 5 (64) 15.6 / 18.0; 1349 of 168, f = 416, 5
+// (189) 26.7 / 31.7; 100 of 504, f = 64, 2 19.2 / 22.7; 13020 of 192, f = 8, 1 21.5 / 26.5.  And up to 16000 rows times pieces of 64 columns: four
+// times as many workgroups as tiles of 64 rows make, no more than run at once (1024).  Of narrow rows, by 1875 calls of 16 to 300000 tokens, 1 to
+// 64 experts, 8 to 240 x 8 to 2560: 46875 of 16, f = 8, 1 expert 19.0 / 24.2; 183593 of 32, f = 8, 1 58.7 / 89.0; 14687 of 8, f = 200, 1 33.4 / 43.5;
+// 10374 of 24, f = 72, 3 14.0 / 15.8.  Of those that the rule takes five are more than 2 % slower, 2148 of 160, f = 16, 32, top-2 the most (13.4 /
+// 14.7); on average of all calls it leaves 1 % to the better way.
 int f32_ff_slices(const FfShapes& sh, int64_t most) {
   const int slices = ceil_div(sh.f, kFfCols);
-  return sh.d <= 192 && (int64_t)sh.R * sh.d * sh.f <= 47000000 && slices <= most ? slices : 0;
+  const bool small = (int64_t)sh.R * sh.d * std::max(sh.f, kFfCols) <= 47000000 && (int64_t)sh.R * slices <= 16000;
+  return sh.d <= 192 && small && slices <= most ? slices : 0;
 }
 int f32_ff(const RowSource& xs, const void* W1, const void* W3, const void* W2, const int32_t* off, const FfShapes& sh, void* h1, void* h3,
            void* sums, hipStream_t s) {

@@ -195,6 +195,15 @@ def test_limits_of_small_fp32_layers(record, T, d, f, E, k, joint):
     assert rc == 0 and found[0].kernel.startswith("f32_ff_kernel" if joint else "f32_gemm_kernel<0")
 
 
+@pytest.mark.parametrize("T,d,f,E,k,joint", [
+    # many narrow rows: more workgroups than run at once; experts of fewer columns than a workgroup takes
+    (16000, 8, 8, 1, 1, True), (16001, 8, 8, 1, 1, False), (4000, 8, 72, 2, 2, True), (4001, 8, 72, 2, 2, False), (300000, 16, 8, 4, 1, False),
+    (11474, 64, 8, 1, 1, True), (11475, 64, 8, 1, 1, False), (13020, 192, 8, 1, 1, False), (1, 8, 4096, 1, 1, True)])
+def test_rows_of_small_fp32_layers(record, T, d, f, E, k, joint):
+    (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32))
+    assert rc == 0 and found[0].kernel.startswith("f32_ff_kernel" if joint else "f32_gemm_kernel<0")
+
+
 def test_sums_of_small_fp32_layers_fit_the_workspace(record):
     """Their slices, [slice][T k, d] from the workspace's start on, at every number of columns: no more than the query asks for."""
     shapes = [(T, d, f, k) for T in (1, 33, 200) for k in (1, 2, 8) for d in range(8, 200, 8) for f in (8, 64, 72, 136, 256, 264, 520, 1024, 1376, 2048)]
