@@ -340,7 +340,7 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
   // of weight gradients that read token rows: all of them, or (tiles) dW2, where transposed rows of dY would lie
-  const bool dw2_rows = dtype == BTX_BF16 && !direct && fused && mfma_dw2_rows(f);
+  const bool dw2_rows = dtype == BTX_BF16 && !direct && fused && mfma_dw2_rows(sh);
   uint32_t* row_bytes = n_dw != 3 ? nullptr : direct ? w.row_bytes : dw2_rows ? static_cast<uint32_t*>(w.dysT) : nullptr;
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));

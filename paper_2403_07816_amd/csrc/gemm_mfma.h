@@ -38,7 +38,7 @@ int mfma_act_pitch(int f);
 int mfma_bwd_dw13(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1,
                   void* dW3, hipStream_t s);
 // row_bytes: dys are token rows, found by it (mfma_dw2_rows(); NULL: transposed like xs)
-bool mfma_dw2_rows(int f);
+bool mfma_dw2_rows(const FfShapes& sh);
 int mfma_bwd_dw2(int dW_dtype, const void* ga, const RowSource& dys, const int32_t* off, const FfShapes& sh, uint32_t* row_bytes, void* dW2,
                  hipStream_t s);
 int mfma_bwd_dw_direct(int dW_dtype, const RowSource& xs, const RowSource& dys, const void* dh1, const void* dh3, const void* ga,

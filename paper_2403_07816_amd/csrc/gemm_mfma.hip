@@ -16,7 +16,7 @@
 //   * an operand whose K index is contiguous in memory is stored [row][BK] with a 16-byte
 //     chunk XOR swizzle and read with ds_read_b128; an operand whose K index is strided
 //     (the weights in UP and DOWN, dh1/dh3 in DW13, token rows of dY in DW2) is stored as it lies in memory,
-//     [BK][cols], and read with the transposing ds_read_b64_tr_b16; x, ga and, for wide experts (mfma_dw2_rows()),
+//     [BK][cols], and read with the transposing ds_read_b64_tr_b16; x, ga and, where mfma_dw2_rows() has it so,
 //     dY reach the dW products of many rows per expert transposed and zero-padded (x and dY from a gather
 //     kernel, ga written that way by BWD_ACT's epilogue; see DwStrip for few rows).  The swizzles are applied by choosing which
 //     global chunk each lane fetches, since a direct copy fixes the LDS position per lane;
@@ -1942,12 +1942,18 @@ bool mfma_dw_direct(const FfShapes& sh, int dW_dtype) {
 }
 
 // dW2 of 256 x 256 tiles from token rows of dY as they lie, turned around by transposing reads as dh1 and dh3 are, or from rows that the
-// gather has transposed with x's?  Rows spare half of that gather, the same for experts of any width, and take a quarter more reads from
-// LDS per product and the looking up of the rows.  Backward pass, us, transposed / rows: 16384 tokens, 32 experts of 4096 x 1376, top-8
-// 8364 / 8077 (the gather 677 / 341, dW2 1217 / 1290); 64 of 4096 x 688 5599 / 5266; 16 of 4096 x 2752, top-4 7274 / 7182; 32 of 1024 x 688,
-// top-8 1756 / 1626; 8 of 4096 x 4096, top-4, 8192 tokens 5041 / 5018; 8 of 4096 x 5504, top-4 13185 / 13078; but 4 of 4096 x 11008, top-2,
-// a training pass 19254 / 19357 (the gather 181 / 94, dW2 1977 / 2150), top-1 10068 / 10137.
-bool mfma_dw2_rows(int f) { return f <= 6144; }
+// gather has transposed with x's?  Rows spare half of that gather, the same for experts of any width (0.63 us per million elements), and take a
+// quarter more reads from LDS per product and the looking up of the rows: 0.12 us of a k tile and round of tiles, so what is lost grows with
+// the width, counted with what a last column tile has too much, and where the tiles do not fill the chip with the k tiles alone.  Backward
+// pass, us, transposed / rows: 16384 tokens, 32 experts of 4096 x 1376, top-8 8364 / 8077 (the gather 677 / 341, dW2 1217 / 1290); 64 of 4096 x
+// 688 5599 / 5266; 16 of 4096 x 2752, top-4 7274 / 7182; 32 of 1024 x 688, top-8 1756 / 1626; 4 of 4096 x 4096, top-2 5010 / 4948, 6144 7363 / 7335,
+// 8192 9622 / 9623, 11008 (a training pass) 19254 / 19357; 4001, 4 of 2048 x 5504 1026 / 1029; 8192, 1 of 4096 x 6144 1910 / 1917.  Few tiles and
+// narrow rows: 16384 tokens, 1 expert of 1024 x 1376 734 / 745, 64 x 344 556 / 587; 4, top-2, of 64 x 344 378 / 393, 512 x 344 454 / 452; 1050 rows,
+// 1 of 64 x 1400 83 / 87, 9 of 520 x 2752 336 / 337.  Of 262 random shapes that the rule takes three are 0.6 to 1.4 % slower, all together 3 % faster;
+// 58 beside it would gain 0.7 % all together, the best 4 %.
+bool mfma_dw2_rows(const FfShapes& sh) {
+  return sh.d >= 256 && (int64_t)sh.d * sh.E >= 4096 && (int64_t)sh.f * (int64_t)align_up((size_t)sh.d, 256) <= (int64_t)4096 * sh.d;
+}
 
 namespace {
 MArgs dw13_args(int dW_dtype, const RowSource& xs, const void* dh1, const void* dh3, const int32_t* off, const FfShapes& sh, void* dW1, void* dW3) {

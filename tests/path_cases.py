@@ -59,13 +59,18 @@ JOINT_FORWARD = [
     (40, 184, 776, 2, 2, dict(poison=True)), (100, 24, 1376, 3, 2, dict(bias=[4.0, 0.0, -60.0])), (1270, 192, 192, 3, 1, {}), (50, 40, 512, 8, 8, {}),
 ]
 
-# weight gradients of tiles whose dW2 reads dY's token rows (experts of up to 6144 columns): experts of 0, 1 and a few k tiles beside long
-# ones, remainders of a k tile, one and several column tiles, tokens of several slots, dropped pairs; and of wider ones, which reads them transposed
+# weight gradients of tiles whose dW2 reads dY's token rows (d E from 4096 on, up to 4096 columns): experts of 0, 1 and a few k tiles beside
+# long ones, remainders of a k tile, one and several column tiles, tokens of several slots, dropped pairs; and those that read them transposed
 DY_ROWS = [
+    (1001, 4104, 1304, 1, 1, {}), (8100, 256, 1400, 16, 1, dict(bias=[2.0, 0.0, -60.0, -3.0] + [0.0] * 12, poison=True)),
+    (1700, 1032, 3208, 4, 1, dict(bias=[5.0, 0.0, 0.0, -60.0], poison=True)), (1000, 1376, 2056, 3, 2, dict(cf=0.8, poison=True)),
+    (1700, 520, 1496, 9, 5, dict(bias=[0.0] * 8 + [-3.0], poison=True)),
+]
+DY_TRANSPOSED = [
+    (500, 264, 6152, 1, 1, {}), (420, 72, 6400, 2, 2, dict(bias=[3.0, 0.0], poison=True)),
     (1001, 64, 1400, 1, 1, {}), (1088, 264, 1400, 1, 1, {}), (1500, 520, 3608, 4, 1, dict(bias=[5.0, 0.0, 0.0, -60.0], poison=True)),
     (1000, 1032, 2056, 3, 2, dict(cf=0.8, poison=True)), (1300, 248, 1496, 9, 5, dict(bias=[0.0] * 8 + [-3.0], poison=True)),
 ]
-DY_TRANSPOSED = [(500, 264, 6152, 1, 1, {}), (420, 72, 6400, 2, 2, dict(bias=[3.0, 0.0], poison=True))]
 
 # fp32 DOWN whose last round of tiles is cut along K: last k tiles of 8, 16 and 32, column tiles of 24 to 64; experts of uneven numbers of
 # rows (other numbers of tiles than expected: more slices, fewer, none), dropped pairs

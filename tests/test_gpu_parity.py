@@ -580,9 +580,10 @@ def test_bf16_weight_gradients_of_tiles_from_token_rows_of_dY(T, d, f, E, k, kw,
     run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, dW_dtype=dW_dtype, **kw)
 
 
-def test_bf16_an_infinity_in_the_last_row_of_dY_stays_in_its_column():
+@pytest.mark.parametrize("d", [64, 4096])          # rows transposed, and token rows as they lie
+def test_bf16_an_infinity_in_the_last_row_of_dY_stays_in_its_column(d):
     """The last k tile's rows past the expert's last one repeat it: they must not turn its infinity into NaN."""
-    T, d, f = 1001, 64, 1400
+    T, f = 1001, 1400
     G = to_dev(synth.make_layer(T, d, f, 1, dtype=BF16, with_dY=True, unit_rms=True))
     r = B.btx_moe_route(G["x"], G["W_router"], k=1)
     _, h1, h3 = B.btx_moe_ff_forward(G["x"], G["W1"], G["W3"], G["W2"], r)

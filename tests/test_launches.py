@@ -105,9 +105,12 @@ def test_shapes_of_transposed_rows_take_that_path(record, case):
 
 
 @pytest.mark.parametrize("case,rows", [(c, True) for c in DY_ROWS] + [(c, False) for c in DY_TRANSPOSED] +
-                         [((16384, 4096, 6144, 4, 2), True), ((16384, 4096, 6152, 4, 2), False), ((1 << 19, 4104, 1024, 4, 1), False)])
+                         [((16384, 4096, 4096, 4, 2), True), ((16384, 4096, 4104, 4, 2), False), ((1 << 19, 4104, 1024, 4, 1), False),
+                          ((16384, 4096, 1376, 1, 1), True), ((16384, 4088, 1376, 1, 1), False), ((16384, 256, 4096, 16, 2), True), ((16384, 248, 4096, 17, 2), False),
+                          ((16384, 520, 2768, 8, 2), True), ((16384, 520, 2776, 8, 2), False), ((16384, 64, 1376, 64, 8), False)])
 def test_dW2_of_tiles_reads_token_rows_of_dY(record, case, rows):
-    """Experts of up to 6144 columns, unless the rows' offsets need more than 32 bits; x alone is transposed then."""
+    """Experts of up to 4096 columns, counted as the tiles' columns of d go over its own, and d times experts from 4096 on, unless the
+    rows' offsets need more than 32 bits; x alone is transposed then."""
     (rc, found), = record(backward_call(*case[:5], B.BTX_BF16))
     gather, = [launch for launch in found if launch.kernel.startswith("gather_rows_t")]
     dw2, = [launch for launch in found if ", 5, 0, " in launch.kernel]
