@@ -154,13 +154,19 @@ def profiled_traffic(stage):
     return (fetch / factors["FETCH_SIZE"] + write / factors["WRITE_SIZE"]) * 1024.0, src
 
 
-def hbm_stages(stage_ms, T, d, E, k, s=2, block=False):
+def transposed_matrices(T, d, f, E):
+    """How many matrices gather_x_bwd hands over: x, and dY unless dW2 reads its token rows as they lie (the library's rule)."""
+    token_rows = d >= 256 and d * E >= 4096 and f * -(-d // 256) * 256 <= 4096 * d
+    return 1 if token_rows and T * d * 2 < 1 << 32 else 2
+
+
+def hbm_stages(stage_ms, T, d, f, E, k, s=2, block=False):
     """The streaming stages against the 8 TB/s HBM peak: algorithmic bytes per token (bf16 rows of d*s bytes) and
     the rate they were moved at.  route: x read once + indices, gates, probabilities written; combine: k rows read,
-    one written; gather_x_bwd: x and dY each read once per routed slot and written once per slot, transposed;
+    one written; gather_x_bwd: x, and dY where it needs to, read once per routed slot and written once per slot, transposed;
     router_bwd: x read (dW_router), k rows of dxs read and one row of dX written (small batches: its first part, which moves none
     of these rows, runs beside the weight gradients)."""
-    per_token = {"route": d * s + k * 8 + E * 4, "combine": d * s * (k + 1), "gather_x_bwd": 2 * d * s * 2 * k,
+    per_token = {"route": d * s + k * 8 + E * 4, "combine": d * s * (k + 1), "gather_x_bwd": transposed_matrices(T, d, f, E) * d * s * 2 * k,
                  "router_bwd": d * s * (k + 2)}
     if block:   # route also writes the normalised rows; combine also reads the residual; norm_bwd: dXn, h, dY in, dH out
         per_token.update({"route": 2 * d * s + k * 8 + E * 4 + 4, "combine": d * s * (k + 2), "norm_bwd": 4 * d * s})
@@ -377,7 +383,7 @@ class Layer:
                 "expert_gemms": {"ms": gemm_ms, "tflops": gemm_tflops, "frac_of_peak": gemm_tflops / PEAK_BF16_TFLOPS,
                                  "layer_frac_of_peak": gemm_coef * d * f * R / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
                                  "per_kernel": gemm},
-                "hbm_stages": hbm_stages(stage_ms, T, d, E, k, block=self.block)}
+                "hbm_stages": hbm_stages(stage_ms, T, d, f, E, k, block=self.block)}
 
 
 def merge_bench(dev, steps=10, warmup=2, cpu_elems=1 << 26):
