@@ -3,13 +3,15 @@
 Argument marshalling only: torch supplies device memory and the current HIP
 stream; every step of the layer runs in the library's kernels.  There is no
 fallback: if the shared library is missing, calls raise.  The calls that every
-layer makes go through _marshal (csrc/marshal.cpp), the others through ctypes: a
+layer makes go through _marshal (csrc/marshal.cpp), which they load; the others
+through ctypes, without it: a
 forward call took 7 us in Python beside its launches' 2.5 us each, and a pass over
 512 tokens of 64 columns (fp32, 4 experts), which the host bounded, 24.7 us; now 16.8.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
@@ -57,7 +59,7 @@ _SIGNATURES = {
 
 def load_library() -> ctypes.CDLL:
     """Load the in-tree shared library; raises if it has not been built."""
-    global _lib, _marshal
+    global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2403_07816_amd.build` "
@@ -66,13 +68,25 @@ def load_library() -> ctypes.CDLL:
         for name, (res, args) in _SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
-        try:
-            from . import _marshal as native
-        except ImportError as e:
-            raise RuntimeError("_marshal.so is missing: build it with `python -m paper_2403_07816_amd.build`") from e
-        native.bind(LIB_PATH)
-        _lib, _marshal = lib, native
+        _lib = lib
     return _lib
+
+
+def load_marshal():
+    """Load the in-tree _marshal.so and bind it to the library; raises if it has not been built, or not for this Python and torch."""
+    global _marshal
+    if _marshal is None:
+        load_library()
+        rebuild = "build it with `python -m paper_2403_07816_amd.build`"
+        try:
+            native = importlib.import_module("._marshal", __package__)
+        except ModuleNotFoundError as e:
+            raise RuntimeError(f"_marshal.so is missing: {rebuild}") from e
+        except ImportError as e:
+            raise RuntimeError(f"_marshal.so does not load beside this Python and torch ({e}): {rebuild}") from e
+        native.bind(LIB_PATH)
+        _marshal = native
+    return _marshal
 
 
 class BtxError(RuntimeError):
@@ -114,9 +128,7 @@ def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> torch.
 
 def _run(entry: str, what: str, x: torch.Tensor, workspace: Optional[torch.Tensor], args: tuple) -> None:
     """An entry point of _marshal, which wants a workspace of as many bytes as it then names where there is none or it is too small."""
-    if _marshal is None:
-        load_library()
-    fn, stream = getattr(_marshal, entry), _stream() if x.is_cuda else 0     # (host tensors are refused)
+    fn, stream = getattr(_marshal or load_marshal(), entry), _stream() if x.is_cuda else 0     # (host tensors are refused)
     st = fn(*args, workspace, stream)
     if st < 0:
         st = fn(*args, torch.empty(-st, dtype=torch.uint8, device=x.device), stream)

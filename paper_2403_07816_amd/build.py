@@ -33,7 +33,8 @@ def _compile(src: str) -> str:
 
 
 def _compile_marshal() -> None:
-    """Host code against the headers of Python and of the torch that is installed; their libraries are loaded wherever it is."""
+    """Host code (CXX: any C++17 compiler) against the headers of Python and of the torch that is installed; their libraries are loaded
+    wherever it is."""
     import torch                                     # (where it lies; nothing of it runs)
     base = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", INCLUDE,
@@ -51,11 +52,11 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         marshal = ex.submit(_compile_marshal)
         objs = list(ex.map(_compile, sources()))
-        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
+    marshal.result()                                 # (behind the library, which needs none of its headers)
     if verbose:
         print(f"built {LIB} from {len(objs)} translation units", file=sys.stderr)
     return LIB

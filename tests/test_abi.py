@@ -3,6 +3,7 @@ function the header declares, and rejects bad arguments before launching anythin
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 import torch
@@ -206,6 +207,52 @@ def test_missing_library_raises(monkeypatch):
     monkeypatch.setattr(B, "LIB_PATH", "/nonexistent/libbtx_moe.so")
     with pytest.raises(RuntimeError):
         B.load_library()
+
+
+class Refusing:
+    """Import of _marshal ends with `error`."""
+
+    def __init__(self, error):
+        self.error = error
+
+    def find_spec(self, name, path=None, target=None):
+        if name == "paper_2403_07816_amd._marshal":
+            raise self.error
+
+
+@pytest.mark.parametrize("error,said", [
+    (ModuleNotFoundError("No module named '_marshal'"), "is missing"), (ImportError("_marshal.so: undefined symbol: _ZN2at6Tensor"), "undefined symbol")])
+def test_calls_that_need_no_marshalling_do_without_it(lib, monkeypatch, error, said):
+    """The library, its size queries and the calls through ctypes; those of every layer say what is wrong with it."""
+    calls = marshalled_calls()
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_marshal", None)
+    monkeypatch.setattr(sys, "meta_path", [Refusing(error), *sys.meta_path])
+    monkeypatch.delitem(sys.modules, "paper_2403_07816_amd._marshal", raising=False)
+    monkeypatch.delattr(sys.modules["paper_2403_07816_amd"], "_marshal", raising=False)
+    assert B.load_library().btx_moe_ff_forward_workspace_bytes(64, 64, 64, 4, 2, B.BTX_BF16) > 0
+    with pytest.raises(AssertionError, match="device-resident"):
+        B.btx_adamw_step(*[torch.zeros(8)] * 4, 1, 1e-4)
+    for call, args, options in calls.values():
+        with pytest.raises(RuntimeError, match=said):
+            call(*args, **options)
+
+
+def test_the_library_is_linked_where_the_marshalling_cannot_be_built(tmp_path, monkeypatch):
+    """Programs without Python need neither torch's headers nor _marshal.so."""
+    from paper_2403_07816_amd import build
+
+    def no_headers():
+        raise RuntimeError("no headers of torch")
+    lib, linked = str(tmp_path / "libbtx_moe.so"), []
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", lib)
+    monkeypatch.setattr(build, "_compile_marshal", no_headers)
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **_: linked.append(cmd) or build.subprocess.CompletedProcess(cmd, 0, "", ""))
+    with pytest.raises(RuntimeError, match="no headers of torch"):
+        build.build(verbose=False)
+    assert [cmd[-1] for cmd in linked] == [lib]
 
 
 def marshalled_calls():
