@@ -627,14 +627,16 @@ int slices_of(const FfShapes& sh, bool two_passes) {
 // / 145.3 (DOWN 70 / 55.7 and 4.8 for the sums; training pass 534.5 / 522.4); of 512 x 688 91.6 / 85.8; 4006 of 256 x 1376 (517) 165.0 / 151.1;
 // but 4 experts of 512 x 1376, 517 tiles expected and 512 there, 140.9 / 143.0.
 bool f32_cut(const FfShapes& sh) {
+  auto gains = [&](double slices) { return 0.5 * ceil_div(sh.f, kTileK) * (1.0 - 1.0 / slices) > 7.0; };
+  if (!gains(Cut::MOST) || sums_bytes(sh, false) < (size_t)8 * Cut::UNITS * kTile * kTile * sizeof(float)) return false;
   const double rows = (double)sh.R / sh.E, spread = std::sqrt(2.0 * rows * (1.0 - 1.0 / sh.E));
-  double row_tiles = 0;                                  // of an expert, for rows spread at random
-  for (int j = 0; j < ceil_div(sh.R, kTile) && kTile * j < rows + 8 * spread; ++j)
+  // row tiles of an expert, for rows spread at random: the first ones for certain (erfc(-8) is 2 to the last bit)
+  const int sure = (int)(std::max(rows - 8 * spread, 0.0) / kTile);
+  double row_tiles = sure;
+  for (int j = sure; j < ceil_div(sh.R, kTile) && kTile * j < rows + 8 * spread; ++j)
     row_tiles += spread > 0 ? 0.5 * std::erfc((kTile * j + 0.5 - rows) / spread) : 1.0;
   const double tiles = std::round(row_tiles * sh.E) * ceil_div(sh.d, kTile), rounds = std::floor(tiles / 256), left = tiles - 256 * rounds;
-  if (rounds < 1 || left < ceil_div(sh.d, kTile) || left > 120 || sums_bytes(sh, false) < (size_t)8 * Cut::UNITS * kTile * kTile * sizeof(float)) return false;
-  const double slices = std::min(std::floor(256 / left), (double)Cut::MOST);
-  return 0.5 * ceil_div(sh.f, kTileK) * (1.0 - 1.0 / slices) > 7.0;
+  return rounds >= 1 && left >= ceil_div(sh.d, kTile) && left <= 120 && gains(std::min(std::floor(256 / left), (double)Cut::MOST));
 }
 
 // Do byte offsets from a tile's first row (gathered: from token 0) need more than 32 bits?  A tile spans 64 rows.

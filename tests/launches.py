@@ -55,7 +55,7 @@ const char* taken() { static std::string out; out.swap(log_text); log_text.clear
 """
 
 CHILD = r"""
-import ctypes, json, sys
+import ctypes, json, sys, time
 log = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 log.taken.restype = ctypes.c_char_p
 lib = ctypes.CDLL(sys.argv[2])
@@ -63,9 +63,12 @@ out = []
 for name, args in json.load(sys.stdin):
     fn = getattr(lib, name)
     fn.restype = ctypes.c_size_t if name.endswith("bytes") else ctypes.c_int
-    rc = fn(*[(ctypes.c_float if isinstance(a[0], float) else ctypes.c_void_p).__mul__(len(a))(*a) if isinstance(a, list) else
-              ctypes.c_float(a) if isinstance(a, float) else ctypes.c_int64(a) for a in args])
-    out.append((rc, log.taken().decode()))
+    args = [(ctypes.c_float if isinstance(a[0], float) else ctypes.c_void_p).__mul__(len(a))(*a) if isinstance(a, list) else
+            ctypes.c_float(a) if isinstance(a, float) else ctypes.c_int64(a) for a in args]
+    start = time.perf_counter()
+    rc = fn(*args)
+    seconds = time.perf_counter() - start
+    out.append((rc, log.taken().decode(), seconds))
 print(json.dumps(out))
 """
 
@@ -90,9 +93,7 @@ def _short(name):
     return name
 
 
-def launches(calls, tmp_path):
-    """calls: (entry point, arguments) with pointers as integers, floats as floats and host arrays as lists; per call its status
-    and its launches."""
+def _recorded(calls, tmp_path):
     source, stand_in = os.path.join(tmp_path, "stand_in.cpp"), os.path.join(tmp_path, "stand_in.so")
     if not os.path.exists(stand_in):
         with open(source, "w") as f:
@@ -101,8 +102,19 @@ def launches(calls, tmp_path):
     r = subprocess.run([sys.executable, "-c", CHILD, stand_in, B.LIB_PATH], input=json.dumps(calls), capture_output=True, text=True,
                        timeout=120)
     assert r.returncode == 0, r.stderr
+    return json.loads(r.stdout)
+
+
+def host_seconds(call, tmp_path):
+    """The least that a call takes on the host."""
+    return min(seconds for _, _, seconds in _recorded([call] * 50, tmp_path))
+
+
+def launches(calls, tmp_path):
+    """calls: (entry point, arguments) with pointers as integers, floats as floats and host arrays as lists; per call its status
+    and its launches."""
     result = []
-    for rc, text in json.loads(r.stdout):
+    for rc, text, _ in _recorded(calls, tmp_path):
         found = []
         for line in text.splitlines():
             *numbers, name = line.split(" ", 8)

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2403_07816_amd import binding as B
 
-from launches import P, adamw_call, backward_call, forward_call, launches, route_call
+from launches import P, adamw_call, backward_call, forward_call, host_seconds, launches, route_call
 from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
@@ -163,6 +163,13 @@ def test_fp32_up_projection_of_weights_from_memory_has_three_stages(record, T, d
     (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32))
     up, = [launch.kernel for launch in found if launch.kernel.startswith("f32_gemm_kernel<0")]
     assert rc == 0 and up.endswith(f", {stages}>")
+
+
+@pytest.mark.parametrize("T,E,k", [(4_000_000, 2, 1), (2_000_000, 2, 2), (1_500_000, 8, 2), (4_000_000, 1, 1)])
+def test_many_fp32_rows_cost_the_host_no_more_than_few(tmp_path, T, E, k):
+    """The expected tiles of DOWN's last round are counted without a step for each of them (117 us beside 5 at 2 000 000 rows of an expert)."""
+    few, many = (host_seconds(forward_call(n, 256, 1376, E, k, B.BTX_F32, save=False), str(tmp_path)) for n in (5000, T))
+    assert many < 5 * few + 50e-6
 
 
 @pytest.mark.parametrize("case,cut", [(c, True) for c in F32_LAST_ROUND] + [
