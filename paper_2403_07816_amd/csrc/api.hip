@@ -46,18 +46,18 @@ BwdWs carve_backward(void* ws, int T, int d, int f, int E, int k, int dtype) {
   const FfShapes sh{(int)R, d, f, E, 0, 0};
   Carver c(ws);
   BwdWs w;
-  // the bf16 dW products of many rows per expert take x and dY transposed and padded
-  const bool tr = ff_dw_transposed(dtype);
+  // the bf16 dW products of many rows per expert take x, and dY where dW2 does not read its token rows, transposed and padded
+  const bool tr = ff_dw_transposed(dtype), dw2_rows = ff_dw2_rows(dtype, T, sh);
   const size_t dw_op = (size_t)d * ff_dw_pitch((int)R, E) * es;
   w.xsT = tr ? c.take(dw_op) : nullptr;
-  w.dysT = tr ? c.take(dw_op) : nullptr;
-  // byte offsets of the token rows, for weight gradients that read them: bf16, where the transposed rows would lie
-  w.row_bytes = static_cast<uint32_t*>(tr ? w.xsT : c.take(R * sizeof(uint32_t)));
+  w.dysT = tr && !dw2_rows ? c.take(dw_op) : nullptr;
+  // byte offsets of the token rows, for weight gradients that read them: where the transposed rows would lie, if all of them do
+  w.row_bytes = static_cast<uint32_t*>(w.dysT ? w.xsT : c.take(R * sizeof(uint32_t)));
   w.dys = ff_gather_fused(dtype, T, d) ? nullptr : c.take(R * d * es);
   const size_t rows_f = R * ff_act_pitch(dtype, f) * es;
   w.dh1 = c.take(rows_f);
   w.dh3 = c.take(rows_f);
-  // transposed path: dW2 reads ga as [f][padded rows]; in row order it is smaller
+  // dW2 reads ga as [f][padded rows], or in row order, rows ff_act_pitch() apart
   w.ga = c.take(std::max(tr ? (size_t)f * ff_dw_pitch((int)R, E) * es : 0, rows_f));
   w.dxs = c.take(R * d * es);
   w.dg_part = static_cast<float*>(c.take(R * (size_t)bwd_act_partials_most(dtype, f) * sizeof(float)));
@@ -339,9 +339,9 @@ int btx_moe_ff_backward(const void* dY, const void* x, const float* W_router, co
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!fused) BTX_STAGE(BTX_STAGE_GATHER_DY, launch_gather_rows(dY, w.dys, perm, R, k, d, dtype, s));
   const RowSource dys = fused ? RowSource{dY, perm, k} : RowSource{w.dys, nullptr, 1};
-  // of weight gradients that read token rows: all of them, or (tiles) dW2, where transposed rows of dY would lie
-  const bool dw2_rows = dtype == BTX_BF16 && !direct && fused && mfma_dw2_rows(sh);
-  uint32_t* row_bytes = n_dw != 3 ? nullptr : direct ? w.row_bytes : dw2_rows ? static_cast<uint32_t*>(w.dysT) : nullptr;
+  // of weight gradients that read token rows: all of them, or (tiles) dW2
+  const bool dw2_rows = !direct && ff_dw2_rows(dtype, T, sh);
+  uint32_t* row_bytes = n_dw == 3 && (direct || dw2_rows) ? w.row_bytes : nullptr;
   BTX_STAGE(BTX_STAGE_BWD_ACT, launch_bwd_act(dtype, dys, W2, save_h1, save_h3, gates, perm, offsets, sh, w.dh1,
                                               w.dh3, w.ga, n_dw == 3, !direct, row_bytes, w.dg_part, s));
   RouterBwdArgs ra{x, dtype, W_router, T, d, E, k, route_mode, lb_mode, lb_alpha, lb_grad_scale, flags, noise, tau,

@@ -312,6 +312,8 @@ struct RouterDs;
 bool ff_dw_transposed(int dtype);
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused);
 int ff_dw_pitch(int R, int E);
+// dW2 of transposed rows reads dY's token rows as they lie (mfma_dw2_rows()): only x is transposed for it and DW13
+bool ff_dw2_rows(int dtype, int T, const FfShapes& sh);
 // elements from a row of act, dh1, dh3 or (in row order) ga to the next: f, or more
 int ff_act_pitch(int dtype, int f);
 // one-time set-up of the expert GEMM kernels on the current device (everything that may not run inside a stream capture)

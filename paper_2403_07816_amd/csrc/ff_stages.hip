@@ -20,6 +20,7 @@ bool ff_dw_transposed(int dtype) { return dtype == BTX_BF16; }
 bool ff_dw_direct(int dtype, int dW_dtype, const FfShapes& sh, bool gather_fused) {
   return dtype != BTX_BF16 || (gather_fused && mfma_dw_direct(sh, dW_dtype));
 }
+bool ff_dw2_rows(int dtype, int T, const FfShapes& sh) { return dtype == BTX_BF16 && ff_gather_fused(dtype, T, sh.d) && mfma_dw2_rows(sh); }
 int ff_dw_pitch(int R, int E) { return mfma_dw_pitch(R, E); }
 int ff_act_pitch(int dtype, int f) { return dtype == BTX_BF16 ? mfma_act_pitch(f) : f; }
 

@@ -63,6 +63,17 @@ def test_bf16_workspaces_of_small_layers_are_small(record, T, d, f, E, k, forwar
     assert 0 < backward <= backward_kb << 10
 
 
+@pytest.mark.parametrize("T,d,f,E,k,transposed", [
+    (16384, 4096, 1376, 32, 8, 1), (16384, 4096, 4096, 4, 2, 1), (16384, 4096, 4104, 4, 2, 2), (1 << 19, 4104, 1024, 4, 1, 2)])
+def test_bf16_workspaces_hold_the_matrices_that_are_transposed(record, T, d, f, E, k, transposed):
+    """x, ga and dY, but no dY where dW2 reads its token rows; and dxs, dh1, dh3, partial sums of d gates, rows that are gathered."""
+    (size, _), = record(("btx_moe_ff_backward_workspace_bytes", [T, d, f, E, k, B.BTX_BF16]))
+    R, pitch = T * k, T * k + 64 * E
+    gathered = R * d if T * d * 2 >= 1 << 32 else 0
+    least = 2 * (transposed * d * pitch + f * pitch + R * d + 2 * R * f + gathered)
+    assert least <= size < least + d * pitch            # half of a matrix more at most
+
+
 @pytest.mark.parametrize("dW_dtype", [B.BTX_F32, B.BTX_BF16])
 def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_dtype):
     """The strips' stores go past the caches where every row starts on 64 bytes: not for a stack that starts on any other 16-byte
