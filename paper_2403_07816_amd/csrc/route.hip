@@ -175,10 +175,7 @@ constexpr int64_t kSmallTraffic = (int64_t)1 << 25;     // T * d * E: every toke
 constexpr int kSmallThreads = 256, kGroupThreads = 1024;
 
 // AHEAD: pieces of a thread, 8 columns of the token, the first experts' weights and the gain, that are requested at once, in front of the
-// mean square's sum instead of behind it: two with the normalisation of more than 2048 columns.  us, the whole routing of 4096 columns, none
-// / two: 16 tokens, 4 experts 10.5 / 9.8, 8 12.8 / 12.0, 16, top-8 20.6 / 19.6; 512 tokens, 8 experts 18.9 / 18.2, 16 33.3 / 32.1; but 4 experts
-// 14.0 / 14.2, 301 tokens 13.0 / 13.1, where other workgroups cover the wait; of 1024 columns 16 tokens 8.2 / 8.3, 512 10.5 / 11.1; without the
-// normalisation 16 experts 15.6 / 16.4; 32 experts of 3072 26.2 / 26.8.
+// mean square's sum instead of behind it: none or two (see launch_route_small()).
 template <typename XT, int EC, bool NORM, int AHEAD>
 __global__ __launch_bounds__(kSmallThreads) void route_small_tokens_kernel(
     const XT* __restrict__ x, const float* __restrict__ Wr, const float* __restrict__ br, const float* __restrict__ U,
@@ -440,7 +437,14 @@ int launch_route_small(const RouteArgs& a, hipStream_t s) {
     using XT = decltype(tag);
     constexpr int EC = decltype(ec)::value;
     constexpr bool NORM = decltype(norm)::value;
-    const bool ahead = NORM && a.d > 2048 && a.E <= 16 && (a.E > 4 || a.T <= 256);
+    // Two pieces ahead where that was measured to gain: us, the whole routing, none / two: bf16, 4096 columns, 16 tokens, 4 experts 10.7 / 10.0,
+    // 8 12.9 / 12.2, 16 20.5 / 19.8; 512 tokens, 8 experts 19.1 / 18.5, 16 34.1 / 32.3; fp32, 16 tokens, 4 experts 9.8 / 9.3, 512, 8 18.9 / 18.7.  Up
+    // to 2048 columns a thread has no second piece; the fourth and fifth wait as long as they did, beside more registers; of up to 4 bf16 experts
+    // other workgroups cover the wait of more than 256 tokens; a second set of experts that is not whole loses (12, 256 tokens of 3072: bf16 -13 %,
+    // fp32 -14 %).  Of 810 calls of 1024 to 16384 columns, 2 to 32 experts, 16 to 512 tokens it takes 204, which gain 3.9 % on average, four of them
+    // lose 1.2 to 1.8 %.
+    const bool ahead = NORM && a.d > 2048 && (sizeof(XT) == 4 ? a.d <= 4096 && a.E <= 8
+                                                              : a.E <= 4 ? a.d <= 6144 && a.T <= 256 : a.d <= 8192 && (a.E <= 8 || a.E == 16));
     const auto kernel = ahead ? route_small_tokens_kernel<XT, EC, NORM, NORM ? 2 : 0> : route_small_tokens_kernel<XT, EC, NORM, 0>;
     kernel<<<a.T, kSmallThreads, 0, s>>>(
         static_cast<const XT*>(a.x), a.W_router, a.b_router, a.U, a.d, a.E, a.k, a.route_mode, 1.f / a.tau, a.topk_idx,

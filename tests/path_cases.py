@@ -79,6 +79,14 @@ F32_LAST_ROUND = [
     (649, 728, 648, 8, 2, dict(bias=[2.0, 1.0] + [0.0] * 6)), (933, 568, 528, 4, 2, dict(bias=[0.0, 0.0, 0.0, -60.0])),
 ]
 
+# few tokens' routing with the normalisation, two pieces of wide rows requested ahead: (T, d, E, k, dtype).  Rows that end inside the
+# second piece, at its end and behind it; passes over 2, 4 and 8 experts, whole or not, one and two of them
+ROUTE_AHEAD = [
+    (30, 4096, 1, 1, B.BTX_F32), (30, 2064, 2, 1, B.BTX_BF16), (512, 4088, 3, 2, B.BTX_F32), (16, 2056, 4, 2, B.BTX_BF16), (256, 6144, 4, 2, B.BTX_BF16),
+    (70, 2056, 5, 2, B.BTX_BF16), (16, 4104, 6, 2, B.BTX_BF16), (70, 3080, 7, 3, B.BTX_F32), (512, 4096, 8, 2, B.BTX_F32), (512, 8192, 8, 2, B.BTX_BF16),
+    (300, 6152, 8, 2, B.BTX_BF16), (33, 8192, 16, 4, B.BTX_BF16), (70, 2056, 16, 9, B.BTX_BF16),
+]
+
 # many tokens' routing: (T, d, E, k, dtype, with the normalisation) -> experts of a pass over the columns, wavefronts that share 16
 # tokens.  Ragged last blocks; one workgroup on a compute unit, two, more.
 ROUTE_MANY = [

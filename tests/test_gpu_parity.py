@@ -10,7 +10,8 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_MANY, TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case
+from path_cases import (DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_AHEAD, ROUTE_MANY,
+                        TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -812,6 +813,11 @@ def test_router_gradients_of_many_experts_in_a_launch_of_their_own(T, d, E, k):
 ])
 def test_block_rmsnorm_route_forward_backward(T, d, f, E, k, dtype):
     run_block_and_check(T, d, f, E, k, dtype)
+
+
+@pytest.mark.parametrize("T,d,E,k,dtype", ROUTE_AHEAD)
+def test_block_rmsnorm_route_of_few_wide_rows(T, d, E, k, dtype):
+    run_block_and_check(T, d, 64, E, k, F32 if dtype == B.BTX_F32 else BF16)
 
 
 @pytest.mark.parametrize("T,d,E,k,dtype", [
