@@ -59,6 +59,15 @@ JOINT_FORWARD = [
     (40, 184, 776, 2, 2, dict(poison=True)), (100, 24, 1376, 3, 2, dict(bias=[4.0, 0.0, -60.0])), (1270, 192, 192, 3, 1, {}), (50, 40, 512, 8, 8, {}),
 ]
 
+# fp32 forward products in two launches just past what takes one: contractions of one short k tile and widths below a tile's, experts of
+# uneven numbers of rows, dropped pairs -> is DOWN cut along K; its slices added by the combine, and by a kernel of their own (12 slots)
+TILED_FORWARD = [
+    ((5700, 136, 8, 3, 2, dict(poison=True)), False), ((300, 264, 8, 3, 2, dict(cf=0.8, poison=True)), False), ((16100, 8, 8, 1, 1, {}), False),
+    ((2700, 8, 136, 2, 2, dict(bias=[1.0, 0.0])), True), ((2700, 24, 136, 3, 2, dict(cf=0.8, poison=True)), True), ((1800, 72, 184, 4, 3, {}), False),
+    ((330, 72, 1032, 4, 2, dict(poison=True)), True), ((300, 136, 1032, 2, 2, dict(cf=0.8, poison=True)), True), ((130, 200, 776, 4, 2, dict(cf=0.8, poison=True)), True),
+    ((30, 264, 1384, 12, 12, dict(poison=True)), True), ((620, 8, 3000, 3, 2, dict(bias=[0.0, 0.0, -60.0])), True),
+]
+
 # weight gradients of tiles whose dW2 reads dY's token rows (d E from 4096 on, up to 4096 columns): experts of 0, 1 and a few k tiles beside
 # long ones, remainders of a k tile, one and several column tiles, tokens of several slots, dropped pairs; and those that read them transposed
 DY_ROWS = [
@@ -77,6 +86,12 @@ DY_TRANSPOSED = [
 F32_LAST_ROUND = [
     (592, 864, 552, 2, 2, {}), (634, 544, 528, 4, 3, dict(cf=0.9)), (808, 640, 552, 3, 2, dict(bias=[1.0, 0.0, 0.0])), (2176, 496, 576, 5, 1, {}),
     (649, 728, 648, 8, 2, dict(bias=[2.0, 1.0] + [0.0] * 6)), (933, 568, 528, 4, 2, dict(bias=[0.0, 0.0, 0.0, -60.0])),
+]
+
+# bf16 experts on both sides of the widths whose rows of act, dh1, dh3 and ga start on whole lines; ga in row order longer than transposed
+ROW_PITCH = [
+    (70, 72, 128, 2, 1, {}), (70, 72, 136, 2, 1, {}), (300, 264, 136, 4, 2, dict(cf=0.8)), (2300, 1032, 136, 2, 1, {}), (5000, 264, 136, 1, 1, {}),
+    (40, 64, 65536, 2, 1, {}), (40, 64, 65544, 2, 1, {}), (600, 64, 65536, 1, 1, {}), (600, 72, 65544, 1, 1, {}),
 ]
 
 # few tokens' routing with the normalisation, two pieces of wide rows requested ahead: (T, d, E, k, dtype).  Rows that end inside the

@@ -10,7 +10,7 @@ from paper_2403_07816_amd import synth
 
 from conftest import assert_close
 from helpers import TOL, as_passed, run_block_and_check, run_layer_and_check, to_dev, to_np, experts_np, check_route
-from path_cases import (DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_AHEAD, ROUTE_MANY,
+from path_cases import (DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_AHEAD, ROUTE_MANY, ROW_PITCH, TILED_FORWARD,
                         TRANSPOSED_ROWS, WHOLE_TILE_CASES, whole_tile_case)
 
 pytestmark = pytest.mark.gpu
@@ -63,6 +63,11 @@ def test_fp32_up_projection_with_three_stages(T, d, f, E, k):
 @pytest.mark.parametrize("T,d,f,E,k,kw", JOINT_FORWARD)
 def test_fp32_small_layers_forward_in_one_launch(T, d, f, E, k, kw):
     run_layer_and_check(T, d, f, E, k, F32, **kw)
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", [case for case, _ in TILED_FORWARD])
+def test_fp32_forward_of_narrow_rows_in_two_launches(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, F32, backward=False, **kw)
 
 
 @pytest.mark.parametrize("T,d,f,E,k,kw", F32_LAST_ROUND)
@@ -597,6 +602,33 @@ def test_bf16_an_infinity_in_the_last_row_of_dY_stays_in_its_column(d):
     assert torch.equal(got[:, others], finite[:, others])
     act = torch.nn.functional.silu(h1[-1].float()) * h3[-1].float()
     assert torch.equal(got[:, 17], torch.where(act > 0, torch.inf, -torch.inf))
+
+
+def test_bf16_weight_gradients_from_token_rows_of_dY_past_2_gib():
+    """Byte offsets of dY's rows from 2^31 on: as the same rows give in batches that stay below, fp32 sums of 500 thousand terms of random
+    signs in two orders.  One expert, whose gate is 1."""
+    T, d, f = 500_000, 4104, 72
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x, dY = (torch.randn((T, d), generator=g, device="cuda", dtype=BF16) for _ in range(2))
+    W1, W3 = (torch.randn((1, d, f), generator=g, device="cuda", dtype=BF16) * d ** -0.5 for _ in range(2))
+    W2, Wr = torch.randn((1, f, d), generator=g, device="cuda", dtype=BF16) * f ** -0.5, torch.zeros((d, 1), device="cuda")
+
+    def step(rows):
+        r = B.btx_moe_route(x[rows], Wr, None, None, 1, B.BTX_ROUTE_SWITCH_TOP1)
+        _, h1, h3 = B.btx_moe_ff_forward(x[rows], W1, W3, W2, r)
+        b = B.btx_moe_ff_backward(dY[rows], x[rows], Wr, W1, W3, W2, r, h1, h3, B.BTX_ROUTE_SWITCH_TOP1, dW_dtype=F32)
+        return [t[0].double() for t in (b.dW1, b.dW3, b.dW2)]
+
+    whole, parts = step(slice(0, T)), [0.0] * 3
+    for at in range(0, T, T // 4):
+        parts = [a + b for a, b in zip(parts, step(slice(at, at + T // 4)))]
+    for got, want in zip(whole, parts):
+        assert float((got - want).norm() / want.norm()) < TOL[F32] / 4
+
+
+@pytest.mark.parametrize("T,d,f,E,k,kw", ROW_PITCH)
+def test_bf16_rows_of_experts_that_start_on_whole_lines(T, d, f, E, k, kw):
+    run_layer_and_check(T, d, f, E, k, BF16, unit_rms=True, poison=True, **kw)
 
 
 @pytest.mark.parametrize("T,d,f,E,k,kw", TRANSPOSED_ROWS)

@@ -8,8 +8,8 @@ import pytest
 from paper_2403_07816_amd import binding as B
 
 from launches import P, adamw_call, backward_call, forward_call, host_seconds, launches, route_call
-from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_AHEAD, ROUTE_MANY,
-                        TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
+from path_cases import (ANY, BWD_ACT, BWD_DX, DOWN, DY_ROWS, DY_TRANSPOSED, F32_LAST_ROUND, FEW_K_TILES, HALF, JOINT_FORWARD, LAST_ROUND_CUT, ROUTE_AHEAD, ROUTE_MANY, ROW_PITCH,
+                        TILED_FORWARD, TRANSPOSED_ROWS, UP, WHOLE, WHOLE_TILE_CASES, whole_tile_case)
 
 MAX_THREADS = (1 << 32) - 1     # of one launch and direction of the grid
 
@@ -75,6 +75,15 @@ def test_bf16_workspaces_hold_the_matrices_that_are_transposed(record, T, d, f, 
     assert least <= size < least + d * pitch            # half of a matrix more at most
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [case[:5] for case in ROW_PITCH])
+def test_bf16_workspaces_hold_rows_that_start_on_whole_lines(record, T, d, f, E, k):
+    """From 136 to 65536 columns; ga has room for either order, transposed rows of an expert starting at multiples of 64."""
+    (forward, _), (backward, _) = record(*((f"btx_moe_ff_{which}_workspace_bytes", [T, d, f, E, k, B.BTX_BF16]) for which in ("forward", "backward")))
+    R, columns = T * k, math.ceil(f / 64) * 64 if 128 < f <= 65536 else f
+    ga = max(R * columns, (math.ceil(R / 64) * 64 + 64 * E) * f)
+    assert forward >= 2 * R * (columns + d) and backward >= 2 * (2 * R * columns + ga + 2 * R * d)
+
+
 @pytest.mark.parametrize("dW_dtype", [B.BTX_F32, B.BTX_BF16])
 def test_strips_of_weight_gradients_are_streamed_from_half_lines_on(record, dW_dtype):
     """The strips' stores go past the caches where every row starts on 64 bytes: not for a stack that starts on any other 16-byte
@@ -117,7 +126,7 @@ def test_shapes_of_transposed_rows_take_that_path(record, case):
 
 
 @pytest.mark.parametrize("case,rows", [(c, True) for c in DY_ROWS] + [(c, False) for c in DY_TRANSPOSED] +
-                         [((16384, 4096, 4096, 4, 2), True), ((16384, 4096, 4104, 4, 2), False), ((1 << 19, 4104, 1024, 4, 1), False),
+                         [((16384, 4096, 4096, 4, 2), True), ((16384, 4096, 4104, 4, 2), False), ((1 << 19, 4104, 1024, 4, 1), False), ((500_000, 4104, 72, 1, 1), True),
                           ((16384, 4096, 1376, 1, 1), True), ((16384, 4088, 1376, 1, 1), False), ((16384, 256, 4096, 16, 2), True), ((16384, 248, 4096, 17, 2), False),
                           ((16384, 520, 2768, 8, 2), True), ((16384, 520, 2776, 8, 2), False), ((16384, 64, 1376, 64, 8), False)])
 def test_dW2_of_tiles_reads_token_rows_of_dY(record, case, rows):
@@ -215,6 +224,16 @@ def test_small_fp32_layers_forward_in_one_launch(record, T, d, f, E, k, save):
 def test_limits_of_small_fp32_layers(record, T, d, f, E, k, joint):
     (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32))
     assert rc == 0 and found[0].kernel.startswith("f32_ff_kernel" if joint else "f32_gemm_kernel<0")
+
+
+@pytest.mark.parametrize("case,cut", TILED_FORWARD)
+def test_fp32_forward_of_narrow_rows_takes_two_launches(record, case, cut):
+    T, d, f, E, k, _ = case
+    (rc, found), = record(forward_call(T, d, f, E, k, B.BTX_F32, save=False))
+    up, down, *finish, combine = [launch.kernel for launch in found]
+    assert rc == 0 and up.startswith("f32_gemm_kernel<0") and down.startswith("f32_gemm_kernel<1")
+    # the slices' sums, which the combine adds for up to 8 slots
+    assert finish == (["f32_slices_finish_kernel"] if cut and k > 8 else []) and combine.endswith("true>") == (cut and k <= 8)
 
 
 @pytest.mark.parametrize("T,d,f,E,k,joint", [
