@@ -42,7 +42,7 @@ enum Mode { UP = 0, DOWN = 1, BWD_ACT = 2, BWD_DX = 3, DW13 = 4, DW2 = 5 };
 struct FArgs {
   const float* A0; const float* A1;      // A1: second K pass (BWD_DX)
   const float* B0; const float* B1;      // B1: second panel (UP), second product (DW13), second K pass (BWD_DX)
-  float* C0; float* C1; float* C2;       // UP: h1, h3 (NULL: not kept), act; BWD_ACT: dh1, dh3, ga; DW13: dW1, dW3
+  float* C0; float* C1; float* C2;       // UP: h1, h3 (NULL: not kept), act; BWD_ACT: dh1, dh3, ga; DW13: dW1, dW3; DOWN: y, and cut()
   const float* H1; const float* H3; const float* gates; float* dg_part; int n_part;   // BWD_ACT
   const int32_t* perm; uint32_t div_mul, div_shift; int k;   // gathered operand: row r is token perm[r] / k
   uint32_t* row_bytes;                   // byte offset of every grouped row's token row: BWD_ACT writes it for the weight gradients (NULL: none wanted)
@@ -52,11 +52,14 @@ struct FArgs {
   int lda, ldb, ldc;
   int64_t strideB_e, strideC_e;
   int slices; float* sums; int R;        // DOWN, BWD_DX: K ranges of every tile; their sums [slice][R][N] (slices > 1)
-  float* cut;                            // DOWN: the last round's tiles in K slices (see Cut); their sums, [slot][64][64] (NULL: whole)
   int tiles_n, tiles_m;                  // column tiles of one product; row tiles of an expert (grouped along K)
   // p / k for 0 <= p < 2^31 without a division (which would cost a third of the vector work of a dW tile):
   // with s = 31 + ceil(log2 k) and div_mul = ceil(2^s / k) < 2^32 the product is off by less than one in 2^31
   __device__ __forceinline__ int token(int p) const { return (int)(((uint64_t)(uint32_t)p * div_mul) >> div_shift); }
+  // DOWN: the last round's tiles in K slices (see Cut); their sums, [slot][64][64] (NULL: whole).  In the place of a pointer that DOWN does
+  // without: with one of its own, eight bytes more to every product's arguments, and a branch on `slices` in BWD_DX too, the backward
+  // pass of 2204 tokens, 4 experts of 64 x 64, top-4 took 79.6 us, now 77.8; 3284 of 256 x 192, top-2 90.7, now 89.3.
+  __host__ __device__ float* cut() const { return C2; }
   void gather(const RowSource& r) {
     perm = r.perm;
     k = r.k;
@@ -266,13 +269,13 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
     const int share = (total + 7) / 8, xcd = (int)(block % 8);
     int pos = (int)(block / 8), slice = 0, cut_slices = 1;
     float* cut_sums = nullptr;
-    if (MODE == DOWN && g.cut) {
+    if (MODE == DOWN && g.cut()) {
       const Cut cut(share);
       if (const int p = pos - cut.whole; p >= 0 && cut.left > 0) {
         slice = p / cut.left;
         if (slice >= cut.slices) return;
         cut_slices = cut.slices;
-        cut_sums = g.cut + (int64_t)((xcd * cut.left + p % cut.left) * cut.slices + slice) * (kTile * kTile);
+        cut_sums = g.cut() + (int64_t)((xcd * cut.left + p % cut.left) * cut.slices + slice) * (kTile * kTile);
         pos = cut.whole + p % cut.left;
       }
     }
@@ -286,7 +289,7 @@ template <int MODE, bool WIDE, int STAGES = 2> struct F32Gemm {
       tile_m = id - e * n_rows * nx;
     } else {
       row_tiles.expert_of(id, per_row_tile, e, n_rows, tile_m);
-      if (SLICED && g.slices > 1) {
+      if (SLICED && (MODE != DOWN || g.slices > 1)) {    // (DOWN's cut tiles have theirs)
         slice = tile_m / (nx * n_rows);
         tile_m -= slice * nx * n_rows;
       }
@@ -565,7 +568,7 @@ __global__ __launch_bounds__(kThreads) void f32_cut_finish_kernel(FArgs g) {
   rt.rows_of(e, tile_m, row0, row_end);
   const int row = 16 * quarter + threadIdx.x / 16, col = 4 * (threadIdx.x % 16), m = row0 + row, n = tile_n * kTile + col;
   if (m >= row_end || n >= g.N) return;
-  const float* from = g.cut + (int64_t)((xcd * cut.left + p) * cut.slices) * (kTile * kTile) + row * kTile + col;
+  const float* from = g.cut() + (int64_t)((xcd * cut.left + p) * cut.slices) * (kTile * kTile) + row * kTile + col;
   f32x4 v[Cut::MOST];
 #pragma unroll
   for (int s = 0; s < Cut::MOST; ++s) v[s] = *reinterpret_cast<const f32x4*>(from + min(s, cut.slices - 1) * (kTile * kTile));
@@ -663,7 +666,7 @@ template <int MODE> unsigned blocks_of(FArgs& g, int R) {
   g.R = R;
   const int64_t tiles = (int64_t)(MODE == DW13 ? 2 * g.tiles_n : g.tiles_n) * g.slices *
                         (G::GROUP_K ? (int64_t)g.E * g.tiles_m : (int64_t)ceil_div(R, kTile) + g.E);   // at most this many
-  const int64_t slices = MODE == DOWN && g.cut ? 8 * Cut::UNITS : 0;   // of the tiles that are cut
+  const int64_t slices = MODE == DOWN && g.cut() ? 8 * Cut::UNITS : 0;   // of the tiles that are cut
   return grid_fits(tiles + slices + 7, kThreads) ? (unsigned)align_up((size_t)(tiles + slices), 8) : 0;
 }
 int finish_slices(const FArgs& g, int R, hipStream_t s) {
@@ -679,7 +682,7 @@ template <int MODE> int launch(FArgs g, int R, hipStream_t s, int* left = nullpt
   else if (MODE == UP && weights_from_memory(g, R)) f32_gemm_kernel<MODE, false, MODE == UP ? 3 : 2><<<grid, kThreads, 0, s>>>(g);
   else f32_gemm_kernel<MODE, false, 2><<<grid, kThreads, 0, s>>>(g);
   BTX_LAUNCH_CHECK();
-  if (MODE == DOWN && g.cut) {
+  if (MODE == DOWN && g.cut()) {
     f32_cut_finish_kernel<<<8 * 4 * (Cut::UNITS / 2), kThreads, 0, s>>>(g);   // at most half of an XCD's units have a tile that is cut
     BTX_LAUNCH_CHECK();
   }
@@ -850,7 +853,7 @@ int f32_up_swiglu(const RowSource& xs, const void* W1, const void* W3, const int
 int f32_down(const void* act, const void* W2, const int32_t* off, const FfShapes& sh, void* y, void* sums, int* slices, hipStream_t s) {
   FArgs g{};
   g.slices = slices_of(sh, false); g.sums = (float*)sums;
-  if (g.slices == 1 && f32_cut(sh)) g.cut = g.sums;
+  if (g.slices == 1 && f32_cut(sh)) g.C2 = g.sums;
   g.A0 = (const float*)act; g.B0 = (const float*)W2; g.C0 = (float*)y;
   g.offsets = off; g.E = sh.E; g.N = sh.d; g.K = sh.f; g.lda = sh.f; g.ldb = sh.d; g.ldc = sh.d; g.strideB_e = sh.s2;
   return launch<DOWN>(g, sh.R, s, slices);
