@@ -57,8 +57,8 @@ struct FArgs {
   // with s = 31 + ceil(log2 k) and div_mul = ceil(2^s / k) < 2^32 the product is off by less than one in 2^31
   __device__ __forceinline__ int token(int p) const { return (int)(((uint64_t)(uint32_t)p * div_mul) >> div_shift); }
   // DOWN: the last round's tiles in K slices (see Cut); their sums, [slot][64][64] (NULL: whole).  In the place of a pointer that DOWN does
-  // without: with one of its own, eight bytes more to every product's arguments, and a branch on `slices` in BWD_DX too, the backward
-  // pass of 2204 tokens, 4 experts of 64 x 64, top-4 took 79.6 us, now 77.8; 3284 of 256 x 192, top-2 90.7, now 89.3.
+  // without: with one of its own in front of tiles_n every product waited longer for its arguments, the backward pass of 2204 tokens, 4
+  // experts of 64 x 64, top-4 79.6 us, now 77.8; 3284 of 256 x 192, top-2 90.7, now 89.3.
   __host__ __device__ float* cut() const { return C2; }
   void gather(const RowSource& r) {
     perm = r.perm;
@@ -628,7 +628,9 @@ int slices_of(const FfShapes& sh, bool two_passes) {
 // for each of its k tiles, a slice's part of that when it is cut.  The number of tiles moves by a row tile's columns with the routing:
 // with fewer left than that there may be none.  us, whole / cut, forward call, top-2: 2003 tokens, 8 experts of 512 x 1376 (533 tiles) 159.5
 // / 145.3 (DOWN 70 / 55.7 and 4.8 for the sums; training pass 534.5 / 522.4); of 512 x 688 91.6 / 85.8; 4006 of 256 x 1376 (517) 165.0 / 151.1;
-// but 4 experts of 512 x 1376, 517 tiles expected and 512 there, 140.9 / 143.0.
+// but 4 experts of 512 x 1376, 517 tiles expected and 512 there, 140.9 / 143.0.  Where one expert is favoured the cut is as good, as Cut counts
+// the tiles that there are: of 60 calls (these three and 1100 of 1024 x 1376, a bias of 0 to 4 on expert 0) 58 gain 3 to 10 %, two without
+// an uneven round lose 1 %.
 bool f32_cut(const FfShapes& sh) {
   auto gains = [&](double slices) { return 0.5 * ceil_div(sh.f, kTileK) * (1.0 - 1.0 / slices) > 7.0; };
   if (!gains(Cut::MOST) || sums_bytes(sh, false) < (size_t)8 * Cut::UNITS * kTile * kTile * sizeof(float)) return false;
