@@ -440,8 +440,8 @@ int launch_route_small(const RouteArgs& a, hipStream_t s) {
     // Two pieces ahead where that was measured to gain: us, the whole routing, none / two: bf16, 4096 columns, 16 tokens, 4 experts 10.7 / 10.0,
     // 8 12.9 / 12.2, 16 20.5 / 19.8; 512 tokens, 8 experts 19.1 / 18.5, 16 34.1 / 32.3; fp32, 16 tokens, 4 experts 9.8 / 9.3, 512, 8 18.9 / 18.7.  Up
     // to 2048 columns a thread has no second piece; the fourth and fifth wait as long as they did, beside more registers; of up to 4 bf16 experts
-    // other workgroups cover the wait of more than 256 tokens; a second set of experts that is not whole loses (12, 256 tokens of 3072: bf16 -13 %,
-    // fp32 -14 %).  Of 810 calls of 1024 to 16384 columns, 2 to 32 experts, 16 to 512 tokens it takes 204, which gain 3.9 % on average, four of them
+    // other workgroups cover the wait of more than 256 tokens; a second set of experts that is not whole loses (12, 256 tokens of 3072: bf16 19.6 / 22.7,
+    // fp32 18.3 / 21.3).  Of 810 calls of 1024 to 16384 columns, 2 to 32 experts, 16 to 512 tokens it takes 204, which gain 3.9 % on average, four of them
     // lose 1.2 to 1.8 %.
     const bool ahead = NORM && a.d > 2048 && (sizeof(XT) == 4 ? a.d <= 4096 && a.E <= 8
                                                               : a.E <= 4 ? a.d <= 6144 && a.T <= 256 : a.d <= 8192 && (a.E <= 8 || a.E == 16));
